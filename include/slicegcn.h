@@ -202,8 +202,9 @@ int slicegcn_slice_feature(const float *X, int64_t n, int64_t ldx, int32_t start
  * call forms dinv[v] * sum of X'[u, :] instead: the same Y up to rounding, without reading the 4-byte value
  * of every stored entry (1/c_vu factors as dinv[v] dinv[u]).
  * X, Y: n_nodes x width with leading dimensions ldx, ldy.  X and Y must not overlap.
- * The fast path needs X 16-byte aligned with ldx a multiple of 4 and ldx >= width rounded up
- * to 4 (padding columns are read but never used); other layouts take a scalar path.  Only
+ * Any base alignment and leading dimension is served by 16-byte accesses; rows on 128-byte boundaries touch the
+ * fewest cache lines.  Where X is 16-byte aligned with ldx a multiple of 4, the columns up to width rounded up to 4
+ * are read (never used); otherwise nothing past column width of a row is read.  Only
  * columns [0, width) of Y are written.  A symmetrised graph serves transpose != 0 with the
  * same arrays; otherwise the handle holds the transposed pattern as well.
  * ws: rows cut into several work items (long rows, see the schedule notes of the library) keep
@@ -246,7 +247,6 @@ int slicegcn_spmm_slice_static(const slicegcn_graph *g, int op, const float *X, 
  * Hin: n x w_in (ldi); Hout: n x w_out (ldo, any value >= w_out: the last layer can store
  * straight into its column block of the concatenated representation).  saved->Z is always
  * written (it is the staging buffer of the aggregation); saved->mask is written for ACT_RELU.
- * Hin must satisfy the fast-path layout of slicegcn_spmm_slice or the scalar path is taken.
  * With SLICEGCN_LAYER_Z_VALID the caller vouches that saved->Z still holds A^ Hin from an earlier
  * call with the same graph and Hin (the first layer over raw, constant features is the same in
  * every epoch); the aggregation is then skipped.  The paper's own implementation recomputes it.

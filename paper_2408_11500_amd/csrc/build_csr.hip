@@ -107,22 +107,22 @@ __global__ void swap_keys_kernel(const uint64_t *__restrict__ in, int64_t nnz, u
 }
 
 // ---- schedule ---------------------------------------------------------------------------
-// Column class c holds the columns [first[c], first[c+1]); the boundaries are the 1/n_classes
+// Column class c holds the columns [first[c], first[c+1]); the boundaries are eighth-
 // quantiles of the stored entries per column, so that the classes carry equal numbers of entries
 // whatever the vertex numbering (with hubs numbered first, equal column ranges would put almost
 // half of the entries into the first class).
 struct ClassBounds {
-    int32_t first[MAX_CLASSES + 1];
+    int32_t first[N_CLASSES + 1];
 };
 
 // colptr: row pointer of the transposed pattern (entries per column, scanned)
-__global__ void class_bounds_kernel(const int32_t *__restrict__ colptr, int64_t n, int n_classes, int32_t *__restrict__ first)
+__global__ void class_bounds_kernel(const int32_t *__restrict__ colptr, int64_t n, int32_t *__restrict__ first)
 {
     const int c = threadIdx.x;
-    if (c > MAX_CLASSES) return;
+    if (c > N_CLASSES) return;
     if (c == 0) { first[0] = 0; return; }
-    if (c >= n_classes) { first[c] = (int32_t)n; return; }
-    const int64_t target = (int64_t)colptr[n] * c / n_classes;
+    if (c == N_CLASSES) { first[c] = (int32_t)n; return; }
+    const int64_t target = (int64_t)colptr[n] * c / N_CLASSES;
     int64_t lo = 0, hi = n; // smallest column j with colptr[j] >= target
     while (lo < hi) {
         const int64_t mid = lo + ((hi - lo) >> 1);
@@ -132,19 +132,19 @@ __global__ void class_bounds_kernel(const int32_t *__restrict__ colptr, int64_t 
 }
 
 // Item tables: 2c = wavefront items of class c (pieces of rows cut by column class), 2c + 1 =
-// lane-group items of class c, 2 * n_classes = wavefront items of rows kept whole, 2 * n_classes + 1
+// lane-group items of class c, 2 * N_CLASSES = wavefront items of rows kept whole, 2 * N_CLASSES + 1
 // = lane-group items that are whole rows.  counts layout: cnt[table * (n+1) + row].
-constexpr int MAX_TABLES = 2 * MAX_CLASSES + 2;
+constexpr int MAX_TABLES = 2 * N_CLASSES + 2;
 struct RowCut {
-    int32_t lo[MAX_CLASSES + 1];
+    int32_t lo[N_CLASSES + 1];
 };
 
 // Per long row: the entries of column class c are [lower_bound(first[c]), lower_bound(first[c+1])).
-__device__ inline RowCut cut_row(const int32_t *__restrict__ colidx, int32_t beg, int32_t end, int n_classes, const ClassBounds &cb)
+__device__ inline RowCut cut_row(const int32_t *__restrict__ colidx, int32_t beg, int32_t end, const ClassBounds &cb)
 {
     RowCut rc;
     rc.lo[0] = beg;
-    for (int c = 1; c < n_classes; ++c) {
+    for (int c = 1; c < N_CLASSES; ++c) {
         const int32_t target = cb.first[c];
         int32_t lo = rc.lo[c - 1], hi = end;
         while (lo < hi) {
@@ -153,7 +153,7 @@ __device__ inline RowCut cut_row(const int32_t *__restrict__ colidx, int32_t beg
         }
         rc.lo[c] = lo;
     }
-    for (int c = n_classes; c <= MAX_CLASSES; ++c) rc.lo[c] = end;
+    rc.lo[N_CLASSES] = end;
     return rc;
 }
 
@@ -162,23 +162,23 @@ __device__ inline int pieces_of(int32_t len) { return (len + SEG_NNZ - 1) / SEG_
 // The items of one row, in (class, piece) order.  F is called as f(table, beg, end).
 template <class F>
 __device__ inline int for_each_item(const int32_t *__restrict__ colidx, int32_t beg, int32_t end,
-                                    int n_classes, const ClassBounds &cb, int32_t part_row, int32_t item_max, F f)
+                                    const ClassBounds &cb, int32_t part_row, int32_t item_max, F f)
 {
     const int32_t d = end - beg;
     int total = 0;
     if (d <= TINY_ROW) return 0;
     if (d <= item_max) {
-        f(2 * n_classes + 1, beg, end);
+        f(2 * N_CLASSES + 1, beg, end);
         return 1;
     }
-    if (n_classes == 1 || d <= part_row) {
+    if (d <= part_row) {
         const int s = pieces_of(d);
         const int32_t piece = (d + s - 1) / s; // equal cuts, the last one takes the remainder
-        for (int j = 0; j < s; ++j) f(2 * n_classes, beg + j * piece, min(end, beg + (j + 1) * piece));
+        for (int j = 0; j < s; ++j) f(2 * N_CLASSES, beg + j * piece, min(end, beg + (j + 1) * piece));
         return s;
     }
-    const RowCut rc = cut_row(colidx, beg, end, n_classes, cb);
-    for (int c = 0; c < n_classes; ++c) {
+    const RowCut rc = cut_row(colidx, beg, end, cb);
+    for (int c = 0; c < N_CLASSES; ++c) {
         const int32_t b = rc.lo[c], e = rc.lo[c + 1], len = e - b;
         if (len <= 0) continue;
         if (len <= item_max) {
@@ -198,7 +198,7 @@ __device__ inline int for_each_item(const int32_t *__restrict__ colidx, int32_t 
 // per-row tables are indexed by position, so the scans below lay the items out in schedule order.
 __global__ void sched_count_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx, int64_t n,
                                    const int32_t *__restrict__ order,
-                                   int n_classes, const ClassBounds cb, int32_t part_row, int32_t item_max, int32_t *__restrict__ cnt,
+                                   const ClassBounds cb, int32_t part_row, int32_t item_max, int32_t *__restrict__ cnt,
                                    int32_t *__restrict__ c_slot, int32_t *__restrict__ c_fix)
 {
     const int64_t p = (int64_t)blockIdx.x * TPB + threadIdx.x;
@@ -209,17 +209,17 @@ __global__ void sched_count_kernel(const int32_t *__restrict__ rowptr, const int
     int total = 0;
     if (p < n) {
         const int64_t r = order ? order[p] : p;
-        total = for_each_item(colidx, rowptr[r], rowptr[r + 1], n_classes, cb, part_row, item_max,
+        total = for_each_item(colidx, rowptr[r], rowptr[r + 1], cb, part_row, item_max,
                               [&](int t, int32_t, int32_t) { per[t] += 1; });
     }
-    for (int t = 0; t < 2 * n_classes + 2; ++t) cnt[t * stride + p] = per[t];
+    for (int t = 0; t < 2 * N_CLASSES + 2; ++t) cnt[t * stride + p] = per[t];
     c_slot[p] = total > 1 ? total : 0;
     c_fix[p] = total > 1 ? 1 : 0;
 }
 
 __global__ void sched_fill_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx, int64_t n,
                                   const int32_t *__restrict__ order,
-                                  int n_classes, const ClassBounds cb, int32_t part_row, int32_t item_max, const int32_t *__restrict__ off,
+                                  const ClassBounds cb, int32_t part_row, int32_t item_max, const int32_t *__restrict__ off,
                                   const int32_t *__restrict__ o_slot, const int32_t *__restrict__ o_fix,
                                   Segment *__restrict__ items, FixRow *__restrict__ fix)
 {
@@ -230,11 +230,11 @@ __global__ void sched_fill_kernel(const int32_t *__restrict__ rowptr, const int3
     const int32_t beg = rowptr[r], end = rowptr[r + 1];
     if (end - beg <= TINY_ROW) return;
     // first pass: how many items (decides whether they write the row or partial slots)
-    const int total = for_each_item(colidx, beg, end, n_classes, cb, part_row, item_max, [](int, int32_t, int32_t) {});
+    const int total = for_each_item(colidx, beg, end, cb, part_row, item_max, [](int, int32_t, int32_t) {});
     int32_t used[MAX_TABLES];
     for (int t = 0; t < MAX_TABLES; ++t) used[t] = 0;
     int slot = o_slot[p]; // slots are handed out in (class, piece) order
-    for_each_item(colidx, beg, end, n_classes, cb, part_row, item_max, [&](int t, int32_t b, int32_t e) {
+    for_each_item(colidx, beg, end, cb, part_row, item_max, [&](int t, int32_t b, int32_t e) {
         Segment sg;
         sg.row = (int32_t)r;
         sg.beg = b;
@@ -307,23 +307,21 @@ void free_csr(Csr &m, bool owns_pattern)
         (void)hipFree(m.colidx);
         (void)hipFree(m.vals);
     }
-    free_schedule(m.wide);
-    free_schedule(m.xcd);
+    free_schedule(m.sched);
     m = Csr();
 }
 
-int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, const int32_t *order, int n_classes, uint32_t flags,
+int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, const int32_t *order, uint32_t flags,
                    Schedule &out, hipStream_t stream)
 {
     out = Schedule();
-    out.n_classes = n_classes;
     // entries (8 bytes each) plus one 128-byte operand row per node against the 256 MB last-level cache
     const bool resident = nnz * 8 + n * 128 <= ((int64_t)256 << 20);
     int32_t item_max = resident ? ITEM_SHORT : ITEM_LONG;
     if (flags & SLICEGCN_SCHED_SHORT_ITEMS) item_max = ITEM_SHORT;
     if (flags & SLICEGCN_SCHED_LONG_ITEMS) item_max = ITEM_LONG;
     out.item_max = item_max;
-    const int n_tables = 2 * n_classes + 2;
+    const int n_tables = 2 * N_CLASSES + 2;
     const size_t stride = (size_t)(n + 1);
     const size_t n_cnt = (size_t)n_tables * stride;
     SG_REQUIRE(n_cnt <= (size_t)INT32_MAX, SLICEGCN_ERANGE, "build_norm_csr: schedule tables exceed int32 indexing");
@@ -333,12 +331,12 @@ int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, 
     if (int rc = aux.alloc((4 * stride + 16) * sizeof(int32_t))) return rc; // slot counts, fix counts, their scans, class bounds
     int32_t *c = cnt.as<int32_t>(), *o = off.as<int32_t>(), *x = aux.as<int32_t>();
     ClassBounds cb;
-    class_bounds_kernel<<<1, 64, 0, stream>>>(colptr, n, n_classes, x + 4 * stride);
+    class_bounds_kernel<<<1, 64, 0, stream>>>(colptr, n, x + 4 * stride);
     SG_LAUNCH_CHECK();
     SG_HIP(hipMemcpyAsync(cb.first, x + 4 * stride, sizeof(cb.first), hipMemcpyDeviceToHost, stream));
     SG_HIP(hipStreamSynchronize(stream));
     const int32_t part_row = PART_ROW;
-    sched_count_kernel<<<blocks_for(n + 1), TPB, 0, stream>>>(m.rowptr, m.colidx, n, order, n_classes, cb, part_row, item_max, c, x, x + stride);
+    sched_count_kernel<<<blocks_for(n + 1), TPB, 0, stream>>>(m.rowptr, m.colidx, n, order, cb, part_row, item_max, c, x, x + stride);
     SG_LAUNCH_CHECK();
     if (int rc = scan_i32(c, o, (int64_t)n_cnt, stream)) return rc;
     if (int rc = scan_i32(x, x + 2 * stride, n + 1, stream)) return rc;
@@ -353,23 +351,23 @@ int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, 
     SG_HIP(hipMemcpy(&n_slots, x + 2 * stride + n, sizeof(int32_t), hipMemcpyDeviceToHost));
     SG_HIP(hipMemcpy(&n_fix, x + 3 * stride + n, sizeof(int32_t), hipMemcpyDeviceToHost));
     starts[n_tables] = last_off + last_cnt;
-    for (int cl = 0; cl < n_classes; ++cl) {
+    for (int cl = 0; cl < N_CLASSES; ++cl) {
         out.big_off[cl] = starts[2 * cl];
         out.big_cnt[cl] = starts[2 * cl + 1] - starts[2 * cl];
         out.small_off[cl] = starts[2 * cl + 1];
         out.small_cnt[cl] = starts[2 * cl + 2] - starts[2 * cl + 1];
     }
-    out.wbig_off = starts[2 * n_classes];
-    out.wbig_cnt = starts[2 * n_classes + 1] - starts[2 * n_classes];
-    out.wsmall_off = starts[2 * n_classes + 1];
-    out.wsmall_cnt = starts[2 * n_classes + 2] - starts[2 * n_classes + 1];
+    out.wbig_off = starts[2 * N_CLASSES];
+    out.wbig_cnt = starts[2 * N_CLASSES + 1] - starts[2 * N_CLASSES];
+    out.wsmall_off = starts[2 * N_CLASSES + 1];
+    out.wsmall_cnt = starts[2 * N_CLASSES + 2] - starts[2 * N_CLASSES + 1];
     out.n_items = starts[n_tables];
     out.n_slots = n_slots;
     out.n_fix = n_fix;
     DevBuf items, fix;
     if (int rc = items.alloc((size_t)out.n_items * sizeof(Segment))) return rc;
     if (int rc = fix.alloc((size_t)out.n_fix * sizeof(FixRow))) return rc;
-    sched_fill_kernel<<<blocks_for(n), TPB, 0, stream>>>(m.rowptr, m.colidx, n, order, n_classes, cb, part_row, item_max, o, x + 2 * stride,
+    sched_fill_kernel<<<blocks_for(n), TPB, 0, stream>>>(m.rowptr, m.colidx, n, order, cb, part_row, item_max, o, x + 2 * stride,
                                                          x + 3 * stride, items.as<Segment>(), fix.as<FixRow>());
     SG_LAUNCH_CHECK();
     SG_HIP(hipStreamSynchronize(stream));
@@ -377,21 +375,14 @@ int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, 
     out.fix = fix.release<FixRow>();
     static const bool verbose = getenv("SLICEGCN_VERBOSE") != nullptr;
     if (verbose) {
-        fprintf(stderr, "[slicegcn] schedule with %d class(es): whole rows %d wavefront + %d lane-group items, %lld rows with "
-                        "several items, %lld partial-sum slots\n", n_classes, out.wbig_cnt, out.wsmall_cnt,
+        fprintf(stderr, "[slicegcn] schedule: whole rows %d wavefront + %d lane-group items, %lld rows with "
+                        "several items, %lld partial-sum slots\n", out.wbig_cnt, out.wsmall_cnt,
                 (long long)out.n_fix, (long long)out.n_slots);
-        for (int cl = 0; cl < n_classes && n_classes > 1; ++cl)
+        for (int cl = 0; cl < N_CLASSES; ++cl)
             fprintf(stderr, "[slicegcn]   class %d: columns [%d, %d), %d wavefront + %d lane-group pieces\n", cl,
                     cb.first[cl], cb.first[cl + 1], out.big_cnt[cl], out.small_cnt[cl]);
     }
     return SLICEGCN_OK;
-}
-
-// colptr: row pointer of the transposed pattern
-static int build_schedules(int64_t n, int64_t nnz, Csr &m, const int32_t *colptr, const int32_t *order, uint32_t flags, hipStream_t stream)
-{
-    if (int rc = build_schedule(n, nnz, m, colptr, order, 1, flags, m.wide, stream)) return rc;
-    return build_schedule(n, nnz, m, colptr, order, MAX_CLASSES, flags, m.xcd, stream);
 }
 
 } // namespace slicegcn
@@ -498,7 +489,7 @@ extern "C" int slicegcn_build_norm_csr(const int64_t *src, const int64_t *dst, i
         if (int rc = build_row_order(n_nodes, g->fwd.rowptr, g->fwd.colidx, (flags & SLICEGCN_REORDER_BFS) != 0, &g->order, stream)) return rc;
 
     if (sym) {
-        if (int rc = build_schedules(n_nodes, nnz, g->fwd, g->fwd.rowptr, g->order, flags, stream)) return rc;
+        if (int rc = build_schedule(n_nodes, nnz, g->fwd, g->fwd.rowptr, g->order, flags, g->fwd.sched, stream)) return rc;
         g->tr = g->fwd; // A^ is symmetric: the same arrays serve the transposed product
     } else {
         uint64_t *swapped = keys_b.as<uint64_t>();
@@ -518,8 +509,8 @@ extern "C" int slicegcn_build_norm_csr(const int64_t *src, const int64_t *dst, i
         SG_LAUNCH_CHECK();
         g->tr.rowptr = rowptr.release<int32_t>();
         if (int rc = pattern_from_keys(keys_c.as<uint64_t>(), nnz, n_nodes, g->dinv, g->tr, stream)) return rc;
-        if (int rc = build_schedules(n_nodes, nnz, g->fwd, g->tr.rowptr, g->order, flags, stream)) return rc;
-        if (int rc = build_schedules(n_nodes, nnz, g->tr, g->fwd.rowptr, g->order, flags, stream)) return rc;
+        if (int rc = build_schedule(n_nodes, nnz, g->fwd, g->tr.rowptr, g->order, flags, g->fwd.sched, stream)) return rc;
+        if (int rc = build_schedule(n_nodes, nnz, g->tr, g->fwd.rowptr, g->order, flags, g->tr.sched, stream)) return rc;
         SG_HIP(hipStreamSynchronize(stream));
     }
 

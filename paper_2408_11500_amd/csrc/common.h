@@ -43,15 +43,15 @@ __host__ __device__ inline bool aligned16(const void *p) { return (reinterpret_c
 //   d <= TINY_ROW            : handled whole, 64 consecutive rows per wavefront, in natural order;
 //   TINY_ROW < d <= item_max : one lane-group item (the whole row);
 //   d > item_max             : wavefront items of at most SEG_NNZ entries;
-//   d > PART_ROW (schedules with 8 classes only): the row is first cut by column class
+//   d > PART_ROW             : the row is first cut by column class
 //       (8 contiguous column ranges holding equal shares of the stored entries; a row's entries of
 //       one class are contiguous because columns ascend); a class piece of at most item_max
 //       entries is a lane-group item, a longer one is cut into wavefront items.
 // item_max is fixed per graph: ITEM_SHORT when the whole working set stays in the last-level cache
 // (the kernels are then bound by instruction issue, and shorter lane-group items win), ITEM_LONG when
 // the gathers go to memory (fewer, longer items keep more gathers in flight).
-// Pieces of class c are executed by workgroups whose index is c modulo n_classes; with 8 classes
-// and the round-robin placement of workgroups over the 8 XCDs, each XCD's L2 only ever sees its
+// Pieces of class c are executed by workgroups whose index is c modulo 8; with
+// the round-robin placement of workgroups over the 8 XCDs, each XCD's L2 only ever sees its
 // own class of columns of the gathered operand for the partitioned rows.  Whole-row items form
 // two lists of their own (wavefront and lane-group items, in row order) that are dealt to the
 // classes in fixed-size chunks, round-robin, and run behind the class's pieces.  A row with
@@ -62,9 +62,8 @@ constexpr int ITEM_SHORT = 32;
 constexpr int ITEM_LONG = 64;
 constexpr int PART_ROW = 256;
 constexpr int SEG_NNZ = 2048;
-constexpr int MAX_CLASSES = 8;
-constexpr int WIDE_SLOT_COLS = 256; // floats per slot, single-class schedule (256 columns per pass)
-constexpr int XCD_SLOT_COLS = 128;  // floats per slot, 8-class schedule (128 columns per pass)
+constexpr int N_CLASSES = 8;   // column classes, one per XCD
+constexpr int PASS_COLS = 128; // columns per pass of the aggregation (floats per partial-sum slot)
 
 struct Segment { // 16 bytes, read as one int4
     int32_t row;
@@ -81,12 +80,11 @@ struct FixRow { // a row whose items went to partial slots [slot_beg, slot_end)
 };
 
 struct Schedule {
-    int32_t n_classes = 0;
     int32_t item_max = ITEM_LONG; // longest lane-group item (whole row or class piece)
     Segment *items = nullptr; // per class its wavefront pieces, then its lane-group pieces; then the whole-row lists
     FixRow *fix = nullptr;
-    int32_t big_off[MAX_CLASSES] = {0}, big_cnt[MAX_CLASSES] = {0};     // wavefront pieces of class c
-    int32_t small_off[MAX_CLASSES] = {0}, small_cnt[MAX_CLASSES] = {0}; // lane-group pieces of class c
+    int32_t big_off[N_CLASSES] = {0}, big_cnt[N_CLASSES] = {0};     // wavefront pieces of class c
+    int32_t small_off[N_CLASSES] = {0}, small_cnt[N_CLASSES] = {0}; // lane-group pieces of class c
     int32_t wbig_off = 0, wbig_cnt = 0;     // wavefront items of rows kept whole
     int32_t wsmall_off = 0, wsmall_cnt = 0; // lane-group items that are whole rows
     int64_t n_items = 0;
@@ -98,8 +96,7 @@ struct Csr {
     int32_t *rowptr = nullptr;
     int32_t *colidx = nullptr;
     float *vals = nullptr;
-    Schedule wide; // one class: rows cut by length only
-    Schedule xcd;  // eight column classes
+    Schedule sched;
 };
 
 } // namespace slicegcn
@@ -143,7 +140,7 @@ struct ProfScope {
 };
 
 // build_csr.hip
-int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, const int32_t *order, int n_classes, uint32_t flags,
+int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, const int32_t *order, uint32_t flags,
                    Schedule &out, hipStream_t stream);
 
 // order.hip: order[p] = id of the row at position p (by degree, or breadth first); *out is a device array the caller frees

@@ -15,15 +15,19 @@
 //     cross-lane reads with eight gathers in flight per lane, and the groups' sums are combined
 //     with cross-lane shuffles;
 //   * a row with several items stores per-item partial sums that a fix-up kernel adds in item order.
-// Workgroup b serves class b mod n_classes.  With 8 classes this pins each column class of the
+// Workgroup b serves column class b mod 8, which pins each column class of the
 // gathered operand to one XCD's L2 (workgroups are placed round-robin over the XCDs), so the
 // eight L2s hold disjoint sets of hot rows instead of eight copies of the same set.  If the
 // placement were different the result would be the same, only slower.
 // No floating-point atomics anywhere: the summation order is a function of the graph only.
 //
-// Lanes map to columns: with vector width V (4 floats when the operand layout allows 16-byte
-// loads, else 1), lane `sub` of a group owns columns [V*sub, V*sub + V) of the current column
-// pass; wider operands take several passes.
+// Lanes map to columns: with vector width V (4 floats; 1 for operands of fewer than 4 columns), lane `sub`
+// of a group owns columns [V*sub, V*sub + V) of the current column pass; wider operands take several passes.
+// The 16-byte loads and stores need 4-byte alignment only (the hardware runs in unaligned mode), so rows may start
+// anywhere: a contiguous 25-wide matrix takes the same kernels as a padded one.  Where the last vector of a row
+// would reach past the row, its lane loads the row's last four columns instead and shifts its sums into place
+// before they are stored, so nothing outside the operand is read.  (One float per lane on the single-class
+// schedule, which such operands took before: 89 us per call for 1.6 M entries of 25 columns; 48 us here.)
 //
 // The partial sums of rows with several items live in a workspace the caller passes in (its size comes
 // from spmm_workspace_bytes), so a graph handle is read-only here and calls on different streams
@@ -51,7 +55,6 @@ struct SpmmArgs {
     int64_t ldx, ldy, ldadd;
     uint32_t ldx_bytes;   // S32 kernels: byte stride of X rows (n * ldx * 4 < 2^32, n and ldx * 4 < 2^24)
     int32_t n;
-    int32_t n_classes;
     int32_t item_max;     // longest lane-group item of the schedule (ITEM_SHORT or ITEM_LONG)
     int32_t ipw;          // wavefront items per wavefront (one-launch kernel: 4; otherwise 1); a workgroup takes 4 * ipw
     int32_t big_blocks;   // workgroups per class in the wavefront-item section
@@ -59,14 +62,27 @@ struct SpmmArgs {
     int32_t slot_cols;    // floats per partial-sum slot
     int32_t col0;         // first column of this pass
     int32_t col_end;      // one past the last column of this pass (<= width)
-    int32_t vec_store;    // Y (and Add) allow 16-byte accesses
-    int32_t big_off[MAX_CLASSES], big_cnt[MAX_CLASSES];     // wavefront pieces of class c
-    int32_t small_off[MAX_CLASSES], small_cnt[MAX_CLASSES]; // lane-group pieces of class c
+    int32_t load_max;     // ragged rows (RAG kernels): last column a 16-byte load may start at; 0: rows end on a whole vector
+    int32_t big_off[N_CLASSES], big_cnt[N_CLASSES];     // wavefront pieces of class c
+    int32_t small_off[N_CLASSES], small_cnt[N_CLASSES]; // lane-group pieces of class c
     int32_t wbig_off, wbig_cnt;     // wavefront items of rows kept whole (dealt to the classes four at a time)
     int32_t wsmall_off, wsmall_cnt; // lane-group whole rows (dealt one wavefront's share at a time)
 };
 
 template <int V> struct Acc;
+// 16-byte accesses at any 4-byte boundary
+typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline float4 load4(const float *p)
+{
+    const floatx4_u v = *reinterpret_cast<const floatx4_u *>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ inline void store4(float *p, const float4 &v)
+{
+    const floatx4_u o = {v.x, v.y, v.z, v.w};
+    *reinterpret_cast<floatx4_u *>(p) = o;
+}
+
 template <> struct Acc<4> {
     float4 v;
     __device__ Acc() : v(make_float4(0.f, 0.f, 0.f, 0.f)) {}
@@ -74,6 +90,12 @@ template <> struct Acc<4> {
     __device__ void plus(const float4 &x) { v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w; }
     __device__ void scale(float a) { v.x *= a; v.y *= a; v.z *= a; v.w *= a; }
     __device__ void add(const Acc &o) { v.x += o.v.x; v.y += o.v.y; v.z += o.v.z; v.w += o.v.w; }
+    __device__ void shift(int s) // drop the first s columns (what moves in from the end is never stored)
+    {
+        v.x = s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w;
+        v.y = s == 0 ? v.y : s == 1 ? v.z : v.w;
+        v.z = s == 0 ? v.z : v.w;
+    }
     __device__ float get(int i) const { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 };
 template <> struct Acc<1> {
@@ -83,6 +105,7 @@ template <> struct Acc<1> {
     __device__ void plus(float x) { v += x; }
     __device__ void scale(float a) { v *= a; }
     __device__ void add(const Acc &o) { v += o.v; }
+    __device__ void shift(int) {}
     __device__ float get(int) const { return v; }
 };
 
@@ -90,7 +113,7 @@ template <int V> struct Ld;
 template <> struct Ld<4> {
     using T = float4;
     static __device__ T zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-    static __device__ T load(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+    static __device__ T load(const float *p) { return load4(p); }
 };
 template <> struct Ld<1> {
     using T = float;
@@ -133,17 +156,25 @@ template <> __device__ inline Acc<1> shfl_xor_acc<1>(const Acc<1> &a, int mask)
     return r;
 }
 
+// Columns of the operand the lane that owns columns [col, col + V) loads (the lane's own, or the row's last four
+// where its own would reach past the row; lanes beyond the pass load what the first lane does and drop it).
+template <bool RAG> __device__ inline int load_col(const SpmmArgs &a, int col)
+{
+    const int c = col < a.col_end ? col : a.col0;
+    return RAG && c > a.load_max ? a.load_max : c;
+}
+
 // Store the V columns a lane owns (clipped to col_end), adding `add_row` when present.
 template <int V>
-__device__ inline void store_cols(const Acc<V> &acc, float *y_row, const float *add_row, int col, int col_end, bool vec_ok)
+__device__ inline void store_cols(const Acc<V> &acc, float *y_row, const float *add_row, int col, int col_end)
 {
-    if (V == 4 && vec_ok && col + 4 <= col_end) {
+    if (V == 4 && col + 4 <= col_end) {
         float4 o = make_float4(acc.get(0), acc.get(1), acc.get(2), acc.get(3));
         if (add_row) {
-            const float4 a = *reinterpret_cast<const float4 *>(add_row + col);
+            const float4 a = load4(add_row + col);
             o.x += a.x; o.y += a.y; o.z += a.z; o.w += a.w;
         }
-        *reinterpret_cast<float4 *>(y_row + col) = o;
+        store4(y_row + col, o);
     } else {
 #pragma unroll
         for (int i = 0; i < V; ++i)
@@ -201,16 +232,16 @@ __device__ inline void gather_chunk(Acc<V> &acc, const SpmmArgs &a, int c_l, flo
 }
 
 // Write an item's (or a row's) sum: to the output row, or to its partial-sum slot.
-template <int V>
+template <int V, bool RAG>
 __device__ inline void store_result(Acc<V> acc, const SpmmArgs &a, int row, int dst, int col)
 {
+    if (RAG) acc.shift(col - load_col<RAG>(a, col));
     if (dst >= 0) {
         if (a.dinv) acc.scale(a.dinv[row]); // factored form: the row's own factor (partial sums stay unscaled)
-        store_cols<V>(acc, a.Y + (int64_t)row * a.ldy, a.Add ? a.Add + (int64_t)row * a.ldadd : nullptr, col, a.col_end,
-                      a.vec_store != 0);
+        store_cols<V>(acc, a.Y + (int64_t)row * a.ldy, a.Add ? a.Add + (int64_t)row * a.ldadd : nullptr, col, a.col_end);
     } else {
         float *p = a.scratch + (int64_t)(-(dst + 1)) * a.slot_cols - a.col0; // slot row, pass-relative columns
-        store_cols<V>(acc, p, nullptr, col, a.col_end, true);
+        store_cols<V>(acc, p, nullptr, col, a.col_end);
     }
 }
 
@@ -255,14 +286,14 @@ __device__ inline void batch_gather(Acc<V> (&acc)[8], const SpmmArgs &a, const i
 // Rows of at most TINY_ROW (= 4) entries: 8 * GROUPS rows per wavefront.  Lane i owns row i
 // (entries [beg_l, end_l), destination dst_l, NO_UNIT = nothing) and loads its entries; the gather
 // phase hands them to the lane groups.  Every lane of the wavefront must call this.
-template <int LPR, int V, bool S32, bool FACT>
+template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __device__ inline void batch_units(const SpmmArgs &a, int beg_l, int end_l, int row_l, int dst_l, int lane)
 {
     constexpr int G = 64 / LPR;
     const int grp = lane / LPR, sub = lane % LPR;
     const int col = a.col0 + sub * V;
     const bool col_ok = col < a.col_end;
-    const int colc = col_ok ? col : a.col0;
+    const int colc = load_col<RAG>(a, col);
     Acc<V> acc[8];
     int c_l[4];
     float v_l[4];
@@ -278,21 +309,21 @@ __device__ inline void batch_units(const SpmmArgs &a, int beg_l, int end_l, int 
     for (int t = 0; t < 8; ++t) {
         const int d = __shfl(dst_l, t * G + grp, 64);
         const int r = __shfl(row_l, t * G + grp, 64);
-        if (d != NO_UNIT && col_ok) store_result<V>(acc[t], a, r, d, col);
+        if (d != NO_UNIT && col_ok) store_result<V, RAG>(acc[t], a, r, d, col);
     }
 }
 
-// Wavefront items: workgroup b serves class b mod n_classes, four items per workgroup: first the
-// class's own pieces, then every n_classes-th group of four whole-row items.  An item's
+// Wavefront items: workgroup b serves class b mod 8, four items per workgroup: first the
+// class's own pieces, then every eighth group of four whole-row items.  An item's
 // entries are read 64 (column, value) pairs at a time with one coalesced load each, lane i holding
 // entry base + i, and the next 64 are requested before the current ones are consumed.  (Giving a
 // wavefront several items and prefetching across them was measured and changes nothing: the
 // kernel is bound by the traffic of the gathers, not by the latency of its index loads.)
-template <int LPR, int V, bool S32, bool FACT>
+template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int cls = block % a.n_classes, j = block / a.n_classes;
+    const int cls = block % N_CLASSES, j = block / N_CLASSES;
     const int piece_blocks = (a.big_cnt[cls] + 3) >> 2;
     int64_t item;
     if (j < piece_blocks) { // uniform per workgroup
@@ -300,7 +331,7 @@ __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
         if (item >= a.big_cnt[cls]) return;
         item += a.big_off[cls];
     } else {
-        item = ((int64_t)(j - piece_blocks) * a.n_classes + cls) * 4 + wave;
+        item = ((int64_t)(j - piece_blocks) * N_CLASSES + cls) * 4 + wave;
         if (item >= a.wbig_cnt) return;
         item += a.wbig_off;
     }
@@ -308,7 +339,7 @@ __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
     const int grp = lane / LPR, sub = lane % LPR;
     const int col = a.col0 + sub * V;
     const bool active = col < a.col_end;
-    const int colc = active ? col : a.col0;
+    const int colc = load_col<RAG>(a, col);
     const int beg = s.y, end = s.z;
     Acc<V> acc;
     int idx = beg + lane;
@@ -328,7 +359,7 @@ __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
     }
 #pragma unroll
     for (int m = LPR; m < 64; m <<= 1) acc.add(shfl_xor_acc<V>(acc, m));
-    if (grp == 0 && active) store_result<V>(acc, a, s.x, s.w, col);
+    if (grp == 0 && active) store_result<V, RAG>(acc, a, s.x, s.w, col);
 }
 
 // The same for graphs that stay in cache (the one-launch kernel below): a workgroup takes 4 * ipw consecutive items,
@@ -336,11 +367,11 @@ __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
 // entries during the item's last chunk.  There a call lasts tens of microseconds and is made of chains of dependent loads
 // (descriptor -> entries -> gathers), which this overlaps across items: 0.049 -> 0.043 ms per call at 2.5 M entries.  On
 // graphs that stream from memory it changes nothing and its eight extra registers cost 2 %, so they keep one item per wavefront.
-template <int LPR, int V, bool S32, bool FACT>
+template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int cls = block % a.n_classes, j = block / a.n_classes;
+    const int cls = block % N_CLASSES, j = block / N_CLASSES;
     const int ipb = 4 * a.ipw; // items per workgroup
     const int piece_blocks = (a.big_cnt[cls] + ipb - 1) / ipb;
     int64_t first, left;
@@ -349,7 +380,7 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block
         left = a.big_cnt[cls] - first;
         first += a.big_off[cls];
     } else {
-        first = ((int64_t)(j - piece_blocks) * a.n_classes + cls) * ipb;
+        first = ((int64_t)(j - piece_blocks) * N_CLASSES + cls) * ipb;
         left = a.wbig_cnt - first;
         first += a.wbig_off;
     }
@@ -359,7 +390,7 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block
     const int grp = lane / LPR, sub = lane % LPR;
     const int col = a.col0 + sub * V;
     const bool active = col < a.col_end;
-    const int colc = active ? col : a.col0;
+    const int colc = load_col<RAG>(a, col);
     int4 s = *reinterpret_cast<const int4 *>(a.items + first + t);
     int idx = s.y + lane;
     int c_l = a.colidx[idx < s.z ? idx : s.y];
@@ -390,7 +421,7 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block
         }
 #pragma unroll
         for (int m = LPR; m < 64; m <<= 1) acc.add(shfl_xor_acc<V>(acc, m));
-        if (grp == 0 && active) store_result<V>(acc, a, s.x, s.w, col);
+        if (grp == 0 && active) store_result<V, RAG>(acc, a, s.x, s.w, col);
         if (!more) break;
         s = sn;
         t += 4;
@@ -398,14 +429,14 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block
 }
 
 // Lane-group items (whole rows and class pieces of 5..GI_MAX entries, GI_MAX = the schedule's item_max):
-// workgroup b serves class b mod n_classes and takes a run of 32 * G consecutive items of its list (first the
-// class's own pieces, then every n_classes-th run of the whole rows).  In round r its four wavefronts work on
+// workgroup b serves class b mod 8 and takes a run of 32 * G consecutive items of its list (first the
+// class's own pieces, then every eighth run of the whole rows).  In round r its four wavefronts work on
 // 4 * G consecutive items of the run, lane group grp of wavefront w on item r * 4 * G + w * G + grp (lane
 // r * G + grp holds that item's descriptor).  The group
 // reads the item's (column, value) pairs with one read per LPR entries (lane `sub` holds entries
 // sub, sub + LPR, ...; the next round's pairs are requested before this round's gathers), and each
 // gather takes its pair from the holding lane by a cross-lane read, eight gathers in flight.
-template <int LPR, int V, bool S32, int GI_MAX, bool FACT>
+template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG>
 __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
 {
     constexpr int G = 64 / LPR;                 // items in flight per wavefront
@@ -415,7 +446,7 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
     using L = Ld<V>;
     constexpr int RUN = 4 * UNITS;              // items per workgroup: one run of consecutive items of its list
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int cls = block % a.n_classes, blk = block / a.n_classes;
+    const int cls = block % N_CLASSES, blk = block / N_CLASSES;
     const int piece_blocks = (a.small_cnt[cls] + RUN - 1) / RUN;
     int64_t first, left;
     if (blk < piece_blocks) { // uniform per workgroup
@@ -423,7 +454,7 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
         left = a.small_cnt[cls] - first;
         first += a.small_off[cls];
     } else {
-        first = ((int64_t)(blk - piece_blocks) * a.n_classes + cls) * RUN;
+        first = ((int64_t)(blk - piece_blocks) * N_CLASSES + cls) * RUN;
         left = a.wsmall_cnt - first;
         first += a.wsmall_off;
     }
@@ -441,7 +472,7 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
     const int grp = lane / LPR, sub = lane % LPR, gbase = lane - sub;
     const int col = a.col0 + sub * V;
     const bool col_ok = col < a.col_end;
-    const int colc = col_ok ? col : a.col0;
+    const int colc = load_col<RAG>(a, col);
     int beg = __shfl(d.y, grp, 64), end = __shfl(d.z, grp, 64);
     int c_k[K];
     float v_k[K];
@@ -486,7 +517,7 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
             for (int u = 0; u < U; ++u)
                 if (j0 + u < len) acc.fma(v[u], x[u]);
         }
-        if (dst != NO_UNIT && col_ok) store_result<V>(acc, a, row, dst, col);
+        if (dst != NO_UNIT && col_ok) store_result<V, RAG>(acc, a, row, dst, col);
         beg = nbeg;
         end = nend;
 #pragma unroll
@@ -496,7 +527,7 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
 
 // Rows of at most TINY_ROW entries, 64 consecutive positions of the schedule per wavefront (consecutive
 // rows in natural order).
-template <int LPR, int V, bool S32, bool FACT>
+template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __device__ __forceinline__ void tiny_rows_body(const SpmmArgs &a, int block)
 {
     constexpr int UNITS = 8 * (64 / LPR); // rows per wavefront
@@ -509,31 +540,31 @@ __device__ __forceinline__ void tiny_rows_body(const SpmmArgs &a, int block)
         const int b = a.rowptr[row], e = a.rowptr[row + 1];
         if (e - b <= TINY_ROW) { row_l = row; beg_l = b; end_l = e; dst_l = row; }
     }
-    batch_units<LPR, V, S32, FACT>(a, beg_l, end_l, row_l, dst_l, lane);
+    batch_units<LPR, V, S32, FACT, RAG>(a, beg_l, end_l, row_l, dst_l, lane);
 }
 
-template <int LPR, int V, bool S32, bool FACT>
-__global__ __launch_bounds__(256) void spmm_wave_items_kernel(const SpmmArgs a) { wave_items_body<LPR, V, S32, FACT>(a, blockIdx.x); }
+template <int LPR, int V, bool S32, bool FACT, bool RAG>
+__global__ __launch_bounds__(256) void spmm_wave_items_kernel(const SpmmArgs a) { wave_items_body<LPR, V, S32, FACT, RAG>(a, blockIdx.x); }
 
-template <int LPR, int V, bool S32, int GI_MAX, bool FACT>
-__global__ __launch_bounds__(256) void spmm_group_items_kernel(const SpmmArgs a) { group_items_body<LPR, V, S32, GI_MAX, FACT>(a, blockIdx.x); }
+template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG>
+__global__ __launch_bounds__(256) void spmm_group_items_kernel(const SpmmArgs a) { group_items_body<LPR, V, S32, GI_MAX, FACT, RAG>(a, blockIdx.x); }
 
-template <int LPR, int V, bool S32, bool FACT>
-__global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a) { tiny_rows_body<LPR, V, S32, FACT>(a, blockIdx.x); }
+template <int LPR, int V, bool S32, bool FACT, bool RAG>
+__global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a) { tiny_rows_body<LPR, V, S32, FACT, RAG>(a, blockIdx.x); }
 
 // All three item kinds in one launch: workgroups [0, g1) take wavefront items, [g1, g1 + g2)
-// lane-group items, the rest tiny rows (g1 and g2 are multiples of n_classes, so workgroup b still
-// serves class b mod n_classes).  For graphs that stay in cache a call takes tens of microseconds and
+// lane-group items, the rest tiny rows (g1 and g2 are multiples of 8, so workgroup b still
+// serves class b mod 8).  For graphs that stay in cache a call takes tens of microseconds and
 // each of three launches would pay its own ramp-up and its own chain of dependent loads; in one launch
 // they overlap (cfg2: 0.075 -> 0.056 ms per call).  Large graphs keep the three launches: there the
 // class pieces must have the L2s to themselves before the whole rows start (merged: cfg5 4.09 -> 4.30 ms).
-template <int LPR, int V, bool S32, bool FACT>
+template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __global__ __launch_bounds__(256) void spmm_merged_kernel(const SpmmArgs a, int g1, int g2)
 {
     const int b = blockIdx.x; // uniform per workgroup
-    if (b < g1) wave_items_run_body<LPR, V, S32, FACT>(a, b);
-    else if (b < g1 + g2) group_items_body<LPR, V, S32, ITEM_SHORT, FACT>(a, b - g1);
-    else tiny_rows_body<LPR, V, S32, FACT>(a, b - g1 - g2);
+    if (b < g1) wave_items_run_body<LPR, V, S32, FACT, RAG>(a, b);
+    else if (b < g1 + g2) group_items_body<LPR, V, S32, ITEM_SHORT, FACT, RAG>(a, b - g1);
+    else tiny_rows_body<LPR, V, S32, FACT, RAG>(a, b - g1 - g2);
 }
 
 // Rows with several items: add the partial slots in order.  One thread per (row, column); eight
@@ -563,83 +594,79 @@ __global__ __launch_bounds__(256) void spmm_fix_kernel(const SpmmArgs a, int32_t
     a.Y[(int64_t)f.x * a.ldy + col] = acc;
 }
 
-template <int LPR, int V, bool S32, bool FACT>
+template <int LPR, int V, bool S32, bool FACT, bool RAG>
 int launch_variant(const SpmmArgs &a, hipStream_t stream)
 {
     constexpr int units_per_block = 4 * 8 * (64 / LPR);
-    const int64_t g1 = (int64_t)a.n_classes * a.big_blocks;
-    const int64_t g2 = (int64_t)a.n_classes * a.small_blocks;
+    const int64_t g1 = (int64_t)N_CLASSES * a.big_blocks;
+    const int64_t g2 = (int64_t)N_CLASSES * a.small_blocks;
     const int64_t g3 = (a.n + units_per_block - 1) / units_per_block;
     SG_REQUIRE(g1 <= INT32_MAX && g2 <= INT32_MAX && g3 <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
     if (a.item_max <= ITEM_SHORT) { // cache-resident graph: one launch (big_blocks counts runs of 4 * ipw items)
         SG_REQUIRE(g1 + g2 + g3 <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
-        spmm_merged_kernel<LPR, V, S32, FACT><<<(unsigned)(g1 + g2 + g3), 256, 0, stream>>>(a, (int)g1, (int)g2);
+        spmm_merged_kernel<LPR, V, S32, FACT, RAG><<<(unsigned)(g1 + g2 + g3), 256, 0, stream>>>(a, (int)g1, (int)g2);
         SG_LAUNCH_CHECK();
         return SLICEGCN_OK;
     }
     if (g1 > 0) {
-        spmm_wave_items_kernel<LPR, V, S32, FACT><<<(unsigned)g1, 256, 0, stream>>>(a);
+        spmm_wave_items_kernel<LPR, V, S32, FACT, RAG><<<(unsigned)g1, 256, 0, stream>>>(a);
         SG_LAUNCH_CHECK();
     }
     if (g2 > 0) {
-        spmm_group_items_kernel<LPR, V, S32, ITEM_LONG, FACT><<<(unsigned)g2, 256, 0, stream>>>(a);
+        spmm_group_items_kernel<LPR, V, S32, ITEM_LONG, FACT, RAG><<<(unsigned)g2, 256, 0, stream>>>(a);
         SG_LAUNCH_CHECK();
     }
-    spmm_tiny_rows_kernel<LPR, V, S32, FACT><<<(unsigned)g3, 256, 0, stream>>>(a);
+    spmm_tiny_rows_kernel<LPR, V, S32, FACT, RAG><<<(unsigned)g3, 256, 0, stream>>>(a);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
+}
+
+template <int LPR, int V, bool FACT>
+int launch_layout(const SpmmArgs &a, hipStream_t stream)
+{
+    if constexpr (V == 1) return launch_variant<LPR, V, false, FACT, false>(a, stream);
+    else {
+        if (a.load_max > 0)
+            return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, true>(a, stream) : launch_variant<LPR, V, false, FACT, true>(a, stream);
+        return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, false>(a, stream) : launch_variant<LPR, V, false, FACT, false>(a, stream);
+    }
 }
 
 template <int LPR, int V>
 int launch_kernels(const SpmmArgs &a, hipStream_t stream)
 {
-    if (a.dinv) { // factored form
-        if (V == 4 && a.ldx_bytes != 0) return launch_variant<LPR, V, V == 4, true>(a, stream);
-        return launch_variant<LPR, V, false, true>(a, stream);
-    }
-    if (V == 4 && a.ldx_bytes != 0) return launch_variant<LPR, V, V == 4, false>(a, stream);
-    return launch_variant<LPR, V, false, false>(a, stream);
+    return a.dinv ? launch_layout<LPR, V, true>(a, stream) : launch_layout<LPR, V, false>(a, stream);
 }
 
-template <int V>
-int launch_pass(const SpmmArgs &a, int lpr, hipStream_t stream)
+int launch_pass(const SpmmArgs &a, int v, int lpr, hipStream_t stream)
 {
+    if (v == 1) return launch_kernels<8, 1>(a, stream); // fewer than 4 columns
     switch (lpr) {
-    case 8: return launch_kernels<8, V>(a, stream);
-    case 16: return launch_kernels<16, V>(a, stream);
-    case 32: return launch_kernels<32, V>(a, stream);
-    default: return launch_kernels<64, V>(a, stream);
+    case 8: return launch_kernels<8, 4>(a, stream);
+    case 16: return launch_kernels<16, 4>(a, stream);
+    default: return launch_kernels<32, 4>(a, stream); // a pass is at most 128 columns
     }
 }
 
 } // namespace
 
-// Bytes of partial-sum workspace an aggregation of `width` columns over pattern `m` may need: the larger
-// of the two schedules (which one runs depends on the operand layout, unknown here), one slot of
-// min(width rounded up to 4, pass width) floats per item of every row cut into several items.
+// Bytes of partial-sum workspace an aggregation of `width` columns over pattern `m` needs: one slot of
+// min(width rounded up to 4, columns per pass) floats per item of every row cut into several items.
 size_t spmm_workspace_bytes(const Csr &m, int32_t width)
 {
     const int64_t w4 = round_up(width, 4);
-    const int64_t a = m.wide.n_slots * (w4 < WIDE_SLOT_COLS ? w4 : WIDE_SLOT_COLS);
-    const int64_t b = m.xcd.n_slots * (w4 < XCD_SLOT_COLS ? w4 : XCD_SLOT_COLS);
-    return (size_t)round_up((a > b ? a : b) * (int64_t)sizeof(float), 256);
+    return (size_t)round_up(m.sched.n_slots * (w4 < PASS_COLS ? w4 : PASS_COLS) * (int64_t)sizeof(float), 256);
 }
 
 int launch_spmm(const slicegcn_graph *g, const Csr &m, const float *X, int64_t ldx, int32_t width,
                 float *Y, int64_t ldy, const float *Add, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream,
                 bool prescaled)
 {
-    // 16-byte gathers need an aligned base, ld % 4 == 0 and room for the last vector of a row
-    const bool vec_load = aligned16(X) && (ldx % 4 == 0) && ldx >= round_up(width, 4);
-    const int V = vec_load ? 4 : 1;
-    // 16-byte gathers use the 8-class schedule in passes of at most 128 columns (32 lanes per row):
-    // narrower passes re-read the index streams more often, wider ones make the set of hot rows of
-    // the operand too large for the L2s (301 columns: 7.8 / 7.4 / 7.7 ms for passes of 64 / 128 / 256);
-    // the scalar path keeps the single-class schedule
-    const bool use_xcd = vec_load;
-    const Schedule &sc = use_xcd ? m.xcd : m.wide;
-    const int slot_cols = use_xcd ? XCD_SLOT_COLS : WIDE_SLOT_COLS;
-    const int64_t used_cols = width < slot_cols ? round_up(width, 4) : slot_cols; // one pass: slots packed densely
+    const int V = width >= 4 ? 4 : 1;
+    // passes of at most 128 columns (32 lanes per row): narrower ones re-read the index streams more often, wider ones
+    // make the set of hot rows of the operand too large for the L2s (301 columns: 7.8 / 7.4 / 7.7 ms for passes of 64 / 128 / 256)
+    const Schedule &sc = m.sched;
+    const int64_t used_cols = width < PASS_COLS ? round_up(width, 4) : PASS_COLS; // one pass: slots packed densely
     const size_t need = (size_t)(sc.n_slots * used_cols) * sizeof(float);
     SG_REQUIRE(need == 0 || (ws != nullptr && ws_bytes >= need), SLICEGCN_EWORKSPACE,
                "aggregation: workspace of %zu bytes, %zu needed", ws_bytes, need);
@@ -653,10 +680,11 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const float *X, int64_t l
     const bool s32 = g->n < (1 << 24) && ldx * 4 < (1 << 24) && (int64_t)g->n * ldx * 4 < ((int64_t)1 << 32);
     a.ldx_bytes = s32 ? (uint32_t)(ldx * 4) : 0u;
     a.n = (int32_t)g->n;
-    a.n_classes = sc.n_classes;
     a.item_max = sc.item_max;
-    a.slot_cols = slot_cols; // narrowed below to the pass width
-    a.vec_store = aligned16(Y) && (ldy % 4 == 0) && (!Add || (aligned16(Add) && ldadd % 4 == 0));
+    a.slot_cols = (int32_t)used_cols;
+    // rows whose last vector stays inside the row: a multiple of four columns, or room for the padding up to one
+    const bool whole = V == 1 || width % 4 == 0 || (aligned16(X) && ldx % 4 == 0);
+    a.load_max = whole ? 0 : width - 4;
     a.wbig_off = sc.wbig_off; a.wbig_cnt = sc.wbig_cnt;
     a.wsmall_off = sc.wsmall_off; a.wsmall_cnt = sc.wsmall_cnt;
     // workgroups per class: the class's own pieces, then its share of the whole-row chunks
@@ -664,34 +692,31 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const float *X, int64_t l
     const int64_t ipb = 4 * a.ipw;
     const int64_t wbig_chunks = ((int64_t)sc.wbig_cnt + ipb - 1) / ipb;
     int64_t big_blocks = 0;
-    for (int c = 0; c < MAX_CLASSES; ++c) {
+    for (int c = 0; c < N_CLASSES; ++c) {
         a.big_off[c] = sc.big_off[c]; a.big_cnt[c] = sc.big_cnt[c];
         a.small_off[c] = sc.small_off[c]; a.small_cnt[c] = sc.small_cnt[c];
-        if (c >= sc.n_classes) continue;
-        const int64_t b = (sc.big_cnt[c] + ipb - 1) / ipb + (wbig_chunks + sc.n_classes - 1 - c) / sc.n_classes;
+        const int64_t b = (sc.big_cnt[c] + ipb - 1) / ipb + (wbig_chunks + N_CLASSES - 1 - c) / N_CLASSES;
         big_blocks = b > big_blocks ? b : big_blocks;
     }
-    SG_REQUIRE(big_blocks * sc.n_classes <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
+    SG_REQUIRE(big_blocks * N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
     a.big_blocks = (int32_t)big_blocks;
     ProfScope prof(Add ? SLICEGCN_PROF_SPMM_ADD : SLICEGCN_PROF_SPMM, width, stream);
-    const int pass_cols = vec_load ? slot_cols : 64;
-    a.slot_cols = (int32_t)used_cols;
-    for (int32_t c0 = 0; c0 < width; c0 += pass_cols) {
+    for (int32_t c0 = 0; c0 < width; c0 += PASS_COLS) {
         a.col0 = c0;
-        a.col_end = width < c0 + pass_cols ? width : c0 + pass_cols;
+        a.col_end = width < c0 + PASS_COLS ? width : c0 + PASS_COLS;
         const int lanes_needed = (a.col_end - c0 + V - 1) / V;
         int lpr = 8;
-        while (lpr < lanes_needed) lpr <<= 1; // 8, 16, 32 or 64
+        while (lpr < lanes_needed) lpr <<= 1; // 8, 16 or 32
         const int64_t run = 4 * 8 * (64 / lpr); // lane-group items per workgroup: runs of consecutive items
         const int64_t wsmall_runs = ((int64_t)sc.wsmall_cnt + run - 1) / run;
         int64_t small_blocks = 0;
-        for (int c = 0; c < sc.n_classes; ++c) { // the class's own pieces, then its share of the whole-row runs
-            const int64_t b = (sc.small_cnt[c] + run - 1) / run + (wsmall_runs + sc.n_classes - 1 - c) / sc.n_classes;
+        for (int c = 0; c < N_CLASSES; ++c) { // the class's own pieces, then its share of the whole-row runs
+            const int64_t b = (sc.small_cnt[c] + run - 1) / run + (wsmall_runs + N_CLASSES - 1 - c) / N_CLASSES;
             small_blocks = b > small_blocks ? b : small_blocks;
         }
-        SG_REQUIRE(small_blocks * sc.n_classes <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
+        SG_REQUIRE(small_blocks * N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
         a.small_blocks = (int32_t)small_blocks;
-        if (int rc = vec_load ? launch_pass<4>(a, lpr, stream) : launch_pass<1>(a, lpr, stream)) return rc;
+        if (int rc = launch_pass(a, V, lpr, stream)) return rc;
         if (sc.n_fix > 0) {
             const int64_t threads = sc.n_fix * (int64_t)(a.col_end - c0);
             spmm_fix_kernel<<<(unsigned)((threads + 255) / 256), 256, 0, stream>>>(a, (int32_t)sc.n_fix);
