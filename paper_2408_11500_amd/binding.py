@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from dataclasses import dataclass
 
 import numpy as np
@@ -84,6 +85,10 @@ class _LayerGrads(ctypes.Structure):
     _fields_ = [("dW_agg", ctypes.c_void_p), ("db", ctypes.c_void_p), ("dW_self", ctypes.c_void_p), ("db_self", ctypes.c_void_p)]
 
 
+class _Allocator(ctypes.Structure):
+    _fields_ = [("ctx", ctypes.c_void_p), ("alloc", ctypes.c_void_p)]
+
+
 _lib = None
 
 
@@ -98,6 +103,10 @@ def lib() -> ctypes.CDLL:
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
         L.slicegcn_slice_strategy.argtypes = [i32, i32, ctypes.c_double, vp, vp, vp]
         L.slicegcn_build_norm_csr.argtypes = [vp, vp, i64, i64, ctypes.c_uint32, vp, ctypes.POINTER(vp)]
+        L.slicegcn_build_workspace_bytes.argtypes = [i64, i64, ctypes.c_uint32]
+        L.slicegcn_build_workspace_bytes.restype = sz
+        L.slicegcn_build_norm_csr_with.argtypes = [vp, vp, i64, i64, ctypes.c_uint32, ctypes.POINTER(_Allocator), vp, sz, vp,
+                                                   ctypes.POINTER(vp)]
         L.slicegcn_graph_view.argtypes = [vp, ctypes.POINTER(_CsrView)]
         L.slicegcn_graph_destroy.argtypes = [vp]
         L.slicegcn_slice_feature.argtypes = [vp, i64, i64, i32, i32, vp, i64, vp]
@@ -197,10 +206,12 @@ class CsrView:
 class Graph:
     """Owner of a ``slicegcn_graph`` handle.  The handle itself is read-only; ``default_ws`` hands out one
     cached device buffer for callers that pass no workspace of their own (such calls must then be ordered
-    on one stream; callers that overlap calls on several streams pass one workspace per stream)."""
+    on one stream; callers that overlap calls on several streams pass one workspace per stream).
+    ``memory``: the tensors the handle's arrays live in."""
 
-    def __init__(self, handle: int):
+    def __init__(self, handle: int, memory=()):
         self._h = handle
+        self._memory = list(memory)
         self._ws = None
 
     def default_ws(self, nbytes: int):
@@ -233,8 +244,11 @@ class Graph:
 
     def destroy(self):
         if self._h:
+            if self._memory:  # a stream other than the one it was made on may still read it
+                torch.cuda.synchronize()
             lib().slicegcn_graph_destroy(self._h)
             self._h = 0
+            self._memory = []
             self._ws = None
 
     def __del__(self):
@@ -263,6 +277,21 @@ def _to_host(ptr: int, count: int, dtype) -> np.ndarray:
     return out
 
 
+_building = threading.local()  # the blocks of the build the calling thread is in
+
+
+@ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t)
+def _alloc_block(_ctx, nbytes):
+    try:
+        _building.blocks.append(torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+        return _building.blocks[-1].data_ptr()
+    except Exception:  # out of memory: the build returns ENOMEM
+        return None
+
+
+_allocator = _Allocator(None, ctypes.cast(_alloc_block, ctypes.c_void_p))
+
+
 def slicegcn_build_norm_csr(src: torch.Tensor, dst: torch.Tensor, n_nodes: int,
                             flags: int = SYMMETRIZE | ADD_SELF_LOOPS) -> Graph:
     ps = _vec(src, "src", torch.int64) if src.numel() else None
@@ -270,8 +299,19 @@ def slicegcn_build_norm_csr(src: torch.Tensor, dst: torch.Tensor, n_nodes: int,
     if src.numel() != dst.numel():
         raise ValueError("src and dst differ in length")
     h = ctypes.c_void_p(0)
-    _check(lib().slicegcn_build_norm_csr(ps, pd, src.numel(), n_nodes, flags, _stream(), ctypes.byref(h)))
-    return Graph(h.value)
+    # scratch memory and the handle's arrays come from torch's caching allocator: device allocations of their own cost
+    # ten times the build (126 M entries: 107 ms with them, 6.8 ms without)
+    ws = None
+    nbytes = int(lib().slicegcn_build_workspace_bytes(src.numel(), n_nodes, flags))
+    if nbytes:
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    _building.blocks = blocks = []
+    try:
+        _check(lib().slicegcn_build_norm_csr_with(ps, pd, src.numel(), n_nodes, flags, ctypes.byref(_allocator), *_ws(ws),
+                                                  _stream(), ctypes.byref(h)))
+    finally:
+        _building.blocks = None
+    return Graph(h.value, blocks)
 
 
 def slicegcn_slice_feature(X: torch.Tensor, start: int, end: int, Xs: torch.Tensor):

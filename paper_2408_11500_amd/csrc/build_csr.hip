@@ -1,76 +1,131 @@
 // Normalised-adjacency builder: edge pairs -> canonical CSR of A^ = D~^-1/2 (A + I) D~^-1/2
 // (the normalisation 1/c_vu of the paper's GCN layer equation), plus the row schedule the
 // aggregation kernels use.  Integer work only, apart from one rsqrt per node and one multiply
-// per stored entry.  Sorting, scanning and duplicate removal use rocPRIM device primitives on
-// 64-bit keys (row << 32 | col); everything else is a small kernel below.
+// per stored entry.
+//
+//   keys      one key (row, col) per candidate entry, packed into as many bits as the node count needs
+//             (32-bit keys up to 65 535 nodes): the fewer bits, the fewer passes of the radix sort;
+//   sort      rocPRIM radix sort of the keys;
+//   compact   a wavefront takes 1024 consecutive keys in rounds of 64: repeats and the sentinel drop out by
+//             ballot, column and row of an entry and the row pointers are written in the same sweep
+//             (126 M keys: 0.7 ms for its two sweeps where unique, row pointers and entries took 4.1 ms);
+//   schedule  rows sorted into the item lists by ballot as well; only rows that are cut by column class
+//             need per-row tables.
+//
+// What bounds a build beside the sort is the host: device allocations and synchronisations.  All scratch
+// memory is one workspace and the handle's arrays are at most five blocks, both from the caller if it has an
+// allocator of its own; the stream is synchronised only where a size has to be known.
 #include "common.h"
+#include "slicegcn_native.h"
 
 #include <rocprim/rocprim.hpp>
 
-#include <cstdarg>
 #include <cstdlib>
 #include <new>
-#include <vector>
 
 namespace slicegcn {
 
 namespace {
 
-struct DevBuf { // frees on scope exit; release() hands the pointer over
-    void *p = nullptr;
-    ~DevBuf() { if (p) (void)hipFree(p); }
-    int alloc(size_t bytes) {
-        hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
-        if (e != hipSuccess) {
-            p = nullptr;
-            set_error("hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
-            return e == hipErrorOutOfMemory ? SLICEGCN_ENOMEM : SLICEGCN_EHIP;
-        }
-        return SLICEGCN_OK;
-    }
-    template <class T> T *as() const { return static_cast<T *>(p); }
-    template <class T> T *release() { T *r = static_cast<T *>(p); p = nullptr; return r; }
-};
-
 constexpr int TPB = 256;
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + TPB - 1) / TPB); }
 
-// One key per directed candidate entry.  Self pairs and out-of-range pairs become the
-// sentinel key (row n), which sorts behind every real row and is dropped later.
+// Device words the host reads back: [0] out-of-range edges, [1] stored entries, [2] ... the schedule's and the row order's.
+constexpr int N_COUNTERS = 64;
+
+// ---- keys -------------------------------------------------------------------------------
+// Key (row, col) = row << col_bits | col.  Out-of-range pairs, and self pairs, become the sentinel (row n), which
+// sorts behind every real row and is dropped later.
+template <class K>
 __global__ void make_keys_kernel(const int64_t *__restrict__ src, const int64_t *__restrict__ dst,
-                                 int64_t n_edges, int64_t n, int sym, int loops,
-                                 uint64_t *__restrict__ keys, int *__restrict__ n_bad)
+                                 int64_t n_edges, int64_t n, int col_bits, int sym, int loops,
+                                 K *__restrict__ keys, int *__restrict__ n_bad)
 {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    const uint64_t sentinel = (uint64_t)n << 32;
+    const K sentinel = (K)n << col_bits;
     if (i < n_edges) {
         const int64_t u = src[i], v = dst[i];
-        uint64_t k1 = sentinel, k2 = sentinel;
+        K k1 = sentinel, k2 = sentinel;
         if (u < 0 || u >= n || v < 0 || v >= n) {
             atomicAdd(n_bad, 1);
         } else if (u != v) {
-            k1 = ((uint64_t)u << 32) | (uint64_t)v;
-            k2 = ((uint64_t)v << 32) | (uint64_t)u;
+            k1 = ((K)u << col_bits) | (K)v;
+            k2 = ((K)v << col_bits) | (K)u;
         }
         keys[i] = k1;
         if (sym) keys[n_edges + i] = k2;
     } else if (loops && i < n_edges + n) {
-        const uint64_t v = (uint64_t)(i - n_edges);
-        keys[(sym ? 2 : 1) * n_edges + (int64_t)v] = (v << 32) | v;
+        const K v = (K)(i - n_edges);
+        keys[(sym ? 2 : 1) * n_edges + (i - n_edges)] = (v << col_bits) | v;
     }
 }
 
-// rowptr[r] = number of keys with row < r = lower bound of (r << 32) in the sorted keys.
-__global__ void rowptr_kernel(const uint64_t *__restrict__ keys, int64_t nnz, int64_t n,
-                              int32_t *__restrict__ rowptr)
+template <class K>
+__global__ void swapped_keys_kernel(const int32_t *__restrict__ row, const int32_t *__restrict__ col, int64_t nnz, int col_bits,
+                                    K *__restrict__ keys)
+{
+    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (i < nnz) keys[i] = ((K)col[i] << col_bits) | (K)row[i];
+}
+
+// ---- sorted keys -> CSR -----------------------------------------------------------------
+constexpr int CHUNK = 1024; // keys per wavefront
+inline int64_t chunks_of(int64_t n_keys) { return (n_keys + CHUNK - 1) / CHUNK; }
+
+// One sweep over the sorted keys: WRITE = false counts the distinct real keys of every chunk, WRITE = true writes
+// their entries from the scanned counts on and, where no row is empty (rowptr != NULL: the diagonal is stored), the
+// row pointers, from the first key of every row.
+template <class K, bool WRITE>
+__global__ __launch_bounds__(256) void compact_kernel(const K *__restrict__ keys, int64_t n_keys, int64_t n, int col_bits,
+                                                      int32_t *__restrict__ chunk, int32_t *__restrict__ colidx,
+                                                      int32_t *__restrict__ rowid, int32_t *__restrict__ rowptr)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t first = c * CHUNK;
+    if (first >= n_keys) return; // uniform per wavefront
+    const K col_mask = ((K)1 << col_bits) - 1;
+    int32_t pos = WRITE ? chunk[c] : 0;
+    K last = first > 0 ? keys[first - 1] : (K)0; // the key before this round's first
+    bool has_last = first > 0;
+#pragma unroll 4
+    for (int r = 0; r < CHUNK / 64; ++r) {
+        const int64_t i = first + r * 64 + lane;
+        const bool in = i < n_keys;
+        const K k = in ? keys[i] : (K)0;
+        K prev = __shfl_up(k, 1, 64);
+        if (lane == 0) prev = last;
+        const bool has_prev = lane > 0 || has_last;
+        const int64_t row = (int64_t)(k >> col_bits);
+        const bool keep = in && row < n && (!has_prev || k != prev);
+        const unsigned long long bits = __ballot(keep);
+        if (WRITE) {
+            const int32_t at = pos + __popcll(bits & ((1ull << lane) - 1ull));
+            if (keep) {
+                colidx[at] = (int32_t)(k & col_mask);
+                rowid[at] = (int32_t)row;
+            }
+            if (rowptr) {
+                if (keep && (!has_prev || (int64_t)(prev >> col_bits) != row)) rowptr[row] = at;
+                if (i == n_keys - 1) rowptr[n] = at + (keep ? 1 : 0);
+            }
+        }
+        pos += __popcll(bits);
+        last = __shfl(k, 63, 64);
+        has_last = true;
+    }
+    if (!WRITE && lane == 0) chunk[c] = pos;
+}
+
+// rowptr[r] = entries of the rows before r = lower bound of r in the entries' rows (patterns with empty rows)
+__global__ void rowptr_kernel(const int32_t *__restrict__ rowid, int64_t nnz, int64_t n, int32_t *__restrict__ rowptr)
 {
     const int64_t r = (int64_t)blockIdx.x * TPB + threadIdx.x;
     if (r > n) return;
-    const uint64_t target = (uint64_t)r << 32;
     int64_t lo = 0, hi = nnz;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
-        if (keys[mid] < target) lo = mid + 1; else hi = mid;
+        if (rowid[mid] < r) lo = mid + 1; else hi = mid;
     }
     rowptr[r] = (int32_t)lo;
 }
@@ -86,234 +141,290 @@ __global__ void degree_kernel(const int32_t *__restrict__ rowptr, int64_t n,
     sqrtd[v] = (float)sqrt((double)(d > 0 ? d : 1));
 }
 
-__global__ void entries_kernel(const uint64_t *__restrict__ keys, int64_t nnz,
-                               const float *__restrict__ dinv,
-                               int32_t *__restrict__ colidx, float *__restrict__ vals)
+// Four entries per thread (the arrays come 16-byte aligned): bound by the gather of dinv[col].
+__global__ void vals_kernel(const int32_t *__restrict__ rowid, const int32_t *__restrict__ colidx, int64_t nnz,
+                            const float *__restrict__ dinv, float *__restrict__ vals)
 {
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (i >= nnz) return;
-    const uint64_t k = keys[i];
-    const uint32_t row = (uint32_t)(k >> 32), col = (uint32_t)(k & 0xffffffffu);
-    colidx[i] = (int32_t)col;
-    vals[i] = dinv[row] * dinv[col];
-}
-
-__global__ void swap_keys_kernel(const uint64_t *__restrict__ in, int64_t nnz, uint64_t *__restrict__ out)
-{
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (i >= nnz) return;
-    const uint64_t k = in[i];
-    out[i] = (k << 32) | (k >> 32);
+    const int64_t i = ((int64_t)blockIdx.x * TPB + threadIdx.x) * 4;
+    if (i + 4 <= nnz) {
+        const int4 r = *reinterpret_cast<const int4 *>(rowid + i), c = *reinterpret_cast<const int4 *>(colidx + i);
+        *reinterpret_cast<float4 *>(vals + i) =
+            make_float4(dinv[r.x] * dinv[c.x], dinv[r.y] * dinv[c.y], dinv[r.z] * dinv[c.z], dinv[r.w] * dinv[c.w]);
+    } else {
+        for (int64_t j = i; j < nnz; ++j) vals[j] = dinv[rowid[j]] * dinv[colidx[j]];
+    }
 }
 
 // ---- schedule ---------------------------------------------------------------------------
-// Column class c holds the columns [first[c], first[c+1]); the boundaries are eighth-
-// quantiles of the stored entries per column, so that the classes carry equal numbers of entries
-// whatever the vertex numbering (with hubs numbered first, equal column ranges would put almost
-// half of the entries into the first class).
+// Column class c holds the columns [first[c], first[c+1]); the boundaries are the eighth-quantiles of the stored
+// entries per column, so that the classes carry equal numbers of entries whatever the vertex numbering (with hubs
+// numbered first, equal column ranges would put almost half of the entries into the first class).
 struct ClassBounds {
     int32_t first[N_CLASSES + 1];
 };
 
 // colptr: row pointer of the transposed pattern (entries per column, scanned)
-__global__ void class_bounds_kernel(const int32_t *__restrict__ colptr, int64_t n, int32_t *__restrict__ first)
+__device__ inline int32_t class_bound(const int32_t *__restrict__ colptr, int64_t n, int c)
 {
-    const int c = threadIdx.x;
-    if (c > N_CLASSES) return;
-    if (c == 0) { first[0] = 0; return; }
-    if (c == N_CLASSES) { first[c] = (int32_t)n; return; }
+    if (c == 0) return 0;
+    if (c == N_CLASSES) return (int32_t)n;
     const int64_t target = (int64_t)colptr[n] * c / N_CLASSES;
     int64_t lo = 0, hi = n; // smallest column j with colptr[j] >= target
     while (lo < hi) {
         const int64_t mid = lo + ((hi - lo) >> 1);
         if (colptr[mid] < target) lo = mid + 1; else hi = mid;
     }
-    first[c] = (int32_t)lo;
+    return (int32_t)lo;
 }
 
-// Item tables: 2c = wavefront items of class c (pieces of rows cut by column class), 2c + 1 =
-// lane-group items of class c, 2 * N_CLASSES = wavefront items of rows kept whole, 2 * N_CLASSES + 1
-// = lane-group items that are whole rows.  counts layout: cnt[table * (n+1) + row].
-constexpr int MAX_TABLES = 2 * N_CLASSES + 2;
-struct RowCut {
-    int32_t lo[N_CLASSES + 1];
-};
-
-// Per long row: the entries of column class c are [lower_bound(first[c]), lower_bound(first[c+1])).
-__device__ inline RowCut cut_row(const int32_t *__restrict__ colidx, int32_t beg, int32_t end, const ClassBounds &cb)
+// Kinds of rows (see common.h): whole rows make one item each, long ones are cut by column class.
+constexpr int ROW_TINY = -1, ROW_WAVE = 0, ROW_GROUP = 1, ROW_LONG = 2;
+__device__ inline int row_kind(int32_t d, int32_t item_max)
 {
-    RowCut rc;
-    rc.lo[0] = beg;
-    for (int c = 1; c < N_CLASSES; ++c) {
-        const int32_t target = cb.first[c];
-        int32_t lo = rc.lo[c - 1], hi = end;
-        while (lo < hi) {
-            const int32_t mid = lo + ((hi - lo) >> 1);
-            if (colidx[mid] < target) lo = mid + 1; else hi = mid;
-        }
-        rc.lo[c] = lo;
-    }
-    rc.lo[N_CLASSES] = end;
-    return rc;
+    return d <= TINY_ROW ? ROW_TINY : d <= item_max ? ROW_GROUP : d <= PART_ROW ? ROW_WAVE : ROW_LONG;
 }
+
+// Thread p handles the row at position p of the schedule (order[p], or p itself in natural order), so that the items
+// come out in schedule order.  FILL = false: rows of every kind per workgroup, counts[kind * n_groups + workgroup];
+// FILL = true, with the scan of those counts: the items of the whole rows (wavefront items, then lane-group items)
+// and the list of the long rows, whichever is asked for.
+template <bool FILL>
+__global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ order,
+                                                         int64_t n, int32_t item_max, int32_t *__restrict__ counts, int64_t n_groups,
+                                                         Segment *__restrict__ items, int32_t *__restrict__ long_rows)
+{
+    __shared__ int32_t per_wave[4][3];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t p = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    int kind = ROW_TINY;
+    int32_t row = 0, beg = 0, end = 0;
+    if (p < n) {
+        row = order ? order[p] : (int32_t)p;
+        beg = rowptr[row];
+        end = rowptr[row + 1];
+        kind = row_kind(end - beg, item_max);
+    }
+    int32_t rank = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const unsigned long long bits = __ballot(kind == k);
+        if (kind == k) rank = __popcll(bits & ((1ull << lane) - 1ull));
+        if (lane == 0) per_wave[wave][k] = __popcll(bits);
+    }
+    __syncthreads();
+    if (!FILL) {
+        if (threadIdx.x < 3)
+            counts[threadIdx.x * n_groups + blockIdx.x] = per_wave[0][threadIdx.x] + per_wave[1][threadIdx.x] +
+                                                          per_wave[2][threadIdx.x] + per_wave[3][threadIdx.x];
+        return;
+    }
+    if (kind == ROW_TINY) return;
+    for (int w = 0; w < wave; ++w) rank += per_wave[w][kind];
+    const int32_t at = counts[kind * n_groups + blockIdx.x] + rank; // the scan ran over the three kinds back to back
+    if (kind == ROW_LONG) {
+        if (long_rows) long_rows[at - counts[ROW_LONG * n_groups]] = row;
+    } else if (items) {
+        Segment sg;
+        sg.row = row; sg.beg = beg; sg.end = end; sg.dst = row;
+        items[at] = sg;
+    }
+}
+
+// Counters for the host: rows of every kind; the column class boundaries stay on the device.
+__global__ void sched_summary_kernel(const int32_t *__restrict__ counts, int64_t n_groups, const int32_t *__restrict__ colptr,
+                                     int64_t n, int32_t *__restrict__ summary, ClassBounds *__restrict__ cb)
+{
+    const int t = threadIdx.x;
+    if (t < 3) summary[t] = counts[(t + 1) * n_groups] - counts[t * n_groups];
+    if (t <= N_CLASSES) cb->first[t] = class_bound(colptr, n, t);
+}
+
+// ---- long rows: cut by column class ------------------------------------------------------
+// Tables: 2c = wavefront pieces of class c, 2c + 1 = lane-group pieces of class c, then partial-sum slots and rows with
+// several items.  cnt[table * (n_long + 1) + i] for the i-th long row.
+constexpr int T_SLOT = 2 * N_CLASSES, T_FIX = T_SLOT + 1, N_TABLES = T_FIX + 1;
 
 __device__ inline int pieces_of(int32_t len) { return (len + SEG_NNZ - 1) / SEG_NNZ; }
 
-// The items of one row, in (class, piece) order.  F is called as f(table, beg, end).
+// The pieces of one long row, in (class, piece) order: f(table, beg, end).  Per row: the entries of column class c are
+// [lower_bound(first[c]), lower_bound(first[c+1])).  Returns how many.
 template <class F>
-__device__ inline int for_each_item(const int32_t *__restrict__ colidx, int32_t beg, int32_t end,
-                                    const ClassBounds &cb, int32_t part_row, int32_t item_max, F f)
+__device__ inline int for_each_piece(const int32_t *__restrict__ colidx, int32_t beg, int32_t end, const ClassBounds &cb, int32_t item_max, F f)
 {
-    const int32_t d = end - beg;
     int total = 0;
-    if (d <= TINY_ROW) return 0;
-    if (d <= item_max) {
-        f(2 * N_CLASSES + 1, beg, end);
-        return 1;
-    }
-    if (d <= part_row) {
-        const int s = pieces_of(d);
-        const int32_t piece = (d + s - 1) / s; // equal cuts, the last one takes the remainder
-        for (int j = 0; j < s; ++j) f(2 * N_CLASSES, beg + j * piece, min(end, beg + (j + 1) * piece));
-        return s;
-    }
-    const RowCut rc = cut_row(colidx, beg, end, cb);
+    int32_t b = beg;
     for (int c = 0; c < N_CLASSES; ++c) {
-        const int32_t b = rc.lo[c], e = rc.lo[c + 1], len = e - b;
-        if (len <= 0) continue;
-        if (len <= item_max) {
+        int32_t e = end;
+        if (c + 1 < N_CLASSES) {
+            const int32_t target = cb.first[c + 1];
+            int32_t lo = b;
+            while (lo < e) {
+                const int32_t mid = lo + ((e - lo) >> 1);
+                if (colidx[mid] < target) lo = mid + 1; else e = mid;
+            }
+        }
+        const int32_t len = e - b;
+        if (len > 0 && len <= item_max) {
             f(2 * c + 1, b, e);
             ++total;
-        } else {
+        } else if (len > 0) {
             const int s = pieces_of(len);
-            const int32_t piece = (len + s - 1) / s;
+            const int32_t piece = (len + s - 1) / s; // equal cuts, the last one takes the remainder
             for (int j = 0; j < s; ++j) f(2 * c, b + j * piece, min(e, b + (j + 1) * piece));
             total += s;
         }
+        b = e;
     }
     return total;
 }
 
-// Thread p handles the row at position p of the schedule (order[p], or p itself in natural order); all
-// per-row tables are indexed by position, so the scans below lay the items out in schedule order.
-__global__ void sched_count_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx, int64_t n,
-                                   const int32_t *__restrict__ order,
-                                   const ClassBounds cb, int32_t part_row, int32_t item_max, int32_t *__restrict__ cnt,
-                                   int32_t *__restrict__ c_slot, int32_t *__restrict__ c_fix)
+__global__ void long_count_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+                                  const int32_t *__restrict__ long_rows, int64_t n_long, const ClassBounds *__restrict__ cb,
+                                  int32_t item_max, int32_t *__restrict__ cnt)
 {
-    const int64_t p = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (p > n) return;
-    const int64_t stride = n + 1;
-    int32_t per[MAX_TABLES];
-    for (int t = 0; t < MAX_TABLES; ++t) per[t] = 0;
+    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (i > n_long) return;
+    const int64_t stride = n_long + 1;
+    int32_t per[2 * N_CLASSES];
+#pragma unroll
+    for (int t = 0; t < 2 * N_CLASSES; ++t) per[t] = 0;
     int total = 0;
-    if (p < n) {
-        const int64_t r = order ? order[p] : p;
-        total = for_each_item(colidx, rowptr[r], rowptr[r + 1], cb, part_row, item_max,
-                              [&](int t, int32_t, int32_t) { per[t] += 1; });
+    if (i < n_long) {
+        const int32_t r = long_rows[i];
+        total = for_each_piece(colidx, rowptr[r], rowptr[r + 1], *cb, item_max, [&](int t, int32_t, int32_t) {
+#pragma unroll
+            for (int q = 0; q < 2 * N_CLASSES; ++q) per[q] += q == t ? 1 : 0;
+        });
     }
-    for (int t = 0; t < 2 * N_CLASSES + 2; ++t) cnt[t * stride + p] = per[t];
-    c_slot[p] = total > 1 ? total : 0;
-    c_fix[p] = total > 1 ? 1 : 0;
+#pragma unroll
+    for (int t = 0; t < 2 * N_CLASSES; ++t) cnt[t * stride + i] = per[t];
+    cnt[T_SLOT * stride + i] = total > 1 ? total : 0;
+    cnt[T_FIX * stride + i] = total > 1 ? 1 : 0;
 }
 
-__global__ void sched_fill_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx, int64_t n,
-                                  const int32_t *__restrict__ order,
-                                  const ClassBounds cb, int32_t part_row, int32_t item_max, const int32_t *__restrict__ off,
-                                  const int32_t *__restrict__ o_slot, const int32_t *__restrict__ o_fix,
-                                  Segment *__restrict__ items, FixRow *__restrict__ fix)
+// starts[t] = first element of table t in the scan over all tables, starts[N_TABLES] = the total
+__global__ void long_starts_kernel(const int32_t *__restrict__ off, const int32_t *__restrict__ cnt, int64_t stride, int32_t *__restrict__ starts)
 {
-    const int64_t p = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (p >= n) return;
-    const int64_t r = order ? order[p] : p;
-    const int64_t stride = n + 1;
-    const int32_t beg = rowptr[r], end = rowptr[r + 1];
-    if (end - beg <= TINY_ROW) return;
-    // first pass: how many items (decides whether they write the row or partial slots)
-    const int total = for_each_item(colidx, beg, end, cb, part_row, item_max, [](int, int32_t, int32_t) {});
-    int32_t used[MAX_TABLES];
-    for (int t = 0; t < MAX_TABLES; ++t) used[t] = 0;
-    int slot = o_slot[p]; // slots are handed out in (class, piece) order
-    for_each_item(colidx, beg, end, cb, part_row, item_max, [&](int t, int32_t b, int32_t e) {
+    const int t = threadIdx.x;
+    if (t < N_TABLES) starts[t] = off[t * stride];
+    if (t == N_TABLES) starts[t] = off[N_TABLES * stride - 1] + cnt[N_TABLES * stride - 1];
+}
+
+__global__ void long_fill_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+                                 const int32_t *__restrict__ long_rows, int64_t n_long, const ClassBounds *__restrict__ cb,
+                                 int32_t item_max, const int32_t *__restrict__ off, Segment *__restrict__ items, FixRow *__restrict__ fix)
+{
+    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (i >= n_long) return;
+    const int64_t stride = n_long + 1;
+    const int32_t r = long_rows[i], beg = rowptr[r], end = rowptr[r + 1];
+    const int32_t *slots = off + T_SLOT * stride, *fixes = off + T_FIX * stride;
+    const int32_t slot0 = slots[i] - slots[0], n_slots = slots[i + 1] - slots[i];
+    int slot = slot0, last = -1, used = 0; // slots are handed out in (class, piece) order, a table's pieces are adjacent
+    for_each_piece(colidx, beg, end, *cb, item_max, [&](int t, int32_t b, int32_t e) {
+        used = t == last ? used + 1 : 0;
+        last = t;
         Segment sg;
-        sg.row = (int32_t)r;
+        sg.row = r;
         sg.beg = b;
         sg.end = e;
-        sg.dst = total == 1 ? (int32_t)r : -(slot + 1);
-        items[off[t * stride + p] + used[t]] = sg;
-        used[t] += 1;
+        sg.dst = n_slots == 0 ? r : -(slot + 1);
+        items[off[t * stride + i] + used] = sg;
         ++slot;
     });
-    if (total > 1) {
+    if (n_slots > 0) {
         FixRow f;
-        f.row = (int32_t)r;
-        f.slot_beg = o_slot[p];
-        f.slot_end = o_slot[p] + total;
+        f.row = r;
+        f.slot_beg = slot0;
+        f.slot_end = slot0 + n_slots;
         f.pad = 0;
-        fix[o_fix[p]] = f;
+        fix[fixes[i] - fixes[0]] = f;
     }
 }
 
-int scan_i32(const int32_t *in, int32_t *out, int64_t count, hipStream_t stream)
+// ---- host side ---------------------------------------------------------------------------
+int scan_i32(const int32_t *in, int32_t *out, int64_t count, Arena &ws, hipStream_t stream)
 {
     size_t bytes = 0;
     SG_HIP(rocprim::exclusive_scan(nullptr, bytes, in, out, (int32_t)0, (size_t)count, rocprim::plus<int32_t>(), stream));
-    DevBuf tmp;
-    if (int rc = tmp.alloc(bytes)) return rc;
-    SG_HIP(rocprim::exclusive_scan(tmp.p, bytes, in, out, (int32_t)0, (size_t)count, rocprim::plus<int32_t>(), stream));
-    SG_HIP(hipStreamSynchronize(stream));
+    const size_t mark = ws.used;
+    void *tmp = nullptr;
+    if (int rc = ws.take(bytes, &tmp)) return rc;
+    SG_HIP(rocprim::exclusive_scan(tmp, bytes, in, out, (int32_t)0, (size_t)count, rocprim::plus<int32_t>(), stream));
+    ws.used = mark; // later users are ordered behind the scan on the stream
     return SLICEGCN_OK;
 }
+size_t scan_bytes(int64_t count)
+{
+    size_t bytes = 0;
+    (void)rocprim::exclusive_scan(nullptr, bytes, (const int32_t *)nullptr, (int32_t *)nullptr, (int32_t)0, (size_t)count, rocprim::plus<int32_t>(), (hipStream_t)0);
+    return Arena::rounded(bytes);
+}
 
-int sort_keys(const uint64_t *in, uint64_t *out, int64_t count, unsigned end_bit, hipStream_t stream)
+template <class K>
+int sort_keys(const K *in, K *out, int64_t count, unsigned end_bit, Arena &ws, hipStream_t stream)
 {
     size_t bytes = 0;
     SG_HIP(rocprim::radix_sort_keys(nullptr, bytes, in, out, (size_t)count, 0u, end_bit, stream));
-    DevBuf tmp;
-    if (int rc = tmp.alloc(bytes)) return rc;
-    SG_HIP(rocprim::radix_sort_keys(tmp.p, bytes, in, out, (size_t)count, 0u, end_bit, stream));
+    const size_t mark = ws.used;
+    void *tmp = nullptr;
+    if (int rc = ws.take(bytes, &tmp)) return rc;
+    SG_HIP(rocprim::radix_sort_keys(tmp, bytes, in, out, (size_t)count, 0u, end_bit, stream));
+    ws.used = mark;
+    return SLICEGCN_OK;
+}
+template <class K>
+size_t sort_bytes(int64_t count, unsigned end_bit)
+{
+    size_t bytes = 0;
+    (void)rocprim::radix_sort_keys(nullptr, bytes, (const K *)nullptr, (K *)nullptr, (size_t)count, 0u, end_bit, (hipStream_t)0);
+    return Arena::rounded(bytes);
+}
+
+inline unsigned bits_for(uint64_t v)
+{
+    unsigned b = 1;
+    while ((v >> b) != 0) ++b;
+    return b;
+}
+
+struct KeyPlan {
+    int64_t n_keys;
+    unsigned col_bits, row_bits; // columns 0 .. n - 1, rows 0 .. n (the sentinel)
+    bool narrow;                 // 32-bit keys
+    size_t key_bytes() const { return narrow ? 4 : 8; }
+};
+KeyPlan key_plan(int64_t n_edges, int64_t n, uint32_t flags)
+{
+    KeyPlan k;
+    k.n_keys = n_edges * ((flags & SLICEGCN_SYMMETRIZE) ? 2 : 1) + ((flags & SLICEGCN_ADD_SELF_LOOPS) ? n : 0);
+    k.col_bits = bits_for((uint64_t)(n - 1));
+    k.row_bits = bits_for((uint64_t)n);
+    k.narrow = k.col_bits + k.row_bits <= 32;
+    return k;
+}
+
+size_t sched_bytes(int64_t n, int64_t n_keys)
+{
+    const int64_t groups = 3 * (int64_t)blocks_for(n) + 1, n_long = n_keys / PART_ROW < n ? n_keys / PART_ROW : n;
+    const int64_t tables = N_TABLES * (n_long + 1);
+    const size_t a = scan_bytes(groups), b = scan_bytes(tables);
+    return 2 * Arena::rounded((size_t)groups * 4) + Arena::rounded((size_t)n_long * 4) + 2 * Arena::rounded((size_t)tables * 4) +
+           Arena::rounded(sizeof(ClassBounds)) + (a > b ? a : b);
+}
+
+int read_counters(const int32_t *from, int32_t *to, int count, hipStream_t stream)
+{
+    SG_HIP(hipMemcpyAsync(to, from, (size_t)count * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
     SG_HIP(hipStreamSynchronize(stream));
     return SLICEGCN_OK;
 }
 
-// rowptr / colidx / vals of the pattern whose sorted distinct keys are given
-int pattern_from_keys(const uint64_t *keys, int64_t nnz, int64_t n, const float *dinv, Csr &m, hipStream_t stream)
-{
-    DevBuf col, val;
-    if (int rc = col.alloc((size_t)nnz * sizeof(int32_t))) return rc;
-    if (int rc = val.alloc((size_t)nnz * sizeof(float))) return rc;
-    if (nnz > 0) {
-        entries_kernel<<<blocks_for(nnz), TPB, 0, stream>>>(keys, nnz, dinv, col.as<int32_t>(), val.as<float>());
-        SG_LAUNCH_CHECK();
-    }
-    m.colidx = col.release<int32_t>();
-    m.vals = val.release<float>();
-    return SLICEGCN_OK;
-}
-
-} // namespace
-
-static void free_schedule(Schedule &sc)
-{
-    (void)hipFree(sc.items);
-    (void)hipFree(sc.fix);
-    sc = Schedule();
-}
-
-void free_csr(Csr &m, bool owns_pattern)
-{
-    if (owns_pattern) {
-        (void)hipFree(m.rowptr);
-        (void)hipFree(m.colidx);
-        (void)hipFree(m.vals);
-    }
-    free_schedule(m.sched);
-    m = Csr();
-}
-
-int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, const int32_t *order, uint32_t flags,
+// colptr: row pointer of the transposed pattern.  counters: at least N_TABLES + 1 device words.
+int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint32_t flags, Keep &keep, Arena ws, int32_t *counters,
                    Schedule &out, hipStream_t stream)
 {
+    const int64_t n = g->n, nnz = g->nnz;
     out = Schedule();
     // entries (8 bytes each) plus one 128-byte operand row per node against the 256 MB last-level cache
     const bool resident = nnz * 8 + n * 128 <= ((int64_t)256 << 20);
@@ -321,76 +432,204 @@ int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, 
     if (flags & SLICEGCN_SCHED_SHORT_ITEMS) item_max = ITEM_SHORT;
     if (flags & SLICEGCN_SCHED_LONG_ITEMS) item_max = ITEM_LONG;
     out.item_max = item_max;
-    const int n_tables = 2 * N_CLASSES + 2;
-    const size_t stride = (size_t)(n + 1);
-    const size_t n_cnt = (size_t)n_tables * stride;
-    SG_REQUIRE(n_cnt <= (size_t)INT32_MAX, SLICEGCN_ERANGE, "build_norm_csr: schedule tables exceed int32 indexing");
-    DevBuf cnt, off, aux;
-    if (int rc = cnt.alloc(n_cnt * sizeof(int32_t))) return rc;
-    if (int rc = off.alloc(n_cnt * sizeof(int32_t))) return rc;
-    if (int rc = aux.alloc((4 * stride + 16) * sizeof(int32_t))) return rc; // slot counts, fix counts, their scans, class bounds
-    int32_t *c = cnt.as<int32_t>(), *o = off.as<int32_t>(), *x = aux.as<int32_t>();
-    ClassBounds cb;
-    class_bounds_kernel<<<1, 64, 0, stream>>>(colptr, n, x + 4 * stride);
+    const int64_t n_groups = blocks_for(n);
+    int32_t *counts = nullptr, *offs = nullptr;
+    ClassBounds *cb = nullptr;
+    if (int rc = ws.take((size_t)(3 * n_groups + 1) * 4, &counts)) return rc;
+    if (int rc = ws.take((size_t)(3 * n_groups + 1) * 4, &offs)) return rc;
+    if (int rc = ws.take(sizeof(ClassBounds), &cb)) return rc;
+    sched_rows_kernel<false><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, counts, n_groups, nullptr, nullptr);
     SG_LAUNCH_CHECK();
-    SG_HIP(hipMemcpyAsync(cb.first, x + 4 * stride, sizeof(cb.first), hipMemcpyDeviceToHost, stream));
-    SG_HIP(hipStreamSynchronize(stream));
-    const int32_t part_row = PART_ROW;
-    sched_count_kernel<<<blocks_for(n + 1), TPB, 0, stream>>>(m.rowptr, m.colidx, n, order, cb, part_row, item_max, c, x, x + stride);
+    if (int rc = scan_i32(counts, offs, 3 * n_groups + 1, ws, stream)) return rc; // the last element is only written
+    sched_summary_kernel<<<1, 64, 0, stream>>>(offs, n_groups, colptr, n, counters, cb);
     SG_LAUNCH_CHECK();
-    if (int rc = scan_i32(c, o, (int64_t)n_cnt, stream)) return rc;
-    if (int rc = scan_i32(x, x + 2 * stride, n + 1, stream)) return rc;
-    if (int rc = scan_i32(x + stride, x + 3 * stride, n + 1, stream)) return rc;
-    // the scan runs over all tables back to back: table t starts at o[t * stride]
-    std::vector<int32_t> starts(n_tables + 1);
-    for (int t = 0; t < n_tables; ++t)
-        SG_HIP(hipMemcpy(&starts[t], o + (size_t)t * stride, sizeof(int32_t), hipMemcpyDeviceToHost));
-    int32_t last_off = 0, last_cnt = 0, n_slots = 0, n_fix = 0;
-    SG_HIP(hipMemcpy(&last_off, o + n_cnt - 1, sizeof(int32_t), hipMemcpyDeviceToHost));
-    SG_HIP(hipMemcpy(&last_cnt, c + n_cnt - 1, sizeof(int32_t), hipMemcpyDeviceToHost));
-    SG_HIP(hipMemcpy(&n_slots, x + 2 * stride + n, sizeof(int32_t), hipMemcpyDeviceToHost));
-    SG_HIP(hipMemcpy(&n_fix, x + 3 * stride + n, sizeof(int32_t), hipMemcpyDeviceToHost));
-    starts[n_tables] = last_off + last_cnt;
-    for (int cl = 0; cl < N_CLASSES; ++cl) {
-        out.big_off[cl] = starts[2 * cl];
-        out.big_cnt[cl] = starts[2 * cl + 1] - starts[2 * cl];
-        out.small_off[cl] = starts[2 * cl + 1];
-        out.small_cnt[cl] = starts[2 * cl + 2] - starts[2 * cl + 1];
+    int32_t kinds[3];
+    if (int rc = read_counters(counters, kinds, 3, stream)) return rc;
+    const int64_t n_group = kinds[ROW_GROUP], n_wave = kinds[ROW_WAVE], n_long = kinds[ROW_LONG];
+
+    int32_t *long_rows = nullptr, *cnt = nullptr, *off = nullptr;
+    int32_t starts[N_TABLES + 1] = {0};
+    const int64_t stride = n_long + 1;
+    if (n_long > 0) {
+        if (int rc = ws.take((size_t)n_long * 4, &long_rows)) return rc;
+        if (int rc = ws.take((size_t)(N_TABLES * stride) * 4, &cnt)) return rc;
+        if (int rc = ws.take((size_t)(N_TABLES * stride) * 4, &off)) return rc;
+        sched_rows_kernel<true><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, offs, n_groups, nullptr, long_rows);
+        SG_LAUNCH_CHECK();
+        long_count_kernel<<<blocks_for(stride), TPB, 0, stream>>>(m.rowptr, m.colidx, long_rows, n_long, cb, item_max, cnt);
+        SG_LAUNCH_CHECK();
+        if (int rc = scan_i32(cnt, off, N_TABLES * stride, ws, stream)) return rc;
+        long_starts_kernel<<<1, 64, 0, stream>>>(off, cnt, stride, counters);
+        SG_LAUNCH_CHECK();
+        if (int rc = read_counters(counters, starts, N_TABLES + 1, stream)) return rc;
     }
-    out.wbig_off = starts[2 * N_CLASSES];
-    out.wbig_cnt = starts[2 * N_CLASSES + 1] - starts[2 * N_CLASSES];
-    out.wsmall_off = starts[2 * N_CLASSES + 1];
-    out.wsmall_cnt = starts[2 * N_CLASSES + 2] - starts[2 * N_CLASSES + 1];
-    out.n_items = starts[n_tables];
-    out.n_slots = n_slots;
-    out.n_fix = n_fix;
-    DevBuf items, fix;
-    if (int rc = items.alloc((size_t)out.n_items * sizeof(Segment))) return rc;
-    if (int rc = fix.alloc((size_t)out.n_fix * sizeof(FixRow))) return rc;
-    sched_fill_kernel<<<blocks_for(n), TPB, 0, stream>>>(m.rowptr, m.colidx, n, order, cb, part_row, item_max, o, x + 2 * stride,
-                                                         x + 3 * stride, items.as<Segment>(), fix.as<FixRow>());
-    SG_LAUNCH_CHECK();
-    SG_HIP(hipStreamSynchronize(stream));
-    out.items = items.release<Segment>();
-    out.fix = fix.release<FixRow>();
+    // items: whole rows (wavefront, lane-group), then per class its wavefront and its lane-group pieces
+    out.wbig_off = 0;
+    out.wbig_cnt = (int32_t)n_wave;
+    out.wsmall_off = (int32_t)n_wave;
+    out.wsmall_cnt = (int32_t)n_group;
+    const int32_t base = (int32_t)(n_wave + n_group);
+    for (int c = 0; c < N_CLASSES; ++c) {
+        out.big_off[c] = base + starts[2 * c];
+        out.big_cnt[c] = starts[2 * c + 1] - starts[2 * c];
+        out.small_off[c] = base + starts[2 * c + 1];
+        out.small_cnt[c] = starts[2 * c + 2] - starts[2 * c + 1];
+    }
+    out.n_items = base + starts[T_SLOT];
+    out.n_slots = starts[T_FIX] - starts[T_SLOT];
+    out.n_fix = starts[N_TABLES] - starts[T_FIX];
+    const size_t item_bytes = Arena::rounded((size_t)out.n_items * sizeof(Segment));
+    char *block = nullptr;
+    if (int rc = keep.take(item_bytes + (size_t)out.n_fix * sizeof(FixRow), &block)) return rc;
+    out.items = reinterpret_cast<Segment *>(block);
+    out.fix = reinterpret_cast<FixRow *>(block + item_bytes);
+    if (base > 0) {
+        sched_rows_kernel<true><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, offs, n_groups, out.items, nullptr);
+        SG_LAUNCH_CHECK();
+    }
+    if (n_long > 0) {
+        long_fill_kernel<<<blocks_for(n_long), TPB, 0, stream>>>(m.rowptr, m.colidx, long_rows, n_long, cb, item_max, off,
+                                                                out.items + base, out.fix);
+        SG_LAUNCH_CHECK();
+    }
     static const bool verbose = getenv("SLICEGCN_VERBOSE") != nullptr;
     if (verbose) {
-        fprintf(stderr, "[slicegcn] schedule: whole rows %d wavefront + %d lane-group items, %lld rows with "
-                        "several items, %lld partial-sum slots\n", out.wbig_cnt, out.wsmall_cnt,
-                (long long)out.n_fix, (long long)out.n_slots);
-        for (int cl = 0; cl < N_CLASSES; ++cl)
-            fprintf(stderr, "[slicegcn]   class %d: columns [%d, %d), %d wavefront + %d lane-group pieces\n", cl,
-                    cb.first[cl], cb.first[cl + 1], out.big_cnt[cl], out.small_cnt[cl]);
+        fprintf(stderr, "[slicegcn] schedule: whole rows %d wavefront + %d lane-group items, %lld rows with several items, "
+                        "%lld partial-sum slots\n", out.wbig_cnt, out.wsmall_cnt, (long long)out.n_fix, (long long)out.n_slots);
+        for (int c = 0; c < N_CLASSES; ++c)
+            fprintf(stderr, "[slicegcn]   class %d: %d wavefront + %d lane-group pieces\n", c, out.big_cnt[c], out.small_cnt[c]);
     }
     return SLICEGCN_OK;
 }
 
-} // namespace slicegcn
+// Sorted keys (may hold repeats and sentinels) -> m.rowptr, m.colidx, and every entry's row in rowid.  With `pattern` = NULL
+// rowptr is given and the pattern has no repeats; otherwise allocates colidx and vals once the number of entries is known.
+template <class K>
+int csr_from_keys(const K *keys, const KeyPlan &kp, int64_t n_keys, slicegcn_graph *g, Csr &m, bool dense_rows, int32_t *rowid, int32_t *counters,
+                  bool count_known, Keep &keep, Arena ws, hipStream_t stream)
+{
+    const int64_t n = g->n, n_chunks = chunks_of(n_keys);
+    int32_t *chunk = nullptr, *offs = nullptr;
+    if (int rc = ws.take((size_t)(n_chunks + 1) * 4, &chunk)) return rc;
+    if (int rc = ws.take((size_t)(n_chunks + 1) * 4, &offs)) return rc;
+    const unsigned grid = (unsigned)((n_chunks + 3) / 4);
+    if (n_keys > 0) {
+        compact_kernel<K, false><<<grid, 256, 0, stream>>>(keys, n_keys, n, (int)kp.col_bits, chunk, nullptr, nullptr, nullptr);
+        SG_LAUNCH_CHECK();
+        if (int rc = scan_i32(chunk, offs, n_chunks + 1, ws, stream)) return rc; // the last element is only written: the total
+    }
+    if (!count_known) {
+        int32_t h[2] = {0, 0};
+        if (n_keys > 0) {
+            SG_HIP(hipMemcpyAsync(h, counters, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+            SG_HIP(hipMemcpyAsync(h + 1, offs + n_chunks, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+            SG_HIP(hipStreamSynchronize(stream));
+        }
+        SG_REQUIRE(h[0] == 0, SLICEGCN_ERANGE, "build_norm_csr: %d edge(s) name a node outside [0, %lld)", h[0], (long long)n);
+        g->nnz = h[1];
+    }
+    const size_t col_bytes = Arena::rounded((size_t)g->nnz * 4);
+    char *block = nullptr;
+    if (int rc = keep.take(2 * col_bytes, &block)) return rc;
+    m.colidx = reinterpret_cast<int32_t *>(block);
+    m.vals = reinterpret_cast<float *>(block + col_bytes);
+    if (n_keys > 0) {
+        compact_kernel<K, true><<<grid, 256, 0, stream>>>(keys, n_keys, n, (int)kp.col_bits, offs, m.colidx, rowid, dense_rows ? m.rowptr : nullptr);
+        SG_LAUNCH_CHECK();
+    }
+    if (!dense_rows) {
+        rowptr_kernel<<<blocks_for(n + 1), TPB, 0, stream>>>(rowid, g->nnz, n, m.rowptr);
+        SG_LAUNCH_CHECK();
+    }
+    return SLICEGCN_OK;
+}
 
-using namespace slicegcn;
+int launch_vals(const int32_t *rowid, const slicegcn_graph *g, const Csr &m, hipStream_t stream)
+{
+    if (g->nnz == 0) return SLICEGCN_OK;
+    vals_kernel<<<blocks_for((g->nnz + 3) / 4), TPB, 0, stream>>>(rowid, m.colidx, g->nnz, g->dinv, m.vals);
+    SG_LAUNCH_CHECK();
+    return SLICEGCN_OK;
+}
 
-extern "C" int slicegcn_build_norm_csr(const int64_t *src, const int64_t *dst, int64_t n_edges,
-                                       int64_t n_nodes, uint32_t flags, void *stream_, slicegcn_graph **out)
+template <class K>
+int build_from_edges(const int64_t *src, const int64_t *dst, int64_t n_edges, uint32_t flags, const KeyPlan &kp, slicegcn_graph *g,
+                     Keep &keep, Arena ws, hipStream_t stream)
+{
+    const int64_t n = g->n;
+    const int sym = (flags & SLICEGCN_SYMMETRIZE) != 0, loops = (flags & SLICEGCN_ADD_SELF_LOOPS) != 0;
+    const unsigned end_bit = kp.col_bits + kp.row_bits;
+    int32_t *counters = nullptr, *rowid = nullptr;
+    K *keys_a = nullptr, *keys_b = nullptr;
+    if (int rc = ws.take(N_COUNTERS * sizeof(int32_t), &counters)) return rc;
+    if (int rc = ws.take((size_t)kp.n_keys * sizeof(K), &keys_a)) return rc;
+    if (int rc = ws.take((size_t)kp.n_keys * sizeof(K), &keys_b)) return rc;
+    if (int rc = ws.take((size_t)kp.n_keys * sizeof(int32_t), &rowid)) return rc;
+    {
+        // rowptr (both directions of a directed pattern), degrees and their roots, row order: one block
+        const size_t a = Arena::rounded((size_t)(n + 1) * 4), b = Arena::rounded((size_t)n * 4);
+        const bool ordered = (flags & (SLICEGCN_REORDER_DEGREE | SLICEGCN_REORDER_BFS)) != 0;
+        char *block = nullptr;
+        if (int rc = keep.take((sym ? 1 : 2) * a + (ordered ? 4 : 3) * b, &block)) return rc;
+        g->deg = reinterpret_cast<int32_t *>(block);
+        g->dinv = reinterpret_cast<float *>(block + b);
+        g->sqrtd = reinterpret_cast<float *>(block + 2 * b);
+        g->fwd.rowptr = reinterpret_cast<int32_t *>(block + 3 * b);
+        if (!sym) g->tr.rowptr = reinterpret_cast<int32_t *>(block + 3 * b + a);
+        if (ordered) g->order = reinterpret_cast<int32_t *>(block + 3 * b + (sym ? 1 : 2) * a);
+    }
+    SG_HIP(hipMemsetAsync(counters, 0, N_COUNTERS * sizeof(int32_t), stream));
+    if (kp.n_keys > 0) {
+        make_keys_kernel<K><<<blocks_for(n_edges + (loops ? n : 0)), TPB, 0, stream>>>(src, dst, n_edges, n, (int)kp.col_bits, sym, loops,
+                                                                                      keys_a, counters);
+        SG_LAUNCH_CHECK();
+        if (int rc = sort_keys(keys_a, keys_b, kp.n_keys, end_bit, ws, stream)) return rc;
+    }
+    if (int rc = csr_from_keys<K>(keys_b, kp, kp.n_keys, g, g->fwd, loops != 0, rowid, counters, false, keep, ws, stream)) return rc;
+    degree_kernel<<<blocks_for(n), TPB, 0, stream>>>(g->fwd.rowptr, n, g->deg, g->dinv, g->sqrtd);
+    SG_LAUNCH_CHECK();
+    if (int rc = launch_vals(rowid, g, g->fwd, stream)) return rc;
+    if (g->order)
+        if (int rc = build_row_order(n, g->fwd.rowptr, g->fwd.colidx, (flags & SLICEGCN_REORDER_BFS) != 0, g->order, ws, counters + 2, stream)) return rc;
+
+    if (sym) {
+        if (int rc = build_schedule(g, g->fwd, g->fwd.rowptr, flags, keep, ws, counters + 2, g->fwd.sched, stream)) return rc;
+        g->tr = g->fwd; // A^ is symmetric: the same arrays serve the transposed product
+    } else {
+        if (g->nnz > 0) {
+            swapped_keys_kernel<K><<<blocks_for(g->nnz), TPB, 0, stream>>>(rowid, g->fwd.colidx, g->nnz, (int)kp.col_bits, keys_a);
+            SG_LAUNCH_CHECK();
+            if (int rc = sort_keys(keys_a, keys_b, g->nnz, end_bit, ws, stream)) return rc;
+        }
+        if (int rc = csr_from_keys<K>(keys_b, kp, g->nnz, g, g->tr, loops != 0, rowid, counters, true, keep, ws, stream)) return rc;
+        if (int rc = launch_vals(rowid, g, g->tr, stream)) return rc;
+        if (int rc = build_schedule(g, g->fwd, g->tr.rowptr, flags, keep, ws, counters + 2, g->fwd.sched, stream)) return rc;
+        if (int rc = build_schedule(g, g->tr, g->fwd.rowptr, flags, keep, ws, counters + 2, g->tr.sched, stream)) return rc;
+    }
+    SG_HIP(hipStreamSynchronize(stream));
+    return SLICEGCN_OK;
+}
+
+size_t build_bytes(int64_t n_edges, int64_t n, uint32_t flags)
+{
+    const KeyPlan kp = key_plan(n_edges, n, flags);
+    const unsigned end_bit = kp.col_bits + kp.row_bits;
+    size_t later = kp.narrow ? sort_bytes<uint32_t>(kp.n_keys, end_bit) : sort_bytes<uint64_t>(kp.n_keys, end_bit);
+    const int64_t chunks = chunks_of(kp.n_keys) + 1;
+    const size_t compact = 2 * Arena::rounded((size_t)chunks * 4) + scan_bytes(chunks);
+    if (compact > later) later = compact;
+    const size_t sched = sched_bytes(n, kp.n_keys);
+    if (sched > later) later = sched;
+    if (flags & (SLICEGCN_REORDER_DEGREE | SLICEGCN_REORDER_BFS)) {
+        const size_t order = row_order_bytes(n);
+        if (order > later) later = order;
+    }
+    return Arena::rounded(N_COUNTERS * sizeof(int32_t)) + 2 * Arena::rounded((size_t)kp.n_keys * kp.key_bytes()) +
+           Arena::rounded((size_t)kp.n_keys * 4) + later;
+}
+
+// Argument checks of both entry points
+int check_build(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_nodes, uint32_t flags, slicegcn_graph **out)
 {
     SG_REQUIRE(out != nullptr, SLICEGCN_EINVAL, "build_norm_csr: out is NULL");
     *out = nullptr;
@@ -405,119 +644,71 @@ extern "C" int slicegcn_build_norm_csr(const int64_t *src, const int64_t *dst, i
     SG_REQUIRE(!((flags & SLICEGCN_SCHED_SHORT_ITEMS) && (flags & SLICEGCN_SCHED_LONG_ITEMS)), SLICEGCN_EINVAL,
                "build_norm_csr: SCHED_SHORT_ITEMS and SCHED_LONG_ITEMS exclude each other");
     SG_REQUIRE(n_nodes <= INT32_MAX, SLICEGCN_ERANGE, "build_norm_csr: n_nodes exceeds int32");
-    const int sym = (flags & SLICEGCN_SYMMETRIZE) != 0, loops = (flags & SLICEGCN_ADD_SELF_LOOPS) != 0;
     SG_REQUIRE(n_edges <= (int64_t)INT32_MAX, SLICEGCN_ERANGE, "build_norm_csr: n_edges exceeds int32");
-    const int64_t n_keys = n_edges * (sym ? 2 : 1) + (loops ? n_nodes : 0);
+    const int64_t n_keys = key_plan(n_edges, n_nodes, flags).n_keys;
     SG_REQUIRE(n_keys <= (int64_t)INT32_MAX, SLICEGCN_ERANGE,
                "build_norm_csr: %lld candidate entries exceed int32 indexing", (long long)n_keys);
+    return SLICEGCN_OK;
+}
+
+} // namespace
+
+} // namespace slicegcn
+
+using namespace slicegcn;
+
+extern "C" size_t slicegcn_build_workspace_bytes(int64_t n_edges, int64_t n_nodes, uint32_t flags)
+{
+    if (n_nodes < 1 || n_nodes > INT32_MAX || n_edges < 0 || n_edges > INT32_MAX) return 0;
+    return build_bytes(n_edges, n_nodes, flags);
+}
+
+extern "C" int slicegcn_build_norm_csr_with(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_nodes, uint32_t flags,
+                                            const slicegcn_allocator *allocator, void *ws, size_t ws_bytes, void *stream_,
+                                            slicegcn_graph **out)
+{
+    if (int rc = check_build(src, dst, n_edges, n_nodes, flags, out)) return rc;
+    SG_REQUIRE(allocator == nullptr || allocator->alloc != nullptr, SLICEGCN_EINVAL, "build_norm_csr: allocator without a function");
+    SG_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL, "build_norm_csr: workspace not 256-byte aligned");
+    const size_t need = build_bytes(n_edges, n_nodes, flags);
+    SG_REQUIRE(ws == nullptr || ws_bytes >= need, SLICEGCN_EWORKSPACE, "build_norm_csr: workspace of %zu bytes, %zu needed", ws_bytes, need);
     hipStream_t stream = as_stream(stream_);
+    const KeyPlan kp = key_plan(n_edges, n_nodes, flags);
 
     slicegcn_graph *g = new (std::nothrow) slicegcn_graph();
     SG_REQUIRE(g != nullptr, SLICEGCN_ENOMEM, "build_norm_csr: host allocation failed");
     struct Guard { // destroys the half-built handle on any early return
         slicegcn_graph *g;
-        ~Guard() { if (g) slicegcn_graph_destroy(g); }
-    } guard{g};
+        void *own_ws;
+        ~Guard() { (void)hipFree(own_ws); if (g) slicegcn_graph_destroy(g); }
+    } guard{g, nullptr};
     g->n = n_nodes;
-    g->symmetric = sym;
+    g->symmetric = (flags & SLICEGCN_SYMMETRIZE) != 0;
     SG_HIP(hipGetDevice(&g->device));
-
-    DevBuf keys_a, keys_b, counters;
-    if (int rc = keys_a.alloc((size_t)n_keys * sizeof(uint64_t))) return rc;
-    if (int rc = keys_b.alloc((size_t)n_keys * sizeof(uint64_t))) return rc;
-    if (int rc = counters.alloc(64)) return rc;
-    SG_HIP(hipMemsetAsync(counters.p, 0, 64, stream));
-    int *d_bad = counters.as<int>();
-    size_t *d_count = reinterpret_cast<size_t *>(counters.as<char>() + 16);
-
-    int64_t nnz = 0;
-    if (n_keys > 0) {
-        make_keys_kernel<<<blocks_for(n_edges + (loops ? n_nodes : 0)), TPB, 0, stream>>>(
-            src, dst, n_edges, n_nodes, sym, loops, keys_a.as<uint64_t>(), d_bad);
-        SG_LAUNCH_CHECK();
-        int h_bad = 0;
-        SG_HIP(hipMemcpyAsync(&h_bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, stream));
-        SG_HIP(hipStreamSynchronize(stream));
-        SG_REQUIRE(h_bad == 0, SLICEGCN_ERANGE, "build_norm_csr: %d edge(s) name a node outside [0, %lld)", h_bad,
-                   (long long)n_nodes);
-
-        unsigned row_bits = 1;
-        while (((uint64_t)n_nodes >> row_bits) != 0) ++row_bits; // bits needed for the value n_nodes (sentinel row)
-        if (int rc = sort_keys(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), n_keys, 32 + row_bits, stream)) return rc;
-
-        size_t bytes = 0;
-        SG_HIP(rocprim::unique(nullptr, bytes, keys_b.as<uint64_t>(), keys_a.as<uint64_t>(), d_count, (size_t)n_keys,
-                               rocprim::equal_to<uint64_t>(), stream));
-        {
-            DevBuf tmp;
-            if (int rc = tmp.alloc(bytes)) return rc;
-            SG_HIP(rocprim::unique(tmp.p, bytes, keys_b.as<uint64_t>(), keys_a.as<uint64_t>(), d_count, (size_t)n_keys,
-                                   rocprim::equal_to<uint64_t>(), stream));
-            SG_HIP(hipStreamSynchronize(stream));
-        }
-        size_t h_count = 0;
-        SG_HIP(hipMemcpy(&h_count, d_count, sizeof(size_t), hipMemcpyDeviceToHost));
-        nnz = (int64_t)h_count;
-        if (nnz > 0) { // drop the sentinel (it is the largest key, so the last distinct one)
-            uint64_t last = 0;
-            SG_HIP(hipMemcpy(&last, keys_a.as<uint64_t>() + (nnz - 1), sizeof(uint64_t), hipMemcpyDeviceToHost));
-            if ((last >> 32) == (uint64_t)n_nodes) --nnz;
-        }
+    if (ws == nullptr) {
+        const hipError_t e = hipMalloc(&guard.own_ws, need);
+        SG_REQUIRE(e == hipSuccess, e == hipErrorOutOfMemory ? SLICEGCN_ENOMEM : SLICEGCN_EHIP, "hipMalloc of %zu bytes failed: %s", need,
+                   hipGetErrorString(e));
+        ws = guard.own_ws;
+        ws_bytes = need;
     }
-    g->nnz = nnz;
-    const uint64_t *uniq = keys_a.as<uint64_t>(); // sorted distinct keys [0, nnz)
-
-    {
-        DevBuf rowptr, deg, dinv, sqrtd;
-        if (int rc = rowptr.alloc((size_t)(n_nodes + 1) * sizeof(int32_t))) return rc;
-        if (int rc = deg.alloc((size_t)n_nodes * sizeof(int32_t))) return rc;
-        if (int rc = dinv.alloc((size_t)n_nodes * sizeof(float))) return rc;
-        if (int rc = sqrtd.alloc((size_t)n_nodes * sizeof(float))) return rc;
-        rowptr_kernel<<<blocks_for(n_nodes + 1), TPB, 0, stream>>>(uniq, nnz, n_nodes, rowptr.as<int32_t>());
-        SG_LAUNCH_CHECK();
-        degree_kernel<<<blocks_for(n_nodes), TPB, 0, stream>>>(rowptr.as<int32_t>(), n_nodes, deg.as<int32_t>(),
-                                                              dinv.as<float>(), sqrtd.as<float>());
-        SG_LAUNCH_CHECK();
-        g->fwd.rowptr = rowptr.release<int32_t>();
-        g->deg = deg.release<int32_t>();
-        g->dinv = dinv.release<float>();
-        g->sqrtd = sqrtd.release<float>();
+    Arena arena{static_cast<char *>(ws), ws_bytes, 0};
+    Keep keep{allocator, g};
+    const int rc = kp.narrow ? build_from_edges<uint32_t>(src, dst, n_edges, flags, kp, g, keep, arena, stream)
+                             : build_from_edges<uint64_t>(src, dst, n_edges, flags, kp, g, keep, arena, stream);
+    if (rc) {
+        (void)hipStreamSynchronize(stream); // nothing may still use the memory given back below
+        return rc;
     }
-    if (int rc = pattern_from_keys(uniq, nnz, n_nodes, g->dinv, g->fwd, stream)) return rc;
-
-    if (flags & (SLICEGCN_REORDER_DEGREE | SLICEGCN_REORDER_BFS))
-        if (int rc = build_row_order(n_nodes, g->fwd.rowptr, g->fwd.colidx, (flags & SLICEGCN_REORDER_BFS) != 0, &g->order, stream)) return rc;
-
-    if (sym) {
-        if (int rc = build_schedule(n_nodes, nnz, g->fwd, g->fwd.rowptr, g->order, flags, g->fwd.sched, stream)) return rc;
-        g->tr = g->fwd; // A^ is symmetric: the same arrays serve the transposed product
-    } else {
-        uint64_t *swapped = keys_b.as<uint64_t>();
-        if (nnz > 0) {
-            swap_keys_kernel<<<blocks_for(nnz), TPB, 0, stream>>>(uniq, nnz, swapped);
-            SG_LAUNCH_CHECK();
-        }
-        DevBuf keys_c;
-        if (int rc = keys_c.alloc((size_t)(nnz > 0 ? nnz : 1) * sizeof(uint64_t))) return rc;
-        unsigned row_bits = 1;
-        while (((uint64_t)n_nodes >> row_bits) != 0) ++row_bits;
-        if (nnz > 0)
-            if (int rc = sort_keys(swapped, keys_c.as<uint64_t>(), nnz, 32 + row_bits, stream)) return rc;
-        DevBuf rowptr;
-        if (int rc = rowptr.alloc((size_t)(n_nodes + 1) * sizeof(int32_t))) return rc;
-        rowptr_kernel<<<blocks_for(n_nodes + 1), TPB, 0, stream>>>(keys_c.as<uint64_t>(), nnz, n_nodes, rowptr.as<int32_t>());
-        SG_LAUNCH_CHECK();
-        g->tr.rowptr = rowptr.release<int32_t>();
-        if (int rc = pattern_from_keys(keys_c.as<uint64_t>(), nnz, n_nodes, g->dinv, g->tr, stream)) return rc;
-        if (int rc = build_schedule(n_nodes, nnz, g->fwd, g->tr.rowptr, g->order, flags, g->fwd.sched, stream)) return rc;
-        if (int rc = build_schedule(n_nodes, nnz, g->tr, g->fwd.rowptr, g->order, flags, g->tr.sched, stream)) return rc;
-        SG_HIP(hipStreamSynchronize(stream));
-    }
-
-    SG_HIP(hipStreamSynchronize(stream));
     guard.g = nullptr;
     *out = g;
     return SLICEGCN_OK;
+}
+
+extern "C" int slicegcn_build_norm_csr(const int64_t *src, const int64_t *dst, int64_t n_edges,
+                                       int64_t n_nodes, uint32_t flags, void *stream, slicegcn_graph **out)
+{
+    return slicegcn_build_norm_csr_with(src, dst, n_edges, n_nodes, flags, nullptr, nullptr, 0, stream, out);
 }
 
 extern "C" int slicegcn_graph_view(const slicegcn_graph *g, slicegcn_csr_view *view)
@@ -538,12 +729,7 @@ extern "C" int slicegcn_graph_view(const slicegcn_graph *g, slicegcn_csr_view *v
 extern "C" int slicegcn_graph_destroy(slicegcn_graph *g)
 {
     if (!g) return SLICEGCN_OK;
-    if (!g->symmetric) free_csr(g->tr, true);
-    free_csr(g->fwd, true);
-    (void)hipFree(g->deg);
-    (void)hipFree(g->dinv);
-    (void)hipFree(g->sqrtd);
-    (void)hipFree(g->order);
+    for (void *p : g->owned) (void)hipFree(p);
     delete g;
     return SLICEGCN_OK;
 }

@@ -6,8 +6,10 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <vector>
 
 #include "slicegcn.h"
+#include "slicegcn_native.h"
 
 namespace slicegcn {
 
@@ -112,6 +114,7 @@ struct slicegcn_graph {
     int32_t *order = nullptr; // order[p] = row at position p of the aggregation's schedule; NULL = natural order
     slicegcn::Csr fwd;  // A^
     slicegcn::Csr tr;   // A^^T (arrays alias fwd when the pattern is symmetric)
+    std::vector<void *> owned; // device blocks to free with the handle (none where the caller's allocator made them)
 };
 
 namespace slicegcn {
@@ -139,12 +142,48 @@ struct ProfScope {
     hipStream_t stream_;
 };
 
-// build_csr.hip
-int build_schedule(int64_t n, int64_t nnz, const Csr &m, const int32_t *colptr, const int32_t *order, uint32_t flags,
-                   Schedule &out, hipStream_t stream);
+// Scratch memory of a graph build, handed out from one workspace.  Passed by value to a phase, it gives back on return
+// what the phase took (phases run in order on one stream).
+struct Arena {
+    char *base;
+    size_t size, used;
+    static size_t rounded(size_t bytes) { return (bytes + 255) / 256 * 256; }
+    template <class T> int take(size_t bytes, T **out)
+    {
+        SG_REQUIRE(used + rounded(bytes) <= size, SLICEGCN_EWORKSPACE, "build_norm_csr: workspace exhausted (%zu of %zu bytes used, %zu wanted)",
+                   used, size, bytes);
+        *out = reinterpret_cast<T *>(base + used);
+        used += rounded(bytes);
+        return SLICEGCN_OK;
+    }
+};
 
-// order.hip: order[p] = id of the row at position p (by degree, or breadth first); *out is a device array the caller frees
-int build_row_order(int64_t n, const int32_t *rowptr, const int32_t *colidx, bool breadth_first, int32_t **out, hipStream_t stream);
-void free_csr(Csr &m, bool owns_pattern);
+// Memory that lives as long as a graph handle: from the caller's allocator, or from the device and owned by the handle.
+struct Keep {
+    const slicegcn_allocator *allocator;
+    slicegcn_graph *g;
+    template <class T> int take(size_t bytes, T **out)
+    {
+        if (bytes == 0) bytes = 256;
+        if (allocator) {
+            *out = static_cast<T *>(allocator->alloc(allocator->ctx, bytes));
+            SG_REQUIRE(*out != nullptr, SLICEGCN_ENOMEM, "build_norm_csr: the caller's allocator gave no %zu bytes", bytes);
+            SG_REQUIRE((reinterpret_cast<uintptr_t>(*out) & 255u) == 0, SLICEGCN_EINVAL, "build_norm_csr: allocation not 256-byte aligned");
+            return SLICEGCN_OK;
+        }
+        void *p = nullptr;
+        const hipError_t e = hipMalloc(&p, bytes);
+        SG_REQUIRE(e == hipSuccess, e == hipErrorOutOfMemory ? SLICEGCN_ENOMEM : SLICEGCN_EHIP, "hipMalloc of %zu bytes failed: %s", bytes,
+                   hipGetErrorString(e));
+        g->owned.push_back(p);
+        *out = static_cast<T *>(p);
+        return SLICEGCN_OK;
+    }
+};
+
+// order.hip: order[p] = id of the row at position p (by degree, or breadth first).  counters: two device words.
+int build_row_order(int64_t n, const int32_t *rowptr, const int32_t *colidx, bool breadth_first, int32_t *order, Arena ws,
+                    int32_t *counters, hipStream_t stream);
+size_t row_order_bytes(int64_t n); // scratch it takes
 
 } // namespace slicegcn
