@@ -85,6 +85,22 @@ class _LayerGrads(ctypes.Structure):
     _fields_ = [("dW_agg", ctypes.c_void_p), ("db", ctypes.c_void_p), ("dW_self", ctypes.c_void_p), ("db_self", ctypes.c_void_p)]
 
 
+class LayerIo(ctypes.Structure):
+    """Pointers of one slice model's layer (``slicegcn_layer_io``)."""
+    _fields_ = [("params", _LayerParams), ("enc", ctypes.c_void_p), ("Hin", ctypes.c_void_p), ("Hout", ctypes.c_void_p),
+                ("Z", ctypes.c_void_p), ("mask", ctypes.c_void_p), ("dHout", ctypes.c_void_p), ("dHin", ctypes.c_void_p),
+                ("grads", _LayerGrads), ("denc", ctypes.c_void_p)]
+
+
+class LayerGroup(ctypes.Structure):
+    """Shape shared by the slices of a group (``slicegcn_layer_group``)."""
+    _fields_ = [("desc", _LayerDesc), ("count", ctypes.c_int32), ("ldi", ctypes.c_int64), ("ldo", ctypes.c_int64),
+                ("ldz", ctypes.c_int64), ("mask_words", ctypes.c_int64), ("ldgo", ctypes.c_int64), ("ldgi", ctypes.c_int64)]
+
+
+MAX_GROUP = 8
+
+
 class _Allocator(ctypes.Structure):
     _fields_ = [("ctx", ctypes.c_void_p), ("alloc", ctypes.c_void_p)]
 
@@ -124,6 +140,12 @@ def lib() -> ctypes.CDLL:
         L.slicegcn_layer_bwd.argtypes = [vp, ctypes.POINTER(_LayerDesc), ctypes.POINTER(_LayerParams), vp, i64,
                                          ctypes.POINTER(_LayerSaved), vp, i64, vp, i64, ctypes.POINTER(_LayerGrads),
                                          vp, sz, vp]
+        L.slicegcn_layers_fwd_workspace_bytes.argtypes = [vp, ctypes.POINTER(_LayerDesc), i32]
+        L.slicegcn_layers_fwd_workspace_bytes.restype = sz
+        L.slicegcn_layers_bwd_workspace_bytes.argtypes = [vp, ctypes.POINTER(_LayerDesc), ctypes.c_int, i32]
+        L.slicegcn_layers_bwd_workspace_bytes.restype = sz
+        for fn in (L.slicegcn_layers_fwd, L.slicegcn_layers_bwd):
+            fn.argtypes = [vp, ctypes.POINTER(LayerGroup), vp, vp, sz, vp]
         L.slicegcn_concat.argtypes = [i32, vp, vp, vp, vp, i64, i64, vp, i64, vp]
         L.slicegcn_concat_bwd_workspace_bytes.argtypes = [i64, i32, vp]
         L.slicegcn_concat_bwd_workspace_bytes.restype = sz
@@ -132,11 +154,14 @@ def lib() -> ctypes.CDLL:
         L.slicegcn_linear_fwd.argtypes = [vp, i64, i64, i32, i32, vp, vp, i32, vp, i64, vp, i64, vp]
         L.slicegcn_linear_bwd_workspace_bytes.argtypes = [i64, i32, i32]
         L.slicegcn_linear_bwd_workspace_bytes.restype = sz
+        L.slicegcn_linear_bwd_full_workspace_bytes.argtypes = [i64, i32, i32]
+        L.slicegcn_linear_bwd_full_workspace_bytes.restype = sz
         L.slicegcn_linear_bwd.argtypes = [vp, i64, i64, i32, i32, vp, i32, vp, i64, vp, i64, vp, i64, vp, vp, vp, sz, vp]
         L.slicegcn_softmax_ce_workspace_bytes.argtypes = [i64]
         L.slicegcn_softmax_ce_workspace_bytes.restype = sz
         L.slicegcn_softmax_ce.argtypes = [vp, i64, i64, i32, vp, vp, vp, i64, vp, sz, vp]
         L.slicegcn_accumulate.argtypes = [vp, i64, vp, i64, i64, i32, vp]
+        L.slicegcn_accumulate_many.argtypes = [vp, i64, vp, i32, i64, i64, i32, vp]
         f64 = ctypes.c_double
         L.slicegcn_adam_step.argtypes = [vp, vp, vp, vp, i64, f64, f64, f64, f64, f64, i32, vp]
         L.slicegcn_cosine_lr.argtypes = [ctypes.c_double, ctypes.c_double, i32, i32]
@@ -156,7 +181,7 @@ def _check(rc: int):
 
 
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _mat(t: torch.Tensor, name: str, dtype=torch.float32):
@@ -433,6 +458,25 @@ def slicegcn_layer_bwd(g: Graph, Hin, W_agg, W_self, Z, mask, dHout, dHin, dW_ag
                                     _stream()))
 
 
+def slicegcn_layers_fwd_workspace_bytes(g: Graph, w_in: int, w_out: int, count: int, flags: int = 0) -> int:
+    desc = _LayerDesc(w_in, w_out, ACT_RELU, flags)
+    return int(lib().slicegcn_layers_fwd_workspace_bytes(g.handle, ctypes.byref(desc), count))
+
+
+def slicegcn_layers_bwd_workspace_bytes(g: Graph, w_in: int, w_out: int, need_dHin: bool, count: int, flags: int = 0) -> int:
+    desc = _LayerDesc(w_in, w_out, ACT_RELU, flags)
+    return int(lib().slicegcn_layers_bwd_workspace_bytes(g.handle, ctypes.byref(desc), int(need_dHin), count))
+
+
+def slicegcn_layers_fwd(g: Graph, group: LayerGroup, io, first: int, ws: torch.Tensor):
+    """Layer forward for ``group.count`` slice models: entries first, first + 1, ... of the LayerIo array ``io``."""
+    _check(lib().slicegcn_layers_fwd(g.handle, ctypes.byref(group), ctypes.byref(io, first * ctypes.sizeof(LayerIo)), *_ws(ws), _stream()))
+
+
+def slicegcn_layers_bwd(g: Graph, group: LayerGroup, io, first: int, ws: torch.Tensor):
+    _check(lib().slicegcn_layers_bwd(g.handle, ctypes.byref(group), ctypes.byref(io, first * ctypes.sizeof(LayerIo)), *_ws(ws), _stream()))
+
+
 def slicegcn_concat(Hs, E, H: torch.Tensor):
     """H[:, off_i : off_i + w_i] = Hs[i] + E[i, :w_i]  (E may be None)."""
     k = len(Hs)
@@ -492,6 +536,11 @@ def slicegcn_linear_bwd_workspace_bytes(n: int, w_in: int, w_out: int) -> int:
     return int(lib().slicegcn_linear_bwd_workspace_bytes(n, w_in, w_out))
 
 
+def slicegcn_linear_bwd_full_workspace_bytes(n: int, w_in: int, w_out: int) -> int:
+    """Workspace with which the reductions of ``slicegcn_linear_bwd`` are split as finely as they gain from."""
+    return int(lib().slicegcn_linear_bwd_full_workspace_bytes(n, w_in, w_out))
+
+
 def slicegcn_linear_bwd(X, W, mask, dY, dX, dW, db, ws, act: int = ACT_NONE):
     """dX = (dY * mask) W^T, dW = X^T (dY * mask), db = colsum(dY * mask); None outputs are skipped."""
     w_in, w_out = int(W.shape[0]), int(W.shape[1])
@@ -513,6 +562,17 @@ def slicegcn_accumulate(dst, src):
     if dst.shape != src.shape:
         raise ValueError("dst and src differ in shape")
     _check(lib().slicegcn_accumulate(pd, ldd, ps, lds, dst.shape[0], dst.shape[1], _stream()))
+    return dst
+
+
+def slicegcn_accumulate_many(dst, srcs):
+    """dst += srcs[0]; dst += srcs[1]; ... in one sweep (equal shapes, one leading dimension for all sources)."""
+    pd, ldd = _mat(dst, "dst")
+    mats = [_mat(t, "src") for t in srcs]
+    if any(t.shape != dst.shape for t in srcs) or any(ld != mats[0][1] for _, ld in mats):
+        raise ValueError("dst and srcs differ in shape or leading dimension")
+    ptrs = (ctypes.c_void_p * len(mats))(*[p for p, _ in mats])
+    _check(lib().slicegcn_accumulate_many(pd, ldd, ctypes.addressof(ptrs), len(mats), mats[0][1], dst.shape[0], dst.shape[1], _stream()))
     return dst
 
 

@@ -119,12 +119,19 @@ struct slicegcn_graph {
 
 namespace slicegcn {
 
-// spmm.hip: Y[:, 0:width] = M X (+ Add), M given by `m`.  Add may alias Y.  ws: 256-byte aligned, at least
-// spmm_workspace_bytes(m, width) bytes (partial sums of rows cut into several items; may be NULL when that is 0).
-int launch_spmm(const slicegcn_graph *g, const Csr &m, const float *X, int64_t ldx, int32_t width,
-                float *Y, int64_t ldy, const float *Add, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream,
-                bool prescaled = false); // prescaled: X rows carry dinv[u] already (the value stream is not read)
-size_t spmm_workspace_bytes(const Csr &m, int32_t width);
+// spmm.hip: Y[:, 0:width] = M X (+ Add) for each of `batch` operands (at most SPMM_BATCH, all with the same leading
+// dimensions), M given by `m`.  Add may alias Y.  ws: 256-byte aligned, at least batch * spmm_workspace_bytes(m, width)
+// bytes (partial sums of rows cut into several items; may be NULL when that is 0).
+// prescaled: X rows carry dinv[u] already (the value stream is not read)
+constexpr int SPMM_BATCH = 8;
+struct SpmmOperands {
+    const float *X;
+    float *Y;
+    const float *Add; // NULL: nothing is added
+};
+int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, int batch, int64_t ldx, int32_t width,
+                int64_t ldy, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream, bool prescaled = false);
+size_t spmm_workspace_bytes(const Csr &m, int32_t width, bool one_pass = false);
 
 // dense.hip: column sums of an n x w matrix: fp32 per block of rows into ws[blocks][w], then
 // out[j] = sum over blocks of ws[b][first + j] in fp64 (ws_row = floats per ws row)

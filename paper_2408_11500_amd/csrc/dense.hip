@@ -23,6 +23,7 @@ struct PairArgs {
     const float *B2;               // W_self (same shape) or NULL
     const float *bias1;            // forward only
     const float *bias2;            // forward only
+    const float *enc = nullptr;    // forward only: second summand of the outer bias (slice encoding)
     float *O1; int64_t ldo1;       // forward: Hout       backward: dZ
     float *O2; int64_t ldo2;       // backward: T (may be NULL)
     uint32_t *mask; int64_t mask_words; // forward: written (act = ReLU); backward: read
@@ -35,6 +36,32 @@ struct PairArgs {
     const float *scale2 = nullptr;   // forward: rows of A2 are multiplied by scale2[row] when read (sqrt(d~): undoes the scaling of Hin)
     const float *scale_o1 = nullptr; // rows of O1 are multiplied by scale_o1[row] (forward: on store; backward: dZ rows, folded into dP)
 };
+
+// The same products for a batch of slice models (equal shapes and leading dimensions): grid row y works on slice y, with
+// the pointers taken from here.  Small graphs need it: their kernels last microseconds and fill a fraction of the chip.
+constexpr int BATCH = SPMM_BATCH;
+constexpr int64_t STRIP64_ROWS = 262144; // from here on layers up to 64 wide take the strip kernel
+struct PairPtrs {
+    const float *A1, *A2, *B1, *B2, *bias1, *bias2, *enc;
+    float *O1, *O2;
+    uint32_t *mask;
+};
+struct PairBatch { PairPtrs p[BATCH]; };
+__device__ inline PairArgs slice_of(const PairArgs &common, const PairBatch &b)
+{
+    PairArgs a = common;
+    const PairPtrs &p = b.p[blockIdx.y];
+    a.A1 = p.A1; a.A2 = p.A2; a.B1 = p.B1; a.B2 = p.B2; a.bias1 = p.bias1; a.bias2 = p.bias2; a.enc = p.enc;
+    a.O1 = p.O1; a.O2 = p.O2; a.mask = p.mask;
+    return a;
+}
+// Biases of output column col: inside the activation, and outside it (the encoding joins the outer one; with a single
+// product there is no outer part and it joins the only one)
+template <bool TWO> __device__ inline float inner_bias(const PairArgs &a, int col)
+{
+    return (a.bias1 ? a.bias1[col] : 0.f) + (!TWO && a.enc ? a.enc[col] : 0.f);
+}
+__device__ inline float outer_bias(const PairArgs &a, int col) { return (a.bias2 ? a.bias2[col] : 0.f) + (a.enc ? a.enc[col] : 0.f); }
 
 __device__ inline void scale4(float4 &v, float s) { v.x *= s; v.y *= s; v.z *= s; v.w *= s; }
 
@@ -65,8 +92,9 @@ __device__ inline float pick(const float4 &v, int i) { return i == 0 ? v.x : i =
 // Workgroups are numbered so that the column tiles of one row tile run back to back on the same
 // XCD (workgroup b goes to XCD b mod 8): the A tile is fetched from HBM once and re-read from L2.
 template <int NT, bool BWD, bool TWO>
-__global__ __launch_bounds__(256) void pair_mfma_kernel(const PairArgs a, int n_col_tiles)
+__global__ __launch_bounds__(256) void pair_mfma_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
 {
+    const PairArgs a = slice_of(common, batch);
     constexpr int BM = 128, KC = 32, AS = KC + 4, BN = NT * 32;
     constexpr int BPT = KC * BN / 256; // B-tile elements per thread and chunk
     __shared__ __attribute__((aligned(16))) float As1[BM][AS];
@@ -194,8 +222,8 @@ __global__ __launch_bounds__(256) void pair_mfma_kernel(const PairArgs a, int n_
     for (int t = 0; t < NT; ++t) {
         const int col = col0 + t * 32 + m;
         const bool col_ok = col < a.Nout;
-        const float bias1 = (!BWD && a.bias1 && col_ok) ? a.bias1[col] : 0.f;
-        const float bias2 = (!BWD && TWO && a.bias2 && col_ok) ? a.bias2[col] : 0.f;
+        const float bias1 = (!BWD && col_ok) ? inner_bias<TWO>(a, col) : 0.f;
+        const float bias2 = (!BWD && TWO && col_ok) ? outer_bias(a, col) : 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int64_t row = row0 + wave * 32 + 8 * (r / 4) + 4 * h + (r % 4);
@@ -227,15 +255,16 @@ __global__ __launch_bounds__(256) void pair_mfma_kernel(const PairArgs a, int n_
 // per row and instruction), so there is no LDS round trip or barrier per row tile and all loads of
 // a tile are in flight at once.
 template <int NT, int KCH, bool BWD> // KCH: number of 32-wide K chunks (1 or 2)
-__global__ __launch_bounds__(256) void pair_mfma_direct_kernel(const PairArgs a)
+__global__ __launch_bounds__(256) void pair_mfma_direct_kernel(const PairArgs common, const PairBatch batch)
 {
+    const PairArgs a = slice_of(common, batch);
     constexpr int BN = NT * 32, KK = KCH * 32;
     __shared__ float Bs1[KK][BN];
     __shared__ float Bs2[KK][BN];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int col0 = blockIdx.y * BN;
+    const int col0 = 0;
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
     const bool vec1 = aligned16(a.A1) && (a.lda1 % 4 == 0);
     const bool vec2 = two && aligned16(a.A2) && (a.lda2 % 4 == 0);
@@ -308,8 +337,8 @@ __global__ __launch_bounds__(256) void pair_mfma_direct_kernel(const PairArgs a)
         for (int t = 0; t < NT; ++t) {
             const int col = col0 + t * 32 + m;
             const bool col_ok = col < a.Nout;
-            const float bias1 = (!BWD && a.bias1 && col_ok) ? a.bias1[col] : 0.f;
-            const float bias2 = (!BWD && two && a.bias2 && col_ok) ? a.bias2[col] : 0.f;
+            const float bias1 = (!BWD && col_ok) ? (two ? inner_bias<true>(a, col) : inner_bias<false>(a, col)) : 0.f;
+            const float bias2 = (!BWD && two && col_ok) ? outer_bias(a, col) : 0.f;
             uint32_t my_word = 0u; // lane L < 32 collects the activation word of strip row L
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -351,8 +380,9 @@ __global__ __launch_bounds__(256) void pair_mfma_direct_kernel(const PairArgs a)
 // product in registers.  No workgroup barrier anywhere: a wavefront only touches its own tile, and
 // its LDS accesses execute in program order.
 template <bool BWD, bool TWO>
-__global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs a)
+__global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common, const PairBatch batch)
 {
+    const PairArgs a = slice_of(common, batch);
     constexpr int ST = 36;
     __shared__ __attribute__((aligned(16))) float T1[4][32][ST];
     __shared__ __attribute__((aligned(16))) float T2[(TWO && !BWD) ? 4 : 1][32][ST];
@@ -380,8 +410,8 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs a)
             b2[q * 4 + i] = w2;
         }
     const bool col_ok = m < a.Nout;
-    const float bias1 = (!BWD && a.bias1 && col_ok) ? a.bias1[m] : 0.f;
-    const float bias2 = (!BWD && TWO && a.bias2 && col_ok) ? a.bias2[m] : 0.f;
+    const float bias1 = (!BWD && col_ok) ? inner_bias<TWO>(a, m) : 0.f;
+    const float bias2 = (!BWD && TWO && col_ok) ? outer_bias(a, m) : 0.f;
 
     const int64_t n_strips = (a.n + 31) / 32;
     const int64_t first = (int64_t)blockIdx.x * 4 + wave, step = (int64_t)gridDim.x * 4;
@@ -514,8 +544,9 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs a)
 // two operand strips of the forward pass go through the wavefront's one tile in turn.  Compiled for
 // two wavefronts per SIMD: one computes while the other moves its strip.
 template <int KC, int NC, bool BWD, bool TWO>
-__global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs a)
+__global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs common, const PairBatch batch)
 {
+    const PairArgs a = slice_of(common, batch);
     constexpr int KW = 32 * KC, NW = 32 * NC;
     constexpr int ST = (KW > NW ? KW : NW) + 4; // tile row stride: 16-byte reads with lane = row stay conflict free
     constexpr int LK = KW / 4, LN = NW / 4;     // lanes per row, operand strips / output strips
@@ -550,8 +581,8 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs a)
 #pragma unroll
     for (int t = 0; t < NC; ++t) {
         const bool ok = 32 * t + m < a.Nout;
-        bias1[t] = (!BWD && a.bias1 && ok) ? a.bias1[32 * t + m] : 0.f;
-        bias2[t] = (!BWD && TWO && a.bias2 && ok) ? a.bias2[32 * t + m] : 0.f;
+        bias1[t] = (!BWD && ok) ? inner_bias<TWO>(a, 32 * t + m) : 0.f;
+        bias2[t] = (!BWD && TWO && ok) ? outer_bias(a, 32 * t + m) : 0.f;
     }
 
     const int64_t n_strips = (a.n + 31) / 32;
@@ -739,82 +770,78 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs a)
 }
 
 template <int KC, int NC, bool BWD>
-void launch_strip64(const PairArgs &a, unsigned gb, hipStream_t stream)
+void launch_strip64(const PairArgs &a, const PairBatch &b, dim3 grid, hipStream_t stream)
 {
-    if (a.A2 != nullptr && a.B2 != nullptr) pair_strip64_kernel<KC, NC, BWD, true><<<gb, 256, 0, stream>>>(a);
-    else pair_strip64_kernel<KC, NC, BWD, false><<<gb, 256, 0, stream>>>(a);
+    if (a.A2 != nullptr && a.B2 != nullptr) pair_strip64_kernel<KC, NC, BWD, true><<<grid, 256, 0, stream>>>(a, b);
+    else pair_strip64_kernel<KC, NC, BWD, false><<<grid, 256, 0, stream>>>(a, b);
 }
 
-template <int NT, bool BWD>
-void launch_direct(const PairArgs &a, dim3 grid, hipStream_t stream)
-{
-    if (a.K <= 32) pair_mfma_direct_kernel<NT, 1, BWD><<<grid, 256, 0, stream>>>(a);
-    else pair_mfma_direct_kernel<NT, 2, BWD><<<grid, 256, 0, stream>>>(a);
-}
-
+// `list`: one entry per slice model of the batch (1 to BATCH, equal but for the pointers)
 template <bool BWD>
-int launch_pair(const PairArgs &a, hipStream_t stream)
+int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
 {
-    const int nt = a.Nout <= 32 ? 1 : a.Nout <= 64 ? 2 : a.Nout <= 96 ? 3 : 4;
-    dim3 grid((unsigned)((a.n + 127) / 128), (unsigned)((a.Nout + nt * 32 - 1) / (nt * 32)));
-    if (a.K <= 32 && a.Nout <= 32) { // narrowest layers: per-wavefront strips, no barriers
-        const int64_t strips = (a.n + 31) / 32;
-        const unsigned gb = (unsigned)((strips + 3) / 4 < 2048 ? (strips + 3) / 4 : 2048);
-        const bool two = a.A2 != nullptr && a.B2 != nullptr;
-        if (two) pair_strip32_kernel<BWD, true><<<gb, 256, 0, stream>>>(a);
-        else pair_strip32_kernel<BWD, false><<<gb, 256, 0, stream>>>(a);
-        SG_LAUNCH_CHECK();
-        return SLICEGCN_OK;
+    const PairArgs &a = list[0];
+    PairBatch b;
+    for (int i = 0; i < BATCH; ++i) {
+        const PairArgs &x = list[i < batch ? i : 0];
+        b.p[i] = PairPtrs{x.A1, x.A2, x.B1, x.B2, x.bias1, x.bias2, x.enc, x.O1, x.O2, x.mask};
     }
-    if (a.K <= 64 && a.Nout <= 64 && a.n >= 262144) { // up to 64 wide: strips, weights in LDS
-        const int64_t strips = (a.n + 31) / 32;
-        // as many workgroups as the chip holds at once (two per CU): each stages the weights once
-        const unsigned gb = (unsigned)((strips + 3) / 4 < 512 ? (strips + 3) / 4 : 512);
-        if (a.K <= 32) launch_strip64<1, 2, BWD>(a, gb, stream);
-        else if (a.Nout <= 32) launch_strip64<2, 1, BWD>(a, gb, stream);
-        else launch_strip64<2, 2, BWD>(a, gb, stream);
-        SG_LAUNCH_CHECK();
-        return SLICEGCN_OK;
-    }
-    if (a.K <= 64 && nt == 1) { // short reduction, one output tile: weights resident in LDS, workgroups walk over row tiles
-        const unsigned tiles = grid.x;
-        grid.x = tiles < 2048u ? tiles : 2048u;
-        switch (nt) {
-        case 1: launch_direct<1, BWD>(a, grid, stream); break;
-        case 2: launch_direct<2, BWD>(a, grid, stream); break;
-        case 3: launch_direct<3, BWD>(a, grid, stream); break;
-        default: launch_direct<4, BWD>(a, grid, stream); break;
-        }
-        SG_LAUNCH_CHECK();
-        return SLICEGCN_OK;
-    }
-    // staged kernel: 1-D grid, 8 row tiles x all column tiles per group of workgroups (see the kernel)
+    const unsigned by = (unsigned)batch;
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
+    const int64_t strips = (a.n + 31) / 32, strip_blocks = (strips + 3) / 4;
+    if (a.K <= 32 && a.Nout <= 32) { // narrowest layers: per-wavefront strips, no barriers
+        const dim3 grid((unsigned)(strip_blocks < 2048 ? strip_blocks : 2048), by);
+        if (two) pair_strip32_kernel<BWD, true><<<grid, 256, 0, stream>>>(a, b);
+        else pair_strip32_kernel<BWD, false><<<grid, 256, 0, stream>>>(a, b);
+        SG_LAUNCH_CHECK();
+        return SLICEGCN_OK;
+    }
+    if (a.K <= 64 && a.Nout <= 64 && a.n >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
+        // as many workgroups as the chip holds at once (two per CU): each stages the weights once
+        const dim3 grid((unsigned)(strip_blocks < 512 ? strip_blocks : 512), by);
+        if (a.K <= 32) launch_strip64<1, 2, BWD>(a, b, grid, stream);
+        else if (a.Nout <= 32) launch_strip64<2, 1, BWD>(a, b, grid, stream);
+        else launch_strip64<2, 2, BWD>(a, b, grid, stream);
+        SG_LAUNCH_CHECK();
+        return SLICEGCN_OK;
+    }
+    const int64_t row_tiles = (a.n + 127) / 128;
+    if (a.K <= 64 && a.Nout <= 32) { // short reduction, one output tile: weights resident in LDS, workgroups walk over row tiles
+        const dim3 grid((unsigned)(row_tiles < 2048 ? row_tiles : 2048), by);
+        if (a.K <= 32) pair_mfma_direct_kernel<1, 1, BWD><<<grid, 256, 0, stream>>>(a, b);
+        else pair_mfma_direct_kernel<1, 2, BWD><<<grid, 256, 0, stream>>>(a, b);
+        SG_LAUNCH_CHECK();
+        return SLICEGCN_OK;
+    }
+    // staged kernel: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     // Column tiles per workgroup: 4 for a single product and 2 for a pair, which keeps two workgroups on a CU (64 and
     // 2 x 32 accumulator registers): the other workgroup's MFMAs fill the barrier waits.  Wider tiles (256 columns,
     // or 128 for a pair) run one workgroup per CU and are 20 % and 16 % slower on 256 -> 256 and 301 -> 128.
+    const int nt = a.Nout <= 32 ? 1 : a.Nout <= 64 ? 2 : a.Nout <= 96 ? 3 : 4;
     const int cap = two ? 2 : 4;
     const int nt2 = nt > cap ? cap : nt;
     const int bn = nt2 * 32;
     const int n_col = (a.Nout + bn - 1) / bn;
-    const int64_t row_tiles = (a.n + 127) / 128;
     const int64_t blocks = (row_tiles + 7) / 8 * 8 * n_col;
     SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
-    const unsigned gb = (unsigned)blocks;
+    const dim3 grid((unsigned)blocks, by);
     if (two) {
-        if (nt2 == 1) pair_mfma_kernel<1, BWD, true><<<gb, 256, 0, stream>>>(a, n_col);
-        else pair_mfma_kernel<2, BWD, true><<<gb, 256, 0, stream>>>(a, n_col);
+        if (nt2 == 1) pair_mfma_kernel<1, BWD, true><<<grid, 256, 0, stream>>>(a, b, n_col);
+        else pair_mfma_kernel<2, BWD, true><<<grid, 256, 0, stream>>>(a, b, n_col);
     } else {
         switch (nt2) {
-        case 1: pair_mfma_kernel<1, BWD, false><<<gb, 256, 0, stream>>>(a, n_col); break;
-        case 2: pair_mfma_kernel<2, BWD, false><<<gb, 256, 0, stream>>>(a, n_col); break;
-        case 3: pair_mfma_kernel<3, BWD, false><<<gb, 256, 0, stream>>>(a, n_col); break;
-        default: pair_mfma_kernel<4, BWD, false><<<gb, 256, 0, stream>>>(a, n_col); break;
+        case 1: pair_mfma_kernel<1, BWD, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 2: pair_mfma_kernel<2, BWD, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 3: pair_mfma_kernel<3, BWD, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        default: pair_mfma_kernel<4, BWD, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
         }
     }
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
 }
+
+template <bool BWD>
+int launch_pair(const PairArgs &a, hipStream_t stream) { return launch_pair<BWD>(&a, 1, stream); }
 
 // ---- weight-gradient reductions over the node axis ----------------------------------------
 constexpr int RED_ROWS = 1024; // rows per block: fp32 chains stay this short
@@ -832,16 +859,32 @@ struct ReduceArgs {
     int32_t stride;                     // 2*w_in*w_out + 2*w_out; compact: w_in*w_out + w_out
     int32_t compact;                    // 1: no self term and no slot for it: [Z^T dP | colsum dP]
     int32_t rows_per_block = RED_ROWS;  // tiled kernels: node rows per workgroup (one partial each)
+    int32_t j_tiles = 1;                // tiled kernels: output tiles along w_out (grid depth = j_tiles x batch)
     const float *hin_scale = nullptr;   // rows of Hin are multiplied by hin_scale[row] when read (Hin stored as D~^-1/2 Hin)
 };
 
-// Partial weight gradients, tiled: grid = (row blocks, w_in tiles, w_out tiles), every workgroup writes its
+struct ReducePtrs {
+    const float *Z, *Hin, *dHout;
+    const uint32_t *mask;
+    float *partial;
+};
+struct ReduceBatch { ReducePtrs p[BATCH]; };
+__device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatch &b, int i)
+{
+    ReduceArgs r = common;
+    const ReducePtrs &p = b.p[i];
+    r.Z = p.Z; r.Hin = p.Hin; r.dHout = p.dHout; r.mask = p.mask; r.partial = p.partial;
+    return r;
+}
+
+// Partial weight gradients, tiled: grid = (row blocks, w_in tiles, slices x w_out tiles), every workgroup writes its
 // tile of the four results [Z^T dP | Hin^T dHout | colsum dP | colsum dHout] of its row block into
 // partial[row block][...].  Per step the workgroup stages 32 rows of the four operand tiles in LDS;
 // wavefront w multiplies rows 8w..8w+7 (the node axis is the MFMA's k axis: A[m][k] = Z[k][m]),
 // and the four wavefronts' accumulators are added in wavefront order at the end.
-__global__ __launch_bounds__(256) void grad_partial_mfma_kernel(const ReduceArgs a)
+__global__ __launch_bounds__(256) void grad_partial_mfma_kernel(const ReduceArgs common, const ReduceBatch batch)
 {
+    const ReduceArgs a = slice_of(common, batch, blockIdx.z / common.j_tiles);
     // one LDS block: the four operand tiles during the row loop, the accumulators of wavefronts 1..3 after it
     constexpr int TILE_FLOATS = RED_RK * RED_TILE;
     __shared__ __attribute__((aligned(16))) float lds[3 * 2 * RED_TILE * RED_TILE];
@@ -853,7 +896,7 @@ __global__ __launch_bounds__(256) void grad_partial_mfma_kernel(const ReduceArgs
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int i_base = blockIdx.y * RED_TILE, j_base = blockIdx.z * RED_TILE;
+    const int i_base = blockIdx.y * RED_TILE, j_base = (blockIdx.z % common.j_tiles) * RED_TILE;
     const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
     const bool self = a.Hin != nullptr;
@@ -956,8 +999,9 @@ __global__ __launch_bounds__(256) void grad_partial_mfma_kernel(const ReduceArgs
 // next strip's loads in flight during the MFMAs), and writes one partial result.  The node axis is the MFMA's k axis (lane (m, h) feeds
 // column m of node row 2s + h).  No workgroup barrier; same output layout as grad_partial_mfma_kernel,
 // one partial per wavefront.
-__global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs a, int64_t n_waves)
+__global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs common, const ReduceBatch batch, int64_t n_waves)
 {
+    const ReduceArgs a = slice_of(common, batch, blockIdx.y);
     __shared__ __attribute__((aligned(16))) float Zs[4][32][32];
     __shared__ __attribute__((aligned(16))) float Hs[4][32][32];
     __shared__ __attribute__((aligned(16))) float Gs[4][32][32];
@@ -1054,8 +1098,11 @@ __global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs a, i
 // leave through the Z and Hin tiles as 16-byte stores.  Partial sums: one per wavefront, layout of
 // grad_partial_mfma_kernel.  `a` carries the input-gradient half: B1 / B2 = W_agg / W_self (ldw), O1 = dZ (rows
 // scaled by scale_o1), O2 = T, K = w_out, Nout = w_in.
-__global__ __launch_bounds__(256, 2) void bwd_strip32_kernel(const ReduceArgs r, const PairArgs a, int64_t n_waves)
+__global__ __launch_bounds__(256, 2) void bwd_strip32_kernel(const ReduceArgs rcommon, const ReduceBatch rbatch, const PairArgs pcommon, const PairBatch pbatch,
+                                                             int64_t n_waves)
 {
+    const ReduceArgs r = slice_of(rcommon, rbatch, blockIdx.y);
+    const PairArgs a = slice_of(pcommon, pbatch);
     constexpr int ST = 36; // row stride: 16-byte row reads and 4-byte column reads are both conflict free
     __shared__ __attribute__((aligned(16))) float Zs[4][32][ST];
     __shared__ __attribute__((aligned(16))) float Hs[4][32][ST];
@@ -1210,8 +1257,9 @@ __global__ __launch_bounds__(256, 2) void bwd_strip32_kernel(const ReduceArgs r,
 // wave-private LDS tiles small enough for two wavefronts per SIMD beside the 128 accumulator
 // registers of the full-width variant, three for the half-width ones.
 template <int MI, int NJ, int SR, int WPS> // SR: node rows per strip; WPS: wavefronts per SIMD to compile for
-__global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs a, int64_t n_waves)
+__global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs common, const ReduceBatch batch, int64_t n_waves)
 {
+    const ReduceArgs a = slice_of(common, batch, blockIdx.y);
     constexpr int WI = 32 * MI, WJ = 32 * NJ; // padded widths
     constexpr int LI = WI / 4, LJ = WJ / 4;   // lanes per row (16-byte accesses)
     constexpr int PI = SR * LI / 64, PJ = SR * LJ / 64; // passes over a strip
@@ -1348,17 +1396,18 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
 // node axis is the MFMA's k axis.  32 flop per staged byte instead of 8 for 32 x 32 tiles.
 constexpr int GB_T = 128;
 
-__global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs a)
+__global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch)
 {
+    const ReduceArgs a = slice_of(common, batch, blockIdx.z / common.j_tiles);
     __shared__ __attribute__((aligned(16))) float Xs[RED_RK][GB_T];
     __shared__ __attribute__((aligned(16))) float Ps[RED_RK][GB_T];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int i_base = blockIdx.y * GB_T, j_base = blockIdx.z * GB_T;
+    const int i_base = blockIdx.y * GB_T, j_base = (blockIdx.z % common.j_tiles) * GB_T;
     const int wi = (wave >> 1) * 64, wj = (wave & 1) * 64;
-    const int64_t r_begin = (int64_t)blockIdx.x * RED_ROWS;
-    const int64_t r_end = r_begin + RED_ROWS < a.n ? r_begin + RED_ROWS : a.n;
+    const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
+    const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
     const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vg = aligned16(a.dHout) && a.ldo % 4 == 0;
     const bool bias_wave = blockIdx.y == 0 && (wave >> 1) == 0;
 
@@ -1519,11 +1568,13 @@ __global__ __launch_bounds__(256) void colsum_partial_vec_kernel(const float *__
 
 // Final stage: out[e] = sum over row blocks of partial[b][e], in fp64, fixed order.
 // 32 elements x 32 parts per block of 1024 threads.
-struct FinalDst { float *ptr[4]; int32_t begin[5]; }; // element ranges [begin[q], begin[q+1]) go to ptr[q]
+struct FinalDst { float *ptr[4]; float *copy; int32_t begin[5]; }; // element ranges [begin[q], begin[q+1]) go to ptr[q], range 3 also to copy
+struct FinalBatch { const float *partial[BATCH]; FinalDst dst[BATCH]; };
 
-__global__ __launch_bounds__(1024) void reduce_final_kernel(const float *__restrict__ partial, int64_t n_blocks,
-                                                            int32_t row_stride, int32_t stride, const FinalDst dst)
+__global__ __launch_bounds__(1024) void reduce_final_kernel(const FinalBatch batch, int64_t n_blocks, int32_t row_stride, int32_t stride)
 {
+    const float *__restrict__ partial = batch.partial[blockIdx.y];
+    const FinalDst &dst = batch.dst[blockIdx.y];
     __shared__ double red[32][33];
     const int el = threadIdx.x % 32, part = threadIdx.x / 32;
     const int64_t e = (int64_t)blockIdx.x * 32 + el;
@@ -1549,6 +1600,7 @@ __global__ __launch_bounds__(1024) void reduce_final_kernel(const float *__restr
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             if (e >= dst.begin[q] && e < dst.begin[q + 1] && dst.ptr[q]) dst.ptr[q][e - dst.begin[q]] = (float)s;
+        if (e >= dst.begin[3] && e < dst.begin[4] && dst.copy) dst.copy[e - dst.begin[3]] = (float)s;
     }
 }
 
@@ -1568,15 +1620,72 @@ inline int64_t layer_grad_blocks(int64_t n, int32_t w_in, int32_t w_out)
     return (n + rows - 1) / rows;
 }
 
+// How the weight gradients of a slice layer are formed: by which kernel, and in how many partial sums.  A function of the
+// sizes alone: the rows that go into one fp32 chain, and so the bits of a gradient, do not depend on the launch.
+struct GradPlan {
+    enum Kind { STRIP32, STRIP64, TILED } kind;
+    int64_t partials;
+    int32_t rows; // TILED: node rows per workgroup
+};
+inline GradPlan grad_plan(int64_t n, int32_t w_in, int32_t w_out)
+{
+    const int64_t nb = layer_grad_blocks(n, w_in, w_out);
+    if (w_in <= 32 && w_out <= 32 && n >= 65536) { // one partial sum per wavefront
+        const int64_t strips = (n + 31) / 32, waves = nb < 8192 ? nb : 8192;
+        return GradPlan{GradPlan::STRIP32, waves < strips ? waves : strips, 0};
+    }
+    if (w_in <= 64 && w_out <= 64 && n >= ((int64_t)1 << 21)) {
+        // whole waves of resident workgroups (256 CUs x 3 workgroups x 4 wavefronts) where there are as many blocks
+        const int64_t resident = 3072;
+        const int64_t waves = nb >= resident ? nb / resident * resident : nb >= 2048 ? 2048 : nb;
+        const int64_t strips = (n + 7) / 8; // strips of 8 rows in every variant launched here
+        return GradPlan{GradPlan::STRIP64, waves < strips ? waves : strips, 0};
+    }
+    return GradPlan{GradPlan::TILED, nb, layer_grad_rows(n, w_in, w_out)};
+}
+
+// A dense layer's weight and bias gradients: 128 x 128 output tiles where the layer is wide, 32 x 32 tiles otherwise, a
+// partial sum per RED_ROWS node rows.  On few rows that would leave most of the chip idle behind chains of RED_ROWS rows, so
+// there (up to SMALL_LINEAR output elements) the rows are split until 512 workgroups are there or a workgroup is down to
+// one step, as far as the workspace has room (`capacity` partial sums): 5000 rows 96 -> 96: 132 -> LINSMALL us.
+struct LinearGradPlan {
+    bool big;
+    int32_t rows;
+    int64_t partials;
+};
+constexpr int64_t NO_LIMIT = (int64_t)1 << 40, SMALL_LINEAR = (int64_t)1 << 19;
+inline LinearGradPlan linear_grad_plan(int64_t n, int32_t w_in, int32_t w_out, int64_t capacity)
+{
+    LinearGradPlan p;
+    p.big = w_in > 64 || w_out > 64;
+    int64_t rows = RED_ROWS;
+    if (n * (w_in > w_out ? w_in : w_out) <= SMALL_LINEAR) {
+        const int32_t t = p.big ? GB_T : RED_TILE;
+        const int64_t tiles = (int64_t)((w_in + t - 1) / t) * ((w_out + t - 1) / t);
+        const int64_t fine = round_up(n * tiles / 512 + 1, RED_RK), least = round_up((n + capacity - 1) / capacity, RED_RK);
+        if (fine < rows) rows = fine > least ? fine : least;
+    }
+    p.rows = (int32_t)rows;
+    p.partials = (n + rows - 1) / rows;
+    return p;
+}
 
 // ---- pieces of the transform-first layer order -------------------------------------------------
 // Hout[v, j] = act(P[v, j] + bias[j]) (+ Hout[v, j] when add), mask bit j of row v = [P + bias > 0].
 // One thread per element of the row padded to a multiple of 32 columns, so every half wavefront lies
 // inside one mask word of one row and a ballot assembles the word.
-__global__ __launch_bounds__(256) void bias_act_add_kernel(const float *__restrict__ P, int64_t ldp, const float *__restrict__ bias,
-                                                           float *__restrict__ Hout, int64_t ldo, int add, uint32_t *__restrict__ mask,
+struct BiasActBatch {
+    const float *P[BATCH], *bias[BATCH];
+    float *Hout[BATCH];
+    uint32_t *mask[BATCH];
+};
+__global__ __launch_bounds__(256) void bias_act_add_kernel(const BiasActBatch b, int64_t ldp, int64_t ldo, int add,
                                                            int64_t mask_words, int64_t n, int32_t w_out, int32_t act)
 {
+    const float *__restrict__ P = b.P[blockIdx.y];
+    const float *__restrict__ bias = b.bias[blockIdx.y];
+    float *__restrict__ Hout = b.Hout[blockIdx.y];
+    uint32_t *__restrict__ mask = b.mask[blockIdx.y];
     const int wpad = (w_out + 31) / 32 * 32;
     const int64_t total = n * (int64_t)wpad;
     const int64_t padded_total = (total + 63) / 64 * 64; // whole wavefronts take part in every ballot
@@ -1599,9 +1708,17 @@ __global__ __launch_bounds__(256) void bias_act_add_kernel(const float *__restri
 }
 
 // dP[v, j] = dHout[v, j] where the activation passed (all of it when mask == NULL)
-__global__ __launch_bounds__(256) void mask_apply_kernel(const float *__restrict__ dHout, int64_t ldo, const uint32_t *__restrict__ mask,
-                                                         int64_t mask_words, float *__restrict__ dP, int64_t ldp, int64_t n, int32_t w_out)
+struct MaskApplyBatch {
+    const float *dHout[BATCH];
+    const uint32_t *mask[BATCH];
+    float *dP[BATCH];
+};
+__global__ __launch_bounds__(256) void mask_apply_kernel(const MaskApplyBatch b, int64_t ldo, int64_t mask_words, int64_t ldp, int64_t n,
+                                                         int32_t w_out)
 {
+    const float *__restrict__ dHout = b.dHout[blockIdx.y];
+    const uint32_t *__restrict__ mask = b.mask[blockIdx.y];
+    float *__restrict__ dP = b.dP[blockIdx.y];
     const int64_t total = n * (int64_t)w_out;
     for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
         const int64_t row = t / w_out;
@@ -1613,8 +1730,14 @@ __global__ __launch_bounds__(256) void mask_apply_kernel(const float *__restrict
 }
 
 // Wt[j][i] = W[i][j] for a rows x cols row-major W (weights are small: one thread per element)
-__global__ __launch_bounds__(256) void transpose_kernel(const float *__restrict__ W, int32_t rows, int32_t cols, float *__restrict__ Wt)
+struct TransposeBatch {
+    const float *W[2 * BATCH];
+    float *Wt[2 * BATCH];
+};
+__global__ __launch_bounds__(256) void transpose_kernel(const TransposeBatch b, int32_t rows, int32_t cols)
 {
+    const float *__restrict__ W = b.W[blockIdx.y];
+    float *__restrict__ Wt = b.Wt[blockIdx.y];
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= rows * cols) return;
     const int i = t / cols, j = t - i * cols;
@@ -1684,10 +1807,10 @@ int launch_colsum_partial(const float *M, int64_t ld, int64_t n, int32_t w, floa
 
 int launch_colsum_final(const float *ws_first, int64_t n, int32_t ws_row, int32_t count, float *out, hipStream_t stream)
 {
-    FinalDst dst;
-    dst.ptr[0] = out; dst.ptr[1] = dst.ptr[2] = dst.ptr[3] = nullptr;
-    dst.begin[0] = 0; dst.begin[1] = dst.begin[2] = dst.begin[3] = dst.begin[4] = count;
-    reduce_final_kernel<<<(unsigned)((count + 31) / 32), 1024, 0, stream>>>(ws_first, red_blocks(n), ws_row, count, dst);
+    FinalBatch f;
+    f.partial[0] = ws_first;
+    f.dst[0] = FinalDst{{out, nullptr, nullptr, nullptr}, nullptr, {0, count, count, count, count}};
+    reduce_final_kernel<<<(unsigned)((count + 31) / 32), 1024, 0, stream>>>(f, red_blocks(n), ws_row, count);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
 }
@@ -1698,143 +1821,362 @@ size_t colsum_workspace_bytes(int64_t n, int32_t w) { return (size_t)red_blocks(
 
 using namespace slicegcn;
 
-// partial sums of a dense layer's weight and bias gradients: one [w_in*w_out + w_out] row per block of 1024 rows
-static size_t linear_partial_bytes(int64_t n, int32_t w_in, int32_t w_out)
+// partial sums of a dense layer's weight and bias gradients: `partials` rows of [w_in*w_out + w_out]
+static size_t linear_partial_bytes(int64_t partials, int32_t w_in, int32_t w_out)
 {
     const size_t stride = (size_t)w_in * w_out + (size_t)w_out;
-    return (size_t)round_up((int64_t)(red_blocks(n) * stride * sizeof(float)), 256);
+    return (size_t)round_up((int64_t)(partials * stride * sizeof(float)), 256);
+}
+// what the kernels use where the workspace allows it
+static size_t linear_full_bytes(int64_t n, int32_t w_in, int32_t w_out)
+{
+    return linear_partial_bytes(linear_grad_plan(n, w_in, w_out, NO_LIMIT).partials, w_in, w_out);
 }
 
-// dW = X^T (dY * mask) (w_in x w_out), db = colsum(dY * mask); NULL outputs are skipped.  ws: linear_partial_bytes bytes.
-static int launch_linear_grads(const float *X, int64_t ldx, int64_t n, int32_t w_in, int32_t w_out, const uint32_t *m,
-                               int64_t mask_words, const float *dY, int64_t lddy, float *dW, float *db, void *ws, hipStream_t stream)
+struct LinearGradArgs { // one layer of a batch (equal shapes and leading dimensions)
+    const float *X;
+    const uint32_t *mask;
+    const float *dY;
+    float *dW, *db;
+    float *db_copy = nullptr;
+};
+
+// dW = X^T (dY * mask) (w_in x w_out), db = colsum(dY * mask); NULL outputs are skipped.  ws: ws_each bytes per layer of
+// the batch, at least linear_partial_bytes(red_blocks(n)).
+static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ldx, int64_t n, int32_t w_in, int32_t w_out,
+                               int64_t mask_words, int64_t lddy, void *ws, size_t ws_each, hipStream_t stream)
 {
-    const int64_t nb = red_blocks(n);
     const int ww = w_in * w_out;
     const int32_t stride = ww + w_out;
+    const LinearGradPlan plan = linear_grad_plan(n, w_in, w_out, (int64_t)(ws_each / ((size_t)stride * sizeof(float))));
     ReduceArgs r;
-    r.Z = X; r.ldz = ldx; r.Hin = nullptr; r.ldi = 0; r.dHout = dY; r.ldo = lddy;
-    r.mask = m; r.mask_words = mask_words;
-    r.partial = static_cast<float *>(ws); r.n = n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 1;
-    dim3 grid((unsigned)nb, (unsigned)((w_in + RED_TILE - 1) / RED_TILE), (unsigned)((w_out + RED_TILE - 1) / RED_TILE));
-    if (w_in > 64 || w_out > 64) { // wide layer: 128 x 128 output tiles
-        dim3 big((unsigned)nb, (unsigned)((w_in + GB_T - 1) / GB_T), (unsigned)((w_out + GB_T - 1) / GB_T));
-        grad_big_mfma_kernel<<<big, 256, 0, stream>>>(r);
-    } else {
-        grad_partial_mfma_kernel<<<grid, 256, 0, stream>>>(r);
+    r.Z = nullptr; r.ldz = ldx; r.Hin = nullptr; r.ldi = 0; r.dHout = nullptr; r.ldo = lddy;
+    r.mask = nullptr; r.mask_words = mask_words;
+    r.partial = nullptr; r.n = n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 1;
+    r.rows_per_block = plan.rows;
+    const int t = plan.big ? GB_T : RED_TILE;
+    r.j_tiles = (w_out + t - 1) / t;
+    ReduceBatch b;
+    FinalBatch f;
+    for (int i = 0; i < BATCH; ++i) {
+        const LinearGradArgs &x = list[i < batch ? i : 0];
+        float *partial = reinterpret_cast<float *>(static_cast<char *>(ws) + (i < batch ? i : 0) * ws_each);
+        b.p[i] = ReducePtrs{x.X, nullptr, x.dY, x.mask, partial};
+        f.partial[i] = partial;
+        f.dst[i] = FinalDst{{x.dW, nullptr, nullptr, x.db}, x.db_copy, {0, ww, ww, ww, stride}};
     }
+    const dim3 grid((unsigned)plan.partials, (unsigned)((w_in + t - 1) / t), (unsigned)(r.j_tiles * batch));
+    if (plan.big) grad_big_mfma_kernel<<<grid, 256, 0, stream>>>(r, b);
+    else grad_partial_mfma_kernel<<<grid, 256, 0, stream>>>(r, b);
     SG_LAUNCH_CHECK();
-    FinalDst dst;
-    dst.ptr[0] = dW; dst.ptr[1] = db; dst.ptr[2] = dst.ptr[3] = nullptr;
-    dst.begin[0] = 0; dst.begin[1] = ww; dst.begin[2] = dst.begin[3] = dst.begin[4] = stride;
-    reduce_final_kernel<<<(unsigned)((stride + 31) / 32), 1024, 0, stream>>>(r.partial, nb, stride, stride, dst);
+    reduce_final_kernel<<<dim3((unsigned)((stride + 31) / 32), (unsigned)batch), 1024, 0, stream>>>(f, plan.partials, stride, stride);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
 }
 
-// ---- transform-first order of a slice layer ------------------------------------------------
+// ---- one layer of a batch of slice models --------------------------------------------------
+static size_t mat_bytes(int64_t n, int32_t w) { return (size_t)round_up(n * round_up(w, 32) * (int64_t)sizeof(float), 256); }
+
+// Transform-first order:
 // forward : T = Hin W_agg;  S = Hin W_self + b_self (stored straight into Hout);  P = A^ T;
 //           Hout = act(P + b) + S,  mask = [P + b > 0]
 // backward: dP = dHout * mask;  db = colsum dP;  G = A^^T dP;  dW_agg = Hin^T G;
 //           dW_self = Hin^T dHout, db_self = colsum dHout;  dHin = G W_agg^T + dHout W_self^T
 // Nothing of the forward pass but the mask is kept: the backward pass aggregates dP instead of re-using A^ Hin.
-static size_t tf_mat_bytes(int64_t n, int32_t w) { return (size_t)round_up(n * round_up(w, 32) * (int64_t)sizeof(float), 256); }
 static size_t tf_wt_bytes(const slicegcn_layer_desc *d) { return (size_t)round_up((int64_t)d->w_in * d->w_out * (int64_t)sizeof(float), 256); }
-static size_t tf_red_bytes(int64_t n, const slicegcn_layer_desc *d)
+static size_t tf_red_bytes(int64_t n, const slicegcn_layer_desc *d, bool full)
 {
-    const size_t a = linear_partial_bytes(n, d->w_in, d->w_out), b = (size_t)round_up((int64_t)colsum_workspace_bytes(n, d->w_out), 256);
-    return a > b ? a : b;
-}
-// backward workspace: [dP | G | W_agg^T | W_self^T | reduction partials | aggregation workspace]
-static size_t tf_bwd_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *d)
-{
-    return 2 * tf_mat_bytes(g->n, d->w_out) + 2 * tf_wt_bytes(d) + tf_red_bytes(g->n, d) + spmm_workspace_bytes(g->tr, d->w_out);
+    const size_t a = full ? linear_full_bytes(n, d->w_in, d->w_out) : 0, c = linear_partial_bytes(red_blocks(n), d->w_in, d->w_out);
+    const size_t b = (size_t)round_up((int64_t)colsum_workspace_bytes(n, d->w_out), 256);
+    const size_t m = a > c ? a : c;
+    return m > b ? m : b;
 }
 
-static int layer_fwd_transform_first(const slicegcn_graph *g, const slicegcn_layer_desc *desc, const slicegcn_layer_params *params,
-                                     const float *Hin, int64_t ldi, float *Hout, int64_t ldo, slicegcn_layer_saved *saved,
-                                     void *ws, size_t ws_bytes, hipStream_t stream)
+// Bytes of workspace per slice of a batch.  `full`: with as many partial sums as the reductions would use.
+static size_t fwd_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *d)
 {
+    if (transform_first(d)) return 2 * mat_bytes(g->n, d->w_out) + spmm_workspace_bytes(g->fwd, d->w_out);
+    return spmm_workspace_bytes(g->fwd, d->w_in);
+}
+static size_t bwd_partial_bytes(int64_t n, const slicegcn_layer_desc *d)
+{
+    const size_t stride = 2 * (size_t)d->w_in * d->w_out + 2 * (size_t)d->w_out;
+    return (size_t)round_up((int64_t)(layer_grad_blocks(n, d->w_in, d->w_out) * stride * sizeof(float)), 256);
+}
+static size_t bwd_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *d, bool need_dHin, bool full)
+{
+    if (transform_first(d)) // [dP | G | W_agg^T | W_self^T | reduction partials | aggregation workspace]
+        return 2 * mat_bytes(g->n, d->w_out) + 2 * tf_wt_bytes(d) + tf_red_bytes(g->n, d, full) + spmm_workspace_bytes(g->tr, d->w_out);
+    // [partial weight gradients | dZ (only with dHin) | aggregation workspace (only with dHin)]
+    size_t bytes = bwd_partial_bytes(g->n, d);
+    if (need_dHin) bytes += mat_bytes(g->n, d->w_in) + spmm_workspace_bytes(g->tr, d->w_in);
+    return bytes;
+}
+
+// Workspace sections: section q of slice i starts at base + batch * (bytes of the sections before) + i * (bytes of section q)
+struct Sections {
+    char *base;
+    int batch;
+    size_t used = 0;
+    char *take(size_t bytes) { char *p = base + used; used += bytes * batch; return p; }
+};
+
+static int fwd_transform_first(const slicegcn_graph *g, const slicegcn_layer_group *lg, const slicegcn_layer_io *io, int batch, void *ws,
+                               hipStream_t stream)
+{
+    const slicegcn_layer_desc *desc = &lg->desc;
     const int w_in = desc->w_in, w_out = desc->w_out;
-    const size_t need = slicegcn_layer_fwd_workspace_bytes(g, desc);
-    SG_REQUIRE(ws != nullptr && ws_bytes >= need, SLICEGCN_EWORKSPACE, "layer_fwd: workspace of %zu bytes, %zu needed", ws_bytes, need);
-    SG_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL, "layer_fwd: workspace not 256-byte aligned");
+    const bool self = io[0].params.W_self != nullptr;
     const int64_t ldt = round_up(w_out, 32);
-    float *T = static_cast<float *>(ws);
-    float *P = reinterpret_cast<float *>(static_cast<char *>(ws) + tf_mat_bytes(g->n, w_out));
-    void *agg_ws = static_cast<char *>(ws) + 2 * tf_mat_bytes(g->n, w_out);
+    const size_t mat = mat_bytes(g->n, w_out), agg = spmm_workspace_bytes(g->fwd, w_out);
+    Sections sec{static_cast<char *>(ws), batch};
+    char *Ts = sec.take(mat), *Ps = sec.take(mat), *agg_ws = sec.take(agg);
     {
         ProfScope prof(SLICEGCN_PROF_DENSE_FWD, w_out, stream);
-        PairArgs a;
-        a.A1 = Hin; a.lda1 = ldi; a.A2 = nullptr; a.lda2 = 0;
-        a.B1 = params->W_agg; a.B2 = nullptr; a.bias1 = a.bias2 = nullptr;
-        a.O1 = T; a.ldo1 = ldt; a.O2 = nullptr; a.ldo2 = 0;
-        a.mask = nullptr; a.mask_words = 0;
-        a.n = g->n; a.K = w_in; a.Nout = w_out; a.ldw = w_out; a.act = SLICEGCN_ACT_NONE;
-        if (int rc = launch_pair<false>(a, stream)) return rc;
-        if (params->W_self) { // the self term goes straight to the output; the epilogue below adds the activated part
-            a.B1 = params->W_self; a.bias1 = params->b_self; a.O1 = Hout; a.ldo1 = ldo;
-            if (int rc = launch_pair<false>(a, stream)) return rc;
+        PairArgs list[BATCH];
+        for (int i = 0; i < batch; ++i) {
+            PairArgs &a = list[i];
+            a.A1 = io[i].Hin; a.lda1 = lg->ldi; a.A2 = nullptr; a.lda2 = 0;
+            a.B1 = io[i].params.W_agg; a.B2 = nullptr; a.bias1 = a.bias2 = nullptr;
+            a.O1 = reinterpret_cast<float *>(Ts + i * mat); a.ldo1 = ldt; a.O2 = nullptr; a.ldo2 = 0;
+            a.mask = nullptr; a.mask_words = 0;
+            a.n = g->n; a.K = w_in; a.Nout = w_out; a.ldw = w_out; a.act = SLICEGCN_ACT_NONE;
+        }
+        if (int rc = launch_pair<false>(list, batch, stream)) return rc;
+        if (self) { // the self term goes straight to the output; the epilogue below adds the activated part
+            for (int i = 0; i < batch; ++i) {
+                list[i].B1 = io[i].params.W_self; list[i].bias1 = io[i].params.b_self; list[i].enc = io[i].enc;
+                list[i].O1 = io[i].Hout; list[i].ldo1 = lg->ldo;
+            }
+            if (int rc = launch_pair<false>(list, batch, stream)) return rc;
         }
     }
-    if (int rc = launch_spmm(g, g->fwd, T, ldt, w_out, P, ldt, nullptr, 0, agg_ws, spmm_workspace_bytes(g->fwd, w_out), stream)) return rc;
+    SpmmOperands ops[BATCH];
+    BiasActBatch b;
+    for (int i = 0; i < BATCH; ++i) {
+        const int q = i < batch ? i : 0;
+        float *P = reinterpret_cast<float *>(Ps + q * mat);
+        ops[i] = SpmmOperands{reinterpret_cast<float *>(Ts + q * mat), P, nullptr};
+        b.P[i] = P; b.bias[i] = io[q].params.b; b.Hout[i] = io[q].Hout;
+        b.mask[i] = desc->act == SLICEGCN_ACT_RELU ? io[q].mask : nullptr;
+    }
+    if (int rc = launch_spmm(g, g->fwd, ops, batch, ldt, w_out, ldt, 0, agg_ws, agg * batch, stream)) return rc;
     ProfScope prof(SLICEGCN_PROF_DENSE_FWD, w_out, stream);
     const int64_t total = g->n * round_up(w_out, 32);
-    bias_act_add_kernel<<<ew_grid(total), 256, 0, stream>>>(P, ldt, params->b, Hout, ldo, params->W_self != nullptr,
-                                                            desc->act == SLICEGCN_ACT_RELU ? saved->mask : nullptr, saved->mask_words,
-                                                            g->n, w_out, desc->act);
+    bias_act_add_kernel<<<dim3(ew_grid(total), (unsigned)batch), 256, 0, stream>>>(b, ldt, lg->ldo, self, lg->mask_words, g->n, w_out, desc->act);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
 }
 
-static int layer_bwd_transform_first(const slicegcn_graph *g, const slicegcn_layer_desc *desc, const slicegcn_layer_params *params,
-                                     const float *Hin, int64_t ldi, const uint32_t *mask, int64_t mask_words, const float *dHout,
-                                     int64_t ldo, float *dHin, int64_t ldgi, slicegcn_layer_grads *grads, void *ws, hipStream_t stream)
+static int bwd_transform_first(const slicegcn_graph *g, const slicegcn_layer_group *lg, const slicegcn_layer_io *io, int batch, void *ws,
+                               bool full, hipStream_t stream)
 {
+    const slicegcn_layer_desc *desc = &lg->desc;
     const int w_in = desc->w_in, w_out = desc->w_out;
     const int64_t n = g->n, ldp = round_up(w_out, 32);
-    char *base = static_cast<char *>(ws);
-    float *dP = reinterpret_cast<float *>(base);
-    float *G = reinterpret_cast<float *>(base + tf_mat_bytes(n, w_out));
-    float *WaT = reinterpret_cast<float *>(base + 2 * tf_mat_bytes(n, w_out));
-    float *WsT = reinterpret_cast<float *>(base + 2 * tf_mat_bytes(n, w_out) + tf_wt_bytes(desc));
-    void *red = base + 2 * tf_mat_bytes(n, w_out) + 2 * tf_wt_bytes(desc);
-    void *agg_ws = static_cast<char *>(red) + tf_red_bytes(n, desc);
+    const bool relu = desc->act == SLICEGCN_ACT_RELU, self = io[0].params.W_self != nullptr;
+    const size_t mat = mat_bytes(n, w_out), wt = tf_wt_bytes(desc), red_each = tf_red_bytes(n, desc, full), agg = spmm_workspace_bytes(g->tr, w_out);
+    Sections sec{static_cast<char *>(ws), batch};
+    char *dPs = sec.take(mat), *Gs = sec.take(mat), *WaTs = sec.take(wt), *WsTs = sec.take(wt), *red = sec.take(red_each), *agg_ws = sec.take(agg);
+    auto dP = [&](int i) { return reinterpret_cast<float *>(dPs + i * mat); };
+    auto G = [&](int i) { return reinterpret_cast<float *>(Gs + i * mat); };
     {
         ProfScope prof(SLICEGCN_PROF_DENSE_BWD, w_out, stream);
-        mask_apply_kernel<<<ew_grid(n * w_out), 256, 0, stream>>>(dHout, ldo, mask, mask_words, dP, ldp, n, w_out);
+        MaskApplyBatch b;
+        for (int i = 0; i < BATCH; ++i) {
+            const int q = i < batch ? i : 0;
+            b.dHout[i] = io[q].dHout; b.mask[i] = relu ? io[q].mask : nullptr; b.dP[i] = dP(q);
+        }
+        mask_apply_kernel<<<dim3(ew_grid(n * w_out), (unsigned)batch), 256, 0, stream>>>(b, lg->ldgo, lg->mask_words, ldp, n, w_out);
         SG_LAUNCH_CHECK();
     }
-    if (int rc = launch_spmm(g, g->tr, dP, ldp, w_out, G, ldp, nullptr, 0, agg_ws, spmm_workspace_bytes(g->tr, w_out), stream)) return rc;
+    SpmmOperands ops[BATCH];
+    for (int i = 0; i < batch; ++i) ops[i] = SpmmOperands{dP(i), G(i), nullptr};
+    if (int rc = launch_spmm(g, g->tr, ops, batch, ldp, w_out, ldp, 0, agg_ws, agg * batch, stream)) return rc;
     {
         ProfScope prof(SLICEGCN_PROF_GRAD_REDUCE, w_out, stream);
-        if (grads->db) {
-            if (int rc = launch_colsum_partial(dP, ldp, n, w_out, static_cast<float *>(red), stream)) return rc;
-            if (int rc = launch_colsum_final(static_cast<float *>(red), n, w_out, w_out, grads->db, stream)) return rc;
+        for (int i = 0; i < batch; ++i)
+            if (io[i].grads.db) {
+                if (int rc = launch_colsum_partial(dP(i), ldp, n, w_out, reinterpret_cast<float *>(red), stream)) return rc;
+                if (int rc = launch_colsum_final(reinterpret_cast<float *>(red), n, w_out, w_out, io[i].grads.db, stream)) return rc;
+            }
+        LinearGradArgs agg_list[BATCH], self_list[BATCH];
+        bool any_agg = false, any_self = false;
+        for (int i = 0; i < batch; ++i) {
+            const slicegcn_layer_grads &gr = io[i].grads;
+            agg_list[i] = LinearGradArgs{io[i].Hin, nullptr, G(i), gr.dW_agg, nullptr};
+            self_list[i] = LinearGradArgs{io[i].Hin, nullptr, io[i].dHout, gr.dW_self, gr.db_self, io[i].denc};
+            any_agg = any_agg || gr.dW_agg;
+            any_self = any_self || (self && (gr.dW_self || gr.db_self || io[i].denc));
         }
-        if (grads->dW_agg)
-            if (int rc = launch_linear_grads(Hin, ldi, n, w_in, w_out, nullptr, 0, G, ldp, grads->dW_agg, nullptr, red, stream)) return rc;
-        if (params->W_self && (grads->dW_self || grads->db_self))
-            if (int rc = launch_linear_grads(Hin, ldi, n, w_in, w_out, nullptr, 0, dHout, ldo, grads->dW_self, grads->db_self, red, stream))
-                return rc;
+        if (any_agg)
+            if (int rc = launch_linear_grads(agg_list, batch, lg->ldi, n, w_in, w_out, 0, ldp, red, red_each, stream)) return rc;
+        if (any_self)
+            if (int rc = launch_linear_grads(self_list, batch, lg->ldi, n, w_in, w_out, 0, lg->ldgo, red, red_each, stream)) return rc;
     }
-    if (dHin) { // dHin = G W_agg^T + dHout W_self^T: one forward-form launch over the transposed weights
+    if (io[0].dHin) { // dHin = G W_agg^T + dHout W_self^T: one forward-form launch over the transposed weights
         ProfScope prof(SLICEGCN_PROF_DENSE_BWD, w_in, stream);
         const int count = w_in * w_out;
-        transpose_kernel<<<(count + 255) / 256, 256, 0, stream>>>(params->W_agg, w_in, w_out, WaT);
-        if (params->W_self) transpose_kernel<<<(count + 255) / 256, 256, 0, stream>>>(params->W_self, w_in, w_out, WsT);
+        TransposeBatch t;
+        int mats = 0;
+        PairArgs list[BATCH];
+        for (int i = 0; i < batch; ++i) {
+            float *WaT = reinterpret_cast<float *>(WaTs + i * wt), *WsT = reinterpret_cast<float *>(WsTs + i * wt);
+            t.W[mats] = io[i].params.W_agg; t.Wt[mats++] = WaT;
+            if (self) { t.W[mats] = io[i].params.W_self; t.Wt[mats++] = WsT; }
+            PairArgs &a = list[i];
+            a.A1 = G(i); a.lda1 = ldp;
+            a.A2 = self ? io[i].dHout : nullptr; a.lda2 = lg->ldgo;
+            a.B1 = WaT; a.B2 = self ? WsT : nullptr;
+            a.bias1 = a.bias2 = nullptr;
+            a.O1 = io[i].dHin; a.ldo1 = lg->ldgi; a.O2 = nullptr; a.ldo2 = 0;
+            a.mask = nullptr; a.mask_words = 0;
+            a.n = n; a.K = w_out; a.Nout = w_in; a.ldw = w_in; a.act = SLICEGCN_ACT_NONE;
+        }
+        transpose_kernel<<<dim3((unsigned)((count + 255) / 256), (unsigned)mats), 256, 0, stream>>>(t, w_in, w_out);
         SG_LAUNCH_CHECK();
-        PairArgs a;
-        a.A1 = G; a.lda1 = ldp;
-        a.A2 = params->W_self ? dHout : nullptr; a.lda2 = ldo;
-        a.B1 = WaT; a.B2 = params->W_self ? WsT : nullptr;
-        a.bias1 = a.bias2 = nullptr;
-        a.O1 = dHin; a.ldo1 = ldgi; a.O2 = nullptr; a.ldo2 = 0;
-        a.mask = nullptr; a.mask_words = 0;
-        a.n = n; a.K = w_out; a.Nout = w_in; a.ldw = w_in; a.act = SLICEGCN_ACT_NONE;
-        if (int rc = launch_pair<false>(a, stream)) return rc;
+        if (int rc = launch_pair<false>(list, batch, stream)) return rc;
     }
     return SLICEGCN_OK;
+}
+
+// Forward pass of one layer for `batch` slice models.  ws: batch * fwd_bytes.
+static int layers_fwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, const slicegcn_layer_io *io, int batch, void *ws,
+                      size_t ws_bytes, hipStream_t stream)
+{
+    const slicegcn_layer_desc *desc = &lg->desc;
+    if (transform_first(desc)) return fwd_transform_first(g, lg, io, batch, ws, stream);
+    const bool self = io[0].params.W_self != nullptr;
+    if (!(desc->flags & SLICEGCN_LAYER_Z_VALID)) {
+        SpmmOperands ops[BATCH];
+        for (int i = 0; i < batch; ++i) ops[i] = SpmmOperands{io[i].Hin, io[i].Z, nullptr};
+        if (int rc = launch_spmm(g, g->fwd, ops, batch, lg->ldi, desc->w_in, lg->ldz, 0, ws, ws_bytes, stream,
+                                 (desc->flags & SLICEGCN_LAYER_IN_SCALED) != 0))
+            return rc;
+    }
+    PairArgs list[BATCH];
+    for (int i = 0; i < batch; ++i) {
+        PairArgs &a = list[i];
+        const slicegcn_layer_params &p = io[i].params;
+        a.A1 = io[i].Z; a.lda1 = lg->ldz;
+        a.A2 = self ? io[i].Hin : nullptr; a.lda2 = lg->ldi;
+        a.B1 = p.W_agg; a.B2 = p.W_self;
+        a.bias1 = p.b; a.bias2 = p.b_self; a.enc = io[i].enc;
+        a.O1 = io[i].Hout; a.ldo1 = lg->ldo; a.O2 = nullptr; a.ldo2 = 0;
+        a.mask = desc->act == SLICEGCN_ACT_RELU ? io[i].mask : nullptr; a.mask_words = lg->mask_words;
+        a.n = g->n; a.K = desc->w_in; a.Nout = desc->w_out; a.ldw = desc->w_out; a.act = desc->act;
+        a.scale2 = ((desc->flags & SLICEGCN_LAYER_IN_SCALED) && self) ? g->sqrtd : nullptr;
+        a.scale_o1 = (desc->flags & SLICEGCN_LAYER_OUT_SCALED) ? g->dinv : nullptr;
+    }
+    ProfScope prof(SLICEGCN_PROF_DENSE_FWD, desc->w_out, stream);
+    return launch_pair<false>(list, batch, stream);
+}
+
+// Backward pass of one layer for `batch` slice models.  ws: batch * bwd_bytes(..., full).
+static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, const slicegcn_layer_io *io, int batch, void *ws, bool full,
+                      hipStream_t stream)
+{
+    const slicegcn_layer_desc *desc = &lg->desc;
+    if (transform_first(desc)) return bwd_transform_first(g, lg, io, batch, ws, full, stream);
+    const int w_in = desc->w_in, w_out = desc->w_out;
+    const bool self = io[0].params.W_self != nullptr, need_dHin = io[0].dHin != nullptr, relu = desc->act == SLICEGCN_ACT_RELU;
+    const size_t part = bwd_partial_bytes(g->n, desc), mat = mat_bytes(g->n, w_in), agg = spmm_workspace_bytes(g->tr, w_in);
+    Sections sec{static_cast<char *>(ws), batch};
+    char *parts = sec.take(part), *dZs = need_dHin ? sec.take(mat) : nullptr, *agg_ws = need_dHin ? sec.take(agg) : nullptr;
+
+    // ---- input gradient, dense half: dZ = dP W_agg^T (staged, rows scaled by D~^-1/2) and T = dHout W_self^T (into dHin) ----
+    const int64_t ldz_in = round_up(w_in, 32); // rows of the gathered operand start on 128-byte boundaries
+    PairArgs list[BATCH];
+    for (int i = 0; i < batch && need_dHin; ++i) {
+        PairArgs &a = list[i];
+        a.A1 = io[i].dHout; a.lda1 = lg->ldgo;
+        a.A2 = self ? io[i].dHout : nullptr; a.lda2 = lg->ldgo;
+        a.B1 = io[i].params.W_agg; a.B2 = io[i].params.W_self;
+        a.bias1 = a.bias2 = nullptr;
+        a.O1 = reinterpret_cast<float *>(dZs + i * mat); a.ldo1 = ldz_in;
+        a.O2 = self ? io[i].dHin : nullptr; a.ldo2 = lg->ldgi;
+        a.mask = relu ? io[i].mask : nullptr; a.mask_words = lg->mask_words;
+        a.n = g->n; a.K = w_out; a.Nout = w_in; a.ldw = w_out; a.act = desc->act;
+        a.scale_o1 = g->dinv; // dZ is staged as D~^-1/2 dZ: its aggregation then skips the stored values
+    }
+    const GradPlan plan = grad_plan(g->n, w_in, w_out);
+    // narrow layers with a self term: the kernel that forms the weight gradients also forms dZ and T (one read of dHout)
+    const bool fused_inputs = need_dHin && self && plan.kind == GradPlan::STRIP32;
+
+    // ---- parameter gradients: per-row-block partial sums, then an fp64 combination ----
+    const int32_t stride = 2 * w_in * w_out + 2 * w_out;
+    {
+        ProfScope prof(SLICEGCN_PROF_GRAD_REDUCE, w_out, stream);
+        ReduceArgs r;
+        r.Z = nullptr; r.ldz = lg->ldz; r.Hin = nullptr; r.ldi = lg->ldi; r.dHout = nullptr; r.ldo = lg->ldgo;
+        r.mask = nullptr; r.mask_words = lg->mask_words;
+        r.partial = nullptr; r.n = g->n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 0;
+        r.rows_per_block = plan.rows;
+        r.j_tiles = (w_out + RED_TILE - 1) / RED_TILE;
+        r.hin_scale = (desc->flags & SLICEGCN_LAYER_IN_SCALED) ? g->sqrtd : nullptr;
+        ReduceBatch b;
+        FinalBatch f;
+        const int ww = w_in * w_out;
+        for (int i = 0; i < BATCH; ++i) {
+            const slicegcn_layer_io &x = io[i < batch ? i : 0];
+            float *partial = reinterpret_cast<float *>(parts + (i < batch ? i : 0) * part);
+            b.p[i] = ReducePtrs{x.Z, self ? x.Hin : nullptr, x.dHout, relu ? x.mask : nullptr, partial};
+            f.partial[i] = partial;
+            f.dst[i] = FinalDst{{x.grads.dW_agg, self ? x.grads.dW_self : nullptr, x.grads.db, self ? x.grads.db_self : nullptr},
+                                self ? x.denc : nullptr, {0, ww, 2 * ww, 2 * ww + w_out, stride}};
+        }
+        const unsigned by = (unsigned)batch, gb = (unsigned)((plan.partials + 3) / 4);
+        switch (plan.kind) {
+        case GradPlan::STRIP32:
+            if (fused_inputs) { // weight gradients and the two input-gradient products in one sweep over the rows
+                PairBatch pb;
+                for (int i = 0; i < BATCH; ++i) {
+                    const PairArgs &x = list[i < batch ? i : 0];
+                    pb.p[i] = PairPtrs{x.A1, x.A2, x.B1, x.B2, x.bias1, x.bias2, nullptr, x.O1, x.O2, x.mask};
+                }
+                bwd_strip32_kernel<<<dim3(gb, by), 256, 0, stream>>>(r, b, list[0], pb, plan.partials);
+            } else {
+                grad_strip32_kernel<<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
+            }
+            break;
+        case GradPlan::STRIP64:
+            if (w_in <= 32) grad_strip64_kernel<1, 2, 8, 3><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
+            else if (w_out <= 32) grad_strip64_kernel<2, 1, 8, 3><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
+            else grad_strip64_kernel<2, 2, 8, 2><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
+            break;
+        case GradPlan::TILED:
+            grad_partial_mfma_kernel<<<dim3((unsigned)plan.partials, (unsigned)((w_in + RED_TILE - 1) / RED_TILE), (unsigned)(r.j_tiles * batch)),
+                                       256, 0, stream>>>(r, b);
+            break;
+        }
+        SG_LAUNCH_CHECK();
+        reduce_final_kernel<<<dim3((unsigned)((stride + 31) / 32), by), 1024, 0, stream>>>(f, plan.partials, stride, stride);
+        SG_LAUNCH_CHECK();
+    }
+
+    // ---- input gradient: dHin = A^^T (dP W_agg^T) + dHout W_self^T ----
+    if (need_dHin) {
+        if (!fused_inputs) {
+            ProfScope prof(SLICEGCN_PROF_DENSE_BWD, w_in, stream);
+            if (int rc = launch_pair<true>(list, batch, stream)) return rc;
+        }
+        // padding columns of dZ are never read as data: the aggregation masks them on store
+        SpmmOperands ops[BATCH];
+        for (int i = 0; i < batch; ++i)
+            ops[i] = SpmmOperands{reinterpret_cast<float *>(dZs + i * mat), io[i].dHin, self ? io[i].dHin : nullptr};
+        if (int rc = launch_spmm(g, g->tr, ops, batch, ldz_in, w_in, lg->ldgi, lg->ldgi, agg_ws, agg * batch, stream, true)) return rc;
+    }
+    return SLICEGCN_OK;
+}
+
+static slicegcn_layer_group one_layer(const slicegcn_layer_desc *desc, int64_t ldi, int64_t ldo, const slicegcn_layer_saved *saved,
+                                      int64_t ldgo, int64_t ldgi)
+{
+    slicegcn_layer_group lg;
+    lg.desc = *desc;
+    lg.count = 1;
+    lg.ldi = ldi; lg.ldo = ldo; lg.ldz = saved->ldz; lg.mask_words = saved->mask_words; lg.ldgo = ldgo; lg.ldgi = ldgi;
+    return lg;
 }
 
 extern "C" int slicegcn_layer_fwd(const slicegcn_graph *g, const slicegcn_layer_desc *desc,
@@ -1846,53 +2188,27 @@ extern "C" int slicegcn_layer_fwd(const slicegcn_graph *g, const slicegcn_layer_
     SG_REQUIRE(Hin && Hout, SLICEGCN_EINVAL, "layer_fwd: NULL Hin or Hout");
     SG_REQUIRE(ldi >= desc->w_in && ldo >= desc->w_out, SLICEGCN_EINVAL, "layer_fwd: leading dimension too small");
     if (int rc = check_saved(desc, saved, "layer_fwd")) return rc;
-    hipStream_t stream = as_stream(stream_);
-    if (transform_first(desc)) return layer_fwd_transform_first(g, desc, params, Hin, ldi, Hout, ldo, saved, ws, ws_bytes, stream);
-
-    if (!(desc->flags & SLICEGCN_LAYER_Z_VALID))
-        if (int rc = launch_spmm(g, g->fwd, Hin, ldi, desc->w_in, saved->Z, saved->ldz, nullptr, 0, ws, ws_bytes, stream,
-                                 (desc->flags & SLICEGCN_LAYER_IN_SCALED) != 0))
-            return rc;
-
-    PairArgs a;
-    a.A1 = saved->Z; a.lda1 = saved->ldz;
-    a.A2 = params->W_self ? Hin : nullptr; a.lda2 = ldi;
-    a.B1 = params->W_agg; a.B2 = params->W_self;
-    a.bias1 = params->b; a.bias2 = params->b_self;
-    a.O1 = Hout; a.ldo1 = ldo; a.O2 = nullptr; a.ldo2 = 0;
-    a.mask = desc->act == SLICEGCN_ACT_RELU ? saved->mask : nullptr; a.mask_words = saved->mask_words;
-    a.n = g->n; a.K = desc->w_in; a.Nout = desc->w_out; a.ldw = desc->w_out; a.act = desc->act;
-    a.scale2 = ((desc->flags & SLICEGCN_LAYER_IN_SCALED) && params->W_self) ? g->sqrtd : nullptr;
-    a.scale_o1 = (desc->flags & SLICEGCN_LAYER_OUT_SCALED) ? g->dinv : nullptr;
-    ProfScope prof(SLICEGCN_PROF_DENSE_FWD, desc->w_out, stream);
-    return launch_pair<false>(a, stream);
+    if (transform_first(desc)) {
+        const size_t need = fwd_bytes(g, desc);
+        SG_REQUIRE(ws != nullptr && ws_bytes >= need, SLICEGCN_EWORKSPACE, "layer_fwd: workspace of %zu bytes, %zu needed", ws_bytes, need);
+        SG_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL, "layer_fwd: workspace not 256-byte aligned");
+    }
+    const slicegcn_layer_group lg = one_layer(desc, ldi, ldo, saved, 0, 0);
+    slicegcn_layer_io io{};
+    io.params = *params; io.Hin = Hin; io.Hout = Hout; io.Z = saved->Z; io.mask = saved->mask;
+    return layers_fwd(g, &lg, &io, 1, ws, ws_bytes, as_stream(stream_));
 }
 
 extern "C" size_t slicegcn_layer_fwd_workspace_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *desc)
 {
     if (!g || !desc || desc->w_in < 1 || desc->w_out < 1) return 0;
-    if (transform_first(desc)) return 2 * tf_mat_bytes(g->n, desc->w_out) + spmm_workspace_bytes(g->fwd, desc->w_out);
-    return spmm_workspace_bytes(g->fwd, desc->w_in);
-}
-
-// layout of the backward workspace: [partial weight gradients | dZ (only with dHin) | aggregation workspace (only with dHin)]
-static size_t bwd_partial_bytes(int64_t n, const slicegcn_layer_desc *desc)
-{
-    const size_t stride = 2 * (size_t)desc->w_in * desc->w_out + 2 * (size_t)desc->w_out;
-    return (size_t)round_up((int64_t)(layer_grad_blocks(n, desc->w_in, desc->w_out) * stride * sizeof(float)), 256);
-}
-static size_t bwd_dz_bytes(int64_t n, const slicegcn_layer_desc *desc)
-{
-    return (size_t)round_up(n * round_up(desc->w_in, 32) * (int64_t)sizeof(float), 256);
+    return fwd_bytes(g, desc);
 }
 
 extern "C" size_t slicegcn_layer_bwd_workspace_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *desc, int need_dHin)
 {
     if (!g || !desc || desc->w_in < 1 || desc->w_out < 1) return 0;
-    if (transform_first(desc)) return tf_bwd_bytes(g, desc);
-    size_t bytes = bwd_partial_bytes(g->n, desc);
-    if (need_dHin) bytes += bwd_dz_bytes(g->n, desc) + spmm_workspace_bytes(g->tr, desc->w_in);
-    return bytes;
+    return bwd_bytes(g, desc, need_dHin != 0, false);
 }
 
 extern "C" int slicegcn_layer_bwd(const slicegcn_graph *g, const slicegcn_layer_desc *desc,
@@ -1906,105 +2222,69 @@ extern "C" int slicegcn_layer_bwd(const slicegcn_graph *g, const slicegcn_layer_
     SG_REQUIRE(ldi >= desc->w_in && ldo >= desc->w_out, SLICEGCN_EINVAL, "layer_bwd: leading dimension too small");
     SG_REQUIRE(dHin == nullptr || ldgi >= desc->w_in, SLICEGCN_EINVAL, "layer_bwd: ldgi < w_in");
     if (int rc = check_saved(desc, saved, "layer_bwd")) return rc;
-    const size_t need = slicegcn_layer_bwd_workspace_bytes(g, desc, dHin != nullptr);
+    const size_t need = bwd_bytes(g, desc, dHin != nullptr, false);
     SG_REQUIRE(ws != nullptr && ws_bytes >= need, SLICEGCN_EWORKSPACE, "layer_bwd: workspace of %zu bytes, %zu needed",
                ws_bytes, need);
     SG_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL, "layer_bwd: workspace not 256-byte aligned");
-    hipStream_t stream = as_stream(stream_);
-    const uint32_t *mask = desc->act == SLICEGCN_ACT_RELU ? saved->mask : nullptr;
-    const int w_in = desc->w_in, w_out = desc->w_out;
-    if (transform_first(desc)) return layer_bwd_transform_first(g, desc, params, Hin, ldi, mask, saved->mask_words, dHout, ldo, dHin, ldgi, grads, ws, stream);
+    const slicegcn_layer_group lg = one_layer(desc, ldi, 0, saved, ldo, ldgi);
+    slicegcn_layer_io io{};
+    io.params = *params; io.Hin = Hin; io.Z = saved->Z; io.mask = saved->mask; io.dHout = dHout; io.dHin = dHin; io.grads = *grads;
+    return layers_bwd(g, &lg, &io, 1, ws, false, as_stream(stream_));
+}
 
-    // ---- input gradient, dense half: dZ = dP W_agg^T (staged, rows scaled by D~^-1/2) and T = dHout W_self^T (into dHin) ----
-    const int64_t ldz_in = round_up(w_in, 32); // rows of the gathered operand start on 128-byte boundaries
-    char *after_partials = static_cast<char *>(ws) + bwd_partial_bytes(g->n, desc);
-    float *dZ = reinterpret_cast<float *>(after_partials);
-    auto input_gradient_args = [&]() {
-        PairArgs a;
-        a.A1 = dHout; a.lda1 = ldo;
-        a.A2 = params->W_self ? dHout : nullptr; a.lda2 = ldo;
-        a.B1 = params->W_agg; a.B2 = params->W_self;
-        a.bias1 = a.bias2 = nullptr;
-        a.O1 = dZ; a.ldo1 = ldz_in;
-        a.O2 = params->W_self ? dHin : nullptr; a.ldo2 = ldgi;
-        a.mask = const_cast<uint32_t *>(mask); a.mask_words = saved->mask_words;
-        a.n = g->n; a.K = w_out; a.Nout = w_in; a.ldw = w_out; a.act = desc->act;
-        a.scale_o1 = g->dinv; // dZ is staged as D~^-1/2 dZ: its aggregation then skips the stored values
-        return a;
-    };
-    // narrow layers with a self term: the kernel that forms the weight gradients also forms dZ and T (one read of dHout)
-    const bool fused_inputs = dHin && params->W_self && w_in <= 32 && w_out <= 32 && g->n >= 65536;
+// ---- the same layer of several slice models -------------------------------------------------
 
-    // ---- parameter gradients: per-row-block partial sums, then an fp64 combination ----
-    float *partial = static_cast<float *>(ws);
-    const int64_t nb = layer_grad_blocks(g->n, w_in, w_out); // partial sums the workspace has room for
-    const int32_t stride = 2 * w_in * w_out + 2 * w_out;
-    {
-        ProfScope prof(SLICEGCN_PROF_GRAD_REDUCE, w_out, stream);
-        ReduceArgs r;
-        r.Z = saved->Z; r.ldz = saved->ldz;
-        r.Hin = params->W_self ? Hin : nullptr; r.ldi = ldi;
-        r.dHout = dHout; r.ldo = ldo;
-        r.mask = mask; r.mask_words = saved->mask_words;
-        r.partial = partial; r.n = g->n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 0;
-        r.rows_per_block = layer_grad_rows(g->n, w_in, w_out);
-        r.hin_scale = (desc->flags & SLICEGCN_LAYER_IN_SCALED) ? g->sqrtd : nullptr;
-        dim3 grid((unsigned)nb, (unsigned)((w_in + RED_TILE - 1) / RED_TILE), (unsigned)((w_out + RED_TILE - 1) / RED_TILE));
-        int64_t n_partials = nb;
-        if (w_in <= 32 && w_out <= 32 && g->n >= 65536) {
-            // one partial per wavefront, at most as many as the workspace has rows (nb) and as fill the chip
-            int64_t waves = nb < 8192 ? nb : 8192;
-            const int64_t n_strips = (g->n + 31) / 32;
-            if (waves > n_strips) waves = n_strips;
-            n_partials = waves;
-            if (fused_inputs) { // weight gradients and the two input-gradient products in one sweep over the rows
-                PairArgs a = input_gradient_args();
-                bwd_strip32_kernel<<<(unsigned)((waves + 3) / 4), 256, 0, stream>>>(r, a, waves);
-            } else {
-                grad_strip32_kernel<<<(unsigned)((waves + 3) / 4), 256, 0, stream>>>(r, waves);
-            }
-        } else if (w_in <= 64 && w_out <= 64 && g->n >= ((int64_t)1 << 21)) {
-            // whole waves of resident workgroups (256 CUs x 3 workgroups x 4 wavefronts) when the workspace allows
-            const int64_t resident = 3072;
-            int64_t waves = nb >= resident ? nb / resident * resident : nb >= 2048 ? 2048 : nb;
-            const int64_t n_strips = (g->n + 7) / 8; // strips of 8 rows in every variant launched here
-            if (waves > n_strips) waves = n_strips;
-            n_partials = waves;
-            const unsigned gb = (unsigned)((waves + 3) / 4);
-            if (w_in <= 32) grad_strip64_kernel<1, 2, 8, 3><<<gb, 256, 0, stream>>>(r, waves);
-            else if (w_out <= 32) grad_strip64_kernel<2, 1, 8, 3><<<gb, 256, 0, stream>>>(r, waves);
-            else grad_strip64_kernel<2, 2, 8, 2><<<gb, 256, 0, stream>>>(r, waves);
-        } else {
-            grad_partial_mfma_kernel<<<grid, 256, 0, stream>>>(r);
-        }
-        SG_LAUNCH_CHECK();
-        FinalDst dst;
-        const int ww = w_in * w_out;
-        dst.ptr[0] = grads->dW_agg;
-        dst.ptr[1] = params->W_self ? grads->dW_self : nullptr;
-        dst.ptr[2] = grads->db;
-        dst.ptr[3] = params->W_self ? grads->db_self : nullptr;
-        dst.begin[0] = 0; dst.begin[1] = ww; dst.begin[2] = 2 * ww; dst.begin[3] = 2 * ww + w_out; dst.begin[4] = stride;
-        reduce_final_kernel<<<(unsigned)((stride + 31) / 32), 1024, 0, stream>>>(partial, n_partials, stride, stride, dst);
-        SG_LAUNCH_CHECK();
+static int check_group(const slicegcn_graph *g, const slicegcn_layer_group *lg, const slicegcn_layer_io *io, bool backward, const char *who)
+{
+    SG_REQUIRE(g && lg && io, SLICEGCN_EINVAL, "%s: NULL graph, group or io", who);
+    SG_REQUIRE(lg->count >= 1 && lg->count <= BATCH, SLICEGCN_EINVAL, "%s: count = %d outside [1, %d]", who, lg->count, BATCH);
+    const slicegcn_layer_desc *d = &lg->desc;
+    for (int i = 0; i < lg->count; ++i) {
+        const slicegcn_layer_io &x = io[i];
+        if (int rc = check_layer(g, d, &x.params, who)) return rc;
+        const slicegcn_layer_saved saved{x.Z, lg->ldz, x.mask, lg->mask_words};
+        if (int rc = check_saved(d, &saved, who)) return rc;
+        SG_REQUIRE(x.Hin && (backward ? x.dHout != nullptr : x.Hout != nullptr), SLICEGCN_EINVAL, "%s: NULL operand", who);
+        SG_REQUIRE((x.params.W_self == nullptr) == (io[0].params.W_self == nullptr) && (x.dHin == nullptr) == (io[0].dHin == nullptr),
+                   SLICEGCN_EINVAL, "%s: slices of a group differ in their terms", who);
+        SG_REQUIRE(x.params.W_self || (!x.enc && !x.denc), SLICEGCN_EINVAL, "%s: encoding without a self term", who);
     }
-
-    // ---- input gradient: dHin = A^^T (dP W_agg^T) + dHout W_self^T ----
-    if (dHin) {
-        void *agg_ws = after_partials + bwd_dz_bytes(g->n, desc);
-        const size_t agg_ws_bytes = spmm_workspace_bytes(g->tr, w_in);
-        const int64_t ldz = ldz_in;
-        if (!fused_inputs) {
-            PairArgs a = input_gradient_args();
-            ProfScope prof(SLICEGCN_PROF_DENSE_BWD, w_in, stream);
-            if (int rc = launch_pair<true>(a, stream)) return rc;
-        }
-        // padding columns of dZ are never read as data: the aggregation masks them on store
-        if (int rc = launch_spmm(g, g->tr, dZ, ldz, w_in, dHin, ldgi, params->W_self ? dHin : nullptr, ldgi, agg_ws, agg_ws_bytes, stream,
-                                 true))
-            return rc;
-    }
+    SG_REQUIRE(lg->ldi >= d->w_in, SLICEGCN_EINVAL, "%s: ldi < w_in", who);
+    if (backward) SG_REQUIRE(lg->ldgo >= d->w_out && (!io[0].dHin || lg->ldgi >= d->w_in), SLICEGCN_EINVAL, "%s: leading dimension too small", who);
+    else SG_REQUIRE(lg->ldo >= d->w_out, SLICEGCN_EINVAL, "%s: ldo < w_out", who);
     return SLICEGCN_OK;
+}
+
+extern "C" size_t slicegcn_layers_fwd_workspace_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *desc, int32_t count)
+{
+    if (!g || !desc || desc->w_in < 1 || desc->w_out < 1 || count < 1) return 0;
+    return (size_t)count * fwd_bytes(g, desc);
+}
+
+extern "C" size_t slicegcn_layers_bwd_workspace_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *desc, int need_dHin, int32_t count)
+{
+    if (!g || !desc || desc->w_in < 1 || desc->w_out < 1 || count < 1) return 0;
+    return (size_t)count * bwd_bytes(g, desc, need_dHin != 0, true);
+}
+
+extern "C" int slicegcn_layers_fwd(const slicegcn_graph *g, const slicegcn_layer_group *group, const slicegcn_layer_io *io,
+                                   void *ws, size_t ws_bytes, void *stream_)
+{
+    if (int rc = check_group(g, group, io, false, "layers_fwd")) return rc;
+    const size_t need = group->count * fwd_bytes(g, &group->desc);
+    SG_REQUIRE(need == 0 || (ws != nullptr && ws_bytes >= need), SLICEGCN_EWORKSPACE, "layers_fwd: workspace of %zu bytes, %zu needed", ws_bytes, need);
+    SG_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL, "layers_fwd: workspace not 256-byte aligned");
+    return layers_fwd(g, group, io, group->count, ws, ws_bytes, as_stream(stream_));
+}
+
+extern "C" int slicegcn_layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *group, const slicegcn_layer_io *io,
+                                   void *ws, size_t ws_bytes, void *stream_)
+{
+    if (int rc = check_group(g, group, io, true, "layers_bwd")) return rc;
+    const size_t need = group->count * bwd_bytes(g, &group->desc, io[0].dHin != nullptr, true);
+    SG_REQUIRE(ws != nullptr && ws_bytes >= need, SLICEGCN_EWORKSPACE, "layers_bwd: workspace of %zu bytes, %zu needed", ws_bytes, need);
+    SG_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL, "layers_bwd: workspace not 256-byte aligned");
+    return layers_bwd(g, group, io, group->count, ws, true, as_stream(stream_));
 }
 
 // ---- dense layer Y = act(X W + b): the unit of the paper's classifier MLP_CLS and of MLP_FF ----
@@ -2034,7 +2314,14 @@ extern "C" int slicegcn_linear_fwd(const float *X, int64_t ldx, int64_t n, int32
 extern "C" size_t slicegcn_linear_bwd_workspace_bytes(int64_t n, int32_t w_in, int32_t w_out)
 {
     if (n < 1 || w_in < 1 || w_out < 1) return 0;
-    return linear_partial_bytes(n, w_in, w_out);
+    return linear_partial_bytes(red_blocks(n), w_in, w_out);
+}
+
+extern "C" size_t slicegcn_linear_bwd_full_workspace_bytes(int64_t n, int32_t w_in, int32_t w_out)
+{
+    if (n < 1 || w_in < 1 || w_out < 1) return 0;
+    const size_t a = linear_partial_bytes(red_blocks(n), w_in, w_out), b = linear_full_bytes(n, w_in, w_out);
+    return a > b ? a : b;
 }
 
 extern "C" int slicegcn_linear_bwd(const float *X, int64_t ldx, int64_t n, int32_t w_in, int32_t w_out, const float *W,
@@ -2052,12 +2339,13 @@ extern "C" int slicegcn_linear_bwd(const float *X, int64_t ldx, int64_t n, int32
     hipStream_t stream = as_stream(stream_);
     const uint32_t *m = act == SLICEGCN_ACT_RELU ? mask : nullptr;
     if (dW || db) {
-        const size_t need = linear_partial_bytes(n, w_in, w_out);
+        const size_t need = linear_partial_bytes(red_blocks(n), w_in, w_out);
         SG_REQUIRE(ws != nullptr && ws_bytes >= need, SLICEGCN_EWORKSPACE, "linear_bwd: workspace of %zu bytes, %zu needed",
                    ws_bytes, need);
         SG_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL, "linear_bwd: workspace not 256-byte aligned");
         ProfScope prof(SLICEGCN_PROF_LINEAR_GRAD, w_out, stream);
-        if (int rc = launch_linear_grads(X, ldx, n, w_in, w_out, m, mask_words, dY, lddy, dW, db, ws, stream)) return rc;
+        const LinearGradArgs args{X, m, dY, dW, db};
+        if (int rc = launch_linear_grads(&args, 1, ldx, n, w_in, w_out, mask_words, lddy, ws, ws_bytes, stream)) return rc;
     }
     if (dX) {
         PairArgs a;

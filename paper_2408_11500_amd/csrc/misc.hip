@@ -123,9 +123,11 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(const float *src, int64
     }
 }
 
-// dst[r, c] += src[r, c] for c < w; 16 bytes per thread when VEC (aligned bases, lds and w multiples of 4).
+// dst[r, c] += srcs[0][r, c], then srcs[1][r, c], ... for c < w; 16 bytes per thread when VEC (aligned bases, ld and w
+// multiples of 4).
+struct SumSources { const float *p[SLICEGCN_MAX_GROUP]; };
 template <bool VEC>
-__global__ __launch_bounds__(256) void accumulate_kernel(float *__restrict__ dst, int64_t ldd, const float *__restrict__ src,
+__global__ __launch_bounds__(256) void accumulate_kernel(float *__restrict__ dst, int64_t ldd, const SumSources src, int count,
                                                          int64_t lds_, int64_t n, int32_t w)
 {
     const int q = VEC ? w >> 2 : w; // elements (float4 or float) per row
@@ -135,11 +137,15 @@ __global__ __launch_bounds__(256) void accumulate_kernel(float *__restrict__ dst
         const int c = (int)(t - r * q);
         if (VEC) {
             float4 d = *reinterpret_cast<const float4 *>(dst + r * ldd + 4 * c);
-            const float4 v = *reinterpret_cast<const float4 *>(src + r * lds_ + 4 * c);
-            d.x += v.x; d.y += v.y; d.z += v.z; d.w += v.w;
+            for (int i = 0; i < count; ++i) {
+                const float4 v = *reinterpret_cast<const float4 *>(src.p[i] + r * lds_ + 4 * c);
+                d.x += v.x; d.y += v.y; d.z += v.z; d.w += v.w;
+            }
             *reinterpret_cast<float4 *>(dst + r * ldd + 4 * c) = d;
         } else {
-            dst[r * ldd + c] += src[r * lds_ + c];
+            float d = dst[r * ldd + c];
+            for (int i = 0; i < count; ++i) d += src.p[i][r * lds_ + c];
+            dst[r * ldd + c] = d;
         }
     }
 }
@@ -185,16 +191,29 @@ int launch_copy_cols(const float *src, int64_t lds_, float *dst, int64_t ldd, in
 
 using namespace slicegcn;
 
-extern "C" int slicegcn_accumulate(float *dst, int64_t ldd, const float *src, int64_t lds_, int64_t n, int32_t w, void *stream)
+extern "C" int slicegcn_accumulate_many(float *dst, int64_t ldd, const float *const *srcs, int32_t count, int64_t lds_, int64_t n,
+                                        int32_t w, void *stream)
 {
-    SG_REQUIRE(dst && src, SLICEGCN_EINVAL, "accumulate: NULL pointer");
+    SG_REQUIRE(dst && srcs, SLICEGCN_EINVAL, "accumulate: NULL pointer");
+    SG_REQUIRE(count >= 1 && count <= SLICEGCN_MAX_GROUP, SLICEGCN_EINVAL, "accumulate: count = %d outside [1, %d]", count, SLICEGCN_MAX_GROUP);
     SG_REQUIRE(n >= 1 && w >= 1 && ldd >= w && lds_ >= w, SLICEGCN_EINVAL, "accumulate: sizes or leading dimensions too small");
+    bool vec = aligned16(dst) && ldd % 4 == 0 && lds_ % 4 == 0 && w % 4 == 0;
+    SumSources s;
+    for (int i = 0; i < SLICEGCN_MAX_GROUP; ++i) {
+        s.p[i] = srcs[i < count ? i : 0];
+        SG_REQUIRE(s.p[i] != nullptr, SLICEGCN_EINVAL, "accumulate: NULL pointer");
+        vec = vec && aligned16(s.p[i]);
+    }
     ProfScope prof(SLICEGCN_PROF_ACCUM, w, as_stream(stream));
-    const bool vec = aligned16(dst) && aligned16(src) && ldd % 4 == 0 && lds_ % 4 == 0 && w % 4 == 0;
-    if (vec) accumulate_kernel<true><<<grid_for(n * (w / 4)), 256, 0, as_stream(stream)>>>(dst, ldd, src, lds_, n, w);
-    else accumulate_kernel<false><<<grid_for(n * (int64_t)w), 256, 0, as_stream(stream)>>>(dst, ldd, src, lds_, n, w);
+    if (vec) accumulate_kernel<true><<<grid_for(n * (w / 4)), 256, 0, as_stream(stream)>>>(dst, ldd, s, count, lds_, n, w);
+    else accumulate_kernel<false><<<grid_for(n * (int64_t)w), 256, 0, as_stream(stream)>>>(dst, ldd, s, count, lds_, n, w);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
+}
+
+extern "C" int slicegcn_accumulate(float *dst, int64_t ldd, const float *src, int64_t lds_, int64_t n, int32_t w, void *stream)
+{
+    return slicegcn_accumulate_many(dst, ldd, &src, 1, lds_, n, w, stream);
 }
 
 extern "C" int slicegcn_adam_step(float *param, const float *grad, float *m, float *v, int64_t count, double lr, double beta1,

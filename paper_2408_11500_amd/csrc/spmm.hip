@@ -47,27 +47,54 @@ struct SpmmArgs {
     const Segment *items;
     const FixRow *fix;
     const int32_t *order; // row at every position of the schedule (NULL: natural order), for the short rows
-    const float *X;
-    float *Y;
-    const float *Add;
     const float *dinv;    // factored form only: X rows come pre-scaled by dinv[u], sums are scaled by dinv[row] on store
     float *scratch;
+    int64_t scratch_stride; // floats of partial-sum slots per operand of the batch
     int64_t ldx, ldy, ldadd;
     uint32_t ldx_bytes;   // S32 kernels: byte stride of X rows (n * ldx * 4 < 2^32, n and ldx * 4 < 2^24)
     int32_t n;
     int32_t item_max;     // longest lane-group item of the schedule (ITEM_SHORT or ITEM_LONG)
-    int32_t ipw;          // wavefront items per wavefront (one-launch kernel: 4; otherwise 1); a workgroup takes 4 * ipw
+    int32_t ipw;          // wavefront items per wavefront (1 to 4 in the one-launch kernel, otherwise 1); a workgroup takes 4 * ipw
+    int32_t rounds;       // lane-group items per lane group (1 to 8)
+    int32_t tiny_rounds;  // short rows per lane group (2, 4, 6 or 8)
     int32_t big_blocks;   // workgroups per class in the wavefront-item section
     int32_t small_blocks; // workgroups per class in the lane-group-item section
     int32_t slot_cols;    // floats per partial-sum slot
-    int32_t col0;         // first column of this pass
-    int32_t col_end;      // one past the last column of this pass (<= width)
+    int32_t col0;         // first column of this launch
+    int32_t col_end;      // one past its last column (<= width)
     int32_t load_max;     // ragged rows (RAG kernels): last column a 16-byte load may start at; 0: rows end on a whole vector
     int32_t big_off[N_CLASSES], big_cnt[N_CLASSES];     // wavefront pieces of class c
     int32_t small_off[N_CLASSES], small_cnt[N_CLASSES]; // lane-group pieces of class c
     int32_t wbig_off, wbig_cnt;     // wavefront items of rows kept whole (dealt to the classes four at a time)
     int32_t wsmall_off, wsmall_cnt; // lane-group whole rows (dealt one wavefront's share at a time)
 };
+
+// The operands of one launch: a batch of slices aggregated over the same graph (workgroups of grid row y work on slice y).
+constexpr int MAX_BATCH = SPMM_BATCH;
+struct SpmmBatch {
+    const float *X[MAX_BATCH];
+    float *Y[MAX_BATCH];
+    const float *Add[MAX_BATCH];
+};
+
+// What a workgroup works on: one slice of the batch and one pass of columns.
+struct SpmmIo {
+    const float *X;
+    float *Y;
+    const float *Add;
+    float *scratch;
+    int32_t col0, col_end; // columns [col0, col_end) of the operand
+};
+__device__ inline SpmmIo pick_io(const SpmmArgs &a, const SpmmBatch &b)
+{
+    const int y = blockIdx.y;
+    SpmmIo io;
+    io.X = b.X[y]; io.Y = b.Y[y]; io.Add = b.Add[y];
+    io.scratch = a.scratch + y * a.scratch_stride;
+    io.col0 = a.col0 + (int32_t)blockIdx.z * PASS_COLS; // grid depth: passes of PASS_COLS columns in one launch
+    io.col_end = io.col0 + PASS_COLS < a.col_end ? io.col0 + PASS_COLS : a.col_end;
+    return io;
+}
 
 template <int V> struct Acc;
 // 16-byte accesses at any 4-byte boundary
@@ -125,13 +152,13 @@ template <> struct Ld<1> {
 // within 4 GiB of its base and both factors fit 24 bits, so one 24-bit multiply-add gives an
 // unsigned 32-bit byte offset from the (wavefront-uniform) base pointer.
 template <int V, bool S32>
-__device__ inline typename Ld<V>::T load_x(const SpmmArgs &a, int c, int col)
+__device__ inline typename Ld<V>::T load_x(const SpmmArgs &a, const float *X, int c, int col)
 {
     if (S32) {
         const uint32_t off = __umul24((uint32_t)c, a.ldx_bytes) + (uint32_t)col * 4u;
-        return Ld<V>::load(reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.X) + off));
+        return Ld<V>::load(reinterpret_cast<const float *>(reinterpret_cast<const char *>(X) + off));
     }
-    return Ld<V>::load(a.X + (int64_t)c * a.ldx + col);
+    return Ld<V>::load(X + (int64_t)c * a.ldx + col);
 }
 
 // Factored form (FACT): the operand rows already carry dinv[u], so every stored entry weighs 1 (the value stream is
@@ -158,9 +185,9 @@ template <> __device__ inline Acc<1> shfl_xor_acc<1>(const Acc<1> &a, int mask)
 
 // Columns of the operand the lane that owns columns [col, col + V) loads (the lane's own, or the row's last four
 // where its own would reach past the row; lanes beyond the pass load what the first lane does and drop it).
-template <bool RAG> __device__ inline int load_col(const SpmmArgs &a, int col)
+template <bool RAG> __device__ inline int load_col(const SpmmArgs &a, const SpmmIo &io, int col)
 {
-    const int c = col < a.col_end ? col : a.col0;
+    const int c = col < io.col_end ? col : io.col0;
     return RAG && c > a.load_max ? a.load_max : c;
 }
 
@@ -188,7 +215,7 @@ __device__ inline void store_cols(const Acc<V> &acc, float *y_row, const float *
 // full chunk (cnt >= 64) runs without any per-entry test.  Every lane of the wavefront must call
 // this (lanes past the last column pass a valid `col` and drop their result).
 template <int LPR, int V, bool S32, bool FACT>
-__device__ inline void gather_chunk(Acc<V> &acc, const SpmmArgs &a, int c_l, float v_l, int cnt, int grp, int col)
+__device__ inline void gather_chunk(Acc<V> &acc, const SpmmArgs &a, const SpmmIo &io, int c_l, float v_l, int cnt, int grp, int col)
 {
     constexpr int G = 64 / LPR; // lane groups = entries per sub-step
     constexpr int U = 8;        // gathers in flight per lane
@@ -207,7 +234,7 @@ __device__ inline void gather_chunk(Acc<V> &acc, const SpmmArgs &a, int c_l, flo
                 v[u] = shfl_val<FACT>(v_l, (t + u) * G + grp);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, c[u], col);
+            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], col);
 #pragma unroll
             for (int u = 0; u < U; ++u) acc.fma(v[u], x[u]);
         }
@@ -223,7 +250,7 @@ __device__ inline void gather_chunk(Acc<V> &acc, const SpmmArgs &a, int c_l, flo
                 v[u] = shfl_val<FACT>(v_l, src);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, c[u], col);
+            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], col);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if ((t + u) * G + grp < cnt) acc.fma(v[u], x[u]);
@@ -233,31 +260,33 @@ __device__ inline void gather_chunk(Acc<V> &acc, const SpmmArgs &a, int c_l, flo
 
 // Write an item's (or a row's) sum: to the output row, or to its partial-sum slot.
 template <int V, bool RAG>
-__device__ inline void store_result(Acc<V> acc, const SpmmArgs &a, int row, int dst, int col)
+__device__ inline void store_result(Acc<V> acc, const SpmmArgs &a, const SpmmIo &io, int row, int dst, int col)
 {
-    if (RAG) acc.shift(col - load_col<RAG>(a, col));
+    if (RAG) acc.shift(col - load_col<RAG>(a, io, col));
     if (dst >= 0) {
         if (a.dinv) acc.scale(a.dinv[row]); // factored form: the row's own factor (partial sums stay unscaled)
-        store_cols<V>(acc, a.Y + (int64_t)row * a.ldy, a.Add ? a.Add + (int64_t)row * a.ldadd : nullptr, col, a.col_end);
+        store_cols<V>(acc, io.Y + (int64_t)row * a.ldy, io.Add ? io.Add + (int64_t)row * a.ldadd : nullptr, col, io.col_end);
     } else {
-        float *p = a.scratch + (int64_t)(-(dst + 1)) * a.slot_cols - a.col0; // slot row, pass-relative columns
-        store_cols<V>(acc, p, nullptr, col, a.col_end);
+        float *p = io.scratch + (int64_t)(-(dst + 1)) * a.slot_cols - a.col0;
+        store_cols<V>(acc, p, nullptr, col, io.col_end);
     }
 }
 
 constexpr int NO_UNIT = INT32_MIN;
+constexpr int64_t SMALL_GRID = 1024; // workgroups of one kind a cache-resident graph is cut into before runs grow
 
 // One gather phase of the tiny-row path: sub-round t hands unit (t * GROUPS + grp) of the wavefront
 // to lane group grp.  c_l / v_l hold, per lane, four (column, value) pairs of the unit that lane
 // owns (column -1 = no entry).  Two sub-rounds (eight gathers per lane) are in flight at a time.
 template <int LPR, int V, bool S32, bool FACT>
-__device__ inline void batch_gather(Acc<V> (&acc)[8], const SpmmArgs &a, const int (&c_l)[4], const float (&v_l)[4],
+__device__ inline void batch_gather(Acc<V> (&acc)[8], const SpmmArgs &a, const SpmmIo &io, const int (&c_l)[4], const float (&v_l)[4],
                                     int grp, int colc)
 {
     constexpr int G = 64 / LPR;
     using L = Ld<V>;
 #pragma unroll
     for (int t0 = 0; t0 < 8; t0 += 2) {
+        if (t0 >= a.tiny_rounds) break; // uniform
         int cc[2][4];
         float vv[2][4];
 #pragma unroll
@@ -273,7 +302,7 @@ __device__ inline void batch_gather(Acc<V> (&acc)[8], const SpmmArgs &a, const i
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int c = cc[u][i] >= 0 ? cc[u][i] : 0; // an absent entry re-reads row 0 and is not accumulated
-                x[u][i] = load_x<V, S32>(a, c, colc);
+                x[u][i] = load_x<V, S32>(a, io.X, c, colc);
             }
 #pragma unroll
         for (int u = 0; u < 2; ++u)
@@ -283,17 +312,17 @@ __device__ inline void batch_gather(Acc<V> (&acc)[8], const SpmmArgs &a, const i
     }
 }
 
-// Rows of at most TINY_ROW (= 4) entries: 8 * GROUPS rows per wavefront.  Lane i owns row i
+// Rows of at most TINY_ROW (= 4) entries: tiny_rounds * GROUPS rows per wavefront.  Lane i owns row i
 // (entries [beg_l, end_l), destination dst_l, NO_UNIT = nothing) and loads its entries; the gather
 // phase hands them to the lane groups.  Every lane of the wavefront must call this.
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__device__ inline void batch_units(const SpmmArgs &a, int beg_l, int end_l, int row_l, int dst_l, int lane)
+__device__ inline void batch_units(const SpmmArgs &a, const SpmmIo &io, int beg_l, int end_l, int row_l, int dst_l, int lane)
 {
     constexpr int G = 64 / LPR;
     const int grp = lane / LPR, sub = lane % LPR;
-    const int col = a.col0 + sub * V;
-    const bool col_ok = col < a.col_end;
-    const int colc = load_col<RAG>(a, col);
+    const int col = io.col0 + sub * V;
+    const bool col_ok = col < io.col_end;
+    const int colc = load_col<RAG>(a, io, col);
     Acc<V> acc[8];
     int c_l[4];
     float v_l[4];
@@ -304,12 +333,13 @@ __device__ inline void batch_units(const SpmmArgs &a, int beg_l, int end_l, int 
         c_l[i] = ok ? a.colidx[idx] : -1;
         v_l[i] = ok ? ld_val<FACT>(a, idx) : 0.f;
     }
-    batch_gather<LPR, V, S32, FACT>(acc, a, c_l, v_l, grp, colc);
+    batch_gather<LPR, V, S32, FACT>(acc, a, io, c_l, v_l, grp, colc);
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
+        if (t >= a.tiny_rounds) break; // uniform
         const int d = __shfl(dst_l, t * G + grp, 64);
         const int r = __shfl(row_l, t * G + grp, 64);
-        if (d != NO_UNIT && col_ok) store_result<V, RAG>(acc[t], a, r, d, col);
+        if (d != NO_UNIT && col_ok) store_result<V, RAG>(acc[t], a, io, r, d, col);
     }
 }
 
@@ -320,7 +350,7 @@ __device__ inline void batch_units(const SpmmArgs &a, int beg_l, int end_l, int 
 // wavefront several items and prefetching across them was measured and changes nothing: the
 // kernel is bound by the traffic of the gathers, not by the latency of its index loads.)
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
+__device__ __forceinline__ void wave_items_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int cls = block % N_CLASSES, j = block / N_CLASSES;
@@ -337,9 +367,9 @@ __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
     }
     const int4 s = *reinterpret_cast<const int4 *>(a.items + item);
     const int grp = lane / LPR, sub = lane % LPR;
-    const int col = a.col0 + sub * V;
-    const bool active = col < a.col_end;
-    const int colc = load_col<RAG>(a, col);
+    const int col = io.col0 + sub * V;
+    const bool active = col < io.col_end;
+    const int colc = load_col<RAG>(a, io, col);
     const int beg = s.y, end = s.z;
     Acc<V> acc;
     int idx = beg + lane;
@@ -353,13 +383,13 @@ __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
             c_n = a.colidx[idx < end ? idx : beg];
             v_n = ld_val<FACT>(a, idx < end ? idx : beg);
         }
-        gather_chunk<LPR, V, S32, FACT>(acc, a, c_l, v_l, end - base, grp, colc);
+        gather_chunk<LPR, V, S32, FACT>(acc, a, io, c_l, v_l, end - base, grp, colc);
         c_l = c_n;
         v_l = v_n;
     }
 #pragma unroll
     for (int m = LPR; m < 64; m <<= 1) acc.add(shfl_xor_acc<V>(acc, m));
-    if (grp == 0 && active) store_result<V, RAG>(acc, a, s.x, s.w, col);
+    if (grp == 0 && active) store_result<V, RAG>(acc, a, io, s.x, s.w, col);
 }
 
 // The same for graphs that stay in cache (the one-launch kernel below): a workgroup takes 4 * ipw consecutive items,
@@ -368,7 +398,7 @@ __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, int block)
 // (descriptor -> entries -> gathers), which this overlaps across items: 0.049 -> 0.043 ms per call at 2.5 M entries.  On
 // graphs that stream from memory it changes nothing and its eight extra registers cost 2 %, so they keep one item per wavefront.
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block)
+__device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int cls = block % N_CLASSES, j = block / N_CLASSES;
@@ -388,9 +418,9 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block
     int t = wave; // this wavefront takes items wave, wave + 4, ... of the workgroup's run
     if (t >= cnt) return;
     const int grp = lane / LPR, sub = lane % LPR;
-    const int col = a.col0 + sub * V;
-    const bool active = col < a.col_end;
-    const int colc = load_col<RAG>(a, col);
+    const int col = io.col0 + sub * V;
+    const bool active = col < io.col_end;
+    const int colc = load_col<RAG>(a, io, col);
     int4 s = *reinterpret_cast<const int4 *>(a.items + first + t);
     int idx = s.y + lane;
     int c_l = a.colidx[idx < s.z ? idx : s.y];
@@ -415,13 +445,13 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block
                 c_n = a.colidx[idx < sn.z ? idx : sn.y];
                 v_n = ld_val<FACT>(a, idx < sn.z ? idx : sn.y);
             }
-            gather_chunk<LPR, V, S32, FACT>(acc, a, c_l, v_l, end - base, grp, colc);
+            gather_chunk<LPR, V, S32, FACT>(acc, a, io, c_l, v_l, end - base, grp, colc);
             c_l = c_n;
             v_l = v_n;
         }
 #pragma unroll
         for (int m = LPR; m < 64; m <<= 1) acc.add(shfl_xor_acc<V>(acc, m));
-        if (grp == 0 && active) store_result<V, RAG>(acc, a, s.x, s.w, col);
+        if (grp == 0 && active) store_result<V, RAG>(acc, a, io, s.x, s.w, col);
         if (!more) break;
         s = sn;
         t += 4;
@@ -429,7 +459,7 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block
 }
 
 // Lane-group items (whole rows and class pieces of 5..GI_MAX entries, GI_MAX = the schedule's item_max):
-// workgroup b serves class b mod 8 and takes a run of 32 * G consecutive items of its list (first the
+// workgroup b serves class b mod 8 and takes a run of 4 * G * rounds consecutive items of its list (first the
 // class's own pieces, then every eighth run of the whole rows).  In round r its four wavefronts work on
 // 4 * G consecutive items of the run, lane group grp of wavefront w on item r * 4 * G + w * G + grp (lane
 // r * G + grp holds that item's descriptor).  The group
@@ -437,14 +467,13 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, int block
 // sub, sub + LPR, ...; the next round's pairs are requested before this round's gathers), and each
 // gather takes its pair from the holding lane by a cross-lane read, eight gathers in flight.
 template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG>
-__device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
+__device__ __forceinline__ void group_items_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
     constexpr int G = 64 / LPR;                 // items in flight per wavefront
-    constexpr int UNITS = 8 * G;                // items per wavefront
     constexpr int K = LPR >= GI_MAX ? 1 : GI_MAX / LPR; // index registers per lane (K * LPR >= GI_MAX entries)
     constexpr int U = 8;
     using L = Ld<V>;
-    constexpr int RUN = 4 * UNITS;              // items per workgroup: one run of consecutive items of its list
+    const int RUN = 4 * G * a.rounds;           // items per workgroup: one run of consecutive items of its list
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int cls = block % N_CLASSES, blk = block / N_CLASSES;
     const int piece_blocks = (a.small_cnt[cls] + RUN - 1) / RUN;
@@ -470,9 +499,9 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
         if (lane < 8 * G && q < run) d = *reinterpret_cast<const int4 *>(a.items + first + q);
     }
     const int grp = lane / LPR, sub = lane % LPR, gbase = lane - sub;
-    const int col = a.col0 + sub * V;
-    const bool col_ok = col < a.col_end;
-    const int colc = load_col<RAG>(a, col);
+    const int col = io.col0 + sub * V;
+    const bool col_ok = col < io.col_end;
+    const int colc = load_col<RAG>(a, io, col);
     int beg = __shfl(d.y, grp, 64), end = __shfl(d.z, grp, 64);
     int c_k[K];
     float v_k[K];
@@ -512,12 +541,12 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
                 c[u] = jj < len ? cc : 0; // an absent entry re-reads row 0 and is not accumulated
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, c[u], colc);
+            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], colc);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (j0 + u < len) acc.fma(v[u], x[u]);
         }
-        if (dst != NO_UNIT && col_ok) store_result<V, RAG>(acc, a, row, dst, col);
+        if (dst != NO_UNIT && col_ok) store_result<V, RAG>(acc, a, io, row, dst, col);
         beg = nbeg;
         end = nend;
 #pragma unroll
@@ -525,32 +554,32 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, int block)
     }
 }
 
-// Rows of at most TINY_ROW entries, 64 consecutive positions of the schedule per wavefront (consecutive
+// Rows of at most TINY_ROW entries, up to 64 consecutive positions of the schedule per wavefront (consecutive
 // rows in natural order).
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__device__ __forceinline__ void tiny_rows_body(const SpmmArgs &a, int block)
+__device__ __forceinline__ void tiny_rows_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
-    constexpr int UNITS = 8 * (64 / LPR); // rows per wavefront
+    const int units = a.tiny_rounds * (64 / LPR); // rows per wavefront
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int first = (block * 4 + wave) * UNITS;
+    const int first = (block * 4 + wave) * units;
     if (first >= a.n) return; // uniform per wavefront
     int beg_l = 0, end_l = 0, row_l = 0, dst_l = NO_UNIT;
-    if (lane < UNITS && first + lane < a.n) {
+    if (lane < units && first + lane < a.n) {
         const int row = a.order ? a.order[first + lane] : first + lane;
         const int b = a.rowptr[row], e = a.rowptr[row + 1];
         if (e - b <= TINY_ROW) { row_l = row; beg_l = b; end_l = e; dst_l = row; }
     }
-    batch_units<LPR, V, S32, FACT, RAG>(a, beg_l, end_l, row_l, dst_l, lane);
+    batch_units<LPR, V, S32, FACT, RAG>(a, io, beg_l, end_l, row_l, dst_l, lane);
 }
 
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_wave_items_kernel(const SpmmArgs a) { wave_items_body<LPR, V, S32, FACT, RAG>(a, blockIdx.x); }
+__global__ __launch_bounds__(256) void spmm_wave_items_kernel(const SpmmArgs a, const SpmmBatch b) { const SpmmIo io = pick_io(a, b); wave_items_body<LPR, V, S32, FACT, RAG>(a, io, blockIdx.x); }
 
 template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_group_items_kernel(const SpmmArgs a) { group_items_body<LPR, V, S32, GI_MAX, FACT, RAG>(a, blockIdx.x); }
+__global__ __launch_bounds__(256) void spmm_group_items_kernel(const SpmmArgs a, const SpmmBatch b) { const SpmmIo io = pick_io(a, b); group_items_body<LPR, V, S32, GI_MAX, FACT, RAG>(a, io, blockIdx.x); }
 
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a) { tiny_rows_body<LPR, V, S32, FACT, RAG>(a, blockIdx.x); }
+__global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a, const SpmmBatch b) { const SpmmIo io = pick_io(a, b); tiny_rows_body<LPR, V, S32, FACT, RAG>(a, io, blockIdx.x); }
 
 // All three item kinds in one launch: workgroups [0, g1) take wavefront items, [g1, g1 + g2)
 // lane-group items, the rest tiny rows (g1 and g2 are multiples of 8, so workgroup b still
@@ -559,25 +588,27 @@ __global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a) {
 // they overlap (cfg2: 0.075 -> 0.056 ms per call).  Large graphs keep the three launches: there the
 // class pieces must have the L2s to themselves before the whole rows start (merged: cfg5 4.09 -> 4.30 ms).
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_merged_kernel(const SpmmArgs a, int g1, int g2)
+__global__ __launch_bounds__(256) void spmm_merged_kernel(const SpmmArgs a, const SpmmBatch batch, int g1, int g2)
 {
+    const SpmmIo io = pick_io(a, batch);
     const int b = blockIdx.x; // uniform per workgroup
-    if (b < g1) wave_items_run_body<LPR, V, S32, FACT, RAG>(a, b);
-    else if (b < g1 + g2) group_items_body<LPR, V, S32, ITEM_SHORT, FACT, RAG>(a, b - g1);
-    else tiny_rows_body<LPR, V, S32, FACT, RAG>(a, b - g1 - g2);
+    if (b < g1) wave_items_run_body<LPR, V, S32, FACT, RAG>(a, io, b);
+    else if (b < g1 + g2) group_items_body<LPR, V, S32, ITEM_SHORT, FACT, RAG>(a, io, b - g1);
+    else tiny_rows_body<LPR, V, S32, FACT, RAG>(a, io, b - g1 - g2);
 }
 
 // Rows with several items: add the partial slots in order.  One thread per (row, column); eight
 // independent slot reads are in flight at a time, the additions stay in slot order.
-__global__ __launch_bounds__(256) void spmm_fix_kernel(const SpmmArgs a, int32_t n_fix)
+__global__ __launch_bounds__(256) void spmm_fix_kernel(const SpmmArgs a, const SpmmBatch b, int32_t n_fix)
 {
+    const SpmmIo io = pick_io(a, b);
     const int w = a.col_end - a.col0;
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t r = t / w;
     if (r >= n_fix) return;
     const int j = (int)(t - r * w);
     const int4 f = *reinterpret_cast<const int4 *>(a.fix + r);
-    const float *p = a.scratch + j;
+    const float *p = io.scratch + j;
     float acc = 0.f;
     int s = f.y;
     for (; s + 8 <= f.z; s += 8) {
@@ -590,136 +621,162 @@ __global__ __launch_bounds__(256) void spmm_fix_kernel(const SpmmArgs a, int32_t
     for (; s < f.z; ++s) acc += p[(int64_t)s * a.slot_cols];
     if (a.dinv) acc *= a.dinv[f.x]; // factored form: the row's own factor
     const int col = a.col0 + j;
-    if (a.Add) acc += a.Add[(int64_t)f.x * a.ldadd + col];
-    a.Y[(int64_t)f.x * a.ldy + col] = acc;
+    if (io.Add) acc += io.Add[(int64_t)f.x * a.ldadd + col];
+    io.Y[(int64_t)f.x * a.ldy + col] = acc;
 }
 
+// `batch`: slices aggregated in this launch; `passes`: column passes in this launch (the one-launch kernel only)
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-int launch_variant(const SpmmArgs &a, hipStream_t stream)
+int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, hipStream_t stream)
 {
-    constexpr int units_per_block = 4 * 8 * (64 / LPR);
+    const int64_t units_per_block = 4 * a.tiny_rounds * (64 / LPR);
     const int64_t g1 = (int64_t)N_CLASSES * a.big_blocks;
     const int64_t g2 = (int64_t)N_CLASSES * a.small_blocks;
     const int64_t g3 = (a.n + units_per_block - 1) / units_per_block;
-    SG_REQUIRE(g1 <= INT32_MAX && g2 <= INT32_MAX && g3 <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
+    SG_REQUIRE(g1 + g2 + g3 + N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
     if (a.item_max <= ITEM_SHORT) { // cache-resident graph: one launch (big_blocks counts runs of 4 * ipw items)
-        SG_REQUIRE(g1 + g2 + g3 <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
-        spmm_merged_kernel<LPR, V, S32, FACT, RAG><<<(unsigned)(g1 + g2 + g3), 256, 0, stream>>>(a, (int)g1, (int)g2);
+        // the grid's first dimension is a multiple of 8, so that a class meets the same XCD in every slice and pass
+        const dim3 grid((unsigned)round_up(g1 + g2 + g3, N_CLASSES), (unsigned)batch, (unsigned)passes);
+        spmm_merged_kernel<LPR, V, S32, FACT, RAG><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2);
         SG_LAUNCH_CHECK();
         return SLICEGCN_OK;
     }
     if (g1 > 0) {
-        spmm_wave_items_kernel<LPR, V, S32, FACT, RAG><<<(unsigned)g1, 256, 0, stream>>>(a);
+        spmm_wave_items_kernel<LPR, V, S32, FACT, RAG><<<dim3((unsigned)g1, (unsigned)batch), 256, 0, stream>>>(a, b);
         SG_LAUNCH_CHECK();
     }
     if (g2 > 0) {
-        spmm_group_items_kernel<LPR, V, S32, ITEM_LONG, FACT, RAG><<<(unsigned)g2, 256, 0, stream>>>(a);
+        spmm_group_items_kernel<LPR, V, S32, ITEM_LONG, FACT, RAG><<<dim3((unsigned)g2, (unsigned)batch), 256, 0, stream>>>(a, b);
         SG_LAUNCH_CHECK();
     }
-    spmm_tiny_rows_kernel<LPR, V, S32, FACT, RAG><<<(unsigned)g3, 256, 0, stream>>>(a);
+    spmm_tiny_rows_kernel<LPR, V, S32, FACT, RAG><<<dim3((unsigned)g3, (unsigned)batch), 256, 0, stream>>>(a, b);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
 }
 
 template <int LPR, int V, bool FACT>
-int launch_layout(const SpmmArgs &a, hipStream_t stream)
+int launch_layout(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, hipStream_t stream)
 {
-    if constexpr (V == 1) return launch_variant<LPR, V, false, FACT, false>(a, stream);
+    if constexpr (V == 1) return launch_variant<LPR, V, false, FACT, false>(a, b, batch, passes, stream);
     else {
         if (a.load_max > 0)
-            return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, true>(a, stream) : launch_variant<LPR, V, false, FACT, true>(a, stream);
-        return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, false>(a, stream) : launch_variant<LPR, V, false, FACT, false>(a, stream);
+            return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, true>(a, b, batch, passes, stream)
+                                    : launch_variant<LPR, V, false, FACT, true>(a, b, batch, passes, stream);
+        return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, false>(a, b, batch, passes, stream)
+                                : launch_variant<LPR, V, false, FACT, false>(a, b, batch, passes, stream);
     }
 }
 
 template <int LPR, int V>
-int launch_kernels(const SpmmArgs &a, hipStream_t stream)
+int launch_kernels(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, hipStream_t stream)
 {
-    return a.dinv ? launch_layout<LPR, V, true>(a, stream) : launch_layout<LPR, V, false>(a, stream);
+    return a.dinv ? launch_layout<LPR, V, true>(a, b, batch, passes, stream) : launch_layout<LPR, V, false>(a, b, batch, passes, stream);
 }
 
-int launch_pass(const SpmmArgs &a, int v, int lpr, hipStream_t stream)
+int launch_pass(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, int v, int lpr, hipStream_t stream)
 {
-    if (v == 1) return launch_kernels<8, 1>(a, stream); // fewer than 4 columns
+    if (v == 1) return launch_kernels<8, 1>(a, b, batch, passes, stream); // fewer than 4 columns
     switch (lpr) {
-    case 8: return launch_kernels<8, 4>(a, stream);
-    case 16: return launch_kernels<16, 4>(a, stream);
-    default: return launch_kernels<32, 4>(a, stream); // a pass is at most 128 columns
+    case 8: return launch_kernels<8, 4>(a, b, batch, passes, stream);
+    case 16: return launch_kernels<16, 4>(a, b, batch, passes, stream);
+    default: return launch_kernels<32, 4>(a, b, batch, passes, stream); // a pass is at most 128 columns
     }
 }
 
 } // namespace
 
-// Bytes of partial-sum workspace an aggregation of `width` columns over pattern `m` needs: one slot of
-// min(width rounded up to 4, columns per pass) floats per item of every row cut into several items.
-size_t spmm_workspace_bytes(const Csr &m, int32_t width)
+// Bytes of partial-sum workspace an aggregation of `width` columns over pattern `m` needs: one slot per item of
+// every row cut into several items, of as many floats as one launch covers columns: all of them (rounded up to 4) on a
+// cache-resident graph, at most one pass otherwise or where the caller has no more room (`one_pass`).
+size_t spmm_workspace_bytes(const Csr &m, int32_t width, bool one_pass)
 {
     const int64_t w4 = round_up(width, 4);
-    return (size_t)round_up(m.sched.n_slots * (w4 < PASS_COLS ? w4 : PASS_COLS) * (int64_t)sizeof(float), 256);
+    const bool all = !one_pass && m.sched.item_max <= ITEM_SHORT;
+    return (size_t)round_up(m.sched.n_slots * (w4 < PASS_COLS || all ? w4 : PASS_COLS) * (int64_t)sizeof(float), 256);
 }
 
-int launch_spmm(const slicegcn_graph *g, const Csr &m, const float *X, int64_t ldx, int32_t width,
-                float *Y, int64_t ldy, const float *Add, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream,
-                bool prescaled)
+int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, int batch, int64_t ldx, int32_t width,
+                int64_t ldy, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream, bool prescaled)
 {
+    SG_REQUIRE(batch >= 1 && batch <= MAX_BATCH, SLICEGCN_EINVAL, "aggregation: batch of %d", batch);
     const int V = width >= 4 ? 4 : 1;
     // passes of at most 128 columns (32 lanes per row): narrower ones re-read the index streams more often, wider ones
     // make the set of hot rows of the operand too large for the L2s (301 columns: 7.8 / 7.4 / 7.7 ms for passes of 64 / 128 / 256)
     const Schedule &sc = m.sched;
-    const int64_t used_cols = width < PASS_COLS ? round_up(width, 4) : PASS_COLS; // one pass: slots packed densely
-    const size_t need = (size_t)(sc.n_slots * used_cols) * sizeof(float);
+    const bool resident = sc.item_max <= ITEM_SHORT;
+    const bool multi_pass = resident && width > PASS_COLS && ws_bytes >= batch * spmm_workspace_bytes(m, width, false);
+    const size_t each = spmm_workspace_bytes(m, width, !multi_pass);
+    const size_t need = sc.n_slots > 0 ? batch * each : 0;
     SG_REQUIRE(need == 0 || (ws != nullptr && ws_bytes >= need), SLICEGCN_EWORKSPACE,
                "aggregation: workspace of %zu bytes, %zu needed", ws_bytes, need);
     SG_REQUIRE(need == 0 || (reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL,
                "aggregation: workspace not 256-byte aligned");
     SpmmArgs a;
+    SpmmBatch b;
+    bool aligned = true, any_add = false;
+    for (int i = 0; i < MAX_BATCH; ++i) {
+        const SpmmOperands &o = ops[i < batch ? i : 0];
+        b.X[i] = o.X; b.Y[i] = o.Y; b.Add[i] = o.Add;
+        aligned = aligned && aligned16(o.X);
+        any_add = any_add || o.Add;
+    }
     a.rowptr = m.rowptr; a.colidx = m.colidx; a.vals = m.vals; a.items = sc.items; a.fix = sc.fix; a.order = g->order;
-    a.X = X; a.Y = Y; a.Add = Add; a.scratch = static_cast<float *>(ws);
+    a.scratch = static_cast<float *>(ws);
+    a.scratch_stride = (int64_t)(each / sizeof(float));
     a.dinv = prescaled ? g->dinv : nullptr;
-    a.ldx = ldx; a.ldy = ldy; a.ldadd = Add ? ldadd : 0;
+    a.ldx = ldx; a.ldy = ldy; a.ldadd = ldadd;
     const bool s32 = g->n < (1 << 24) && ldx * 4 < (1 << 24) && (int64_t)g->n * ldx * 4 < ((int64_t)1 << 32);
     a.ldx_bytes = s32 ? (uint32_t)(ldx * 4) : 0u;
     a.n = (int32_t)g->n;
     a.item_max = sc.item_max;
-    a.slot_cols = (int32_t)used_cols;
+    const int64_t w4 = round_up(width, 4);
+    a.slot_cols = (int32_t)(multi_pass || w4 < PASS_COLS ? w4 : PASS_COLS);
     // rows whose last vector stays inside the row: a multiple of four columns, or room for the padding up to one
-    const bool whole = V == 1 || width % 4 == 0 || (aligned16(X) && ldx % 4 == 0);
+    const bool whole = V == 1 || width % 4 == 0 || (aligned && ldx % 4 == 0);
     a.load_max = whole ? 0 : width - 4;
     a.wbig_off = sc.wbig_off; a.wbig_cnt = sc.wbig_cnt;
     a.wsmall_off = sc.wsmall_off; a.wsmall_cnt = sc.wsmall_cnt;
-    // workgroups per class: the class's own pieces, then its share of the whole-row chunks
-    a.ipw = sc.item_max <= ITEM_SHORT ? 4 : 1; // the one-launch kernel works through runs of items
-    const int64_t ipb = 4 * a.ipw;
-    const int64_t wbig_chunks = ((int64_t)sc.wbig_cnt + ipb - 1) / ipb;
-    int64_t big_blocks = 0;
     for (int c = 0; c < N_CLASSES; ++c) {
         a.big_off[c] = sc.big_off[c]; a.big_cnt[c] = sc.big_cnt[c];
         a.small_off[c] = sc.small_off[c]; a.small_cnt[c] = sc.small_cnt[c];
-        const int64_t b = (sc.big_cnt[c] + ipb - 1) / ipb + (wbig_chunks + N_CLASSES - 1 - c) / N_CLASSES;
-        big_blocks = b > big_blocks ? b : big_blocks;
     }
-    SG_REQUIRE(big_blocks * N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
-    a.big_blocks = (int32_t)big_blocks;
-    ProfScope prof(Add ? SLICEGCN_PROF_SPMM_ADD : SLICEGCN_PROF_SPMM, width, stream);
-    for (int32_t c0 = 0; c0 < width; c0 += PASS_COLS) {
+    ProfScope prof(any_add ? SLICEGCN_PROF_SPMM_ADD : SLICEGCN_PROF_SPMM, width, stream);
+    const int32_t full_cols = width / PASS_COLS * PASS_COLS; // whole passes share a launch, the rest has lane groups of its own width
+    for (int32_t c0 = 0; c0 < width; c0 = a.col_end) {
         a.col0 = c0;
-        a.col_end = width < c0 + PASS_COLS ? width : c0 + PASS_COLS;
-        const int lanes_needed = (a.col_end - c0 + V - 1) / V;
+        a.col_end = c0 >= full_cols ? width : multi_pass ? full_cols : c0 + PASS_COLS;
+        const int passes = (a.col_end - c0 + PASS_COLS - 1) / PASS_COLS;
+        const int pass_cols = passes > 1 ? PASS_COLS : a.col_end - c0;
         int lpr = 8;
-        while (lpr < lanes_needed) lpr <<= 1; // 8, 16 or 32
-        const int64_t run = 4 * 8 * (64 / lpr); // lane-group items per workgroup: runs of consecutive items
-        const int64_t wsmall_runs = ((int64_t)sc.wsmall_cnt + run - 1) / run;
-        int64_t small_blocks = 0;
-        for (int c = 0; c < N_CLASSES; ++c) { // the class's own pieces, then its share of the whole-row runs
-            const int64_t b = (sc.small_cnt[c] + run - 1) / run + (wsmall_runs + N_CLASSES - 1 - c) / N_CLASSES;
-            small_blocks = b > small_blocks ? b : small_blocks;
+        while (lpr < (pass_cols + V - 1) / V) lpr <<= 1; // 8, 16 or 32
+        // How much a wavefront works through in turn.  On a large graph long runs amortise the chain of dependent loads
+        // (descriptor, entries, gathers) across items; a small graph has too few items to fill the chip with such runs, so
+        // they are cut until about SMALL_GRID workgroups of each kind are there (2048 nodes, 64 columns: 11.3 -> SMALL_US us).
+        const int64_t groups = 4 * (64 / lpr), copies = (int64_t)batch * passes;
+        auto turns = [&](int64_t items, int64_t per_turn, int most) {
+            const int64_t t = items * copies / (per_turn * SMALL_GRID);
+            return (int)(t < 1 ? 1 : t > most ? most : t);
+        };
+        a.ipw = resident ? turns(sc.wbig_cnt, 4, 4) : 1;
+        a.rounds = resident ? turns(sc.wsmall_cnt, groups, 8) : 8;
+        a.tiny_rounds = resident ? 2 * turns(g->n, 2 * groups, 4) : 8;
+        // workgroups per class: the class's own pieces, then its share of the whole-row chunks
+        const int64_t ipb = 4 * a.ipw, run = groups * a.rounds;
+        const int64_t wbig_chunks = ((int64_t)sc.wbig_cnt + ipb - 1) / ipb, wsmall_runs = ((int64_t)sc.wsmall_cnt + run - 1) / run;
+        int64_t big_blocks = 0, small_blocks = 0;
+        for (int c = 0; c < N_CLASSES; ++c) {
+            const int64_t x = (sc.big_cnt[c] + ipb - 1) / ipb + (wbig_chunks + N_CLASSES - 1 - c) / N_CLASSES;
+            const int64_t y = (sc.small_cnt[c] + run - 1) / run + (wsmall_runs + N_CLASSES - 1 - c) / N_CLASSES;
+            big_blocks = x > big_blocks ? x : big_blocks;
+            small_blocks = y > small_blocks ? y : small_blocks;
         }
-        SG_REQUIRE(small_blocks * N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
+        SG_REQUIRE(big_blocks * N_CLASSES <= INT32_MAX && small_blocks * N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
+        a.big_blocks = (int32_t)big_blocks;
         a.small_blocks = (int32_t)small_blocks;
-        if (int rc = launch_pass(a, V, lpr, stream)) return rc;
+        if (int rc = launch_pass(a, b, batch, passes, V, lpr, stream)) return rc;
         if (sc.n_fix > 0) {
             const int64_t threads = sc.n_fix * (int64_t)(a.col_end - c0);
-            spmm_fix_kernel<<<(unsigned)((threads + 255) / 256), 256, 0, stream>>>(a, (int32_t)sc.n_fix);
+            spmm_fix_kernel<<<dim3((unsigned)((threads + 255) / 256), (unsigned)batch), 256, 0, stream>>>(a, b, (int32_t)sc.n_fix);
             SG_LAUNCH_CHECK();
         }
     }
@@ -767,20 +824,22 @@ extern "C" int slicegcn_spmm_slice_static(const slicegcn_graph *g, int op, const
     SG_REQUIRE(width >= 1, SLICEGCN_EINVAL, "spmm_slice_static: width = %d < 1", width);
     SG_REQUIRE(ldx >= width && ldy >= width, SLICEGCN_EINVAL, "spmm_slice_static: leading dimension smaller than width");
     const Csr &m = (op & SLICEGCN_SPMM_TRANSPOSE) ? g->tr : g->fwd;
-    const size_t need = spmm_workspace_bytes(m, width);
+    const size_t need = spmm_workspace_bytes(m, width, true);
     SG_REQUIRE(need <= (size_t)SLICEGCN_STATIC_WS_BYTES, SLICEGCN_EWORKSPACE,
                "spmm_slice_static: this graph and width need %zu bytes of partial sums, the built-in buffer holds %zu; "
                "use slicegcn_spmm_slice with a workspace", need, (size_t)SLICEGCN_STATIC_WS_BYTES);
     void *ptr = nullptr;
     if (need > 0)
         if (int rc = static_scratch(&ptr)) return rc;
-    return launch_spmm(g, m, X, ldx, width, Y, ldy, nullptr, 0, ptr, need, as_stream(stream), (op & SLICEGCN_SPMM_PRESCALED) != 0);
+    const SpmmOperands o{X, Y, nullptr};
+    return launch_spmm(g, m, &o, 1, ldx, width, ldy, 0, ptr, need > 0 ? SLICEGCN_STATIC_WS_BYTES : 0, as_stream(stream),
+                       (op & SLICEGCN_SPMM_PRESCALED) != 0);
 }
 
 extern "C" size_t slicegcn_spmm_workspace_bytes(const slicegcn_graph *g, int op, int32_t width)
 {
     if (!g || width < 1) return 0;
-    return spmm_workspace_bytes((op & SLICEGCN_SPMM_TRANSPOSE) ? g->tr : g->fwd, width);
+    return spmm_workspace_bytes((op & SLICEGCN_SPMM_TRANSPOSE) ? g->tr : g->fwd, width, false);
 }
 
 extern "C" int slicegcn_spmm_slice(const slicegcn_graph *g, int op, const float *X, int64_t ldx,
@@ -790,6 +849,7 @@ extern "C" int slicegcn_spmm_slice(const slicegcn_graph *g, int op, const float 
     SG_REQUIRE((op & ~(SLICEGCN_SPMM_TRANSPOSE | SLICEGCN_SPMM_PRESCALED)) == 0, SLICEGCN_EINVAL, "spmm_slice: unknown op bits 0x%x", op);
     SG_REQUIRE(width >= 1, SLICEGCN_EINVAL, "spmm_slice: width = %d < 1", width);
     SG_REQUIRE(ldx >= width && ldy >= width, SLICEGCN_EINVAL, "spmm_slice: leading dimension smaller than width");
-    return launch_spmm(g, (op & SLICEGCN_SPMM_TRANSPOSE) ? g->tr : g->fwd, X, ldx, width, Y, ldy, nullptr, 0, ws, ws_bytes,
+    const SpmmOperands o{X, Y, nullptr};
+    return launch_spmm(g, (op & SLICEGCN_SPMM_TRANSPOSE) ? g->tr : g->fwd, &o, 1, ldx, width, ldy, 0, ws, ws_bytes,
                        as_stream(stream), (op & SLICEGCN_SPMM_PRESCALED) != 0);
 }

@@ -5,9 +5,15 @@ library calls; every arithmetic step is a kernel of ``libslicegcn.so``.
 """
 from __future__ import annotations
 
+import ctypes
+
 import torch
 
 from . import binding as B
+
+# Slices run in groups whose layers share their launches while the rows one launch works on stay within this many bytes
+# (see SliceStack.group).
+GROUP_BYTES = 64 << 20
 
 
 def padded_ld(width: int) -> int:
@@ -64,7 +70,6 @@ class SliceStack:
         self.X = ([shared_input] * k if self.shared
                   else [torch.zeros((n_nodes, padded_ld(first_width)), **f32) for _ in range(k)])
         self.dXin = torch.empty((n_nodes, padded_ld(first_width)), **f32) if self.shared else None
-        self.dXtmp = torch.empty((n_nodes, padded_ld(first_width)), **f32) if self.shared and k > 1 else None
         # parameters and their gradients: [slice][layer] -> dict
         self.params = [[None] * layers for _ in range(k)]
         self.grads = [[None] * layers for _ in range(k)]
@@ -81,23 +86,30 @@ class SliceStack:
         # the same, so E[i] can ride on it: the last layer then stores the encoded output straight into its column
         # block (no encoding pass) and dE[i] is that layer's db_self (no column-sum pass over dH).
         self.fuse_encoding = fuse_encoding and slice_encoding
-        self.b_eff = torch.zeros((k, slice_hidden), **f32) if self.fuse_encoding else None
         # slice i runs on lane i mod lanes; a lane has its own stream, workspace and backward scratch
         self.lanes = max(1, min(k, int(streams)))
         self.streams = [torch.cuda.Stream(device=self.dev) for _ in range(self.lanes)] if self.lanes > 1 else []
+        # On one lane the slices run in groups of `group`: a layer of all of them is one set of launches, which is what a
+        # small graph needs (its kernels last microseconds and leave most of the chip idle).  A large graph gains nothing
+        # and would need every buffer of the backward pass per slice, so a group ends where one launch touches GROUP_BYTES.
+        row_bytes = 4 * 4 * max(padded_ld(first_width), padded_ld(slice_hidden))  # Z, input and output, twice the widest
+        self.group = 1 if self.lanes > 1 else max(1, min(k, B.MAX_GROUP, GROUP_BYTES // (n_nodes * row_bytes)))
+        slots = max(self.lanes, self.group)
         self.dbuf = [[torch.empty((n_nodes, padded_ld(slice_hidden)), **f32) for _ in range(2)] if layers > 1 else []
-                     for _ in range(self.lanes)]
-        # with a shared (learned) input and several lanes every slice keeps its own input gradient until the lanes
-        # have joined; they are then added in slice order, as the one-lane pass adds them
-        self.dXs = ([torch.empty((n_nodes, padded_ld(first_width)), **f32) for _ in range(k - 1)]
-                    if self.shared and self.lanes > 1 else [])
+                     for _ in range(slots)]
+        # with a shared (learned) input and several slices at a time every slice keeps its own input gradient until all
+        # are there; they are then added in slice order, as one slice after the other adds them
+        self.deferred = self.shared and slots > 1
+        self.dXs = [torch.empty((n_nodes, padded_ld(first_width)), **f32) for _ in range(k - 1)] if self.deferred else []
+        self.dXtmp = torch.empty((n_nodes, padded_ld(first_width)), **f32) if self.shared and k > 1 and not self.deferred else None
         ws = 0
         for l, (wi, wo) in enumerate(self.widths):
-            ws = max(ws, B.slicegcn_layer_fwd_workspace_bytes(graph, wi, wo, order),
-                     B.slicegcn_layer_bwd_workspace_bytes(graph, wi, wo, l > 0 or self.shared, order))
+            ws = max(ws, B.slicegcn_layers_fwd_workspace_bytes(graph, wi, wo, self.group, order),
+                     B.slicegcn_layers_bwd_workspace_bytes(graph, wi, wo, l > 0 or self.shared, self.group, order))
         ws = max(ws, B.slicegcn_concat_bwd_workspace_bytes(n_nodes, [slice_hidden] * k))
         self.ws_lane = [torch.empty(ws, dtype=torch.uint8, device=self.dev) for _ in range(self.lanes)]
         self.ws = self.ws_lane[0]
+        self._plan_key = None
 
     # ---------------------------------------------------------------------------------
     def set_params(self, i: int, l: int, W_agg, b, W_self, b_self):
@@ -155,80 +167,131 @@ class SliceStack:
         return self.fuse_encoding and all(self.params[i][last]["W_self"] is not None and
                                           self.params[i][last]["b_self"] is not None for i in range(self.k))
 
+    # ---- call arguments of every layer, laid out once ---------------------------------
+    def _tensors(self):
+        out = [*self.X, self.Hcat, self.E, self.dE]
+        for i in range(self.k):
+            out += self.H[i]
+            out += self.Z[i]
+            out += self.mask[i]
+            for p, gr in zip(self.params[i], self.grads[i]):
+                out += (p["W_agg"], p["b"], p["W_self"], p["b_self"], gr["dW_agg"], gr["db"], gr["dW_self"], gr["db_self"])
+        return out
+
+    def _plan(self):
+        """Brings the argument blocks up to date: they are laid out again when a tensor of the stack has been replaced
+        (parameters are rebound when an optimiser takes them over)."""
+        tensors = self._tensors()
+        key = [0 if t is None else t.data_ptr() for t in tensors]
+        if key == self._plan_key:
+            return
+        fused = self.encoding_fused()
+        self._io, self._shape = [], []
+        for l, (wi, wo) in enumerate(self.widths):
+            last = l == self.L - 1
+            io = (B.LayerIo * self.k)()
+            for i in range(self.k):
+                p, gr, x = self.params[i][l], self.grads[i][l], io[i]
+                for name, W in (("W_agg", p["W_agg"]), ("W_self", p["W_self"])):
+                    if W is not None and tuple(W.shape) != (wi, wo):
+                        raise ValueError(f"{name} must be w_in x w_out")
+                x.params = B._LayerParams(*(B._vec(p[n], n) for n in ("W_agg", "b", "W_self", "b_self")))
+                x.grads = B._LayerGrads(*(B._vec(gr[n], n) for n in ("dW_agg", "db", "dW_self", "db_self")))
+                x.Hin, ldi = B._mat(self.hin(i, l), "Hin")
+                x.Hout, ldo = B._mat(self.hout(i, l), "Hout")
+                x.Z, ldz = B._mat(self.zbuf(i, l), "Z") if self.Z[i][l] is not None else (None, 0)
+                x.mask, mask_words = B._mat(self.mask[i][l], "mask", torch.int32)
+                if fused and last:
+                    x.enc, x.denc = B._vec(self.E[i], "E"), B._vec(self.dE[i], "dE")
+                slot = i % len(self.dbuf)
+                if l > 0:
+                    x.dHin, ldgi = B._mat(self.dbuf[slot][l % 2], "dHin")
+                elif self.shared:
+                    x.dHin, ldgi = B._mat(self.dXin if i == 0 else self.dXs[i - 1] if self.deferred else self.dXtmp, "dHin")
+                else:  # raw features need no gradient
+                    x.dHin, ldgi = None, 0
+                if not last:
+                    x.dHout, ldgo = B._mat(self.dbuf[slot][(l + 1) % 2], "dHout")
+                else:
+                    ldgo = 0
+                same = (ldi, ldo, ldz, mask_words, ldgo, ldgi)
+                if i > 0 and same != lds:
+                    raise ValueError("the slices' tensors differ in their leading dimensions")
+                lds = same
+            desc = B._LayerDesc(wi, wo, self.act(l), self.order | self.layout[l])
+            self._io.append(io)
+            self._shape.append(B.LayerGroup(desc, 1, *lds))
+        self._dH_key = None
+        self._plan_key = key
+
+    def _forward_group(self, first: int, count: int, ws):
+        cached = self.cache_first and all(self.first_valid[first:first + count])
+        for l in range(self.L):
+            sh = self._shape[l]
+            sh.count = count
+            if l == 0:
+                sh.desc.flags = self.order | self.layout[0] | (B.LAYER_Z_VALID if cached else 0)
+            B.slicegcn_layers_fwd(self.g, sh, self._io[l], first, ws)
+        self.first_valid[first:first + count] = [True] * count
+
     def forward_slice(self, i: int):
         if not self.inputs_prepared:
             self.prepare_inputs()
-        fused = self.encoding_fused()
-        for l in range(self.L):
-            p = self.params[i][l]
-            wi = self.widths[l][0]
-            b_self = p["b_self"]
-            if fused and l == self.L - 1:  # b_self + E[i], two tiny launches
-                b_self = self.b_eff[i]
-                B.slicegcn_slice_feature(p["b_self"].view(1, -1), 0, self.hs, b_self.view(1, -1))
-                B.slicegcn_accumulate(b_self.view(1, -1), self.E[i].view(1, -1))
-            B.slicegcn_layer_fwd(self.g, self.hin(i, l), p["W_agg"], p["b"], p["W_self"], b_self, self.hout(i, l),
-                                 self.zbuf(i, l), self.mask[i][l], act=self.act(l),
-                                 z_valid=l == 0 and self.cache_first and self.first_valid[i], ws=self.ws_lane[i % self.lanes],
-                                 order=self.order, layout=self.layout[l])
-        self.first_valid[i] = True
+        self._plan()
+        self._forward_group(i, 1, self.ws_lane[i % self.lanes])
 
     def _on_lanes(self, fn):
-        """fn(i) for every slice: in turn on the caller's stream, or slice i on lane i mod lanes, the lanes
-        starting after what the caller's stream holds so far and the caller's stream going on after all of them."""
+        """fn(first slice, count, workspace) for every group of slices: in turn on the caller's stream, or slice i on lane
+        i mod lanes, the lanes starting after what the caller's stream holds so far and the caller's stream going on after
+        all of them."""
         if self.lanes == 1:
-            for i in range(self.k):
-                fn(i)
+            for i in range(0, self.k, self.group):
+                fn(i, min(self.group, self.k - i), self.ws)
             return
         main = torch.cuda.current_stream()
         for s in self.streams:
             s.wait_stream(main)
         for i in range(self.k):
             with torch.cuda.stream(self.streams[i % self.lanes]):
-                fn(i)
+                fn(i, 1, self.ws_lane[i % self.lanes])
         for s in self.streams:
             main.wait_stream(s)
 
     def forward(self) -> torch.Tensor:
         if not self.inputs_prepared:
             self.prepare_inputs()
-        self._on_lanes(self.forward_slice)
+        self._plan()
+        self._on_lanes(self._forward_group)
         # the last layer of every slice already stored into its column block: encode in place, unless that is done
         if not self.encoding_fused():
             B.slicegcn_concat([self.hout(i, self.L - 1) for i in range(self.k)], self.E, self.Hcat)
         return self.Hcat
 
     def backward(self, dH: torch.Tensor):
-        fused = self.encoding_fused()
-        if self.E is not None and not fused:
+        self._plan()
+        if self.E is not None and not self.encoding_fused():
             B.slicegcn_concat_bwd(dH, [self.hs] * self.k, dE=self.dE, ws=self.ws)
-        deferred = self.shared and self.lanes > 1   # the slices' input gradients are added after the lanes have joined
+        dkey = (dH.data_ptr(), dH.stride(0))
+        if dkey != self._dH_key:  # CONCAT backward is a column view
+            ptr, ld = B._mat(dH, "dH")
+            for i in range(self.k):
+                self._io[-1][i].dHout = ptr + 4 * i * self.hs
+            self._shape[-1].ldgo = ld
+            self._dH_key = dkey
 
-        def backward_slice(i: int):
-            lane = i % self.lanes
-            g_out = dH[:, i * self.hs:(i + 1) * self.hs]  # CONCAT backward is a column view
+        def backward_group(first: int, count: int, ws):
             for l in reversed(range(self.L)):
-                p, gr = self.params[i][l], self.grads[i][l]
-                wi = self.widths[l][0]
-                if l > 0:
-                    g_in = self.dbuf[lane][l % 2][:, :wi]
-                elif self.shared:  # the fused features are learned: the first slice writes, the others add
-                    g_in = (self.dXin if i == 0 else self.dXs[i - 1] if deferred else self.dXtmp)[:, :wi]
-                else:
-                    g_in = None  # raw features need no gradient
-                B.slicegcn_layer_bwd(self.g, self.hin(i, l), p["W_agg"], p["W_self"], self.zbuf(i, l), self.mask[i][l],
-                                     g_out, g_in, gr["dW_agg"], gr["db"], gr["dW_self"], gr["db_self"], self.ws_lane[lane],
-                                     act=self.act(l), order=self.order, layout=self.layout[l])
-                if l == 0 and self.shared and i > 0 and not deferred:
-                    B.slicegcn_accumulate(self.dXin[:, :wi], g_in)
-                if fused and l == self.L - 1:  # dE[i] = column sums of dH^i = this layer's db_self
-                    B.slicegcn_slice_feature(gr["db_self"].view(1, -1), 0, self.hs, self.dE[i].view(1, -1))
-                g_out = g_in
+                sh = self._shape[l]
+                sh.count = count
+                sh.desc.flags = self.order | self.layout[l]
+                B.slicegcn_layers_bwd(self.g, sh, self._io[l], first, ws)
+            if self.shared and not self.deferred and first > 0:  # learned inputs: the first slice writes, the others add
+                B.slicegcn_accumulate(self.dXin[:, :self.w0], self.dXtmp[:, :self.w0])
 
-        self._on_lanes(backward_slice)
-        if deferred:
-            for i in range(1, self.k):
-                B.slicegcn_accumulate(self.dXin[:, :self.w0], self.dXs[i - 1][:, :self.w0])
+        self._on_lanes(backward_group)
+        if self.deferred:
+            for i in range(0, self.k - 1, B.MAX_GROUP):
+                B.slicegcn_accumulate_many(self.dXin[:, :self.w0], [t[:, :self.w0] for t in self.dXs[i:i + B.MAX_GROUP]])
 
 
 class Classifier:
@@ -249,8 +312,8 @@ class Classifier:
         self.mask = torch.zeros((n_nodes, (hidden + 31) // 32), dtype=torch.int32, device=self.dev)
         self.logits = torch.empty((n_nodes, classes), **f32)  # overwritten by its own gradient in backward
         self.loss = torch.zeros(1, **f32)
-        ws = max(B.slicegcn_softmax_ce_workspace_bytes(n_nodes), B.slicegcn_linear_bwd_workspace_bytes(n_nodes, width, hidden),
-                 B.slicegcn_linear_bwd_workspace_bytes(n_nodes, hidden, classes))
+        ws = max(B.slicegcn_softmax_ce_workspace_bytes(n_nodes), B.slicegcn_linear_bwd_full_workspace_bytes(n_nodes, width, hidden),
+                 B.slicegcn_linear_bwd_full_workspace_bytes(n_nodes, hidden, classes))
         self.ws = torch.empty(ws, dtype=torch.uint8, device=self.dev)
 
     def set_params(self, W1, b1, W2, b2):
@@ -294,8 +357,8 @@ class FeatureFusion:
         self.dA = torch.empty((n_nodes, feat), **f32)
         self.mask = torch.zeros((n_nodes, (feat + 31) // 32), dtype=torch.int32, device=self.dev)
         self.Xff = torch.zeros((n_nodes, padded_ld(out_width)), **f32)  # padding columns stay zero
-        ws = max(B.slicegcn_linear_bwd_workspace_bytes(n_nodes, feat, feat),
-                 B.slicegcn_linear_bwd_workspace_bytes(n_nodes, feat, out_width))
+        ws = max(B.slicegcn_linear_bwd_full_workspace_bytes(n_nodes, feat, feat),
+                 B.slicegcn_linear_bwd_full_workspace_bytes(n_nodes, feat, out_width))
         self.ws = torch.empty(ws, dtype=torch.uint8, device=self.dev)
 
     def set_params(self, W1, b1, W2, b2):
