@@ -6,8 +6,8 @@
 //   backward:  dZ = (dHout * mask) W_agg^T,  T = dHout W_self^T            (pair kernel, transposed)
 //              dW_agg = Z^T (dHout * mask), dW_self = Hin^T dHout, db, db_self   (reduce kernels)
 //
-// Every product runs on v_mfma_f32_32x32x2_f32 tiles (fp32 in, fp32 accumulate), one 32-row strip per
-// wavefront, operands staged through LDS with coalesced 16-byte loads.
+// Wide products run on the bf16 matrix cores with operands split into three terms (see split8), the narrow layers' on
+// v_mfma_f32_32x32x2_f32 tiles (fp32 in, fp32 accumulate), one 32-row strip per wavefront.
 // Lane layout of the 32x32x2 fp32 MFMA (64 lanes, l = lane): A operand = A[m = l % 32][k = l / 32],
 // B operand = B[k = l / 32][n = l % 32], accumulator register r (0..15) = C[8*(r/4) + 4*(l/32) + r%4][l % 32].
 #include "common.h"
@@ -82,292 +82,276 @@ __device__ inline float4 load_k4(const float *__restrict__ base, int64_t ld, int
 
 __device__ inline float pick(const float4 &v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
-// MFMA pair kernel.  Workgroup = 4 wavefronts = 128 rows (32 per wavefront) x NT*32 output
-// columns.  The reduction axis is walked in chunks of 32: the A tile(s) (128 x 32) and the B
-// tile(s) (32 x NT*32) are staged in LDS; a lane then reads 4 consecutive k of its row with one
-// 16-byte LDS read and feeds them to four MFMA steps (the k pairing of a step is (k, k+4), the B
-// tile is read with the same pairing).  The global loads of chunk c+1 are issued into registers
-// before the MFMAs of chunk c and written to LDS after them, so memory latency hides behind the
-// matrix instructions.  TWO: second product A2 B2 (self term / T output) present.
-// Workgroups are numbered so that the column tiles of one row tile run back to back on the same
-// XCD (workgroup b goes to XCD b mod 8): the A tile is fetched from HBM once and re-read from L2.
-template <int NT, bool BWD, bool TWO>
-__global__ __launch_bounds__(256) void pair_mfma_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+// ---- fp32 products on the bf16 matrix cores --------------------------------------------------
+// A float is the exact sum of three bf16 numbers (8 mantissa bits each, round to nearest: |mid| <= 2^-9 |x|, |low| <= 2^-18 |x|),
+// so a product of two floats is the sum of nine bf16 products, of which the three smallest (mid low, low mid, low low; together
+// at most 2^-26 of it, a quarter of the rounding of an fp32 product) are left out.  The other six run on
+// v_mfma_f32_32x32x16_bf16 with fp32 accumulation, smallest first: six instructions of 32 cycles for 16 steps of k, where
+// v_mfma_f32_32x32x2_f32 takes 512 cycles (192 against 512).  Against fp64, normal operands, sums of 32 / 256 / 4096 products: error (rms over rms
+// of the result) 0.69 / 2.4 / 10.0 e-7, with the fp32 instruction 1.02 / 2.9 / 11.6 e-7; the same order for positive operands and
+// for operands over eight decades, and all nine products give the same figures as six.  Beyond the bf16 range (|x| > 3.39e38)
+// and for infinities the split gives NaN where the fp32 product may be infinite.
+// Lane layout (l = lane): A operand = A[m = l % 32][k = 8 * (l / 32) + i], B operand = B[k = 8 * (l / 32) + i][n = l % 32],
+// accumulator register r = C[8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32].
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4))); // 16-byte accesses at any 4-byte boundary
+
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+
+struct Split { bf16x8 hi, mid, low; };
+__device__ inline Split split8(const float (&x)[8])
+{
+    uintx4 o[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { // two floats at a time: 11 instructions
+        floatx2 r = {x[2 * i], x[2 * i + 1]};
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+            o[t][i] = u;
+            if (t < 2) { // what the terms so far leave over: exact
+                r.x -= __builtin_bit_cast(float, u << 16);
+                r.y -= __builtin_bit_cast(float, u & 0xffff0000u);
+            }
+        }
+    }
+    return Split{__builtin_bit_cast(bf16x8, o[0]), __builtin_bit_cast(bf16x8, o[1]), __builtin_bit_cast(bf16x8, o[2])};
+}
+__device__ inline floatx16 mfma_bf16(const bf16x8 &a, const bf16x8 &b, const floatx16 &c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+__device__ inline floatx16 mfma_split(const Split &a, const Split &b, floatx16 c)
+{
+    c = mfma_bf16(a.low, b.hi, c);
+    c = mfma_bf16(a.hi, b.low, c);
+    c = mfma_bf16(a.mid, b.mid, c);
+    c = mfma_bf16(a.mid, b.hi, c);
+    c = mfma_bf16(a.hi, b.mid, c);
+    return mfma_bf16(a.hi, b.hi, c);
+}
+
+// Eight consecutive floats of a row of K columns from column k on, zero beyond column K
+__device__ inline void load_k8(float (&x)[8], const float *p, int k, int K)
+{
+    if (k + 8 <= K) {
+        const floatx4_u u = *reinterpret_cast<const floatx4_u *>(p), v = *reinterpret_cast<const floatx4_u *>(p + 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { x[i] = u[i]; x[4 + i] = v[i]; }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = k + i < K ? p[i] : 0.f;
+    }
+}
+
+// Pair kernel.  Workgroup = 4 wavefronts; a wavefront owns 32 rows and all NT * 32 columns of the workgroup's tile.
+// A row is used by one wavefront only, so it goes from memory straight into registers (a lane loads the eight k of its row
+// that it feeds to the matrix cores) and is split there.  The weights are shared: 32 steps of k at a time are split on their way
+// to LDS (two buffers, one barrier per chunk), in units of eight k of a column, so that an operand is one 16-byte read.
+// The weights are the A operand and the rows the B operand: a lane then holds four consecutive columns of one row in four
+// registers, stores them as 16 bytes and collects the activation bits of its row without votes.  The rows of the next
+// chunk are requested as soon as the current ones are split (both steps at once: they share cache lines), its weights
+// before the current chunk's matrix instructions.
+// Two products run one after the other over the same accumulators: forward the second one is added to the activated first
+// one; backward the first result is stored before the second begins.
+// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 take 2.2 ms (fp32 instruction: 3.7), 147 TFLOP/s = 880 of bf16,
+// where a large bf16 matrix product of the library reaches 1270 on this card (the clock gives way under matrix load).  64 rows
+// per wavefront, 64 columns per workgroup, and the weights resident in LDS for the whole reduction (no barriers) were within 10 % of
+// this or slower.  256 -> 47: 0.74 ms (0.98), bound by the rows' loads (4.0 TB/s).
+// Workgroups are numbered so that the column tiles of one row tile run back to back on the same XCD (workgroup b goes to
+// XCD b mod 8): the rows are fetched from memory once and re-read from L2.
+template <int NT, bool BWD>
+__global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
 {
     const PairArgs a = slice_of(common, batch);
-    constexpr int BM = 128, KC = 32, AS = KC + 4, BN = NT * 32;
-    constexpr int BPT = KC * BN / 256; // B-tile elements per thread and chunk
-    __shared__ __attribute__((aligned(16))) float As1[BM][AS];
-    __shared__ __attribute__((aligned(16))) float As2[TWO ? BM : 1][AS];
-    // the B tiles are kept column-major ([column][k], the A tiles' row stride), so that a lane reads the four
-    // consecutive k of its column with one 16-byte LDS read, as it does for A: one LDS read per four MFMAs
-    __shared__ __attribute__((aligned(16))) float Bt1[BN][AS];
-    __shared__ __attribute__((aligned(16))) float Bt2[TWO ? BN : 1][AS];
-
+    constexpr int BN = NT * 32, KC = 32;
+    constexpr int GS = BN + 4;                 // units per group of eight k (padded: conflict-free writes in both directions)
+    constexpr int UB = (4 * BN + 255) / 256;   // units a thread stages per chunk
+    __shared__ bf16x8 Bs[2][3][4][GS];
+    __shared__ __attribute__((aligned(16))) float bias_s[2][BN];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
     const int64_t b = blockIdx.x;
     const int64_t row_tile = (b / (8 * n_col_tiles)) * 8 + (b % 8);
-    const int col_tile = (int)((b / 8) % n_col_tiles);
-    const int64_t row0 = row_tile * BM;
-    if (row0 >= a.n) return; // uniform per workgroup (the last group of 8 row tiles may be partial)
-    const int col0 = col_tile * BN;
-    const bool vec1 = aligned16(a.A1) && (a.lda1 % 4 == 0);
-    const bool vec2 = TWO && !BWD && aligned16(a.A2) && (a.lda2 % 4 == 0);
-
-    floatx16 acc1[NT], acc2[TWO ? NT : 1];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { acc1[t][r] = 0.f; if (TWO) acc2[t][r] = 0.f; }
-
-    float4 ra1[4], ra2[TWO ? 4 : 1];
-    float rs[4]; // per-row factor of this thread's four rows (applied when the registers go to LDS, so that the loads stay in flight)
-    float rb1[BPT], rb2[TWO ? BPT : 1];
-    auto fetch = [&](int k0) { // this thread's share of the tiles of chunk k0, into registers
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int idx = tid + it * 256;
-            const int r = idx >> 3, c4 = (idx & 7) * 4;
-            const int64_t row = row0 + r;
-            const int kk = k0 + c4;
-            float4 v1 = make_float4(0.f, 0.f, 0.f, 0.f), v2 = v1;
-            float f = 1.f;
-            if (row < a.n && kk < a.K) {
-                v1 = load_k4(a.A1, a.lda1, row, kk, a.K, vec1);
-                if (!BWD) {
-                    if (TWO) {
-                        v2 = load_k4(a.A2, a.lda2, row, kk, a.K, vec2);
-                        if (a.scale2) f = a.scale2[row];
-                    }
-                } else {
-                    if (TWO) v2 = v1;
-                    if (a.mask) { // four mask bits of this row; kk % 4 == 0 keeps them inside one word
-                        const uint32_t bits = a.mask[row * a.mask_words + (kk >> 5)] >> (kk & 31);
-                        if (!(bits & 1u)) v1.x = 0.f;
-                        if (!(bits & 2u)) v1.y = 0.f;
-                        if (!(bits & 4u)) v1.z = 0.f;
-                        if (!(bits & 8u)) v1.w = 0.f;
-                    }
-                    if (a.scale_o1) f = a.scale_o1[row];
-                }
-            }
-            ra1[it] = v1;
-            rs[it] = f;
-            if (TWO) ra2[it] = v2;
-        }
-#pragma unroll
-        for (int it = 0; it < BPT; ++it) {
-            const int idx = tid + it * 256;
-            // consecutive threads walk the contiguous axis of W: columns forward, k backward (W^T)
-            const int kk = BWD ? idx % KC : idx / BN, j = BWD ? idx / KC : idx % BN;
-            const int gk = k0 + kk, col = col0 + j;
-            float w1 = 0.f, w2 = 0.f;
-            if (gk < a.K && col < a.Nout) {
-                const int64_t id = BWD ? (int64_t)col * a.ldw + gk : (int64_t)gk * a.ldw + col;
-                w1 = a.B1[id];
-                if (TWO) w2 = a.B2[id];
-            }
-            rb1[it] = w1;
-            if (TWO) rb2[it] = w2;
-        }
-    };
-    auto stash = [&]() { // registers -> LDS
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int idx = tid + it * 256;
-            const int r = idx >> 3, c4 = (idx & 7) * 4;
-            if (BWD && a.scale_o1) scale4(ra1[it], rs[it]);         // rows of the first product only (dZ rows)
-            if (!BWD && TWO && a.scale2) scale4(ra2[it], rs[it]);   // rows of Hin kept scaled
-            *reinterpret_cast<float4 *>(&As1[r][c4]) = ra1[it];
-            if (TWO) *reinterpret_cast<float4 *>(&As2[r][c4]) = ra2[it];
-        }
-#pragma unroll
-        for (int it = 0; it < BPT; ++it) {
-            const int idx = tid + it * 256;
-            const int kk = BWD ? idx % KC : idx / BN, j = BWD ? idx / KC : idx % BN;
-            Bt1[j][kk] = rb1[it];
-            if (TWO) Bt2[j][kk] = rb2[it];
-        }
-    };
-
-    fetch(0);
-    for (int k0 = 0; k0 < a.K; k0 += KC) {
-        stash();
-        __syncthreads();
-        if (k0 + KC < a.K) fetch(k0 + KC);
-#pragma unroll
-        for (int j8 = 0; j8 < 4; ++j8) {
-            const float4 a1 = *reinterpret_cast<const float4 *>(&As1[wave * 32 + m][8 * j8 + 4 * h]);
-            float4 a2 = a1;
-            if (TWO) a2 = *reinterpret_cast<const float4 *>(&As2[wave * 32 + m][8 * j8 + 4 * h]);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const float4 b1 = *reinterpret_cast<const float4 *>(&Bt1[t * 32 + m][8 * j8 + 4 * h]);
-                float4 b2 = b1;
-                if (TWO) b2 = *reinterpret_cast<const float4 *>(&Bt2[t * 32 + m][8 * j8 + 4 * h]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc1[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(pick(a1, i), pick(b1, i), acc1[t], 0, 0, 0);
-                    if (TWO) acc2[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(pick(a2, i), pick(b2, i), acc2[t], 0, 0, 0);
-                }
-            }
-        }
-        __syncthreads();
-    }
-
-    // ---- epilogue: register r of a lane is row 8*(r/4) + 4*h + r%4 of the strip, column m of tile t ----
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int col = col0 + t * 32 + m;
-        const bool col_ok = col < a.Nout;
-        const float bias1 = (!BWD && col_ok) ? inner_bias<TWO>(a, col) : 0.f;
-        const float bias2 = (!BWD && TWO && col_ok) ? outer_bias(a, col) : 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t row = row0 + wave * 32 + 8 * (r / 4) + 4 * h + (r % 4);
-            if (!BWD) {
-                const float p = acc1[t][r] + bias1;
-                const bool pos = p > 0.f && col_ok;
-                if (a.act == SLICEGCN_ACT_RELU) {
-                    // lanes 0..31 hold one row of this tile, lanes 32..63 the row four below it
-                    const unsigned long long bal = __ballot(pos);
-                    if (m == 0 && row < a.n && col0 + t * 32 < a.Nout)
-                        a.mask[row * a.mask_words + ((col0 + t * 32) >> 5)] = h ? (uint32_t)(bal >> 32) : (uint32_t)bal;
-                }
-                const float rl = (a.act == SLICEGCN_ACT_RELU) ? (p > 0.f ? p : 0.f) : p;
-                const float o = rl + (TWO ? acc2[t][r] + bias2 : 0.f);
-                if (row < a.n && col_ok) a.O1[row * a.ldo1 + col] = a.scale_o1 ? o * a.scale_o1[row] : o;
-            } else {
-                if (row < a.n && col_ok) {
-                    a.O1[row * a.ldo1 + col] = acc1[t][r];
-                    if (TWO && a.O2) a.O2[row * a.ldo2 + col] = acc2[t][r];
-                }
-            }
-        }
-    }
-}
-
-// Variant for reduction lengths K <= 64 (every layer of the narrow-slice workloads): the weight
-// tiles are staged in LDS once per workgroup, which then walks over row tiles; each lane loads the
-// k values it feeds to the MFMA straight from global memory (16-byte loads, 32 contiguous bytes
-// per row and instruction), so there is no LDS round trip or barrier per row tile and all loads of
-// a tile are in flight at once.
-template <int NT, int KCH, bool BWD> // KCH: number of 32-wide K chunks (1 or 2)
-__global__ __launch_bounds__(256) void pair_mfma_direct_kernel(const PairArgs common, const PairBatch batch)
-{
-    const PairArgs a = slice_of(common, batch);
-    constexpr int BN = NT * 32, KK = KCH * 32;
-    __shared__ float Bs1[KK][BN];
-    __shared__ float Bs2[KK][BN];
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
-    const int m = lane & 31, h = lane >> 5;
-    const int col0 = 0;
+    const int col0 = (int)((b / 8) % n_col_tiles) * BN;
+    if (row_tile * 128 >= a.n) return; // uniform per workgroup (the last group of 8 row tiles may be partial)
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
-    const bool vec1 = aligned16(a.A1) && (a.lda1 % 4 == 0);
-    const bool vec2 = two && aligned16(a.A2) && (a.lda2 % 4 == 0);
+    const int chunks = (a.K + KC - 1) / KC, total = two ? 2 * chunks : chunks;
 
-    for (int idx = tid; idx < KK * BN; idx += 256) {
-        const int kk = idx / BN, j = idx % BN;
-        const int col = col0 + j;
-        float w1 = 0.f, w2 = 0.f;
-        if (kk < a.K && col < a.Nout) {
-            const int64_t id = BWD ? (int64_t)col * a.ldw + kk : (int64_t)kk * a.ldw + col;
-            w1 = a.B1[id];
-            if (two) w2 = a.B2[id];
-        }
-        Bs1[kk][j] = w1;
-        Bs2[kk][j] = w2;
+    if (!BWD && tid < BN) {
+        const int col = col0 + tid;
+        bias_s[0][tid] = col < a.Nout ? (two ? inner_bias<true>(a, col) : inner_bias<false>(a, col)) : 0.f;
+        bias_s[1][tid] = two && col < a.Nout ? outer_bias(a, col) : 0.f;
     }
-    __syncthreads();
 
-    const int64_t n_tiles = (a.n + 127) / 128;
-    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        // the weight tiles are re-read from LDS for every row tile: keeping them in registers across
-        // the loop would cost 64 registers per product and halve the wavefronts per SIMD
-        asm volatile("" ::: "memory");
-        const int64_t row = tile * 128 + wave * 32 + m; // the row this lane feeds as A operand
-        float4 a1[KCH * 4], a2[KCH * 4];
+    // The row this lane feeds.  Rows past the end and columns past the last one re-read the last: what they give is not
+    // stored.  Steps of k past K are zero in both operands.
+    const int64_t my_row = row_tile * 128 + wave * 32 + m, row = my_row < a.n ? my_row : a.n - 1;
+    const float *in_scale = BWD ? a.scale_o1 : (two ? a.scale2 : nullptr); // factor on the rows of one of the products:
+    const int scaled_product = BWD ? 0 : 1;                                // dZ rows; rows of Hin kept scaled
+    const float f_in = in_scale ? in_scale[row] : 1.f;
+
+    float raw[2][8];            // this lane's part of the next chunk of its row
+    uint32_t word = ~0u;        // backward: its activation bits
+    const float *src = nullptr;
+    const uint32_t *src_words = BWD && a.mask ? a.mask + row * a.mask_words : nullptr;
+    auto fetch_rows = [&](int cc) {
+        const bool second = cc >= chunks;
+        const int c = second ? cc - chunks : cc, k0 = c * KC;
+        if (c == 0) src = (second ? a.A2 + row * a.lda2 : a.A1 + row * a.lda1) + 8 * h; // first chunk of a product
 #pragma unroll
-        for (int q = 0; q < KCH * 4; ++q) {
-            const int kk = 8 * q + 4 * h;
-            float4 v1 = make_float4(0.f, 0.f, 0.f, 0.f), v2 = v1;
-            if (row < a.n && kk < a.K) {
-                v1 = load_k4(a.A1, a.lda1, row, kk, a.K, vec1);
-                if (!BWD) {
-                    if (two) {
-                        v2 = load_k4(a.A2, a.lda2, row, kk, a.K, vec2);
-                        if (a.scale2) scale4(v2, a.scale2[row]);
-                    }
-                } else {
-                    if (two) v2 = v1;
-                    if (a.mask) {
-                        const uint32_t bits = a.mask[row * a.mask_words + (kk >> 5)] >> (kk & 31);
-                        if (!(bits & 1u)) v1.x = 0.f;
-                        if (!(bits & 2u)) v1.y = 0.f;
-                        if (!(bits & 4u)) v1.z = 0.f;
-                        if (!(bits & 8u)) v1.w = 0.f;
-                    }
-                    if (a.scale_o1) scale4(v1, a.scale_o1[row]); // scales the rows of the first product only
-                }
+        for (int s = 0; s < 2; ++s) {
+            const float *p = src + k0 + 16 * s;
+            if (k0 + KC <= a.K) {
+                const floatx4_u u = *reinterpret_cast<const floatx4_u *>(p), v = *reinterpret_cast<const floatx4_u *>(p + 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { raw[s][i] = u[i]; raw[s][4 + i] = v[i]; }
+            } else {
+                load_k8(raw[s], p, k0 + 16 * s + 8 * h, a.K);
             }
-            a1[q] = v1;
-            a2[q] = v2;
         }
-        floatx16 acc1[NT], acc2[NT];
+        if (BWD && src_words) word = second ? ~0u : src_words[c];
+    };
+    float rw[UB][8];            // this thread's weights of the next chunk
+    // unit u of a chunk: consecutive threads walk the contiguous axis of W (columns forward, k backward)
+    auto unit_g = [&](int u) { return BWD ? u & 3 : u / BN; };
+    auto unit_c = [&](int u) { return BWD ? u >> 2 : u % BN; };
+    auto fetch_weights = [&](int cc) {
+        const bool second = cc >= chunks;
+        const float *W = second ? a.B2 : a.B1;
+        const int k0 = (second ? cc - chunks : cc) * KC;
+#pragma unroll
+        for (int j = 0; j < UB; ++j) {
+            const int u = tid + 256 * j;
+            if (4 * BN % 256 != 0 && u >= 4 * BN) break;
+            const int c = col0 + unit_c(u), k = k0 + 8 * unit_g(u), col = c < a.Nout ? c : a.Nout - 1;
+            const float *p = W + (BWD ? (int64_t)col * a.ldw + k : (int64_t)k * a.ldw + col);
+            if (BWD && k0 + KC <= a.K) {
+                const floatx4_u x = *reinterpret_cast<const floatx4_u *>(p), y = *reinterpret_cast<const floatx4_u *>(p + 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { rw[j][i] = x[i]; rw[j][4 + i] = y[i]; }
+            } else if (k0 + KC <= a.K) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) rw[j][i] = p[(int64_t)i * a.ldw];
+            } else if (BWD) {
+                load_k8(rw[j], p, k, a.K);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) rw[j][i] = k + i < a.K ? p[(int64_t)i * a.ldw] : 0.f;
+            }
+        }
+    };
+    auto stash_weights = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < UB; ++j) {
+            const int u = tid + 256 * j;
+            if (4 * BN % 256 != 0 && u >= 4 * BN) break;
+            const Split w = split8(rw[j]);
+            const int g = unit_g(u), c = unit_c(u);
+            Bs[buf][0][g][c] = w.hi; Bs[buf][1][g][c] = w.mid; Bs[buf][2][g][c] = w.low;
+        }
+    };
+
+    floatx16 acc[NT];
+    auto clear = [&]() {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) { acc1[t][r] = 0.f; acc2[t][r] = 0.f; }
+            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    };
+    // register r of lane (m, h): column 8 * (r / 4) + 4 * h + r % 4 of tile t
+    auto store = [&](float *O, int64_t ldo, const float *rs) {
+        if (my_row >= a.n) return;
+        const float f = rs ? rs[row] : 1.f;
+        float *o = O + row * ldo + col0 + 4 * h;
 #pragma unroll
-        for (int q = 0; q < KCH * 4; ++q)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int kk = 8 * q + 4 * h + i;
+            for (int q = 0; q < 4; ++q) {
+                const int c = 32 * t + 8 * q, left = a.Nout - col0 - 4 * h - c;
+                if (col0 + 32 * t + 32 <= a.Nout || left >= 4) { // the first test is the same for the whole workgroup
+                    floatx4_u v;
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    acc1[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(pick(a1[q], i), Bs1[kk][t * 32 + m], acc1[t], 0, 0, 0);
-                    if (two) acc2[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(pick(a2[q], i), Bs2[kk][t * 32 + m], acc2[t], 0, 0, 0);
+                    for (int i = 0; i < 4; ++i) v[i] = acc[t][4 * q + i] * f;
+                    *reinterpret_cast<floatx4_u *>(o + c) = v;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (i < left) o[c + i] = acc[t][4 * q + i] * f;
                 }
             }
-        const int64_t row0 = tile * 128;
+    };
+    auto activate = [&]() { // end of the first forward product: bias, activation and its bits, outer bias
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const int col = col0 + t * 32 + m;
-            const bool col_ok = col < a.Nout;
-            const float bias1 = (!BWD && col_ok) ? (two ? inner_bias<true>(a, col) : inner_bias<false>(a, col)) : 0.f;
-            const float bias2 = (!BWD && two && col_ok) ? outer_bias(a, col) : 0.f;
-            uint32_t my_word = 0u; // lane L < 32 collects the activation word of strip row L
+            uint32_t bits = 0u;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t orow = row0 + wave * 32 + 8 * (r / 4) + 4 * h + (r % 4);
-                if (!BWD) {
-                    const float p = acc1[t][r] + bias1;
-                    const bool pos = p > 0.f && col_ok;
+            for (int q = 0; q < 4; ++q) {
+                const float4 b1 = *reinterpret_cast<const float4 *>(&bias_s[0][32 * t + 8 * q + 4 * h]);
+                const float4 b2 = *reinterpret_cast<const float4 *>(&bias_s[1][32 * t + 8 * q + 4 * h]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float p = acc[t][4 * q + i] + pick(b1, i);
                     if (a.act == SLICEGCN_ACT_RELU) {
-                        // lanes 0..31 hold strip row 8*(r/4) + r%4 of this tile, lanes 32..63 the row four below it
-                        const unsigned long long bal = __ballot(pos);
-                        if (lane < 32 && r == 4 * (lane >> 3) + (lane & 3))
-                            my_word = ((lane >> 2) & 1) ? (uint32_t)(bal >> 32) : (uint32_t)bal;
+                        if (p > 0.f) bits |= 1u << (8 * q + i);
+                        else p = 0.f;
                     }
-                    const float rl = (a.act == SLICEGCN_ACT_RELU) ? (p > 0.f ? p : 0.f) : p;
-                    const float o = rl + (two ? acc2[t][r] + bias2 : 0.f);
-                    if (orow < a.n && col_ok) a.O1[orow * a.ldo1 + col] = a.scale_o1 ? o * a.scale_o1[orow] : o;
-                } else {
-                    if (orow < a.n && col_ok) {
-                        a.O1[orow * a.ldo1 + col] = acc1[t][r];
-                        if (a.O2) a.O2[orow * a.ldo2 + col] = acc2[t][r];
-                    }
+                    acc[t][4 * q + i] = two ? p + pick(b2, i) : p;
                 }
             }
-            if (!BWD && a.act == SLICEGCN_ACT_RELU && lane < 32 && col0 + t * 32 < a.Nout) {
-                const int64_t wrow = row0 + wave * 32 + lane; // one coalesced store of the strip's 32 words
-                if (wrow < a.n) a.mask[wrow * a.mask_words + ((col0 + t * 32) >> 5)] = my_word;
+            if (a.act == SLICEGCN_ACT_RELU) {
+                const int left = a.Nout - col0 - 32 * t; // columns of this word
+                bits <<= 4 * h;
+                bits |= __shfl_xor(bits, 32, 64);
+                if (left < 32) bits &= left > 0 ? (1u << left) - 1u : 0u;
+                if (h == 0 && my_row < a.n && left > 0) a.mask[row * a.mask_words + ((col0 >> 5) + t)] = bits;
+            }
+        }
+    };
+
+    clear();
+    fetch_weights(0);
+    fetch_rows(0);
+    stash_weights(0);
+    __syncthreads();
+    for (int cc = 0; cc < total; ++cc) {
+        const bool more = cc + 1 < total;
+        if (more) fetch_weights(cc + 1);
+        const bool scale_now = in_scale && (cc >= chunks) == (scaled_product == 1);
+        Split x[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if (BWD && src_words) {
+                const uint32_t bits = word >> (16 * s + 8 * h);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) raw[s][i] = __uint_as_float(__float_as_uint(raw[s][i]) & (uint32_t)((int32_t)(bits << (31 - i)) >> 31));
+            }
+            if (scale_now) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) raw[s][i] *= f_in;
+            }
+            x[s] = split8(raw[s]);
+        }
+        if (more) fetch_rows(cc + 1);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const bf16x8 (*w)[4][GS] = Bs[cc & 1];
+                acc[t] = mfma_split(Split{w[0][2 * s + h][32 * t + m], w[1][2 * s + h][32 * t + m], w[2][2 * s + h][32 * t + m]}, x[s], acc[t]);
+            }
+        if (more) stash_weights((cc + 1) & 1); // the buffer of the chunk before this one, which every wavefront has left
+        __syncthreads();
+        if (cc == chunks - 1) { // end of the first product
+            if (!BWD) activate();
+            else {
+                store(a.O1, a.ldo1, nullptr);
+                clear();
             }
         }
     }
+    if (!BWD) store(a.O1, a.ldo1, a.scale_o1);
+    else if (two && a.O2) store(a.O2, a.ldo2, nullptr);
 }
 
 // Variant for the narrowest layers (K <= 32, at most 32 output columns: every layer of the workload
@@ -805,36 +789,18 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
         SG_LAUNCH_CHECK();
         return SLICEGCN_OK;
     }
+    // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
-    if (a.K <= 64 && a.Nout <= 32) { // short reduction, one output tile: weights resident in LDS, workgroups walk over row tiles
-        const dim3 grid((unsigned)(row_tiles < 2048 ? row_tiles : 2048), by);
-        if (a.K <= 32) pair_mfma_direct_kernel<1, 1, BWD><<<grid, 256, 0, stream>>>(a, b);
-        else pair_mfma_direct_kernel<1, 2, BWD><<<grid, 256, 0, stream>>>(a, b);
-        SG_LAUNCH_CHECK();
-        return SLICEGCN_OK;
-    }
-    // staged kernel: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
-    // Column tiles per workgroup: 4 for a single product and 2 for a pair, which keeps two workgroups on a CU (64 and
-    // 2 x 32 accumulator registers): the other workgroup's MFMAs fill the barrier waits.  Wider tiles (256 columns,
-    // or 128 for a pair) run one workgroup per CU and are 20 % and 16 % slower on 256 -> 256 and 301 -> 128.
-    const int nt = a.Nout <= 32 ? 1 : a.Nout <= 64 ? 2 : a.Nout <= 96 ? 3 : 4;
-    const int cap = two ? 2 : 4;
-    const int nt2 = nt > cap ? cap : nt;
-    const int bn = nt2 * 32;
-    const int n_col = (a.Nout + bn - 1) / bn;
+    const int tiles = (a.Nout + 31) / 32;
+    const int nt = tiles < 4 ? tiles : 4, n_col = (tiles + nt - 1) / nt;
     const int64_t blocks = (row_tiles + 7) / 8 * 8 * n_col;
     SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
     const dim3 grid((unsigned)blocks, by);
-    if (two) {
-        if (nt2 == 1) pair_mfma_kernel<1, BWD, true><<<grid, 256, 0, stream>>>(a, b, n_col);
-        else pair_mfma_kernel<2, BWD, true><<<grid, 256, 0, stream>>>(a, b, n_col);
-    } else {
-        switch (nt2) {
-        case 1: pair_mfma_kernel<1, BWD, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 2: pair_mfma_kernel<2, BWD, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 3: pair_mfma_kernel<3, BWD, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        default: pair_mfma_kernel<4, BWD, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        }
+    switch (nt) {
+    case 1: pair_split_kernel<1, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    case 2: pair_split_kernel<2, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    case 3: pair_split_kernel<3, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    default: pair_split_kernel<4, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
     }
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -1647,7 +1613,7 @@ inline GradPlan grad_plan(int64_t n, int32_t w_in, int32_t w_out)
 // A dense layer's weight and bias gradients: 128 x 128 output tiles where the layer is wide, 32 x 32 tiles otherwise, a
 // partial sum per RED_ROWS node rows.  On few rows that would leave most of the chip idle behind chains of RED_ROWS rows, so
 // there (up to SMALL_LINEAR output elements) the rows are split until 512 workgroups are there or a workgroup is down to
-// one step, as far as the workspace has room (`capacity` partial sums): 5000 rows 96 -> 96: 132 -> LINSMALL us.
+// one step, as far as the workspace has room (`capacity` partial sums): 5000 rows 96 -> 96: 132 -> 15 us.
 struct LinearGradPlan {
     bool big;
     int32_t rows;

@@ -751,7 +751,7 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, 
         while (lpr < (pass_cols + V - 1) / V) lpr <<= 1; // 8, 16 or 32
         // How much a wavefront works through in turn.  On a large graph long runs amortise the chain of dependent loads
         // (descriptor, entries, gathers) across items; a small graph has too few items to fill the chip with such runs, so
-        // they are cut until about SMALL_GRID workgroups of each kind are there (2048 nodes, 64 columns: 11.3 -> SMALL_US us).
+        // they are cut until about SMALL_GRID workgroups of each kind are there (2048 nodes, 64 columns: 11.3 -> 6.5 us).
         const int64_t groups = 4 * (64 / lpr), copies = (int64_t)batch * passes;
         auto turns = [&](int64_t items, int64_t per_turn, int most) {
             const int64_t t = items * copies / (per_turn * SMALL_GRID);

@@ -1,0 +1,53 @@
+"""The dense products on the bf16 matrix cores keep fp32 accuracy: outputs and gradients at the edges of the kernels'
+tiles against fp64, with a bound an fp32 sum meets, operands over eight decades, and NaN in the padding of every operand."""
+import pytest
+import torch
+
+from paper_2408_11500_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 33, 1), (127, 65, 31), (128, 96, 33), (129, 97, 95), (1025, 128, 127), (511, 79, 129), (260, 609, 66), (4096, 40, 257),
+          (300_001, 72, 70)]
+
+
+def operand(gen, rows, cols, pad, spread):
+    full = torch.full((rows, cols + pad), float("nan"), device="cuda")
+    full[:, :cols] = torch.randn((rows, cols), generator=gen, device="cuda")
+    if spread:
+        full[:, :cols] *= 10 ** (torch.rand((rows, cols), generator=gen, device="cuda") * 8 - 4)
+    return full[:, :cols]
+
+
+def assert_fp32(got, want, scale, what):
+    """|got - want| within 3e-6 of the sum of the products' magnitudes, element by element."""
+    assert bool(torch.isfinite(got).all()), what
+    worst = ((got.double() - want).abs() / scale.clamp_min(1e-300)).max().item()
+    assert worst <= 3e-6, f"{what}: {worst:.2e}"
+
+
+@pytest.mark.parametrize("n,w_in,w_out", SHAPES)
+@pytest.mark.parametrize("pad,spread", [(0, False), (5, True)])
+def test_products_match_fp64(n, w_in, w_out, pad, spread):
+    gen = torch.Generator(device="cuda").manual_seed(n + 3 * w_in + 7 * w_out + pad)
+    X, dY = operand(gen, n, w_in, pad, spread), operand(gen, n, w_out, pad, spread)
+    W, b = operand(gen, w_in, w_out, 0, spread).contiguous(), torch.randn(w_out, generator=gen, device="cuda")
+    mask = torch.zeros((n, (w_out + 31) // 32), dtype=torch.int32, device="cuda")
+    Y = torch.full((n, w_out + 1), 7.0, device="cuda")
+    B.slicegcn_linear_fwd(X, W, b, Y[:, :w_out], mask, act=B.ACT_RELU)
+    bits = torch.stack([(mask >> j) & 1 for j in range(32)], dim=2).reshape(n, -1)
+    assert not bool(bits[:, w_out:].any()) and bool((Y[:, w_out] == 7.0).all())
+    on = bits[:, :w_out].double()
+    Xd, Wd, Gd = X.double(), W.double(), dY.double() * on
+    size = Xd.abs() @ Wd.abs() + b.double().abs()
+    pre = Xd @ Wd + b.double()
+    assert_fp32(Y[:, :w_out], pre * on, size, "Y")
+    assert bool(((on > 0) == (pre > 0))[pre.abs() > 3e-6 * size].all()), "activation pattern"
+    dX = torch.full((n, w_in + 1), 7.0, device="cuda")
+    dW, db = torch.empty_like(W), torch.empty_like(b)
+    ws = torch.empty(B.slicegcn_linear_bwd_full_workspace_bytes(n, w_in, w_out), dtype=torch.uint8, device="cuda")
+    B.slicegcn_linear_bwd(X, W, mask, dY, dX[:, :w_in], dW, db, ws, act=B.ACT_RELU)
+    assert bool((dX[:, w_in] == 7.0).all())
+    assert_fp32(dX[:, :w_in], Gd @ Wd.t(), Gd.abs() @ Wd.abs().t(), "dX")
+    assert_fp32(dW, Xd.t() @ Gd, Xd.abs().t() @ Gd.abs(), "dW")
+    assert_fp32(db, Gd.sum(0), Gd.abs().sum(0), "db")
