@@ -91,6 +91,9 @@ __device__ inline float pick(const float4 &v, int i) { return i == 0 ? v.x : i =
 // of the result) 0.69 / 2.4 / 10.0 e-7, with the fp32 instruction 1.02 / 2.9 / 11.6 e-7; the same order for positive operands and
 // for operands over eight decades, and all nine products give the same figures as six.  Beyond the bf16 range (|x| > 3.39e38)
 // and for infinities the split gives NaN where the fp32 product may be infinite.
+// The instruction rounds its sums down rather than to nearest: -2e-9 of the summed magnitudes at 256 products, invisible in one
+// result, but a sum over millions of results (a bias gradient) would add it up.  So the kernels negate one operand for half of what
+// is summed later (odd rows, every second block of rows) and negate the result back: what is left has no sign of its own.
 // Lane layout (l = lane): A operand = A[m = l % 32][k = 8 * (l / 32) + i], B operand = B[k = 8 * (l / 32) + i][n = l % 32],
 // accumulator register r = C[8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32].
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -187,6 +190,8 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
     // The row this lane feeds.  Rows past the end and columns past the last one re-read the last: what they give is not
     // stored.  Steps of k past K are zero in both operands.
     const int64_t my_row = row_tile * 128 + wave * 32 + m, row = my_row < a.n ? my_row : a.n - 1;
+    const uint32_t flip = (uint32_t)(m & 1) << 31; // odd rows are multiplied negated (see split8)
+    const float sign = m & 1 ? -1.f : 1.f;
     const float *in_scale = BWD ? a.scale_o1 : (two ? a.scale2 : nullptr); // factor on the rows of one of the products:
     const int scaled_product = BWD ? 0 : 1;                                // dZ rows; rows of Hin kept scaled
     const float f_in = in_scale ? in_scale[row] : 1.f;
@@ -262,7 +267,7 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
     // register r of lane (m, h): column 8 * (r / 4) + 4 * h + r % 4 of tile t
     auto store = [&](float *O, int64_t ldo, const float *rs) {
         if (my_row >= a.n) return;
-        const float f = rs ? rs[row] : 1.f;
+        const float f = rs ? sign * rs[row] : sign;
         float *o = O + row * ldo + col0 + 4 * h;
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -291,12 +296,12 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
                 const float4 b2 = *reinterpret_cast<const float4 *>(&bias_s[1][32 * t + 8 * q + 4 * h]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    float p = acc[t][4 * q + i] + pick(b1, i);
+                    float p = acc[t][4 * q + i] * sign + pick(b1, i);
                     if (a.act == SLICEGCN_ACT_RELU) {
                         if (p > 0.f) bits |= 1u << (8 * q + i);
                         else p = 0.f;
                     }
-                    acc[t][4 * q + i] = two ? p + pick(b2, i) : p;
+                    acc[t][4 * q + i] = sign * (two ? p + pick(b2, i) : p);
                 }
             }
             if (a.act == SLICEGCN_ACT_RELU) {
@@ -330,6 +335,8 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
 #pragma unroll
                 for (int i = 0; i < 8; ++i) raw[s][i] *= f_in;
             }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) raw[s][i] = __uint_as_float(__float_as_uint(raw[s][i]) ^ flip);
             x[s] = split8(raw[s]);
         }
         if (more) fetch_rows(cc + 1);
@@ -811,8 +818,6 @@ int launch_pair(const PairArgs &a, hipStream_t stream) { return launch_pair<BWD>
 
 // ---- weight-gradient reductions over the node axis ----------------------------------------
 constexpr int RED_ROWS = 1024; // rows per block: fp32 chains stay this short
-constexpr int RED_TILE = 32;   // output tile edge
-constexpr int RED_RK = 32;     // rows staged per step
 
 struct ReduceArgs {
     const float *Z; int64_t ldz;
@@ -824,8 +829,8 @@ struct ReduceArgs {
     int32_t w_in, w_out;
     int32_t stride;                     // 2*w_in*w_out + 2*w_out; compact: w_in*w_out + w_out
     int32_t compact;                    // 1: no self term and no slot for it: [Z^T dP | colsum dP]
-    int32_t rows_per_block = RED_ROWS;  // tiled kernels: node rows per workgroup (one partial each)
-    int32_t j_tiles = 1;                // tiled kernels: output tiles along w_out (grid depth = j_tiles x batch)
+    int32_t rows_per_block = RED_ROWS;  // grad_split_kernel: node rows per workgroup (one partial each)
+    int32_t j_tiles = 1;                // and output tiles along w_out
     const float *hin_scale = nullptr;   // rows of Hin are multiplied by hin_scale[row] when read (Hin stored as D~^-1/2 Hin)
 };
 
@@ -843,127 +848,228 @@ __device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatc
     return r;
 }
 
-// Partial weight gradients, tiled: grid = (row blocks, w_in tiles, slices x w_out tiles), every workgroup writes its
-// tile of the four results [Z^T dP | Hin^T dHout | colsum dP | colsum dHout] of its row block into
-// partial[row block][...].  Per step the workgroup stages 32 rows of the four operand tiles in LDS;
-// wavefront w multiplies rows 8w..8w+7 (the node axis is the MFMA's k axis: A[m][k] = Z[k][m]),
-// and the four wavefronts' accumulators are added in wavefront order at the end.
-__global__ __launch_bounds__(256) void grad_partial_mfma_kernel(const ReduceArgs common, const ReduceBatch batch)
+// Words and factors that are the same for a whole wavefront come through the scalar cache (read-only data of earlier launches).
+template <class T> __device__ inline T scalar_load(const T *p) { return *(const __attribute__((address_space(4))) T *)(uintptr_t)p; }
+
+// Partial weight gradients of every layer the strip kernels do not take: a workgroup forms one TI x TJ tile of one product (Z^T dP
+// or Hin^T dHout, the grid's depth) over its rows_per_block node rows.  The node axis is the k axis of the matrix
+// instructions.  Per step RK rows of both tiles are loaded (a thread reads eight rows of one column: a wavefront reads
+// contiguous pieces of rows, and their mask bits are the wavefront's lane mask), split into bf16 terms (see split8) on their way to LDS
+// in units of eight rows of a column, and multiplied by four wavefronts that own quarters of the tile; with fewer than four
+// 32 x 32 tiles they own steps of k and add up at the end in fixed order.  The next rows' loads are in flight behind the matrix
+// instructions.  Sums over RED_ROWS rows are added to a second set of accumulators, so chains stay as short as with one
+// partial per RED_ROWS rows while a workgroup can work through many of them: 2.4 M rows 256 x 256 wrote and re-read 1.2 GB of
+// partials before.  2.4 M rows 256 x 256: 3.82 -> 2.76 ms (116 TFLOP/s); 256 x 47: 1.91 -> 0.84 ms; 169 k rows, slice layers 64 x 64:
+// 65 -> 50 us per layer and product pair.  Bound by the loads and the splitting in turn with the matrix instructions (two workgroups
+// per CU).  Column sums (bias gradients) are taken from the loaded values.
+// Grid: x = 8 row blocks x all tiles per group of workgroups (a row block's tiles meet on one XCD), y = slice, z = product.
+template <int TI, int TJ>
+__global__ __launch_bounds__(256, 2) void grad_split_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
 {
-    const ReduceArgs a = slice_of(common, batch, blockIdx.z / common.j_tiles);
-    // one LDS block: the four operand tiles during the row loop, the accumulators of wavefronts 1..3 after it
-    constexpr int TILE_FLOATS = RED_RK * RED_TILE;
-    __shared__ __attribute__((aligned(16))) float lds[3 * 2 * RED_TILE * RED_TILE];
-    float (*Zs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds);
-    float (*Hs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + TILE_FLOATS);
-    float (*Ps)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + 2 * TILE_FLOATS);
-    float (*Gs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + 3 * TILE_FLOATS);
-    float (*red)[2][RED_TILE * RED_TILE] = reinterpret_cast<float (*)[2][RED_TILE * RED_TILE]>(lds);
+    const ReduceArgs a = slice_of(common, batch, blockIdx.y);
+    constexpr int RK = TI == 32 || TJ == 32 || TI + TJ <= 128 ? 64 : 32; // rows per step
+    constexpr int G = RK / 8, S = RK / 16;                               // units per column and step, k steps of the instructions
+    constexpr int UA = TI * G / 256, UB = TJ * G / 256;                  // units a thread stages
+    constexpr int MI = TI / 32, NJ = TJ / 32;
+    constexpr int WJ = NJ == 4 ? (MI == 1 ? 4 : 2) : NJ, WI = MI < 4 / WJ ? MI : 4 / WJ; // wavefronts along j and along i
+    constexpr int KS = 4 / (WI * WJ);                                    // wavefronts that share the k steps of a quarter
+    constexpr int TPI = MI / WI, TPJ = NJ / WJ;                          // 32 x 32 tiles of a wavefront
+    static_assert(WI * WJ * KS == 4 && TPI * WI == MI && TPJ * WJ == NJ && UA >= 1 && UB >= 1, "tile split");
+    __shared__ bf16x8 As[3][G][TI];
+    __shared__ bf16x8 Bs[3][G][TJ];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int i_base = blockIdx.y * RED_TILE, j_base = (blockIdx.z % common.j_tiles) * RED_TILE;
-    const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
+    const int64_t b = blockIdx.x;
+    const int64_t block = (b / (8 * n_tiles)) * 8 + (b % 8);
+    const int tile = (int)((b / 8) % n_tiles);
+    const int i_base = (tile / common.j_tiles) * TI, j_base = (tile % common.j_tiles) * TJ;
+    const int64_t r_begin = block * a.rows_per_block;
+    if (r_begin >= a.n) return; // uniform per workgroup
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
-    const bool self = a.Hin != nullptr;
-    const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vh = self && aligned16(a.Hin) && a.ldi % 4 == 0;
-    const bool vg = aligned16(a.dHout) && a.ldo % 4 == 0;
+    const bool self = blockIdx.z == 1; // the product Hin^T dHout
+    const float *X = self ? a.Hin : a.Z;
+    const int64_t ldx = self ? a.ldi : a.ldz;
+    const float *x_scale = self ? a.hin_scale : nullptr;
+    const uint32_t *mask = self ? nullptr : a.mask;
+    const bool sums = i_base == 0; // this workgroup also forms the column sums of its columns
 
-    floatx16 accA, accS;
+    float ra[UA][8], rb[UB][8];
+    // a wavefront's unit is 64 columns of eight rows (or 32 columns of two groups of rows): two mask words per row, together
+    // the lane mask of the loaded values
+    uint32_t mask_lo[UB][8], mask_hi[UB][8];
+    const float *pa[UA], *pb[UB];
+    // unit u of a tile of T columns: eight rows from row 8 * (u / T) of the step on, column u % T (past the last one: the
+    // last, what it gives is not stored)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { accA[r] = 0.f; accS[r] = 0.f; }
-    float accb = 0.f; // lanes 0..31: column (j_base + m) of dP, lanes 32..63: of dH_out; rows of this wavefront only
-
-    const int lr = tid >> 3, lc = (tid & 7) * 4; // this thread's float4 of each 32 x 32 tile
-    float4 z, hh, p, g;
-    float hf = 1.f; // factor of this thread's row of Hin (scaled layout); applied when the registers go to LDS
-    auto fetch = [&](int64_t r0) { // this thread's share of the four tiles of rows [r0, r0 + 32)
-        const int64_t row = r0 + lr;
-        z = make_float4(0.f, 0.f, 0.f, 0.f); hh = z; p = z; g = z;
-        if (row < r_end) {
-            if (i_base + lc < a.w_in) {
-                z = load_k4(a.Z, a.ldz, row, i_base + lc, a.w_in, vz);
-                if (self) {
-                    hh = load_k4(a.Hin, a.ldi, row, i_base + lc, a.w_in, vh);
-                    if (a.hin_scale) hf = a.hin_scale[row];
+    for (int q = 0; q < UA; ++q) {
+        const int u = tid + 256 * q, c = i_base + u % TI;
+        pa[q] = X + (r_begin + 8 * (u / TI)) * ldx + (c < a.w_in ? c : a.w_in - 1);
+    }
+#pragma unroll
+    for (int q = 0; q < UB; ++q) {
+        const int u = tid + 256 * q, c = j_base + u % TJ;
+        pb[q] = a.dHout + (r_begin + 8 * (u / TJ)) * a.ldo + (c < a.w_out ? c : a.w_out - 1);
+    }
+    auto fetch = [&](int64_t r0) {
+        const bool full = r0 + RK <= r_end; // uniform
+#pragma unroll
+        for (int q = 0; q < UA; ++q)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ra[q][i] = full || r0 + 8 * ((tid + 256 * q) / TI) + i < r_end ? pa[q][i * ldx] : 0.f;
+#pragma unroll
+        for (int q = 0; q < UB; ++q)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) rb[q][i] = full || r0 + 8 * ((tid + 256 * q) / TJ) + i < r_end ? pb[q][i * a.ldo] : 0.f;
+        if (mask) {
+#pragma unroll
+            for (int q = 0; q < UB; ++q) {
+                const int first = __builtin_amdgcn_readfirstlane(tid + 256 * q - lane);
+                const int64_t r_lo = r0 + 8 * (first / TJ), r_hi = r0 + 8 * ((first + 32) / TJ);
+                const int w_lo = (j_base + first % TJ) >> 5, w_hi = (j_base + (first + 32) % TJ) >> 5, words = (a.w_out + 31) >> 5;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int64_t lo = r_lo + i < r_end ? r_lo + i : r_end - 1, hi = r_hi + i < r_end ? r_hi + i : r_end - 1;
+                    mask_lo[q][i] = scalar_load(mask + lo * a.mask_words + (w_lo < words ? w_lo : words - 1));
+                    mask_hi[q][i] = scalar_load(mask + hi * a.mask_words + (w_hi < words ? w_hi : words - 1));
                 }
             }
-            if (j_base + lc < a.w_out) {
-                g = load_k4(a.dHout, a.ldo, row, j_base + lc, a.w_out, vg);
-                p = g;
-                if (a.mask) {
-                    const int j = j_base + lc;
-                    const uint32_t bits = a.mask[row * a.mask_words + (j >> 5)] >> (j & 31);
-                    if (!(bits & 1u)) p.x = 0.f;
-                    if (!(bits & 2u)) p.y = 0.f;
-                    if (!(bits & 4u)) p.z = 0.f;
-                    if (!(bits & 8u)) p.w = 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < UA; ++q) pa[q] += RK * ldx;
+#pragma unroll
+        for (int q = 0; q < UB; ++q) pb[q] += RK * a.ldo;
+    };
+    float col_sum[UB], col_total[UB];
+#pragma unroll
+    for (int q = 0; q < UB; ++q) { col_sum[q] = 0.f; col_total[q] = 0.f; }
+    auto stash = [&](int64_t r0, uint32_t flip) {
+#pragma unroll
+        for (int q = 0; q < UA; ++q) {
+            const int u = tid + 256 * q;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ra[q][i] = __uint_as_float(__float_as_uint(ra[q][i]) ^ flip);
+            if (x_scale) {
+                if constexpr (TI >= 64) { // one group of eight rows per wavefront
+                    const int64_t r = r0 + 8 * __builtin_amdgcn_readfirstlane(u / TI);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) ra[q][i] *= scalar_load(x_scale + (r + i < r_end ? r + i : r_end - 1));
+                } else {
+                    const int64_t r = r0 + 8 * (u / TI);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) ra[q][i] *= x_scale[r + i < r_end ? r + i : r_end - 1];
                 }
             }
+            const Split x = split8(ra[q]);
+            As[0][u / TI][u % TI] = x.hi; As[1][u / TI][u % TI] = x.mid; As[2][u / TI][u % TI] = x.low;
+        }
+#pragma unroll
+        for (int q = 0; q < UB; ++q) {
+            const int u = tid + 256 * q;
+            if (mask) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    rb[q][i] = __builtin_amdgcn_inverse_ballot_w64(((uint64_t)mask_hi[q][i] << 32) | mask_lo[q][i]) ? rb[q][i] : 0.f;
+            }
+            if (sums) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) col_sum[q] += rb[q][i];
+            }
+            const Split x = split8(rb[q]);
+            Bs[0][u / TJ][u % TJ] = x.hi; Bs[1][u / TJ][u % TJ] = x.mid; Bs[2][u / TJ][u % TJ] = x.low;
         }
     };
-    fetch(r_begin);
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += RED_RK) {
-        if (a.hin_scale) scale4(hh, hf);
-        *reinterpret_cast<float4 *>(&Zs[lr][lc]) = z;
-        *reinterpret_cast<float4 *>(&Hs[lr][lc]) = hh;
-        *reinterpret_cast<float4 *>(&Ps[lr][lc]) = p;
-        *reinterpret_cast<float4 *>(&Gs[lr][lc]) = g;
-        __syncthreads();
-        if (r0 + RED_RK < r_end) fetch(r0 + RED_RK); // next step's loads fly during this step's MFMAs
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-            const int k = wave * 8 + s4 * 2 + h;
-            accA = __builtin_amdgcn_mfma_f32_32x32x2f32(Zs[k][m], Ps[k][m], accA, 0, 0, 0);
-            if (self) accS = __builtin_amdgcn_mfma_f32_32x32x2f32(Hs[k][m], Gs[k][m], accS, 0, 0, 0);
-        }
-        if (blockIdx.y == 0) {
-            float (*T)[RED_TILE] = h ? Gs : Ps;
-#pragma unroll
-            for (int r = 0; r < 8; ++r) accb += T[wave * 8 + r][m];
-        }
-        __syncthreads();
-    }
 
-    // ---- add the four wavefronts' tiles in order, then store (the tile memory is free now) ----
-    __shared__ float bsum[4][64];
-    bsum[wave][lane] = accb;
-    if (wave > 0) {
+    floatx16 acc[TPI][TPJ], total[TPI][TPJ];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = 8 * (r / 4) + 4 * h + (r % 4);
-            red[wave - 1][0][i * RED_TILE + m] = accA[r];
-            red[wave - 1][1][i * RED_TILE + m] = accS[r];
-        }
-    }
-    __syncthreads();
-    float *out = a.partial + (int64_t)blockIdx.x * a.stride;
-    const int ww = a.w_in * a.w_out;
-    if (wave == 0) {
+    for (int ti = 0; ti < TPI; ++ti)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int il = 8 * (r / 4) + 4 * h + (r % 4);
-            float va = accA[r], vs = accS[r];
-            for (int q = 0; q < 3; ++q) { va += red[q][0][il * RED_TILE + m]; vs += red[q][1][il * RED_TILE + m]; }
-            const int i = i_base + il, j = j_base + m;
-            if (i < a.w_in && j < a.w_out) {
-                out[i * a.w_out + j] = va;
-                if (!a.compact) out[ww + i * a.w_out + j] = vs;
+        for (int tj = 0; tj < TPJ; ++tj)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { acc[ti][tj][r] = 0.f; total[ti][tj][r] = 0.f; }
+    const int ks = wave / (WI * WJ), wi = (wave / WJ) % WI * (TPI * 32), wj = wave % WJ * (TPJ * 32);
+
+    fetch(r_begin);
+    int chain = 0;
+    bool negated = block & 1; // every second chain of rows is multiplied negated (see split8)
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += RK) {
+        stash(r0, negated ? 0x80000000u : 0u);
+        __syncthreads();
+        if (r0 + RK < r_end) fetch(r0 + RK);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if (KS > 1 && s % KS != ks) continue; // uniform per wavefront
+            Split x[TPI];
+#pragma unroll
+            for (int ti = 0; ti < TPI; ++ti)
+                x[ti] = Split{As[0][2 * s + h][wi + 32 * ti + m], As[1][2 * s + h][wi + 32 * ti + m], As[2][2 * s + h][wi + 32 * ti + m]};
+#pragma unroll
+            for (int tj = 0; tj < TPJ; ++tj) {
+                const Split p{Bs[0][2 * s + h][wj + 32 * tj + m], Bs[1][2 * s + h][wj + 32 * tj + m], Bs[2][2 * s + h][wj + 32 * tj + m]};
+#pragma unroll
+                for (int ti = 0; ti < TPI; ++ti) acc[ti][tj] = mfma_split(x[ti], p, acc[ti][tj]);
             }
         }
-        if (blockIdx.y == 0) {
-            const int j = j_base + m;
-            const float sum = ((bsum[0][lane] + bsum[1][lane]) + bsum[2][lane]) + bsum[3][lane];
-            if (j < a.w_out && !(a.compact && h)) out[(a.compact ? ww : 2 * ww) + (h ? a.w_out : 0) + j] = sum;
+        __syncthreads();
+        chain += RK;
+        if (chain >= RED_ROWS || r0 + RK >= r_end) {
+            const float sign = negated ? -1.f : 1.f;
+            chain = 0;
+            negated = !negated;
+#pragma unroll
+            for (int ti = 0; ti < TPI; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < TPJ; ++tj)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) { total[ti][tj][r] += sign * acc[ti][tj][r]; acc[ti][tj][r] = 0.f; }
+#pragma unroll
+            for (int q = 0; q < UB; ++q) { col_total[q] += col_sum[q]; col_sum[q] = 0.f; }
         }
     }
+
+    float *out = a.partial + block * a.stride;
+    const int ww = a.w_in * a.w_out;
+    if (sums) { // the groups' column sums, added in order
+        float *red = reinterpret_cast<float *>(Bs);
+#pragma unroll
+        for (int q = 0; q < UB; ++q) red[tid + 256 * q] = col_total[q];
+        __syncthreads();
+        if (tid < TJ && j_base + tid < a.w_out) {
+            float s = 0.f;
+#pragma unroll
+            for (int g = 0; g < G; ++g) s += red[g * TJ + tid];
+            out[(a.compact ? ww : 2 * ww + (self ? a.w_out : 0)) + j_base + tid] = s;
+        }
+    }
+    if constexpr (KS > 1) {
+        float (*red)[32 * 32] = reinterpret_cast<float (*)[32 * 32]>(As); // one tile per wavefront in these variants
+        if (ks > 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) red[wave - WI * WJ][64 * r + lane] = total[0][0][r];
+        }
+        __syncthreads();
+        if (ks > 0) return;
+        for (int q = 1; q < KS; ++q)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) total[0][0][r] += red[wave + (q - 1) * WI * WJ][64 * r + lane];
+    }
+    if (self) out += ww;
+#pragma unroll
+    for (int ti = 0; ti < TPI; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < TPJ; ++tj)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int i = i_base + wi + 32 * ti + 8 * (r / 4) + 4 * h + (r % 4), j = j_base + wj + 32 * tj + m;
+                if (i < a.w_in && j < a.w_out) out[i * a.w_out + j] = total[ti][tj][r];
+            }
 }
 
 // Partial weight gradients of the narrowest layers (w_in, w_out <= 32, large n): every wavefront owns
 // its own accumulators and every n_waves-th strip of 32 rows (so that the chip reads one contiguous
 // window at a time), reads a strip with coalesced 16-byte loads into wave-private LDS tiles (the
 // next strip's loads in flight during the MFMAs), and writes one partial result.  The node axis is the MFMA's k axis (lane (m, h) feeds
-// column m of node row 2s + h).  No workgroup barrier; same output layout as grad_partial_mfma_kernel,
+// column m of node row 2s + h).  No workgroup barrier; same output layout as grad_split_kernel,
 // one partial per wavefront.
 __global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs common, const ReduceBatch batch, int64_t n_waves)
 {
@@ -1061,8 +1167,8 @@ __global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs comm
 // instead of twice.  Per strip of 32 rows: Z, Hin and dHout go to LDS with coalesced 16-byte loads (the next strip's
 // loads in flight behind the MFMAs); the node axis is the k axis of Z^T dP and Hin^T dHout (column reads of the
 // tiles), the column axis that of dZ = dP W_agg^T and T = dHout W_self^T (row reads, weights in registers); dZ and T
-// leave through the Z and Hin tiles as 16-byte stores.  Partial sums: one per wavefront, layout of
-// grad_partial_mfma_kernel.  `a` carries the input-gradient half: B1 / B2 = W_agg / W_self (ldw), O1 = dZ (rows
+// leave through the Z and Hin tiles as 16-byte stores.  Partial sums: one per wavefront, layout
+// of grad_split_kernel.  `a` carries the input-gradient half: B1 / B2 = W_agg / W_self (ldw), O1 = dZ (rows
 // scaled by scale_o1), O2 = T, K = w_out, Nout = w_in.
 __global__ __launch_bounds__(256, 2) void bwd_strip32_kernel(const ReduceArgs rcommon, const ReduceBatch rbatch, const PairArgs pcommon, const PairBatch pbatch,
                                                              int64_t n_waves)
@@ -1355,108 +1461,6 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
     }
 }
 
-// Partial weight gradient of a single product (compact layout: [X^T dP | colsum dP]) for wide
-// layers: one workgroup per 128 x 128 output tile and block of RED_ROWS rows, each wavefront owning a
-// 64 x 64 quarter (four MFMA accumulators).  Per step 32 rows of the X tile and of the dP tile are
-// staged in LDS (the next step's loads are issued into registers before this step's MFMAs); the
-// node axis is the MFMA's k axis.  32 flop per staged byte instead of 8 for 32 x 32 tiles.
-constexpr int GB_T = 128;
-
-__global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch)
-{
-    const ReduceArgs a = slice_of(common, batch, blockIdx.z / common.j_tiles);
-    __shared__ __attribute__((aligned(16))) float Xs[RED_RK][GB_T];
-    __shared__ __attribute__((aligned(16))) float Ps[RED_RK][GB_T];
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
-    const int m = lane & 31, h = lane >> 5;
-    const int i_base = blockIdx.y * GB_T, j_base = (blockIdx.z % common.j_tiles) * GB_T;
-    const int wi = (wave >> 1) * 64, wj = (wave & 1) * 64;
-    const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
-    const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
-    const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vg = aligned16(a.dHout) && a.ldo % 4 == 0;
-    const bool bias_wave = blockIdx.y == 0 && (wave >> 1) == 0;
-
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[ti][tj][r] = 0.f;
-    float accb = 0.f; // column j_base + wj + lane of dP
-
-    float4 rx[4], rp[4];
-    auto fetch = [&](int64_t r0) {
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int idx = tid + it * 256;
-            const int r = idx >> 5, c4 = (idx & 31) * 4;
-            const int64_t row = r0 + r;
-            float4 x = make_float4(0.f, 0.f, 0.f, 0.f), p = x;
-            if (row < r_end) {
-                if (i_base + c4 < a.w_in) x = load_k4(a.Z, a.ldz, row, i_base + c4, a.w_in, vz);
-                if (j_base + c4 < a.w_out) {
-                    p = load_k4(a.dHout, a.ldo, row, j_base + c4, a.w_out, vg);
-                    if (a.mask) {
-                        const int j = j_base + c4;
-                        const uint32_t bits = a.mask[row * a.mask_words + (j >> 5)] >> (j & 31);
-                        if (!(bits & 1u)) p.x = 0.f;
-                        if (!(bits & 2u)) p.y = 0.f;
-                        if (!(bits & 4u)) p.z = 0.f;
-                        if (!(bits & 8u)) p.w = 0.f;
-                    }
-                }
-            }
-            rx[it] = x;
-            rp[it] = p;
-        }
-    };
-    fetch(r_begin);
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += RED_RK) {
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int idx = tid + it * 256;
-            const int r = idx >> 5, c4 = (idx & 31) * 4;
-            *reinterpret_cast<float4 *>(&Xs[r][c4]) = rx[it];
-            *reinterpret_cast<float4 *>(&Ps[r][c4]) = rp[it];
-        }
-        __syncthreads();
-        if (r0 + RED_RK < r_end) fetch(r0 + RED_RK);
-#pragma unroll
-        for (int kp = 0; kp < RED_RK / 2; ++kp) {
-            const int k = 2 * kp + h;
-            const float a0 = Xs[k][wi + m], a1 = Xs[k][wi + 32 + m];
-            const float b0 = Ps[k][wj + m], b1 = Ps[k][wj + 32 + m];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-        }
-        if (bias_wave) {
-#pragma unroll
-            for (int r = 0; r < RED_RK; ++r) accb += Ps[r][wj + lane];
-        }
-        __syncthreads();
-    }
-
-    float *out = a.partial + (int64_t)blockIdx.x * a.stride;
-#pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = i_base + wi + 32 * ti + 8 * (r / 4) + 4 * h + (r % 4);
-                const int j = j_base + wj + 32 * tj + m;
-                if (i < a.w_in && j < a.w_out) out[i * a.w_out + j] = acc[ti][tj][r];
-            }
-    if (bias_wave) {
-        const int j = j_base + wj + lane;
-        if (j < a.w_out) out[a.w_in * a.w_out + j] = accb;
-    }
-}
-
 // Column sums of an n x w matrix (slice-encoding gradient): partial[block][w].
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const float *__restrict__ M, int64_t ld, int64_t n, int32_t w,
                                                              float *__restrict__ partial)
@@ -1572,68 +1576,85 @@ __global__ __launch_bounds__(1024) void reduce_final_kernel(const FinalBatch bat
 
 inline int64_t red_blocks(int64_t n) { return (n + RED_ROWS - 1) / RED_ROWS; }
 
-// Node rows per partial sum of a slice layer's weight gradients: RED_ROWS, or a quarter of it when that
-// would give the tiled kernel fewer than 2048 workgroups (a workgroup walks its rows in dependent steps
-// of 32, so on small graphs shorter walks in more workgroups finish sooner: cfg2 80 -> 35 us).
-inline int32_t layer_grad_rows(int64_t n, int32_t w_in, int32_t w_out)
+// Tiles and row blocks of grad_split_kernel for `products` products of w_in x w_out over n rows.
+struct SplitPlan {
+    int32_t ti, tj, tiles_i, tiles_j;
+    int32_t rows;     // node rows per workgroup
+    int64_t partials; // row blocks
+};
+inline SplitPlan split_plan(int64_t n, int32_t w_in, int32_t w_out, int products, int64_t capacity)
 {
-    const int64_t tiles = (int64_t)((w_in + RED_TILE - 1) / RED_TILE) * ((w_out + RED_TILE - 1) / RED_TILE);
-    return red_blocks(n) * tiles < 2048 ? RED_ROWS / 4 : RED_ROWS;
-}
-inline int64_t layer_grad_blocks(int64_t n, int32_t w_in, int32_t w_out)
-{
-    const int32_t rows = layer_grad_rows(n, w_in, w_out);
-    return (n + rows - 1) / rows;
+    SplitPlan p{32, 32, 0, 0, 0, 0};
+    // The tile with the least work: per 32 rows a SIMD spends about ti * tj * 0.094 cycles in matrix instructions and
+    // (ti + tj) * 3.5 on loading and splitting, on padding as on data (301 x 128: 5 x 1 tiles of 64 x 128, not 3 x 1 of 128 x 128).
+    double best = 0.;
+    for (int32_t ti = 32; ti <= 128; ti *= 2)
+        for (int32_t tj = 32; tj <= 128; tj *= 2) {
+            const int32_t ni = (w_in + ti - 1) / ti, nj = (w_out + tj - 1) / tj;
+            const double cost = (double)ni * nj * (ti * tj * 0.094 + (ti + tj) * 3.5);
+            if (p.tiles_i == 0 || cost < best) { best = cost; p.ti = ti; p.tj = tj; p.tiles_i = ni; p.tiles_j = nj; }
+        }
+    // Row blocks: 1024 workgroups, four per CU (two at a time), or as many as there are steps of rows on a small graph, as
+    // far as the workspace has room (`capacity` partial sums).
+    const int64_t step = p.ti == 32 || p.tj == 32 || p.ti + p.tj <= 128 ? 64 : 32;
+    int64_t blocks = 1024 / ((int64_t)p.tiles_i * p.tiles_j * products);
+    blocks = blocks < 1 ? 1 : blocks < capacity ? blocks : capacity;
+    p.rows = (int32_t)round_up((n + blocks - 1) / blocks, step);
+    p.partials = (n + p.rows - 1) / p.rows;
+    return p;
 }
 
 // How the weight gradients of a slice layer are formed: by which kernel, and in how many partial sums.  A function of the
-// sizes alone: the rows that go into one fp32 chain, and so the bits of a gradient, do not depend on the launch.
+// sizes and of the room for partial sums the entry point asks its callers for: the rows that go into one fp32 chain, and so
+// the bits of a gradient, do not depend on the launch.
+constexpr int64_t NO_LIMIT = (int64_t)1 << 40;
+// Partial sums slicegcn_layer_bwd has room for: one per 1024 rows, or per 256 while that leaves few (the size its callers know).
+inline int64_t layer_grad_blocks(int64_t n, int32_t w_in, int32_t w_out)
+{
+    const int64_t tiles = (int64_t)((w_in + 31) / 32) * ((w_out + 31) / 32), rows = red_blocks(n) * tiles < 2048 ? RED_ROWS / 4 : RED_ROWS;
+    return (n + rows - 1) / rows;
+}
 struct GradPlan {
     enum Kind { STRIP32, STRIP64, TILED } kind;
     int64_t partials;
-    int32_t rows; // TILED: node rows per workgroup
 };
-inline GradPlan grad_plan(int64_t n, int32_t w_in, int32_t w_out)
+inline GradPlan grad_plan(int64_t n, int32_t w_in, int32_t w_out, int64_t capacity)
 {
     const int64_t nb = layer_grad_blocks(n, w_in, w_out);
     if (w_in <= 32 && w_out <= 32 && n >= 65536) { // one partial sum per wavefront
         const int64_t strips = (n + 31) / 32, waves = nb < 8192 ? nb : 8192;
-        return GradPlan{GradPlan::STRIP32, waves < strips ? waves : strips, 0};
+        return GradPlan{GradPlan::STRIP32, waves < strips ? waves : strips};
     }
     if (w_in <= 64 && w_out <= 64 && n >= ((int64_t)1 << 21)) {
         // whole waves of resident workgroups (256 CUs x 3 workgroups x 4 wavefronts) where there are as many blocks
         const int64_t resident = 3072;
         const int64_t waves = nb >= resident ? nb / resident * resident : nb >= 2048 ? 2048 : nb;
         const int64_t strips = (n + 7) / 8; // strips of 8 rows in every variant launched here
-        return GradPlan{GradPlan::STRIP64, waves < strips ? waves : strips, 0};
+        return GradPlan{GradPlan::STRIP64, waves < strips ? waves : strips};
     }
-    return GradPlan{GradPlan::TILED, nb, layer_grad_rows(n, w_in, w_out)};
+    return GradPlan{GradPlan::TILED, split_plan(n, w_in, w_out, 2, capacity).partials};
 }
 
-// A dense layer's weight and bias gradients: 128 x 128 output tiles where the layer is wide, 32 x 32 tiles otherwise, a
-// partial sum per RED_ROWS node rows.  On few rows that would leave most of the chip idle behind chains of RED_ROWS rows, so
-// there (up to SMALL_LINEAR output elements) the rows are split until 512 workgroups are there or a workgroup is down to
-// one step, as far as the workspace has room (`capacity` partial sums): 5000 rows 96 -> 96: 132 -> 15 us.
-struct LinearGradPlan {
-    bool big;
-    int32_t rows;
-    int64_t partials;
-};
-constexpr int64_t NO_LIMIT = (int64_t)1 << 40, SMALL_LINEAR = (int64_t)1 << 19;
-inline LinearGradPlan linear_grad_plan(int64_t n, int32_t w_in, int32_t w_out, int64_t capacity)
+template <int TI>
+void launch_grad_split_i(const SplitPlan &p, dim3 grid, const ReduceArgs &r, const ReduceBatch &b, hipStream_t stream)
 {
-    LinearGradPlan p;
-    p.big = w_in > 64 || w_out > 64;
-    int64_t rows = RED_ROWS;
-    if (n * (w_in > w_out ? w_in : w_out) <= SMALL_LINEAR) {
-        const int32_t t = p.big ? GB_T : RED_TILE;
-        const int64_t tiles = (int64_t)((w_in + t - 1) / t) * ((w_out + t - 1) / t);
-        const int64_t fine = round_up(n * tiles / 512 + 1, RED_RK), least = round_up((n + capacity - 1) / capacity, RED_RK);
-        if (fine < rows) rows = fine > least ? fine : least;
-    }
-    p.rows = (int32_t)rows;
-    p.partials = (n + rows - 1) / rows;
-    return p;
+    const int tiles = p.tiles_i * p.tiles_j;
+    if (p.tj == 32) grad_split_kernel<TI, 32><<<grid, 256, 0, stream>>>(r, b, tiles);
+    else if (p.tj == 64) grad_split_kernel<TI, 64><<<grid, 256, 0, stream>>>(r, b, tiles);
+    else grad_split_kernel<TI, 128><<<grid, 256, 0, stream>>>(r, b, tiles);
+}
+int launch_grad_split(const SplitPlan &p, ReduceArgs r, const ReduceBatch &b, int batch, int products, hipStream_t stream)
+{
+    r.rows_per_block = p.rows;
+    r.j_tiles = p.tiles_j;
+    const int64_t blocks = (p.partials + 7) / 8 * 8 * p.tiles_i * p.tiles_j;
+    SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "weight gradients: grid too large");
+    const dim3 grid((unsigned)blocks, (unsigned)batch, (unsigned)products);
+    if (p.ti == 32) launch_grad_split_i<32>(p, grid, r, b, stream);
+    else if (p.ti == 64) launch_grad_split_i<64>(p, grid, r, b, stream);
+    else launch_grad_split_i<128>(p, grid, r, b, stream);
+    SG_LAUNCH_CHECK();
+    return SLICEGCN_OK;
 }
 
 // ---- pieces of the transform-first layer order -------------------------------------------------
@@ -1796,7 +1817,7 @@ static size_t linear_partial_bytes(int64_t partials, int32_t w_in, int32_t w_out
 // what the kernels use where the workspace allows it
 static size_t linear_full_bytes(int64_t n, int32_t w_in, int32_t w_out)
 {
-    return linear_partial_bytes(linear_grad_plan(n, w_in, w_out, NO_LIMIT).partials, w_in, w_out);
+    return linear_partial_bytes(split_plan(n, w_in, w_out, 1, NO_LIMIT).partials, w_in, w_out);
 }
 
 struct LinearGradArgs { // one layer of a batch (equal shapes and leading dimensions)
@@ -1814,14 +1835,11 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
 {
     const int ww = w_in * w_out;
     const int32_t stride = ww + w_out;
-    const LinearGradPlan plan = linear_grad_plan(n, w_in, w_out, (int64_t)(ws_each / ((size_t)stride * sizeof(float))));
+    const SplitPlan plan = split_plan(n, w_in, w_out, 1, (int64_t)(ws_each / ((size_t)stride * sizeof(float))));
     ReduceArgs r;
     r.Z = nullptr; r.ldz = ldx; r.Hin = nullptr; r.ldi = 0; r.dHout = nullptr; r.ldo = lddy;
     r.mask = nullptr; r.mask_words = mask_words;
     r.partial = nullptr; r.n = n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 1;
-    r.rows_per_block = plan.rows;
-    const int t = plan.big ? GB_T : RED_TILE;
-    r.j_tiles = (w_out + t - 1) / t;
     ReduceBatch b;
     FinalBatch f;
     for (int i = 0; i < BATCH; ++i) {
@@ -1831,10 +1849,7 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
         f.partial[i] = partial;
         f.dst[i] = FinalDst{{x.dW, nullptr, nullptr, x.db}, x.db_copy, {0, ww, ww, ww, stride}};
     }
-    const dim3 grid((unsigned)plan.partials, (unsigned)((w_in + t - 1) / t), (unsigned)(r.j_tiles * batch));
-    if (plan.big) grad_big_mfma_kernel<<<grid, 256, 0, stream>>>(r, b);
-    else grad_partial_mfma_kernel<<<grid, 256, 0, stream>>>(r, b);
-    SG_LAUNCH_CHECK();
+    if (int rc = launch_grad_split(plan, r, b, batch, 1, stream)) return rc;
     reduce_final_kernel<<<dim3((unsigned)((stride + 31) / 32), (unsigned)batch), 1024, 0, stream>>>(f, plan.partials, stride, stride);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -1864,17 +1879,18 @@ static size_t fwd_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *d)
     if (transform_first(d)) return 2 * mat_bytes(g->n, d->w_out) + spmm_workspace_bytes(g->fwd, d->w_out);
     return spmm_workspace_bytes(g->fwd, d->w_in);
 }
-static size_t bwd_partial_bytes(int64_t n, const slicegcn_layer_desc *d)
+static int64_t layer_capacity(int64_t n, const slicegcn_layer_desc *d, bool full) { return full ? NO_LIMIT : layer_grad_blocks(n, d->w_in, d->w_out); }
+static size_t bwd_partial_bytes(int64_t n, const slicegcn_layer_desc *d, bool full)
 {
     const size_t stride = 2 * (size_t)d->w_in * d->w_out + 2 * (size_t)d->w_out;
-    return (size_t)round_up((int64_t)(layer_grad_blocks(n, d->w_in, d->w_out) * stride * sizeof(float)), 256);
+    return (size_t)round_up((int64_t)((full ? grad_plan(n, d->w_in, d->w_out, NO_LIMIT).partials : layer_grad_blocks(n, d->w_in, d->w_out)) * stride * sizeof(float)), 256);
 }
 static size_t bwd_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *d, bool need_dHin, bool full)
 {
     if (transform_first(d)) // [dP | G | W_agg^T | W_self^T | reduction partials | aggregation workspace]
         return 2 * mat_bytes(g->n, d->w_out) + 2 * tf_wt_bytes(d) + tf_red_bytes(g->n, d, full) + spmm_workspace_bytes(g->tr, d->w_out);
     // [partial weight gradients | dZ (only with dHin) | aggregation workspace (only with dHin)]
-    size_t bytes = bwd_partial_bytes(g->n, d);
+    size_t bytes = bwd_partial_bytes(g->n, d, full);
     if (need_dHin) bytes += mat_bytes(g->n, d->w_in) + spmm_workspace_bytes(g->tr, d->w_in);
     return bytes;
 }
@@ -2046,7 +2062,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
     if (transform_first(desc)) return bwd_transform_first(g, lg, io, batch, ws, full, stream);
     const int w_in = desc->w_in, w_out = desc->w_out;
     const bool self = io[0].params.W_self != nullptr, need_dHin = io[0].dHin != nullptr, relu = desc->act == SLICEGCN_ACT_RELU;
-    const size_t part = bwd_partial_bytes(g->n, desc), mat = mat_bytes(g->n, w_in), agg = spmm_workspace_bytes(g->tr, w_in);
+    const size_t part = bwd_partial_bytes(g->n, desc, full), mat = mat_bytes(g->n, w_in), agg = spmm_workspace_bytes(g->tr, w_in);
     Sections sec{static_cast<char *>(ws), batch};
     char *parts = sec.take(part), *dZs = need_dHin ? sec.take(mat) : nullptr, *agg_ws = need_dHin ? sec.take(agg) : nullptr;
 
@@ -2065,7 +2081,8 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         a.n = g->n; a.K = w_out; a.Nout = w_in; a.ldw = w_out; a.act = desc->act;
         a.scale_o1 = g->dinv; // dZ is staged as D~^-1/2 dZ: its aggregation then skips the stored values
     }
-    const GradPlan plan = grad_plan(g->n, w_in, w_out);
+    const int64_t capacity = layer_capacity(g->n, desc, full);
+    const GradPlan plan = grad_plan(g->n, w_in, w_out, capacity);
     // narrow layers with a self term: the kernel that forms the weight gradients also forms dZ and T (one read of dHout)
     const bool fused_inputs = need_dHin && self && plan.kind == GradPlan::STRIP32;
 
@@ -2077,8 +2094,6 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         r.Z = nullptr; r.ldz = lg->ldz; r.Hin = nullptr; r.ldi = lg->ldi; r.dHout = nullptr; r.ldo = lg->ldgo;
         r.mask = nullptr; r.mask_words = lg->mask_words;
         r.partial = nullptr; r.n = g->n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 0;
-        r.rows_per_block = plan.rows;
-        r.j_tiles = (w_out + RED_TILE - 1) / RED_TILE;
         r.hin_scale = (desc->flags & SLICEGCN_LAYER_IN_SCALED) ? g->sqrtd : nullptr;
         ReduceBatch b;
         FinalBatch f;
@@ -2111,8 +2126,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
             else grad_strip64_kernel<2, 2, 8, 2><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
             break;
         case GradPlan::TILED:
-            grad_partial_mfma_kernel<<<dim3((unsigned)plan.partials, (unsigned)((w_in + RED_TILE - 1) / RED_TILE), (unsigned)(r.j_tiles * batch)),
-                                       256, 0, stream>>>(r, b);
+            if (int rc = launch_grad_split(split_plan(g->n, w_in, w_out, 2, capacity), r, b, batch, self ? 2 : 1, stream)) return rc;
             break;
         }
         SG_LAUNCH_CHECK();
