@@ -89,14 +89,17 @@ __device__ inline float pick(const float4 &v, int i) { return i == 0 ? v.x : i =
 // v_mfma_f32_32x32x16_bf16 with fp32 accumulation, smallest first: six instructions of 32 cycles for 16 steps of k, where
 // v_mfma_f32_32x32x2_f32 takes 512 cycles (192 against 512).  Against fp64, normal operands, sums of 32 / 256 / 4096 products: error (rms over rms
 // of the result) 0.69 / 2.4 / 10.0 e-7, with the fp32 instruction 1.02 / 2.9 / 11.6 e-7; the same order for positive operands and
-// for operands over eight decades, and all nine products give the same figures as six.  Beyond the bf16 range (|x| > 3.39e38)
-// and for infinities the split gives NaN where the fp32 product may be infinite.
+// for operands over eight decades, and all nine products give the same figures as six.
+// An infinite operand, or one beyond the bf16 range (|x| > 3.39e38), leaves NaN where the fp32 product may be infinite or finite, and an
+// activation would turn that NaN into zero.  So every wavefront looks at its sums (nonfinite) and forms its tile again with the
+// fp32 instruction if one of them is not finite: infinities and NaN come out as a chain of fp32 products gives them.
 // The instruction rounds its sums down rather than to nearest: -2e-9 of the summed magnitudes at 256 products, invisible in one
 // result, but a sum over millions of results (a bias gradient) would add it up.  So the kernels negate one operand for half of what
 // is summed later (odd rows, every second block of rows) and negate the result back: what is left has no sign of its own.
 // Lane layout (l = lane): A operand = A[m = l % 32][k = 8 * (l / 32) + i], B operand = B[k = 8 * (l / 32) + i][n = l % 32],
 // accumulator register r = C[8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32].
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4))); // 16-byte accesses at any 4-byte boundary
 
 typedef float floatx2 __attribute__((ext_vector_type(2)));
@@ -132,6 +135,13 @@ __device__ inline floatx16 mfma_split(const Split &a, const Split &b, floatx16 c
     c = mfma_bf16(a.hi, b.mid, c);
     return mfma_bf16(a.hi, b.hi, c);
 }
+// 0 where every element of c is finite, otherwise NaN; added to `seen`
+__device__ inline float nonfinite(const floatx16 &c, float seen)
+{
+#pragma unroll
+    for (int r = 0; r < 16; ++r) seen = fmaf(c[r], 0.f, seen);
+    return seen;
+}
 
 // Eight consecutive floats of a row of K columns from column k on, zero beyond column K
 __device__ inline void load_k8(float (&x)[8], const float *p, int k, int K)
@@ -146,60 +156,233 @@ __device__ inline void load_k8(float (&x)[8], const float *p, int k, int K)
     }
 }
 
-// Pair kernel.  Workgroup = 4 wavefronts; a wavefront owns 32 rows and all NT * 32 columns of the workgroup's tile.
-// A row is used by one wavefront only, so it goes from memory straight into registers (a lane loads the eight k of its row
-// that it feeds to the matrix cores) and is split there.  The weights are shared: 32 steps of k at a time are split on their way
-// to LDS (two buffers, one barrier per chunk), in units of eight k of a column, so that an operand is one 16-byte read.
-// The weights are the A operand and the rows the B operand: a lane then holds four consecutive columns of one row in four
-// registers, stores them as 16 bytes and collects the activation bits of its row without votes.  The rows of the next
-// chunk are requested as soon as the current ones are split (both steps at once: they share cache lines), its weights
-// before the current chunk's matrix instructions.
-// Two products run one after the other over the same accumulators: forward the second one is added to the activated first
-// one; backward the first result is stored before the second begins.
-// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 take 2.2 ms (fp32 instruction: 3.7), 147 TFLOP/s = 880 of bf16,
-// where a large bf16 matrix product of the library reaches 1270 on this card (the clock gives way under matrix load).  64 rows
-// per wavefront, 64 columns per workgroup, and the weights resident in LDS for the whole reduction (no barriers) were within 10 % of
-// this or slower.  256 -> 47: 0.74 ms (0.98), bound by the rows' loads (4.0 TB/s).
-// Workgroups are numbered so that the column tiles of one row tile run back to back on the same XCD (workgroup b goes to
-// XCD b mod 8): the rows are fetched from memory once and re-read from L2.
-template <int NT, bool BWD>
-__global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+// Workgroup b of a grid of row tiles x column tiles (1-D, 8 row tiles x all column tiles per group of workgroups): the column
+// tiles of one row tile run back to back on the same XCD (workgroup b goes to XCD b mod 8), so the rows are fetched from memory
+// once and re-read from L2.  The last group of 8 row tiles may be partial.
+struct TilePlace { int64_t row_tile; int col_tile; };
+__device__ inline TilePlace tile_place(int n_col_tiles)
+{
+    const int64_t b = blockIdx.x;
+    return TilePlace{(b / (8 * n_col_tiles)) * 8 + (b % 8), (int)((b / 8) % n_col_tiles)};
+}
+
+// Four consecutive columns per lane and register group of a 32-column tile to row `o` (+ 4 * h + 8 * q); `width` columns exist from
+// the tile's first one on
+__device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int width, float f)
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int at = 8 * q + 4 * h, left = width - at;
+        if (width >= 32 || left >= 4) { // the first test is the same for the whole workgroup
+            floatx4_u v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = c[4 * q + i] * f;
+            *reinterpret_cast<floatx4_u *>(o + at) = v;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (i < left) o[at + i] = c[4 * q + i] * f;
+        }
+    }
+}
+
+// Forward products of every layer the strip kernels do not take: Hout = act(Z W_agg + b) + Hin W_self + b_self.  Workgroup = 4
+// wavefronts; a wavefront owns 32 rows and all NT * 32 columns of the workgroup's tile.  A row is used by one wavefront only, so it
+// goes from memory straight into registers (a lane loads the k of its row that it feeds to the matrix cores, the next chunk's
+// while the current one is multiplied).  The weights are shared and go through LDS: 32 steps of k at a time, two buffers, one
+// barrier per chunk, in units of four k of a column, so that a 16-byte read feeds four instructions.  The weights are the A
+// operand and the rows the B operand: a lane then holds four consecutive columns of one row in four registers, stores
+// them as 16 bytes and collects the activation bits of its row without votes.
+// It stays on the fp32 instruction, and in the order of the strip kernels (chains over all of k, a step takes k and k + 4, one chain
+// per product): whether an activation passes depends on the last bit of its sum where that is near zero, and then a row's
+// gradient changes by a whole term.  Every kernel and size gives the same pattern for the same operands.
+template <int NT, bool TWO>
+__global__ __launch_bounds__(256, NT == 4 ? 2 : 3) void pair_fwd_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
 {
     const PairArgs a = slice_of(common, batch);
-    constexpr int BN = NT * 32, KC = 32;
-    constexpr int GS = BN + 4;                 // units per group of eight k (padded: conflict-free writes in both directions)
-    constexpr int UB = (4 * BN + 255) / 256;   // units a thread stages per chunk
-    __shared__ bf16x8 Bs[2][3][4][GS];
+    constexpr int BN = NT * 32, KC = 32, GS = BN + 4; // GS: units per group of four k (padded: conflict-free writes and reads)
+    __shared__ floatx4 Bs[2][KC / 4][GS];
     __shared__ __attribute__((aligned(16))) float bias_s[2][BN];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int64_t b = blockIdx.x;
-    const int64_t row_tile = (b / (8 * n_col_tiles)) * 8 + (b % 8);
-    const int col0 = (int)((b / 8) % n_col_tiles) * BN;
-    if (row_tile * 128 >= a.n) return; // uniform per workgroup (the last group of 8 row tiles may be partial)
+    const TilePlace place = tile_place(n_col_tiles);
+    const int64_t row_tile = place.row_tile;
+    const int col0 = place.col_tile * BN;
+    if (row_tile * 128 >= a.n) return; // uniform per workgroup
+    const int chunks = (a.K + KC - 1) / KC, total = TWO ? 2 * chunks : chunks;
+
+    if (tid < BN) {
+        const int col = col0 + tid;
+        bias_s[0][tid] = col < a.Nout ? inner_bias<TWO>(a, col) : 0.f;
+        bias_s[1][tid] = TWO && col < a.Nout ? outer_bias(a, col) : 0.f;
+    }
+    // The row this lane feeds.  Rows past the end and columns past the last one re-read the last: what they give is not
+    // stored.  Steps of k past K are zero in both operands.
+    const int64_t my_row = row_tile * 128 + wave * 32 + m, row = my_row < a.n ? my_row : a.n - 1;
+    const float f_in = TWO && a.scale2 ? a.scale2[row] : 1.f; // rows of Hin kept scaled
+
+    floatx4 next[KC / 8];
+    const float *src = nullptr;
+    auto fetch_rows = [&](int cc) {
+        const bool second = TWO && cc >= chunks;
+        const int c = second ? cc - chunks : cc, k0 = c * KC;
+        if (c == 0) src = (second ? a.A2 + row * a.lda2 : a.A1 + row * a.lda1) + 4 * h; // first chunk of a product
+#pragma unroll
+        for (int q = 0; q < KC / 8; ++q) {
+            const float *p = src + k0 + 8 * q;
+            if (k0 + KC <= a.K) {
+                next[q] = *reinterpret_cast<const floatx4_u *>(p);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) next[q][i] = k0 + 8 * q + 4 * h + i < a.K ? p[i] : 0.f;
+            }
+        }
+    };
+    floatx4 rw[NT]; // this thread's weights of the next chunk: unit u = group u / BN of four k, column u % BN
+    auto fetch_weights = [&](int cc) {
+        const bool second = TWO && cc >= chunks;
+        const int k0 = (second ? cc - chunks : cc) * KC;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int u = tid + 256 * j, c = col0 + u % BN, k = k0 + 4 * (u / BN), col = c < a.Nout ? c : a.Nout - 1;
+            const float *p = (second ? a.B2 : a.B1) + (int64_t)k * a.ldw + col;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) rw[j][i] = k0 + KC <= a.K || k + i < a.K ? p[(int64_t)i * a.ldw] : 0.f;
+        }
+    };
+    auto stash_weights = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int u = tid + 256 * j;
+            Bs[buf][u / BN][u % BN] = rw[j];
+        }
+    };
+
+    floatx16 acc[NT], first[TWO ? NT : 1]; // first: the activated first product
+    auto clear = [&]() {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    };
+    // register r of lane (m, h): column 8 * (r / 4) + 4 * h + r % 4 of tile t
+    auto activate = [&](floatx16 &c, int t) { // end of the first product: bias, activation and its bits
+        uint32_t bits = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 b1 = *reinterpret_cast<const float4 *>(&bias_s[0][32 * t + 8 * q + 4 * h]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float p = c[4 * q + i] + pick(b1, i);
+                if (a.act == SLICEGCN_ACT_RELU) {
+                    if (p > 0.f) bits |= 1u << (8 * q + i);
+                    else p = 0.f;
+                }
+                c[4 * q + i] = p;
+            }
+        }
+        if (a.act == SLICEGCN_ACT_RELU) {
+            const int left = a.Nout - col0 - 32 * t; // columns of this word
+            bits <<= 4 * h;
+            bits |= __shfl_xor(bits, 32, 64);
+            if (left < 32) bits &= left > 0 ? (1u << left) - 1u : 0u;
+            if (h == 0 && my_row < a.n && left > 0) a.mask[row * a.mask_words + ((col0 >> 5) + t)] = bits;
+        }
+    };
+
+    clear();
+    fetch_weights(0);
+    fetch_rows(0);
+    stash_weights(0);
+    __syncthreads();
+    for (int cc = 0; cc < total; ++cc) {
+        const bool more = cc + 1 < total;
+        if (more) fetch_weights(cc + 1);
+        floatx4 x[KC / 8];
+#pragma unroll
+        for (int q = 0; q < KC / 8; ++q) x[q] = next[q];
+        if (TWO && a.scale2 && cc >= chunks) {
+#pragma unroll
+            for (int q = 0; q < KC / 8; ++q) x[q] *= f_in;
+        }
+        if (more) fetch_rows(cc + 1);
+#pragma unroll
+        for (int q = 0; q < KC / 8; ++q) {
+            floatx4 w[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) w[t] = Bs[cc & 1][2 * q + h][32 * t + m];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[t][i], x[q][i], acc[t], 0, 0, 0);
+        }
+        if (more) stash_weights((cc + 1) & 1); // the buffer of the chunk before this one, which every wavefront has left
+        __syncthreads();
+        if (TWO && cc == chunks - 1) { // end of the first product
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                activate(acc[t], t);
+                first[TWO ? t : 0] = acc[t];
+            }
+            clear();
+        }
+    }
+    const float f_out = a.scale_o1 ? a.scale_o1[row] : 1.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if constexpr (TWO) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 b2 = *reinterpret_cast<const float4 *>(&bias_s[1][32 * t + 8 * q + 4 * h]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[t][4 * q + i] = first[t][4 * q + i] + (acc[t][4 * q + i] + pick(b2, i));
+            }
+        } else {
+            activate(acc[t], t);
+        }
+        if (my_row < a.n) store_tile_row(acc[t], a.O1 + row * a.ldo1 + col0 + 32 * t, h, a.Nout - col0 - 32 * t, f_out);
+    }
+}
+
+// Backward products of the layers the strip kernels do not take: dZ = (dHout * mask) W_agg^T, T = dHout W_self^T, one after the
+// other over the same accumulators.  Rows, weights and tiles as in the forward kernel, but on the bf16 matrix cores (see split8):
+// a lane loads and splits eight k of its row, the weights are split on their way to LDS in units of eight k of a column.
+// The rows of the next chunk are requested as soon as the current ones are split (both steps at once: they share cache
+// lines), its weights before the current chunk's matrix instructions.
+// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 take 2.0 ms (fp32 instruction, two column tiles of 128: 4.3), 160 TFLOP/s =
+// 960 of bf16, where a large bf16 matrix product of the library reaches 1270 on this card (the clock gives way under matrix
+// load).  64 rows per wavefront, 64 columns per workgroup, and the weights resident in LDS for the whole reduction (no
+// barriers) were within 10 % of this or slower.
+template <int NT>
+__global__ __launch_bounds__(256, 3) void pair_bwd_split_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+{
+    const PairArgs a = slice_of(common, batch);
+    constexpr int BN = NT * 32, KC = 32;
+    constexpr int GS = BN + 4;                 // units per group of eight k (padded: conflict-free writes and reads)
+    constexpr int UB = (4 * BN + 255) / 256;   // units a thread stages per chunk
+    __shared__ bf16x8 Bs[2][3][4][GS];
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63;
+    const int m = lane & 31, h = lane >> 5;
+    const TilePlace place = tile_place(n_col_tiles);
+    const int64_t row_tile = place.row_tile;
+    const int col0 = place.col_tile * BN;
+    if (row_tile * 128 >= a.n) return; // uniform per workgroup
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
     const int chunks = (a.K + KC - 1) / KC, total = two ? 2 * chunks : chunks;
-
-    if (!BWD && tid < BN) {
-        const int col = col0 + tid;
-        bias_s[0][tid] = col < a.Nout ? (two ? inner_bias<true>(a, col) : inner_bias<false>(a, col)) : 0.f;
-        bias_s[1][tid] = two && col < a.Nout ? outer_bias(a, col) : 0.f;
-    }
 
     // The row this lane feeds.  Rows past the end and columns past the last one re-read the last: what they give is not
     // stored.  Steps of k past K are zero in both operands.
     const int64_t my_row = row_tile * 128 + wave * 32 + m, row = my_row < a.n ? my_row : a.n - 1;
     const uint32_t flip = (uint32_t)(m & 1) << 31; // odd rows are multiplied negated (see split8)
     const float sign = m & 1 ? -1.f : 1.f;
-    const float *in_scale = BWD ? a.scale_o1 : (two ? a.scale2 : nullptr); // factor on the rows of one of the products:
-    const int scaled_product = BWD ? 0 : 1;                                // dZ rows; rows of Hin kept scaled
-    const float f_in = in_scale ? in_scale[row] : 1.f;
+    const float f_in = a.scale_o1 ? a.scale_o1[row] : 1.f; // rows of the first product
 
     float raw[2][8];            // this lane's part of the next chunk of its row
-    uint32_t word = ~0u;        // backward: its activation bits
+    uint32_t word = ~0u;        // its activation bits
     const float *src = nullptr;
-    const uint32_t *src_words = BWD && a.mask ? a.mask + row * a.mask_words : nullptr;
+    const uint32_t *src_words = a.mask ? a.mask + row * a.mask_words : nullptr;
     auto fetch_rows = [&](int cc) {
         const bool second = cc >= chunks;
         const int c = second ? cc - chunks : cc, k0 = c * KC;
@@ -215,12 +398,9 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
                 load_k8(raw[s], p, k0 + 16 * s + 8 * h, a.K);
             }
         }
-        if (BWD && src_words) word = second ? ~0u : src_words[c];
+        if (src_words) word = second ? ~0u : src_words[c];
     };
-    float rw[UB][8];            // this thread's weights of the next chunk
-    // unit u of a chunk: consecutive threads walk the contiguous axis of W (columns forward, k backward)
-    auto unit_g = [&](int u) { return BWD ? u & 3 : u / BN; };
-    auto unit_c = [&](int u) { return BWD ? u >> 2 : u % BN; };
+    float rw[UB][8];            // this thread's weights of the next chunk: unit u = group u % 4 of eight k, column u / 4
     auto fetch_weights = [&](int cc) {
         const bool second = cc >= chunks;
         const float *W = second ? a.B2 : a.B1;
@@ -229,21 +409,8 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
         for (int j = 0; j < UB; ++j) {
             const int u = tid + 256 * j;
             if (4 * BN % 256 != 0 && u >= 4 * BN) break;
-            const int c = col0 + unit_c(u), k = k0 + 8 * unit_g(u), col = c < a.Nout ? c : a.Nout - 1;
-            const float *p = W + (BWD ? (int64_t)col * a.ldw + k : (int64_t)k * a.ldw + col);
-            if (BWD && k0 + KC <= a.K) {
-                const floatx4_u x = *reinterpret_cast<const floatx4_u *>(p), y = *reinterpret_cast<const floatx4_u *>(p + 4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { rw[j][i] = x[i]; rw[j][4 + i] = y[i]; }
-            } else if (k0 + KC <= a.K) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) rw[j][i] = p[(int64_t)i * a.ldw];
-            } else if (BWD) {
-                load_k8(rw[j], p, k, a.K);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) rw[j][i] = k + i < a.K ? p[(int64_t)i * a.ldw] : 0.f;
-            }
+            const int c = col0 + (u >> 2), k = k0 + 8 * (u & 3), col = c < a.Nout ? c : a.Nout - 1;
+            load_k8(rw[j], W + (int64_t)col * a.ldw + k, k, a.K);
         }
     };
     auto stash_weights = [&](int buf) {
@@ -252,7 +419,7 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
             const int u = tid + 256 * j;
             if (4 * BN % 256 != 0 && u >= 4 * BN) break;
             const Split w = split8(rw[j]);
-            const int g = unit_g(u), c = unit_c(u);
+            const int g = u & 3, c = u >> 2;
             Bs[buf][0][g][c] = w.hi; Bs[buf][1][g][c] = w.mid; Bs[buf][2][g][c] = w.low;
         }
     };
@@ -264,53 +431,15 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
     };
-    // register r of lane (m, h): column 8 * (r / 4) + 4 * h + r % 4 of tile t
-    auto store = [&](float *O, int64_t ldo, const float *rs) {
-        if (my_row >= a.n) return;
-        const float f = rs ? sign * rs[row] : sign;
-        float *o = O + row * ldo + col0 + 4 * h;
+    uint64_t bad = 0; // lanes of this wavefront that had a sum that was not finite
+    auto store_all = [&](float *O, int64_t ldo) {
+        float seen = 0.f;
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t) seen = nonfinite(acc[t], seen);
+        bad |= __ballot(seen != 0.f);
+        if (my_row < a.n) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int c = 32 * t + 8 * q, left = a.Nout - col0 - 4 * h - c;
-                if (col0 + 32 * t + 32 <= a.Nout || left >= 4) { // the first test is the same for the whole workgroup
-                    floatx4_u v;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = acc[t][4 * q + i] * f;
-                    *reinterpret_cast<floatx4_u *>(o + c) = v;
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 3; ++i)
-                        if (i < left) o[c + i] = acc[t][4 * q + i] * f;
-                }
-            }
-    };
-    auto activate = [&]() { // end of the first forward product: bias, activation and its bits, outer bias
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            uint32_t bits = 0u;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 b1 = *reinterpret_cast<const float4 *>(&bias_s[0][32 * t + 8 * q + 4 * h]);
-                const float4 b2 = *reinterpret_cast<const float4 *>(&bias_s[1][32 * t + 8 * q + 4 * h]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float p = acc[t][4 * q + i] * sign + pick(b1, i);
-                    if (a.act == SLICEGCN_ACT_RELU) {
-                        if (p > 0.f) bits |= 1u << (8 * q + i);
-                        else p = 0.f;
-                    }
-                    acc[t][4 * q + i] = sign * (two ? p + pick(b2, i) : p);
-                }
-            }
-            if (a.act == SLICEGCN_ACT_RELU) {
-                const int left = a.Nout - col0 - 32 * t; // columns of this word
-                bits <<= 4 * h;
-                bits |= __shfl_xor(bits, 32, 64);
-                if (left < 32) bits &= left > 0 ? (1u << left) - 1u : 0u;
-                if (h == 0 && my_row < a.n && left > 0) a.mask[row * a.mask_words + ((col0 >> 5) + t)] = bits;
-            }
+            for (int t = 0; t < NT; ++t) store_tile_row(acc[t], O + row * ldo + col0 + 32 * t, h, a.Nout - col0 - 32 * t, sign);
         }
     };
 
@@ -322,16 +451,15 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
     for (int cc = 0; cc < total; ++cc) {
         const bool more = cc + 1 < total;
         if (more) fetch_weights(cc + 1);
-        const bool scale_now = in_scale && (cc >= chunks) == (scaled_product == 1);
         Split x[2];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            if (BWD && src_words) {
+            if (src_words) {
                 const uint32_t bits = word >> (16 * s + 8 * h);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) raw[s][i] = __uint_as_float(__float_as_uint(raw[s][i]) & (uint32_t)((int32_t)(bits << (31 - i)) >> 31));
             }
-            if (scale_now) {
+            if (a.scale_o1 && cc < chunks) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) raw[s][i] *= f_in;
             }
@@ -350,15 +478,40 @@ __global__ __launch_bounds__(256, 3) void pair_split_kernel(const PairArgs commo
         if (more) stash_weights((cc + 1) & 1); // the buffer of the chunk before this one, which every wavefront has left
         __syncthreads();
         if (cc == chunks - 1) { // end of the first product
-            if (!BWD) activate();
-            else {
-                store(a.O1, a.ldo1, nullptr);
-                clear();
-            }
+            store_all(a.O1, a.ldo1);
+            clear();
         }
     }
-    if (!BWD) store(a.O1, a.ldo1, a.scale_o1);
-    else if (two && a.O2) store(a.O2, a.ldo2, nullptr);
+    if (two && a.O2) store_all(a.O2, a.ldo2);
+    if (bad == 0) return;
+    // Not finite: the wavefront's tiles again, one after the other, with the fp32 instruction and operands straight from memory.
+    // (The lane number is formed anew: kept over the loop above it costs registers.)
+    const int lane_now = __lane_id();
+#pragma unroll 1
+    for (int t = 0; t < NT; ++t) {
+        const int c = col0 + 32 * t + (lane_now & 31), col = c < a.Nout ? c : a.Nout - 1;
+#pragma unroll 1
+        for (int product = 0; product <= (int)(two && a.O2); ++product) {
+            const float *in = product ? a.A2 + row * a.lda2 : a.A1 + row * a.lda1;
+            const float *W = (product ? a.B2 : a.B1) + (int64_t)col * a.ldw;
+            const float f = a.scale_o1 && product == 0 ? a.scale_o1[row] : 1.f;
+            floatx16 sum;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+#pragma unroll 1
+            for (int k0 = 0; k0 < a.K; k0 += 2) {
+                const int k = k0 + (lane_now >> 5);
+                float x = 0.f, w = 0.f;
+                if (k < a.K) {
+                    w = W[k];
+                    if (product == 1 || !src_words || ((src_words[k >> 5] >> (k & 31)) & 1u)) x = in[k] * f;
+                }
+                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(w, x, sum, 0, 0, 0);
+            }
+            if (my_row < a.n)
+                store_tile_row(sum, (product ? a.O2 + row * a.ldo2 : a.O1 + row * a.ldo1) + col0 + 32 * t, h, a.Nout - col0 - 32 * t, 1.f);
+        }
+    }
 }
 
 // Variant for the narrowest layers (K <= 32, at most 32 output columns: every layer of the workload
@@ -798,16 +951,28 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
     }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
-    const int tiles = (a.Nout + 31) / 32;
-    const int nt = tiles < 4 ? tiles : 4, n_col = (tiles + nt - 1) / nt;
+    const int tiles = (a.Nout + 31) / 32, most = !BWD && two ? 2 : 4; // 32-column tiles of a workgroup: as many as the registers hold
+    const int n_col = (tiles + most - 1) / most, nt = (tiles + n_col - 1) / n_col;
     const int64_t blocks = (row_tiles + 7) / 8 * 8 * n_col;
     SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
     const dim3 grid((unsigned)blocks, by);
-    switch (nt) {
-    case 1: pair_split_kernel<1, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    case 2: pair_split_kernel<2, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    case 3: pair_split_kernel<3, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    default: pair_split_kernel<4, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    if (BWD) {
+        switch (nt) {
+        case 1: pair_bwd_split_kernel<1><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 2: pair_bwd_split_kernel<2><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 3: pair_bwd_split_kernel<3><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        default: pair_bwd_split_kernel<4><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        }
+    } else if (two) {
+        if (nt == 1) pair_fwd_kernel<1, true><<<grid, 256, 0, stream>>>(a, b, n_col);
+        else pair_fwd_kernel<2, true><<<grid, 256, 0, stream>>>(a, b, n_col);
+    } else {
+        switch (nt) {
+        case 1: pair_fwd_kernel<1, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 2: pair_fwd_kernel<2, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 3: pair_fwd_kernel<3, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        default: pair_fwd_kernel<4, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        }
     }
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -1052,6 +1217,41 @@ __global__ __launch_bounds__(256, 2) void grad_split_kernel(const ReduceArgs com
         for (int q = 1; q < KS; ++q)
 #pragma unroll
             for (int r = 0; r < 16; ++r) total[0][0][r] += red[wave + (q - 1) * WI * WJ][64 * r + lane];
+    }
+    float seen = 0.f; // NaN if a sum of this wavefront is not finite
+#pragma unroll
+    for (int ti = 0; ti < TPI; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < TPJ; ++tj) seen = nonfinite(total[ti][tj], seen);
+    if (__ballot(seen != 0.f) != 0) { // the wavefront's tiles again with the fp32 instruction (see split8), operands straight from memory
+        for (int ti = 0; ti < TPI; ++ti)
+            for (int tj = 0; tj < TPJ; ++tj) {
+                const int ci = i_base + wi + 32 * ti + m, cj = j_base + wj + 32 * tj + m;
+                const int i = ci < a.w_in ? ci : a.w_in - 1, j = cj < a.w_out ? cj : a.w_out - 1;
+                floatx16 sum, part;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+                for (int64_t c0 = r_begin; c0 < r_end; c0 += RED_ROWS) {
+                    const int64_t c1 = c0 + RED_ROWS < r_end ? c0 + RED_ROWS : r_end;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) part[r] = 0.f;
+                    for (int64_t r0 = c0; r0 < c1; r0 += 2) {
+                        const int64_t r = r0 + h;
+                        float x = 0.f, p = 0.f;
+                        if (r < c1) {
+                            x = X[r * ldx + i] * (x_scale ? x_scale[r] : 1.f);
+                            if (!mask || ((mask[r * a.mask_words + (j >> 5)] >> (j & 31)) & 1u)) p = a.dHout[r * a.ldo + j];
+                        }
+                        part = __builtin_amdgcn_mfma_f32_32x32x2f32(x, p, part, 0, 0, 0);
+                    }
+                    sum += part;
+                }
+#pragma unroll
+                for (int ui = 0; ui < TPI; ++ui)
+#pragma unroll
+                    for (int uj = 0; uj < TPJ; ++uj)
+                        if (ui == ti && uj == tj) total[ui][uj] = sum;
+            }
     }
     if (self) out += ww;
 #pragma unroll

@@ -1,4 +1,4 @@
-"""The dense products on the bf16 matrix cores keep fp32 accuracy: outputs and gradients at the edges of the kernels'
+"""The dense products (forward on the fp32 instruction, gradients on the bf16 matrix cores) keep fp32 accuracy: outputs and gradients at the edges of the kernels'
 tiles against fp64, with a bound an fp32 sum meets, operands over eight decades, and NaN in the padding of every operand."""
 import pytest
 import torch
@@ -51,3 +51,40 @@ def test_products_match_fp64(n, w_in, w_out, pad, spread):
     assert_fp32(dX[:, :w_in], Gd @ Wd.t(), Gd.abs() @ Wd.abs().t(), "dX")
     assert_fp32(dW, Xd.t() @ Gd, Xd.abs().t() @ Gd.abs(), "dW")
     assert_fp32(db, Gd.sum(0), Gd.abs().sum(0), "db")
+
+
+@pytest.mark.parametrize("n,w_in,w_out", [(1, 33, 1), (130, 97, 95), (1025, 128, 127), (2100, 40, 257), (300_001, 72, 70)])
+def test_infinities_and_nan_come_through(n, w_in, w_out):
+    """Infinite, NaN and largest operands give what a chain of fp32 products gives: infinities stay infinities (none becomes NaN
+    on the way, which an activation would turn into zero), and a finite result stays finite."""
+    gen = torch.Generator(device="cuda").manual_seed(n + w_in + w_out)
+    inf, big = float("inf"), 3.399e38  # big: a float that no bf16 number is close to
+    X, dY = operand(gen, n, w_in, 3, False), operand(gen, n, w_out, 3, False)
+    W, b = operand(gen, w_in, w_out, 0, False).contiguous() * 0.01, torch.randn(w_out, generator=gen, device="cuda")
+    for M, values in ((X, (inf, big, -inf)), (dY, (-inf, big, inf)), (W, (inf,))):
+        for i, v in enumerate(values):
+            M[(5 + 41 * i) % M.shape[0], (3 + 11 * i) % M.shape[1]] = v
+    if n > 1:
+        X[n - 1, w_in - 1] = float("nan")
+        dY[n // 2, w_out - 1] = -big
+    mask = torch.zeros((n, (w_out + 31) // 32), dtype=torch.int32, device="cuda")
+    Y, dX, dW, db = torch.empty((n, w_out), device="cuda"), torch.empty((n, w_in), device="cuda"), torch.empty_like(W), torch.empty_like(b)
+    ws = torch.empty(B.slicegcn_linear_bwd_full_workspace_bytes(n, w_in, w_out), dtype=torch.uint8, device="cuda")
+    B.slicegcn_linear_fwd(X, W, b, Y, mask, act=B.ACT_RELU)
+    B.slicegcn_linear_bwd(X, W, mask, dY, dX, dW, db, ws, act=B.ACT_RELU)
+    on = torch.stack([(mask >> j) & 1 for j in range(32)], dim=2).reshape(n, -1)[:, :w_out].bool()
+    Xd, Wd, Gd = X.double(), W.double(), torch.where(on, dY, 0.).double()
+
+    def same(got, want, size, what):
+        # fp32 sums: the bound of assert_fp32, and where a finite sum overflows on the way it may leave the range
+        want32, sure = want.float(), size < 3.3e38
+        sure |= ~torch.isfinite(want)
+        assert bool((torch.isnan(got) == torch.isnan(want32))[sure].all()), f"{what}: NaN"
+        assert bool((got == want32)[sure & torch.isinf(want)].all()), f"{what}: infinities"
+        ok = sure & torch.isfinite(want)
+        assert bool(((got.double() - want).abs() <= 3e-6 * size)[ok].all()), what
+
+    pre = Xd @ Wd + b.double()
+    same(Y, torch.where(pre > 0, pre, 0.), Xd.abs() @ Wd.abs() + b.double().abs(), "Y")
+    same(dX, Gd @ Wd.t(), Gd.abs() @ Wd.abs().t(), "dX")
+    same(dW, Xd.t() @ Gd, Xd.abs().t() @ Gd.abs(), "dW")
