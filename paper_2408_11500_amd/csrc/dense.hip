@@ -196,8 +196,10 @@ __device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int wi
 // It stays on the fp32 instruction, and in the order of the strip kernels (chains over all of k, a step takes k and k + 4, one chain
 // per product): whether an activation passes depends on the last bit of its sum where that is near zero, and then a row's
 // gradient changes by a whole term.  Every kernel and size gives the same pattern for the same operands.
+// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 2.98 ms = 108 TFLOP/s (the kernel with rows and weights in LDS: 3.71), 169 k rows
+// 0.238 (0.288); slice layers 64 -> 64 with self term, 169 k rows: 47 us (61).
 template <int NT, bool TWO>
-__global__ __launch_bounds__(256, NT == 4 ? 2 : 3) void pair_fwd_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+__global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
 {
     const PairArgs a = slice_of(common, batch);
     constexpr int BN = NT * 32, KC = 32, GS = BN + 4; // GS: units per group of four k (padded: conflict-free writes and reads)
@@ -228,15 +230,14 @@ __global__ __launch_bounds__(256, NT == 4 ? 2 : 3) void pair_fwd_kernel(const Pa
         const bool second = TWO && cc >= chunks;
         const int c = second ? cc - chunks : cc, k0 = c * KC;
         if (c == 0) src = (second ? a.A2 + row * a.lda2 : a.A1 + row * a.lda1) + 4 * h; // first chunk of a product
+        if (k0 + KC <= a.K) {
 #pragma unroll
-        for (int q = 0; q < KC / 8; ++q) {
-            const float *p = src + k0 + 8 * q;
-            if (k0 + KC <= a.K) {
-                next[q] = *reinterpret_cast<const floatx4_u *>(p);
-            } else {
+            for (int q = 0; q < KC / 8; ++q) next[q] = *reinterpret_cast<const floatx4_u *>(src + k0 + 8 * q);
+        } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) next[q][i] = k0 + 8 * q + 4 * h + i < a.K ? p[i] : 0.f;
-            }
+            for (int q = 0; q < KC / 8; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) next[q][i] = k0 + 8 * q + 4 * h + i < a.K ? src[k0 + 8 * q + i] : 0.f;
         }
     };
     floatx4 rw[NT]; // this thread's weights of the next chunk: unit u = group u / BN of four k, column u % BN
@@ -247,8 +248,13 @@ __global__ __launch_bounds__(256, NT == 4 ? 2 : 3) void pair_fwd_kernel(const Pa
         for (int j = 0; j < NT; ++j) {
             const int u = tid + 256 * j, c = col0 + u % BN, k = k0 + 4 * (u / BN), col = c < a.Nout ? c : a.Nout - 1;
             const float *p = (second ? a.B2 : a.B1) + (int64_t)k * a.ldw + col;
+            if (k0 + KC <= a.K) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) rw[j][i] = k0 + KC <= a.K || k + i < a.K ? p[(int64_t)i * a.ldw] : 0.f;
+                for (int i = 0; i < 4; ++i) rw[j][i] = p[(int64_t)i * a.ldw];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) rw[j][i] = k + i < a.K ? p[(int64_t)i * a.ldw] : 0.f;
+            }
         }
     };
     auto stash_weights = [&](int buf) {
@@ -951,8 +957,21 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
     }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
-    const int tiles = (a.Nout + 31) / 32, most = !BWD && two ? 2 : 4; // 32-column tiles of a workgroup: as many as the registers hold
-    const int n_col = (tiles + most - 1) / most, nt = (tiles + n_col - 1) / n_col;
+    const int tiles = (a.Nout + 31) / 32; // of 32 columns
+    // Tiles of a workgroup.  Backward up to four (the rows are split once per workgroup).  Forward two: 64 columns keep three or four
+    // workgroups on a CU, where four tiles (two workgroups) take 244 us instead of 238 for 169 k rows 256 -> 256 and 158 instead of 130 for
+    // 20 k rows 512 -> 512; three for widths of three tiles, which two would pad to four; one where that would leave
+    // fewer than eight workgroups per CU (20 k rows 256 -> 256: 38 us instead of 41, 169 k rows 256 -> 40: 67 instead of 75; 169 k rows
+    // 256 -> 256, above the line: 253 instead of 238).
+    int nt;
+    if (BWD) {
+        const int n = (tiles + 3) / 4;
+        nt = (tiles + n - 1) / n;
+    } else {
+        nt = tiles % 2 != 0 && tiles % 3 == 0 ? 3 : tiles < 2 ? 1 : 2;
+        if (row_tiles * ((tiles + nt - 1) / nt) * batch < 2048) nt = 1;
+    }
+    const int n_col = (tiles + nt - 1) / nt;
     const int64_t blocks = (row_tiles + 7) / 8 * 8 * n_col;
     SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
     const dim3 grid((unsigned)blocks, by);
@@ -965,14 +984,12 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
         }
     } else if (two) {
         if (nt == 1) pair_fwd_kernel<1, true><<<grid, 256, 0, stream>>>(a, b, n_col);
-        else pair_fwd_kernel<2, true><<<grid, 256, 0, stream>>>(a, b, n_col);
+        else if (nt == 2) pair_fwd_kernel<2, true><<<grid, 256, 0, stream>>>(a, b, n_col);
+        else pair_fwd_kernel<3, true><<<grid, 256, 0, stream>>>(a, b, n_col);
     } else {
-        switch (nt) {
-        case 1: pair_fwd_kernel<1, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 2: pair_fwd_kernel<2, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 3: pair_fwd_kernel<3, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        default: pair_fwd_kernel<4, false><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        }
+        if (nt == 1) pair_fwd_kernel<1, false><<<grid, 256, 0, stream>>>(a, b, n_col);
+        else if (nt == 2) pair_fwd_kernel<2, false><<<grid, 256, 0, stream>>>(a, b, n_col);
+        else pair_fwd_kernel<3, false><<<grid, 256, 0, stream>>>(a, b, n_col);
     }
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
