@@ -1041,8 +1041,8 @@ template <class T> __device__ inline T scalar_load(const T *p) { return *(const 
 // 32 x 32 tiles they own steps of k and add up at the end in fixed order.  The next rows' loads are in flight behind the matrix
 // instructions.  Sums over RED_ROWS rows are added to a second set of accumulators, so chains stay as short as with one
 // partial per RED_ROWS rows while a workgroup can work through many of them: 2.4 M rows 256 x 256 wrote and re-read 1.2 GB of
-// partials before.  2.4 M rows 256 x 256: 3.82 -> 2.76 ms (116 TFLOP/s); 256 x 47: 1.91 -> 0.84 ms; 169 k rows, slice layers 64 x 64:
-// 65 -> 50 us per layer and product pair.  Bound by the loads and the splitting in turn with the matrix instructions (two workgroups
+// partials before.  2.4 M rows 256 x 256: 3.82 -> 2.80 ms (115 TFLOP/s); 256 x 47: 1.91 -> 0.83 ms; 169 k rows, slice layers 64 x 64:
+// 65 -> 48 us per layer and product pair.  Bound by the loads and the splitting in turn with the matrix instructions (two workgroups
 // per CU).  Column sums (bias gradients) are taken from the loaded values.
 // Grid: x = 8 row blocks x all tiles per group of workgroups (a row block's tiles meet on one XCD), y = slice, z = product.
 template <int TI, int TJ>
@@ -1811,10 +1811,21 @@ inline SplitPlan split_plan(int64_t n, int32_t w_in, int32_t w_out, int products
             const double cost = (double)ni * nj * (ti * tj * 0.094 + (ti + tj) * 3.5);
             if (p.tiles_i == 0 || cost < best) { best = cost; p.ti = ti; p.tj = tj; p.tiles_i = ni; p.tiles_j = nj; }
         }
-    // Row blocks: 1024 workgroups, four per CU (two at a time), or as many as there are steps of rows on a small graph, as
-    // far as the workspace has room (`capacity` partial sums).
+    // Row blocks.  The workgroups of a row block meet on one XCD (32 CUs), which gets every eighth block: as many blocks as fill
+    // each XCD's resident workgroups (per_cu of them on a CU, by registers and LDS) in whole rounds, one if that leaves few places
+    // empty, at most four.  1024 workgroups whatever the tile were 1.3 rounds of three per CU: 169 k rows 128 x 128 91 us, now
+    // 75; 64 x 64 pair 58, now 48; 20 k rows 256 x 256 61, now 48.  Fewer blocks on a small graph (one per step of rows), or where
+    // the workspace has no room for more (`capacity` partial sums).
     const int64_t step = p.ti == 32 || p.tj == 32 || p.ti + p.tj <= 128 ? 64 : 32;
-    int64_t blocks = 1024 / ((int64_t)p.tiles_i * p.tiles_j * products);
+    const int per_cu = p.ti + p.tj <= 96 ? 4 : p.ti + p.tj == 128 || p.ti + p.tj == 192 ? 3 : 2;
+    const int64_t tiles = (int64_t)p.tiles_i * p.tiles_j * products, places = 32 * per_cu;
+    int64_t blocks = 1;
+    double filled = 0.;
+    for (int rounds = 1; rounds <= 4; ++rounds) {
+        const int64_t per_xcd = rounds * places / tiles;
+        const double f = (double)(per_xcd * tiles) / (double)(rounds * places);
+        if (f > filled + 0.05) { filled = f; blocks = 8 * per_xcd; }
+    }
     blocks = blocks < 1 ? 1 : blocks < capacity ? blocks : capacity;
     p.rows = (int32_t)round_up((n + blocks - 1) / blocks, step);
     p.partials = (n + p.rows - 1) / p.rows;
