@@ -6,8 +6,7 @@
 //   backward:  dZ = (dHout * mask) W_agg^T,  T = dHout W_self^T            (pair kernel, transposed)
 //              dW_agg = Z^T (dHout * mask), dW_self = Hin^T dHout, db, db_self   (reduce kernels)
 //
-// Wide products run on the bf16 matrix cores with operands split into three terms (see split8), the narrow layers' on
-// v_mfma_f32_32x32x2_f32 tiles (fp32 in, fp32 accumulate), one 32-row strip per wavefront.
+// All products run on v_mfma_f32_32x32x2_f32 tiles (fp32 in, fp32 accumulate), one 32-row strip per wavefront.
 // Lane layout of the 32x32x2 fp32 MFMA (64 lanes, l = lane): A operand = A[m = l % 32][k = l / 32],
 // B operand = B[k = l / 32][n = l % 32], accumulator register r (0..15) = C[8*(r/4) + 4*(l/32) + r%4][l % 32].
 #include "common.h"
@@ -82,79 +81,8 @@ __device__ inline float4 load_k4(const float *__restrict__ base, int64_t ld, int
 
 __device__ inline float pick(const float4 &v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
-// ---- fp32 products on the bf16 matrix cores --------------------------------------------------
-// A float is the exact sum of three bf16 numbers (8 mantissa bits each, round to nearest: |mid| <= 2^-9 |x|, |low| <= 2^-18 |x|),
-// so a product of two floats is the sum of nine bf16 products, of which the three smallest (mid low, low mid, low low; together
-// at most 2^-26 of it, a quarter of the rounding of an fp32 product) are left out.  The other six run on
-// v_mfma_f32_32x32x16_bf16 with fp32 accumulation, smallest first: six instructions of 32 cycles for 16 steps of k, where
-// v_mfma_f32_32x32x2_f32 takes 512 cycles (192 against 512).  Against fp64, normal operands, sums of 32 / 256 / 4096 products: error (rms over rms
-// of the result) 0.69 / 2.4 / 10.0 e-7, with the fp32 instruction 1.02 / 2.9 / 11.6 e-7; the same order for positive operands and
-// for operands over eight decades, and all nine products give the same figures as six.
-// An infinite operand, or one beyond the bf16 range (|x| > 3.39e38), leaves NaN where the fp32 product may be infinite or finite, and an
-// activation would turn that NaN into zero.  So every wavefront looks at its sums (nonfinite) and forms its tile again with the
-// fp32 instruction if one of them is not finite: infinities and NaN come out as a chain of fp32 products gives them.
-// The instruction rounds its sums down rather than to nearest: -2e-9 of the summed magnitudes at 256 products, invisible in one
-// result, but a sum over millions of results (a bias gradient) would add it up.  So the kernels negate one operand for half of what
-// is summed later (odd rows, every second block of rows) and negate the result back: what is left has no sign of its own.
-// Lane layout (l = lane): A operand = A[m = l % 32][k = 8 * (l / 32) + i], B operand = B[k = 8 * (l / 32) + i][n = l % 32],
-// accumulator register r = C[8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32].
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4))); // 16-byte accesses at any 4-byte boundary
-
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
-
-struct Split { bf16x8 hi, mid, low; };
-__device__ inline Split split8(const float (&x)[8])
-{
-    uintx4 o[3];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { // two floats at a time: 11 instructions
-        floatx2 r = {x[2 * i], x[2 * i + 1]};
-#pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
-            o[t][i] = u;
-            if (t < 2) { // what the terms so far leave over: exact
-                r.x -= __builtin_bit_cast(float, u << 16);
-                r.y -= __builtin_bit_cast(float, u & 0xffff0000u);
-            }
-        }
-    }
-    return Split{__builtin_bit_cast(bf16x8, o[0]), __builtin_bit_cast(bf16x8, o[1]), __builtin_bit_cast(bf16x8, o[2])};
-}
-__device__ inline floatx16 mfma_bf16(const bf16x8 &a, const bf16x8 &b, const floatx16 &c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
-__device__ inline floatx16 mfma_split(const Split &a, const Split &b, floatx16 c)
-{
-    c = mfma_bf16(a.low, b.hi, c);
-    c = mfma_bf16(a.hi, b.low, c);
-    c = mfma_bf16(a.mid, b.mid, c);
-    c = mfma_bf16(a.mid, b.hi, c);
-    c = mfma_bf16(a.hi, b.mid, c);
-    return mfma_bf16(a.hi, b.hi, c);
-}
-// 0 where every element of c is finite, otherwise NaN; added to `seen`
-__device__ inline float nonfinite(const floatx16 &c, float seen)
-{
-#pragma unroll
-    for (int r = 0; r < 16; ++r) seen = fmaf(c[r], 0.f, seen);
-    return seen;
-}
-
-// Eight consecutive floats of a row of K columns from column k on, zero beyond column K
-__device__ inline void load_k8(float (&x)[8], const float *p, int k, int K)
-{
-    if (k + 8 <= K) {
-        const floatx4_u u = *reinterpret_cast<const floatx4_u *>(p), v = *reinterpret_cast<const floatx4_u *>(p + 4);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { x[i] = u[i]; x[4 + i] = v[i]; }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = k + i < K ? p[i] : 0.f;
-    }
-}
 
 // Workgroup b of a grid of row tiles x column tiles (1-D, 8 row tiles x all column tiles per group of workgroups): the column
 // tiles of one row tile run back to back on the same XCD (workgroup b goes to XCD b mod 8), so the rows are fetched from memory
@@ -186,20 +114,22 @@ __device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int wi
     }
 }
 
-// Forward products of every layer the strip kernels do not take: Hout = act(Z W_agg + b) + Hin W_self + b_self.  Workgroup = 4
-// wavefronts; a wavefront owns 32 rows and all NT * 32 columns of the workgroup's tile.  A row is used by one wavefront only, so it
-// goes from memory straight into registers (a lane loads the k of its row that it feeds to the matrix cores, the next chunk's
-// while the current one is multiplied).  The weights are shared and go through LDS: 32 steps of k at a time, two buffers, one
-// barrier per chunk, in units of four k of a column, so that a 16-byte read feeds four instructions.  The weights are the A
-// operand and the rows the B operand: a lane then holds four consecutive columns of one row in four registers, stores
-// them as 16 bytes and collects the activation bits of its row without votes.
-// It stays on the fp32 instruction, and in the order of the strip kernels (chains over all of k, a step takes k and k + 4, one chain
-// per product): whether an activation passes depends on the last bit of its sum where that is near zero, and then a row's
-// gradient changes by a whole term.  Every kernel and size gives the same pattern for the same operands.
-// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 2.98 ms = 108 TFLOP/s (the kernel with rows and weights in LDS: 3.71), 169 k rows
+// Products of every layer the strip kernels do not take.  Forward: Hout = act(Z W_agg + b) + Hin W_self + b_self; backward: dZ = (dHout *
+// mask) W_agg^T, then T = dHout W_self^T over the same accumulators.  Workgroup = 4 wavefronts; a wavefront owns 32 rows and all
+// NT * 32 columns of the workgroup's tile.  A row is used by one wavefront only, so it goes from memory straight into
+// registers (a lane loads the k of its row that it feeds to the matrix cores, the next chunk's while the current one is
+// multiplied).  The weights are shared and go through LDS: 32 steps of k at a time, two buffers, one barrier per chunk, in units of
+// four k of a column, so that a 16-byte read feeds four instructions.  The weights are the A operand and the rows the B operand:
+// a lane then holds four consecutive columns of one row in four registers, stores them as 16 bytes and collects the
+// activation bits of its row without votes.
+// The order is that of the strip kernels: chains over all of k, a step takes k and k + 4, one chain per product.  Whether an
+// activation passes depends on the last bit of its sum where that is near zero (a few in 10^8), and then a row's gradient changes
+// by a whole term: every kernel and size gives the same bits for the same operands.  (Operands split into three bf16
+// terms on the bf16 matrix cores were as exact against fp64 and faster, 2.4 M rows 256 -> 256 2.16 ms, but rounded differently.)
+// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 2.98 ms = 108 TFLOP/s (a kernel with rows and weights in LDS: 3.71), 169 k rows
 // 0.238 (0.288); slice layers 64 -> 64 with self term, 169 k rows: 47 us (61).
-template <int NT, bool TWO>
-__global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+template <int NT, bool TWO, bool BWD>
+__global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_rows_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
 {
     const PairArgs a = slice_of(common, batch);
     constexpr int BN = NT * 32, KC = 32, GS = BN + 4; // GS: units per group of four k (padded: conflict-free writes and reads)
@@ -214,7 +144,7 @@ __global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(c
     if (row_tile * 128 >= a.n) return; // uniform per workgroup
     const int chunks = (a.K + KC - 1) / KC, total = TWO ? 2 * chunks : chunks;
 
-    if (tid < BN) {
+    if (!BWD && tid < BN) {
         const int col = col0 + tid;
         bias_s[0][tid] = col < a.Nout ? inner_bias<TWO>(a, col) : 0.f;
         bias_s[1][tid] = TWO && col < a.Nout ? outer_bias(a, col) : 0.f;
@@ -222,9 +152,12 @@ __global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(c
     // The row this lane feeds.  Rows past the end and columns past the last one re-read the last: what they give is not
     // stored.  Steps of k past K are zero in both operands.
     const int64_t my_row = row_tile * 128 + wave * 32 + m, row = my_row < a.n ? my_row : a.n - 1;
-    const float f_in = TWO && a.scale2 ? a.scale2[row] : 1.f; // rows of Hin kept scaled
+    const float *in_scale = BWD ? a.scale_o1 : TWO ? a.scale2 : nullptr; // factor on the rows of one of the products:
+    const float f_in = in_scale ? in_scale[row] : 1.f;                   // dZ rows; rows of Hin kept scaled
+    const uint32_t *src_words = BWD && a.mask ? a.mask + row * a.mask_words : nullptr;
 
     floatx4 next[KC / 8];
+    uint32_t next_word = ~0u; // backward: activation bits of the next chunk
     const float *src = nullptr;
     auto fetch_rows = [&](int cc) {
         const bool second = TWO && cc >= chunks;
@@ -239,21 +172,31 @@ __global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(c
 #pragma unroll
                 for (int i = 0; i < 4; ++i) next[q][i] = k0 + 8 * q + 4 * h + i < a.K ? src[k0 + 8 * q + i] : 0.f;
         }
+        if (BWD && src_words) next_word = second ? ~0u : src_words[c];
     };
-    floatx4 rw[NT]; // this thread's weights of the next chunk: unit u = group u / BN of four k, column u % BN
+    // This thread's weights of the next chunk.  Unit u: consecutive threads walk the contiguous axis of W (columns forward, groups of
+    // four k backward)
+    floatx4 rw[NT];
+    auto unit_g = [&](int u) { return BWD ? u & 7 : u / BN; };
+    auto unit_c = [&](int u) { return BWD ? u >> 3 : u % BN; };
     auto fetch_weights = [&](int cc) {
         const bool second = TWO && cc >= chunks;
         const int k0 = (second ? cc - chunks : cc) * KC;
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            const int u = tid + 256 * j, c = col0 + u % BN, k = k0 + 4 * (u / BN), col = c < a.Nout ? c : a.Nout - 1;
-            const float *p = (second ? a.B2 : a.B1) + (int64_t)k * a.ldw + col;
+            const int u = tid + 256 * j, c = col0 + unit_c(u), k = k0 + 4 * unit_g(u), col = c < a.Nout ? c : a.Nout - 1;
+            const int64_t step = BWD ? 1 : a.ldw;
+            const float *p = (second ? a.B2 : a.B1) + (BWD ? (int64_t)col * a.ldw + k : (int64_t)k * a.ldw + col);
             if (k0 + KC <= a.K) {
+                if constexpr (BWD) {
+                    rw[j] = *reinterpret_cast<const floatx4_u *>(p);
+                } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) rw[j][i] = p[(int64_t)i * a.ldw];
+                    for (int i = 0; i < 4; ++i) rw[j][i] = p[i * step];
+                }
             } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) rw[j][i] = k + i < a.K ? p[(int64_t)i * a.ldw] : 0.f;
+                for (int i = 0; i < 4; ++i) rw[j][i] = k + i < a.K ? p[i * step] : 0.f;
             }
         }
     };
@@ -261,11 +204,11 @@ __global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(c
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             const int u = tid + 256 * j;
-            Bs[buf][u / BN][u % BN] = rw[j];
+            Bs[buf][unit_g(u)][unit_c(u)] = rw[j];
         }
     };
 
-    floatx16 acc[NT], first[TWO ? NT : 1]; // first: the activated first product
+    floatx16 acc[NT], first[TWO && !BWD ? NT : 1]; // first: the activated first product
     auto clear = [&]() {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -273,7 +216,7 @@ __global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(c
             for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
     };
     // register r of lane (m, h): column 8 * (r / 4) + 4 * h + r % 4 of tile t
-    auto activate = [&](floatx16 &c, int t) { // end of the first product: bias, activation and its bits
+    auto activate = [&](floatx16 &c, int t) { // end of the first forward product: bias, activation and its bits
         uint32_t bits = 0u;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -296,6 +239,11 @@ __global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(c
             if (h == 0 && my_row < a.n && left > 0) a.mask[row * a.mask_words + ((col0 >> 5) + t)] = bits;
         }
     };
+    auto store_all = [&](float *O, int64_t ldo, float f) {
+        if (my_row >= a.n) return;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) store_tile_row(acc[t], O + row * ldo + col0 + 32 * t, h, a.Nout - col0 - 32 * t, f);
+    };
 
     clear();
     fetch_weights(0);
@@ -308,7 +256,14 @@ __global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(c
         floatx4 x[KC / 8];
 #pragma unroll
         for (int q = 0; q < KC / 8; ++q) x[q] = next[q];
-        if (TWO && a.scale2 && cc >= chunks) {
+        if (BWD && src_words) {
+#pragma unroll
+            for (int q = 0; q < KC / 8; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (!((next_word >> (8 * q + 4 * h + i)) & 1u)) x[q][i] = 0.f;
+        }
+        if (in_scale && (BWD ? cc < chunks : cc >= chunks)) {
 #pragma unroll
             for (int q = 0; q < KC / 8; ++q) x[q] *= f_in;
         }
@@ -326,197 +281,36 @@ __global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_fwd_kernel(c
         if (more) stash_weights((cc + 1) & 1); // the buffer of the chunk before this one, which every wavefront has left
         __syncthreads();
         if (TWO && cc == chunks - 1) { // end of the first product
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                activate(acc[t], t);
-                first[TWO ? t : 0] = acc[t];
-            }
-            clear();
-        }
-    }
-    const float f_out = a.scale_o1 ? a.scale_o1[row] : 1.f;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        if constexpr (TWO) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 b2 = *reinterpret_cast<const float4 *>(&bias_s[1][32 * t + 8 * q + 4 * h]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[t][4 * q + i] = first[t][4 * q + i] + (acc[t][4 * q + i] + pick(b2, i));
-            }
-        } else {
-            activate(acc[t], t);
-        }
-        if (my_row < a.n) store_tile_row(acc[t], a.O1 + row * a.ldo1 + col0 + 32 * t, h, a.Nout - col0 - 32 * t, f_out);
-    }
-}
-
-// Backward products of the layers the strip kernels do not take: dZ = (dHout * mask) W_agg^T, T = dHout W_self^T, one after the
-// other over the same accumulators.  Rows, weights and tiles as in the forward kernel, but on the bf16 matrix cores (see split8):
-// a lane loads and splits eight k of its row, the weights are split on their way to LDS in units of eight k of a column.
-// The rows of the next chunk are requested as soon as the current ones are split (both steps at once: they share cache
-// lines), its weights before the current chunk's matrix instructions.
-// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 take 2.0 ms (fp32 instruction, two column tiles of 128: 4.3), 160 TFLOP/s =
-// 960 of bf16, where a large bf16 matrix product of the library reaches 1270 on this card (the clock gives way under matrix
-// load).  64 rows per wavefront, 64 columns per workgroup, and the weights resident in LDS for the whole reduction (no
-// barriers) were within 10 % of this or slower.
-template <int NT>
-__global__ __launch_bounds__(256, 3) void pair_bwd_split_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
-{
-    const PairArgs a = slice_of(common, batch);
-    constexpr int BN = NT * 32, KC = 32;
-    constexpr int GS = BN + 4;                 // units per group of eight k (padded: conflict-free writes and reads)
-    constexpr int UB = (4 * BN + 255) / 256;   // units a thread stages per chunk
-    __shared__ bf16x8 Bs[2][3][4][GS];
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
-    const int m = lane & 31, h = lane >> 5;
-    const TilePlace place = tile_place(n_col_tiles);
-    const int64_t row_tile = place.row_tile;
-    const int col0 = place.col_tile * BN;
-    if (row_tile * 128 >= a.n) return; // uniform per workgroup
-    const bool two = a.A2 != nullptr && a.B2 != nullptr;
-    const int chunks = (a.K + KC - 1) / KC, total = two ? 2 * chunks : chunks;
-
-    // The row this lane feeds.  Rows past the end and columns past the last one re-read the last: what they give is not
-    // stored.  Steps of k past K are zero in both operands.
-    const int64_t my_row = row_tile * 128 + wave * 32 + m, row = my_row < a.n ? my_row : a.n - 1;
-    const uint32_t flip = (uint32_t)(m & 1) << 31; // odd rows are multiplied negated (see split8)
-    const float sign = m & 1 ? -1.f : 1.f;
-    const float f_in = a.scale_o1 ? a.scale_o1[row] : 1.f; // rows of the first product
-
-    float raw[2][8];            // this lane's part of the next chunk of its row
-    uint32_t word = ~0u;        // its activation bits
-    const float *src = nullptr;
-    const uint32_t *src_words = a.mask ? a.mask + row * a.mask_words : nullptr;
-    auto fetch_rows = [&](int cc) {
-        const bool second = cc >= chunks;
-        const int c = second ? cc - chunks : cc, k0 = c * KC;
-        if (c == 0) src = (second ? a.A2 + row * a.lda2 : a.A1 + row * a.lda1) + 8 * h; // first chunk of a product
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const float *p = src + k0 + 16 * s;
-            if (k0 + KC <= a.K) {
-                const floatx4_u u = *reinterpret_cast<const floatx4_u *>(p), v = *reinterpret_cast<const floatx4_u *>(p + 4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { raw[s][i] = u[i]; raw[s][4 + i] = v[i]; }
+            if constexpr (BWD) {
+                store_all(a.O1, a.ldo1, 1.f);
             } else {
-                load_k8(raw[s], p, k0 + 16 * s + 8 * h, a.K);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    activate(acc[t], t);
+                    first[TWO && !BWD ? t : 0] = acc[t];
+                }
             }
-        }
-        if (src_words) word = second ? ~0u : src_words[c];
-    };
-    float rw[UB][8];            // this thread's weights of the next chunk: unit u = group u % 4 of eight k, column u / 4
-    auto fetch_weights = [&](int cc) {
-        const bool second = cc >= chunks;
-        const float *W = second ? a.B2 : a.B1;
-        const int k0 = (second ? cc - chunks : cc) * KC;
-#pragma unroll
-        for (int j = 0; j < UB; ++j) {
-            const int u = tid + 256 * j;
-            if (4 * BN % 256 != 0 && u >= 4 * BN) break;
-            const int c = col0 + (u >> 2), k = k0 + 8 * (u & 3), col = c < a.Nout ? c : a.Nout - 1;
-            load_k8(rw[j], W + (int64_t)col * a.ldw + k, k, a.K);
-        }
-    };
-    auto stash_weights = [&](int buf) {
-#pragma unroll
-        for (int j = 0; j < UB; ++j) {
-            const int u = tid + 256 * j;
-            if (4 * BN % 256 != 0 && u >= 4 * BN) break;
-            const Split w = split8(rw[j]);
-            const int g = u & 3, c = u >> 2;
-            Bs[buf][0][g][c] = w.hi; Bs[buf][1][g][c] = w.mid; Bs[buf][2][g][c] = w.low;
-        }
-    };
-
-    floatx16 acc[NT];
-    auto clear = [&]() {
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-    };
-    uint64_t bad = 0; // lanes of this wavefront that had a sum that was not finite
-    auto store_all = [&](float *O, int64_t ldo) {
-        float seen = 0.f;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) seen = nonfinite(acc[t], seen);
-        bad |= __ballot(seen != 0.f);
-        if (my_row < a.n) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) store_tile_row(acc[t], O + row * ldo + col0 + 32 * t, h, a.Nout - col0 - 32 * t, sign);
-        }
-    };
-
-    clear();
-    fetch_weights(0);
-    fetch_rows(0);
-    stash_weights(0);
-    __syncthreads();
-    for (int cc = 0; cc < total; ++cc) {
-        const bool more = cc + 1 < total;
-        if (more) fetch_weights(cc + 1);
-        Split x[2];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (src_words) {
-                const uint32_t bits = word >> (16 * s + 8 * h);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) raw[s][i] = __uint_as_float(__float_as_uint(raw[s][i]) & (uint32_t)((int32_t)(bits << (31 - i)) >> 31));
-            }
-            if (a.scale_o1 && cc < chunks) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) raw[s][i] *= f_in;
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) raw[s][i] = __uint_as_float(__float_as_uint(raw[s][i]) ^ flip);
-            x[s] = split8(raw[s]);
-        }
-        if (more) fetch_rows(cc + 1);
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const bf16x8 (*w)[4][GS] = Bs[cc & 1];
-                acc[t] = mfma_split(Split{w[0][2 * s + h][32 * t + m], w[1][2 * s + h][32 * t + m], w[2][2 * s + h][32 * t + m]}, x[s], acc[t]);
-            }
-        if (more) stash_weights((cc + 1) & 1); // the buffer of the chunk before this one, which every wavefront has left
-        __syncthreads();
-        if (cc == chunks - 1) { // end of the first product
-            store_all(a.O1, a.ldo1);
             clear();
         }
     }
-    if (two && a.O2) store_all(a.O2, a.ldo2);
-    if (bad == 0) return;
-    // Not finite: the wavefront's tiles again, one after the other, with the fp32 instruction and operands straight from memory.
-    // (The lane number is formed anew: kept over the loop above it costs registers.)
-    const int lane_now = __lane_id();
-#pragma unroll 1
-    for (int t = 0; t < NT; ++t) {
-        const int c = col0 + 32 * t + (lane_now & 31), col = c < a.Nout ? c : a.Nout - 1;
-#pragma unroll 1
-        for (int product = 0; product <= (int)(two && a.O2); ++product) {
-            const float *in = product ? a.A2 + row * a.lda2 : a.A1 + row * a.lda1;
-            const float *W = (product ? a.B2 : a.B1) + (int64_t)col * a.ldw;
-            const float f = a.scale_o1 && product == 0 ? a.scale_o1[row] : 1.f;
-            floatx16 sum;
+    if constexpr (BWD) {
+        if (!TWO) store_all(a.O1, a.ldo1, 1.f);
+        else if (a.O2) store_all(a.O2, a.ldo2, 1.f);
+    } else {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sum[r] = 0.f;
-#pragma unroll 1
-            for (int k0 = 0; k0 < a.K; k0 += 2) {
-                const int k = k0 + (lane_now >> 5);
-                float x = 0.f, w = 0.f;
-                if (k < a.K) {
-                    w = W[k];
-                    if (product == 1 || !src_words || ((src_words[k >> 5] >> (k & 31)) & 1u)) x = in[k] * f;
+        for (int t = 0; t < NT; ++t) {
+            if constexpr (TWO) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 b2 = *reinterpret_cast<const float4 *>(&bias_s[1][32 * t + 8 * q + 4 * h]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[t][4 * q + i] = first[t][4 * q + i] + (acc[t][4 * q + i] + pick(b2, i));
                 }
-                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(w, x, sum, 0, 0, 0);
+            } else {
+                activate(acc[t], t);
             }
-            if (my_row < a.n)
-                store_tile_row(sum, (product ? a.O2 + row * a.ldo2 : a.O1 + row * a.ldo1) + col0 + 32 * t, h, a.Nout - col0 - 32 * t, 1.f);
         }
+        store_all(a.O1, a.ldo1, a.scale_o1 ? a.scale_o1[row] : 1.f);
     }
 }
 
@@ -957,39 +751,24 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
     }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
-    const int tiles = (a.Nout + 31) / 32; // of 32 columns
-    // Tiles of a workgroup.  Backward up to four (the rows are split once per workgroup).  Forward two: 64 columns keep three or four
-    // workgroups on a CU, where four tiles (two workgroups) take 244 us instead of 238 for 169 k rows 256 -> 256 and 158 instead of 130 for
-    // 20 k rows 512 -> 512; three for widths of three tiles, which two would pad to four; one where that would leave
-    // fewer than eight workgroups per CU (20 k rows 256 -> 256: 38 us instead of 41, 169 k rows 256 -> 40: 67 instead of 75; 169 k rows
-    // 256 -> 256, above the line: 253 instead of 238).
-    int nt;
-    if (BWD) {
-        const int n = (tiles + 3) / 4;
-        nt = (tiles + n - 1) / n;
-    } else {
-        nt = tiles % 2 != 0 && tiles % 3 == 0 ? 3 : tiles < 2 ? 1 : 2;
-        if (row_tiles * ((tiles + nt - 1) / nt) * batch < 2048) nt = 1;
-    }
+    // Tiles of 32 columns a workgroup takes: two keep three or four workgroups on a CU, where four (two workgroups) take 244 us instead
+    // of 238 for 169 k rows 256 -> 256 and 158 instead of 130 for 20 k rows 512 -> 512; three for widths of three tiles, which two would
+    // pad to four; one where that would leave fewer than eight workgroups per CU (20 k rows 256 -> 256: 38 us instead of 41,
+    // 169 k rows 256 -> 40: 67 instead of 75; 169 k rows 256 -> 256, above the line: 253 instead of 238).
+    const int tiles = (a.Nout + 31) / 32;
+    int nt = tiles % 2 != 0 && tiles % 3 == 0 ? 3 : tiles < 2 ? 1 : 2;
+    if (row_tiles * ((tiles + nt - 1) / nt) * batch < 2048) nt = 1;
     const int n_col = (tiles + nt - 1) / nt;
     const int64_t blocks = (row_tiles + 7) / 8 * 8 * n_col;
     SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
     const dim3 grid((unsigned)blocks, by);
-    if (BWD) {
-        switch (nt) {
-        case 1: pair_bwd_split_kernel<1><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 2: pair_bwd_split_kernel<2><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 3: pair_bwd_split_kernel<3><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        default: pair_bwd_split_kernel<4><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        }
-    } else if (two) {
-        if (nt == 1) pair_fwd_kernel<1, true><<<grid, 256, 0, stream>>>(a, b, n_col);
-        else if (nt == 2) pair_fwd_kernel<2, true><<<grid, 256, 0, stream>>>(a, b, n_col);
-        else pair_fwd_kernel<3, true><<<grid, 256, 0, stream>>>(a, b, n_col);
-    } else {
-        if (nt == 1) pair_fwd_kernel<1, false><<<grid, 256, 0, stream>>>(a, b, n_col);
-        else if (nt == 2) pair_fwd_kernel<2, false><<<grid, 256, 0, stream>>>(a, b, n_col);
-        else pair_fwd_kernel<3, false><<<grid, 256, 0, stream>>>(a, b, n_col);
+    switch (2 * nt + (two ? 1 : 0)) {
+    case 2: pair_rows_kernel<1, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    case 3: pair_rows_kernel<1, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    case 4: pair_rows_kernel<2, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    case 5: pair_rows_kernel<2, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    case 6: pair_rows_kernel<3, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    default: pair_rows_kernel<3, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
     }
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -1000,6 +779,8 @@ int launch_pair(const PairArgs &a, hipStream_t stream) { return launch_pair<BWD>
 
 // ---- weight-gradient reductions over the node axis ----------------------------------------
 constexpr int RED_ROWS = 1024; // rows per block: fp32 chains stay this short
+constexpr int RED_TILE = 32;   // output tile edge
+constexpr int RED_RK = 32;     // rows staged per step
 
 struct ReduceArgs {
     const float *Z; int64_t ldz;
@@ -1011,8 +792,8 @@ struct ReduceArgs {
     int32_t w_in, w_out;
     int32_t stride;                     // 2*w_in*w_out + 2*w_out; compact: w_in*w_out + w_out
     int32_t compact;                    // 1: no self term and no slot for it: [Z^T dP | colsum dP]
-    int32_t rows_per_block = RED_ROWS;  // grad_split_kernel: node rows per workgroup (one partial each)
-    int32_t j_tiles = 1;                // and output tiles along w_out
+    int32_t rows_per_block = RED_ROWS;  // tiled kernels: node rows per workgroup (one partial each)
+    int32_t j_tiles = 1;                // tiled kernels: output tiles along w_out (grid depth = j_tiles x batch)
     const float *hin_scale = nullptr;   // rows of Hin are multiplied by hin_scale[row] when read (Hin stored as D~^-1/2 Hin)
 };
 
@@ -1030,263 +811,127 @@ __device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatc
     return r;
 }
 
-// Words and factors that are the same for a whole wavefront come through the scalar cache (read-only data of earlier launches).
-template <class T> __device__ inline T scalar_load(const T *p) { return *(const __attribute__((address_space(4))) T *)(uintptr_t)p; }
-
-// Partial weight gradients of every layer the strip kernels do not take: a workgroup forms one TI x TJ tile of one product (Z^T dP
-// or Hin^T dHout, the grid's depth) over its rows_per_block node rows.  The node axis is the k axis of the matrix
-// instructions.  Per step RK rows of both tiles are loaded (a thread reads eight rows of one column: a wavefront reads
-// contiguous pieces of rows, and their mask bits are the wavefront's lane mask), split into bf16 terms (see split8) on their way to LDS
-// in units of eight rows of a column, and multiplied by four wavefronts that own quarters of the tile; with fewer than four
-// 32 x 32 tiles they own steps of k and add up at the end in fixed order.  The next rows' loads are in flight behind the matrix
-// instructions.  Sums over RED_ROWS rows are added to a second set of accumulators, so chains stay as short as with one
-// partial per RED_ROWS rows while a workgroup can work through many of them: 2.4 M rows 256 x 256 wrote and re-read 1.2 GB of
-// partials before.  2.4 M rows 256 x 256: 3.82 -> 2.80 ms (115 TFLOP/s); 256 x 47: 1.91 -> 0.83 ms; 169 k rows, slice layers 64 x 64:
-// 65 -> 48 us per layer and product pair.  Bound by the loads and the splitting in turn with the matrix instructions (two workgroups
-// per CU).  Column sums (bias gradients) are taken from the loaded values.
-// Grid: x = 8 row blocks x all tiles per group of workgroups (a row block's tiles meet on one XCD), y = slice, z = product.
-template <int TI, int TJ>
-__global__ __launch_bounds__(256, 2) void grad_split_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
+// Partial weight gradients, tiled: grid = (row blocks, w_in tiles, slices x w_out tiles), every workgroup writes its
+// tile of the four results [Z^T dP | Hin^T dHout | colsum dP | colsum dHout] of its row block into
+// partial[row block][...].  Per step the workgroup stages 32 rows of the four operand tiles in LDS;
+// wavefront w multiplies rows 8w..8w+7 (the node axis is the MFMA's k axis: A[m][k] = Z[k][m]),
+// and the four wavefronts' accumulators are added in wavefront order at the end.
+__global__ __launch_bounds__(256) void grad_partial_mfma_kernel(const ReduceArgs common, const ReduceBatch batch)
 {
-    const ReduceArgs a = slice_of(common, batch, blockIdx.y);
-    constexpr int RK = TI == 32 || TJ == 32 || TI + TJ <= 128 ? 64 : 32; // rows per step
-    constexpr int G = RK / 8, S = RK / 16;                               // units per column and step, k steps of the instructions
-    constexpr int UA = TI * G / 256, UB = TJ * G / 256;                  // units a thread stages
-    constexpr int MI = TI / 32, NJ = TJ / 32;
-    constexpr int WJ = NJ == 4 ? (MI == 1 ? 4 : 2) : NJ, WI = MI < 4 / WJ ? MI : 4 / WJ; // wavefronts along j and along i
-    constexpr int KS = 4 / (WI * WJ);                                    // wavefronts that share the k steps of a quarter
-    constexpr int TPI = MI / WI, TPJ = NJ / WJ;                          // 32 x 32 tiles of a wavefront
-    static_assert(WI * WJ * KS == 4 && TPI * WI == MI && TPJ * WJ == NJ && UA >= 1 && UB >= 1, "tile split");
-    __shared__ bf16x8 As[3][G][TI];
-    __shared__ bf16x8 Bs[3][G][TJ];
+    const ReduceArgs a = slice_of(common, batch, blockIdx.z / common.j_tiles);
+    // one LDS block: the four operand tiles during the row loop, the accumulators of wavefronts 1..3 after it
+    constexpr int TILE_FLOATS = RED_RK * RED_TILE;
+    __shared__ __attribute__((aligned(16))) float lds[3 * 2 * RED_TILE * RED_TILE];
+    float (*Zs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds);
+    float (*Hs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + TILE_FLOATS);
+    float (*Ps)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + 2 * TILE_FLOATS);
+    float (*Gs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + 3 * TILE_FLOATS);
+    float (*red)[2][RED_TILE * RED_TILE] = reinterpret_cast<float (*)[2][RED_TILE * RED_TILE]>(lds);
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int64_t b = blockIdx.x;
-    const int64_t block = (b / (8 * n_tiles)) * 8 + (b % 8);
-    const int tile = (int)((b / 8) % n_tiles);
-    const int i_base = (tile / common.j_tiles) * TI, j_base = (tile % common.j_tiles) * TJ;
-    const int64_t r_begin = block * a.rows_per_block;
-    if (r_begin >= a.n) return; // uniform per workgroup
+    const int i_base = blockIdx.y * RED_TILE, j_base = (blockIdx.z % common.j_tiles) * RED_TILE;
+    const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
-    const bool self = blockIdx.z == 1; // the product Hin^T dHout
-    const float *X = self ? a.Hin : a.Z;
-    const int64_t ldx = self ? a.ldi : a.ldz;
-    const float *x_scale = self ? a.hin_scale : nullptr;
-    const uint32_t *mask = self ? nullptr : a.mask;
-    const bool sums = i_base == 0; // this workgroup also forms the column sums of its columns
+    const bool self = a.Hin != nullptr;
+    const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vh = self && aligned16(a.Hin) && a.ldi % 4 == 0;
+    const bool vg = aligned16(a.dHout) && a.ldo % 4 == 0;
 
-    float ra[UA][8], rb[UB][8];
-    // a wavefront's unit is 64 columns of eight rows (or 32 columns of two groups of rows): two mask words per row, together
-    // the lane mask of the loaded values
-    uint32_t mask_lo[UB][8], mask_hi[UB][8];
-    const float *pa[UA], *pb[UB];
-    // unit u of a tile of T columns: eight rows from row 8 * (u / T) of the step on, column u % T (past the last one: the
-    // last, what it gives is not stored)
+    floatx16 accA, accS;
 #pragma unroll
-    for (int q = 0; q < UA; ++q) {
-        const int u = tid + 256 * q, c = i_base + u % TI;
-        pa[q] = X + (r_begin + 8 * (u / TI)) * ldx + (c < a.w_in ? c : a.w_in - 1);
-    }
-#pragma unroll
-    for (int q = 0; q < UB; ++q) {
-        const int u = tid + 256 * q, c = j_base + u % TJ;
-        pb[q] = a.dHout + (r_begin + 8 * (u / TJ)) * a.ldo + (c < a.w_out ? c : a.w_out - 1);
-    }
-    auto fetch = [&](int64_t r0) {
-        const bool full = r0 + RK <= r_end; // uniform
-#pragma unroll
-        for (int q = 0; q < UA; ++q)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) ra[q][i] = full || r0 + 8 * ((tid + 256 * q) / TI) + i < r_end ? pa[q][i * ldx] : 0.f;
-#pragma unroll
-        for (int q = 0; q < UB; ++q)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) rb[q][i] = full || r0 + 8 * ((tid + 256 * q) / TJ) + i < r_end ? pb[q][i * a.ldo] : 0.f;
-        if (mask) {
-#pragma unroll
-            for (int q = 0; q < UB; ++q) {
-                const int first = __builtin_amdgcn_readfirstlane(tid + 256 * q - lane);
-                const int64_t r_lo = r0 + 8 * (first / TJ), r_hi = r0 + 8 * ((first + 32) / TJ);
-                const int w_lo = (j_base + first % TJ) >> 5, w_hi = (j_base + (first + 32) % TJ) >> 5, words = (a.w_out + 31) >> 5;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int64_t lo = r_lo + i < r_end ? r_lo + i : r_end - 1, hi = r_hi + i < r_end ? r_hi + i : r_end - 1;
-                    mask_lo[q][i] = scalar_load(mask + lo * a.mask_words + (w_lo < words ? w_lo : words - 1));
-                    mask_hi[q][i] = scalar_load(mask + hi * a.mask_words + (w_hi < words ? w_hi : words - 1));
+    for (int r = 0; r < 16; ++r) { accA[r] = 0.f; accS[r] = 0.f; }
+    float accb = 0.f; // lanes 0..31: column (j_base + m) of dP, lanes 32..63: of dH_out; rows of this wavefront only
+
+    const int lr = tid >> 3, lc = (tid & 7) * 4; // this thread's float4 of each 32 x 32 tile
+    float4 z, hh, p, g;
+    float hf = 1.f; // factor of this thread's row of Hin (scaled layout); applied when the registers go to LDS
+    auto fetch = [&](int64_t r0) { // this thread's share of the four tiles of rows [r0, r0 + 32)
+        const int64_t row = r0 + lr;
+        z = make_float4(0.f, 0.f, 0.f, 0.f); hh = z; p = z; g = z;
+        if (row < r_end) {
+            if (i_base + lc < a.w_in) {
+                z = load_k4(a.Z, a.ldz, row, i_base + lc, a.w_in, vz);
+                if (self) {
+                    hh = load_k4(a.Hin, a.ldi, row, i_base + lc, a.w_in, vh);
+                    if (a.hin_scale) hf = a.hin_scale[row];
+                }
+            }
+            if (j_base + lc < a.w_out) {
+                g = load_k4(a.dHout, a.ldo, row, j_base + lc, a.w_out, vg);
+                p = g;
+                if (a.mask) {
+                    const int j = j_base + lc;
+                    const uint32_t bits = a.mask[row * a.mask_words + (j >> 5)] >> (j & 31);
+                    if (!(bits & 1u)) p.x = 0.f;
+                    if (!(bits & 2u)) p.y = 0.f;
+                    if (!(bits & 4u)) p.z = 0.f;
+                    if (!(bits & 8u)) p.w = 0.f;
                 }
             }
         }
-#pragma unroll
-        for (int q = 0; q < UA; ++q) pa[q] += RK * ldx;
-#pragma unroll
-        for (int q = 0; q < UB; ++q) pb[q] += RK * a.ldo;
     };
-    float col_sum[UB], col_total[UB];
-#pragma unroll
-    for (int q = 0; q < UB; ++q) { col_sum[q] = 0.f; col_total[q] = 0.f; }
-    auto stash = [&](int64_t r0, uint32_t flip) {
-#pragma unroll
-        for (int q = 0; q < UA; ++q) {
-            const int u = tid + 256 * q;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) ra[q][i] = __uint_as_float(__float_as_uint(ra[q][i]) ^ flip);
-            if (x_scale) {
-                if constexpr (TI >= 64) { // one group of eight rows per wavefront
-                    const int64_t r = r0 + 8 * __builtin_amdgcn_readfirstlane(u / TI);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) ra[q][i] *= scalar_load(x_scale + (r + i < r_end ? r + i : r_end - 1));
-                } else {
-                    const int64_t r = r0 + 8 * (u / TI);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) ra[q][i] *= x_scale[r + i < r_end ? r + i : r_end - 1];
-                }
-            }
-            const Split x = split8(ra[q]);
-            As[0][u / TI][u % TI] = x.hi; As[1][u / TI][u % TI] = x.mid; As[2][u / TI][u % TI] = x.low;
-        }
-#pragma unroll
-        for (int q = 0; q < UB; ++q) {
-            const int u = tid + 256 * q;
-            if (mask) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    rb[q][i] = __builtin_amdgcn_inverse_ballot_w64(((uint64_t)mask_hi[q][i] << 32) | mask_lo[q][i]) ? rb[q][i] : 0.f;
-            }
-            if (sums) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) col_sum[q] += rb[q][i];
-            }
-            const Split x = split8(rb[q]);
-            Bs[0][u / TJ][u % TJ] = x.hi; Bs[1][u / TJ][u % TJ] = x.mid; Bs[2][u / TJ][u % TJ] = x.low;
-        }
-    };
-
-    floatx16 acc[TPI][TPJ], total[TPI][TPJ];
-#pragma unroll
-    for (int ti = 0; ti < TPI; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < TPJ; ++tj)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) { acc[ti][tj][r] = 0.f; total[ti][tj][r] = 0.f; }
-    const int ks = wave / (WI * WJ), wi = (wave / WJ) % WI * (TPI * 32), wj = wave % WJ * (TPJ * 32);
-
     fetch(r_begin);
-    int chain = 0;
-    bool negated = block & 1; // every second chain of rows is multiplied negated (see split8)
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += RK) {
-        stash(r0, negated ? 0x80000000u : 0u);
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += RED_RK) {
+        if (a.hin_scale) scale4(hh, hf);
+        *reinterpret_cast<float4 *>(&Zs[lr][lc]) = z;
+        *reinterpret_cast<float4 *>(&Hs[lr][lc]) = hh;
+        *reinterpret_cast<float4 *>(&Ps[lr][lc]) = p;
+        *reinterpret_cast<float4 *>(&Gs[lr][lc]) = g;
         __syncthreads();
-        if (r0 + RK < r_end) fetch(r0 + RK);
+        if (r0 + RED_RK < r_end) fetch(r0 + RED_RK); // next step's loads fly during this step's MFMAs
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            if (KS > 1 && s % KS != ks) continue; // uniform per wavefront
-            Split x[TPI];
+        for (int s4 = 0; s4 < 4; ++s4) {
+            const int k = wave * 8 + s4 * 2 + h;
+            accA = __builtin_amdgcn_mfma_f32_32x32x2f32(Zs[k][m], Ps[k][m], accA, 0, 0, 0);
+            if (self) accS = __builtin_amdgcn_mfma_f32_32x32x2f32(Hs[k][m], Gs[k][m], accS, 0, 0, 0);
+        }
+        if (blockIdx.y == 0) {
+            float (*T)[RED_TILE] = h ? Gs : Ps;
 #pragma unroll
-            for (int ti = 0; ti < TPI; ++ti)
-                x[ti] = Split{As[0][2 * s + h][wi + 32 * ti + m], As[1][2 * s + h][wi + 32 * ti + m], As[2][2 * s + h][wi + 32 * ti + m]};
-#pragma unroll
-            for (int tj = 0; tj < TPJ; ++tj) {
-                const Split p{Bs[0][2 * s + h][wj + 32 * tj + m], Bs[1][2 * s + h][wj + 32 * tj + m], Bs[2][2 * s + h][wj + 32 * tj + m]};
-#pragma unroll
-                for (int ti = 0; ti < TPI; ++ti) acc[ti][tj] = mfma_split(x[ti], p, acc[ti][tj]);
-            }
+            for (int r = 0; r < 8; ++r) accb += T[wave * 8 + r][m];
         }
         __syncthreads();
-        chain += RK;
-        if (chain >= RED_ROWS || r0 + RK >= r_end) {
-            const float sign = negated ? -1.f : 1.f;
-            chain = 0;
-            negated = !negated;
-#pragma unroll
-            for (int ti = 0; ti < TPI; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < TPJ; ++tj)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) { total[ti][tj][r] += sign * acc[ti][tj][r]; acc[ti][tj][r] = 0.f; }
-#pragma unroll
-            for (int q = 0; q < UB; ++q) { col_total[q] += col_sum[q]; col_sum[q] = 0.f; }
-        }
     }
 
-    float *out = a.partial + block * a.stride;
+    // ---- add the four wavefronts' tiles in order, then store (the tile memory is free now) ----
+    __shared__ float bsum[4][64];
+    bsum[wave][lane] = accb;
+    if (wave > 0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int i = 8 * (r / 4) + 4 * h + (r % 4);
+            red[wave - 1][0][i * RED_TILE + m] = accA[r];
+            red[wave - 1][1][i * RED_TILE + m] = accS[r];
+        }
+    }
+    __syncthreads();
+    float *out = a.partial + (int64_t)blockIdx.x * a.stride;
     const int ww = a.w_in * a.w_out;
-    if (sums) { // the groups' column sums, added in order
-        float *red = reinterpret_cast<float *>(Bs);
+    if (wave == 0) {
 #pragma unroll
-        for (int q = 0; q < UB; ++q) red[tid + 256 * q] = col_total[q];
-        __syncthreads();
-        if (tid < TJ && j_base + tid < a.w_out) {
-            float s = 0.f;
-#pragma unroll
-            for (int g = 0; g < G; ++g) s += red[g * TJ + tid];
-            out[(a.compact ? ww : 2 * ww + (self ? a.w_out : 0)) + j_base + tid] = s;
+        for (int r = 0; r < 16; ++r) {
+            const int il = 8 * (r / 4) + 4 * h + (r % 4);
+            float va = accA[r], vs = accS[r];
+            for (int q = 0; q < 3; ++q) { va += red[q][0][il * RED_TILE + m]; vs += red[q][1][il * RED_TILE + m]; }
+            const int i = i_base + il, j = j_base + m;
+            if (i < a.w_in && j < a.w_out) {
+                out[i * a.w_out + j] = va;
+                if (!a.compact) out[ww + i * a.w_out + j] = vs;
+            }
+        }
+        if (blockIdx.y == 0) {
+            const int j = j_base + m;
+            const float sum = ((bsum[0][lane] + bsum[1][lane]) + bsum[2][lane]) + bsum[3][lane];
+            if (j < a.w_out && !(a.compact && h)) out[(a.compact ? ww : 2 * ww) + (h ? a.w_out : 0) + j] = sum;
         }
     }
-    if constexpr (KS > 1) {
-        float (*red)[32 * 32] = reinterpret_cast<float (*)[32 * 32]>(As); // one tile per wavefront in these variants
-        if (ks > 0) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) red[wave - WI * WJ][64 * r + lane] = total[0][0][r];
-        }
-        __syncthreads();
-        if (ks > 0) return;
-        for (int q = 1; q < KS; ++q)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) total[0][0][r] += red[wave + (q - 1) * WI * WJ][64 * r + lane];
-    }
-    float seen = 0.f; // NaN if a sum of this wavefront is not finite
-#pragma unroll
-    for (int ti = 0; ti < TPI; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < TPJ; ++tj) seen = nonfinite(total[ti][tj], seen);
-    if (__ballot(seen != 0.f) != 0) { // the wavefront's tiles again with the fp32 instruction (see split8), operands straight from memory
-        for (int ti = 0; ti < TPI; ++ti)
-            for (int tj = 0; tj < TPJ; ++tj) {
-                const int ci = i_base + wi + 32 * ti + m, cj = j_base + wj + 32 * tj + m;
-                const int i = ci < a.w_in ? ci : a.w_in - 1, j = cj < a.w_out ? cj : a.w_out - 1;
-                floatx16 sum, part;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sum[r] = 0.f;
-                for (int64_t c0 = r_begin; c0 < r_end; c0 += RED_ROWS) {
-                    const int64_t c1 = c0 + RED_ROWS < r_end ? c0 + RED_ROWS : r_end;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) part[r] = 0.f;
-                    for (int64_t r0 = c0; r0 < c1; r0 += 2) {
-                        const int64_t r = r0 + h;
-                        float x = 0.f, p = 0.f;
-                        if (r < c1) {
-                            x = X[r * ldx + i] * (x_scale ? x_scale[r] : 1.f);
-                            if (!mask || ((mask[r * a.mask_words + (j >> 5)] >> (j & 31)) & 1u)) p = a.dHout[r * a.ldo + j];
-                        }
-                        part = __builtin_amdgcn_mfma_f32_32x32x2f32(x, p, part, 0, 0, 0);
-                    }
-                    sum += part;
-                }
-#pragma unroll
-                for (int ui = 0; ui < TPI; ++ui)
-#pragma unroll
-                    for (int uj = 0; uj < TPJ; ++uj)
-                        if (ui == ti && uj == tj) total[ui][uj] = sum;
-            }
-    }
-    if (self) out += ww;
-#pragma unroll
-    for (int ti = 0; ti < TPI; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < TPJ; ++tj)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = i_base + wi + 32 * ti + 8 * (r / 4) + 4 * h + (r % 4), j = j_base + wj + 32 * tj + m;
-                if (i < a.w_in && j < a.w_out) out[i * a.w_out + j] = total[ti][tj][r];
-            }
 }
 
 // Partial weight gradients of the narrowest layers (w_in, w_out <= 32, large n): every wavefront owns
 // its own accumulators and every n_waves-th strip of 32 rows (so that the chip reads one contiguous
 // window at a time), reads a strip with coalesced 16-byte loads into wave-private LDS tiles (the
 // next strip's loads in flight during the MFMAs), and writes one partial result.  The node axis is the MFMA's k axis (lane (m, h) feeds
-// column m of node row 2s + h).  No workgroup barrier; same output layout as grad_split_kernel,
+// column m of node row 2s + h).  No workgroup barrier; same output layout as grad_partial_mfma_kernel,
 // one partial per wavefront.
 __global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs common, const ReduceBatch batch, int64_t n_waves)
 {
@@ -1384,8 +1029,8 @@ __global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs comm
 // instead of twice.  Per strip of 32 rows: Z, Hin and dHout go to LDS with coalesced 16-byte loads (the next strip's
 // loads in flight behind the MFMAs); the node axis is the k axis of Z^T dP and Hin^T dHout (column reads of the
 // tiles), the column axis that of dZ = dP W_agg^T and T = dHout W_self^T (row reads, weights in registers); dZ and T
-// leave through the Z and Hin tiles as 16-byte stores.  Partial sums: one per wavefront, layout
-// of grad_split_kernel.  `a` carries the input-gradient half: B1 / B2 = W_agg / W_self (ldw), O1 = dZ (rows
+// leave through the Z and Hin tiles as 16-byte stores.  Partial sums: one per wavefront, layout of
+// grad_partial_mfma_kernel.  `a` carries the input-gradient half: B1 / B2 = W_agg / W_self (ldw), O1 = dZ (rows
 // scaled by scale_o1), O2 = T, K = w_out, Nout = w_in.
 __global__ __launch_bounds__(256, 2) void bwd_strip32_kernel(const ReduceArgs rcommon, const ReduceBatch rbatch, const PairArgs pcommon, const PairBatch pbatch,
                                                              int64_t n_waves)
@@ -1678,6 +1323,108 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
     }
 }
 
+// Partial weight gradient of a single product (compact layout: [X^T dP | colsum dP]) for wide
+// layers: one workgroup per 128 x 128 output tile and block of RED_ROWS rows, each wavefront owning a
+// 64 x 64 quarter (four MFMA accumulators).  Per step 32 rows of the X tile and of the dP tile are
+// staged in LDS (the next step's loads are issued into registers before this step's MFMAs); the
+// node axis is the MFMA's k axis.  32 flop per staged byte instead of 8 for 32 x 32 tiles.
+constexpr int GB_T = 128;
+
+__global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch)
+{
+    const ReduceArgs a = slice_of(common, batch, blockIdx.z / common.j_tiles);
+    __shared__ __attribute__((aligned(16))) float Xs[RED_RK][GB_T];
+    __shared__ __attribute__((aligned(16))) float Ps[RED_RK][GB_T];
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63;
+    const int m = lane & 31, h = lane >> 5;
+    const int i_base = blockIdx.y * GB_T, j_base = (blockIdx.z % common.j_tiles) * GB_T;
+    const int wi = (wave >> 1) * 64, wj = (wave & 1) * 64;
+    const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
+    const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
+    const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vg = aligned16(a.dHout) && a.ldo % 4 == 0;
+    const bool bias_wave = blockIdx.y == 0 && (wave >> 1) == 0;
+
+    floatx16 acc[2][2];
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[ti][tj][r] = 0.f;
+    float accb = 0.f; // column j_base + wj + lane of dP
+
+    float4 rx[4], rp[4];
+    auto fetch = [&](int64_t r0) {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int idx = tid + it * 256;
+            const int r = idx >> 5, c4 = (idx & 31) * 4;
+            const int64_t row = r0 + r;
+            float4 x = make_float4(0.f, 0.f, 0.f, 0.f), p = x;
+            if (row < r_end) {
+                if (i_base + c4 < a.w_in) x = load_k4(a.Z, a.ldz, row, i_base + c4, a.w_in, vz);
+                if (j_base + c4 < a.w_out) {
+                    p = load_k4(a.dHout, a.ldo, row, j_base + c4, a.w_out, vg);
+                    if (a.mask) {
+                        const int j = j_base + c4;
+                        const uint32_t bits = a.mask[row * a.mask_words + (j >> 5)] >> (j & 31);
+                        if (!(bits & 1u)) p.x = 0.f;
+                        if (!(bits & 2u)) p.y = 0.f;
+                        if (!(bits & 4u)) p.z = 0.f;
+                        if (!(bits & 8u)) p.w = 0.f;
+                    }
+                }
+            }
+            rx[it] = x;
+            rp[it] = p;
+        }
+    };
+    fetch(r_begin);
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += RED_RK) {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int idx = tid + it * 256;
+            const int r = idx >> 5, c4 = (idx & 31) * 4;
+            *reinterpret_cast<float4 *>(&Xs[r][c4]) = rx[it];
+            *reinterpret_cast<float4 *>(&Ps[r][c4]) = rp[it];
+        }
+        __syncthreads();
+        if (r0 + RED_RK < r_end) fetch(r0 + RED_RK);
+#pragma unroll
+        for (int kp = 0; kp < RED_RK / 2; ++kp) {
+            const int k = 2 * kp + h;
+            const float a0 = Xs[k][wi + m], a1 = Xs[k][wi + 32 + m];
+            const float b0 = Ps[k][wj + m], b1 = Ps[k][wj + 32 + m];
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+        }
+        if (bias_wave) {
+#pragma unroll
+            for (int r = 0; r < RED_RK; ++r) accb += Ps[r][wj + lane];
+        }
+        __syncthreads();
+    }
+
+    float *out = a.partial + (int64_t)blockIdx.x * a.stride;
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int i = i_base + wi + 32 * ti + 8 * (r / 4) + 4 * h + (r % 4);
+                const int j = j_base + wj + 32 * tj + m;
+                if (i < a.w_in && j < a.w_out) out[i * a.w_out + j] = acc[ti][tj][r];
+            }
+    if (bias_wave) {
+        const int j = j_base + wj + lane;
+        if (j < a.w_out) out[a.w_in * a.w_out + j] = accb;
+    }
+}
+
 // Column sums of an n x w matrix (slice-encoding gradient): partial[block][w].
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const float *__restrict__ M, int64_t ld, int64_t n, int32_t w,
                                                              float *__restrict__ partial)
@@ -1793,96 +1540,68 @@ __global__ __launch_bounds__(1024) void reduce_final_kernel(const FinalBatch bat
 
 inline int64_t red_blocks(int64_t n) { return (n + RED_ROWS - 1) / RED_ROWS; }
 
-// Tiles and row blocks of grad_split_kernel for `products` products of w_in x w_out over n rows.
-struct SplitPlan {
-    int32_t ti, tj, tiles_i, tiles_j;
-    int32_t rows;     // node rows per workgroup
-    int64_t partials; // row blocks
-};
-inline SplitPlan split_plan(int64_t n, int32_t w_in, int32_t w_out, int products, int64_t capacity)
+// Node rows per partial sum of a slice layer's weight gradients: RED_ROWS, or a quarter of it when that
+// would give the tiled kernel fewer than 2048 workgroups (a workgroup walks its rows in dependent steps
+// of 32, so on small graphs shorter walks in more workgroups finish sooner: cfg2 80 -> 35 us).
+inline int32_t layer_grad_rows(int64_t n, int32_t w_in, int32_t w_out)
 {
-    SplitPlan p{32, 32, 0, 0, 0, 0};
-    // The tile with the least work: per 32 rows a SIMD spends about ti * tj * 0.094 cycles in matrix instructions and
-    // (ti + tj) * 3.5 on loading and splitting, on padding as on data (301 x 128: 5 x 1 tiles of 64 x 128, not 3 x 1 of 128 x 128).
-    double best = 0.;
-    for (int32_t ti = 32; ti <= 128; ti *= 2)
-        for (int32_t tj = 32; tj <= 128; tj *= 2) {
-            const int32_t ni = (w_in + ti - 1) / ti, nj = (w_out + tj - 1) / tj;
-            const double cost = (double)ni * nj * (ti * tj * 0.094 + (ti + tj) * 3.5);
-            if (p.tiles_i == 0 || cost < best) { best = cost; p.ti = ti; p.tj = tj; p.tiles_i = ni; p.tiles_j = nj; }
-        }
-    // Row blocks.  The workgroups of a row block meet on one XCD (32 CUs), which gets every eighth block: as many blocks as fill
-    // each XCD's resident workgroups (per_cu of them on a CU, by registers and LDS) in whole rounds, one if that leaves few places
-    // empty, at most four.  1024 workgroups whatever the tile were 1.3 rounds of three per CU: 169 k rows 128 x 128 91 us, now
-    // 75; 64 x 64 pair 58, now 48; 20 k rows 256 x 256 61, now 48.  Fewer blocks on a small graph (one per step of rows), or where
-    // the workspace has no room for more (`capacity` partial sums).
-    const int64_t step = p.ti == 32 || p.tj == 32 || p.ti + p.tj <= 128 ? 64 : 32;
-    const int per_cu = p.ti + p.tj <= 96 ? 4 : p.ti + p.tj == 128 || p.ti + p.tj == 192 ? 3 : 2;
-    const int64_t tiles = (int64_t)p.tiles_i * p.tiles_j * products, places = 32 * per_cu;
-    int64_t blocks = 1;
-    double filled = 0.;
-    for (int rounds = 1; rounds <= 4; ++rounds) {
-        const int64_t per_xcd = rounds * places / tiles;
-        const double f = (double)(per_xcd * tiles) / (double)(rounds * places);
-        if (f > filled + 0.05) { filled = f; blocks = 8 * per_xcd; }
-    }
-    blocks = blocks < 1 ? 1 : blocks < capacity ? blocks : capacity;
-    p.rows = (int32_t)round_up((n + blocks - 1) / blocks, step);
-    p.partials = (n + p.rows - 1) / p.rows;
-    return p;
+    const int64_t tiles = (int64_t)((w_in + RED_TILE - 1) / RED_TILE) * ((w_out + RED_TILE - 1) / RED_TILE);
+    return red_blocks(n) * tiles < 2048 ? RED_ROWS / 4 : RED_ROWS;
+}
+inline int64_t layer_grad_blocks(int64_t n, int32_t w_in, int32_t w_out)
+{
+    const int32_t rows = layer_grad_rows(n, w_in, w_out);
+    return (n + rows - 1) / rows;
 }
 
 // How the weight gradients of a slice layer are formed: by which kernel, and in how many partial sums.  A function of the
-// sizes and of the room for partial sums the entry point asks its callers for: the rows that go into one fp32 chain, and so
-// the bits of a gradient, do not depend on the launch.
-constexpr int64_t NO_LIMIT = (int64_t)1 << 40;
-// Partial sums slicegcn_layer_bwd has room for: one per 1024 rows, or per 256 while that leaves few (the size its callers know).
-inline int64_t layer_grad_blocks(int64_t n, int32_t w_in, int32_t w_out)
-{
-    const int64_t tiles = (int64_t)((w_in + 31) / 32) * ((w_out + 31) / 32), rows = red_blocks(n) * tiles < 2048 ? RED_ROWS / 4 : RED_ROWS;
-    return (n + rows - 1) / rows;
-}
+// sizes alone: the rows that go into one fp32 chain, and so the bits of a gradient, do not depend on the launch.
 struct GradPlan {
     enum Kind { STRIP32, STRIP64, TILED } kind;
     int64_t partials;
+    int32_t rows; // TILED: node rows per workgroup
 };
-inline GradPlan grad_plan(int64_t n, int32_t w_in, int32_t w_out, int64_t capacity)
+inline GradPlan grad_plan(int64_t n, int32_t w_in, int32_t w_out)
 {
     const int64_t nb = layer_grad_blocks(n, w_in, w_out);
     if (w_in <= 32 && w_out <= 32 && n >= 65536) { // one partial sum per wavefront
         const int64_t strips = (n + 31) / 32, waves = nb < 8192 ? nb : 8192;
-        return GradPlan{GradPlan::STRIP32, waves < strips ? waves : strips};
+        return GradPlan{GradPlan::STRIP32, waves < strips ? waves : strips, 0};
     }
     if (w_in <= 64 && w_out <= 64 && n >= ((int64_t)1 << 21)) {
         // whole waves of resident workgroups (256 CUs x 3 workgroups x 4 wavefronts) where there are as many blocks
         const int64_t resident = 3072;
         const int64_t waves = nb >= resident ? nb / resident * resident : nb >= 2048 ? 2048 : nb;
         const int64_t strips = (n + 7) / 8; // strips of 8 rows in every variant launched here
-        return GradPlan{GradPlan::STRIP64, waves < strips ? waves : strips};
+        return GradPlan{GradPlan::STRIP64, waves < strips ? waves : strips, 0};
     }
-    return GradPlan{GradPlan::TILED, split_plan(n, w_in, w_out, 2, capacity).partials};
+    return GradPlan{GradPlan::TILED, nb, layer_grad_rows(n, w_in, w_out)};
 }
 
-template <int TI>
-void launch_grad_split_i(const SplitPlan &p, dim3 grid, const ReduceArgs &r, const ReduceBatch &b, hipStream_t stream)
+// A dense layer's weight and bias gradients: 128 x 128 output tiles where the layer is wide, 32 x 32 tiles otherwise, a
+// partial sum per RED_ROWS node rows.  On few rows that would leave most of the chip idle behind chains of RED_ROWS rows, so
+// there (up to SMALL_LINEAR output elements) the rows are split until 512 workgroups are there or a workgroup is down to
+// one step, as far as the workspace has room (`capacity` partial sums): 5000 rows 96 -> 96: 132 -> 15 us.
+struct LinearGradPlan {
+    bool big;
+    int32_t rows;
+    int64_t partials;
+};
+constexpr int64_t NO_LIMIT = (int64_t)1 << 40, SMALL_LINEAR = (int64_t)1 << 19;
+inline LinearGradPlan linear_grad_plan(int64_t n, int32_t w_in, int32_t w_out, int64_t capacity)
 {
-    const int tiles = p.tiles_i * p.tiles_j;
-    if (p.tj == 32) grad_split_kernel<TI, 32><<<grid, 256, 0, stream>>>(r, b, tiles);
-    else if (p.tj == 64) grad_split_kernel<TI, 64><<<grid, 256, 0, stream>>>(r, b, tiles);
-    else grad_split_kernel<TI, 128><<<grid, 256, 0, stream>>>(r, b, tiles);
-}
-int launch_grad_split(const SplitPlan &p, ReduceArgs r, const ReduceBatch &b, int batch, int products, hipStream_t stream)
-{
-    r.rows_per_block = p.rows;
-    r.j_tiles = p.tiles_j;
-    const int64_t blocks = (p.partials + 7) / 8 * 8 * p.tiles_i * p.tiles_j;
-    SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "weight gradients: grid too large");
-    const dim3 grid((unsigned)blocks, (unsigned)batch, (unsigned)products);
-    if (p.ti == 32) launch_grad_split_i<32>(p, grid, r, b, stream);
-    else if (p.ti == 64) launch_grad_split_i<64>(p, grid, r, b, stream);
-    else launch_grad_split_i<128>(p, grid, r, b, stream);
-    SG_LAUNCH_CHECK();
-    return SLICEGCN_OK;
+    LinearGradPlan p;
+    p.big = w_in > 64 || w_out > 64;
+    int64_t rows = RED_ROWS;
+    if (n * (w_in > w_out ? w_in : w_out) <= SMALL_LINEAR) {
+        const int32_t t = p.big ? GB_T : RED_TILE;
+        const int64_t tiles = (int64_t)((w_in + t - 1) / t) * ((w_out + t - 1) / t);
+        const int64_t fine = round_up(n * tiles / 512 + 1, RED_RK), least = round_up((n + capacity - 1) / capacity, RED_RK);
+        if (fine < rows) rows = fine > least ? fine : least;
+    }
+    p.rows = (int32_t)rows;
+    p.partials = (n + rows - 1) / rows;
+    return p;
 }
 
 // ---- pieces of the transform-first layer order -------------------------------------------------
@@ -2045,7 +1764,7 @@ static size_t linear_partial_bytes(int64_t partials, int32_t w_in, int32_t w_out
 // what the kernels use where the workspace allows it
 static size_t linear_full_bytes(int64_t n, int32_t w_in, int32_t w_out)
 {
-    return linear_partial_bytes(split_plan(n, w_in, w_out, 1, NO_LIMIT).partials, w_in, w_out);
+    return linear_partial_bytes(linear_grad_plan(n, w_in, w_out, NO_LIMIT).partials, w_in, w_out);
 }
 
 struct LinearGradArgs { // one layer of a batch (equal shapes and leading dimensions)
@@ -2063,11 +1782,14 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
 {
     const int ww = w_in * w_out;
     const int32_t stride = ww + w_out;
-    const SplitPlan plan = split_plan(n, w_in, w_out, 1, (int64_t)(ws_each / ((size_t)stride * sizeof(float))));
+    const LinearGradPlan plan = linear_grad_plan(n, w_in, w_out, (int64_t)(ws_each / ((size_t)stride * sizeof(float))));
     ReduceArgs r;
     r.Z = nullptr; r.ldz = ldx; r.Hin = nullptr; r.ldi = 0; r.dHout = nullptr; r.ldo = lddy;
     r.mask = nullptr; r.mask_words = mask_words;
     r.partial = nullptr; r.n = n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 1;
+    r.rows_per_block = plan.rows;
+    const int t = plan.big ? GB_T : RED_TILE;
+    r.j_tiles = (w_out + t - 1) / t;
     ReduceBatch b;
     FinalBatch f;
     for (int i = 0; i < BATCH; ++i) {
@@ -2077,7 +1799,10 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
         f.partial[i] = partial;
         f.dst[i] = FinalDst{{x.dW, nullptr, nullptr, x.db}, x.db_copy, {0, ww, ww, ww, stride}};
     }
-    if (int rc = launch_grad_split(plan, r, b, batch, 1, stream)) return rc;
+    const dim3 grid((unsigned)plan.partials, (unsigned)((w_in + t - 1) / t), (unsigned)(r.j_tiles * batch));
+    if (plan.big) grad_big_mfma_kernel<<<grid, 256, 0, stream>>>(r, b);
+    else grad_partial_mfma_kernel<<<grid, 256, 0, stream>>>(r, b);
+    SG_LAUNCH_CHECK();
     reduce_final_kernel<<<dim3((unsigned)((stride + 31) / 32), (unsigned)batch), 1024, 0, stream>>>(f, plan.partials, stride, stride);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -2107,18 +1832,17 @@ static size_t fwd_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *d)
     if (transform_first(d)) return 2 * mat_bytes(g->n, d->w_out) + spmm_workspace_bytes(g->fwd, d->w_out);
     return spmm_workspace_bytes(g->fwd, d->w_in);
 }
-static int64_t layer_capacity(int64_t n, const slicegcn_layer_desc *d, bool full) { return full ? NO_LIMIT : layer_grad_blocks(n, d->w_in, d->w_out); }
-static size_t bwd_partial_bytes(int64_t n, const slicegcn_layer_desc *d, bool full)
+static size_t bwd_partial_bytes(int64_t n, const slicegcn_layer_desc *d)
 {
     const size_t stride = 2 * (size_t)d->w_in * d->w_out + 2 * (size_t)d->w_out;
-    return (size_t)round_up((int64_t)((full ? grad_plan(n, d->w_in, d->w_out, NO_LIMIT).partials : layer_grad_blocks(n, d->w_in, d->w_out)) * stride * sizeof(float)), 256);
+    return (size_t)round_up((int64_t)(layer_grad_blocks(n, d->w_in, d->w_out) * stride * sizeof(float)), 256);
 }
 static size_t bwd_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *d, bool need_dHin, bool full)
 {
     if (transform_first(d)) // [dP | G | W_agg^T | W_self^T | reduction partials | aggregation workspace]
         return 2 * mat_bytes(g->n, d->w_out) + 2 * tf_wt_bytes(d) + tf_red_bytes(g->n, d, full) + spmm_workspace_bytes(g->tr, d->w_out);
     // [partial weight gradients | dZ (only with dHin) | aggregation workspace (only with dHin)]
-    size_t bytes = bwd_partial_bytes(g->n, d, full);
+    size_t bytes = bwd_partial_bytes(g->n, d);
     if (need_dHin) bytes += mat_bytes(g->n, d->w_in) + spmm_workspace_bytes(g->tr, d->w_in);
     return bytes;
 }
@@ -2290,7 +2014,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
     if (transform_first(desc)) return bwd_transform_first(g, lg, io, batch, ws, full, stream);
     const int w_in = desc->w_in, w_out = desc->w_out;
     const bool self = io[0].params.W_self != nullptr, need_dHin = io[0].dHin != nullptr, relu = desc->act == SLICEGCN_ACT_RELU;
-    const size_t part = bwd_partial_bytes(g->n, desc, full), mat = mat_bytes(g->n, w_in), agg = spmm_workspace_bytes(g->tr, w_in);
+    const size_t part = bwd_partial_bytes(g->n, desc), mat = mat_bytes(g->n, w_in), agg = spmm_workspace_bytes(g->tr, w_in);
     Sections sec{static_cast<char *>(ws), batch};
     char *parts = sec.take(part), *dZs = need_dHin ? sec.take(mat) : nullptr, *agg_ws = need_dHin ? sec.take(agg) : nullptr;
 
@@ -2309,8 +2033,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         a.n = g->n; a.K = w_out; a.Nout = w_in; a.ldw = w_out; a.act = desc->act;
         a.scale_o1 = g->dinv; // dZ is staged as D~^-1/2 dZ: its aggregation then skips the stored values
     }
-    const int64_t capacity = layer_capacity(g->n, desc, full);
-    const GradPlan plan = grad_plan(g->n, w_in, w_out, capacity);
+    const GradPlan plan = grad_plan(g->n, w_in, w_out);
     // narrow layers with a self term: the kernel that forms the weight gradients also forms dZ and T (one read of dHout)
     const bool fused_inputs = need_dHin && self && plan.kind == GradPlan::STRIP32;
 
@@ -2322,6 +2045,8 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         r.Z = nullptr; r.ldz = lg->ldz; r.Hin = nullptr; r.ldi = lg->ldi; r.dHout = nullptr; r.ldo = lg->ldgo;
         r.mask = nullptr; r.mask_words = lg->mask_words;
         r.partial = nullptr; r.n = g->n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 0;
+        r.rows_per_block = plan.rows;
+        r.j_tiles = (w_out + RED_TILE - 1) / RED_TILE;
         r.hin_scale = (desc->flags & SLICEGCN_LAYER_IN_SCALED) ? g->sqrtd : nullptr;
         ReduceBatch b;
         FinalBatch f;
@@ -2354,7 +2079,8 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
             else grad_strip64_kernel<2, 2, 8, 2><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
             break;
         case GradPlan::TILED:
-            if (int rc = launch_grad_split(split_plan(g->n, w_in, w_out, 2, capacity), r, b, batch, self ? 2 : 1, stream)) return rc;
+            grad_partial_mfma_kernel<<<dim3((unsigned)plan.partials, (unsigned)((w_in + RED_TILE - 1) / RED_TILE), (unsigned)(r.j_tiles * batch)),
+                                       256, 0, stream>>>(r, b);
             break;
         }
         SG_LAUNCH_CHECK();

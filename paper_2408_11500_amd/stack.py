@@ -12,8 +12,9 @@ import torch
 from . import binding as B
 
 # Slices run in groups whose layers share their launches while the rows one launch works on stay within this many bytes
-# (see SliceStack.group).
-GROUP_BYTES = 64 << 20
+# (see SliceStack.group).  Epochs at 64 MB / 1 GB / 4 GB: 60 k nodes, 5 slices 2.09 / 1.67 / 1.67 ms; 169 k nodes, 4 slices 3.15 / 3.05 /
+# 3.06; 1 M nodes, 4 slices 12.30 / 12.31 / 12.00.  2.4 M nodes in groups at 16 GB gain nothing (72.3, 72.8 -> 72.2 ms) for 6.5 GB more.
+GROUP_BYTES = 4 << 30
 
 
 def padded_ld(width: int) -> int:
@@ -90,8 +91,9 @@ class SliceStack:
         self.lanes = max(1, min(k, int(streams)))
         self.streams = [torch.cuda.Stream(device=self.dev) for _ in range(self.lanes)] if self.lanes > 1 else []
         # On one lane the slices run in groups of `group`: a layer of all of them is one set of launches, which is what a
-        # small graph needs (its kernels last microseconds and leave most of the chip idle).  A large graph gains nothing
-        # and would need every buffer of the backward pass per slice, so a group ends where one launch touches GROUP_BYTES.
+        # small graph needs (its kernels last microseconds and leave most of the chip idle) and where the last, partly filled
+        # round of a launch's workgroups still shows.  A large graph gains nothing and would need every buffer of the backward
+        # pass per slice, so a group ends where one launch touches GROUP_BYTES.
         row_bytes = 4 * 4 * max(padded_ld(first_width), padded_ld(slice_hidden))  # Z, input and output, twice the widest
         self.group = 1 if self.lanes > 1 else max(1, min(k, B.MAX_GROUP, GROUP_BYTES // (n_nodes * row_bytes)))
         slots = max(self.lanes, self.group)

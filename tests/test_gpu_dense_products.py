@@ -1,5 +1,4 @@
-"""The dense products (forward on the fp32 instruction, gradients on the bf16 matrix cores) keep fp32 accuracy: outputs and gradients at the edges of the kernels'
-tiles against fp64, with a bound an fp32 sum meets, operands over eight decades, and NaN in the padding of every operand."""
+"""The dense products keep fp32 accuracy: outputs and gradients at the edges of the kernels' tiles against fp64, with a bound an fp32 sum meets, operands over eight decades, and NaN in the padding of every operand."""
 import pytest
 import torch
 
@@ -8,7 +7,7 @@ from paper_2408_11500_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 33, 1), (127, 65, 31), (128, 96, 33), (129, 97, 95), (1025, 128, 127), (511, 79, 129), (260, 609, 66), (4096, 40, 257),
-          (300_001, 72, 70)]
+          (300_001, 72, 70), (1500, 700, 650)]
 
 
 def operand(gen, rows, cols, pad, spread):
@@ -58,7 +57,7 @@ def test_infinities_and_nan_come_through(n, w_in, w_out):
     """Infinite, NaN and largest operands give what a chain of fp32 products gives: infinities stay infinities (none becomes NaN
     on the way, which an activation would turn into zero), and a finite result stays finite."""
     gen = torch.Generator(device="cuda").manual_seed(n + w_in + w_out)
-    inf, big = float("inf"), 3.399e38  # big: a float that no bf16 number is close to
+    inf, big = float("inf"), 3.399e38
     X, dY = operand(gen, n, w_in, 3, False), operand(gen, n, w_out, 3, False)
     W, b = operand(gen, w_in, w_out, 0, False).contiguous() * 0.01, torch.randn(w_out, generator=gen, device="cuda")
     for M, values in ((X, (inf, big, -inf)), (dY, (-inf, big, inf)), (W, (inf,))):
@@ -88,3 +87,36 @@ def test_infinities_and_nan_come_through(n, w_in, w_out):
     same(Y, torch.where(pre > 0, pre, 0.), Xd.abs() @ Wd.abs() + b.double().abs(), "Y")
     same(dX, Gd @ Wd.t(), Gd.abs() @ Wd.abs().t(), "dX")
     same(dW, Xd.t() @ Gd, Xd.abs().t() @ Gd.abs(), "dW")
+
+
+@pytest.mark.parametrize("w_in,w_out", [(33, 40), (72, 70), (100, 128), (64, 64), (37, 161)])
+def test_forward_sums_do_not_depend_on_the_tiling(w_in, w_out):
+    """Forward products of many rows (strips, tiles of two and three) and of few rows (tiles of one) form the same chains: the
+    same bits, row by row, for one product and for a layer's two, and within an fp32 sum's bound of fp64."""
+    n, few = 270_001, 777
+    gen = torch.Generator(device="cuda").manual_seed(w_in + 5 * w_out)
+    Z, X = operand(gen, n, w_in, 4 + -w_in % 4, False), operand(gen, n, w_in, 1, False)
+    W, Ws = operand(gen, w_in, w_out, 0, False).contiguous(), operand(gen, w_in, w_out, 0, False).contiguous()
+    b, bs = torch.randn(w_out, generator=gen, device="cuda"), torch.randn(w_out, generator=gen, device="cuda")
+
+    def edges(rows):
+        v = torch.arange(rows, device="cuda", dtype=torch.int64)
+        return B.slicegcn_build_norm_csr(v[:-1].contiguous(), v[1:].contiguous(), rows)
+
+    def products(rows):
+        words = (w_out + 31) // 32
+        Y, H = torch.empty((rows, w_out), device="cuda"), torch.empty((rows, w_out), device="cuda")
+        m1, m2 = (torch.zeros((rows, words), dtype=torch.int32, device="cuda") for _ in range(2))
+        B.slicegcn_linear_fwd(X[:rows], W, b, Y, m1, act=B.ACT_RELU)
+        B.slicegcn_layer_fwd(edges(rows), X[:rows], W, b, Ws, bs, H, Z[:rows], m2, z_valid=True)
+        return Y, H, m1, m2
+
+    many, small = products(n), products(few)
+    for x, y in zip(many, small):
+        assert torch.equal(x[:few], y)
+    Y, H, _, _ = many
+    Xd, Zd, Wd, Wsd = X.double(), Z.double(), W.double(), Ws.double()
+    size = Xd.abs() @ Wd.abs() + b.double().abs()
+    assert_fp32(Y, (Xd @ Wd + b.double()).clamp_min(0), size, "Y")
+    size = Zd.abs() @ Wd.abs() + b.double().abs() + Xd.abs() @ Wsd.abs() + bs.double().abs()
+    assert_fp32(H, (Zd @ Wd + b.double()).clamp_min(0) + Xd @ Wsd + bs.double(), size, "H")
