@@ -811,118 +811,180 @@ __device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatc
     return r;
 }
 
-// Partial weight gradients, tiled: grid = (row blocks, w_in tiles, slices x w_out tiles), every workgroup writes its
-// tile of the four results [Z^T dP | Hin^T dHout | colsum dP | colsum dHout] of its row block into
-// partial[row block][...].  Per step the workgroup stages 32 rows of the four operand tiles in LDS;
-// wavefront w multiplies rows 8w..8w+7 (the node axis is the MFMA's k axis: A[m][k] = Z[k][m]),
-// and the four wavefronts' accumulators are added in wavefront order at the end.
-__global__ __launch_bounds__(256) void grad_partial_mfma_kernel(const ReduceArgs common, const ReduceBatch batch)
+// Partial weight gradients of the layers the strip kernels do not take (but see grad_big_mfma_kernel): a workgroup forms a tile of one
+// product (Z^T dP or Hin^T dHout, the grid's depth) over rows_per_block node rows.  The node axis is the matrix instruction's k axis, so an operand register
+// is 32 consecutive columns of two rows: they come straight from memory, several pairs of rows ahead, with no LDS and no
+// barrier in the row loop.  Two forms, which differ in the order of the sums and so are not chosen by speed:
+//   WJ = 0  wavefront w takes rows 8 w to 8 w + 7 of every 32 for the whole tile of MI x NJ times 32 x 32; the four sums are added in
+//           order at the end (slice layers, and dense layers up to 64 wide)
+//   WJ > 0  the four wavefronts own tiles of their own, WJ of them along w_out, over all rows (wider dense layers)
+// Column sums (bias gradients) run in row order over the loaded values.
+// A kernel that staged 32 x 32 tiles in LDS re-read its operands per tile and waited at two barriers per 32 rows.  Pairs of products:
+// 233 k rows 301 x 128 823 -> 591 us (61 TFLOP/s), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
+// 256 x 47 1.93 -> 1.40 ms, 60 k rows 64 x 64 46 -> 22 us.  Bound by the loads, one register of two rows' pieces at a time.
+// Grid: x = 8 row blocks x all tiles per group of workgroups (a row block's tiles meet on one XCD), y = slice, z = product.
+template <int MI, int NJ, int WJ>
+__global__ __launch_bounds__(256, 3) void grad_rows_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
 {
-    const ReduceArgs a = slice_of(common, batch, blockIdx.z / common.j_tiles);
-    // one LDS block: the four operand tiles during the row loop, the accumulators of wavefronts 1..3 after it
-    constexpr int TILE_FLOATS = RED_RK * RED_TILE;
-    __shared__ __attribute__((aligned(16))) float lds[3 * 2 * RED_TILE * RED_TILE];
-    float (*Zs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds);
-    float (*Hs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + TILE_FLOATS);
-    float (*Ps)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + 2 * TILE_FLOATS);
-    float (*Gs)[RED_TILE] = reinterpret_cast<float (*)[RED_TILE]>(lds + 3 * TILE_FLOATS);
-    float (*red)[2][RED_TILE * RED_TILE] = reinterpret_cast<float (*)[2][RED_TILE * RED_TILE]>(lds);
+    const ReduceArgs a = slice_of(common, batch, blockIdx.y);
+    constexpr bool SPLIT = WJ == 0;
+    constexpr int WI = SPLIT ? 1 : 4 / (SPLIT ? 1 : WJ);
+    constexpr int PAIRS = MI * NJ == 1 ? 8 : 4; // pairs of rows a wavefront loads at a time
+    constexpr int ROWS = (SPLIT ? 8 : 2) * PAIRS;                   // rows the workgroup advances by
+    __shared__ __attribute__((aligned(16))) float red[SPLIT ? 4 : 1][SPLIT ? 32 * 32 : 1];
+    __shared__ float bsum[SPLIT ? 4 : 1][SPLIT ? NJ * 32 : 1];
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int i_base = blockIdx.y * RED_TILE, j_base = (blockIdx.z % common.j_tiles) * RED_TILE;
-    const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
+    const TilePlace place = tile_place(n_tiles);
+    const int64_t block = place.row_tile, r_begin = block * a.rows_per_block;
+    if (r_begin >= a.n) return; // uniform per workgroup
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
-    const bool self = a.Hin != nullptr;
-    const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vh = self && aligned16(a.Hin) && a.ldi % 4 == 0;
-    const bool vg = aligned16(a.dHout) && a.ldo % 4 == 0;
+    const int i_base = (place.col_tile / common.j_tiles) * (WI * MI * 32) + (SPLIT ? 0 : wave / (SPLIT ? 1 : WJ) * (MI * 32));
+    const int j_base = (place.col_tile % common.j_tiles) * ((SPLIT ? 1 : WJ) * NJ * 32) + (SPLIT ? 0 : wave % (SPLIT ? 1 : WJ) * (NJ * 32));
+    if (!SPLIT && (i_base >= a.w_in || j_base >= a.w_out)) return; // uniform per wavefront; no barriers in this form
+    const bool self = blockIdx.z == 1; // the product Hin^T dHout
+    const float *X = self ? a.Hin : a.Z;
+    const int64_t ldx = self ? a.ldi : a.ldz;
+    const float *x_scale = self ? a.hin_scale : nullptr;
+    const uint32_t *mask = self ? nullptr : a.mask;
+    const bool sums = i_base == 0; // this workgroup (wavefront) also forms the column sums of its columns
 
-    floatx16 accA, accS;
+    // columns past the last one re-read the last: what they give is not stored
+    const float *px[MI], *pg[NJ]; // this lane's column of row h
+    const uint32_t *pw[NJ];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { accA[r] = 0.f; accS[r] = 0.f; }
-    float accb = 0.f; // lanes 0..31: column (j_base + m) of dP, lanes 32..63: of dH_out; rows of this wavefront only
-
-    const int lr = tid >> 3, lc = (tid & 7) * 4; // this thread's float4 of each 32 x 32 tile
-    float4 z, hh, p, g;
-    float hf = 1.f; // factor of this thread's row of Hin (scaled layout); applied when the registers go to LDS
-    auto fetch = [&](int64_t r0) { // this thread's share of the four tiles of rows [r0, r0 + 32)
-        const int64_t row = r0 + lr;
-        z = make_float4(0.f, 0.f, 0.f, 0.f); hh = z; p = z; g = z;
-        if (row < r_end) {
-            if (i_base + lc < a.w_in) {
-                z = load_k4(a.Z, a.ldz, row, i_base + lc, a.w_in, vz);
-                if (self) {
-                    hh = load_k4(a.Hin, a.ldi, row, i_base + lc, a.w_in, vh);
-                    if (a.hin_scale) hf = a.hin_scale[row];
-                }
-            }
-            if (j_base + lc < a.w_out) {
-                g = load_k4(a.dHout, a.ldo, row, j_base + lc, a.w_out, vg);
-                p = g;
-                if (a.mask) {
-                    const int j = j_base + lc;
-                    const uint32_t bits = a.mask[row * a.mask_words + (j >> 5)] >> (j & 31);
-                    if (!(bits & 1u)) p.x = 0.f;
-                    if (!(bits & 2u)) p.y = 0.f;
-                    if (!(bits & 4u)) p.z = 0.f;
-                    if (!(bits & 8u)) p.w = 0.f;
-                }
-            }
+    for (int t = 0; t < MI; ++t) px[t] = X + h * ldx + (i_base + 32 * t + m < a.w_in ? i_base + 32 * t + m : a.w_in - 1);
+#pragma unroll
+    for (int t = 0; t < NJ; ++t) {
+        pg[t] = a.dHout + h * a.ldo + (j_base + 32 * t + m < a.w_out ? j_base + 32 * t + m : a.w_out - 1);
+        pw[t] = mask + h * a.mask_words + ((j_base + 32 * t < a.w_out ? j_base + 32 * t : a.w_out - 1) >> 5);
+    }
+    float nx[PAIRS][MI], np[PAIRS][NJ], nf[PAIRS];
+    uint32_t nw[PAIRS][NJ];
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p) {
+        nf[p] = 1.f;
+#pragma unroll
+        for (int t = 0; t < NJ; ++t) nw[p][t] = ~0u;
+    }
+    auto row_of = [&](int64_t r0, int p) { return r0 + (SPLIT ? 32 * (p / 4) + 8 * wave + 2 * (p % 4) : 2 * p); }; // of pair p, and the next one
+    auto fetch = [&](int64_t r0) {
+        int64_t at[PAIRS]; // rows past the end re-read the last (what they give is zeroed below): no load depends on a lane
+        if (r0 + ROWS <= r_end) {
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) at[p] = row_of(r0, p);
+        } else {
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) at[p] = row_of(r0, p) + h < r_end ? row_of(r0, p) : r_end - 1 - h;
+        }
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+#pragma unroll
+            for (int t = 0; t < MI; ++t) nx[p][t] = px[t][at[p] * ldx];
+#pragma unroll
+            for (int t = 0; t < NJ; ++t) np[p][t] = pg[t][at[p] * a.ldo];
+        }
+        if (mask) {
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) nw[p][t] = pw[t][at[p] * a.mask_words];
+        }
+        if (x_scale) {
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) nf[p] = x_scale[at[p] + h];
         }
     };
-    fetch(r_begin);
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += RED_RK) {
-        if (a.hin_scale) scale4(hh, hf);
-        *reinterpret_cast<float4 *>(&Zs[lr][lc]) = z;
-        *reinterpret_cast<float4 *>(&Hs[lr][lc]) = hh;
-        *reinterpret_cast<float4 *>(&Ps[lr][lc]) = p;
-        *reinterpret_cast<float4 *>(&Gs[lr][lc]) = g;
-        __syncthreads();
-        if (r0 + RED_RK < r_end) fetch(r0 + RED_RK); // next step's loads fly during this step's MFMAs
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-            const int k = wave * 8 + s4 * 2 + h;
-            accA = __builtin_amdgcn_mfma_f32_32x32x2f32(Zs[k][m], Ps[k][m], accA, 0, 0, 0);
-            if (self) accS = __builtin_amdgcn_mfma_f32_32x32x2f32(Hs[k][m], Gs[k][m], accS, 0, 0, 0);
-        }
-        if (blockIdx.y == 0) {
-            float (*T)[RED_TILE] = h ? Gs : Ps;
-#pragma unroll
-            for (int r = 0; r < 8; ++r) accb += T[wave * 8 + r][m];
-        }
-        __syncthreads();
-    }
 
-    // ---- add the four wavefronts' tiles in order, then store (the tile memory is free now) ----
-    __shared__ float bsum[4][64];
-    bsum[wave][lane] = accb;
-    if (wave > 0) {
+    floatx16 acc[MI][NJ];
+    float accb[NJ]; // lanes 0..31: column sums
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = 8 * (r / 4) + 4 * h + (r % 4);
-            red[wave - 1][0][i * RED_TILE + m] = accA[r];
-            red[wave - 1][1][i * RED_TILE + m] = accS[r];
-        }
+    for (int tj = 0; tj < NJ; ++tj) {
+        accb[tj] = 0.f;
+#pragma unroll
+        for (int ti = 0; ti < MI; ++ti)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[ti][tj][r] = 0.f;
     }
-    __syncthreads();
-    float *out = a.partial + (int64_t)blockIdx.x * a.stride;
-    const int ww = a.w_in * a.w_out;
-    if (wave == 0) {
+    fetch(r_begin);
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += ROWS) {
+        float x[PAIRS][MI], g[PAIRS][NJ];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int il = 8 * (r / 4) + 4 * h + (r % 4);
-            float va = accA[r], vs = accS[r];
-            for (int q = 0; q < 3; ++q) { va += red[q][0][il * RED_TILE + m]; vs += red[q][1][il * RED_TILE + m]; }
-            const int i = i_base + il, j = j_base + m;
-            if (i < a.w_in && j < a.w_out) {
-                out[i * a.w_out + j] = va;
-                if (!a.compact) out[ww + i * a.w_out + j] = vs;
+        for (int p = 0; p < PAIRS; ++p) {
+#pragma unroll
+            for (int t = 0; t < MI; ++t) x[p][t] = x_scale ? nx[p][t] * nf[p] : nx[p][t];
+#pragma unroll
+            for (int t = 0; t < NJ; ++t) g[p][t] = (nw[p][t] >> m) & 1u ? np[p][t] : 0.f;
+        }
+        if (r0 + ROWS > r_end) {
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) {
+                const bool there = row_of(r0, p) + h < r_end;
+#pragma unroll
+                for (int t = 0; t < MI; ++t) x[p][t] = there ? x[p][t] : 0.f;
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) g[p][t] = there ? g[p][t] : 0.f;
             }
         }
-        if (blockIdx.y == 0) {
-            const int j = j_base + m;
-            const float sum = ((bsum[0][lane] + bsum[1][lane]) + bsum[2][lane]) + bsum[3][lane];
-            if (j < a.w_out && !(a.compact && h)) out[(a.compact ? ww : 2 * ww) + (h ? a.w_out : 0) + j] = sum;
+        if (r0 + ROWS < r_end) fetch(r0 + ROWS);
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+            for (int ti = 0; ti < MI; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < NJ; ++tj) acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[p][ti], g[p][tj], acc[ti][tj], 0, 0, 0);
+        if (sums) {
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) accb[t] = (accb[t] + g[p][t]) + __shfl_xor(g[p][t], 32, 64); // rows in order
+        }
+    }
+
+    const int ww = a.w_in * a.w_out;
+    float *out = a.partial + block * a.stride, *out_b = out + (a.compact ? ww : 2 * ww + (self ? a.w_out : 0));
+    if (self) out += ww;
+    if constexpr (SPLIT) {
+        if (sums && h == 0) {
+#pragma unroll
+            for (int t = 0; t < NJ; ++t) bsum[wave][32 * t + m] = accb[t];
+        }
+#pragma unroll
+        for (int ti = 0; ti < MI; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < NJ; ++tj) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) red[wave][(8 * (r / 4) + 4 * h + (r % 4)) * 32 + m] = acc[ti][tj][r];
+                __syncthreads();
+                const int i = i_base + 32 * ti + (tid >> 3), j = j_base + 32 * tj + 4 * (tid & 7); // four columns of a row per thread
+                floatx4 v = *reinterpret_cast<const floatx4 *>(&red[0][4 * tid]);
+#pragma unroll
+                for (int q = 1; q < 4; ++q) v += *reinterpret_cast<const floatx4 *>(&red[q][4 * tid]);
+                if (i < a.w_in) {
+                    float *o = out + (int64_t)i * a.w_out + j;
+                    if (j + 4 <= a.w_out) *reinterpret_cast<floatx4_u *>(o) = v;
+                    else
+                        for (int c = 0; c < 3; ++c)
+                            if (j + c < a.w_out) o[c] = v[c];
+                }
+                __syncthreads();
+            }
+        if (sums && tid < NJ * 32 && j_base + tid < a.w_out) out_b[j_base + tid] = ((bsum[0][tid] + bsum[1][tid]) + bsum[2][tid]) + bsum[3][tid];
+    } else {
+#pragma unroll
+        for (int ti = 0; ti < MI; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < NJ; ++tj)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int i = i_base + 32 * ti + 8 * (r / 4) + 4 * h + (r % 4), j = j_base + 32 * tj + m;
+                    if (i < a.w_in && j < a.w_out) out[(int64_t)i * a.w_out + j] = acc[ti][tj][r];
+                }
+        if (sums && h == 0) {
+#pragma unroll
+            for (int t = 0; t < NJ; ++t)
+                if (j_base + 32 * t + m < a.w_out) out_b[j_base + 32 * t + m] = accb[t];
         }
     }
 }
@@ -1604,6 +1666,49 @@ inline LinearGradPlan linear_grad_plan(int64_t n, int32_t w_in, int32_t w_out, i
     return p;
 }
 
+// Launches grad_rows_kernel for `products` products (r.rows_per_block rows a workgroup).  Tiles of 64 x 64 per workgroup or wavefront
+// as far as the widths go; 32 x 32, whose operands are loaded twice as often, where those would leave fewer than two workgroups per CU.
+template <int WJ>
+int launch_grad_tiles(ReduceArgs r, const ReduceBatch &b, int batch, int products, int mi, int nj, hipStream_t stream)
+{
+    const int ti = (WJ ? 4 / (WJ ? WJ : 1) : 1) * mi * 32, tj = (WJ ? WJ : 1) * nj * 32;
+    const int64_t n_blocks = (r.n + r.rows_per_block - 1) / r.rows_per_block;
+    r.j_tiles = (r.w_out + tj - 1) / tj;
+    const int n_tiles = (r.w_in + ti - 1) / ti * r.j_tiles;
+    const int64_t blocks = (n_blocks + 7) / 8 * 8 * n_tiles;
+    SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "weight gradients: grid too large");
+    const dim3 grid((unsigned)blocks, (unsigned)batch, (unsigned)products);
+    if (mi == 1 && nj == 1) grad_rows_kernel<1, 1, WJ><<<grid, 256, 0, stream>>>(r, b, n_tiles);
+    else if (mi == 1) grad_rows_kernel<1, 2, WJ><<<grid, 256, 0, stream>>>(r, b, n_tiles);
+    else if (nj == 1) grad_rows_kernel<2, 1, WJ><<<grid, 256, 0, stream>>>(r, b, n_tiles);
+    else grad_rows_kernel<2, 2, WJ><<<grid, 256, 0, stream>>>(r, b, n_tiles);
+    SG_LAUNCH_CHECK();
+    return SLICEGCN_OK;
+}
+int launch_grad_rows(const ReduceArgs &r, const ReduceBatch &b, int batch, int products, bool big, hipStream_t stream)
+{
+    int mi = r.w_in > 32 ? 2 : 1, nj = r.w_out > 32 ? 2 : 1;
+    const int64_t n_blocks = (r.n + r.rows_per_block - 1) / r.rows_per_block;
+    if (big && r.w_in > 64 && r.w_out > 64) {
+        // both wide: operands are re-read so often that staging them in LDS pays once there are enough 128 x 128 tiles for the chip
+        // (2.4 M rows 256 x 256: 3.85 ms, from registers 5.36; below the line 169 k rows 128 x 128: 166 us, from registers 154)
+        ReduceArgs t = r;
+        t.j_tiles = (r.w_out + GB_T - 1) / GB_T;
+        const int64_t i_tiles = (r.w_in + GB_T - 1) / GB_T;
+        if (n_blocks * i_tiles * t.j_tiles * batch >= 256) {
+            grad_big_mfma_kernel<<<dim3((unsigned)n_blocks, (unsigned)i_tiles, (unsigned)(t.j_tiles * batch)), 256, 0, stream>>>(t, b);
+            SG_LAUNCH_CHECK();
+            return SLICEGCN_OK;
+        }
+    }
+    const int64_t tiles = (int64_t)((r.w_in + 32 * mi - 1) / (32 * mi)) * ((r.w_out + 32 * nj - 1) / (32 * nj));
+    if (n_blocks * tiles * products * batch < (big ? 4 : 1) * 512) mi = nj = 1;
+    if (!big) return launch_grad_tiles<0>(r, b, batch, products, mi, nj, stream);
+    // the wavefronts of a workgroup share their operands through L1: along both widths, or along w_in if one covers w_out
+    if (r.w_out <= 32 * nj) return launch_grad_tiles<1>(r, b, batch, products, mi, nj, stream);
+    return launch_grad_tiles<2>(r, b, batch, products, mi, nj, stream);
+}
+
 // ---- pieces of the transform-first layer order -------------------------------------------------
 // Hout[v, j] = act(P[v, j] + bias[j]) (+ Hout[v, j] when add), mask bit j of row v = [P + bias > 0].
 // One thread per element of the row padded to a multiple of 32 columns, so every half wavefront lies
@@ -1788,8 +1893,6 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
     r.mask = nullptr; r.mask_words = mask_words;
     r.partial = nullptr; r.n = n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 1;
     r.rows_per_block = plan.rows;
-    const int t = plan.big ? GB_T : RED_TILE;
-    r.j_tiles = (w_out + t - 1) / t;
     ReduceBatch b;
     FinalBatch f;
     for (int i = 0; i < BATCH; ++i) {
@@ -1799,10 +1902,7 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
         f.partial[i] = partial;
         f.dst[i] = FinalDst{{x.dW, nullptr, nullptr, x.db}, x.db_copy, {0, ww, ww, ww, stride}};
     }
-    const dim3 grid((unsigned)plan.partials, (unsigned)((w_in + t - 1) / t), (unsigned)(r.j_tiles * batch));
-    if (plan.big) grad_big_mfma_kernel<<<grid, 256, 0, stream>>>(r, b);
-    else grad_partial_mfma_kernel<<<grid, 256, 0, stream>>>(r, b);
-    SG_LAUNCH_CHECK();
+    if (int rc = launch_grad_rows(r, b, batch, 1, plan.big, stream)) return rc;
     reduce_final_kernel<<<dim3((unsigned)((stride + 31) / 32), (unsigned)batch), 1024, 0, stream>>>(f, plan.partials, stride, stride);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -2046,7 +2146,6 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         r.mask = nullptr; r.mask_words = lg->mask_words;
         r.partial = nullptr; r.n = g->n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 0;
         r.rows_per_block = plan.rows;
-        r.j_tiles = (w_out + RED_TILE - 1) / RED_TILE;
         r.hin_scale = (desc->flags & SLICEGCN_LAYER_IN_SCALED) ? g->sqrtd : nullptr;
         ReduceBatch b;
         FinalBatch f;
@@ -2079,8 +2178,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
             else grad_strip64_kernel<2, 2, 8, 2><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
             break;
         case GradPlan::TILED:
-            grad_partial_mfma_kernel<<<dim3((unsigned)plan.partials, (unsigned)((w_in + RED_TILE - 1) / RED_TILE), (unsigned)(r.j_tiles * batch)),
-                                       256, 0, stream>>>(r, b);
+            if (int rc = launch_grad_rows(r, b, batch, self ? 2 : 1, false, stream)) return rc;
             break;
         }
         SG_LAUNCH_CHECK();
