@@ -993,7 +993,7 @@ __global__ __launch_bounds__(256, 3) void grad_rows_kernel(const ReduceArgs comm
 // its own accumulators and every n_waves-th strip of 32 rows (so that the chip reads one contiguous
 // window at a time), reads a strip with coalesced 16-byte loads into wave-private LDS tiles (the
 // next strip's loads in flight during the MFMAs), and writes one partial result.  The node axis is the MFMA's k axis (lane (m, h) feeds
-// column m of node row 2s + h).  No workgroup barrier; same output layout as grad_partial_mfma_kernel,
+// column m of node row 2s + h).  No workgroup barrier; same output layout as grad_rows_kernel,
 // one partial per wavefront.
 __global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs common, const ReduceBatch batch, int64_t n_waves)
 {
@@ -1092,7 +1092,7 @@ __global__ __launch_bounds__(256) void grad_strip32_kernel(const ReduceArgs comm
 // loads in flight behind the MFMAs); the node axis is the k axis of Z^T dP and Hin^T dHout (column reads of the
 // tiles), the column axis that of dZ = dP W_agg^T and T = dHout W_self^T (row reads, weights in registers); dZ and T
 // leave through the Z and Hin tiles as 16-byte stores.  Partial sums: one per wavefront, layout of
-// grad_partial_mfma_kernel.  `a` carries the input-gradient half: B1 / B2 = W_agg / W_self (ldw), O1 = dZ (rows
+// grad_rows_kernel.  `a` carries the input-gradient half: B1 / B2 = W_agg / W_self (ldw), O1 = dZ (rows
 // scaled by scale_o1), O2 = T, K = w_out, Nout = w_in.
 __global__ __launch_bounds__(256, 2) void bwd_strip32_kernel(const ReduceArgs rcommon, const ReduceBatch rbatch, const PairArgs pcommon, const PairBatch pbatch,
                                                              int64_t n_waves)
@@ -1389,23 +1389,26 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
 // layers: one workgroup per 128 x 128 output tile and block of RED_ROWS rows, each wavefront owning a
 // 64 x 64 quarter (four MFMA accumulators).  Per step 32 rows of the X tile and of the dP tile are
 // staged in LDS (the next step's loads are issued into registers before this step's MFMAs); the
-// node axis is the MFMA's k axis.  32 flop per staged byte instead of 8 for 32 x 32 tiles.
+// node axis is the MFMA's k axis.  32 flop per staged byte instead of 8 for 32 x 32 tiles.  The tiles of a row block run back to back on
+// one XCD (grid as in grad_rows_kernel): 2.4 M rows 256 x 256 3.84 -> 3.65 ms (88 TFLOP/s), 233 k rows 0.480 -> 0.456 ms.
 constexpr int GB_T = 128;
 
-__global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch)
+__global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
 {
-    const ReduceArgs a = slice_of(common, batch, blockIdx.z / common.j_tiles);
+    const ReduceArgs a = slice_of(common, batch, blockIdx.y);
+    const TilePlace place = tile_place(n_tiles);
     __shared__ __attribute__((aligned(16))) float Xs[RED_RK][GB_T];
     __shared__ __attribute__((aligned(16))) float Ps[RED_RK][GB_T];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int i_base = blockIdx.y * GB_T, j_base = (blockIdx.z % common.j_tiles) * GB_T;
+    const int i_base = place.col_tile / common.j_tiles * GB_T, j_base = place.col_tile % common.j_tiles * GB_T;
     const int wi = (wave >> 1) * 64, wj = (wave & 1) * 64;
-    const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
+    const int64_t r_begin = place.row_tile * a.rows_per_block;
+    if (r_begin >= a.n) return; // uniform per workgroup
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
     const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vg = aligned16(a.dHout) && a.ldo % 4 == 0;
-    const bool bias_wave = blockIdx.y == 0 && (wave >> 1) == 0;
+    const bool bias_wave = i_base == 0 && (wave >> 1) == 0;
 
     floatx16 acc[2][2];
 #pragma unroll
@@ -1470,7 +1473,7 @@ __global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs com
         __syncthreads();
     }
 
-    float *out = a.partial + (int64_t)blockIdx.x * a.stride;
+    float *out = a.partial + place.row_tile * a.stride;
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
@@ -1691,12 +1694,15 @@ int launch_grad_rows(const ReduceArgs &r, const ReduceBatch &b, int batch, int p
     const int64_t n_blocks = (r.n + r.rows_per_block - 1) / r.rows_per_block;
     if (big && r.w_in > 64 && r.w_out > 64) {
         // both wide: operands are re-read so often that staging them in LDS pays once there are enough 128 x 128 tiles for the chip
-        // (2.4 M rows 256 x 256: 3.85 ms, from registers 5.36; below the line 169 k rows 128 x 128: 166 us, from registers 154)
+        // (2.4 M rows 256 x 256: 3.65 ms, from registers 5.36; below the line 169 k rows 128 x 128: 166 us, from registers 154)
         ReduceArgs t = r;
         t.j_tiles = (r.w_out + GB_T - 1) / GB_T;
         const int64_t i_tiles = (r.w_in + GB_T - 1) / GB_T;
         if (n_blocks * i_tiles * t.j_tiles * batch >= 256) {
-            grad_big_mfma_kernel<<<dim3((unsigned)n_blocks, (unsigned)i_tiles, (unsigned)(t.j_tiles * batch)), 256, 0, stream>>>(t, b);
+            const int n_tiles = (int)(i_tiles * t.j_tiles);
+            const int64_t blocks = (n_blocks + 7) / 8 * 8 * n_tiles;
+            SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "weight gradients: grid too large");
+            grad_big_mfma_kernel<<<dim3((unsigned)blocks, (unsigned)batch), 256, 0, stream>>>(t, b, n_tiles);
             SG_LAUNCH_CHECK();
             return SLICEGCN_OK;
         }
