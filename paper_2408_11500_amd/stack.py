@@ -223,7 +223,6 @@ class SliceStack:
             desc = B._LayerDesc(wi, wo, self.act(l), self.order | self.layout[l])
             self._io.append(io)
             self._shape.append(B.LayerGroup(desc, 1, *lds))
-        self._dH_key = None
         self._plan_key = key
 
     def _forward_group(self, first: int, count: int, ws):
@@ -273,13 +272,10 @@ class SliceStack:
         self._plan()
         if self.E is not None and not self.encoding_fused():
             B.slicegcn_concat_bwd(dH, [self.hs] * self.k, dE=self.dE, ws=self.ws)
-        dkey = (dH.data_ptr(), dH.stride(0))
-        if dkey != self._dH_key:  # CONCAT backward is a column view
-            ptr, ld = B._mat(dH, "dH")
-            for i in range(self.k):
-                self._io[-1][i].dHout = ptr + 4 * i * self.hs
-            self._shape[-1].ldgo = ld
-            self._dH_key = dkey
+        ptr, ld = B._mat(dH, "dH")
+        for i in range(self.k):  # CONCAT backward is a column view
+            self._io[-1][i].dHout = ptr + 4 * i * self.hs
+        self._shape[-1].ldgo = ld
 
         def backward_group(first: int, count: int, ws):
             for l in reversed(range(self.L)):
