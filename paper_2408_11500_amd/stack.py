@@ -5,8 +5,6 @@ library calls; every arithmetic step is a kernel of ``libslicegcn.so``.
 """
 from __future__ import annotations
 
-import ctypes
-
 import torch
 
 from . import binding as B
@@ -22,6 +20,48 @@ def padded_ld(width: int) -> int:
     row (or a column pass over it) touches the fewest cache lines (a 301-wide slice at ld 304 has
     every other row straddle one line more: 8.7 vs 7.8 ms per aggregation)."""
     return (width + 31) // 32 * 32
+
+
+try:  # torch's own comparison of many tensors' type, device, shape and strides in one call
+    from torch._C._dynamo.guards import TensorGuards
+except ImportError:
+    TensorGuards = None
+
+
+class TensorLayouts:
+    """Whether a list of tensors (or None) still is the memory, types, devices, shapes and strides of the list it was made
+    from.  55 tensors: 14 us; with tuples of these attributes (TensorGuards = None) 30, a quarter of a pass over 2048 nodes."""
+
+    NONE = torch.empty(0)  # stands where there is none
+
+    def __init__(self, tensors=()):
+        tensors = self._filled(tensors)
+        self.ptrs = list(map(torch.Tensor.data_ptr, tensors))
+        first = {}  # TensorGuards takes no tensor twice (slices may share their input or weights)
+        self.twins = [(i, first[id(t)]) for i, t in enumerate(tensors) if first.setdefault(id(t), i) != i]
+        self.unique = sorted(first.values())
+        tensors = [tensors[i] for i in self.unique]
+        self.guards = TensorGuards and tensors and TensorGuards(*tensors, dynamic_dims_sizes=[list(t.shape) for t in tensors],
+                                                                dynamic_dims_strides=[list(t.stride()) for t in tensors])
+        self.layouts = None if self.guards else self._layouts(tensors)
+
+    @classmethod
+    def _filled(cls, tensors):
+        return [cls.NONE if t is None else t for t in tensors]
+
+    @staticmethod
+    def _layouts(tensors):
+        return [(t.dtype, t.device, t.shape, t.stride()) for t in tensors]
+
+    def same(self, tensors) -> bool:
+        tensors = self._filled(tensors)
+        if list(map(torch.Tensor.data_ptr, tensors)) != self.ptrs:
+            return False
+        if self.twins:
+            if any(tensors[i] is not tensors[j] for i, j in self.twins):
+                return False
+            tensors = [tensors[i] for i in self.unique]
+        return self.guards.check(*tensors) if self.guards else self._layouts(tensors) == self.layouts
 
 
 class SliceStack:
@@ -111,7 +151,7 @@ class SliceStack:
         ws = max(ws, B.slicegcn_concat_bwd_workspace_bytes(n_nodes, [slice_hidden] * k))
         self.ws_lane = [torch.empty(ws, dtype=torch.uint8, device=self.dev) for _ in range(self.lanes)]
         self.ws = self.ws_lane[0]
-        self._plan_key = None
+        self._laid_out = TensorLayouts()
 
     # ---------------------------------------------------------------------------------
     def set_params(self, i: int, l: int, W_agg, b, W_self, b_self):
@@ -172,6 +212,10 @@ class SliceStack:
     # ---- call arguments of every layer, laid out once ---------------------------------
     def _tensors(self):
         out = [*self.X, self.Hcat, self.E, self.dE]
+        if self.shared:
+            out += (self.dXin, self.dXtmp, *self.dXs)
+        for pair in self.dbuf:
+            out += pair
         for i in range(self.k):
             out += self.H[i]
             out += self.Z[i]
@@ -181,12 +225,12 @@ class SliceStack:
         return out
 
     def _plan(self):
-        """Brings the argument blocks up to date: they are laid out again when a tensor of the stack has been replaced
-        (parameters are rebound when an optimiser takes them over)."""
+        """Brings the argument blocks up to date: they are laid out again, with every check, when a tensor of the stack is
+        no longer what it was (parameters are rebound when an optimiser takes them over)."""
         tensors = self._tensors()
-        key = [0 if t is None else t.data_ptr() for t in tensors]
-        if key == self._plan_key:
+        if self._laid_out.same(tensors):
             return
+        self._laid_out = TensorLayouts()
         fused = self.encoding_fused()
         self._io, self._shape = [], []
         for l, (wi, wo) in enumerate(self.widths):
@@ -223,7 +267,7 @@ class SliceStack:
             desc = B._LayerDesc(wi, wo, self.act(l), self.order | self.layout[l])
             self._io.append(io)
             self._shape.append(B.LayerGroup(desc, 1, *lds))
-        self._plan_key = key
+        self._laid_out = TensorLayouts(tensors)
 
     def _forward_group(self, first: int, count: int, ws):
         cached = self.cache_first and all(self.first_valid[first:first + count])

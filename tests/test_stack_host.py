@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from paper_2408_11500_amd import binding as B
+from paper_2408_11500_amd import stack as stack_module
 from paper_2408_11500_amd.stack import SliceStack
 
 N, K, FIRST, HS, L = 70, 3, 40, 32, 2
@@ -78,3 +79,88 @@ def test_backward_checks_every_gradient(rec):
     group, io = rec.layers("bwd")[-L]                       # the last layer runs first
     assert group.ldgo == 2 * w
     assert [x.dHout for x in io] == [buf[:, w:].data_ptr() + 4 * i * HS for i in range(K)]
+
+
+def replace(st, name, change):
+    """Puts change(tensor) in the place of one of the stack's tensors (same address)."""
+    holder, key = {"Z": (st.Z[-1], 0), "H": (st.H[-1], 0), "mask": (st.mask[-1], 1), "X": (st.X, -1), "W_self": (st.params[-1][1], "W_self"),
+                   "b": (st.params[-1][1], "b"), "dW_agg": (st.grads[-1][1], "dW_agg"), "Hcat": (st.__dict__, "Hcat"),
+                   "E": (st.__dict__, "E"), "dbuf": (st.dbuf[-1], 1)}[name]
+    old = holder[key]
+    holder[key] = change(old)
+    assert holder[key].data_ptr() == old.data_ptr()
+    return holder[key]
+
+
+@pytest.fixture(params=[True, False], ids=["guards", "tuples"])
+def comparison(request, monkeypatch):
+    """The two ways the stack compares its tensors' layouts."""
+    if not request.param:
+        monkeypatch.setattr(stack_module, "TensorGuards", None)
+
+
+@pytest.mark.parametrize("name", ["Z", "H", "X", "W_self", "b", "dW_agg", "Hcat", "E", "dbuf", "mask"])
+def test_plan_sees_another_type_at_the_same_address(rec, comparison, name):
+    st = stack()
+    st.forward()
+    st.backward(torch.randn(N, K * HS))
+    replace(st, name, lambda t: t.view(torch.float32 if t.dtype == torch.int32 else torch.int32))
+    good = len(rec.calls)
+    for call in (st.forward, lambda: st.backward(torch.randn(N, K * HS))):
+        with pytest.raises(TypeError):
+            call()
+    assert len(rec.calls) == good
+
+
+@pytest.mark.parametrize("name", ["W_self", "dW_agg", "Hcat", "X"])
+def test_plan_sees_other_strides_at_the_same_address(rec, comparison, name):
+    st = stack()
+    st.forward()
+    replace(st, name, lambda t: t.t() if t.shape[0] == t.shape[1] else t.as_strided((N, t.shape[1] // 2), (t.stride(0), 2)))
+    with pytest.raises(TypeError):
+        st.forward()
+
+
+def test_plan_follows_leading_dimensions(rec, comparison):
+    st = stack(k=1)
+    st.forward()
+    replace(st, "Hcat", lambda t: t.as_strided((N // 2, HS), (2 * HS, 1)))
+    st.forward()
+    assert [g.ldo for g, _ in rec.layers("fwd")] == [HS, HS, HS, 2 * HS]
+
+
+@pytest.mark.parametrize("what", ["W_agg", "W_self"])
+def test_plan_sees_another_shape_at_the_same_address(rec, comparison, what):
+    st = stack()
+    st.forward()
+    st.params[0][0][what] = st.params[0][0][what].view(HS, FIRST)
+    with pytest.raises(ValueError):
+        st.forward()
+
+
+def test_plan_sees_which_parameter_is_missing(rec, comparison):
+    st = stack()
+    p = st.params[0][0]
+    p["b_self"] = None
+    st.forward()
+    p["b"], p["b_self"] = None, p["b"]
+    st.forward()
+    first, second = rec.layers("fwd")[0][1][0], rec.layers("fwd")[L][1][0]
+    assert first.params.b and not first.params.b_self
+    assert second.params.b_self == first.params.b and not second.params.b
+
+
+def test_plan_is_kept_while_nothing_changes(rec, comparison, monkeypatch):
+    """Also where a tensor stands in several places (shared inputs, shared weights, absent biases)."""
+    st = stack(shared_input=torch.zeros(N, 64))
+    for p in st.params:
+        p[0].update(st.params[0][0], b=None)
+    st.forward()
+    made = []
+    monkeypatch.setattr(B, "_LayerDesc", lambda *a, inner=B._LayerDesc: made.append(a) or inner(*a))
+    st.forward()
+    st.backward(torch.randn(N, K * HS))
+    assert not made
+    st.params[1][0]["W_agg"] = st.params[1][0]["W_agg"].clone()
+    st.forward()
+    assert len(made) == L
