@@ -186,9 +186,11 @@ def _stream() -> int:
 
 def _mat(t: torch.Tensor, name: str, dtype=torch.float32):
     """(pointer, leading dimension) of a 2-D device tensor with unit column stride."""
-    if not t.is_cuda or t.dtype != dtype or t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
+    strides = t.stride()
+    if not t.is_cuda or t.dtype != dtype or len(strides) != 2 or (strides[1] != 1 and t.shape[1] > 1):
         raise TypeError(f"{name}: expected a 2-D {dtype} device tensor with unit column stride")
-    return t.data_ptr(), int(t.stride(0)) if t.shape[0] > 1 else max(int(t.stride(0)), int(t.shape[1]))
+    rows, cols = t.shape
+    return t.data_ptr(), strides[0] if rows > 1 else max(strides[0], cols)
 
 
 def _vec(t, name: str, dtype=torch.float32):
