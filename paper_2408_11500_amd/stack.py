@@ -151,7 +151,7 @@ class SliceStack:
         ws = max(ws, B.slicegcn_concat_bwd_workspace_bytes(n_nodes, [slice_hidden] * k))
         self.ws_lane = [torch.empty(ws, dtype=torch.uint8, device=self.dev) for _ in range(self.lanes)]
         self.ws = self.ws_lane[0]
-        self._laid_out = TensorLayouts()
+        self._laid_out, self._fused = TensorLayouts(), None
 
     # ---------------------------------------------------------------------------------
     def set_params(self, i: int, l: int, W_agg, b, W_self, b_self):
@@ -224,14 +224,14 @@ class SliceStack:
                 out += (p["W_agg"], p["b"], p["W_self"], p["b_self"], gr["dW_agg"], gr["db"], gr["dW_self"], gr["db_self"])
         return out
 
-    def _plan(self):
+    def _plan(self, fused: bool):
         """Brings the argument blocks up to date: they are laid out again, with every check, when a tensor of the stack is
-        no longer what it was (parameters are rebound when an optimiser takes them over)."""
+        no longer what it was (parameters are rebound when an optimiser takes them over) or the encoding changed its place.
+        The activation and the flags of a layer are put in by each call."""
         tensors = self._tensors()
-        if self._laid_out.same(tensors):
+        if fused == self._fused and self._laid_out.same(tensors):
             return
         self._laid_out = TensorLayouts()
-        fused = self.encoding_fused()
         self._io, self._shape = [], []
         for l, (wi, wo) in enumerate(self.widths):
             last = l == self.L - 1
@@ -264,25 +264,27 @@ class SliceStack:
                 if i > 0 and same != lds:
                     raise ValueError("the slices' tensors differ in their leading dimensions")
                 lds = same
-            desc = B._LayerDesc(wi, wo, self.act(l), self.order | self.layout[l])
             self._io.append(io)
-            self._shape.append(B.LayerGroup(desc, 1, *lds))
-        self._laid_out = TensorLayouts(tensors)
+            self._shape.append(B.LayerGroup(B._LayerDesc(wi, wo, 0, 0), 1, *lds))
+        self._laid_out, self._fused = TensorLayouts(tensors), fused
+
+    def _group(self, l: int, count: int, flags: int = 0) -> B.LayerGroup:
+        sh = self._shape[l]
+        sh.count = count
+        sh.desc.act, sh.desc.flags = self.act(l), self.order | self.layout[l] | flags
+        return sh
 
     def _forward_group(self, first: int, count: int, ws):
         cached = self.cache_first and all(self.first_valid[first:first + count])
         for l in range(self.L):
-            sh = self._shape[l]
-            sh.count = count
-            if l == 0:
-                sh.desc.flags = self.order | self.layout[0] | (B.LAYER_Z_VALID if cached else 0)
+            sh = self._group(l, count, B.LAYER_Z_VALID if cached and l == 0 else 0)
             B.slicegcn_layers_fwd(self.g, sh, self._io[l], first, ws)
         self.first_valid[first:first + count] = [True] * count
 
     def forward_slice(self, i: int):
         if not self.inputs_prepared:
             self.prepare_inputs()
-        self._plan()
+        self._plan(self.encoding_fused())
         self._forward_group(i, 1, self.ws_lane[i % self.lanes])
 
     def _on_lanes(self, fn):
@@ -305,16 +307,18 @@ class SliceStack:
     def forward(self) -> torch.Tensor:
         if not self.inputs_prepared:
             self.prepare_inputs()
-        self._plan()
+        fused = self.encoding_fused()
+        self._plan(fused)
         self._on_lanes(self._forward_group)
         # the last layer of every slice already stored into its column block: encode in place, unless that is done
-        if not self.encoding_fused():
+        if not fused:
             B.slicegcn_concat([self.hout(i, self.L - 1) for i in range(self.k)], self.E, self.Hcat)
         return self.Hcat
 
     def backward(self, dH: torch.Tensor):
-        self._plan()
-        if self.E is not None and not self.encoding_fused():
+        fused = self.encoding_fused()
+        self._plan(fused)
+        if self.E is not None and not fused:
             B.slicegcn_concat_bwd(dH, [self.hs] * self.k, dE=self.dE, ws=self.ws)
         ptr, ld = B._mat(dH, "dH")
         for i in range(self.k):  # CONCAT backward is a column view
@@ -323,10 +327,7 @@ class SliceStack:
 
         def backward_group(first: int, count: int, ws):
             for l in reversed(range(self.L)):
-                sh = self._shape[l]
-                sh.count = count
-                sh.desc.flags = self.order | self.layout[l]
-                B.slicegcn_layers_bwd(self.g, sh, self._io[l], first, ws)
+                B.slicegcn_layers_bwd(self.g, self._group(l, count), self._io[l], first, ws)
             if self.shared and not self.deferred and first > 0:  # learned inputs: the first slice writes, the others add
                 B.slicegcn_accumulate(self.dXin[:, :self.w0], self.dXtmp[:, :self.w0])
 

@@ -164,3 +164,23 @@ def test_plan_is_kept_while_nothing_changes(rec, comparison, monkeypatch):
     st.params[1][0]["W_agg"] = st.params[1][0]["W_agg"].clone()
     st.forward()
     assert len(made) == L
+
+
+def test_flags_changed_after_a_pass_take_effect(rec):
+    """fuse_encoding, act_last and the layers' flags are what they are at the call, as the encoding pass looks at them."""
+    st = stack()
+    st.forward()
+    st.backward(torch.randn(N, K * HS))
+    assert all(x.enc and x.denc for _, io in (rec.layers("fwd")[L - 1], rec.layers("bwd")[0]) for x in io)
+    assert "slicegcn_concat" not in [c[0] for c in rec.calls]
+    st.fuse_encoding, st.act_last = False, B.ACT_NONE
+    st.layout[1] |= B.LAYER_OUT_SCALED
+    del rec.calls[:]
+    st.forward()
+    st.backward(torch.randn(N, K * HS))
+    (first, _), (last, io) = rec.layers("fwd")
+    (last_b, io_b), _ = rec.layers("bwd")
+    assert not any(x.enc or x.denc for x in io + io_b)     # the encoding is added once, by the pass of its own
+    assert [c[0] for c in rec.calls].count("slicegcn_concat") == 1 and [c[0] for c in rec.calls].count("slicegcn_concat_bwd") == 1
+    assert (first.desc.act, last.desc.act, last_b.desc.act) == (B.ACT_RELU, B.ACT_NONE, B.ACT_NONE)
+    assert last.desc.flags == last_b.desc.flags == B.LAYER_OUT_SCALED
