@@ -232,10 +232,11 @@ class SliceStack:
         if fused == self._fused and self._laid_out.same(tensors):
             return
         self._laid_out = TensorLayouts()
-        self._io, self._shape = [], []
+        self._io, self._shapes, self._alike = [], [], True
         for l, (wi, wo) in enumerate(self.widths):
             last = l == self.L - 1
             io = (B.LayerIo * self.k)()
+            shapes, terms = [], set()
             for i in range(self.k):
                 p, gr, x = self.params[i][l], self.grads[i][l], io[i]
                 for name, W in (("W_agg", p["W_agg"]), ("W_self", p["W_self"])):
@@ -260,16 +261,16 @@ class SliceStack:
                     x.dHout, ldgo = B._mat(self.dbuf[slot][(l + 1) % 2], "dHout")
                 else:
                     ldgo = 0
-                same = (ldi, ldo, ldz, mask_words, ldgo, ldgi)
-                if i > 0 and same != lds:
-                    raise ValueError("the slices' tensors differ in their leading dimensions")
-                lds = same
+                lds = (ldi, ldo, ldz, mask_words, ldgo, ldgi)
+                shapes.append(B.LayerGroup(B._LayerDesc(wi, wo, 0, 0), 1, *lds))
+                terms.add((p["W_self"] is None, lds))
             self._io.append(io)
-            self._shape.append(B.LayerGroup(B._LayerDesc(wi, wo, 0, 0), 1, *lds))
+            self._shapes.append(shapes)
+            self._alike = self._alike and len(terms) == 1  # slices of other leading dimensions or terms share no launch
         self._laid_out, self._fused = TensorLayouts(tensors), fused
 
-    def _group(self, l: int, count: int, flags: int = 0) -> B.LayerGroup:
-        sh = self._shape[l]
+    def _group(self, l: int, first: int, count: int, flags: int = 0) -> B.LayerGroup:
+        sh = self._shapes[l][first]
         sh.count = count
         sh.desc.act, sh.desc.flags = self.act(l), self.order | self.layout[l] | flags
         return sh
@@ -277,7 +278,7 @@ class SliceStack:
     def _forward_group(self, first: int, count: int, ws):
         cached = self.cache_first and all(self.first_valid[first:first + count])
         for l in range(self.L):
-            sh = self._group(l, count, B.LAYER_Z_VALID if cached and l == 0 else 0)
+            sh = self._group(l, first, count, B.LAYER_Z_VALID if cached and l == 0 else 0)
             B.slicegcn_layers_fwd(self.g, sh, self._io[l], first, ws)
         self.first_valid[first:first + count] = [True] * count
 
@@ -292,8 +293,9 @@ class SliceStack:
         i mod lanes, the lanes starting after what the caller's stream holds so far and the caller's stream going on after
         all of them."""
         if self.lanes == 1:
-            for i in range(0, self.k, self.group):
-                fn(i, min(self.group, self.k - i), self.ws)
+            group = self.group if self._alike else 1
+            for i in range(0, self.k, group):
+                fn(i, min(group, self.k - i), self.ws)
             return
         main = torch.cuda.current_stream()
         for s in self.streams:
@@ -323,11 +325,11 @@ class SliceStack:
         ptr, ld = B._mat(dH, "dH")
         for i in range(self.k):  # CONCAT backward is a column view
             self._io[-1][i].dHout = ptr + 4 * i * self.hs
-        self._shape[-1].ldgo = ld
+            self._shapes[-1][i].ldgo = ld
 
         def backward_group(first: int, count: int, ws):
             for l in reversed(range(self.L)):
-                B.slicegcn_layers_bwd(self.g, self._group(l, count), self._io[l], first, ws)
+                B.slicegcn_layers_bwd(self.g, self._group(l, first, count), self._io[l], first, ws)
             if self.shared and not self.deferred and first > 0:  # learned inputs: the first slice writes, the others add
                 B.slicegcn_accumulate(self.dXin[:, :self.w0], self.dXtmp[:, :self.w0])
 
