@@ -252,8 +252,9 @@ int slicegcn_spmm_slice_static(const slicegcn_graph *g, int op, const float *X, 
  * every epoch); the aggregation is then skipped.  The paper's own implementation recomputes it.
  * ws: at least slicegcn_layer_fwd_workspace_bytes(g, desc) bytes (the aggregation's workspace; in the
  * transform-first order also the staged Hin W_agg and its aggregation).
+ * Outputs must not overlap inputs, except that Hout may be Hin (rows at the same addresses, ldo = ldi) where w_out <= 96.
  * EINVAL: NULL Hin/Hout/W_agg/saved->Z, widths < 1, ld too small, ldz not a multiple of 4,
- *         mask NULL or mask_words too small with ACT_RELU, unknown act or flag, misaligned ws;
+ *         mask NULL or mask_words too small with ACT_RELU, unknown act or flag, misaligned ws, Hout in Hin's rows where wider;
  * EWORKSPACE: ws NULL or too small.
  * ------------------------------------------------------------------------------------- */
 size_t slicegcn_layer_fwd_workspace_bytes(const slicegcn_graph *g, const slicegcn_layer_desc *desc);
@@ -276,7 +277,8 @@ size_t slicegcn_layer_bwd_workspace_bytes(const slicegcn_graph *g, const slicegc
  * fixed order.  ws: at least slicegcn_layer_bwd_workspace_bytes bytes (partial weight gradients,
  * the staged dZ = dP W_agg^T and the aggregation's workspace).  In the transform-first order the pass reads
  * G = A^^T dP instead of Z: dW_agg = Hin^T G, dHin = G W_agg^T + dHout W_self^T.
- * EINVAL as for the forward; EWORKSPACE when ws is NULL or ws_bytes too small.
+ * Outputs must not overlap inputs, except that dHin may be dHout (rows at the same addresses, ldgi = ldo) where w_in <= 96.
+ * EINVAL as for the forward, and for dHin in dHout's rows where wider; EWORKSPACE when ws is NULL or ws_bytes too small.
  * ------------------------------------------------------------------------------------- */
 int slicegcn_layer_bwd(const slicegcn_graph *g, const slicegcn_layer_desc *desc,
                        const slicegcn_layer_params *params, const float *Hin, int64_t ldi,
@@ -327,7 +329,8 @@ size_t slicegcn_linear_bwd_workspace_bytes(int64_t n, int32_t w_in, int32_t w_ou
  * slicegcn_linear_fwd wrote (read only; ignored for ACT_NONE).  The node-axis reductions run in
  * fp32 over blocks of 1024 rows and are combined in fp64 in a fixed order.  ws: 256-byte aligned,
  * at least slicegcn_linear_bwd_workspace_bytes bytes when dW or db is non-NULL, else unused.
- * EINVAL as for the forward; EWORKSPACE when ws is NULL or too small. */
+ * Outputs must not overlap inputs, except that dX may be dY (rows at the same addresses, lddx = lddy) where w_in <= 128.
+ * EINVAL as for the forward, and for dX in dY's rows where wider; EWORKSPACE when ws is NULL or too small. */
 int slicegcn_linear_bwd(const float *X, int64_t ldx, int64_t n, int32_t w_in, int32_t w_out,
                         const float *W, int32_t act, const uint32_t *mask, int64_t mask_words,
                         const float *dY, int64_t lddy, float *dX, int64_t lddx, float *dW, float *db,

@@ -36,6 +36,7 @@ int slicegcn_build_norm_csr_with(const int64_t *src, const int64_t *dst, int64_t
  * results do not depend on the slices it shares a call with.
  *   enc  : row added to the output outside the activation, beside b_self (the slice encoding), or NULL
  *   denc : receives the column sums of dHout as well (the gradient of enc, equal to db_self), or NULL; both need W_self
+ * No slice's output may overlap an operand of another slice of the call.
  * ld*: leading dimensions common to the group (ldgo of dHout, ldgi of dHin).  The forward pass uses Hin, Hout, Z, mask,
  * the backward pass Hin, Z, mask, dHout, dHin (NULL in every entry: not wanted) and grads. */
 #define SLICEGCN_MAX_GROUP 8

@@ -129,7 +129,7 @@ __device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int wi
 // Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 2.98 ms = 108 TFLOP/s (a kernel with rows and weights in LDS: 3.71), 169 k rows
 // 0.238 (0.288); slice layers 64 -> 64 with self term, 169 k rows: 47 us (61).
 template <int NT, bool TWO, bool BWD>
-__global__ __launch_bounds__(256, TWO && NT == 3 ? 2 : 3) void pair_rows_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+__global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair_rows_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
 {
     const PairArgs a = slice_of(common, batch);
     constexpr int BN = NT * 32, KC = 32, GS = BN + 4; // GS: units per group of four k (padded: conflict-free writes and reads)
@@ -720,10 +720,40 @@ void launch_strip64(const PairArgs &a, const PairBatch &b, dim3 grid, hipStream_
     else pair_strip64_kernel<KC, NC, BWD, false><<<grid, 256, 0, stream>>>(a, b);
 }
 
+// Products in place: whether output rows are rows of an operand (the leading dimensions agree; the kernels read a row before they
+// store it, but another workgroup may still read the row for its own columns)
+inline bool same_rows(const float *o, int64_t ldo, int32_t wo, const float *x, int64_t ldx, int32_t wx)
+{
+    const int64_t d = (reinterpret_cast<intptr_t>(x) - reinterpret_cast<intptr_t>(o)) / (int64_t)sizeof(float);
+    return o && x && ldo == ldx && d < wo && -d < wx;
+}
+inline bool in_place(const PairArgs *list, int batch)
+{
+    bool any = false;
+    for (int i = 0; i < batch; ++i) {
+        const PairArgs &a = list[i];
+        const float *second = a.B2 ? a.A2 : nullptr;
+        any = any || same_rows(a.O1, a.ldo1, a.Nout, a.A1, a.lda1, a.K) || same_rows(a.O1, a.ldo1, a.Nout, second, a.lda2, a.K) ||
+              same_rows(a.O2, a.ldo2, a.Nout, a.A1, a.lda1, a.K) || same_rows(a.O2, a.ldo2, a.Nout, second, a.lda2, a.K);
+    }
+    return any;
+}
+// Tiles of 32 columns a workgroup of pair_rows_kernel can take (three for two products, and four, have their registers at two workgroups
+// per CU; four are compiled for products in place alone)
+inline int most_tiles(const PairArgs &a) { return a.A2 != nullptr && a.B2 != nullptr ? 3 : 4; }
+int check_in_place(const PairArgs *list, int batch)
+{
+    const int tiles = (list[0].Nout + 31) / 32, most = most_tiles(list[0]);
+    SG_REQUIRE(tiles <= most || !in_place(list, batch), SLICEGCN_EINVAL, "dense product in place: %d output columns, at most %d", list[0].Nout,
+               32 * most);
+    return SLICEGCN_OK;
+}
+
 // `list`: one entry per slice model of the batch (1 to BATCH, equal but for the pointers)
 template <bool BWD>
 int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
 {
+    if (int rc = check_in_place(list, batch)) return rc;
     const PairArgs &a = list[0];
     PairBatch b;
     for (int i = 0; i < BATCH; ++i) {
@@ -758,6 +788,7 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
     const int tiles = (a.Nout + 31) / 32;
     int nt = tiles % 2 != 0 && tiles % 3 == 0 ? 3 : tiles < 2 ? 1 : 2;
     if (row_tiles * ((tiles + nt - 1) / nt) * batch < 2048) nt = 1;
+    if (tiles > nt && in_place(list, batch)) nt = tiles; // whole rows
     const int n_col = (tiles + nt - 1) / nt;
     const int64_t blocks = (row_tiles + 7) / 8 * 8 * n_col;
     SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
@@ -768,7 +799,8 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
     case 4: pair_rows_kernel<2, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
     case 5: pair_rows_kernel<2, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
     case 6: pair_rows_kernel<3, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    default: pair_rows_kernel<3, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    case 7: pair_rows_kernel<3, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    default: pair_rows_kernel<4, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
     }
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -2020,6 +2052,25 @@ static int bwd_transform_first(const slicegcn_graph *g, const slicegcn_layer_gro
     char *dPs = sec.take(mat), *Gs = sec.take(mat), *WaTs = sec.take(wt), *WsTs = sec.take(wt), *red = sec.take(red_each), *agg_ws = sec.take(agg);
     auto dP = [&](int i) { return reinterpret_cast<float *>(dPs + i * mat); };
     auto G = [&](int i) { return reinterpret_cast<float *>(Gs + i * mat); };
+    // dHin = G W_agg^T + dHout W_self^T, the last step: one forward-form launch over the transposed weights
+    TransposeBatch t;
+    int mats = 0;
+    PairArgs list[BATCH];
+    for (int i = 0; i < batch && io[0].dHin; ++i) {
+        float *WaT = reinterpret_cast<float *>(WaTs + i * wt), *WsT = reinterpret_cast<float *>(WsTs + i * wt);
+        t.W[mats] = io[i].params.W_agg; t.Wt[mats++] = WaT;
+        if (self) { t.W[mats] = io[i].params.W_self; t.Wt[mats++] = WsT; }
+        PairArgs &a = list[i];
+        a.A1 = G(i); a.lda1 = ldp;
+        a.A2 = self ? io[i].dHout : nullptr; a.lda2 = lg->ldgo;
+        a.B1 = WaT; a.B2 = self ? WsT : nullptr;
+        a.bias1 = a.bias2 = nullptr;
+        a.O1 = io[i].dHin; a.ldo1 = lg->ldgi; a.O2 = nullptr; a.ldo2 = 0;
+        a.mask = nullptr; a.mask_words = 0;
+        a.n = n; a.K = w_out; a.Nout = w_in; a.ldw = w_in; a.act = SLICEGCN_ACT_NONE;
+    }
+    if (mats > 0)
+        if (int rc = check_in_place(list, batch)) return rc; // before anything is launched
     {
         ProfScope prof(SLICEGCN_PROF_DENSE_BWD, w_out, stream);
         MaskApplyBatch b;
@@ -2054,25 +2105,9 @@ static int bwd_transform_first(const slicegcn_graph *g, const slicegcn_layer_gro
         if (any_self)
             if (int rc = launch_linear_grads(self_list, batch, lg->ldi, n, w_in, w_out, 0, lg->ldgo, red, red_each, stream)) return rc;
     }
-    if (io[0].dHin) { // dHin = G W_agg^T + dHout W_self^T: one forward-form launch over the transposed weights
+    if (mats > 0) {
         ProfScope prof(SLICEGCN_PROF_DENSE_BWD, w_in, stream);
         const int count = w_in * w_out;
-        TransposeBatch t;
-        int mats = 0;
-        PairArgs list[BATCH];
-        for (int i = 0; i < batch; ++i) {
-            float *WaT = reinterpret_cast<float *>(WaTs + i * wt), *WsT = reinterpret_cast<float *>(WsTs + i * wt);
-            t.W[mats] = io[i].params.W_agg; t.Wt[mats++] = WaT;
-            if (self) { t.W[mats] = io[i].params.W_self; t.Wt[mats++] = WsT; }
-            PairArgs &a = list[i];
-            a.A1 = G(i); a.lda1 = ldp;
-            a.A2 = self ? io[i].dHout : nullptr; a.lda2 = lg->ldgo;
-            a.B1 = WaT; a.B2 = self ? WsT : nullptr;
-            a.bias1 = a.bias2 = nullptr;
-            a.O1 = io[i].dHin; a.ldo1 = lg->ldgi; a.O2 = nullptr; a.ldo2 = 0;
-            a.mask = nullptr; a.mask_words = 0;
-            a.n = n; a.K = w_out; a.Nout = w_in; a.ldw = w_in; a.act = SLICEGCN_ACT_NONE;
-        }
         transpose_kernel<<<dim3((unsigned)((count + 255) / 256), (unsigned)mats), 256, 0, stream>>>(t, w_in, w_out);
         SG_LAUNCH_CHECK();
         if (int rc = launch_pair<false>(list, batch, stream)) return rc;
@@ -2139,6 +2174,8 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         a.n = g->n; a.K = w_out; a.Nout = w_in; a.ldw = w_out; a.act = desc->act;
         a.scale_o1 = g->dinv; // dZ is staged as D~^-1/2 dZ: its aggregation then skips the stored values
     }
+    if (need_dHin)
+        if (int rc = check_in_place(list, batch)) return rc; // before anything is launched
     const GradPlan plan = grad_plan(g->n, w_in, w_out);
     // narrow layers with a self term: the kernel that forms the weight gradients also forms dZ and T (one read of dHout)
     const bool fused_inputs = need_dHin && self && plan.kind == GradPlan::STRIP32;
@@ -2376,6 +2413,13 @@ extern "C" int slicegcn_linear_bwd(const float *X, int64_t ldx, int64_t n, int32
                    "linear_bwd: mask is NULL or mask_words < ceil(w_out / 32)");
     hipStream_t stream = as_stream(stream_);
     const uint32_t *m = act == SLICEGCN_ACT_RELU ? mask : nullptr;
+    PairArgs a;
+    a.A1 = dY; a.lda1 = lddy; a.A2 = nullptr; a.lda2 = 0;
+    a.B1 = W; a.B2 = nullptr; a.bias1 = a.bias2 = nullptr;
+    a.O1 = dX; a.ldo1 = lddx; a.O2 = nullptr; a.ldo2 = 0;
+    a.mask = const_cast<uint32_t *>(m); a.mask_words = mask_words;
+    a.n = n; a.K = w_out; a.Nout = w_in; a.ldw = w_out; a.act = act;
+    if (int rc = check_in_place(&a, 1)) return rc; // before anything is launched
     if (dW || db) {
         const size_t need = linear_partial_bytes(red_blocks(n), w_in, w_out);
         SG_REQUIRE(ws != nullptr && ws_bytes >= need, SLICEGCN_EWORKSPACE, "linear_bwd: workspace of %zu bytes, %zu needed",
@@ -2386,12 +2430,6 @@ extern "C" int slicegcn_linear_bwd(const float *X, int64_t ldx, int64_t n, int32
         if (int rc = launch_linear_grads(&args, 1, ldx, n, w_in, w_out, mask_words, lddy, ws, ws_bytes, stream)) return rc;
     }
     if (dX) {
-        PairArgs a;
-        a.A1 = dY; a.lda1 = lddy; a.A2 = nullptr; a.lda2 = 0;
-        a.B1 = W; a.B2 = nullptr; a.bias1 = a.bias2 = nullptr;
-        a.O1 = dX; a.ldo1 = lddx; a.O2 = nullptr; a.ldo2 = 0;
-        a.mask = const_cast<uint32_t *>(m); a.mask_words = mask_words;
-        a.n = n; a.K = w_out; a.Nout = w_in; a.ldw = w_out; a.act = act;
         ProfScope prof(SLICEGCN_PROF_LINEAR_BWD, w_in, stream);
         if (int rc = launch_pair<true>(a, stream)) return rc;
     }

@@ -94,3 +94,16 @@ def test_widened_entry_points_validate_before_device_work(L):
     assert L.slicegcn_adam_step(None, None, None, None, 4, 1e-3, 0.9, 0.999, 1e-8, 0.0, 1, None) == binding.EINVAL
     assert L.slicegcn_adam_step(one, one, one, one, 4, 1e-3, 0.9, 0.999, 1e-8, 0.0, 0, None) == binding.EINVAL  # step < 1
     assert L.slicegcn_adam_step(one, one, one, one, 4, 1e-3, 1.0, 0.999, 1e-8, 0.0, 1, None) == binding.EINVAL  # beta1 = 1
+
+
+def test_gradients_in_place_are_refused_where_rows_are_shared(L):
+    """dX in dY's rows: one workgroup forms whole rows up to 128 columns; wider ones are formed by several, of which one
+    would store before another has read.  Columns beside each other in one buffer are no overlap."""
+    vp, base = ctypes.c_void_p, 1 << 20
+    W = vp(256)
+
+    def bwd(w, dX, ld):
+        return L.slicegcn_linear_bwd(W, w, 64, w, w, W, 0, None, 0, vp(base), ld, vp(dX), ld, None, None, None, 0, None)
+    for w, dX, ld in ((129, base, 129), (200, base, 256), (200, base + 400, 256), (1000, base - 40, 1024)):
+        assert bwd(w, dX, ld) == binding.EINVAL, (w, dX, ld)
+        assert b"in place" in L.slicegcn_last_error()
