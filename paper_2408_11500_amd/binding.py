@@ -271,12 +271,14 @@ class Graph:
 
     def destroy(self):
         if self._h:
-            if self._memory:  # a stream other than the one it was made on may still read it
-                torch.cuda.synchronize()
-            lib().slicegcn_graph_destroy(self._h)
-            self._h = 0
-            self._memory = []
-            self._ws = None
+            try:
+                if self._memory:  # a stream other than the one it was made on may still read it
+                    torch.cuda.synchronize(self._memory[0].device)
+            finally:
+                lib().slicegcn_graph_destroy(self._h)
+                self._h = 0
+                self._memory = []
+                self._ws = None
 
     def __del__(self):
         try:

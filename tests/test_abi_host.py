@@ -4,8 +4,10 @@ returns error codes before any device work."""
 import ctypes
 import os
 import re
+import types
 
 import pytest
+import torch
 
 import oracle
 from paper_2408_11500_amd import binding
@@ -107,3 +109,33 @@ def test_gradients_in_place_are_refused_where_rows_are_shared(L):
     for w, dX, ld in ((129, base, 129), (200, base, 256), (200, base + 400, 256), (1000, base - 40, 1024)):
         assert bwd(w, dX, ld) == binding.EINVAL, (w, dX, ld)
         assert b"in place" in L.slicegcn_last_error()
+
+
+class _Destroys:
+    def __init__(self):
+        self.handles = []
+
+    def slicegcn_graph_destroy(self, h):
+        self.handles.append(h)
+
+
+def test_destroy_waits_for_the_handles_device_and_frees_it_all_the_same(monkeypatch):
+    """The memory of a handle goes back to the allocator once its own device has finished, whichever one is current; if the
+    wait fails the handle is freed nevertheless."""
+    lib, waits = _Destroys(), []
+    monkeypatch.setattr(binding, "lib", lambda: lib)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda device=None: waits.append(device))
+    block = types.SimpleNamespace(device=torch.device("cuda", 3))
+    g = binding.Graph(11, [block])
+    g.destroy()
+    assert waits == [torch.device("cuda", 3)] and lib.handles == [11] and g._memory == []
+
+    def broken(device=None):
+        raise RuntimeError("device lost")
+    monkeypatch.setattr(torch.cuda, "synchronize", broken)
+    g = binding.Graph(12, [block])
+    with pytest.raises(RuntimeError, match="device lost"):
+        g.destroy()
+    assert lib.handles == [11, 12] and g._memory == [] and g._ws is None
+    with pytest.raises(ValueError):
+        g.handle
