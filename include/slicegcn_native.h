@@ -18,7 +18,7 @@ typedef struct {
     void *(*alloc)(void *ctx, size_t bytes);
 } slicegcn_allocator;
 
-/* Bytes of scratch memory slicegcn_build_norm_csr_with needs (0 on bad input). */
+/* Bytes of scratch memory slicegcn_build_norm_csr_with needs (0 where it returns EINVAL or ERANGE for these sizes and flags). */
 size_t slicegcn_build_workspace_bytes(int64_t n_edges, int64_t n_nodes, uint32_t flags);
 
 /* slicegcn_build_norm_csr with the caller's memory.  allocator: where the handle's arrays come from; the caller gives

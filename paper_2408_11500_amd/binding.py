@@ -332,8 +332,11 @@ def slicegcn_build_norm_csr(src: torch.Tensor, dst: torch.Tensor, n_nodes: int,
     # ten times the build (126 M entries: 107 ms with them, 6.8 ms without)
     ws = None
     nbytes = int(lib().slicegcn_build_workspace_bytes(src.numel(), n_nodes, flags))
-    if nbytes:
-        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    if nbytes:  # 0: the build is refused below
+        try:
+            ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        except torch.OutOfMemoryError as e:
+            raise SliceGCNError(ENOMEM, f"build_norm_csr: no {nbytes} bytes of workspace: {e}") from e
     _building.blocks = blocks = []
     try:
         _check(lib().slicegcn_build_norm_csr_with(ps, pd, src.numel(), n_nodes, flags, ctypes.byref(_allocator), *_ws(ws),

@@ -628,14 +628,11 @@ size_t build_bytes(int64_t n_edges, int64_t n, uint32_t flags)
            Arena::rounded((size_t)kp.n_keys * 4) + later;
 }
 
-// Argument checks of both entry points
-int check_build(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_nodes, uint32_t flags, slicegcn_graph **out)
+// Checks of what is to be built, for both entry points and the workspace query
+int check_sizes(int64_t n_edges, int64_t n_nodes, uint32_t flags)
 {
-    SG_REQUIRE(out != nullptr, SLICEGCN_EINVAL, "build_norm_csr: out is NULL");
-    *out = nullptr;
     SG_REQUIRE(n_nodes >= 1, SLICEGCN_EINVAL, "build_norm_csr: n_nodes = %lld < 1", (long long)n_nodes);
     SG_REQUIRE(n_edges >= 0, SLICEGCN_EINVAL, "build_norm_csr: n_edges = %lld < 0", (long long)n_edges);
-    SG_REQUIRE(n_edges == 0 || (src && dst), SLICEGCN_EINVAL, "build_norm_csr: NULL edge arrays");
     SG_REQUIRE((flags & ~(SLICEGCN_SYMMETRIZE | SLICEGCN_ADD_SELF_LOOPS | SLICEGCN_REORDER_DEGREE | SLICEGCN_REORDER_BFS |
                           SLICEGCN_SCHED_SHORT_ITEMS | SLICEGCN_SCHED_LONG_ITEMS)) == 0,
                SLICEGCN_EINVAL, "build_norm_csr: unknown flag bits 0x%x", flags);
@@ -650,6 +647,13 @@ int check_build(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t
                "build_norm_csr: %lld candidate entries exceed int32 indexing", (long long)n_keys);
     return SLICEGCN_OK;
 }
+int check_build(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_nodes, uint32_t flags, slicegcn_graph **out)
+{
+    SG_REQUIRE(out != nullptr, SLICEGCN_EINVAL, "build_norm_csr: out is NULL");
+    *out = nullptr;
+    SG_REQUIRE(n_edges <= 0 || (src && dst), SLICEGCN_EINVAL, "build_norm_csr: NULL edge arrays");
+    return check_sizes(n_edges, n_nodes, flags);
+}
 
 } // namespace
 
@@ -659,7 +663,7 @@ using namespace slicegcn;
 
 extern "C" size_t slicegcn_build_workspace_bytes(int64_t n_edges, int64_t n_nodes, uint32_t flags)
 {
-    if (n_nodes < 1 || n_nodes > INT32_MAX || n_edges < 0 || n_edges > INT32_MAX) return 0;
+    if (check_sizes(n_edges, n_nodes, flags)) return 0;
     return build_bytes(n_edges, n_nodes, flags);
 }
 

@@ -139,3 +139,25 @@ def test_destroy_waits_for_the_handles_device_and_frees_it_all_the_same(monkeypa
     assert lib.handles == [11, 12] and g._memory == [] and g._ws is None
     with pytest.raises(ValueError):
         g.handle
+
+
+def test_build_workspace_of_a_refused_build_is_zero(L):
+    """What the build would refuse needs no workspace: the caller then gets the build's own error, not one of its allocator."""
+    size, big = L.slicegcn_build_workspace_bytes, 2**31 - 1
+    assert size(1000, 100, 3) > 8000
+    assert size(2**30, 1000, 3) == 0            # both directions of 2^30 edges exceed int32
+    assert size(2**30 - 500, 1000, 3) == 0      # ... and these with the self loops
+    assert size(2**30 - 501, 1000, 3) > 0
+    assert size(big, big, 0) > 0 and size(big, big, 2) == 0 and size(big, 2**31, 0) == 0
+    for flags in (1 << 20, 4 | 8, 16 | 32):
+        assert size(1000, 100, flags) == 0
+
+
+def test_build_out_of_memory_is_the_librarys_error(L, monkeypatch):
+    def full(*a, **k):
+        raise torch.OutOfMemoryError("tried to allocate 60 GiB")
+    monkeypatch.setattr(torch, "empty", full)
+    none = torch.zeros(0, dtype=torch.int64)
+    with pytest.raises(binding.SliceGCNError) as e:
+        binding.slicegcn_build_norm_csr(none, none, 100)
+    assert e.value.status == binding.ENOMEM and "60 GiB" in str(e.value)
