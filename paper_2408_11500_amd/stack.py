@@ -135,15 +135,17 @@ class SliceStack:
         # round of a launch's workgroups still shows.  A large graph gains nothing and would need every buffer of the backward
         # pass per slice, so a group ends where one launch touches GROUP_BYTES.
         row_bytes = 4 * 4 * max(padded_ld(first_width), padded_ld(slice_hidden))  # Z, input and output, twice the widest
+        if self.shared:
+            row_bytes += 4 * padded_ld(first_width)  # the slice's input gradient
         self.group = 1 if self.lanes > 1 else max(1, min(k, B.MAX_GROUP, GROUP_BYTES // (n_nodes * row_bytes)))
         slots = max(self.lanes, self.group)
         self.dbuf = [[torch.empty((n_nodes, padded_ld(slice_hidden)), **f32) for _ in range(2)] if layers > 1 else []
                      for _ in range(slots)]
-        # with a shared (learned) input and several slices at a time every slice keeps its own input gradient until all
-        # are there; they are then added in slice order, as one slice after the other adds them
-        self.deferred = self.shared and slots > 1
-        self.dXs = [torch.empty((n_nodes, padded_ld(first_width)), **f32) for _ in range(k - 1)] if self.deferred else []
-        self.dXtmp = torch.empty((n_nodes, padded_ld(first_width)), **f32) if self.shared and k > 1 and not self.deferred else None
+        # with a shared (learned) input the first slice's gradient is formed where the sum is wanted; the other slices that run
+        # together keep theirs until all of them are there, and they are added in slice order
+        self.together = k if self.lanes > 1 else self.group
+        self.dXs = [torch.empty((n_nodes, padded_ld(first_width)), **f32)
+                    for _ in range(k - 1 if k <= self.together else self.together)] if self.shared else []
         ws = 0
         for l, (wi, wo) in enumerate(self.widths):
             ws = max(ws, B.slicegcn_layers_fwd_workspace_bytes(graph, wi, wo, self.group, order),
@@ -200,6 +202,10 @@ class SliceStack:
     def zbuf(self, i: int, l: int):
         return None if self.tf[l] else self.Z[i][l][:, :self.widths[l][0]]
 
+    def input_gradient(self, i: int) -> torch.Tensor:
+        """Where slice i's gradient of a shared input goes."""
+        return self.dXin if i == 0 else self.dXs[i % self.together - (i < self.together)]
+
     def act(self, l: int) -> int:
         return self.act_last if l == self.L - 1 else B.ACT_RELU
 
@@ -213,7 +219,7 @@ class SliceStack:
     def _tensors(self):
         out = [*self.X, self.Hcat, self.E, self.dE]
         if self.shared:
-            out += (self.dXin, self.dXtmp, *self.dXs)
+            out += (self.dXin, *self.dXs)
         for pair in self.dbuf:
             out += pair
         for i in range(self.k):
@@ -254,7 +260,7 @@ class SliceStack:
                 if l > 0:
                     x.dHin, ldgi = B._mat(self.dbuf[slot][l % 2], "dHin")
                 elif self.shared:
-                    x.dHin, ldgi = B._mat(self.dXin if i == 0 else self.dXs[i - 1] if self.deferred else self.dXtmp, "dHin")
+                    x.dHin, ldgi = B._mat(self.input_gradient(i), "dHin")
                 else:  # raw features need no gradient
                     x.dHin, ldgi = None, 0
                 if not last:
@@ -330,13 +336,18 @@ class SliceStack:
         def backward_group(first: int, count: int, ws):
             for l in reversed(range(self.L)):
                 B.slicegcn_layers_bwd(self.g, self._group(l, first, count), self._io[l], first, ws)
-            if self.shared and not self.deferred and first > 0:  # learned inputs: the first slice writes, the others add
-                B.slicegcn_accumulate(self.dXin[:, :self.w0], self.dXtmp[:, :self.w0])
+            if self.lanes == 1:
+                self._add_input_gradients(first, count)
 
         self._on_lanes(backward_group)
-        if self.deferred:
-            for i in range(0, self.k - 1, B.MAX_GROUP):
-                B.slicegcn_accumulate_many(self.dXin[:, :self.w0], [t[:, :self.w0] for t in self.dXs[i:i + B.MAX_GROUP]])
+        if self.lanes > 1:
+            for i in range(0, self.k, B.MAX_GROUP):
+                self._add_input_gradients(i, min(B.MAX_GROUP, self.k - i))
+
+    def _add_input_gradients(self, first: int, count: int):
+        others = [self.input_gradient(i)[:, :self.w0] for i in range(max(first, 1), first + count)] if self.shared else []
+        if others:
+            B.slicegcn_accumulate_many(self.dXin[:, :self.w0], others)
 
 
 class Classifier:

@@ -1,5 +1,6 @@
 """What SliceStack hands to the library, looked at without a GPU: CPU tensors pass for device tensors and a recording
 stand-in takes the calls, so arguments can be checked that must never reach a kernel."""
+import contextlib
 import ctypes
 import types
 
@@ -28,13 +29,15 @@ class Recorder:
                 group = B.LayerGroup.from_buffer_copy(a[1]._obj)
                 io = (B.LayerIo * group.count).from_address(ctypes.addressof(a[2]._obj) + self.first * ctypes.sizeof(B.LayerIo))
                 self.calls.append((name, group, [B.LayerIo.from_buffer_copy(x) for x in io]))
+            elif name == "slicegcn_accumulate_many":   # the list of sources ends with the call
+                self.calls.append((name, a[0], list((ctypes.c_void_p * a[3]).from_address(a[2]))))
             else:
                 self.calls.append((name, a))
             return 0
         return call
 
     def layers(self, name):
-        return [(g, io) for n, g, io in [c for c in self.calls if c[0] == f"slicegcn_layers_{name}"]]
+        return [c[1:] for c in self.calls if c[0] == f"slicegcn_layers_{name}"]
 
 
 @pytest.fixture
@@ -203,3 +206,36 @@ def test_slices_that_differ_run_on_their_own(rec, what):
         assert [io[0].Hin for _, io in got] == [x.data_ptr() for x in st.X]
         assert [bool(io[0].params.W_self) for _, io in got] == [True, what != "self term", True]
     assert [g.ldgo for g, _ in rec.layers("bwd")] == [K * HS] * K
+
+
+@pytest.mark.parametrize("streams,k,group", [(1, 1, 1), (1, 3, 1), (1, 3, 2), (1, 8, 8), (1, 19, 8), (1, 9, 8), (1, 20, 3), (4, 6, 1)])
+def test_shared_input_gradients_alive(rec, monkeypatch, streams, k, group):
+    """With feature fusion only the input gradients of the slices that run together are kept, and they are added in slice
+    order, the first slice's being where the sum is formed."""
+    monkeypatch.setattr(stack_module, "GROUP_BYTES", group * N * 20 * 64)
+    if streams > 1:
+        monkeypatch.setattr(torch.cuda, "Stream", lambda device=None: types.SimpleNamespace(wait_stream=lambda s: None))
+        monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(wait_stream=lambda s: None))
+        monkeypatch.setattr(torch.cuda, "stream", lambda s: contextlib.nullcontext())
+    st = stack(k=k, shared_input=torch.zeros(N, 64), streams=streams)
+    assert st.group == group
+    together = k if streams > 1 else min(group, k)
+    assert sum(t.numel() for t in st.dXs) <= (together if k > together else k - 1) * N * 64
+    st.forward()
+    del rec.calls[:]
+    st.backward(torch.randn(N, k * HS))
+    pending, order = {}, []
+    for name, *a in rec.calls:
+        if name == "slicegcn_layers_bwd" and a[0].desc.w_in == FIRST:
+            for x in a[1]:
+                slot = len(order) + len(pending)
+                assert x.dHin not in pending, "a gradient is overwritten before it was added"
+                if slot == 0:
+                    assert x.dHin == st.dXin.data_ptr()
+                    order.append(0)
+                else:
+                    pending[x.dHin] = slot
+        elif name == "slicegcn_accumulate_many":
+            assert a[0] == st.dXin.data_ptr() and 1 <= len(a[1]) <= B.MAX_GROUP
+            order += [pending.pop(p) for p in a[1]]
+    assert not pending and order == list(range(k))
