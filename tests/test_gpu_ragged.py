@@ -38,3 +38,25 @@ def test_spmm_contiguous_rows(graph, width, offset):
         sg.slicegcn_spmm_slice(g, flat[offset:].view(n, width), Y[:, :width], prescaled=pre)
         assert_close(Y[:, :width].cpu().numpy(), want, f"contiguous w={width}")
         assert bool(torch.isnan(Y[:, width]).all())                            # nothing written past width
+
+
+@pytest.mark.parametrize("width", [129, 200, 301])
+@pytest.mark.parametrize("pre", [False, True])
+def test_wide_operand_with_the_workspace_of_one_pass(graph, width, pre):
+    """On a cache-resident graph all passes of 128 columns share a launch where the workspace holds their partial sums, and
+    follow each other in the workspace of one pass otherwise: the same bits."""
+    n, o, g = graph
+    X = torch.randn((n, width), generator=torch.Generator(device="cuda").manual_seed(width), device="cuda")
+    full, least = sg.slicegcn_spmm_workspace_bytes(g, width), sg.slicegcn_spmm_workspace_bytes(g, 128)
+    assert 0 < least < full
+    got = []
+    for size in (full, full - 256, least):
+        Y = torch.full((n, width), float("nan"), device="cuda")
+        sg.slicegcn_spmm_slice(g, X, Y, ws=torch.empty(size, dtype=torch.uint8, device="cuda"), prescaled=pre)
+        got.append(Y)
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    want = oracle.spmm(o, X.cpu().numpy() * (1 / o.dinv[:, None] if pre else 1))
+    assert_close(got[0].cpu().numpy(), want, f"w={width}")
+    with pytest.raises(sg.binding.SliceGCNError) as e:
+        sg.slicegcn_spmm_slice(g, X, Y, ws=torch.empty(least - 256, dtype=torch.uint8, device="cuda"), prescaled=pre)
+    assert e.value.status == sg.binding.EWORKSPACE
