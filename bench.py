@@ -35,6 +35,12 @@ def spmm_bytes(n: int, nnz: int, w: int, with_add: bool = False) -> int:
     return 8 * nnz + 4 * (n + 1) + 8 * n * w + (4 * n * w if with_add else 0)
 
 
+def slices_per_launch(k: int, group: int) -> float:
+    """Slice aggregations in one launch group of a layer whose k slices share launches `group` at a time (the average where
+    the last group is smaller)."""
+    return k / -(-k // group)
+
+
 def cpu_model() -> str:
     try:
         for line in open("/proc/cpuinfo"):
@@ -330,6 +336,7 @@ def main():
     kernels = {f"{kind}_w{wd}": {"launches": cnt, "avg_ms": tot / cnt, "median_ms": med, "min_ms": lo, "max_ms": hi}
                for kind, wd, cnt, tot, lo, hi, med in prof_full}
     dom = next(((cnt, tot) for kind, wd, cnt, tot in prof if kind == "spmm" and wd == width), None)
+    shared = 1.0 if args.spmm_only or dom is None else slices_per_launch(k, st.group)  # the figures below are per slice
     if dom is None:
         # this variant of the step ran no aggregation at the slice width (cached first layer, or the transform-first
         # order, which aggregates at the hidden width): time the slice-width aggregation on its own
@@ -342,7 +349,8 @@ def main():
     if dom is None:
         print("bench.py: no aggregation at the slice width was timed", file=sys.stderr)
         sys.exit(1)
-    avg_s = dom[1] / dom[0] / 1e3
+    avg_s = dom[1] / dom[0] / shared / 1e3
+    one = kernels.get(f"spmm_w{width}", {})
     nbytes = spmm_bytes(n, view.nnz, width)
     achieved = nbytes / avg_s / 1e9
     traffic = traffic_source = None
@@ -379,9 +387,9 @@ def main():
         "epoch_ms": None if args.spmm_only else ms_per_step,
         "epochs_per_s": None if args.spmm_only else 1e3 / ms_per_step,
         "ms_per_step_without_events": ms_no_events, "graph_ms_per_step": graph_ms,
-        "spmm_avg_ms": avg_s * 1e3, "spmm_median_ms": kernels.get(f"spmm_w{width}", {}).get("median_ms"),
-        "spmm_min_ms": kernels.get(f"spmm_w{width}", {}).get("min_ms"),
-        "spmm_launches_timed": dom[0], "build_norm_csr_ms": build_ms,
+        "spmm_avg_ms": avg_s * 1e3, "spmm_median_ms": one["median_ms"] / shared if one else None,
+        "spmm_min_ms": one["min_ms"] / shared if one else None,
+        "spmm_launches_timed": dom[0], "spmm_slices_per_launch": shared, "build_norm_csr_ms": build_ms,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_source, "kernel": "slice aggregation (spmm_wave_items + spmm_group_items + spmm_tiny_rows + spmm_fix kernels of one call)",
                      "algorithmic_bytes_per_launch": nbytes,

@@ -23,6 +23,12 @@ def test_algorithmic_bytes_formula():
     assert bench.spmm_bytes(n, nnz, w) == 8 * nnz + 4 * (n + 1) + 8 * n * w == 5_080_000_004
 
 
+def test_slices_per_launch():
+    """The headline rate is per slice: launches that work on several slices count for all of them."""
+    import bench
+    assert [bench.slices_per_launch(*a) for a in ((8, 1), (4, 4), (2, 8), (9, 8), (17, 8), (1, 1))] == [1, 4, 2, 4.5, 17 / 3, 1]
+
+
 def test_workloads_match_the_stated_sizes():
     import synth
     want = {"cfg1": (2048, 10_240, 128, 2), "cfg2": (169_343, 2_540_145, 128, 4), "cfg3": (232_965, 114_232_965, 602, 2),
