@@ -360,7 +360,7 @@ def main():
     if os.path.exists(tfile) and args.vertex_order == "permuted" and args.reorder == "none":
         import re
         # the summary holds one figure per form of the aggregation; take the one the timed launches ran in
-        factored = args.prescaled if args.spmm_only else st.in_scaled
+        factored = args.prescaled if args.spmm_only else st.in_scaled[0]
         key = "hbm_bytes_per_launch" if factored else "hbm_bytes_per_launch_with_values"
         m = re.search(rf"^{key} = (\d+)", open(tfile).read(), flags=re.M)
         traffic = int(m.group(1)) if m else None
