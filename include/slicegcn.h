@@ -28,7 +28,8 @@
  *    and after a call; `ws` may be NULL when that size is 0.  Two calls that share a workspace
  *    must be ordered on one stream.
  *  - Results are deterministic: kernels use no floating-point atomics, so two calls on the
- *    same inputs give bitwise equal outputs.
+ *    same inputs give bitwise equal outputs.  (slicegcn_linear_bwd: with the same ws_bytes; its
+ *    reductions over the nodes have as many partial sums as the workspace has room for.)
  */
 #ifndef SLICEGCN_H
 #define SLICEGCN_H
@@ -328,7 +329,10 @@ size_t slicegcn_linear_bwd_workspace_bytes(int64_t n, int32_t w_in, int32_t w_ou
  * NULL outputs are skipped (dX = NULL for a first layer over constant inputs).  mask is what
  * slicegcn_linear_fwd wrote (read only; ignored for ACT_NONE).  The node-axis reductions run in
  * fp32 over blocks of 1024 rows and are combined in fp64 in a fixed order.  ws: 256-byte aligned,
- * at least slicegcn_linear_bwd_workspace_bytes bytes when dW or db is non-NULL, else unused.
+ * at least slicegcn_linear_bwd_workspace_bytes bytes when dW or db is non-NULL, else unused.  On few
+ * rows (n * max(w_in, w_out) <= 2^19) a larger workspace, up to the size
+ * slicegcn_linear_bwd_full_workspace_bytes gives, means shorter blocks: faster, and other last bits of
+ * dW and db (dX does not change).
  * Outputs must not overlap inputs, except that dX may be dY (rows at the same addresses, lddx = lddy) where w_in <= 128.
  * EINVAL as for the forward, and for dX in dY's rows where wider; EWORKSPACE when ws is NULL or too small. */
 int slicegcn_linear_bwd(const float *X, int64_t ldx, int64_t n, int32_t w_in, int32_t w_out,

@@ -24,7 +24,7 @@ size_t slicegcn_build_workspace_bytes(int64_t n_edges, int64_t n_nodes, uint32_t
 /* slicegcn_build_norm_csr with the caller's memory.  allocator: where the handle's arrays come from; the caller gives
  * that memory back after slicegcn_graph_destroy, which then frees no device memory (NULL: the library allocates and
  * frees it).  ws: scratch memory, free again when the call returns (NULL: allocated and freed inside).  Device
- * allocations cost more than the build itself on most graphs, so a host with a caching allocator passes both.
+ * allocations cost as much as the build itself and more, so a host with a caching allocator passes both.
  * EINVAL / ERANGE as slicegcn_build_norm_csr; EWORKSPACE: ws too small; ENOMEM: the allocator returned NULL. */
 int slicegcn_build_norm_csr_with(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_nodes, uint32_t flags,
                                  const slicegcn_allocator *allocator, void *ws, size_t ws_bytes, void *stream,
@@ -33,7 +33,9 @@ int slicegcn_build_norm_csr_with(const int64_t *src, const int64_t *dst, int64_t
 /* ---------------------------------------------------------------------------------------
  * One layer of up to SLICEGCN_MAX_GROUP slice models of equal shape in one set of launches (slicegcn_layer_fwd and
  * slicegcn_layer_bwd for each of them; on a small graph a slice model's kernels fill a fraction of the chip).  A slice's
- * results do not depend on the slices it shares a call with.
+ * results do not depend on the slices it shares a call with.  In the transform-first order the weight gradients of few rows
+ * (n * max(w_in, w_out) <= 2^19) are summed over shorter blocks of rows here than by slicegcn_layer_bwd, whose workspace has no
+ * room for more partial sums: they agree up to rounding; everything else is bitwise the same.
  *   enc  : row added to the output outside the activation, beside b_self (the slice encoding), or NULL
  *   denc : receives the column sums of dHout as well (the gradient of enc, equal to db_self), or NULL; both need W_self
  * No slice's output may overlap an operand of another slice of the call.
@@ -67,7 +69,7 @@ int slicegcn_layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *gro
                         void *ws, size_t ws_bytes, void *stream);
 
 /* slicegcn_linear_bwd takes a larger workspace than it requires: with this many bytes its reductions over the nodes are
- * split as finely as they gain from (0 on bad input). */
+ * split as finely as they gain from (0 on bad input).  The last bits of dW and db depend on the split, and so on ws_bytes. */
 size_t slicegcn_linear_bwd_full_workspace_bytes(int64_t n, int32_t w_in, int32_t w_out);
 
 /* slicegcn_accumulate over 1 to SLICEGCN_MAX_GROUP sources in one sweep: dst[:, 0:w] += srcs[0], then srcs[1], ... (the

@@ -502,8 +502,9 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
     return SLICEGCN_OK;
 }
 
-// Sorted keys (may hold repeats and sentinels) -> m.rowptr, m.colidx, and every entry's row in rowid.  With `pattern` = NULL
-// rowptr is given and the pattern has no repeats; otherwise allocates colidx and vals once the number of entries is known.
+// Sorted keys (may hold repeats and sentinels) -> m.rowptr, m.colidx, and every entry's row in rowid; allocates colidx and vals.
+// `count_known`: the number of entries is g->nnz (the transposed pattern); otherwise it is read back, with the count of bad ids.
+// `dense_rows`: every row has an entry (self loops), so the sweep over the keys writes the row pointers too.
 template <class K>
 int csr_from_keys(const K *keys, const KeyPlan &kp, int64_t n_keys, slicegcn_graph *g, Csr &m, bool dense_rows, int32_t *rowid, int32_t *counters,
                   bool count_known, Keep &keep, Arena ws, hipStream_t stream)

@@ -852,7 +852,7 @@ __device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatc
 //   WJ > 0  the four wavefronts own tiles of their own, WJ of them along w_out, over all rows (wider dense layers)
 // Column sums (bias gradients) run in row order over the loaded values.
 // A kernel that staged 32 x 32 tiles in LDS re-read its operands per tile and waited at two barriers per 32 rows.  Pairs of products:
-// 233 k rows 301 x 128 823 -> 591 us (61 TFLOP/s), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
+// two slices of 233 k rows 301 x 128 1.65 -> 1.19 ms (64 TFLOP/s), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
 // 256 x 47 1.93 -> 1.40 ms, 60 k rows 64 x 64 46 -> 22 us.  Bound by the loads, one register of two rows' pieces at a time.
 // Grid: x = 8 row blocks x all tiles per group of workgroups (a row block's tiles meet on one XCD), y = slice, z = product.
 template <int MI, int NJ, int WJ>
@@ -1418,7 +1418,7 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
 }
 
 // Partial weight gradient of a single product (compact layout: [X^T dP | colsum dP]) for wide
-// layers: one workgroup per 128 x 128 output tile and block of RED_ROWS rows, each wavefront owning a
+// layers: one workgroup per 128 x 128 output tile and block of rows_per_block rows, each wavefront owning a
 // 64 x 64 quarter (four MFMA accumulators).  Per step 32 rows of the X tile and of the dP tile are
 // staged in LDS (the next step's loads are issued into registers before this step's MFMAs); the
 // node axis is the MFMA's k axis.  32 flop per staged byte instead of 8 for 32 x 32 tiles.  The tiles of a row block run back to back on
@@ -1637,9 +1637,10 @@ __global__ __launch_bounds__(1024) void reduce_final_kernel(const FinalBatch bat
 
 inline int64_t red_blocks(int64_t n) { return (n + RED_ROWS - 1) / RED_ROWS; }
 
-// Node rows per partial sum of a slice layer's weight gradients: RED_ROWS, or a quarter of it when that
-// would give the tiled kernel fewer than 2048 workgroups (a workgroup walks its rows in dependent steps
-// of 32, so on small graphs shorter walks in more workgroups finish sooner: cfg2 80 -> 35 us).
+// Node rows per partial sum of a slice layer's weight gradients: RED_ROWS, or a quarter of it when that would give fewer than
+// 2048 workgroups of one 32 x 32 tile each (a workgroup walks its rows in dependent steps, so on small graphs shorter walks in more
+// workgroups finish sooner: cfg2 80 -> 35 us with such tiles).  grad_rows_kernel takes up to 64 x 64 a workgroup; the line stays where
+// it is all the same, since the rows of a sum decide a gradient's last bits.
 inline int32_t layer_grad_rows(int64_t n, int32_t w_in, int32_t w_out)
 {
     const int64_t tiles = (int64_t)((w_in + RED_TILE - 1) / RED_TILE) * ((w_out + RED_TILE - 1) / RED_TILE);
@@ -1675,10 +1676,16 @@ inline GradPlan grad_plan(int64_t n, int32_t w_in, int32_t w_out)
     return GradPlan{GradPlan::TILED, nb, layer_grad_rows(n, w_in, w_out)};
 }
 
-// A dense layer's weight and bias gradients: 128 x 128 output tiles where the layer is wide, 32 x 32 tiles otherwise, a
-// partial sum per RED_ROWS node rows.  On few rows that would leave most of the chip idle behind chains of RED_ROWS rows, so
-// there (up to SMALL_LINEAR output elements) the rows are split until 512 workgroups are there or a workgroup is down to
-// one step, as far as the workspace has room (`capacity` partial sums): 5000 rows 96 -> 96: 132 -> 15 us.
+// A dense layer's weight and bias gradients: by grad_rows_kernel or, where both widths are large, in 128 x 128 tiles (`big`: layers
+// wider than 64; see launch_grad_rows), a partial sum per RED_ROWS node rows.  On few rows that leaves most of the chip idle behind
+// chains of RED_ROWS rows, so up to SMALL_LINEAR elements of the wider operand the rows are split until 512 workgroups of one tile are
+// there or a workgroup is down to one step, as far as the workspace has room (`capacity` partial sums; the least workspace leaves
+// RED_ROWS): the last bits of these gradients depend on it.  Split / in chains of 1024, 96 -> 96: 1000 rows 11 / 57 us, 5000 rows
+// 14 / 58, 5461 rows (the line) 14 / 53.
+// The line is not where splitting stops paying (8000 rows 17 / 58, 40 000 30 / 58, 160 000 67 / 122; 256 -> 256 from 160 000 rows
+// on 256 either way).  Above it the sums keep the order they have with every workspace: an update carries a gradient's last bits
+// into the next forward pass, where a few activations in 10^8 lie within rounding of zero and, passing or not, change a whole
+// term.  Up to 2^19 elements that is one activation in a hundred passes.
 struct LinearGradPlan {
     bool big;
     int32_t rows;

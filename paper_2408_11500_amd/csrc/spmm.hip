@@ -27,7 +27,7 @@
 // anywhere: a contiguous 25-wide matrix takes the same kernels as a padded one.  Where the last vector of a row
 // would reach past the row, its lane loads the row's last four columns instead and shifts its sums into place
 // before they are stored, so nothing outside the operand is read.  (One float per lane on the single-class
-// schedule, which such operands took before: 89 us per call for 1.6 M entries of 25 columns; 48 us here.)
+// schedule, which such operands took before: 93 us per call for 1.6 M entries of 25 columns; 39 us here.)
 //
 // The partial sums of rows with several items live in a workspace the caller passes in (its size comes
 // from spmm_workspace_bytes), so a graph handle is read-only here and calls on different streams
@@ -699,6 +699,9 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, 
                 int64_t ldy, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream, bool prescaled)
 {
     SG_REQUIRE(batch >= 1 && batch <= MAX_BATCH, SLICEGCN_EINVAL, "aggregation: batch of %d", batch);
+    // Operands of 1 to 3 columns: one float per lane, also where their rows have room for a 16-byte gather.  1 column in rows of 4 / 32
+    // floats, 126 M entries: 1.07 / 1.28 ms (with 16-byte gathers, which they took before: 1.17 / 1.34); 310 M entries 3.35 / 4.12 (3.48 /
+    // 4.15); 2.5 M entries 26 / 29 us (43 / 45, of which the shorter runs on small graphs are the larger part).
     const int V = width >= 4 ? 4 : 1;
     // passes of at most 128 columns (32 lanes per row): narrower ones re-read the index streams more often, wider ones
     // make the set of hot rows of the operand too large for the L2s (301 columns: 7.8 / 7.4 / 7.7 ms for passes of 64 / 128 / 256)

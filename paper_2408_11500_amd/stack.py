@@ -10,8 +10,9 @@ import torch
 from . import binding as B
 
 # Slices run in groups whose layers share their launches while the rows one launch works on stay within this many bytes
-# (see SliceStack.group).  Epochs at 64 MB / 1 GB / 4 GB: 60 k nodes, 5 slices 2.09 / 1.67 / 1.67 ms; 169 k nodes, 4 slices 3.15 / 3.05 /
-# 3.06; 1 M nodes, 4 slices 12.30 / 12.31 / 12.00.  2.4 M nodes in groups at 16 GB gain nothing (72.3, 72.8 -> 72.2 ms) for 6.5 GB more.
+# (see SliceStack.group).  Training epochs at 64 MB / 1 GB / 4 GB, 3 layers of 64-wide slices: 60 k nodes, 5 slices 2.31 / 1.86 / 1.86
+# ms; 169 k nodes, 4 slices 3.62 / 3.42 / 3.42; 1 M nodes, 4 slices 20.8 / 20.8 / 19.9.  At 16 GB 2.4 M nodes, 4 slices run as a group
+# too: 74.1 -> 73.1 ms for 6.5 GB more.
 GROUP_BYTES = 4 << 30
 
 

@@ -120,3 +120,25 @@ def test_forward_sums_do_not_depend_on_the_tiling(w_in, w_out):
     assert_fp32(Y, (Xd @ Wd + b.double()).clamp_min(0), size, "Y")
     size = Zd.abs() @ Wd.abs() + b.double().abs() + Xd.abs() @ Wsd.abs() + bs.double().abs()
     assert_fp32(H, (Zd @ Wd + b.double()).clamp_min(0) + Xd @ Wsd + bs.double(), size, "H")
+
+
+@pytest.mark.parametrize("n,w_in,w_out", [(1, 40, 30), (1500, 64, 64), (5461, 96, 96), (5462, 96, 96), (2600, 200, 130), (9000, 70, 50)])
+def test_workspace_decides_the_split_of_the_gradients_only(n, w_in, w_out):
+    """Between the least and the full workspace dW and db differ by rounding at most (not at all past 2^19 elements, where both
+    are the same), each within an fp32 sum's bound of fp64; dX is the same bits."""
+    gen = torch.Generator(device="cuda").manual_seed(n + w_in)
+    X, dY, W = operand(gen, n, w_in, 0, False), operand(gen, n, w_out, 0, False), operand(gen, w_in, w_out, 0, False)
+    least, full = B.slicegcn_linear_bwd_workspace_bytes(n, w_in, w_out), B.slicegcn_linear_bwd_full_workspace_bytes(n, w_in, w_out)
+    split = n * max(w_in, w_out) <= 1 << 19
+    assert (full > least) == (split and n > 32)
+    got = []
+    for size in (least, (least + full) // 512 * 256, full):
+        dX, dW, db = torch.empty_like(X), torch.empty_like(W), torch.empty(w_out, device="cuda")
+        B.slicegcn_linear_bwd(X, W, None, dY, dX, dW, db, torch.empty(max(size, least), dtype=torch.uint8, device="cuda"), act=B.ACT_NONE)
+        assert_fp32(dW, X.double().t() @ dY.double(), X.double().abs().t() @ dY.double().abs(), "dW")
+        assert_fp32(db, dY.double().sum(0), dY.double().abs().sum(0), "db")
+        got.append((dX, dW, db))
+    for other in got[1:]:
+        assert torch.equal(got[0][0], other[0])
+        if not split:
+            assert torch.equal(got[0][1], other[1]) and torch.equal(got[0][2], other[2])
