@@ -172,8 +172,8 @@ def main():
                          "stored values); by default graphs of 16 M stored entries or more keep them as D~^-1/2 H "
                          "(SLICEGCN_LAYER_IN/OUT_SCALED)")
     ap.add_argument("--streams", type=int, default=1,
-                    help="slice models in flight at a time, each on its own HIP stream (default 1: one after the other); "
-                         "pays on the small workloads, whose kernels leave most of the chip idle.  The per-kernel "
+                    help="slice models in flight at a time, each on its own HIP stream (default 1: slices that share launches, or "
+                         "one after the other on large graphs, which is no slower on any workload here).  The per-kernel "
                          "times then overlap and say little; ms_per_step is what to read")
     ap.add_argument("--reorder", choices=("none", "degree", "bfs"), default="none",
                     help="row order of the aggregation schedule (SLICEGCN_REORDER_*): by degree, or breadth first "
@@ -183,7 +183,7 @@ def main():
                          "of the seeded random relabelling: a secondary data point on how much the numbering matters")
     args = ap.parse_args()
     if args.gpus != 1:
-        print("bench.py: this build runs on one GPU only (all k slices execute sequentially on it); "
+        print("bench.py: this build runs on one GPU only (all k slices execute on it); "
               "--gpus must be 1", file=sys.stderr)
         sys.exit(2)
 
