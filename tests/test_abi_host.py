@@ -23,8 +23,8 @@ def L():
     return binding.lib()
 
 
-def declared_symbols():
-    text = open(os.path.join(ROOT, "include", "slicegcn.h")).read()
+def declared_symbols(header="slicegcn.h"):
+    text = open(os.path.join(ROOT, "include", header)).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
     return sorted(set(re.findall(r"\b(slicegcn_[a-z_]+)\s*\(", text)))
 
@@ -34,6 +34,13 @@ def test_every_declared_symbol_is_exported(L):
     assert len(names) == 29 and set(names) == set(binding.EXPORTS)
     for n in names:
         assert getattr(L, n) is not None
+
+
+def test_the_native_header_is_exported_too(L):
+    names = set(declared_symbols("slicegcn_native.h"))
+    assert {"slicegcn_build_norm_csr_with", "slicegcn_layers_fwd", "slicegcn_layers_bwd", "slicegcn_accumulate_many"} <= names
+    for n in names:
+        assert getattr(L, n).argtypes is not None
 
 
 def test_slice_strategy_matches_oracle(L):
