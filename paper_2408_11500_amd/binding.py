@@ -92,6 +92,9 @@ class LayerIo(ctypes.Structure):
                 ("grads", _LayerGrads), ("denc", ctypes.c_void_p)]
 
 
+_IO_BYTES = ctypes.sizeof(LayerIo)
+
+
 class LayerGroup(ctypes.Structure):
     """Shape shared by the slices of a group (``slicegcn_layer_group``)."""
     _fields_ = [("desc", _LayerDesc), ("count", ctypes.c_int32), ("ldi", ctypes.c_int64), ("ldo", ctypes.c_int64),
@@ -478,11 +481,11 @@ def slicegcn_layers_bwd_workspace_bytes(g: Graph, w_in: int, w_out: int, need_dH
 
 def slicegcn_layers_fwd(g: Graph, group: LayerGroup, io, first: int, ws: torch.Tensor):
     """Layer forward for ``group.count`` slice models: entries first, first + 1, ... of the LayerIo array ``io``."""
-    _check(lib().slicegcn_layers_fwd(g.handle, ctypes.byref(group), ctypes.byref(io, first * ctypes.sizeof(LayerIo)), *_ws(ws), _stream()))
+    _check(lib().slicegcn_layers_fwd(g.handle, ctypes.byref(group), ctypes.byref(io, first * _IO_BYTES), *_ws(ws), _stream()))
 
 
 def slicegcn_layers_bwd(g: Graph, group: LayerGroup, io, first: int, ws: torch.Tensor):
-    _check(lib().slicegcn_layers_bwd(g.handle, ctypes.byref(group), ctypes.byref(io, first * ctypes.sizeof(LayerIo)), *_ws(ws), _stream()))
+    _check(lib().slicegcn_layers_bwd(g.handle, ctypes.byref(group), ctypes.byref(io, first * _IO_BYTES), *_ws(ws), _stream()))
 
 
 def slicegcn_concat(Hs, E, H: torch.Tensor):
@@ -529,13 +532,14 @@ def slicegcn_concat_bwd(dH: torch.Tensor, widths, dHs=None, dE=None, ws=None):
 
 def slicegcn_linear_fwd(X, W, b, Y, mask=None, act: int = ACT_NONE):
     """Y = act(X W + b); fills mask (n x ceil(w_out/32) int32) for ReLU."""
-    w_in, w_out = int(W.shape[0]), int(W.shape[1])
+    w_in, w_out = W.shape
     px, ldx = _mat(X, "X")
     py, ldy = _mat(Y, "Y")
-    if X.shape[1] != w_in or Y.shape[1] != w_out or X.shape[0] != Y.shape[0]:
+    n, cols = X.shape
+    if cols != w_in or Y.shape != (n, w_out):
         raise ValueError("X, W, Y shapes do not match")
     pm, ldm = _mat(mask, "mask", torch.int32) if mask is not None else (None, 0)
-    _check(lib().slicegcn_linear_fwd(px, ldx, X.shape[0], w_in, w_out, _vec(W, "W"), _vec(b, "b"), act, py, ldy, pm, ldm,
+    _check(lib().slicegcn_linear_fwd(px, ldx, n, w_in, w_out, _vec(W, "W"), _vec(b, "b"), act, py, ldy, pm, ldm,
                                      _stream()))
     return Y
 
@@ -551,12 +555,12 @@ def slicegcn_linear_bwd_full_workspace_bytes(n: int, w_in: int, w_out: int) -> i
 
 def slicegcn_linear_bwd(X, W, mask, dY, dX, dW, db, ws, act: int = ACT_NONE):
     """dX = (dY * mask) W^T, dW = X^T (dY * mask), db = colsum(dY * mask); None outputs are skipped."""
-    w_in, w_out = int(W.shape[0]), int(W.shape[1])
+    w_in, w_out = W.shape
     px, ldx = _mat(X, "X")
     pg, ldg = _mat(dY, "dY")
     pdx, lddx = _mat(dX, "dX") if dX is not None else (None, 0)
     pm, ldm = _mat(mask, "mask", torch.int32) if mask is not None else (None, 0)
-    if dW is not None and tuple(dW.shape) != (w_in, w_out):
+    if dW is not None and dW.shape != (w_in, w_out):
         raise ValueError("dW must be w_in x w_out")
     pws, nws = _ws(ws)
     _check(lib().slicegcn_linear_bwd(px, ldx, X.shape[0], w_in, w_out, _vec(W, "W"), act, pm, ldm, pg, ldg, pdx, lddx,
@@ -606,10 +610,11 @@ def slicegcn_softmax_ce(logits, labels, loss, dlogits, ws):
     """loss[0] = mean softmax cross-entropy over the rows; dlogits (or None) its gradient."""
     pl, ld = _mat(logits, "logits")
     pd, ldd = _mat(dlogits, "dlogits") if dlogits is not None else (None, 0)
-    if labels.shape != (logits.shape[0],):
+    n, classes = logits.shape
+    if labels.shape != (n,):
         raise ValueError("one label per row expected")
     pws, nws = _ws(ws)
-    _check(lib().slicegcn_softmax_ce(pl, ld, logits.shape[0], logits.shape[1], _vec(labels, "labels", torch.int32),
+    _check(lib().slicegcn_softmax_ce(pl, ld, n, classes, _vec(labels, "labels", torch.int32),
                                      _vec(loss, "loss"), pd, ldd, pws, nws, _stream()))
     return loss
 

@@ -31,19 +31,22 @@ except ImportError:
 
 class TensorLayouts:
     """Whether a list of tensors (or None) still is the memory, types, devices, shapes and strides of the list it was made
-    from.  55 tensors: 14 us; with tuples of these attributes (TensorGuards = None) 30, a quarter of a pass over 2048 nodes."""
+    from.  51 tensors: 11 us; with tuples of these attributes (TensorGuards = None) 30, a quarter of a pass over 2048 nodes."""
 
     NONE = torch.empty(0)  # stands where there is none
 
     def __init__(self, tensors=()):
-        tensors = self._filled(tensors)
+        self.gaps = any(t is None for t in tensors)
+        if self.gaps:
+            tensors = self._filled(tensors)
         self.ptrs = list(map(torch.Tensor.data_ptr, tensors))
-        first = {}  # TensorGuards takes no tensor twice (slices may share their input or weights)
-        self.twins = [(i, first[id(t)]) for i, t in enumerate(tensors) if first.setdefault(id(t), i) != i]
-        self.unique = sorted(first.values())
-        tensors = [tensors[i] for i in self.unique]
-        self.guards = TensorGuards and tensors and TensorGuards(*tensors, dynamic_dims_sizes=[list(t.shape) for t in tensors],
-                                                                dynamic_dims_strides=[list(t.stride()) for t in tensors])
+        self.twins = ()
+        if len(set(map(id, tensors))) < len(tensors):  # TensorGuards takes no tensor twice (slices may share inputs or weights)
+            first = {}
+            self.twins = [(i, first[id(t)]) for i, t in enumerate(tensors) if first.setdefault(id(t), i) != i]
+            self.unique = sorted(first.values())
+            tensors = [tensors[i] for i in self.unique]
+        self.guards = TensorGuards and tensors and TensorGuards(*tensors, dynamic_dims_sizes=None, dynamic_dims_strides=None)
         self.layouts = None if self.guards else self._layouts(tensors)
 
     @classmethod
@@ -55,8 +58,12 @@ class TensorLayouts:
         return [(t.dtype, t.device, t.shape, t.stride()) for t in tensors]
 
     def same(self, tensors) -> bool:
-        tensors = self._filled(tensors)
-        if list(map(torch.Tensor.data_ptr, tensors)) != self.ptrs:
+        if self.gaps:
+            tensors = self._filled(tensors)
+        try:
+            if list(map(torch.Tensor.data_ptr, tensors)) != self.ptrs:
+                return False
+        except TypeError:  # None, where there was none
             return False
         if self.twins:
             if any(tensors[i] is not tensors[j] for i, j in self.twins):
@@ -270,8 +277,9 @@ class SliceStack:
                 else:
                     ldgo = 0
                 lds = (ldi, ldo, ldz, mask_words, ldgo, ldgi)
-                shapes.append(B.LayerGroup(B._LayerDesc(wi, wo, 0, 0), 1, *lds))
                 terms.add((p["W_self"] is None, lds))
+                shapes.append(shapes[-1] if i > 0 and lds == before else B.LayerGroup(B._LayerDesc(wi, wo, 0, 0), 1, *lds))
+                before = lds
             self._io.append(io)
             self._shapes.append(shapes)
             self._alike = self._alike and len(terms) == 1  # slices of other leading dimensions or terms share no launch
@@ -279,8 +287,8 @@ class SliceStack:
 
     def _group(self, l: int, first: int, count: int, flags: int = 0) -> B.LayerGroup:
         sh = self._shapes[l][first]
-        sh.count = count
-        sh.desc.act, sh.desc.flags = self.act(l), self.order | self.layout[l] | flags
+        sh.count, desc = count, sh.desc
+        desc.act, desc.flags = self.act(l), self.order | self.layout[l] | flags
         return sh
 
     def _forward_group(self, first: int, count: int, ws):
