@@ -5,6 +5,8 @@ library calls; every arithmetic step is a kernel of ``libslicegcn.so``.
 """
 from __future__ import annotations
 
+from typing import NamedTuple
+
 import torch
 
 from . import binding as B
@@ -36,7 +38,7 @@ class TensorLayouts:
     NONE = torch.empty(0)  # stands where there is none
 
     def __init__(self, tensors=()):
-        self.gaps = any(t is None for t in tensors)
+        self.gaps = type(None) in map(type, tensors)
         if self.gaps:
             tensors = self._filled(tensors)
         self.ptrs = list(map(torch.Tensor.data_ptr, tensors))
@@ -70,6 +72,15 @@ class TensorLayouts:
                 return False
             tensors = [tensors[i] for i in self.unique]
         return self.guards.check(*tensors) if self.guards else self._layouts(tensors) == self.layouts
+
+
+class LayerPlan(NamedTuple):
+    """Argument blocks of one direction of a pass, and what they were laid out for."""
+    ios: list      # per layer: LayerIo of every slice
+    shapes: list   # per layer: LayerGroup of every slice
+    alike: bool    # all slices fit one group
+    fused: bool    # the encoding rides on the last layer
+    layouts: TensorLayouts
 
 
 class SliceStack:
@@ -162,7 +173,7 @@ class SliceStack:
         ws = max(ws, B.slicegcn_concat_bwd_workspace_bytes(n_nodes, [slice_hidden] * k))
         self.ws_lane = [torch.empty(ws, dtype=torch.uint8, device=self.dev) for _ in range(self.lanes)]
         self.ws = self.ws_lane[0]
-        self._laid_out, self._fused = TensorLayouts(), None
+        self._plans = [None, None]  # forward, backward
 
     # ---------------------------------------------------------------------------------
     def set_params(self, i: int, l: int, W_agg, b, W_self, b_self):
@@ -208,9 +219,6 @@ class SliceStack:
             return self.Hcat[:, i * self.hs:(i + 1) * self.hs]
         return self.H[i][l][:, :self.hs]
 
-    def zbuf(self, i: int, l: int):
-        return None if self.tf[l] else self.Z[i][l][:, :self.widths[l][0]]
-
     def input_gradient(self, i: int) -> torch.Tensor:
         """Where slice i's gradient of a shared input goes."""
         return self.dXin if i == 0 else self.dXs[i % self.together - (i < self.together)]
@@ -225,100 +233,116 @@ class SliceStack:
                                           self.params[i][last]["b_self"] is not None for i in range(self.k))
 
     # ---- call arguments of every layer, laid out once ---------------------------------
-    def _tensors(self):
-        out = [*self.X, self.Hcat, self.E, self.dE]
-        if self.shared:
-            out += (self.dXin, *self.dXs)
-        for pair in self.dbuf:
-            out += pair
+    def _tensors(self, back: bool):
+        """The tensors one direction of a pass hands to the layers, in a fixed order."""
+        out = [*self.X]
+        if back:
+            out.append(self.dE)
+            if self.shared:
+                out += (self.dXin, *self.dXs)
+            for pair in self.dbuf:
+                out += pair
+        else:
+            out += (self.Hcat, self.E)
         for i in range(self.k):
             out += self.H[i]
             out += self.Z[i]
             out += self.mask[i]
-            for p, gr in zip(self.params[i], self.grads[i]):
-                out += (p["W_agg"], p["b"], p["W_self"], p["b_self"], gr["dW_agg"], gr["db"], gr["dW_self"], gr["db_self"])
+            for l, p in enumerate(self.params[i]):
+                if p is None:  # not set yet
+                    out.append(None)
+                elif back:
+                    gr = self.grads[i][l]
+                    out += (p["W_agg"], p["W_self"], gr["dW_agg"], gr["db"], gr["dW_self"], gr["db_self"])
+                else:
+                    out += (p["W_agg"], p["b"], p["W_self"], p["b_self"])
         return out
 
-    def _plan(self, fused: bool):
-        """Brings the argument blocks up to date: they are laid out again, with every check, when a tensor of the stack is
-        no longer what it was (parameters are rebound when an optimiser takes them over) or the encoding changed its place.
-        The activation and the flags of a layer are put in by each call."""
-        tensors = self._tensors()
-        if fused == self._fused and self._laid_out.same(tensors):
-            return
-        self._laid_out = TensorLayouts()
-        self._io, self._shapes, self._alike = [], [], True
+    def _plan(self, back: bool, fused: bool) -> LayerPlan:
+        """The argument blocks of one direction.  They are laid out again, with every check, when a tensor they are made from
+        is no longer what it was (parameters are rebound when an optimiser takes them over) or the encoding changed its place;
+        the activation and the flags of a layer are put in by each call."""
+        tensors, plan = self._tensors(back), self._plans[back]
+        if plan is not None and fused == plan.fused and plan.layouts.same(tensors):
+            return plan
+        self._plans[back] = None
+        ios, shapes, alike = [], [], True
         for l, (wi, wo) in enumerate(self.widths):
             last = l == self.L - 1
-            io = (B.LayerIo * self.k)()
-            shapes, terms = [], set()
+            io, of_layer, kinds = (B.LayerIo * self.k)(), [], set()
             for i in range(self.k):
-                p, gr, x = self.params[i][l], self.grads[i][l], io[i]
+                p, x = self.params[i][l], io[i]
+                if p is None:  # the call refuses it
+                    of_layer.append(B.LayerGroup(B._LayerDesc(wi, wo, 0, 0), 1, 0, 0, 0, 0, 0, 0))
+                    kinds.add(None)
+                    continue
                 for name, W in (("W_agg", p["W_agg"]), ("W_self", p["W_self"])):
                     if W is not None and tuple(W.shape) != (wi, wo):
                         raise ValueError(f"{name} must be w_in x w_out")
-                x.params = B._LayerParams(*(B._vec(p[n], n) for n in ("W_agg", "b", "W_self", "b_self")))
-                x.grads = B._LayerGrads(*(B._vec(gr[n], n) for n in ("dW_agg", "db", "dW_self", "db_self")))
-                x.Hin, ldi = B._mat(self.hin(i, l), "Hin")
-                x.Hout, ldo = B._mat(self.hout(i, l), "Hout")
-                x.Z, ldz = B._mat(self.zbuf(i, l), "Z") if self.Z[i][l] is not None else (None, 0)
+                x.Hin, ldi = B._mat(self.hin(i, 0) if l == 0 else self.H[i][l - 1], "Hin")
+                x.Z, ldz = B._mat(self.Z[i][l], "Z") if self.Z[i][l] is not None else (None, 0)
                 x.mask, mask_words = B._mat(self.mask[i][l], "mask", torch.int32)
-                if fused and last:
-                    x.enc, x.denc = B._vec(self.E[i], "E"), B._vec(self.dE[i], "dE")
-                slot = i % len(self.dbuf)
-                if l > 0:
-                    x.dHin, ldgi = B._mat(self.dbuf[slot][l % 2], "dHin")
-                elif self.shared:
-                    x.dHin, ldgi = B._mat(self.input_gradient(i), "dHin")
-                else:  # raw features need no gradient
-                    x.dHin, ldgi = None, 0
-                if not last:
-                    x.dHout, ldgo = B._mat(self.dbuf[slot][(l + 1) % 2], "dHout")
+                ldo = ldgo = ldgi = 0
+                if not back:
+                    x.params = B._LayerParams(*(B._vec(p[n], n) for n in ("W_agg", "b", "W_self", "b_self")))
+                    x.Hout, ldo = B._mat(self.hout(i, l) if last else self.H[i][l], "Hout")
+                    if fused and last:
+                        x.enc = B._vec(self.E[i], "E")
                 else:
-                    ldgo = 0
-                lds = (ldi, ldo, ldz, mask_words, ldgo, ldgi)
-                terms.add((p["W_self"] is None, lds))
-                shapes.append(shapes[-1] if i > 0 and lds == before else B.LayerGroup(B._LayerDesc(wi, wo, 0, 0), 1, *lds))
-                before = lds
-            self._io.append(io)
-            self._shapes.append(shapes)
-            self._alike = self._alike and len(terms) == 1  # slices of other leading dimensions or terms share no launch
-        self._laid_out, self._fused = TensorLayouts(tensors), fused
+                    gr, slot = self.grads[i][l], i % len(self.dbuf)
+                    x.params = B._LayerParams(B._vec(p["W_agg"], "W_agg"), None, B._vec(p["W_self"], "W_self"), None)
+                    x.grads = B._LayerGrads(*(B._vec(gr[n], n) for n in ("dW_agg", "db", "dW_self", "db_self")))
+                    if l > 0:
+                        x.dHin, ldgi = B._mat(self.dbuf[slot][l % 2], "dHin")
+                    elif self.shared:  # raw features need no gradient
+                        x.dHin, ldgi = B._mat(self.input_gradient(i), "dHin")
+                    if not last:  # the last layer's comes with the call
+                        x.dHout, ldgo = B._mat(self.dbuf[slot][(l + 1) % 2], "dHout")
+                    if fused and last:
+                        x.denc = B._vec(self.dE[i], "dE")
+                kind = (p["W_self"] is None, ldi, ldo, ldz, mask_words, ldgo, ldgi)
+                of_layer.append(of_layer[-1] if i > 0 and kind == before else B.LayerGroup(B._LayerDesc(wi, wo, 0, 0), 1, *kind[1:]))
+                before = kind
+                kinds.add(kind)
+            ios.append(io)
+            shapes.append(of_layer)
+            alike = alike and len(kinds) == 1  # slices of other leading dimensions or terms share no launch
+        plan = self._plans[back] = LayerPlan(ios, shapes, alike, fused, TensorLayouts(tensors))
+        return plan
 
-    def _group(self, l: int, first: int, count: int, flags: int = 0) -> B.LayerGroup:
-        sh = self._shapes[l][first]
+    def _shape(self, plan: LayerPlan, l: int, first: int, count: int, flags: int = 0) -> B.LayerGroup:
+        sh = plan.shapes[l][first]
         sh.count, desc = count, sh.desc
         desc.act, desc.flags = self.act(l), self.order | self.layout[l] | flags
         return sh
 
-    def _forward_group(self, first: int, count: int, ws):
+    def _forward_group(self, plan: LayerPlan, first: int, count: int, ws):
         cached = self.cache_first and all(self.first_valid[first:first + count])
         for l in range(self.L):
-            sh = self._group(l, first, count, B.LAYER_Z_VALID if cached and l == 0 else 0)
-            B.slicegcn_layers_fwd(self.g, sh, self._io[l], first, ws)
+            sh = self._shape(plan, l, first, count, B.LAYER_Z_VALID if cached and l == 0 else 0)
+            B.slicegcn_layers_fwd(self.g, sh, plan.ios[l], first, ws)
         self.first_valid[first:first + count] = [True] * count
 
     def forward_slice(self, i: int):
         if not self.inputs_prepared:
             self.prepare_inputs()
-        self._plan(self.encoding_fused())
-        self._forward_group(i, 1, self.ws_lane[i % self.lanes])
+        self._forward_group(self._plan(False, self.encoding_fused()), i, 1, self.ws_lane[i % self.lanes])
 
-    def _on_lanes(self, fn):
-        """fn(first slice, count, workspace) for every group of slices: in turn on the caller's stream, or slice i on lane
+    def _on_lanes(self, fn, plan: LayerPlan):
+        """fn(plan, first slice, count, workspace) for every group of slices: in turn on the caller's stream, or slice i on lane
         i mod lanes, the lanes starting after what the caller's stream holds so far and the caller's stream going on after
         all of them."""
         if self.lanes == 1:
-            group = self.group if self._alike else 1
+            group = self.group if plan.alike else 1
             for i in range(0, self.k, group):
-                fn(i, min(group, self.k - i), self.ws)
+                fn(plan, i, min(group, self.k - i), self.ws)
             return
         main = torch.cuda.current_stream()
         for s in self.streams:
             s.wait_stream(main)
         for i in range(self.k):
             with torch.cuda.stream(self.streams[i % self.lanes]):
-                fn(i, 1, self.ws_lane[i % self.lanes])
+                fn(plan, i, 1, self.ws_lane[i % self.lanes])
         for s in self.streams:
             main.wait_stream(s)
 
@@ -326,8 +350,7 @@ class SliceStack:
         if not self.inputs_prepared:
             self.prepare_inputs()
         fused = self.encoding_fused()
-        self._plan(fused)
-        self._on_lanes(self._forward_group)
+        self._on_lanes(self._forward_group, self._plan(False, fused))
         # the last layer of every slice already stored into its column block: encode in place, unless that is done
         if not fused:
             B.slicegcn_concat([self.hout(i, self.L - 1) for i in range(self.k)], self.E, self.Hcat)
@@ -335,21 +358,21 @@ class SliceStack:
 
     def backward(self, dH: torch.Tensor):
         fused = self.encoding_fused()
-        self._plan(fused)
+        plan = self._plan(True, fused)
         if self.E is not None and not fused:
             B.slicegcn_concat_bwd(dH, [self.hs] * self.k, dE=self.dE, ws=self.ws)
         ptr, ld = B._mat(dH, "dH")
         for i in range(self.k):  # CONCAT backward is a column view
-            self._io[-1][i].dHout = ptr + 4 * i * self.hs
-            self._shapes[-1][i].ldgo = ld
+            plan.ios[-1][i].dHout = ptr + 4 * i * self.hs
+            plan.shapes[-1][i].ldgo = ld
 
-        def backward_group(first: int, count: int, ws):
+        def backward_group(plan: LayerPlan, first: int, count: int, ws):
             for l in reversed(range(self.L)):
-                B.slicegcn_layers_bwd(self.g, self._group(l, first, count), self._io[l], first, ws)
+                B.slicegcn_layers_bwd(self.g, self._shape(plan, l, first, count), plan.ios[l], first, ws)
             if self.lanes == 1:
                 self._add_input_gradients(first, count)
 
-        self._on_lanes(backward_group)
+        self._on_lanes(backward_group, plan)
         if self.lanes > 1:
             for i in range(0, self.k, B.MAX_GROUP):
                 self._add_input_gradients(i, min(B.MAX_GROUP, self.k - i))
