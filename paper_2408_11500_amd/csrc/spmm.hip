@@ -27,7 +27,7 @@
 // anywhere: a contiguous 25-wide matrix takes the same kernels as a padded one.  Where the last vector of a row
 // would reach past the row, its lane loads the row's last four columns instead and shifts its sums into place
 // before they are stored, so nothing outside the operand is read.  (One float per lane on the single-class
-// schedule, which such operands took before: 93 us per call for 1.6 M entries of 25 columns; 39 us here.)
+// schedule, which such operands took before: 93 us per call for 1.6 M entries of 25 columns; 28 us here.)
 //
 // The partial sums of rows with several items live in a workspace the caller passes in (its size comes
 // from spmm_workspace_bytes), so a graph handle is read-only here and calls on different streams
@@ -117,11 +117,17 @@ template <> struct Acc<4> {
     __device__ void plus(const float4 &x) { v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w; }
     __device__ void scale(float a) { v.x *= a; v.y *= a; v.z *= a; v.w *= a; }
     __device__ void add(const Acc &o) { v.x += o.v.x; v.y += o.v.y; v.z += o.v.z; v.w += o.v.w; }
-    __device__ void shift(int s) // drop the first s columns (what moves in from the end is never stored)
+    // drop the first s columns (what moves in from the end is never stored).  In two steps of fixed distance: written as one choice per
+    // column the compiler made it an array indexed by s, moved that to LDS, and read the workgroup's size for its address from the
+    // dispatch packet, which lies in host memory: every wavefront began with a read across the bus (100 003 nodes, 1.6 M entries,
+    // 25 columns: 4 392 workgroups that return at once took 16.9 us with that read, 2.8 us without).
+    __device__ void shift(int s)
     {
-        v.x = s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w;
-        v.y = s == 0 ? v.y : s == 1 ? v.z : v.w;
-        v.z = s == 0 ? v.z : v.w;
+        const bool one = s & 1, two = s & 2;
+        const float x = one ? v.y : v.x, y = one ? v.z : v.y, z = one ? v.w : v.z;
+        v.x = two ? z : x;
+        v.y = two ? v.w : y;
+        v.z = z;
     }
     __device__ float get(int i) const { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 };
