@@ -7,9 +7,8 @@
 //     so one wavefront keeps many independent row gathers in flight and the output stream stays
 //     contiguous;
 //   * lane-group items (whole rows of up to item_max entries, short class pieces of partitioned
-//     rows): one item per lane group at a time, its (column, value) pairs read LPR at a time by the
-//     group's lanes and handed out by cross-lane reads, the next item's pairs requested before the
-//     current item's gathers;
+//     rows): one item per lane group, its (column, value) pairs read LPR at a time by the
+//     group's lanes and handed out by cross-lane reads;
 //   * wavefront items (everything longer, cut at SEG_NNZ entries): the wavefront loads 64
 //     (column, value) pairs per coalesced read, the 64/LPR lane groups take them in turn through
 //     cross-lane reads with eight gathers in flight per lane, and the groups' sums are combined
@@ -55,7 +54,7 @@ struct SpmmArgs {
     int32_t n;
     int32_t item_max;     // longest lane-group item of the schedule (ITEM_SHORT or ITEM_LONG)
     int32_t ipw;          // wavefront items per wavefront (1 to 4 in the one-launch kernel, otherwise 1); a workgroup takes 4 * ipw
-    int32_t rounds;       // lane-group items per lane group (1 to 8)
+    int32_t deal;         // log2 of the chunks of lane-group whole rows a class takes in turn
     int32_t tiny_rounds;  // short rows per lane group (2, 4, 6 or 8)
     int32_t big_blocks;   // workgroups per class in the wavefront-item section
     int32_t small_blocks; // workgroups per class in the lane-group-item section
@@ -279,6 +278,16 @@ __device__ inline void store_result(Acc<V> acc, const SpmmArgs &a, const SpmmIo 
 }
 
 constexpr int NO_UNIT = INT32_MIN;
+
+// Which chunk of the whole-row lane-group items the q-th workgroup of class c takes: 2^deal consecutive chunks per class in
+// turn, so that with a row order that puts rows with common neighbours side by side (breadth first) an XCD works on a
+// stretch of some thousand rows at a time and their gathers meet in its L2, while every class still gets its share of
+// each part of the list.  2^deal = 1 / 8 / 16 / 32 / 64 / 512, 2 M nodes in communities in breadth-first order, 32 columns:
+// 1.29 / 1.11 / 1.09 / 1.08 / 1.08 / 1.09 ms (64 columns 2.53 / 2.17 / 2.15 / 2.14 / 2.14 / 2.17); R-MAT and uniform
+// random graphs of 0.3 to 2.4 M nodes, any order: no difference above 1 %.  Shorter lists are dealt in smaller stretches,
+// eight turns per class or single chunks, so that no class runs dry.
+constexpr int MAX_DEAL = 5;
+__device__ inline int64_t dealt(int q, int c, int deal) { return ((((int64_t)(q >> deal) * N_CLASSES + c) << deal) + (q & ((1 << deal) - 1))); }
 constexpr int64_t SMALL_GRID = 1024; // workgroups of one kind a cache-resident graph is cut into before runs grow
 
 // One gather phase of the tiny-row path: sub-round t hands unit (t * GROUPS + grp) of the wavefront
@@ -465,50 +474,40 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, const Spm
 }
 
 // Lane-group items (whole rows and class pieces of 5..GI_MAX entries, GI_MAX = the schedule's item_max):
-// workgroup b serves class b mod 8 and takes a run of 4 * G * rounds consecutive items of its list (first the
-// class's own pieces, then every eighth run of the whole rows).  In round r its four wavefronts work on
-// 4 * G consecutive items of the run, lane group grp of wavefront w on item r * 4 * G + w * G + grp (lane
-// r * G + grp holds that item's descriptor).  The group
-// reads the item's (column, value) pairs with one read per LPR entries (lane `sub` holds entries
-// sub, sub + LPR, ...; the next round's pairs are requested before this round's gathers), and each
-// gather takes its pair from the holding lane by a cross-lane read, eight gathers in flight.
+// workgroup b serves class b mod 8 and takes 4 * G consecutive items of its list (first the class's own pieces, then its
+// share of the whole rows), lane group grp of wavefront w the item w * G + grp of them.  The group reads the item's
+// (column, value) pairs with one read per LPR entries (lane `sub` holds entries sub, sub + LPR, ...), and each gather takes
+// its pair from the holding lane by a cross-lane read, eight gathers in flight.
+// One item per lane group, not a run of several: what is in flight together on an XCD is then a short stretch of rows
+// (with a row order its gathers meet in the L2), the last workgroups end together, and the registers that held the next
+// item's pairs are free.  Runs of 8 / 4 / 2 / 1 items per lane group: 6.3 M entries, 300 k nodes 70 / 64 / 63 / 63 us;
+// 41 M entries, 1 M nodes 0.422 / 0.410 / 0.406 / 0.404 ms; 126 M entries 1.246 / 1.237 / 1.232 / 1.229 ms; 2 M nodes in
+// communities, breadth-first order 1.55 / 1.53 / 1.42 / 1.29 ms (all 32 columns).
 template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG>
 __device__ __forceinline__ void group_items_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
-    constexpr int G = 64 / LPR;                 // items in flight per wavefront
+    constexpr int G = 64 / LPR;                 // items per wavefront
     constexpr int K = LPR >= GI_MAX ? 1 : GI_MAX / LPR; // index registers per lane (K * LPR >= GI_MAX entries)
     constexpr int U = 8;
+    constexpr int RUN = 4 * G;                  // items per workgroup
     using L = Ld<V>;
-    const int RUN = 4 * G * a.rounds;           // items per workgroup: one run of consecutive items of its list
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int cls = block % N_CLASSES, blk = block / N_CLASSES;
     const int piece_blocks = (a.small_cnt[cls] + RUN - 1) / RUN;
-    int64_t first, left;
-    if (blk < piece_blocks) { // uniform per workgroup
-        first = (int64_t)blk * RUN;
-        left = a.small_cnt[cls] - first;
-        first += a.small_off[cls];
-    } else {
-        first = ((int64_t)(blk - piece_blocks) * N_CLASSES + cls) * RUN;
-        left = a.wsmall_cnt - first;
-        first += a.wsmall_off;
-    }
-    const int run = left < RUN ? (int)left : RUN;
-    // Round r of the workgroup works on the 4 * G consecutive items [r * 4 * G, (r + 1) * 4 * G) of its run, wavefront w
-    // on the G of them from w * G on: what is in flight together on a CU is a window of consecutive rows, so with a row
-    // order that puts rows with common neighbours side by side their gathers meet in the caches while the rows are live.
-    if (run <= wave * G) return; // uniform per wavefront
-    const int rounds = (run - wave * G + 4 * G - 1) / (4 * G);
-    int4 d = make_int4(0, 0, 0, NO_UNIT);
-    {
-        const int q = (lane / G) * (4 * G) + wave * G + lane % G; // lane r * G + g holds the descriptor of round r, group g
-        if (lane < 8 * G && q < run) d = *reinterpret_cast<const int4 *>(a.items + first + q);
-    }
     const int grp = lane / LPR, sub = lane % LPR, gbase = lane - sub;
+    int64_t item = wave * G + grp;
+    int4 d = make_int4(0, 0, 0, NO_UNIT);
+    if (blk < piece_blocks) { // uniform per workgroup
+        item += (int64_t)blk * RUN;
+        if (item < a.small_cnt[cls]) d = *reinterpret_cast<const int4 *>(a.items + a.small_off[cls] + item);
+    } else {
+        item += dealt(blk - piece_blocks, cls, a.deal) * RUN;
+        if (item < a.wsmall_cnt) d = *reinterpret_cast<const int4 *>(a.items + a.wsmall_off + item);
+    }
     const int col = io.col0 + sub * V;
     const bool col_ok = col < io.col_end;
     const int colc = load_col<RAG>(a, io, col);
-    int beg = __shfl(d.y, grp, 64), end = __shfl(d.z, grp, 64);
+    const int beg = d.y, end = d.z, len = end - beg;
     int c_k[K];
     float v_k[K];
 #pragma unroll
@@ -518,46 +517,27 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, const SpmmIo
         c_k[k] = ok ? a.colidx[e] : 0;
         v_k[k] = ok ? ld_val<FACT>(a, e) : 0.f;
     }
-    for (int r = 0; r < rounds; ++r) {
-        const int row = __shfl(d.x, r * G + grp, 64), dst = __shfl(d.w, r * G + grp, 64);
-        const int len = end - beg;
-        const int nsrc = (r + 1 < rounds ? (r + 1) * G : 0) + grp;
-        const int nbeg = __shfl(d.y, nsrc, 64), nend = r + 1 < rounds ? __shfl(d.z, nsrc, 64) : nbeg;
-        int c_n[K];
-        float v_n[K];
+    Acc<V> acc;
 #pragma unroll
-        for (int k = 0; k < K; ++k) { // the next round's pairs (none after the last round: nend == nbeg)
-            const int e = nbeg + sub + LPR * k;
-            const bool ok = e < nend;
-            c_n[k] = ok ? a.colidx[e] : 0;
-            v_n[k] = ok ? ld_val<FACT>(a, e) : 0.f;
+    for (int j0 = 0; j0 < GI_MAX; j0 += U) {
+        if (!__any(j0 < len)) break; // wavefront-uniform
+        int c[U];
+        float v[U];
+        typename L::T x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int jj = j0 + u;
+            const int cc = __shfl(c_k[jj / LPR < K ? jj / LPR : 0], gbase + jj % LPR, 64);
+            v[u] = shfl_val<FACT>(v_k[jj / LPR < K ? jj / LPR : 0], gbase + jj % LPR);
+            c[u] = jj < len ? cc : 0; // an absent entry re-reads row 0 and is not accumulated
         }
-        Acc<V> acc;
 #pragma unroll
-        for (int j0 = 0; j0 < GI_MAX; j0 += U) {
-            if (!__any(j0 < len)) break; // wavefront-uniform
-            int c[U];
-            float v[U];
-            typename L::T x[U];
+        for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], colc);
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int jj = j0 + u;
-                const int cc = __shfl(c_k[jj / LPR < K ? jj / LPR : 0], gbase + jj % LPR, 64);
-                v[u] = shfl_val<FACT>(v_k[jj / LPR < K ? jj / LPR : 0], gbase + jj % LPR);
-                c[u] = jj < len ? cc : 0; // an absent entry re-reads row 0 and is not accumulated
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], colc);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (j0 + u < len) acc.fma(v[u], x[u]);
-        }
-        if (dst != NO_UNIT && col_ok) store_result<V, RAG>(acc, a, io, row, dst, col);
-        beg = nbeg;
-        end = nend;
-#pragma unroll
-        for (int k = 0; k < K; ++k) { c_k[k] = c_n[k]; v_k[k] = v_n[k]; }
+        for (int u = 0; u < U; ++u)
+            if (j0 + u < len) acc.fma(v[u], x[u]);
     }
+    if (d.w != NO_UNIT && col_ok) store_result<V, RAG>(acc, a, io, d.x, d.w, col);
 }
 
 // Rows of at most TINY_ROW entries, up to 64 consecutive positions of the schedule per wavefront (consecutive
@@ -767,15 +747,18 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, 
             return (int)(t < 1 ? 1 : t > most ? most : t);
         };
         a.ipw = resident ? turns(sc.wbig_cnt, 4, 4) : 1;
-        a.rounds = resident ? turns(sc.wsmall_cnt, groups, 8) : 8;
         a.tiny_rounds = resident ? 2 * turns(g->n, 2 * groups, 4) : 8;
         // workgroups per class: the class's own pieces, then its share of the whole-row chunks
-        const int64_t ipb = 4 * a.ipw, run = groups * a.rounds;
-        const int64_t wbig_chunks = ((int64_t)sc.wbig_cnt + ipb - 1) / ipb, wsmall_runs = ((int64_t)sc.wsmall_cnt + run - 1) / run;
+        const int64_t ipb = 4 * a.ipw;
+        const int64_t wbig_chunks = ((int64_t)sc.wbig_cnt + ipb - 1) / ipb;
+        const int64_t wsmall_chunks = ((int64_t)sc.wsmall_cnt + groups - 1) / groups;
+        a.deal = 0;
+        while (a.deal < MAX_DEAL && (wsmall_chunks >> (a.deal + 1)) >= 8 * N_CLASSES) ++a.deal;
+        const int64_t wsmall_blocks = round_up(wsmall_chunks, N_CLASSES << a.deal) / N_CLASSES;
         int64_t big_blocks = 0, small_blocks = 0;
         for (int c = 0; c < N_CLASSES; ++c) {
             const int64_t x = (sc.big_cnt[c] + ipb - 1) / ipb + (wbig_chunks + N_CLASSES - 1 - c) / N_CLASSES;
-            const int64_t y = (sc.small_cnt[c] + run - 1) / run + (wsmall_runs + N_CLASSES - 1 - c) / N_CLASSES;
+            const int64_t y = (sc.small_cnt[c] + groups - 1) / groups + wsmall_blocks;
             big_blocks = x > big_blocks ? x : big_blocks;
             small_blocks = y > small_blocks ? y : small_blocks;
         }
