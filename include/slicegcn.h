@@ -172,8 +172,8 @@ int slicegcn_slice_strategy(int32_t in_d, int32_t p, double slice_size_scale,
  * On success *out holds a new handle (free it with slicegcn_graph_destroy).  Allocates device
  * memory (the handle's arrays plus temporaries of a few times the edge list, freed before it
  * returns) and synchronises `stream` several times: it runs once per graph, not per epoch.
- * Sorting, duplicate removal and prefix sums are rocPRIM device primitives; the kernels around
- * them are this library's.  rowptr/colidx/deg are exact integers; dinv/vals are fp32 and always
+ * Prefix sums, and the sorts of a row order, are rocPRIM device primitives; everything else is
+ * this library's.  rowptr/colidx/deg are exact integers; dinv/vals are fp32 and always
  * kept (there is no flag to drop vals: every aggregation path reads them).
  * EINVAL: NULL out, n_nodes < 1, n_edges < 0, NULL src/dst with n_edges > 0, unknown flag, both
  *         REORDER flags or both SCHED flags.

@@ -3,12 +3,7 @@
 // aggregation kernels use.  Integer work only, apart from one rsqrt per node and one multiply
 // per stored entry.
 //
-//   keys      one key (row, col) per candidate entry, packed into as many bits as the node count needs
-//             (32-bit keys up to 65 535 nodes): the fewer bits, the fewer passes of the radix sort;
-//   sort      rocPRIM radix sort of the keys;
-//   compact   a wavefront takes 1024 consecutive keys in rounds of 64: repeats and the sentinel drop out by
-//             ballot, column and row of an entry and the row pointers are written in the same sweep
-//             (126 M keys: 0.7 ms for its two sweeps where unique, row pointers and entries took 4.1 ms);
+//   entries   edge_sort.hip: edges distributed to buckets of rows, sorted there in registers, repeats dropped, rows counted;
 //   schedule  rows sorted into the item lists by ballot as well; only rows that are cut by column class
 //             need per-row tables.
 //
@@ -32,128 +27,6 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + TPB - 1) / TPB); 
 
 // Device words the host reads back: [0] out-of-range edges, [1] stored entries, [2] ... the schedule's and the row order's.
 constexpr int N_COUNTERS = 64;
-
-// ---- keys -------------------------------------------------------------------------------
-// Key (row, col) = row << col_bits | col.  Out-of-range pairs, and self pairs, become the sentinel (row n), which
-// sorts behind every real row and is dropped later.
-template <class K>
-__global__ void make_keys_kernel(const int64_t *__restrict__ src, const int64_t *__restrict__ dst,
-                                 int64_t n_edges, int64_t n, int col_bits, int sym, int loops,
-                                 K *__restrict__ keys, int *__restrict__ n_bad)
-{
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    const K sentinel = (K)n << col_bits;
-    if (i < n_edges) {
-        const int64_t u = src[i], v = dst[i];
-        K k1 = sentinel, k2 = sentinel;
-        if (u < 0 || u >= n || v < 0 || v >= n) {
-            atomicAdd(n_bad, 1);
-        } else if (u != v) {
-            k1 = ((K)u << col_bits) | (K)v;
-            k2 = ((K)v << col_bits) | (K)u;
-        }
-        keys[i] = k1;
-        if (sym) keys[n_edges + i] = k2;
-    } else if (loops && i < n_edges + n) {
-        const K v = (K)(i - n_edges);
-        keys[(sym ? 2 : 1) * n_edges + (i - n_edges)] = (v << col_bits) | v;
-    }
-}
-
-template <class K>
-__global__ void swapped_keys_kernel(const int32_t *__restrict__ row, const int32_t *__restrict__ col, int64_t nnz, int col_bits,
-                                    K *__restrict__ keys)
-{
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (i < nnz) keys[i] = ((K)col[i] << col_bits) | (K)row[i];
-}
-
-// ---- sorted keys -> CSR -----------------------------------------------------------------
-constexpr int CHUNK = 1024; // keys per wavefront
-inline int64_t chunks_of(int64_t n_keys) { return (n_keys + CHUNK - 1) / CHUNK; }
-
-// One sweep over the sorted keys: WRITE = false counts the distinct real keys of every chunk, WRITE = true writes
-// their entries from the scanned counts on and, where no row is empty (rowptr != NULL: the diagonal is stored), the
-// row pointers, from the first key of every row.
-template <class K, bool WRITE>
-__global__ __launch_bounds__(256) void compact_kernel(const K *__restrict__ keys, int64_t n_keys, int64_t n, int col_bits,
-                                                      int32_t *__restrict__ chunk, int32_t *__restrict__ colidx,
-                                                      int32_t *__restrict__ rowid, int32_t *__restrict__ rowptr)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t first = c * CHUNK;
-    if (first >= n_keys) return; // uniform per wavefront
-    const K col_mask = ((K)1 << col_bits) - 1;
-    int32_t pos = WRITE ? chunk[c] : 0;
-    K last = first > 0 ? keys[first - 1] : (K)0; // the key before this round's first
-    bool has_last = first > 0;
-#pragma unroll 4
-    for (int r = 0; r < CHUNK / 64; ++r) {
-        const int64_t i = first + r * 64 + lane;
-        const bool in = i < n_keys;
-        const K k = in ? keys[i] : (K)0;
-        K prev = __shfl_up(k, 1, 64);
-        if (lane == 0) prev = last;
-        const bool has_prev = lane > 0 || has_last;
-        const int64_t row = (int64_t)(k >> col_bits);
-        const bool keep = in && row < n && (!has_prev || k != prev);
-        const unsigned long long bits = __ballot(keep);
-        if (WRITE) {
-            const int32_t at = pos + __popcll(bits & ((1ull << lane) - 1ull));
-            if (keep) {
-                colidx[at] = (int32_t)(k & col_mask);
-                rowid[at] = (int32_t)row;
-            }
-            if (rowptr) {
-                if (keep && (!has_prev || (int64_t)(prev >> col_bits) != row)) rowptr[row] = at;
-                if (i == n_keys - 1) rowptr[n] = at + (keep ? 1 : 0);
-            }
-        }
-        pos += __popcll(bits);
-        last = __shfl(k, 63, 64);
-        has_last = true;
-    }
-    if (!WRITE && lane == 0) chunk[c] = pos;
-}
-
-// rowptr[r] = entries of the rows before r = lower bound of r in the entries' rows (patterns with empty rows)
-__global__ void rowptr_kernel(const int32_t *__restrict__ rowid, int64_t nnz, int64_t n, int32_t *__restrict__ rowptr)
-{
-    const int64_t r = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (r > n) return;
-    int64_t lo = 0, hi = nnz;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (rowid[mid] < r) lo = mid + 1; else hi = mid;
-    }
-    rowptr[r] = (int32_t)lo;
-}
-
-__global__ void degree_kernel(const int32_t *__restrict__ rowptr, int64_t n,
-                              int32_t *__restrict__ deg, float *__restrict__ dinv, float *__restrict__ sqrtd)
-{
-    const int64_t v = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (v >= n) return;
-    const int32_t d = rowptr[v + 1] - rowptr[v];
-    deg[v] = d;
-    dinv[v] = (float)(1.0 / sqrt((double)(d > 0 ? d : 1)));
-    sqrtd[v] = (float)sqrt((double)(d > 0 ? d : 1));
-}
-
-// Four entries per thread (the arrays come 16-byte aligned): bound by the gather of dinv[col].
-__global__ void vals_kernel(const int32_t *__restrict__ rowid, const int32_t *__restrict__ colidx, int64_t nnz,
-                            const float *__restrict__ dinv, float *__restrict__ vals)
-{
-    const int64_t i = ((int64_t)blockIdx.x * TPB + threadIdx.x) * 4;
-    if (i + 4 <= nnz) {
-        const int4 r = *reinterpret_cast<const int4 *>(rowid + i), c = *reinterpret_cast<const int4 *>(colidx + i);
-        *reinterpret_cast<float4 *>(vals + i) =
-            make_float4(dinv[r.x] * dinv[c.x], dinv[r.y] * dinv[c.y], dinv[r.z] * dinv[c.z], dinv[r.w] * dinv[c.w]);
-    } else {
-        for (int64_t j = i; j < nnz; ++j) vals[j] = dinv[rowid[j]] * dinv[colidx[j]];
-    }
-}
 
 // ---- schedule ---------------------------------------------------------------------------
 // Column class c holds the columns [first[c], first[c+1]); the boundaries are the eighth-quantiles of the stored
@@ -246,60 +119,62 @@ constexpr int T_SLOT = 2 * N_CLASSES, T_FIX = T_SLOT + 1, N_TABLES = T_FIX + 1;
 
 __device__ inline int pieces_of(int32_t len) { return (len + SEG_NNZ - 1) / SEG_NNZ; }
 
-// The pieces of one long row, in (class, piece) order: f(table, beg, end).  Per row: the entries of column class c are
-// [lower_bound(first[c]), lower_bound(first[c+1])).  Returns how many.
-template <class F>
-__device__ inline int for_each_piece(const int32_t *__restrict__ colidx, int32_t beg, int32_t end, const ClassBounds &cb, int32_t item_max, F f)
+// The entries of the classes of long row i, one lane per class (eight lanes per row): [beg, end) of this lane's class.  Per row: the entries
+// of column class c are [lower_bound(first[c]), lower_bound(first[c+1])); every lane searches its own start and takes its end from the
+// next lane.  The searches read most lines of a row (126 M entries, 98 k long rows: 80 us), so they are done once and the starts kept in
+// class_beg for the second kernel.
+struct ClassPiece { int32_t row, beg, end; };
+template <bool SEARCH>
+__device__ inline ClassPiece class_piece(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx, const int32_t *__restrict__ long_rows,
+                                         int64_t i, int64_t n_long, const ClassBounds &cb, int c, int32_t *__restrict__ class_beg)
 {
-    int total = 0;
-    int32_t b = beg;
-    for (int c = 0; c < N_CLASSES; ++c) {
-        int32_t e = end;
-        if (c + 1 < N_CLASSES) {
-            const int32_t target = cb.first[c + 1];
-            int32_t lo = b;
-            while (lo < e) {
-                const int32_t mid = lo + ((e - lo) >> 1);
-                if (colidx[mid] < target) lo = mid + 1; else e = mid;
-            }
-        }
-        const int32_t len = e - b;
-        if (len > 0 && len <= item_max) {
-            f(2 * c + 1, b, e);
-            ++total;
-        } else if (len > 0) {
-            const int s = pieces_of(len);
-            const int32_t piece = (len + s - 1) / s; // equal cuts, the last one takes the remainder
-            for (int j = 0; j < s; ++j) f(2 * c, b + j * piece, min(e, b + (j + 1) * piece));
-            total += s;
-        }
-        b = e;
-    }
-    return total;
-}
-
-__global__ void long_count_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
-                                  const int32_t *__restrict__ long_rows, int64_t n_long, const ClassBounds *__restrict__ cb,
-                                  int32_t item_max, int32_t *__restrict__ cnt)
-{
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (i > n_long) return;
-    const int64_t stride = n_long + 1;
-    int32_t per[2 * N_CLASSES];
-#pragma unroll
-    for (int t = 0; t < 2 * N_CLASSES; ++t) per[t] = 0;
-    int total = 0;
+    ClassPiece p{0, 0, 0};
     if (i < n_long) {
-        const int32_t r = long_rows[i];
-        total = for_each_piece(colidx, rowptr[r], rowptr[r + 1], *cb, item_max, [&](int t, int32_t, int32_t) {
-#pragma unroll
-            for (int q = 0; q < 2 * N_CLASSES; ++q) per[q] += q == t ? 1 : 0;
-        });
+        p.row = long_rows[i];
+        p.end = rowptr[p.row + 1];
+        if (SEARCH) {
+            p.beg = rowptr[p.row];
+            if (c > 0) {
+                int32_t hi = p.end;
+                const int32_t target = cb.first[c];
+                while (p.beg < hi) {
+                    const int32_t mid = p.beg + ((hi - p.beg) >> 1);
+                    if (colidx[mid] < target) p.beg = mid + 1; else hi = mid;
+                }
+            }
+            class_beg[i * N_CLASSES + c] = p.beg;
+        } else {
+            p.beg = class_beg[i * N_CLASSES + c];
+        }
     }
+    const int32_t next = __shfl_down(p.beg, 1, 64);
+    if (c + 1 < N_CLASSES) p.end = next;
+    return p;
+}
+// items of a class piece, and whether they are wavefront items
+__device__ inline int items_of(int32_t len, int32_t item_max) { return len <= 0 ? 0 : len <= item_max ? 1 : pieces_of(len); }
+constexpr int LONG_PER_BLOCK = TPB / N_CLASSES; // rows per workgroup
+
+__global__ __launch_bounds__(TPB) void long_count_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+                                                         const int32_t *__restrict__ long_rows, int64_t n_long, const ClassBounds *__restrict__ cb,
+                                                         int32_t item_max, int32_t *__restrict__ class_beg, int32_t *__restrict__ cnt)
+{
+    const int64_t i = (int64_t)blockIdx.x * LONG_PER_BLOCK + threadIdx.x / N_CLASSES;
+    const int c = threadIdx.x % N_CLASSES;
+    const ClassPiece p = class_piece<true>(rowptr, colidx, long_rows, i, n_long, *cb, c, class_beg);
+    const int mine = items_of(p.end - p.beg, item_max);
+    int total = mine;
 #pragma unroll
-    for (int t = 0; t < 2 * N_CLASSES; ++t) cnt[t * stride + i] = per[t];
-    cnt[T_SLOT * stride + i] = total > 1 ? total : 0;
-    cnt[T_FIX * stride + i] = total > 1 ? 1 : 0;
+    for (int s = 1; s < N_CLASSES; s <<= 1) total += __shfl_xor(total, s, 64);
+    if (i > n_long) return; // row n_long: the zeros the scan's totals come from
+    const int64_t stride = n_long + 1;
+    const bool wide = p.end - p.beg > item_max;
+    cnt[(2 * c) * stride + i] = wide ? mine : 0;
+    cnt[(2 * c + 1) * stride + i] = wide ? 0 : mine;
+    if (c == 0) {
+        cnt[T_SLOT * stride + i] = total > 1 ? total : 0;
+        cnt[T_FIX * stride + i] = total > 1 ? 1 : 0;
+    }
 }
 
 // starts[t] = first element of table t in the scan over all tables, starts[N_TABLES] = the total
@@ -310,31 +185,40 @@ __global__ void long_starts_kernel(const int32_t *__restrict__ off, const int32_
     if (t == N_TABLES) starts[t] = off[N_TABLES * stride - 1] + cnt[N_TABLES * stride - 1];
 }
 
-__global__ void long_fill_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
-                                 const int32_t *__restrict__ long_rows, int64_t n_long, const ClassBounds *__restrict__ cb,
-                                 int32_t item_max, const int32_t *__restrict__ off, Segment *__restrict__ items, FixRow *__restrict__ fix)
+// items of the long rows: slots are handed out in (class, piece) order, a table's pieces of a row are adjacent
+__global__ __launch_bounds__(TPB) void long_fill_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+                                                        const int32_t *__restrict__ long_rows, int64_t n_long, const ClassBounds *__restrict__ cb,
+                                                        int32_t item_max, int32_t *__restrict__ class_beg, const int32_t *__restrict__ off, Segment *__restrict__ items, FixRow *__restrict__ fix)
 {
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * LONG_PER_BLOCK + threadIdx.x / N_CLASSES;
+    const int c = threadIdx.x % N_CLASSES;
+    const ClassPiece p = class_piece<false>(rowptr, colidx, long_rows, i, n_long, *cb, c, class_beg);
+    const int32_t len = p.end - p.beg;
+    const int mine = items_of(len, item_max);
+    int before = mine; // items of this row up to this class
+#pragma unroll
+    for (int s = 1; s < N_CLASSES; s <<= 1) {
+        const int up = __shfl_up(before, s, N_CLASSES);
+        if (c >= s) before += up;
+    }
+    before -= mine;
     if (i >= n_long) return;
     const int64_t stride = n_long + 1;
-    const int32_t r = long_rows[i], beg = rowptr[r], end = rowptr[r + 1];
     const int32_t *slots = off + T_SLOT * stride, *fixes = off + T_FIX * stride;
     const int32_t slot0 = slots[i] - slots[0], n_slots = slots[i + 1] - slots[i];
-    int slot = slot0, last = -1, used = 0; // slots are handed out in (class, piece) order, a table's pieces are adjacent
-    for_each_piece(colidx, beg, end, *cb, item_max, [&](int t, int32_t b, int32_t e) {
-        used = t == last ? used + 1 : 0;
-        last = t;
+    const int table = len > item_max ? 2 * c : 2 * c + 1;
+    const int32_t piece = mine > 0 ? (len + mine - 1) / mine : 0; // equal cuts, the last one takes the remainder
+    for (int j = 0; j < mine; ++j) {
         Segment sg;
-        sg.row = r;
-        sg.beg = b;
-        sg.end = e;
-        sg.dst = n_slots == 0 ? r : -(slot + 1);
-        items[off[t * stride + i] + used] = sg;
-        ++slot;
-    });
-    if (n_slots > 0) {
+        sg.row = p.row;
+        sg.beg = p.beg + j * piece;
+        sg.end = min(p.end, p.beg + (j + 1) * piece);
+        sg.dst = n_slots == 0 ? p.row : -(slot0 + before + j + 1);
+        items[off[table * stride + i] + j] = sg;
+    }
+    if (n_slots > 0 && c == 0) {
         FixRow f;
-        f.row = r;
+        f.row = p.row;
         f.slot_beg = slot0;
         f.slot_end = slot0 + n_slots;
         f.pad = 0;
@@ -342,7 +226,8 @@ __global__ void long_fill_kernel(const int32_t *__restrict__ rowptr, const int32
     }
 }
 
-// ---- host side ---------------------------------------------------------------------------
+} // namespace
+
 int scan_i32(const int32_t *in, int32_t *out, int64_t count, Arena &ws, hipStream_t stream)
 {
     size_t bytes = 0;
@@ -361,47 +246,12 @@ size_t scan_bytes(int64_t count)
     return Arena::rounded(bytes);
 }
 
-template <class K>
-int sort_keys(const K *in, K *out, int64_t count, unsigned end_bit, Arena &ws, hipStream_t stream)
-{
-    size_t bytes = 0;
-    SG_HIP(rocprim::radix_sort_keys(nullptr, bytes, in, out, (size_t)count, 0u, end_bit, stream));
-    const size_t mark = ws.used;
-    void *tmp = nullptr;
-    if (int rc = ws.take(bytes, &tmp)) return rc;
-    SG_HIP(rocprim::radix_sort_keys(tmp, bytes, in, out, (size_t)count, 0u, end_bit, stream));
-    ws.used = mark;
-    return SLICEGCN_OK;
-}
-template <class K>
-size_t sort_bytes(int64_t count, unsigned end_bit)
-{
-    size_t bytes = 0;
-    (void)rocprim::radix_sort_keys(nullptr, bytes, (const K *)nullptr, (K *)nullptr, (size_t)count, 0u, end_bit, (hipStream_t)0);
-    return Arena::rounded(bytes);
-}
+namespace {
 
-inline unsigned bits_for(uint64_t v)
+// ---- host side ---------------------------------------------------------------------------
+int64_t candidates(int64_t n_edges, int64_t n, uint32_t flags) // entries the pattern can have
 {
-    unsigned b = 1;
-    while ((v >> b) != 0) ++b;
-    return b;
-}
-
-struct KeyPlan {
-    int64_t n_keys;
-    unsigned col_bits, row_bits; // columns 0 .. n - 1, rows 0 .. n (the sentinel)
-    bool narrow;                 // 32-bit keys
-    size_t key_bytes() const { return narrow ? 4 : 8; }
-};
-KeyPlan key_plan(int64_t n_edges, int64_t n, uint32_t flags)
-{
-    KeyPlan k;
-    k.n_keys = n_edges * ((flags & SLICEGCN_SYMMETRIZE) ? 2 : 1) + ((flags & SLICEGCN_ADD_SELF_LOOPS) ? n : 0);
-    k.col_bits = bits_for((uint64_t)(n - 1));
-    k.row_bits = bits_for((uint64_t)n);
-    k.narrow = k.col_bits + k.row_bits <= 32;
-    return k;
+    return n_edges * ((flags & SLICEGCN_SYMMETRIZE) ? 2 : 1) + ((flags & SLICEGCN_ADD_SELF_LOOPS) ? n : 0);
 }
 
 size_t sched_bytes(int64_t n, int64_t n_keys)
@@ -409,7 +259,7 @@ size_t sched_bytes(int64_t n, int64_t n_keys)
     const int64_t groups = 3 * (int64_t)blocks_for(n) + 1, n_long = n_keys / PART_ROW < n ? n_keys / PART_ROW : n;
     const int64_t tables = N_TABLES * (n_long + 1);
     const size_t a = scan_bytes(groups), b = scan_bytes(tables);
-    return 2 * Arena::rounded((size_t)groups * 4) + Arena::rounded((size_t)n_long * 4) + 2 * Arena::rounded((size_t)tables * 4) +
+    return 2 * Arena::rounded((size_t)groups * 4) + Arena::rounded((size_t)n_long * 4) + Arena::rounded((size_t)n_long * N_CLASSES * 4) + 2 * Arena::rounded((size_t)tables * 4) +
            Arena::rounded(sizeof(ClassBounds)) + (a > b ? a : b);
 }
 
@@ -447,16 +297,17 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
     if (int rc = read_counters(counters, kinds, 3, stream)) return rc;
     const int64_t n_group = kinds[ROW_GROUP], n_wave = kinds[ROW_WAVE], n_long = kinds[ROW_LONG];
 
-    int32_t *long_rows = nullptr, *cnt = nullptr, *off = nullptr;
+    int32_t *long_rows = nullptr, *class_beg = nullptr, *cnt = nullptr, *off = nullptr;
     int32_t starts[N_TABLES + 1] = {0};
     const int64_t stride = n_long + 1;
     if (n_long > 0) {
         if (int rc = ws.take((size_t)n_long * 4, &long_rows)) return rc;
+        if (int rc = ws.take((size_t)n_long * N_CLASSES * 4, &class_beg)) return rc;
         if (int rc = ws.take((size_t)(N_TABLES * stride) * 4, &cnt)) return rc;
         if (int rc = ws.take((size_t)(N_TABLES * stride) * 4, &off)) return rc;
         sched_rows_kernel<true><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, offs, n_groups, nullptr, long_rows);
         SG_LAUNCH_CHECK();
-        long_count_kernel<<<blocks_for(stride), TPB, 0, stream>>>(m.rowptr, m.colidx, long_rows, n_long, cb, item_max, cnt);
+        long_count_kernel<<<blocks_for(stride * N_CLASSES), TPB, 0, stream>>>(m.rowptr, m.colidx, long_rows, n_long, cb, item_max, class_beg, cnt);
         SG_LAUNCH_CHECK();
         if (int rc = scan_i32(cnt, off, N_TABLES * stride, ws, stream)) return rc;
         long_starts_kernel<<<1, 64, 0, stream>>>(off, cnt, stride, counters);
@@ -488,7 +339,7 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
         SG_LAUNCH_CHECK();
     }
     if (n_long > 0) {
-        long_fill_kernel<<<blocks_for(n_long), TPB, 0, stream>>>(m.rowptr, m.colidx, long_rows, n_long, cb, item_max, off,
+        long_fill_kernel<<<blocks_for(n_long * N_CLASSES), TPB, 0, stream>>>(m.rowptr, m.colidx, long_rows, n_long, cb, item_max, class_beg, off,
                                                                 out.items + base, out.fix);
         SG_LAUNCH_CHECK();
     }
@@ -502,94 +353,49 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
     return SLICEGCN_OK;
 }
 
-// Sorted keys (may hold repeats and sentinels) -> m.rowptr, m.colidx, and every entry's row in rowid; allocates colidx and vals.
-// `count_known`: the number of entries is g->nnz (the transposed pattern); otherwise it is read back, with the count of bad ids.
-// `dense_rows`: every row has an entry (self loops), so the sweep over the keys writes the row pointers too.
-template <class K>
-int csr_from_keys(const K *keys, const KeyPlan &kp, int64_t n_keys, slicegcn_graph *g, Csr &m, bool dense_rows, int32_t *rowid, int32_t *counters,
-                  bool count_known, Keep &keep, Arena ws, hipStream_t stream)
+// Column indices and values of a pattern whose rows have been counted; allocates both.
+int csr_entries(const EdgeSort &sorted, const slicegcn_graph *g, Csr &m, Keep &keep, hipStream_t stream)
 {
-    const int64_t n = g->n, n_chunks = chunks_of(n_keys);
-    int32_t *chunk = nullptr, *offs = nullptr;
-    if (int rc = ws.take((size_t)(n_chunks + 1) * 4, &chunk)) return rc;
-    if (int rc = ws.take((size_t)(n_chunks + 1) * 4, &offs)) return rc;
-    const unsigned grid = (unsigned)((n_chunks + 3) / 4);
-    if (n_keys > 0) {
-        compact_kernel<K, false><<<grid, 256, 0, stream>>>(keys, n_keys, n, (int)kp.col_bits, chunk, nullptr, nullptr, nullptr);
-        SG_LAUNCH_CHECK();
-        if (int rc = scan_i32(chunk, offs, n_chunks + 1, ws, stream)) return rc; // the last element is only written: the total
-    }
-    if (!count_known) {
-        int32_t h[2] = {0, 0};
-        if (n_keys > 0) {
-            SG_HIP(hipMemcpyAsync(h, counters, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-            SG_HIP(hipMemcpyAsync(h + 1, offs + n_chunks, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-            SG_HIP(hipStreamSynchronize(stream));
-        }
-        SG_REQUIRE(h[0] == 0, SLICEGCN_ERANGE, "build_norm_csr: %d edge(s) name a node outside [0, %lld)", h[0], (long long)n);
-        g->nnz = h[1];
-    }
     const size_t col_bytes = Arena::rounded((size_t)g->nnz * 4);
     char *block = nullptr;
     if (int rc = keep.take(2 * col_bytes, &block)) return rc;
     m.colidx = reinterpret_cast<int32_t *>(block);
     m.vals = reinterpret_cast<float *>(block + col_bytes);
-    if (n_keys > 0) {
-        compact_kernel<K, true><<<grid, 256, 0, stream>>>(keys, n_keys, n, (int)kp.col_bits, offs, m.colidx, rowid, dense_rows ? m.rowptr : nullptr);
-        SG_LAUNCH_CHECK();
-    }
-    if (!dense_rows) {
-        rowptr_kernel<<<blocks_for(n + 1), TPB, 0, stream>>>(rowid, g->nnz, n, m.rowptr);
-        SG_LAUNCH_CHECK();
-    }
-    return SLICEGCN_OK;
+    return g->nnz > 0 ? edge_sort_emit(sorted, m.rowptr, m.colidx, m.vals, g->dinv, stream) : SLICEGCN_OK;
 }
 
-int launch_vals(const int32_t *rowid, const slicegcn_graph *g, const Csr &m, hipStream_t stream)
-{
-    if (g->nnz == 0) return SLICEGCN_OK;
-    vals_kernel<<<blocks_for((g->nnz + 3) / 4), TPB, 0, stream>>>(rowid, m.colidx, g->nnz, g->dinv, m.vals);
-    SG_LAUNCH_CHECK();
-    return SLICEGCN_OK;
-}
-
-template <class K>
-int build_from_edges(const int64_t *src, const int64_t *dst, int64_t n_edges, uint32_t flags, const KeyPlan &kp, slicegcn_graph *g,
-                     Keep &keep, Arena ws, hipStream_t stream)
+int build_from_edges(const int64_t *src, const int64_t *dst, int64_t n_edges, uint32_t flags, slicegcn_graph *g, Keep &keep, Arena ws, hipStream_t stream)
 {
     const int64_t n = g->n;
-    const int sym = (flags & SLICEGCN_SYMMETRIZE) != 0, loops = (flags & SLICEGCN_ADD_SELF_LOOPS) != 0;
-    const unsigned end_bit = kp.col_bits + kp.row_bits;
-    int32_t *counters = nullptr, *rowid = nullptr;
-    K *keys_a = nullptr, *keys_b = nullptr;
+    const bool sym = (flags & SLICEGCN_SYMMETRIZE) != 0, loops = (flags & SLICEGCN_ADD_SELF_LOOPS) != 0;
+    int32_t *counters = nullptr;
     if (int rc = ws.take(N_COUNTERS * sizeof(int32_t), &counters)) return rc;
-    if (int rc = ws.take((size_t)kp.n_keys * sizeof(K), &keys_a)) return rc;
-    if (int rc = ws.take((size_t)kp.n_keys * sizeof(K), &keys_b)) return rc;
-    if (int rc = ws.take((size_t)kp.n_keys * sizeof(int32_t), &rowid)) return rc;
     {
-        // rowptr (both directions of a directed pattern), degrees and their roots, row order: one block
+        // rowptr (both directions of a directed pattern), degrees (one element more than rows) and their roots, row order: one block
         const size_t a = Arena::rounded((size_t)(n + 1) * 4), b = Arena::rounded((size_t)n * 4);
         const bool ordered = (flags & (SLICEGCN_REORDER_DEGREE | SLICEGCN_REORDER_BFS)) != 0;
         char *block = nullptr;
-        if (int rc = keep.take((sym ? 1 : 2) * a + (ordered ? 4 : 3) * b, &block)) return rc;
+        if (int rc = keep.take(a + (sym ? 1 : 2) * a + (ordered ? 3 : 2) * b, &block)) return rc;
         g->deg = reinterpret_cast<int32_t *>(block);
-        g->dinv = reinterpret_cast<float *>(block + b);
-        g->sqrtd = reinterpret_cast<float *>(block + 2 * b);
-        g->fwd.rowptr = reinterpret_cast<int32_t *>(block + 3 * b);
-        if (!sym) g->tr.rowptr = reinterpret_cast<int32_t *>(block + 3 * b + a);
-        if (ordered) g->order = reinterpret_cast<int32_t *>(block + 3 * b + (sym ? 1 : 2) * a);
+        g->dinv = reinterpret_cast<float *>(block + a);
+        g->sqrtd = reinterpret_cast<float *>(block + a + b);
+        g->fwd.rowptr = reinterpret_cast<int32_t *>(block + a + 2 * b);
+        if (!sym) g->tr.rowptr = reinterpret_cast<int32_t *>(block + 2 * a + 2 * b);
+        if (ordered) g->order = reinterpret_cast<int32_t *>(block + (sym ? 2 : 3) * a + 2 * b);
     }
     SG_HIP(hipMemsetAsync(counters, 0, N_COUNTERS * sizeof(int32_t), stream));
-    if (kp.n_keys > 0) {
-        make_keys_kernel<K><<<blocks_for(n_edges + (loops ? n : 0)), TPB, 0, stream>>>(src, dst, n_edges, n, (int)kp.col_bits, sym, loops,
-                                                                                      keys_a, counters);
-        SG_LAUNCH_CHECK();
-        if (int rc = sort_keys(keys_a, keys_b, kp.n_keys, end_bit, ws, stream)) return rc;
+    {
+        Arena phase = ws;
+        EdgeSort sorted;
+        if (int rc = edge_sort_rows(src, dst, n_edges, n, sym, loops, g->deg, g->dinv, g->sqrtd, g->fwd.rowptr, counters, phase, &sorted, stream)) return rc;
+        int32_t bad = 0, nnz = 0;
+        SG_HIP(hipMemcpyAsync(&bad, counters, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+        SG_HIP(hipMemcpyAsync(&nnz, g->fwd.rowptr + n, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+        SG_HIP(hipStreamSynchronize(stream));
+        SG_REQUIRE(bad == 0, SLICEGCN_ERANGE, "build_norm_csr: %d edge(s) name a node outside [0, %lld)", bad, (long long)n);
+        g->nnz = nnz;
+        if (int rc = csr_entries(sorted, g, g->fwd, keep, stream)) return rc;
     }
-    if (int rc = csr_from_keys<K>(keys_b, kp, kp.n_keys, g, g->fwd, loops != 0, rowid, counters, false, keep, ws, stream)) return rc;
-    degree_kernel<<<blocks_for(n), TPB, 0, stream>>>(g->fwd.rowptr, n, g->deg, g->dinv, g->sqrtd);
-    SG_LAUNCH_CHECK();
-    if (int rc = launch_vals(rowid, g, g->fwd, stream)) return rc;
     if (g->order)
         if (int rc = build_row_order(n, g->fwd.rowptr, g->fwd.colidx, (flags & SLICEGCN_REORDER_BFS) != 0, g->order, ws, counters + 2, stream)) return rc;
 
@@ -597,13 +403,12 @@ int build_from_edges(const int64_t *src, const int64_t *dst, int64_t n_edges, ui
         if (int rc = build_schedule(g, g->fwd, g->fwd.rowptr, flags, keep, ws, counters + 2, g->fwd.sched, stream)) return rc;
         g->tr = g->fwd; // A^ is symmetric: the same arrays serve the transposed product
     } else {
-        if (g->nnz > 0) {
-            swapped_keys_kernel<K><<<blocks_for(g->nnz), TPB, 0, stream>>>(rowid, g->fwd.colidx, g->nnz, (int)kp.col_bits, keys_a);
-            SG_LAUNCH_CHECK();
-            if (int rc = sort_keys(keys_a, keys_b, g->nnz, end_bit, ws, stream)) return rc;
-        }
-        if (int rc = csr_from_keys<K>(keys_b, kp, g->nnz, g, g->tr, loops != 0, rowid, counters, true, keep, ws, stream)) return rc;
-        if (int rc = launch_vals(rowid, g, g->tr, stream)) return rc;
+        Arena phase = ws;
+        EdgeSort sorted;
+        int32_t *in_deg = nullptr; // entries of the transposed pattern's rows; its values use the degrees of the pattern itself
+        if (int rc = phase.take((size_t)(n + 1) * 4, &in_deg)) return rc;
+        if (int rc = edge_sort_rows(dst, src, n_edges, n, false, loops, in_deg, nullptr, nullptr, g->tr.rowptr, counters + 1, phase, &sorted, stream)) return rc;
+        if (int rc = csr_entries(sorted, g, g->tr, keep, stream)) return rc;
         if (int rc = build_schedule(g, g->fwd, g->tr.rowptr, flags, keep, ws, counters + 2, g->fwd.sched, stream)) return rc;
         if (int rc = build_schedule(g, g->tr, g->fwd.rowptr, flags, keep, ws, counters + 2, g->tr.sched, stream)) return rc;
     }
@@ -613,20 +418,15 @@ int build_from_edges(const int64_t *src, const int64_t *dst, int64_t n_edges, ui
 
 size_t build_bytes(int64_t n_edges, int64_t n, uint32_t flags)
 {
-    const KeyPlan kp = key_plan(n_edges, n, flags);
-    const unsigned end_bit = kp.col_bits + kp.row_bits;
-    size_t later = kp.narrow ? sort_bytes<uint32_t>(kp.n_keys, end_bit) : sort_bytes<uint64_t>(kp.n_keys, end_bit);
-    const int64_t chunks = chunks_of(kp.n_keys) + 1;
-    const size_t compact = 2 * Arena::rounded((size_t)chunks * 4) + scan_bytes(chunks);
-    if (compact > later) later = compact;
-    const size_t sched = sched_bytes(n, kp.n_keys);
-    if (sched > later) later = sched;
+    const bool sym = (flags & SLICEGCN_SYMMETRIZE) != 0;
+    size_t most = edge_sort_bytes(n_edges, n, sym, (flags & SLICEGCN_ADD_SELF_LOOPS) != 0) + (sym ? 0 : Arena::rounded((size_t)(n + 1) * 4));
+    const size_t sched = sched_bytes(n, candidates(n_edges, n, flags));
+    if (sched > most) most = sched;
     if (flags & (SLICEGCN_REORDER_DEGREE | SLICEGCN_REORDER_BFS)) {
         const size_t order = row_order_bytes(n);
-        if (order > later) later = order;
+        if (order > most) most = order;
     }
-    return Arena::rounded(N_COUNTERS * sizeof(int32_t)) + 2 * Arena::rounded((size_t)kp.n_keys * kp.key_bytes()) +
-           Arena::rounded((size_t)kp.n_keys * 4) + later;
+    return Arena::rounded(N_COUNTERS * sizeof(int32_t)) + most;
 }
 
 // Checks of what is to be built, for both entry points and the workspace query
@@ -643,7 +443,7 @@ int check_sizes(int64_t n_edges, int64_t n_nodes, uint32_t flags)
                "build_norm_csr: SCHED_SHORT_ITEMS and SCHED_LONG_ITEMS exclude each other");
     SG_REQUIRE(n_nodes <= INT32_MAX, SLICEGCN_ERANGE, "build_norm_csr: n_nodes exceeds int32");
     SG_REQUIRE(n_edges <= (int64_t)INT32_MAX, SLICEGCN_ERANGE, "build_norm_csr: n_edges exceeds int32");
-    const int64_t n_keys = key_plan(n_edges, n_nodes, flags).n_keys;
+    const int64_t n_keys = candidates(n_edges, n_nodes, flags);
     SG_REQUIRE(n_keys <= (int64_t)INT32_MAX, SLICEGCN_ERANGE,
                "build_norm_csr: %lld candidate entries exceed int32 indexing", (long long)n_keys);
     return SLICEGCN_OK;
@@ -678,7 +478,6 @@ extern "C" int slicegcn_build_norm_csr_with(const int64_t *src, const int64_t *d
     const size_t need = build_bytes(n_edges, n_nodes, flags);
     SG_REQUIRE(ws == nullptr || ws_bytes >= need, SLICEGCN_EWORKSPACE, "build_norm_csr: workspace of %zu bytes, %zu needed", ws_bytes, need);
     hipStream_t stream = as_stream(stream_);
-    const KeyPlan kp = key_plan(n_edges, n_nodes, flags);
 
     slicegcn_graph *g = new (std::nothrow) slicegcn_graph();
     SG_REQUIRE(g != nullptr, SLICEGCN_ENOMEM, "build_norm_csr: host allocation failed");
@@ -699,8 +498,7 @@ extern "C" int slicegcn_build_norm_csr_with(const int64_t *src, const int64_t *d
     }
     Arena arena{static_cast<char *>(ws), ws_bytes, 0};
     Keep keep{allocator, g};
-    const int rc = kp.narrow ? build_from_edges<uint32_t>(src, dst, n_edges, flags, kp, g, keep, arena, stream)
-                             : build_from_edges<uint64_t>(src, dst, n_edges, flags, kp, g, keep, arena, stream);
+    const int rc = build_from_edges(src, dst, n_edges, flags, g, keep, arena, stream);
     if (rc) {
         (void)hipStreamSynchronize(stream); // nothing may still use the memory given back below
         return rc;

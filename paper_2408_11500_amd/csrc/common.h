@@ -188,6 +188,24 @@ struct Keep {
     }
 };
 
+// build_csr.hip: exclusive prefix sums (in and out may not overlap) and the scratch they take
+int scan_i32(const int32_t *in, int32_t *out, int64_t count, Arena &ws, hipStream_t stream);
+size_t scan_bytes(int64_t count);
+
+// edge_sort.hip: the distinct entries of a pattern, sorted in buckets of rows in the workspace, and with them the rows' numbers of entries
+// (deg has room for one more element than rows; dinv and sqrtd, from deg, may be NULL) and row pointers.  n_bad is increased by the
+// pairs with an id outside [0, n).  Then, with room for rowptr[n] entries, edge_sort_emit writes columns and values.
+struct EdgeSort {
+    const void *keys;
+    int64_t max_pieces;
+    bool wide;
+    alignas(8) unsigned char state[192]; // pointers into the workspace, for edge_sort.hip alone
+};
+size_t edge_sort_bytes(int64_t n_edges, int64_t n, bool sym, bool loops);
+int edge_sort_rows(const int64_t *row, const int64_t *col, int64_t n_edges, int64_t n, bool sym, bool loops, int32_t *deg, float *dinv, float *sqrtd,
+                   int32_t *rowptr, int32_t *n_bad, Arena &ws, EdgeSort *out, hipStream_t stream);
+int edge_sort_emit(const EdgeSort &e, const int32_t *rowptr, int32_t *colidx, float *vals, const float *dinv, hipStream_t stream);
+
 // order.hip: order[p] = id of the row at position p (by degree, or breadth first).  counters: two device words.
 int build_row_order(int64_t n, const int32_t *rowptr, const int32_t *colidx, bool breadth_first, int32_t *order, Arena ws,
                     int32_t *counters, hipStream_t stream);
