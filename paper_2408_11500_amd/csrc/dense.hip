@@ -11,6 +11,8 @@
 // B operand = B[k = l / 32][n = l % 32], accumulator register r (0..15) = C[8*(r/4) + 4*(l/32) + r%4][l % 32].
 #include "common.h"
 
+#include <type_traits>
+
 namespace slicegcn {
 
 namespace {
@@ -482,11 +484,48 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common
     }
 }
 
-// The same idea for layers up to 64 wide (K <= 32 * KC, at most 32 * NC output columns).  The weights no
-// longer fit in registers next to the accumulators, so the workgroup keeps them (zero padded, already
-// transposed for the backward products) in LDS and every MFMA reads its B operand from there; the
-// two operand strips of the forward pass go through the wavefront's one tile in turn.  Compiled for
-// two wavefronts per SIMD: one computes while the other moves its strip.
+// Four consecutive floats of an operand row as a strip kernel's lane loads them.  The lane that owns columns [c, c + 4) loads
+// from column min(c, K - 4) on, so that nothing outside the row's K columns is read and no load depends on a branch: a loop of such loads
+// and of unconditional stores has wait counts the compiler knows, and the next strip's loads and the last one's stores stay in flight (with
+// a branch per row it waited for every access at the top of the loop).  What a tail lane loaded is moved into place, and zeroed
+// beyond K, where it is used.
+struct LaneCols {
+    int at, shift; // first column loaded; columns to drop
+    __device__ LaneCols(int c, int K) : at(c < K - 4 ? c : K - 4), shift(c - at) {}
+    __device__ float4 load(const float *row) const
+    {
+        const floatx4_u v = *reinterpret_cast<const floatx4_u *>(row + at);
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+    __device__ void place(float4 &v) const
+    {
+        const bool one = shift & 1, two = shift & 2, none = shift >= 4;
+        const float x = one ? v.y : v.x, y = one ? v.z : v.y, z = one ? v.w : v.z, w = one ? 0.f : v.w;
+        v.x = none ? 0.f : two ? z : x;
+        v.y = none ? 0.f : two ? w : y;
+        v.z = none || two ? 0.f : z;
+        v.w = none || two ? 0.f : w;
+    }
+};
+
+// Four columns of a row from column c on, `left` of which exist; WHOLE: all four, of a row that exists
+template <bool WHOLE> __device__ inline void store_cols4(float *o, const float4 &v, bool row_ok, int left)
+{
+    if (WHOLE || (row_ok && left >= 4)) {
+        const floatx4_u w = {v.x, v.y, v.z, v.w};
+        *reinterpret_cast<floatx4_u *>(o) = w;
+    } else if (row_ok) {
+        if (left > 0) o[0] = v.x;
+        if (left > 1) o[1] = v.y;
+        if (left > 2) o[2] = v.z;
+    }
+}
+
+// Layers up to 64 wide (4 <= K <= 32 * KC, at most 32 * NC output columns) on many rows: a wavefront owns strips of 32 rows, reads a strip with
+// coalesced 16-byte loads, parks it in its own LDS tile and reads it back in the operand layout of the matrix instruction.  The weights
+// do not fit in registers next to the accumulators, so the workgroup keeps them (zero padded, already transposed for the backward
+// products) in LDS and every MFMA reads its B operand from there; the two operand strips of the forward pass go through the
+// wavefront's one tile in turn.  Compiled for two wavefronts per SIMD: one computes while the other moves its strip.
 template <int KC, int NC, bool BWD, bool TWO>
 __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs common, const PairBatch batch)
 {
@@ -495,102 +534,110 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     constexpr int ST = (KW > NW ? KW : NW) + 4; // tile row stride: 16-byte reads with lane = row stay conflict free
     constexpr int LK = KW / 4, LN = NW / 4;     // lanes per row, operand strips / output strips
     constexpr int PK = 32 * LK / 64, PN = 32 * LN / 64; // 16-byte accesses per lane and strip
+    constexpr int RK = 64 / LK, RN = 64 / LN;   // rows per access
     constexpr int QN = 4 * KC;                  // float4 of the reduction axis per row
+    constexpr bool PAIR = TWO && !BWD;          // two operand strips
     __shared__ __attribute__((aligned(16))) float Tl[4][32][ST];
     __shared__ float W1s[KW][NW];
     __shared__ float W2s[TWO ? KW : 1][NW];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int rk = lane / LK, ck = (lane % LK) * 4; // coalesced layout of an operand strip
-    const int rn = lane / LN, cn = (lane % LN) * 4; // and of an output strip
-    const bool vec1 = aligned16(a.A1) && (a.lda1 % 4 == 0);
-    const bool vec2 = TWO && !BWD && aligned16(a.A2) && (a.lda2 % 4 == 0);
+    const int rk = lane / LK, rn = lane / LN, cn = (lane % LN) * 4; // coalesced layouts of an operand and of an output strip
+    const LaneCols cols((lane % LK) * 4, a.K);
+    const bool place = a.K < KW; // uniform: some lanes' columns have to be moved or zeroed
     float (*tl)[ST] = Tl[wave];
 
-    for (int idx = threadIdx.x; idx < KW * NW; idx += 256) {
-        // consecutive threads walk the contiguous axis of W: columns forward, k backward (W^T)
-        const int kk = BWD ? idx % KW : idx / NW, j = BWD ? idx / KW : idx % NW;
-        float w1 = 0.f, w2 = 0.f;
-        if (kk < a.K && j < a.Nout) {
-            const int64_t id = BWD ? (int64_t)j * a.ldw + kk : (int64_t)kk * a.ldw + j;
-            w1 = a.B1[id];
-            if (TWO) w2 = a.B2[id];
-        }
-        W1s[kk][j] = w1;
-        if (TWO) W2s[kk][j] = w2;
-    }
-    __syncthreads(); // the only workgroup barrier: from here on a wavefront touches its own tile only
+    const int64_t n_full = a.n / 32; // whole strips
+    const int64_t first = (int64_t)blockIdx.x * 4 + wave, step = (int64_t)gridDim.x * 4;
+    // what is absent is read from an operand and replaced, so that every strip has the same accesses
+    const uint32_t *words = BWD && a.mask ? a.mask : reinterpret_cast<const uint32_t *>(a.A1);
+    const int64_t word_ld = BWD && a.mask ? a.mask_words : 0;
+    const float *s2 = PAIR && a.scale2 ? a.scale2 : a.A1, *so = a.scale_o1 ? a.scale_o1 : a.A1;
+    const int64_t s2_ld = PAIR && a.scale2 ? 1 : 0, so_ld = a.scale_o1 ? 1 : 0;
 
+    float4 p1[PK], p2[PAIR ? PK : 1];
+    uint32_t pw[KC];                // backward: activation words of strip row m
+    float f2[PAIR ? PK : 1], fo[PN]; // factors of the rows this lane loads and stores
+    auto fetch = [&](int64_t strip, auto whole) {
+        const int64_t r0 = strip * 32, end = a.n - 1;
+        auto row = [&](int64_t r) { return whole || r < end ? r : end; }; // rows past the end re-read the last
+#pragma unroll
+        for (int it = 0; it < PK; ++it) {
+            const int64_t r = row(r0 + rk + RK * it);
+            p1[it] = cols.load(a.A1 + r * a.lda1);
+            if (PAIR) {
+                p2[it] = cols.load(a.A2 + r * a.lda2);
+                f2[it] = s2[r * s2_ld];
+            }
+        }
+        if (BWD) {
+#pragma unroll
+            for (int w = 0; w < KC; ++w) pw[w] = words[row(r0 + m) * word_ld + (32 * w < a.K ? w : 0)];
+        }
+#pragma unroll
+        for (int it = 0; it < PN; ++it) fo[it] = so[row(r0 + rn + RN * it) * so_ld];
+    };
+    if (first < n_full) fetch(first, std::true_type());
+
+    constexpr int WN = KW * NW / 256; // weights of a thread
+    float w1[WN], w2[TWO ? WN : 1];
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+        // consecutive threads walk the contiguous axis of W: columns forward, k backward (W^T)
+        const int idx = threadIdx.x + 256 * i, kk = BWD ? idx % KW : idx / NW, j = BWD ? idx / KW : idx % NW;
+        const int kc = kk < a.K ? kk : a.K - 1, jc = j < a.Nout ? j : a.Nout - 1;
+        const int64_t id = BWD ? (int64_t)jc * a.ldw + kc : (int64_t)kc * a.ldw + jc;
+        w1[i] = a.B1[id];
+        if (TWO) w2[i] = a.B2[id];
+    }
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+        const int idx = threadIdx.x + 256 * i, kk = BWD ? idx % KW : idx / NW, j = BWD ? idx / KW : idx % NW;
+        const bool there = kk < a.K && j < a.Nout;
+        W1s[kk][j] = there ? w1[i] : 0.f;
+        if (TWO) W2s[kk][j] = there ? w2[i] : 0.f;
+    }
     float bias1[NC], bias2[NC];
 #pragma unroll
     for (int t = 0; t < NC; ++t) {
         const bool ok = 32 * t + m < a.Nout;
         bias1[t] = (!BWD && ok) ? inner_bias<TWO>(a, 32 * t + m) : 0.f;
-        bias2[t] = (!BWD && TWO && ok) ? outer_bias(a, 32 * t + m) : 0.f;
+        bias2[t] = (PAIR && ok) ? outer_bias(a, 32 * t + m) : 0.f;
     }
+    __syncthreads(); // the only workgroup barrier: from here on a wavefront touches its own tile only
 
-    const int64_t n_strips = (a.n + 31) / 32;
-    const int64_t first = (int64_t)blockIdx.x * 4 + wave, step = (int64_t)gridDim.x * 4;
-    float4 p1[PK], p2[(TWO && !BWD) ? PK : 1];
-    uint32_t pw[KC]; // backward: activation words of strip row m
-    // forward, scaled layout: factors of the rows this lane loads (f2) and stores (fo); fetched a strip ahead, applied
-    // where the strip is consumed
-    float f2[(TWO && !BWD) ? PK : 1], fo[BWD ? 1 : PN];
+    // One strip from the registers fetched; `next`: the strip to fetch meanwhile.  WHOLE: 32 rows and NW columns to store.
+    auto strip_step = [&](int64_t strip, int64_t next, auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        float out_f[PN]; // output factors of this strip's rows (the fetch below overwrites fo)
 #pragma unroll
-    for (int w = 0; w < KC; ++w) pw[w] = ~0u;
-    auto fetch = [&](int64_t strip) {
+        for (int it = 0; it < PN; ++it) out_f[it] = so_ld ? fo[it] : 1.f;
+        if (place) {
 #pragma unroll
-        for (int it = 0; it < PK; ++it) {
-            const int64_t row = strip * 32 + rk + (64 / LK) * it;
-            float4 v1 = make_float4(0.f, 0.f, 0.f, 0.f), v2 = v1;
-            if (row < a.n && ck < a.K) {
-                v1 = load_k4(a.A1, a.lda1, row, ck, a.K, vec1);
-                if (!BWD && TWO) v2 = load_k4(a.A2, a.lda2, row, ck, a.K, vec2);
-            }
-            if (!BWD && TWO) f2[it] = (a.scale2 && row < a.n) ? a.scale2[row] : 1.f;
-            p1[it] = v1;
-            if (!BWD && TWO) p2[it] = v2;
-        }
-        if (BWD && a.mask) {
-#pragma unroll
-            for (int w = 0; w < KC; ++w)
-                pw[w] = (strip * 32 + m < a.n && 32 * w < a.K) ? a.mask[(strip * 32 + m) * a.mask_words + w] : 0u;
-        }
-        if (!BWD) {
-#pragma unroll
-            for (int it = 0; it < PN; ++it) {
-                const int64_t row = strip * 32 + rn + (64 / LN) * it;
-                fo[it] = (a.scale_o1 && row < a.n) ? a.scale_o1[row] : 1.f;
+            for (int it = 0; it < PK; ++it) {
+                cols.place(p1[it]);
+                if (PAIR) cols.place(p2[it]);
             }
         }
-    };
-    if (first < n_strips) fetch(first);
-    for (int64_t strip = first; strip < n_strips; strip += step) {
-        float out_f[BWD ? 1 : PN]; // output factors of this strip's rows (the fetch below overwrites fo)
-        if (!BWD) {
 #pragma unroll
-            for (int it = 0; it < PN; ++it) out_f[it] = fo[it];
-        }
-#pragma unroll
-        for (int it = 0; it < PK; ++it) *reinterpret_cast<float4 *>(&tl[rk + (64 / LK) * it][ck]) = p1[it];
+        for (int it = 0; it < PK; ++it) *reinterpret_cast<float4 *>(&tl[rk + RK * it][(lane % LK) * 4]) = p1[it];
         __builtin_amdgcn_wave_barrier();
         float4 a1[QN];
 #pragma unroll
         for (int q = 0; q < QN; ++q) a1[q] = *reinterpret_cast<const float4 *>(&tl[m][8 * q + 4 * h]);
         __builtin_amdgcn_wave_barrier();
-        if (TWO && !BWD) { // the second operand strip takes the tile while the first product runs from registers
+        if (PAIR) { // the second operand strip takes the tile while the first product runs from registers
 #pragma unroll
             for (int it = 0; it < PK; ++it) {
-                if (a.scale2) scale4(p2[it], f2[it]);
-                *reinterpret_cast<float4 *>(&tl[rk + (64 / LK) * it][ck]) = p2[it];
+                scale4(p2[it], s2_ld ? f2[it] : 1.f);
+                *reinterpret_cast<float4 *>(&tl[rk + RK * it][(lane % LK) * 4]) = p2[it];
             }
             __builtin_amdgcn_wave_barrier();
         }
-        const bool more = strip + step < n_strips;
         uint32_t word[KC];
 #pragma unroll
-        for (int w = 0; w < KC; ++w) word[w] = pw[w];
-        if (more) fetch(strip + step); // flies during the MFMAs and the stores below
+        for (int w = 0; w < KC; ++w) word[w] = !BWD ? 0u : !a.mask ? ~0u : pw[w];
+        if (WHOLE) fetch(next, std::true_type()); // flies during the MFMAs and the stores below
         floatx16 acc1[NC], acc2[NC];
 #pragma unroll
         for (int t = 0; t < NC; ++t)
@@ -665,51 +712,48 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
             }
         }
         // Outputs leave through the wavefront's tile so that a row goes out as 16-byte stores
-        // (register r of lane (m, h) is strip row 8*(r/4) + 4*h + r%4, column 32 t + m); layouts that
-        // do not allow 16-byte stores write the registers directly.
-        // `rs`: per-row factor applied on the way out (forward outputs kept in the scaled layout), or NULL.
-        auto store_tile = [&](const floatx16 (&o)[NC], float *O, int64_t ldo, bool vec_ok, const float *rs) {
-            if (vec_ok) {
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int t = 0; t < NC; ++t)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) tl[8 * (r / 4) + 4 * h + (r % 4)][32 * t + m] = o[t][r];
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int it = 0; it < PN; ++it) {
-                    const int64_t row = row0 + rn + (64 / LN) * it;
-                    float4 v = *reinterpret_cast<const float4 *>(&tl[rn + (64 / LN) * it][cn]);
-                    if (row < a.n && cn < a.Nout) {
-                        if constexpr (!BWD) {
-                            if (rs) scale4(v, out_f[it]);
-                        } else { // backward: the accumulators leave no register for a factor fetched ahead
-                            if (rs) scale4(v, rs[row]);
-                        }
-                        *reinterpret_cast<float4 *>(O + row * ldo + cn) = v;
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-            } else {
-#pragma unroll
-                for (int t = 0; t < NC; ++t)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int64_t orow = row0 + 8 * (r / 4) + 4 * h + (r % 4);
-                        if (orow < a.n && 32 * t + m < a.Nout) O[orow * ldo + 32 * t + m] = rs ? o[t][r] * rs[orow] : o[t][r];
-                    }
-            }
-        };
-        const bool nout4 = a.Nout % 4 == 0;
-        store_tile(acc1, a.O1, a.ldo1, nout4 && aligned16(a.O1) && a.ldo1 % 4 == 0, a.scale_o1);
-        if constexpr (BWD && TWO) {
-            if (a.O2) store_tile(acc2, a.O2, a.ldo2, nout4 && aligned16(a.O2) && a.ldo2 % 4 == 0, nullptr);
-        }
-        if (!BWD && a.act == SLICEGCN_ACT_RELU && lane < 32 && row0 + lane < a.n) {
+        // (register r of lane (m, h) is strip row 8*(r/4) + 4*h + r%4, column 32 t + m).
+        // `scaled`: rows take out_f on the way out (outputs kept in the scaled layout)
+        auto store_tile = [&](const floatx16 (&o)[NC], float *O, int64_t ldo, bool scaled) {
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int t = 0; t < NC; ++t)
-                if (32 * t < a.Nout) a.mask[(row0 + lane) * a.mask_words + t] = my_word[t];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) tl[8 * (r / 4) + 4 * h + (r % 4)][32 * t + m] = o[t][r];
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int it = 0; it < PN; ++it) {
+                const int64_t row = row0 + rn + RN * it;
+                float4 v = *reinterpret_cast<const float4 *>(&tl[rn + RN * it][cn]);
+                if (scaled) scale4(v, out_f[it]);
+                store_cols4<WHOLE>(O + row * ldo + cn, v, row < a.n, a.Nout - cn);
+            }
+            __builtin_amdgcn_wave_barrier();
+        };
+        store_tile(acc1, a.O1, a.ldo1, so_ld != 0);
+        if constexpr (BWD && TWO) {
+            if (a.O2) store_tile(acc2, a.O2, a.ldo2, false);
         }
+        if (!BWD && a.act == SLICEGCN_ACT_RELU && lane < 32 && (WHOLE || row0 + lane < a.n)) {
+#pragma unroll
+            for (int t = 0; t < NC; ++t)
+                if (WHOLE || 32 * t < a.Nout) a.mask[(row0 + lane) * a.mask_words + t] = my_word[t];
+        }
+    };
+    int64_t strip = first;
+    if (a.Nout == NW) {
+#pragma unroll 1
+        for (; strip < n_full; strip += step) strip_step(strip, strip + step < n_full ? strip + step : strip, std::true_type());
+    } else {
+#pragma unroll 1
+        for (; strip < n_full; strip += step) {
+            strip_step(strip, 0, std::false_type());
+            if (strip + step < n_full) fetch(strip + step, std::true_type());
+        }
+    }
+    if (strip == n_full && a.n % 32 != 0) { // the rows left
+        fetch(strip, std::false_type());
+        strip_step(strip, 0, std::false_type());
     }
 }
 
@@ -770,7 +814,7 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
         SG_LAUNCH_CHECK();
         return SLICEGCN_OK;
     }
-    if (a.K <= 64 && a.Nout <= 64 && a.n >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
+    if (a.K >= 4 && a.K <= 64 && a.Nout <= 64 && a.n >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
         // as many workgroups as the chip holds at once (two per CU): each stages the weights once
         const dim3 grid((unsigned)(strip_blocks < 512 ? strip_blocks : 512), by);
         if (a.K <= 32) launch_strip64<1, 2, BWD>(a, b, grid, stream);
