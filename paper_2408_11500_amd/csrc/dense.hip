@@ -316,7 +316,54 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
     }
 }
 
-// Variant for the narrowest layers (K <= 32, at most 32 output columns: every layer of the workload
+// Four consecutive floats of an operand row as a strip kernel's lane loads them.  The lane that owns columns [c, c + 4) loads
+// from column min(c, K - 4) on, so that nothing outside the row's K columns is read and no load depends on a branch: a loop of such loads
+// and of unconditional stores has wait counts the compiler knows, and the next strip's loads and the last one's stores stay in flight (with
+// a branch per row it waited for every access at the top of the loop).  What a tail lane loaded is moved into place, and zeroed
+// beyond K, where it is used.
+// NARROW: rows of fewer than four columns, one float at a time.
+template <bool NARROW = false> struct LaneCols {
+    int at, shift; // first column loaded; columns to drop
+    int last;      // NARROW: last column of the row
+    __device__ LaneCols(int c, int K) : at(NARROW || c < K - 4 ? c : K - 4), shift(c - at), last(K - 1) {}
+    __device__ float4 load(const float *row) const
+    {
+        if constexpr (NARROW) return make_float4(row[min(at, last)], row[min(at + 1, last)], row[min(at + 2, last)], row[min(at + 3, last)]);
+        const floatx4_u v = *reinterpret_cast<const floatx4_u *>(row + at);
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+    __device__ void place(float4 &v) const
+    {
+        if constexpr (NARROW) {
+            v.x = at <= last ? v.x : 0.f;
+            v.y = at + 1 <= last ? v.y : 0.f;
+            v.z = at + 2 <= last ? v.z : 0.f;
+            v.w = 0.f;
+            return;
+        }
+        const bool one = shift & 1, two = shift & 2, none = shift >= 4;
+        const float x = one ? v.y : v.x, y = one ? v.z : v.y, z = one ? v.w : v.z, w = one ? 0.f : v.w;
+        v.x = none ? 0.f : two ? z : x;
+        v.y = none ? 0.f : two ? w : y;
+        v.z = none || two ? 0.f : z;
+        v.w = none || two ? 0.f : w;
+    }
+};
+
+// Four columns of a row from column c on, `left` of which exist; WHOLE: all four, of a row that exists
+template <bool WHOLE> __device__ inline void store_cols4(float *o, const float4 &v, bool row_ok, int left)
+{
+    if (WHOLE || (row_ok && left >= 4)) {
+        const floatx4_u w = {v.x, v.y, v.z, v.w};
+        *reinterpret_cast<floatx4_u *>(o) = w;
+    } else if (row_ok) {
+        if (left > 0) o[0] = v.x;
+        if (left > 1) o[1] = v.y;
+        if (left > 2) o[2] = v.z;
+    }
+}
+
+// Variant for the narrowest layers (4 <= K <= 32, at most 32 output columns: every layer of the workload
 // with slices and hidden width 32).  These layers are HBM bound (about 10 flop per byte), so the kernel
 // is built around the memory accesses: a wavefront owns strips of 32 rows; it reads a strip with fully
 // coalesced 16-byte loads (eight lanes per 128-byte row), parks it in its own LDS tile, and reads it
@@ -330,81 +377,97 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common
 {
     const PairArgs a = slice_of(common, batch);
     constexpr int ST = 36;
+    constexpr bool PAIR = TWO && !BWD; // two operand strips
     __shared__ __attribute__((aligned(16))) float T1[4][32][ST];
-    __shared__ __attribute__((aligned(16))) float T2[(TWO && !BWD) ? 4 : 1][32][ST];
+    __shared__ __attribute__((aligned(16))) float T2[PAIR ? 4 : 1][32][ST];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int m = lane & 31, h = lane >> 5;
     const int lr = lane >> 3, lc = (lane & 7) * 4; // coalesced layout: row lr + 8 * it, columns lc..lc+3
-    const bool vec1 = aligned16(a.A1) && (a.lda1 % 4 == 0);
-    const bool vec2 = TWO && !BWD && aligned16(a.A2) && (a.lda2 % 4 == 0);
+    const LaneCols<> cols(lc, a.K);
+    const bool place = a.K < 32; // uniform: some lanes' columns have to be moved or zeroed
     float (*t1)[ST] = T1[wave];
-    float (*t2)[ST] = T2[(TWO && !BWD) ? wave : 0];
+    float (*t2)[ST] = T2[PAIR ? wave : 0];
 
-    float b1[16], b2[16];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int kk = 8 * q + 4 * h + i;
-            float w1 = 0.f, w2 = 0.f;
-            if (kk < a.K && m < a.Nout) {
-                const int64_t id = BWD ? (int64_t)m * a.ldw + kk : (int64_t)kk * a.ldw + m;
-                w1 = a.B1[id];
-                if (TWO) w2 = a.B2[id];
-            }
-            b1[q * 4 + i] = w1;
-            b2[q * 4 + i] = w2;
-        }
-    const bool col_ok = m < a.Nout;
-    const float bias1 = (!BWD && col_ok) ? inner_bias<TWO>(a, m) : 0.f;
-    const float bias2 = (!BWD && TWO && col_ok) ? outer_bias(a, m) : 0.f;
-
-    const int64_t n_strips = (a.n + 31) / 32;
+    const int64_t n_full = a.n / 32; // whole strips
     const int64_t first = (int64_t)blockIdx.x * 4 + wave, step = (int64_t)gridDim.x * 4;
-    float4 p1[4], p2[4];
+    if (first * 32 >= a.n) return; // uniform per wavefront
+    // what is absent is read from an operand and replaced, so that every strip has the same accesses
+    const uint32_t *words = BWD && a.mask ? a.mask : reinterpret_cast<const uint32_t *>(a.A1);
+    const int64_t word_ld = BWD && a.mask ? a.mask_words : 0;
+    const float *s2 = PAIR && a.scale2 ? a.scale2 : a.A1, *so = a.scale_o1 ? a.scale_o1 : a.A1;
+    const int64_t s2_ld = PAIR && a.scale2 ? 1 : 0, so_ld = a.scale_o1 ? 1 : 0;
+
+    float4 p1[4], p2[PAIR ? 4 : 1];
     uint32_t pw = ~0u; // backward: activation word of strip row m (the row this lane feeds to the MFMAs)
     float ps = 1.f;    // backward: scale_o1 of strip row m
     // forward, scaled layout: factors of the rows lr + 8 it this lane loads and stores (only fetched here; they are
     // applied where the strip is consumed, so that the next strip's loads stay in flight behind the MFMAs).  One
     // load per lane and strip handed on by cross-lane reads was measured slower (the LDS pipe carries the tiles).
-    float f2[4] = {1.f, 1.f, 1.f, 1.f}, fo[4] = {1.f, 1.f, 1.f, 1.f};
-    auto fetch = [&](int64_t strip) {
+    float f2[PAIR ? 4 : 1], fo[BWD ? 1 : 4];
+    auto fetch = [&](int64_t strip, auto whole) {
+        const int64_t r0 = strip * 32, end = a.n - 1;
+        auto row = [&](int64_t r) { return whole || r < end ? r : end; }; // rows past the end re-read the last
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            const int64_t row = strip * 32 + lr + 8 * it;
-            float4 v1 = make_float4(0.f, 0.f, 0.f, 0.f), v2 = v1;
-            if (row < a.n && lc < a.K) {
-                v1 = load_k4(a.A1, a.lda1, row, lc, a.K, vec1);
-                if (!BWD && TWO) v2 = load_k4(a.A2, a.lda2, row, lc, a.K, vec2);
+            const int64_t r = row(r0 + lr + 8 * it);
+            p1[it] = cols.load(a.A1 + r * a.lda1);
+            if (PAIR) {
+                p2[it] = cols.load(a.A2 + r * a.lda2);
+                f2[it] = s2[r * s2_ld];
             }
-            if (!BWD && row < a.n) {
-                if (TWO && a.scale2) f2[it] = a.scale2[row];
-                if (a.scale_o1) fo[it] = a.scale_o1[row];
-            }
-            p1[it] = v1;
-            p2[it] = v2;
+            if (!BWD) fo[it] = so[r * so_ld];
         }
-        if (BWD && a.mask) pw = strip * 32 + m < a.n ? a.mask[(strip * 32 + m) * a.mask_words] : 0u;
-        if (BWD && a.scale_o1) ps = strip * 32 + m < a.n ? a.scale_o1[strip * 32 + m] : 1.f;
+        if (BWD) {
+            pw = words[row(r0 + m) * word_ld];
+            ps = so[row(r0 + m) * so_ld];
+        }
     };
-    if (first < n_strips) fetch(first);
-    for (int64_t strip = first; strip < n_strips; strip += step) {
+    if (first < n_full) fetch(first, std::true_type());
+    else fetch(first, std::false_type());
+
+    float b1[16], b2[16];
+    const int mc = m < a.Nout ? m : a.Nout - 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int kk = 8 * q + 4 * h + i, kc = kk < a.K ? kk : a.K - 1;
+            const int64_t id = BWD ? (int64_t)mc * a.ldw + kc : (int64_t)kc * a.ldw + mc;
+            b1[q * 4 + i] = a.B1[id];
+            b2[q * 4 + i] = TWO ? a.B2[id] : 0.f;
+        }
+    const bool col_ok = m < a.Nout;
+    const float bias1 = (!BWD && col_ok) ? inner_bias<TWO>(a, m) : 0.f;
+    const float bias2 = (PAIR && col_ok) ? outer_bias(a, m) : 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (8 * q + 4 * h + i >= a.K || !col_ok) b1[q * 4 + i] = b2[q * 4 + i] = 0.f;
+
+    // One strip from the registers fetched; `next`: the strip to fetch meanwhile.  WHOLE: 32 rows and 32 columns to store.
+    auto strip_step = [&](int64_t strip, int64_t next, auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
         float out_f[4]; // output factors of the rows lr + 8 it of this strip (the fetch below overwrites fo)
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            if (TWO && !BWD && a.scale2) scale4(p2[it], f2[it]);
-            out_f[it] = fo[it];
+            if (place) {
+                cols.place(p1[it]);
+                if (PAIR) cols.place(p2[it]);
+            }
+            if (PAIR) scale4(p2[it], s2_ld ? f2[it] : 1.f);
+            out_f[it] = !BWD && so_ld ? fo[it] : 1.f;
             *reinterpret_cast<float4 *>(&t1[lr + 8 * it][lc]) = p1[it];
-            if (TWO && !BWD) *reinterpret_cast<float4 *>(&t2[lr + 8 * it][lc]) = p2[it];
+            if (PAIR) *reinterpret_cast<float4 *>(&t2[lr + 8 * it][lc]) = p2[it];
         }
         __builtin_amdgcn_wave_barrier();
         float4 a1[4], a2[4];
-        const uint32_t word = pw;
-        const float so = ps;
+        const uint32_t word = BWD && a.mask ? pw : ~0u;
+        const float scale = BWD && so_ld ? ps : 1.f;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             a1[q] = *reinterpret_cast<const float4 *>(&t1[m][8 * q + 4 * h]);
-            if (TWO && !BWD) a2[q] = *reinterpret_cast<const float4 *>(&t2[m][8 * q + 4 * h]);
+            if (PAIR) a2[q] = *reinterpret_cast<const float4 *>(&t2[m][8 * q + 4 * h]);
             if (BWD) { // second product: dHout as it is; first product: dP = dHout * mask (times the row's output factor)
                 a2[q] = a1[q];
                 const uint32_t bits = word >> (8 * q + 4 * h);
@@ -412,11 +475,11 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common
                 if (!(bits & 2u)) a1[q].y = 0.f;
                 if (!(bits & 4u)) a1[q].z = 0.f;
                 if (!(bits & 8u)) a1[q].w = 0.f;
-                if (a.scale_o1) scale4(a1[q], so);
+                scale4(a1[q], scale);
             }
         }
         __builtin_amdgcn_wave_barrier();
-        if (strip + step < n_strips) fetch(strip + step); // flies during the MFMAs and the stores below
+        if (WHOLE) fetch(next, std::true_type()); // flies during the MFMAs and the stores below
         floatx16 acc1, acc2;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { acc1[r] = 0.f; acc2[r] = 0.f; }
@@ -448,76 +511,41 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common
             }
         }
         // Outputs leave through the wavefront's tile so that a row goes out as eight 16-byte stores
-        // (register r of lane (m, h) is strip row 8*(r/4) + 4*h + r%4, column m); layouts that do not
-        // allow 16-byte stores write the registers directly.
-        // `rs`: per-row factor applied on the way out (forward outputs kept in the scaled layout), or NULL; the
-        // 16-byte path takes the factors from out_f, fetched a strip ahead.
-        auto store_tile = [&](const float (&o)[16], float *O, int64_t ldo, bool vec_ok, const float *rs) {
-            if (vec_ok) {
-                __builtin_amdgcn_wave_barrier();
+        // (register r of lane (m, h) is strip row 8*(r/4) + 4*h + r%4, column m).
+        // `scaled`: rows take out_f on the way out (forward outputs kept in the scaled layout)
+        auto store_tile = [&](const float (&o)[16], float *O, int64_t ldo, bool scaled) {
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int r = 0; r < 16; ++r) t1[8 * (r / 4) + 4 * h + (r % 4)][m] = o[r];
-                __builtin_amdgcn_wave_barrier();
+            for (int r = 0; r < 16; ++r) t1[8 * (r / 4) + 4 * h + (r % 4)][m] = o[r];
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int64_t row = row0 + lr + 8 * it;
-                    float4 v = *reinterpret_cast<const float4 *>(&t1[lr + 8 * it][lc]);
-                    if (row < a.n && lc < a.Nout) {
-                        if (rs) scale4(v, out_f[it]);
-                        *reinterpret_cast<float4 *>(O + row * ldo + lc) = v;
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t orow = row0 + 8 * (r / 4) + 4 * h + (r % 4);
-                    if (orow < a.n && col_ok) O[orow * ldo + m] = rs ? o[r] * rs[orow] : o[r];
-                }
+            for (int it = 0; it < 4; ++it) {
+                const int64_t row = row0 + lr + 8 * it;
+                float4 v = *reinterpret_cast<const float4 *>(&t1[lr + 8 * it][lc]);
+                if (scaled) scale4(v, out_f[it]);
+                store_cols4<WHOLE>(O + row * ldo + lc, v, row < a.n, a.Nout - lc);
             }
+            __builtin_amdgcn_wave_barrier();
         };
-        const bool nout4 = a.Nout % 4 == 0;
-        store_tile(o1, a.O1, a.ldo1, nout4 && aligned16(a.O1) && a.ldo1 % 4 == 0, BWD ? nullptr : a.scale_o1);
-        if (BWD && TWO && a.O2) store_tile(o2, a.O2, a.ldo2, nout4 && aligned16(a.O2) && a.ldo2 % 4 == 0, nullptr);
-        if (!BWD && a.act == SLICEGCN_ACT_RELU && lane < 32 && row0 + lane < a.n)
+        store_tile(o1, a.O1, a.ldo1, !BWD && so_ld != 0);
+        if (BWD && TWO && a.O2) store_tile(o2, a.O2, a.ldo2, false);
+        if (!BWD && a.act == SLICEGCN_ACT_RELU && lane < 32 && (WHOLE || row0 + lane < a.n))
             a.mask[(row0 + lane) * a.mask_words] = my_word;
+    };
+    int64_t strip = first;
+    if (a.Nout == 32) {
+#pragma unroll 1
+        for (; strip < n_full; strip += step) strip_step(strip, strip + step < n_full ? strip + step : strip, std::true_type());
+    } else {
+#pragma unroll 1
+        for (; strip < n_full; strip += step) {
+            strip_step(strip, 0, std::false_type());
+            if (strip + step < n_full) fetch(strip + step, std::true_type());
+        }
     }
-}
-
-// Four consecutive floats of an operand row as a strip kernel's lane loads them.  The lane that owns columns [c, c + 4) loads
-// from column min(c, K - 4) on, so that nothing outside the row's K columns is read and no load depends on a branch: a loop of such loads
-// and of unconditional stores has wait counts the compiler knows, and the next strip's loads and the last one's stores stay in flight (with
-// a branch per row it waited for every access at the top of the loop).  What a tail lane loaded is moved into place, and zeroed
-// beyond K, where it is used.
-struct LaneCols {
-    int at, shift; // first column loaded; columns to drop
-    __device__ LaneCols(int c, int K) : at(c < K - 4 ? c : K - 4), shift(c - at) {}
-    __device__ float4 load(const float *row) const
-    {
-        const floatx4_u v = *reinterpret_cast<const floatx4_u *>(row + at);
-        return make_float4(v.x, v.y, v.z, v.w);
-    }
-    __device__ void place(float4 &v) const
-    {
-        const bool one = shift & 1, two = shift & 2, none = shift >= 4;
-        const float x = one ? v.y : v.x, y = one ? v.z : v.y, z = one ? v.w : v.z, w = one ? 0.f : v.w;
-        v.x = none ? 0.f : two ? z : x;
-        v.y = none ? 0.f : two ? w : y;
-        v.z = none || two ? 0.f : z;
-        v.w = none || two ? 0.f : w;
-    }
-};
-
-// Four columns of a row from column c on, `left` of which exist; WHOLE: all four, of a row that exists
-template <bool WHOLE> __device__ inline void store_cols4(float *o, const float4 &v, bool row_ok, int left)
-{
-    if (WHOLE || (row_ok && left >= 4)) {
-        const floatx4_u w = {v.x, v.y, v.z, v.w};
-        *reinterpret_cast<floatx4_u *>(o) = w;
-    } else if (row_ok) {
-        if (left > 0) o[0] = v.x;
-        if (left > 1) o[1] = v.y;
-        if (left > 2) o[2] = v.z;
+    if (strip == n_full && a.n % 32 != 0) { // the rows left
+        if (strip != first) fetch(strip, std::false_type());
+        strip_step(strip, 0, std::false_type());
     }
 }
 
@@ -543,7 +571,7 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int m = lane & 31, h = lane >> 5;
     const int rk = lane / LK, rn = lane / LN, cn = (lane % LN) * 4; // coalesced layouts of an operand and of an output strip
-    const LaneCols cols((lane % LK) * 4, a.K);
+    const LaneCols<> cols((lane % LK) * 4, a.K);
     const bool place = a.K < KW; // uniform: some lanes' columns have to be moved or zeroed
     float (*tl)[ST] = Tl[wave];
 
@@ -807,7 +835,7 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
     const unsigned by = (unsigned)batch;
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
     const int64_t strips = (a.n + 31) / 32, strip_blocks = (strips + 3) / 4;
-    if (a.K <= 32 && a.Nout <= 32) { // narrowest layers: per-wavefront strips, no barriers
+    if (a.K >= 4 && a.K <= 32 && a.Nout <= 32) { // narrowest layers: per-wavefront strips, no barriers
         const dim3 grid((unsigned)(strip_blocks < 2048 ? strip_blocks : 2048), by);
         if (two) pair_strip32_kernel<BWD, true><<<grid, 256, 0, stream>>>(a, b);
         else pair_strip32_kernel<BWD, false><<<grid, 256, 0, stream>>>(a, b);
