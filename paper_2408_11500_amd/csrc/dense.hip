@@ -321,7 +321,7 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
 // and of unconditional stores has wait counts the compiler knows, and the next strip's loads and the last one's stores stay in flight (with
 // a branch per row it waited for every access at the top of the loop).  What a tail lane loaded is moved into place, and zeroed
 // beyond K, where it is used.
-// NARROW: rows of fewer than four columns, one float at a time.
+// NARROW: rows that may have fewer than four columns, one float at a time.
 template <bool NARROW = false> struct LaneCols {
     int at, shift; // first column loaded; columns to drop
     int last;      // NARROW: last column of the row
@@ -338,7 +338,7 @@ template <bool NARROW = false> struct LaneCols {
             v.x = at <= last ? v.x : 0.f;
             v.y = at + 1 <= last ? v.y : 0.f;
             v.z = at + 2 <= last ? v.z : 0.f;
-            v.w = 0.f;
+            v.w = at + 3 <= last ? v.w : 0.f;
             return;
         }
         const bool one = shift & 1, two = shift & 2, none = shift >= 4;
@@ -1356,7 +1356,7 @@ __global__ __launch_bounds__(256, 2) void bwd_strip32_kernel(const ReduceArgs rc
 // faster, nor is keeping two or three strips in flight) keep the staging registers and the
 // wave-private LDS tiles small enough for two wavefronts per SIMD beside the 128 accumulator
 // registers of the full-width variant, three for the half-width ones.
-template <int MI, int NJ, int SR, int WPS> // SR: node rows per strip; WPS: wavefronts per SIMD to compile for
+template <int MI, int NJ, int SR, int WPS, bool SELF, bool NARROW> // SR: node rows per strip; WPS: wavefronts per SIMD to compile for
 __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs common, const ReduceBatch batch, int64_t n_waves)
 {
     const ReduceArgs a = slice_of(common, batch, blockIdx.y);
@@ -1372,11 +1372,16 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
     const int ri = lane / LI, ci = (lane % LI) * 4; // coalesced layout of the w_in-wide operands
     const int rj = lane / LJ, cj = (lane % LJ) * 4; // and of dHout
     const int64_t w_id = (int64_t)blockIdx.x * 4 + wave;
-    const int64_t n_strips = (a.n + SR - 1) / SR;
-    if (w_id >= n_waves) return; // uniform per wavefront; no workgroup barriers below (n_waves <= n_strips)
-    const bool self = a.Hin != nullptr;
-    const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vh = self && aligned16(a.Hin) && a.ldi % 4 == 0;
-    const bool vg = aligned16(a.dHout) && a.ldo % 4 == 0;
+    const int64_t n_full = a.n / SR; // whole strips
+    if (w_id >= n_waves) return; // uniform per wavefront; no workgroup barriers below (no more wavefronts than strips)
+    const LaneCols<NARROW> ic(ci, a.w_in), oc(cj, a.w_out);
+    const bool place_i = a.w_in < WI, place_o = a.w_out < WJ; // uniform
+    // what is absent is read from an operand and replaced, so that every strip has the same accesses
+    const uint32_t *words = a.mask ? a.mask : reinterpret_cast<const uint32_t *>(a.dHout);
+    const int64_t word_ld = a.mask ? a.mask_words : 0;
+    const float *hs_f = SELF && a.hin_scale ? a.hin_scale : a.Z;
+    const int64_t hs_ld = SELF && a.hin_scale ? 1 : 0;
+    const int word = lane % NJ; // lane l < SR * NJ: word l % NJ of strip row l / NJ
     float (*zs)[WI] = Zs[wave];
     float (*hs)[WI] = Hs[wave];
     float (*gs)[WJ] = Gs[wave];
@@ -1393,50 +1398,50 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
 #pragma unroll
     for (int j = 0; j < NJ; ++j) { sum_p[j] = 0.f; sum_g[j] = 0.f; }
 
-    float4 pz[PI], ph[PI], pg[PJ];
-    float hf[PI]; // factors of the rows of Hin this lane loads (scaled layout); applied on the way to LDS
-    uint32_t pw = ~0u; // lane l < SR * NJ: word l % NJ of strip row l / NJ
-    auto fetch = [&](int64_t r0) {
+    float4 pz[PI], ph[SELF ? PI : 1], pg[PJ];
+    float hf[SELF ? PI : 1]; // factors of the rows of Hin this lane loads (scaled layout); applied on the way to LDS
+    uint32_t pw;
+    auto fetch = [&](int64_t strip, auto whole) {
+        const int64_t r0 = strip * SR, end = a.n - 1;
+        auto row = [&](int64_t r) { return whole || r < end ? r : end; }; // rows past the end re-read the last
 #pragma unroll
         for (int it = 0; it < PI; ++it) {
-            const int64_t row = r0 + ri + (64 / LI) * it;
-            float4 z = make_float4(0.f, 0.f, 0.f, 0.f), hh = z;
-            hf[it] = 1.f;
-            if (row < a.n && ci < a.w_in) {
-                z = load_k4(a.Z, a.ldz, row, ci, a.w_in, vz);
-                if (self) {
-                    hh = load_k4(a.Hin, a.ldi, row, ci, a.w_in, vh);
-                    if (a.hin_scale) hf[it] = a.hin_scale[row];
-                }
+            const int64_t r = row(r0 + ri + (64 / LI) * it);
+            pz[it] = ic.load(a.Z + r * a.ldz);
+            if (SELF) {
+                ph[it] = ic.load(a.Hin + r * a.ldi);
+                hf[it] = hs_f[r * hs_ld];
             }
-            pz[it] = z; ph[it] = hh;
+        }
+#pragma unroll
+        for (int it = 0; it < PJ; ++it) pg[it] = oc.load(a.dHout + row(r0 + rj + (64 / LJ) * it) * a.ldo);
+        pw = words[row(r0 + lane / NJ % SR) * word_ld + (32 * word < a.w_out && word_ld ? word : 0)];
+    };
+    auto strip_step = [&](int64_t strip, int64_t next, auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
+#pragma unroll
+        for (int it = 0; it < PI; ++it) {
+            if (place_i) {
+                ic.place(pz[it]);
+                if (SELF) ic.place(ph[it]);
+            }
+            if (SELF) scale4(ph[it], hs_ld ? hf[it] : 1.f);
+            if (!WHOLE && strip * SR + ri + (64 / LI) * it >= a.n) {
+                pz[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (SELF) ph[it] = pz[it];
+            }
+            *reinterpret_cast<float4 *>(&zs[ri + (64 / LI) * it][ci]) = pz[it];
+            if (SELF) *reinterpret_cast<float4 *>(&hs[ri + (64 / LI) * it][ci]) = ph[it];
         }
 #pragma unroll
         for (int it = 0; it < PJ; ++it) {
-            const int64_t row = r0 + rj + (64 / LJ) * it;
-            float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (row < a.n && cj < a.w_out) g = load_k4(a.dHout, a.ldo, row, cj, a.w_out, vg);
-            pg[it] = g;
+            if (place_o) oc.place(pg[it]);
+            if (!WHOLE && strip * SR + rj + (64 / LJ) * it >= a.n) pg[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+            *reinterpret_cast<float4 *>(&gs[rj + (64 / LJ) * it][cj]) = pg[it];
         }
-        if (a.mask && lane < SR * NJ) {
-            const int64_t row = r0 + lane / NJ;
-            const int word = lane % NJ;
-            pw = (row < a.n && 32 * word < a.w_out) ? a.mask[row * a.mask_words + word] : 0u;
-        }
-    };
-    fetch(w_id * SR);
-    for (int64_t strip = w_id; strip < n_strips; strip += n_waves) { // wavefront w takes strips w, w + n_waves, ...
-#pragma unroll
-        for (int it = 0; it < PI; ++it) {
-            if (a.hin_scale) scale4(ph[it], hf[it]);
-            *reinterpret_cast<float4 *>(&zs[ri + (64 / LI) * it][ci]) = pz[it];
-            *reinterpret_cast<float4 *>(&hs[ri + (64 / LI) * it][ci]) = ph[it];
-        }
-#pragma unroll
-        for (int it = 0; it < PJ; ++it) *reinterpret_cast<float4 *>(&gs[rj + (64 / LJ) * it][cj]) = pg[it];
-        if (lane < SR * NJ) ms[lane / NJ][lane % NJ] = pw;
+        if (lane < SR * NJ) ms[lane / NJ][word] = a.mask ? pw : ~0u;
         __builtin_amdgcn_wave_barrier();
-        if (strip + n_waves < n_strips) fetch((strip + n_waves) * SR);
+        if (WHOLE) fetch(next, std::true_type());
 #pragma unroll
         for (int s2 = 0; s2 < SR / 2; ++s2) {
             const int k = 2 * s2 + h;
@@ -1451,17 +1456,25 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
                 z[i] = zs[k][32 * i + m];
-                hh[i] = hs[k][32 * i + m];
+                hh[i] = SELF ? hs[k][32 * i + m] : 0.f;
             }
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     accA[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(z[i], pp[j], accA[i][j], 0, 0, 0);
-                    if (self) accS[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(hh[i], g[j], accS[i][j], 0, 0, 0);
+                    if (SELF) accS[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(hh[i], g[j], accS[i][j], 0, 0, 0);
                 }
         }
         __builtin_amdgcn_wave_barrier();
+    };
+    int64_t strip = w_id; // wavefront w takes strips w, w + n_waves, ...
+    if (strip < n_full) fetch(strip, std::true_type());
+#pragma unroll 1
+    for (; strip < n_full; strip += n_waves) strip_step(strip, strip + n_waves < n_full ? strip + n_waves : strip, std::true_type());
+    if (strip == n_full && a.n % SR != 0) { // the rows left
+        fetch(strip, std::false_type());
+        strip_step(strip, 0, std::false_type());
     }
     float *out = a.partial + w_id * a.stride;
     const int ww = a.w_in * a.w_out;
@@ -1778,6 +1791,15 @@ inline LinearGradPlan linear_grad_plan(int64_t n, int32_t w_in, int32_t w_out, i
     p.rows = (int32_t)rows;
     p.partials = (n + rows - 1) / rows;
     return p;
+}
+
+// launch(self, narrow) with both as constants; narrow: a row of an operand is too short for 16-byte loads
+template <class F> void launch_grad_strip(bool self, bool narrow, F launch)
+{
+    if (self && narrow) launch(std::true_type(), std::true_type());
+    else if (self) launch(std::true_type(), std::false_type());
+    else if (narrow) launch(std::false_type(), std::true_type());
+    else launch(std::false_type(), std::false_type());
 }
 
 // Launches grad_rows_kernel for `products` products (r.rows_per_block rows a workgroup).  Tiles of 64 x 64 per workgroup or wavefront
@@ -2295,9 +2317,11 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
             }
             break;
         case GradPlan::STRIP64:
-            if (w_in <= 32) grad_strip64_kernel<1, 2, 8, 3><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
-            else if (w_out <= 32) grad_strip64_kernel<2, 1, 8, 3><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
-            else grad_strip64_kernel<2, 2, 8, 2><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
+            launch_grad_strip(self, w_in < 4 || w_out < 4, [&](auto s, auto w) {
+                if (w_in <= 32) grad_strip64_kernel<1, 2, 8, 3, s.value, w.value><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
+                else if (w_out <= 32) grad_strip64_kernel<2, 1, 8, 3, s.value, w.value><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
+                else grad_strip64_kernel<2, 2, 8, 2, s.value, false><<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
+            });
             break;
         case GradPlan::TILED:
             if (int rc = launch_grad_rows(r, b, batch, self ? 2 : 1, false, stream)) return rc;

@@ -1,0 +1,86 @@
+"""Slice layers through the strip kernels (many rows, widths up to 64): widths that fill the kernels' tiles, end inside a 16-byte access or are
+narrower than one, a last strip that is not whole, rows on any boundary with NaN behind them, with and without self term."""
+import pytest
+import torch
+
+from paper_2408_11500_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+ROWS32, ROWS64 = 65_536 + 21, (1 << 21) + 13   # from 2^16 rows on the 32-wide kernels, from 2^21 on all of the 64-wide ones
+
+
+@pytest.fixture(scope="module")
+def graphs():
+    """No edges but the diagonal: the aggregation copies, so that the products stand alone."""
+    none = torch.empty(0, dtype=torch.int64, device="cuda")
+    made = {n: B.slicegcn_build_norm_csr(none, none, n) for n in (ROWS32, ROWS64)}
+    yield made
+    for g in made.values():
+        g.destroy()
+
+
+def operand(gen, rows, cols, pad):
+    full = torch.full((rows, cols + pad), float("nan"), device="cuda")
+    full[:, :cols] = torch.randn((rows, cols), generator=gen, device="cuda")
+    return full[:, :cols]
+
+
+def assert_fp32(got, want, scale, what):
+    """Within 3e-6 of the sum of the products' magnitudes, element by element: what chains of some thousand fp32 products stay below."""
+    assert bool(torch.isfinite(got).all()), what
+    worst = ((got.double() - want).abs() / scale.clamp_min(1e-300)).max().item()
+    assert worst <= 3e-6, f"{what}: {worst:.2e}"
+
+
+CASES = [(ROWS32, i, o, self_term, pad) for i, o in ((32, 32), (25, 32), (32, 25), (4, 4), (5, 31), (3, 32), (32, 2), (1, 1), (30, 7))
+         for self_term, pad in ((True, 0), (True, 3), (False, 1))]
+CASES += [(ROWS64, i, o, self_term, pad) for i, o, self_term, pad in ((64, 64, True, 3), (25, 64, True, 3), (40, 30, True, 0), (40, 30, False, 1),
+                                                                     (2, 50, True, 3), (2, 50, False, 0), (61, 3, True, 3), (64, 64, False, 0))]
+
+
+@pytest.mark.parametrize("n,w_in,w_out,self_term,pad", CASES)
+def test_layer_matches_fp64(graphs, n, w_in, w_out, self_term, pad):
+    gen = torch.Generator(device="cuda").manual_seed(w_in + 7 * w_out + pad)
+    X, G = operand(gen, n, w_in, pad), operand(gen, n, w_out, pad)
+    W, Ws = (torch.randn((w_in, w_out), generator=gen, device="cuda") for _ in range(2))
+    b, bs = (torch.randn(w_out, generator=gen, device="cuda") for _ in range(2))
+    if not self_term:
+        Ws = bs = None
+    Z = torch.full((n, (w_in + 3) // 4 * 4), float("nan"), device="cuda")[:, :w_in]   # rows on 16-byte boundaries, as the call asks
+    H = torch.full((n, w_out + 1), 7.0, device="cuda")
+    words = torch.zeros((n, (w_out + 31) // 32), dtype=torch.int32, device="cuda")
+    B.slicegcn_layer_fwd(graphs[n], X, W, b, Ws, bs, H[:, :w_out], Z, words)
+    assert torch.equal(Z, X) and bool((H[:, w_out] == 7.0).all())
+    on = torch.stack([(words >> j) & 1 for j in range(32)], dim=2).reshape(n, -1)
+    assert not bool(on[:, w_out:].any())
+    on = on[:, :w_out].bool()
+    pre, size = X.double() @ W.double() + b.double(), X.double().abs() @ W.double().abs() + b.double().abs()
+    assert bool((on == (pre > 0))[pre.abs() > 3e-6 * size].all())
+    want = torch.where(on, pre, 0.)
+    if self_term:
+        want, size = want + X.double() @ Ws.double() + bs.double(), size + X.double().abs() @ Ws.double().abs() + bs.double().abs()
+    assert_fp32(H[:, :w_out], want, size, "H")
+    del pre, size, want
+
+    for input_gradient in (True, False):
+        dX = torch.full((n, w_in + 1), 7.0, device="cuda") if input_gradient else None
+        dW, db = torch.empty_like(W), torch.empty_like(b)
+        dWs, dbs = (torch.empty_like(W), torch.empty_like(b)) if self_term else (None, None)
+        ws = torch.empty(B.slicegcn_layer_bwd_workspace_bytes(graphs[n], w_in, w_out, input_gradient), dtype=torch.uint8, device="cuda")
+        B.slicegcn_layer_bwd(graphs[n], X, W, Ws, Z, words, G, dX[:, :w_in] if input_gradient else None, dW, db, dWs, dbs, ws)
+        P, Gd, Xd = torch.where(on, G, 0.).double(), G.double(), X.double()
+        if input_gradient:
+            want, size = P @ W.double().t(), P.abs() @ W.double().abs().t()
+            if self_term:
+                want, size = want + Gd @ Ws.double().t(), size + Gd.abs() @ Ws.double().abs().t()
+            assert bool((dX[:, w_in] == 7.0).all())
+            assert_fp32(dX[:, :w_in], want, size, "dHin")
+            first = dW.clone()
+        else:
+            assert torch.equal(first, dW)   # the same sums with and without the input gradient
+        assert_fp32(dW, Xd.t() @ P, Xd.abs().t() @ P.abs(), "dW_agg")
+        assert_fp32(db, P.sum(0), P.abs().sum(0), "db")
+        if self_term:
+            assert_fp32(dWs, Xd.t() @ Gd, Xd.abs().t() @ Gd.abs(), "dW_self")
+            assert_fp32(dbs, Gd.sum(0), Gd.abs().sum(0), "db_self")
