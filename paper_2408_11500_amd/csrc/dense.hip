@@ -140,16 +140,20 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const TilePlace place = tile_place(n_col_tiles);
-    const int64_t row_tile = place.row_tile;
-    const int col0 = place.col_tile * BN;
+    // tile_place in 32 bits: the 64-bit division is as long as a small layer's loads
+    const uint32_t group = blockIdx.x / (8u * n_col_tiles);
+    const int64_t row_tile = (int64_t)group * 8 + blockIdx.x % 8;
+    const int col0 = (int)(blockIdx.x / 8 - group * n_col_tiles) * BN;
     if (row_tile * 128 >= a.n) return; // uniform per workgroup
     const int chunks = (a.K + KC - 1) / KC, total = TWO ? 2 * chunks : chunks;
 
-    if (!BWD && tid < BN) {
-        const int col = col0 + tid;
-        bias_s[0][tid] = col < a.Nout ? inner_bias<TWO>(a, col) : 0.f;
-        bias_s[1][tid] = TWO && col < a.Nout ? outer_bias(a, col) : 0.f;
+    // biases of this thread's column: requested here, added and put into LDS behind the first chunk's requests
+    float in_b = 0.f, out_b = 0.f, enc_b = 0.f;
+    if (!BWD) {
+        const int col = col0 + (tid < BN ? tid : 0), c = col < a.Nout ? col : a.Nout - 1;
+        in_b = a.bias1 ? a.bias1[c] : 0.f;
+        if (TWO) out_b = a.bias2 ? a.bias2[c] : 0.f;
+        enc_b = a.enc ? a.enc[c] : 0.f;
     }
     // The row this lane feeds.  Rows past the end and columns past the last one re-read the last: what they give is not
     // stored.  Steps of k past K are zero in both operands.
@@ -250,6 +254,10 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
     clear();
     fetch_weights(0);
     fetch_rows(0);
+    if (!BWD && tid < BN) { // inside the activation, and outside it (the encoding joins the outer one; with a single product the only one)
+        bias_s[0][tid] = in_b + (TWO ? 0.f : enc_b);
+        bias_s[1][tid] = out_b + enc_b;
+    }
     stash_weights(0);
     __syncthreads();
     for (int cc = 0; cc < total; ++cc) {
@@ -270,15 +278,20 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
             for (int q = 0; q < KC / 8; ++q) x[q] *= f_in;
         }
         if (more) fetch_rows(cc + 1);
+        floatx4 w[2][NT]; // the weights of four steps are read while the four before them are multiplied
+#pragma unroll
+        for (int t = 0; t < NT; ++t) w[0][t] = Bs[cc & 1][h][32 * t + m];
 #pragma unroll
         for (int q = 0; q < KC / 8; ++q) {
-            floatx4 w[NT];
+            if (q + 1 < KC / 8) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) w[t] = Bs[cc & 1][2 * q + h][32 * t + m];
+                for (int t = 0; t < NT; ++t) w[(q + 1) & 1][t] = Bs[cc & 1][2 * (q + 1) + h][32 * t + m];
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[t][i], x[q][i], acc[t], 0, 0, 0);
+                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[q & 1][t][i], x[q][i], acc[t], 0, 0, 0);
         }
         if (more) stash_weights((cc + 1) & 1); // the buffer of the chunk before this one, which every wavefront has left
         __syncthreads();
