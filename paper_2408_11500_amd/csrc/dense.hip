@@ -1520,10 +1520,12 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
 // 64 x 64 quarter (four MFMA accumulators).  Per step 32 rows of the X tile and of the dP tile are
 // staged in LDS (the next step's loads are issued into registers before this step's MFMAs); the
 // node axis is the MFMA's k axis.  32 flop per staged byte instead of 8 for 32 x 32 tiles.  The tiles of a row block run back to back on
-// one XCD (grid as in grad_rows_kernel): 2.4 M rows 256 x 256 3.84 -> 3.65 ms (88 TFLOP/s), 233 k rows 0.480 -> 0.456 ms.
+// one XCD (grid as in grad_rows_kernel).  Loads are unconditional and the activation bits are applied on the way to LDS: applied
+// where they were fetched, with a test per row, every step waited for its own accesses.  2.4 M rows 256 x 256 3.66 -> 2.95 ms
+// (109 TFLOP/s), 169 k rows 312 -> 251 us; three wavefronts per SIMD (two: 3.01 ms), one buffer (two, with half the barriers: 3.14).
 constexpr int GB_T = 128;
 
-__global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
+__global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
 {
     const ReduceArgs a = slice_of(common, batch, blockIdx.y);
     const TilePlace place = tile_place(n_tiles);
@@ -1537,8 +1539,14 @@ __global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs com
     const int64_t r_begin = place.row_tile * a.rows_per_block;
     if (r_begin >= a.n) return; // uniform per workgroup
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
-    const bool vz = aligned16(a.Z) && a.ldz % 4 == 0, vg = aligned16(a.dHout) && a.ldo % 4 == 0;
     const bool bias_wave = i_base == 0 && (wave >> 1) == 0;
+    // this thread's four columns of the tiles, of rows tid / 32, tid / 32 + 8, ... of a step
+    const int c4 = (tid & 31) * 4, lr = tid >> 5;
+    const LaneCols<> xc(i_base + c4, a.w_in), pc(j_base + c4, a.w_out);
+    const bool place_x = i_base + GB_T > a.w_in, place_p = j_base + GB_T > a.w_out; // uniform
+    const int j = j_base + c4 < a.w_out ? j_base + c4 : a.w_out - 1;
+    const uint32_t *words = a.mask ? a.mask + (j >> 5) : reinterpret_cast<const uint32_t *>(a.dHout); // none: read anything, use all ones
+    const int64_t word_ld = a.mask ? a.mask_words : 0;
 
     floatx16 acc[2][2];
 #pragma unroll
@@ -1550,42 +1558,35 @@ __global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs com
     float accb = 0.f; // column j_base + wj + lane of dP
 
     float4 rx[4], rp[4];
-    auto fetch = [&](int64_t r0) {
+    uint32_t rw[4];
+    auto fetch = [&](int64_t r0, auto whole) {
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            const int idx = tid + it * 256;
-            const int r = idx >> 5, c4 = (idx & 31) * 4;
-            const int64_t row = r0 + r;
-            float4 x = make_float4(0.f, 0.f, 0.f, 0.f), p = x;
-            if (row < r_end) {
-                if (i_base + c4 < a.w_in) x = load_k4(a.Z, a.ldz, row, i_base + c4, a.w_in, vz);
-                if (j_base + c4 < a.w_out) {
-                    p = load_k4(a.dHout, a.ldo, row, j_base + c4, a.w_out, vg);
-                    if (a.mask) {
-                        const int j = j_base + c4;
-                        const uint32_t bits = a.mask[row * a.mask_words + (j >> 5)] >> (j & 31);
-                        if (!(bits & 1u)) p.x = 0.f;
-                        if (!(bits & 2u)) p.y = 0.f;
-                        if (!(bits & 4u)) p.z = 0.f;
-                        if (!(bits & 8u)) p.w = 0.f;
-                    }
-                }
-            }
-            rx[it] = x;
-            rp[it] = p;
+            const int64_t r = r0 + lr + 8 * it, row = whole || r < r_end ? r : r_end - 1; // rows past the end re-read the last
+            rx[it] = xc.load(a.Z + row * a.ldz);
+            rp[it] = pc.load(a.dHout + row * a.ldo);
+            rw[it] = words[row * word_ld];
         }
     };
-    fetch(r_begin);
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += RED_RK) {
+    // `next`: first row to fetch meanwhile.  The activation bits are applied on the way to LDS, not where they are fetched: the next
+    // step's accesses stay in flight behind this one's products.
+    auto step = [&](int64_t r0, int64_t next, auto whole, auto more) {
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            const int idx = tid + it * 256;
-            const int r = idx >> 5, c4 = (idx & 31) * 4;
-            *reinterpret_cast<float4 *>(&Xs[r][c4]) = rx[it];
-            *reinterpret_cast<float4 *>(&Ps[r][c4]) = rp[it];
+            float4 x = rx[it], p = rp[it];
+            if (place_x) xc.place(x);
+            if (place_p) pc.place(p);
+            const uint32_t bits = a.mask ? rw[it] >> (j & 31) : ~0u;
+            p.x = bits & 1u ? p.x : 0.f;
+            p.y = bits & 2u ? p.y : 0.f;
+            p.z = bits & 4u ? p.z : 0.f;
+            p.w = bits & 8u ? p.w : 0.f;
+            if (!whole && r0 + lr + 8 * it >= r_end) x = p = make_float4(0.f, 0.f, 0.f, 0.f);
+            *reinterpret_cast<float4 *>(&Xs[lr + 8 * it][c4]) = x;
+            *reinterpret_cast<float4 *>(&Ps[lr + 8 * it][c4]) = p;
         }
         __syncthreads();
-        if (r0 + RED_RK < r_end) fetch(r0 + RED_RK);
+        if constexpr (decltype(more)::value) fetch(next, std::true_type());
 #pragma unroll
         for (int kp = 0; kp < RED_RK / 2; ++kp) {
             const int k = 2 * kp + h;
@@ -1601,6 +1602,14 @@ __global__ __launch_bounds__(256) void grad_big_mfma_kernel(const ReduceArgs com
             for (int r = 0; r < RED_RK; ++r) accb += Ps[r][wj + lane];
         }
         __syncthreads();
+    };
+    int64_t r0 = r_begin;
+    if (r0 + RED_RK <= r_end) fetch(r0, std::true_type());
+#pragma unroll 1
+    for (; r0 + RED_RK <= r_end; r0 += RED_RK) step(r0, r0 + 2 * RED_RK <= r_end ? r0 + RED_RK : r0, std::true_type(), std::true_type());
+    if (r0 < r_end) { // the rows left
+        fetch(r0, std::false_type());
+        step(r0, 0, std::false_type(), std::false_type());
     }
 
     float *out = a.partial + place.row_tile * a.stride;
@@ -1840,11 +1849,12 @@ int launch_grad_rows(const ReduceArgs &r, const ReduceBatch &b, int batch, int p
     const int64_t n_blocks = (r.n + r.rows_per_block - 1) / r.rows_per_block;
     if (big && r.w_in > 64 && r.w_out > 64) {
         // both wide: operands are re-read so often that staging them in LDS pays once there are enough 128 x 128 tiles for the chip
-        // (2.4 M rows 256 x 256: 3.65 ms, from registers 5.36; below the line 169 k rows 128 x 128: 166 us, from registers 154)
+        // (from LDS / from registers: 2.4 M rows 256 x 256 2.95 / 5.36 ms; 169 k rows 128 x 128, 166 tiles, 106 / 153 us; 98 tiles 104 / 106;
+        // 49 tiles 100 / 65)
         ReduceArgs t = r;
         t.j_tiles = (r.w_out + GB_T - 1) / GB_T;
         const int64_t i_tiles = (r.w_in + GB_T - 1) / GB_T;
-        if (n_blocks * i_tiles * t.j_tiles * batch >= 256) {
+        if (n_blocks * i_tiles * t.j_tiles * batch >= 128) {
             const int n_tiles = (int)(i_tiles * t.j_tiles);
             const int64_t blocks = (n_blocks + 7) / 8 * 8 * n_tiles;
             SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "weight gradients: grid too large");
