@@ -1369,7 +1369,10 @@ __global__ __launch_bounds__(256, 2) void bwd_strip32_kernel(const ReduceArgs rc
 // faster, nor is keeping two or three strips in flight) keep the staging registers and the
 // wave-private LDS tiles small enough for two wavefronts per SIMD beside the 128 accumulator
 // registers of the full-width variant, three for the half-width ones.
-template <int MI, int NJ, int SR, int WPS, bool SELF, bool NARROW> // SR: node rows per strip; WPS: wavefronts per SIMD to compile for
+// BLOCKS: the sums of grad_rows_kernel<.., 0> instead, for fewer rows: a workgroup takes rows_per_block rows, wavefront w the strips w, w + 4, ...
+// of them, and the four sums are added in order; column sums in row order.  Both products from one read of dHout, with 16-byte loads:
+// four slices of 169 k rows 64 x 64 172 -> 151 us, 32 x 64 107 -> 87.
+template <int MI, int NJ, int SR, int WPS, bool SELF, bool NARROW, bool BLOCKS = false> // SR: node rows per strip; WPS: wavefronts per SIMD to compile for
 __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs common, const ReduceBatch batch, int64_t n_waves)
 {
     const ReduceArgs a = slice_of(common, batch, blockIdx.y);
@@ -1384,9 +1387,13 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
     const int m = lane & 31, h = lane >> 5;
     const int ri = lane / LI, ci = (lane % LI) * 4; // coalesced layout of the w_in-wide operands
     const int rj = lane / LJ, cj = (lane % LJ) * 4; // and of dHout
-    const int64_t w_id = (int64_t)blockIdx.x * 4 + wave;
-    const int64_t n_full = a.n / SR; // whole strips
-    if (w_id >= n_waves) return; // uniform per wavefront; no workgroup barriers below (no more wavefronts than strips)
+    __shared__ __attribute__((aligned(16))) float red[BLOCKS ? 4 : 1][BLOCKS ? 32 * 32 : 1];
+    __shared__ float bsum[BLOCKS ? 4 : 1][BLOCKS ? 2 * WJ : 1];
+    const int64_t block_strips = a.rows_per_block / SR, left = (a.n + SR - 1) / SR - blockIdx.x * block_strips; // BLOCKS: strips of a block
+    const int64_t w_id = BLOCKS ? blockIdx.x * block_strips + wave : (int64_t)blockIdx.x * 4 + wave, hop = BLOCKS ? 4 : n_waves;
+    const int64_t past = BLOCKS ? blockIdx.x * block_strips + (left < block_strips ? left : block_strips) : (a.n + SR - 1) / SR; // strips end here
+    const int64_t n_full = past * SR <= a.n ? past : past - 1; // whole strips before it
+    if (!BLOCKS && w_id >= n_waves) return; // uniform per wavefront; no workgroup barriers in this form (no more wavefronts than strips)
     const LaneCols<NARROW> ic(ci, a.w_in), oc(cj, a.w_out);
     const bool place_i = a.w_in < WI, place_o = a.w_out < WJ; // uniform
     // what is absent is read from an operand and replaced, so that every strip has the same accesses
@@ -1463,8 +1470,13 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
             for (int j = 0; j < NJ; ++j) {
                 g[j] = gs[k][32 * j + m];
                 pp[j] = ((ms[k][j] >> m) & 1u) ? g[j] : 0.f;
-                sum_p[j] += pp[j];
-                sum_g[j] += g[j];
+                if constexpr (BLOCKS) { // rows in order
+                    sum_p[j] = (sum_p[j] + pp[j]) + __shfl_xor(pp[j], 32, 64);
+                    if (SELF) sum_g[j] = (sum_g[j] + g[j]) + __shfl_xor(g[j], 32, 64);
+                } else {
+                    sum_p[j] += pp[j];
+                    sum_g[j] += g[j];
+                }
             }
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
@@ -1481,13 +1493,44 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
         }
         __builtin_amdgcn_wave_barrier();
     };
-    int64_t strip = w_id; // wavefront w takes strips w, w + n_waves, ...
+    int64_t strip = w_id; // wavefront w takes strips w, w + hop, ...
     if (strip < n_full) fetch(strip, std::true_type());
 #pragma unroll 1
-    for (; strip < n_full; strip += n_waves) strip_step(strip, strip + n_waves < n_full ? strip + n_waves : strip, std::true_type());
-    if (strip == n_full && a.n % SR != 0) { // the rows left
+    for (; strip < n_full; strip += hop) strip_step(strip, strip + hop < n_full ? strip + hop : strip, std::true_type());
+    if (strip == n_full && strip < past) { // the rows left
         fetch(strip, std::false_type());
         strip_step(strip, 0, std::false_type());
+    }
+    if constexpr (BLOCKS) {
+        const int tid = threadIdx.x, ww = a.w_in * a.w_out;
+        float *out = a.partial + (int64_t)blockIdx.x * a.stride;
+        if (h == 0) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                bsum[wave][32 * j + m] = sum_p[j];
+                bsum[wave][WJ + 32 * j + m] = sum_g[j];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < (SELF ? 2 : 1); ++s)
+#pragma unroll
+            for (int ti = 0; ti < MI; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < NJ; ++tj) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) red[wave][(8 * (r / 4) + 4 * h + (r % 4)) * 32 + m] = s ? accS[ti][tj][r] : accA[ti][tj][r];
+                    __syncthreads();
+                    const int i = 32 * ti + (tid >> 3), j = 32 * tj + 4 * (tid & 7); // four columns of a row per thread
+                    floatx4 v = *reinterpret_cast<const floatx4 *>(&red[0][4 * tid]);
+#pragma unroll
+                    for (int q = 1; q < 4; ++q) v += *reinterpret_cast<const floatx4 *>(&red[q][4 * tid]);
+                    if (i < a.w_in) store_cols4<false>(out + s * ww + (int64_t)i * a.w_out + j, make_float4(v[0], v[1], v[2], v[3]), true, a.w_out - j);
+                    __syncthreads();
+                }
+        const int q = tid / WJ, col = tid % WJ; // 0: sums of dP, 1: of dHout
+        if (q < (SELF ? 2 : 1) && col < a.w_out)
+            out[(a.compact ? ww : 2 * ww) + q * a.w_out + col] = ((bsum[0][tid] + bsum[1][tid]) + bsum[2][tid]) + bsum[3][tid];
+        return;
     }
     float *out = a.partial + w_id * a.stride;
     const int ww = a.w_in * a.w_out;
@@ -1847,6 +1890,19 @@ int launch_grad_rows(const ReduceArgs &r, const ReduceBatch &b, int batch, int p
 {
     int mi = r.w_in > 32 ? 2 : 1, nj = r.w_out > 32 ? 2 : 1;
     const int64_t n_blocks = (r.n + r.rows_per_block - 1) / r.rows_per_block;
+    if (!big && r.w_in <= 64 && r.w_out <= 64 && r.w_in >= 4 && r.w_out >= 4 && n_blocks * batch >= (products == 2 ? 160 : 512)) {
+        // From enough workgroups on: a workgroup does both products, so there are half as many or fewer (pairs 64 x 64, here / by grad_rows_kernel:
+        // 79 workgroups 21.5 / 16.3 us, 157 22.9 / 23.3, 235 24.0 / 30.2, 662 47.3 / 57.5; single products 127 36.3 / 31.8, 977 121 / 147).
+        const dim3 grid((unsigned)n_blocks, (unsigned)batch);
+        launch_grad_strip(products == 2, false, [&](auto s, auto) {
+            if (mi == 1 && nj == 1) grad_strip64_kernel<1, 1, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
+            else if (mi == 1) grad_strip64_kernel<1, 2, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
+            else if (nj == 1) grad_strip64_kernel<2, 1, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
+            else grad_strip64_kernel<2, 2, 8, 2, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
+        });
+        SG_LAUNCH_CHECK();
+        return SLICEGCN_OK;
+    }
     if (big && r.w_in > 64 && r.w_out > 64) {
         // both wide: operands are re-read so often that staging them in LDS pays once there are enough 128 x 128 tiles for the chip
         // (from LDS / from registers: 2.4 M rows 256 x 256 2.95 / 5.36 ms; 169 k rows 128 x 128, 166 tiles, 106 / 153 us; 98 tiles 104 / 106;
