@@ -41,7 +41,9 @@ struct PairArgs {
 // The same products for a batch of slice models (equal shapes and leading dimensions): grid row y works on slice y, with
 // the pointers taken from here.  Small graphs need it: their kernels last microseconds and fill a fraction of the chip.
 constexpr int BATCH = SPMM_BATCH;
-constexpr int64_t STRIP64_ROWS = 262144; // from here on layers up to 64 wide take the strip kernel
+// From so many rows of all slices of a launch on, layers up to 64 wide take the strip kernel (64 -> 64 with self term, strips / pair_rows_kernel:
+// four slices of 66 k rows forward 75 / 71 us, backward 69 / 78; of 169 k rows 149 / 157 and 130 / 172).
+constexpr int64_t STRIP64_ROWS = 262144;
 struct PairPtrs {
     const float *A1, *A2, *B1, *B2, *bias1, *bias2, *enc;
     float *O1, *O2;
@@ -124,7 +126,8 @@ __device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int wi
 // four k of a column, so that a 16-byte read feeds four instructions.  The weights are the A operand and the rows the B operand:
 // a lane then holds four consecutive columns of one row in four registers, stores them as 16 bytes and collects the
 // activation bits of its row without votes.
-// The order is that of the strip kernels: chains over all of k, a step takes k and k + 4, one chain per product.  Whether an
+// The order is that of the strip kernels: chains over all of k, a step takes k and k + 4, one chain per product (for the row factor of dZ see
+// scale_operand there).  Whether an
 // activation passes depends on the last bit of its sum where that is near zero (a few in 10^8), and then a row's gradient changes
 // by a whole term: every kernel and size gives the same bits for the same operands.  (Operands split into three bf16
 // terms on the bf16 matrix cores were as exact against fp64 and faster, 2.4 M rows 256 -> 256 2.16 ms, but rounded differently.)
@@ -596,8 +599,13 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     const float *s2 = PAIR && a.scale2 ? a.scale2 : a.A1, *so = a.scale_o1 ? a.scale_o1 : a.A1;
     const int64_t s2_ld = PAIR && a.scale2 ? 1 : 0, so_ld = a.scale_o1 ? 1 : 0;
 
+    // The row factor of dZ: on the operand on fewer rows, as pair_rows_kernel has it, on the result on many.  The two differ in the last bit;
+    // a gradient keeps its bits however many slices share a launch.
+    const bool scale_operand = BWD && a.n < STRIP64_ROWS;
+
     float4 p1[PK], p2[PAIR ? PK : 1];
     uint32_t pw[KC];                // backward: activation words of strip row m
+    float ps = 1.f;                 // and its row factor
     float f2[PAIR ? PK : 1], fo[PN]; // factors of the rows this lane loads and stores
     auto fetch = [&](int64_t strip, auto whole) {
         const int64_t r0 = strip * 32, end = a.n - 1;
@@ -614,6 +622,7 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
         if (BWD) {
 #pragma unroll
             for (int w = 0; w < KC; ++w) pw[w] = words[row(r0 + m) * word_ld + (32 * w < a.K ? w : 0)];
+            ps = so[row(r0 + m) * so_ld];
         }
 #pragma unroll
         for (int it = 0; it < PN; ++it) fo[it] = so[row(r0 + rn + RN * it) * so_ld];
@@ -652,7 +661,8 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
         constexpr bool WHOLE = decltype(whole)::value;
         float out_f[PN]; // output factors of this strip's rows (the fetch below overwrites fo)
 #pragma unroll
-        for (int it = 0; it < PN; ++it) out_f[it] = so_ld ? fo[it] : 1.f;
+        for (int it = 0; it < PN; ++it) out_f[it] = so_ld && !scale_operand ? fo[it] : 1.f;
+        const float in_f = BWD && so_ld && scale_operand ? ps : 1.f;
         if (place) {
 #pragma unroll
             for (int it = 0; it < PK; ++it) {
@@ -691,7 +701,7 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
                 for (int i = 0; i < 4; ++i) {
                     const int kk = 8 * q + 4 * h + i;
                     const float g = pick(a1[q], i);
-                    const float gp = ((word[q >> 2] >> (8 * (q & 3) + 4 * h + i)) & 1u) ? g : 0.f;
+                    const float gp = (((word[q >> 2] >> (8 * (q & 3) + 4 * h + i)) & 1u) ? g : 0.f) * in_f;
 #pragma unroll
                     for (int t = 0; t < NC; ++t)
                         acc1[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(gp, W1s[kk][32 * t + m], acc1[t], 0, 0, 0);
@@ -771,7 +781,7 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
             }
             __builtin_amdgcn_wave_barrier();
         };
-        store_tile(acc1, a.O1, a.ldo1, so_ld != 0);
+        store_tile(acc1, a.O1, a.ldo1, so_ld != 0 && !scale_operand);
         if constexpr (BWD && TWO) {
             if (a.O2) store_tile(acc2, a.O2, a.ldo2, false);
         }
@@ -855,9 +865,11 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
         SG_LAUNCH_CHECK();
         return SLICEGCN_OK;
     }
-    if (a.K >= 4 && a.K <= 64 && a.Nout <= 64 && a.n >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
-        // as many workgroups as the chip holds at once (two per CU): each stages the weights once
-        const dim3 grid((unsigned)(strip_blocks < 512 ? strip_blocks : 512), by);
+    if (a.K >= 4 && a.K <= 64 && a.Nout <= 64 && a.n * batch >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
+        // as many workgroups as the chip holds at once (two per CU): each stages the weights once (four slices of 169 k rows with 2048
+        // workgroups: forward 164 us instead of 149, backward 151 instead of 130)
+        const int64_t most = 512 / batch;
+        const dim3 grid((unsigned)(strip_blocks < most ? strip_blocks : most), by);
         if (a.K <= 32) launch_strip64<1, 2, BWD>(a, b, grid, stream);
         else if (a.Nout <= 32) launch_strip64<2, 1, BWD>(a, b, grid, stream);
         else launch_strip64<2, 2, BWD>(a, b, grid, stream);

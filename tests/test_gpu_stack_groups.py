@@ -114,3 +114,32 @@ def test_encoding_fused_or_not_after_a_pass(graph):
     for a, b in zip(fused, outputs(st)):
         # the same sums in another order: one addition more per element forward, column sums of N rows backward
         assert float((a - b).abs().max()) <= 3e-6 * float(a.abs().max()) * (1 if a.shape[0] == N else 16)
+
+
+@pytest.mark.parametrize("first,hs", [(37, 64), (64, 40), (30, 30)])
+def test_group_takes_the_strip_kernels_and_one_slice_does_not(monkeypatch, first, hs):
+    """Together the slices of a launch have rows enough for the strip kernels, one alone has not: the same bits."""
+    n, k = 66_003, 4
+    rng = np.random.default_rng(first)
+    g = sg.slicegcn_build_norm_csr(dev(rng.integers(0, n, 3 * n), torch.int64), dev(rng.integers(0, n, 3 * n), torch.int64), n)
+    runs = []
+    for limit in (stack_module.GROUP_BYTES, 0):
+        monkeypatch.setattr(stack_module, "GROUP_BYTES", limit)
+        gen = torch.Generator(device="cuda").manual_seed(first)
+        r = lambda *s: torch.randn(s, generator=gen, device="cuda")
+        X = torch.zeros((n, 64), device="cuda")
+        X[:, :first] = r(n, first)
+        st = SliceStack(g, n, k, first, hs, L, shared_input=X)
+        st.E.copy_(r(k, hs))
+        for i in range(k):
+            for l, (wi, wo) in enumerate(st.widths):
+                st.set_params(i, l, r(wi, wo) * 0.1, r(wo), r(wi, wo) * 0.1, r(wo))
+        assert st.group == (k if limit else 1)
+        dH = r(n, k * hs)
+        st.forward()
+        st.backward(dH)
+        runs.append([st.Hcat.clone(), st.dE.clone(), st.dXin[:, :first].clone()] +
+                    [gr[key].clone() for per_slice in st.grads for gr in per_slice for key in ("dW_agg", "db", "dW_self", "db_self")])
+    g.destroy()
+    for a, b in zip(*runs):
+        assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
