@@ -92,9 +92,8 @@ typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4))); // 16-b
 // tiles of one row tile run back to back on the same XCD (workgroup b goes to XCD b mod 8), so the rows are fetched from memory
 // once and re-read from L2.  The last group of 8 row tiles may be partial.
 struct TilePlace { int64_t row_tile; int col_tile; };
-__device__ inline TilePlace tile_place(int n_col_tiles)
+__device__ inline TilePlace tile_place(int64_t b, int n_col_tiles)
 {
-    const int64_t b = blockIdx.x;
     return TilePlace{(b / (8 * n_col_tiles)) * 8 + (b % 8), (int)((b / 8) % n_col_tiles)};
 }
 
@@ -134,9 +133,8 @@ __device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int wi
 // Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 2.98 ms = 108 TFLOP/s (a kernel with rows and weights in LDS: 3.71), 169 k rows
 // 0.238 (0.288); slice layers 64 -> 64 with self term, 169 k rows: 47 us (61).
 template <int NT, bool TWO, bool BWD>
-__global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair_rows_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+__device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, int n_col_tiles)
 {
-    const PairArgs a = slice_of(common, batch);
     constexpr int BN = NT * 32, KC = 32, GS = BN + 4; // GS: units per group of four k (padded: conflict-free writes and reads)
     __shared__ floatx4 Bs[2][KC / 4][GS];
     __shared__ __attribute__((aligned(16))) float bias_s[2][BN];
@@ -144,9 +142,9 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
     const int wave = tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
     // tile_place in 32 bits: the 64-bit division is as long as a small layer's loads
-    const uint32_t group = blockIdx.x / (8u * n_col_tiles);
-    const int64_t row_tile = (int64_t)group * 8 + blockIdx.x % 8;
-    const int col0 = (int)(blockIdx.x / 8 - group * n_col_tiles) * BN;
+    const uint32_t group = wg / (8u * n_col_tiles);
+    const int64_t row_tile = (int64_t)group * 8 + wg % 8;
+    const int col0 = (int)(wg / 8 - group * n_col_tiles) * BN;
     if (row_tile * 128 >= a.n) return; // uniform per workgroup
     const int chunks = (a.K + KC - 1) / KC, total = TWO ? 2 * chunks : chunks;
 
@@ -331,6 +329,11 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
         store_all(a.O1, a.ldo1, a.scale_o1 ? a.scale_o1[row] : 1.f);
     }
 }
+template <int NT, bool TWO, bool BWD>
+__global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair_rows_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+{
+    pair_rows_tile<NT, TWO, BWD>(slice_of(common, batch), blockIdx.x, n_col_tiles);
+}
 
 // Four consecutive floats of an operand row as a strip kernel's lane loads them.  The lane that owns columns [c, c + 4) loads
 // from column min(c, K - 4) on, so that nothing outside the row's K columns is read and no load depends on a branch: a loop of such loads
@@ -389,9 +392,8 @@ template <bool WHOLE> __device__ inline void store_cols4(float *o, const float4 
 // product in registers.  No workgroup barrier anywhere: a wavefront only touches its own tile, and
 // its LDS accesses execute in program order.
 template <bool BWD, bool TWO>
-__global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common, const PairBatch batch)
+__device__ __forceinline__ void pair_strip32(const PairArgs &a, uint32_t wg, uint32_t n_wg) // workgroup wg of n_wg
 {
-    const PairArgs a = slice_of(common, batch);
     constexpr int ST = 36;
     constexpr bool PAIR = TWO && !BWD; // two operand strips
     __shared__ __attribute__((aligned(16))) float T1[4][32][ST];
@@ -405,7 +407,7 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common
     float (*t2)[ST] = T2[PAIR ? wave : 0];
 
     const int64_t n_full = a.n / 32; // whole strips
-    const int64_t first = (int64_t)blockIdx.x * 4 + wave, step = (int64_t)gridDim.x * 4;
+    const int64_t first = (int64_t)wg * 4 + wave, step = (int64_t)n_wg * 4;
     if (first * 32 >= a.n) return; // uniform per wavefront
     // what is absent is read from an operand and replaced, so that every strip has the same accesses
     const uint32_t *words = BWD && a.mask ? a.mask : reinterpret_cast<const uint32_t *>(a.A1);
@@ -563,6 +565,11 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common
         if (strip != first) fetch(strip, std::false_type());
         strip_step(strip, 0, std::false_type());
     }
+}
+template <bool BWD, bool TWO>
+__global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common, const PairBatch batch)
+{
+    pair_strip32<BWD, TWO>(slice_of(common, batch), blockIdx.x, gridDim.x);
 }
 
 // Layers up to 64 wide (4 <= K <= 32 * KC, at most 32 * NC output columns) on many rows: a wavefront owns strips of 32 rows, reads a strip with
@@ -844,37 +851,25 @@ int check_in_place(const PairArgs *list, int batch)
     return SLICEGCN_OK;
 }
 
-// `list`: one entry per slice model of the batch (1 to BATCH, equal but for the pointers)
-template <bool BWD>
-int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
+// Which kernel forms the products, with how many workgroups per slice
+struct PairForm {
+    enum Kernel { STRIP32, STRIP64, ROWS } kernel;
+    bool two;
+    int64_t blocks;
+    int nt, n_col; // ROWS: tiles of 32 columns a workgroup takes, workgroups along the columns
+};
+inline PairForm pair_form(const PairArgs *list, int batch)
 {
-    if (int rc = check_in_place(list, batch)) return rc;
     const PairArgs &a = list[0];
-    PairBatch b;
-    for (int i = 0; i < BATCH; ++i) {
-        const PairArgs &x = list[i < batch ? i : 0];
-        b.p[i] = PairPtrs{x.A1, x.A2, x.B1, x.B2, x.bias1, x.bias2, x.enc, x.O1, x.O2, x.mask};
-    }
-    const unsigned by = (unsigned)batch;
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
     const int64_t strips = (a.n + 31) / 32, strip_blocks = (strips + 3) / 4;
-    if (a.K >= 4 && a.K <= 32 && a.Nout <= 32) { // narrowest layers: per-wavefront strips, no barriers
-        const dim3 grid((unsigned)(strip_blocks < 2048 ? strip_blocks : 2048), by);
-        if (two) pair_strip32_kernel<BWD, true><<<grid, 256, 0, stream>>>(a, b);
-        else pair_strip32_kernel<BWD, false><<<grid, 256, 0, stream>>>(a, b);
-        SG_LAUNCH_CHECK();
-        return SLICEGCN_OK;
-    }
+    if (a.K >= 4 && a.K <= 32 && a.Nout <= 32) // narrowest layers: per-wavefront strips, no barriers
+        return PairForm{PairForm::STRIP32, two, strip_blocks < 2048 ? strip_blocks : 2048, 0, 0};
     if (a.K >= 4 && a.K <= 64 && a.Nout <= 64 && a.n * batch >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
         // as many workgroups as the chip holds at once (two per CU): each stages the weights once (four slices of 169 k rows with 2048
         // workgroups: forward 164 us instead of 149, backward 151 instead of 130)
         const int64_t most = 512 / batch;
-        const dim3 grid((unsigned)(strip_blocks < most ? strip_blocks : most), by);
-        if (a.K <= 32) launch_strip64<1, 2, BWD>(a, b, grid, stream);
-        else if (a.Nout <= 32) launch_strip64<2, 1, BWD>(a, b, grid, stream);
-        else launch_strip64<2, 2, BWD>(a, b, grid, stream);
-        SG_LAUNCH_CHECK();
-        return SLICEGCN_OK;
+        return PairForm{PairForm::STRIP64, two, strip_blocks < most ? strip_blocks : most, 0, 0};
     }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
@@ -887,17 +882,50 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
     if (row_tiles * ((tiles + nt - 1) / nt) * batch < 2048) nt = 1;
     if (tiles > nt && in_place(list, batch)) nt = tiles; // whole rows
     const int n_col = (tiles + nt - 1) / nt;
-    const int64_t blocks = (row_tiles + 7) / 8 * 8 * n_col;
-    SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
-    const dim3 grid((unsigned)blocks, by);
-    switch (2 * nt + (two ? 1 : 0)) {
-    case 2: pair_rows_kernel<1, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    case 3: pair_rows_kernel<1, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    case 4: pair_rows_kernel<2, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    case 5: pair_rows_kernel<2, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    case 6: pair_rows_kernel<3, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    case 7: pair_rows_kernel<3, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-    default: pair_rows_kernel<4, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+    return PairForm{PairForm::ROWS, two, (row_tiles + 7) / 8 * 8 * n_col, nt, n_col};
+}
+inline PairBatch pair_batch(const PairArgs *list, int batch)
+{
+    PairBatch b;
+    for (int i = 0; i < BATCH; ++i) {
+        const PairArgs &x = list[i < batch ? i : 0];
+        b.p[i] = PairPtrs{x.A1, x.A2, x.B1, x.B2, x.bias1, x.bias2, x.enc, x.O1, x.O2, x.mask};
+    }
+    return b;
+}
+
+// `list`: one entry per slice model of the batch (1 to BATCH, equal but for the pointers)
+template <bool BWD>
+int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
+{
+    if (int rc = check_in_place(list, batch)) return rc;
+    const PairArgs &a = list[0];
+    const PairBatch b = pair_batch(list, batch);
+    const PairForm f = pair_form(list, batch);
+    SG_REQUIRE(f.blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
+    const dim3 grid((unsigned)f.blocks, (unsigned)batch);
+    const int n_col = f.n_col;
+    switch (f.kernel) {
+    case PairForm::STRIP32:
+        if (f.two) pair_strip32_kernel<BWD, true><<<grid, 256, 0, stream>>>(a, b);
+        else pair_strip32_kernel<BWD, false><<<grid, 256, 0, stream>>>(a, b);
+        break;
+    case PairForm::STRIP64:
+        if (a.K <= 32) launch_strip64<1, 2, BWD>(a, b, grid, stream);
+        else if (a.Nout <= 32) launch_strip64<2, 1, BWD>(a, b, grid, stream);
+        else launch_strip64<2, 2, BWD>(a, b, grid, stream);
+        break;
+    case PairForm::ROWS:
+        switch (2 * f.nt + (f.two ? 1 : 0)) {
+        case 2: pair_rows_kernel<1, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 3: pair_rows_kernel<1, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 4: pair_rows_kernel<2, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 5: pair_rows_kernel<2, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 6: pair_rows_kernel<3, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        case 7: pair_rows_kernel<3, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        default: pair_rows_kernel<4, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
+        }
+        break;
     }
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -953,9 +981,8 @@ __device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatc
 // 256 x 47 1.93 -> 1.40 ms, 60 k rows 64 x 64 46 -> 22 us.  Bound by the loads, one register of two rows' pieces at a time.
 // Grid: x = 8 row blocks x all tiles per group of workgroups (a row block's tiles meet on one XCD), y = slice, z = product.
 template <int MI, int NJ, int WJ>
-__global__ __launch_bounds__(256, 3) void grad_rows_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
+__device__ __forceinline__ void grad_rows_tile(const ReduceArgs &a, int64_t wg, bool self, int n_tiles) // self: the product Hin^T dHout
 {
-    const ReduceArgs a = slice_of(common, batch, blockIdx.y);
     constexpr bool SPLIT = WJ == 0;
     constexpr int WI = SPLIT ? 1 : 4 / (SPLIT ? 1 : WJ);
     constexpr int PAIRS = MI * NJ == 1 ? 8 : 4; // pairs of rows a wavefront loads at a time
@@ -965,14 +992,13 @@ __global__ __launch_bounds__(256, 3) void grad_rows_kernel(const ReduceArgs comm
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const TilePlace place = tile_place(n_tiles);
+    const TilePlace place = tile_place(wg, n_tiles);
     const int64_t block = place.row_tile, r_begin = block * a.rows_per_block;
     if (r_begin >= a.n) return; // uniform per workgroup
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
-    const int i_base = (place.col_tile / common.j_tiles) * (WI * MI * 32) + (SPLIT ? 0 : wave / (SPLIT ? 1 : WJ) * (MI * 32));
-    const int j_base = (place.col_tile % common.j_tiles) * ((SPLIT ? 1 : WJ) * NJ * 32) + (SPLIT ? 0 : wave % (SPLIT ? 1 : WJ) * (NJ * 32));
+    const int i_base = (place.col_tile / a.j_tiles) * (WI * MI * 32) + (SPLIT ? 0 : wave / (SPLIT ? 1 : WJ) * (MI * 32));
+    const int j_base = (place.col_tile % a.j_tiles) * ((SPLIT ? 1 : WJ) * NJ * 32) + (SPLIT ? 0 : wave % (SPLIT ? 1 : WJ) * (NJ * 32));
     if (!SPLIT && (i_base >= a.w_in || j_base >= a.w_out)) return; // uniform per wavefront; no barriers in this form
-    const bool self = blockIdx.z == 1; // the product Hin^T dHout
     const float *X = self ? a.Hin : a.Z;
     const int64_t ldx = self ? a.ldi : a.ldz;
     const float *x_scale = self ? a.hin_scale : nullptr;
@@ -1116,6 +1142,11 @@ __global__ __launch_bounds__(256, 3) void grad_rows_kernel(const ReduceArgs comm
                 if (j_base + 32 * t + m < a.w_out) out_b[j_base + 32 * t + m] = accb[t];
         }
     }
+}
+template <int MI, int NJ, int WJ>
+__global__ __launch_bounds__(256, 3) void grad_rows_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
+{
+    grad_rows_tile<MI, NJ, WJ>(slice_of(common, batch, blockIdx.y), blockIdx.x, blockIdx.z == 1, n_tiles);
 }
 
 // Partial weight gradients of the narrowest layers (w_in, w_out <= 32, large n): every wavefront owns
@@ -1583,7 +1614,7 @@ constexpr int GB_T = 128;
 __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
 {
     const ReduceArgs a = slice_of(common, batch, blockIdx.y);
-    const TilePlace place = tile_place(n_tiles);
+    const TilePlace place = tile_place(blockIdx.x, n_tiles);
     __shared__ __attribute__((aligned(16))) float Xs[RED_RK][GB_T];
     __shared__ __attribute__((aligned(16))) float Ps[RED_RK][GB_T];
     const int tid = threadIdx.x;
@@ -1879,64 +1910,147 @@ template <class F> void launch_grad_strip(bool self, bool narrow, F launch)
     else launch(std::false_type(), std::false_type());
 }
 
-// Launches grad_rows_kernel for `products` products (r.rows_per_block rows a workgroup).  Tiles of 64 x 64 per workgroup or wavefront
-// as far as the widths go; 32 x 32, whose operands are loaded twice as often, where those would leave fewer than two workgroups per CU.
-template <int WJ>
-int launch_grad_tiles(ReduceArgs r, const ReduceBatch &b, int batch, int products, int mi, int nj, hipStream_t stream)
-{
-    const int ti = (WJ ? 4 / (WJ ? WJ : 1) : 1) * mi * 32, tj = (WJ ? WJ : 1) * nj * 32;
-    const int64_t n_blocks = (r.n + r.rows_per_block - 1) / r.rows_per_block;
-    r.j_tiles = (r.w_out + tj - 1) / tj;
-    const int n_tiles = (r.w_in + ti - 1) / ti * r.j_tiles;
-    const int64_t blocks = (n_blocks + 7) / 8 * 8 * n_tiles;
-    SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "weight gradients: grid too large");
-    const dim3 grid((unsigned)blocks, (unsigned)batch, (unsigned)products);
-    if (mi == 1 && nj == 1) grad_rows_kernel<1, 1, WJ><<<grid, 256, 0, stream>>>(r, b, n_tiles);
-    else if (mi == 1) grad_rows_kernel<1, 2, WJ><<<grid, 256, 0, stream>>>(r, b, n_tiles);
-    else if (nj == 1) grad_rows_kernel<2, 1, WJ><<<grid, 256, 0, stream>>>(r, b, n_tiles);
-    else grad_rows_kernel<2, 2, WJ><<<grid, 256, 0, stream>>>(r, b, n_tiles);
-    SG_LAUNCH_CHECK();
-    return SLICEGCN_OK;
-}
-int launch_grad_rows(const ReduceArgs &r, const ReduceBatch &b, int batch, int products, bool big, hipStream_t stream)
+// Which kernel forms the partial weight gradients (r.rows_per_block rows a workgroup), with how many workgroups per slice and product
+struct GradForm {
+    enum Kernel { STRIPS, LDS, ROWS } kernel;
+    int64_t blocks;
+    int mi, nj, wj;       // ROWS: its template arguments
+    int j_tiles, n_tiles; // LDS, ROWS: output tiles along w_out, and in all
+};
+inline GradForm grad_form(const ReduceArgs &r, int batch, int products, bool big, bool from_lds = true) // from_lds: LDS where it pays alone
 {
     int mi = r.w_in > 32 ? 2 : 1, nj = r.w_out > 32 ? 2 : 1;
     const int64_t n_blocks = (r.n + r.rows_per_block - 1) / r.rows_per_block;
-    if (!big && r.w_in <= 64 && r.w_out <= 64 && r.w_in >= 4 && r.w_out >= 4 && n_blocks * batch >= (products == 2 ? 160 : 512)) {
-        // From enough workgroups on: a workgroup does both products, so there are half as many or fewer (pairs 64 x 64, here / by grad_rows_kernel:
-        // 79 workgroups 21.5 / 16.3 us, 157 22.9 / 23.3, 235 24.0 / 30.2, 662 47.3 / 57.5; single products 127 36.3 / 31.8, 977 121 / 147).
-        const dim3 grid((unsigned)n_blocks, (unsigned)batch);
-        launch_grad_strip(products == 2, false, [&](auto s, auto) {
-            if (mi == 1 && nj == 1) grad_strip64_kernel<1, 1, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
-            else if (mi == 1) grad_strip64_kernel<1, 2, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
-            else if (nj == 1) grad_strip64_kernel<2, 1, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
-            else grad_strip64_kernel<2, 2, 8, 2, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
-        });
-        SG_LAUNCH_CHECK();
-        return SLICEGCN_OK;
+    // From enough workgroups on: a workgroup does both products, so there are half as many or fewer (pairs 64 x 64, strips / grad_rows_kernel:
+    // 79 workgroups 21.5 / 16.3 us, 157 22.9 / 23.3, 235 24.0 / 30.2, 662 47.3 / 57.5; single products 127 36.3 / 31.8, 977 121 / 147).
+    if (!big && r.w_in <= 64 && r.w_out <= 64 && r.w_in >= 4 && r.w_out >= 4 && n_blocks * batch >= (products == 2 ? 160 : 512))
+        return GradForm{GradForm::STRIPS, n_blocks, mi, nj, 0, 1, 1};
+    auto tiled = [&](GradForm::Kernel kernel, int ti, int tj, int wj) { // output tiles of ti x tj per workgroup
+        const int j_tiles = (r.w_out + tj - 1) / tj, n_tiles = (r.w_in + ti - 1) / ti * j_tiles;
+        return GradForm{kernel, (n_blocks + 7) / 8 * 8 * n_tiles, mi, nj, wj, j_tiles, n_tiles};
+    };
+    // both wide: operands are re-read so often that staging them in LDS pays once there are enough 128 x 128 tiles for the chip
+    // (from LDS / from registers: 2.4 M rows 256 x 256 2.95 / 5.36 ms; 169 k rows 128 x 128, 166 tiles, 106 / 153 us; 98 tiles 104 / 106;
+    // 49 tiles 100 / 65)
+    if (from_lds && big && r.w_in > 64 && r.w_out > 64) {
+        const GradForm f = tiled(GradForm::LDS, GB_T, GB_T, 0);
+        if (n_blocks * f.n_tiles * batch >= 128) return f;
     }
-    if (big && r.w_in > 64 && r.w_out > 64) {
-        // both wide: operands are re-read so often that staging them in LDS pays once there are enough 128 x 128 tiles for the chip
-        // (from LDS / from registers: 2.4 M rows 256 x 256 2.95 / 5.36 ms; 169 k rows 128 x 128, 166 tiles, 106 / 153 us; 98 tiles 104 / 106;
-        // 49 tiles 100 / 65)
-        ReduceArgs t = r;
-        t.j_tiles = (r.w_out + GB_T - 1) / GB_T;
-        const int64_t i_tiles = (r.w_in + GB_T - 1) / GB_T;
-        if (n_blocks * i_tiles * t.j_tiles * batch >= 128) {
-            const int n_tiles = (int)(i_tiles * t.j_tiles);
-            const int64_t blocks = (n_blocks + 7) / 8 * 8 * n_tiles;
-            SG_REQUIRE(blocks <= INT32_MAX, SLICEGCN_ERANGE, "weight gradients: grid too large");
-            grad_big_mfma_kernel<<<dim3((unsigned)blocks, (unsigned)batch), 256, 0, stream>>>(t, b, n_tiles);
-            SG_LAUNCH_CHECK();
-            return SLICEGCN_OK;
-        }
-    }
+    // Tiles of 64 x 64 per workgroup or wavefront as far as the widths go; 32 x 32, whose operands are loaded twice as often, where
+    // those would leave fewer than two workgroups per CU.
     const int64_t tiles = (int64_t)((r.w_in + 32 * mi - 1) / (32 * mi)) * ((r.w_out + 32 * nj - 1) / (32 * nj));
     if (n_blocks * tiles * products * batch < (big ? 4 : 1) * 512) mi = nj = 1;
-    if (!big) return launch_grad_tiles<0>(r, b, batch, products, mi, nj, stream);
+    if (!big) return tiled(GradForm::ROWS, 32 * mi, 32 * nj, 0);
     // the wavefronts of a workgroup share their operands through L1: along both widths, or along w_in if one covers w_out
-    if (r.w_out <= 32 * nj) return launch_grad_tiles<1>(r, b, batch, products, mi, nj, stream);
-    return launch_grad_tiles<2>(r, b, batch, products, mi, nj, stream);
+    if (r.w_out <= 32 * nj) return tiled(GradForm::ROWS, 128 * mi, 32 * nj, 1);
+    return tiled(GradForm::ROWS, 64 * mi, 64 * nj, 2);
+}
+
+template <int WJ> void launch_grad_tiles(const GradForm &f, const ReduceArgs &r, const ReduceBatch &b, dim3 grid, hipStream_t stream)
+{
+    if (f.mi == 1 && f.nj == 1) grad_rows_kernel<1, 1, WJ><<<grid, 256, 0, stream>>>(r, b, f.n_tiles);
+    else if (f.mi == 1) grad_rows_kernel<1, 2, WJ><<<grid, 256, 0, stream>>>(r, b, f.n_tiles);
+    else if (f.nj == 1) grad_rows_kernel<2, 1, WJ><<<grid, 256, 0, stream>>>(r, b, f.n_tiles);
+    else grad_rows_kernel<2, 2, WJ><<<grid, 256, 0, stream>>>(r, b, f.n_tiles);
+}
+int launch_grad_rows(ReduceArgs r, const ReduceBatch &b, int batch, int products, bool big, hipStream_t stream)
+{
+    const GradForm f = grad_form(r, batch, products, big);
+    SG_REQUIRE(f.blocks <= INT32_MAX, SLICEGCN_ERANGE, "weight gradients: grid too large");
+    r.j_tiles = f.j_tiles;
+    dim3 grid((unsigned)f.blocks, (unsigned)batch);
+    switch (f.kernel) {
+    case GradForm::STRIPS:
+        launch_grad_strip(products == 2, false, [&](auto s, auto) {
+            if (f.mi == 1 && f.nj == 1) grad_strip64_kernel<1, 1, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
+            else if (f.mi == 1) grad_strip64_kernel<1, 2, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
+            else if (f.nj == 1) grad_strip64_kernel<2, 1, 8, 3, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
+            else grad_strip64_kernel<2, 2, 8, 2, s.value, false, true><<<grid, 256, 0, stream>>>(r, b, 0);
+        });
+        break;
+    case GradForm::LDS:
+        grad_big_mfma_kernel<<<grid, 256, 0, stream>>>(r, b, f.n_tiles);
+        break;
+    case GradForm::ROWS:
+        grid.z = (unsigned)products;
+        if (f.wj == 0) launch_grad_tiles<0>(f, r, b, grid, stream);
+        else if (f.wj == 1) launch_grad_tiles<1>(f, r, b, grid, stream);
+        else launch_grad_tiles<2>(f, r, b, grid, stream);
+        break;
+    }
+    SG_LAUNCH_CHECK();
+    return SLICEGCN_OK;
+}
+
+// Weight gradients and the products of the input gradients read the same dHout and do not depend on each other: on few rows, where
+// either is a chain of a few dependent loads in a fraction of the chip, one launch does both.  The first `grads` workgroups of a slice form
+// weight gradients (products x grad_x), the others what pair_strip32_kernel (STRIP) or pair_rows_kernel would.  Backward passes of dense
+// layers, in two launches / one: 1000 rows 64 -> 8 10.1 / 6.8 us, 2048 rows 64 -> 64 11.9 / 8.8, 20 k rows 64 -> 64 27.2 / 23.1, 60 k rows
+// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1; of slice layers 2048 rows 64 -> 32 18.5 / 12.9, 30 k rows 64 -> 64 39.5 / 35.9.
+template <int WJ, bool STRIP, bool TWO>
+__global__ __launch_bounds__(256, 3) void grad_pair_kernel(const ReduceArgs r, const ReduceBatch rb, const PairArgs p, const PairBatch pb,
+                                                           uint32_t grad_x, uint32_t grads, int n_tiles, int n_col)
+{
+    const uint32_t wg = blockIdx.x;
+    if (wg < grads) {
+        const bool self = wg >= grad_x;
+        grad_rows_tile<1, 1, WJ>(slice_of(r, rb, blockIdx.y), self ? wg - grad_x : wg, self, n_tiles);
+    } else if constexpr (STRIP) {
+        pair_strip32<true, TWO>(slice_of(p, pb), wg - grads, gridDim.x - grads);
+    } else {
+        pair_rows_tile<1, TWO, true>(slice_of(p, pb), wg - grads, n_col);
+    }
+}
+
+// Whether the n x w rows at o, in leading dimension ldo, may share memory with those at x (by the address ranges from first to last element)
+inline bool may_share(const void *o, int64_t ldo, int64_t wo, const void *x, int64_t ldx, int64_t wx, int64_t n)
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(o), q = reinterpret_cast<uintptr_t>(x);
+    return o && x && p < q + 4 * ((n - 1) * ldx + wx) && q < p + 4 * ((n - 1) * ldo + wo);
+}
+
+// launch_grad_rows, and launch_pair<true> for `list` in the same launch where both take their smallest tiles and nothing that is stored is
+// read by the other (an input gradient may take the place of an operand); `pair_done` says whether it was.  A layer whose gradients are cut
+// into chains shorter than RED_ROWS leaves the LDS form for it (5000 rows 96 -> 96 19.5 / 14.9 us, 2048 rows 256 -> 256 34.7 / 30.3).
+int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, int products, bool big, const PairArgs *list, bool *pair_done,
+                          hipStream_t stream)
+{
+    *pair_done = false;
+    if (!list) return launch_grad_rows(r, b, batch, products, big, stream);
+    const GradForm g = grad_form(r, batch, products, big, r.rows_per_block == RED_ROWS);
+    const PairForm f = pair_form(list, batch);
+    bool merge = g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 && (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && f.nt == 1));
+    for (int i = 0; merge && i < batch; ++i)
+        for (int q = 0; merge && q < batch; ++q)
+            for (int o = 0; o < 2; ++o) {
+                const float *out = o ? list[i].O2 : list[i].O1;
+                const int64_t ldo = o ? list[i].ldo2 : list[i].ldo1;
+                auto reads = [&](const void *x, int64_t ldx, int64_t wx) { return may_share(out, ldo, list[i].Nout, x, ldx, wx, r.n); };
+                if (reads(b.p[q].Z, r.ldz, r.w_in) || reads(b.p[q].Hin, r.ldi, r.w_in) || reads(b.p[q].dHout, r.ldo, r.w_out) ||
+                    reads(b.p[q].mask, r.mask_words, (r.w_out + 31) / 32))
+                    merge = false;
+            }
+    if (!merge) return launch_grad_rows(r, b, batch, products, big, stream);
+    ReduceArgs t = r;
+    t.j_tiles = g.j_tiles;
+    const PairBatch pb = pair_batch(list, batch);
+    const uint32_t grad_x = (uint32_t)g.blocks, grads = grad_x * products;
+    const dim3 grid(grads + (unsigned)f.blocks, (unsigned)batch);
+    auto launch = [&](auto wj, auto strip, auto two) {
+        grad_pair_kernel<wj.value, strip.value, two.value><<<grid, 256, 0, stream>>>(t, b, list[0], pb, grad_x, grads, g.n_tiles, f.n_col);
+    };
+    using std::integral_constant;
+    const std::true_type yes;
+    const std::false_type no;
+    if (g.wj == 1) launch(integral_constant<int, 1>(), no, no); // layers wider than 64: one product, no strips
+    else if (g.wj == 2) launch(integral_constant<int, 2>(), no, no);
+    else if (f.kernel == PairForm::STRIP32 && f.two) launch(integral_constant<int, 0>(), yes, yes);
+    else if (f.kernel == PairForm::STRIP32) launch(integral_constant<int, 0>(), yes, no);
+    else if (f.two) launch(integral_constant<int, 0>(), no, yes);
+    else launch(integral_constant<int, 0>(), no, no);
+    SG_LAUNCH_CHECK();
+    *pair_done = true;
+    return SLICEGCN_OK;
 }
 
 // ---- pieces of the transform-first layer order -------------------------------------------------
@@ -2113,7 +2227,8 @@ struct LinearGradArgs { // one layer of a batch (equal shapes and leading dimens
 // dW = X^T (dY * mask) (w_in x w_out), db = colsum(dY * mask); NULL outputs are skipped.  ws: ws_each bytes per layer of
 // the batch, at least linear_partial_bytes(red_blocks(n)).
 static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ldx, int64_t n, int32_t w_in, int32_t w_out,
-                               int64_t mask_words, int64_t lddy, void *ws, size_t ws_each, hipStream_t stream)
+                               int64_t mask_words, int64_t lddy, void *ws, size_t ws_each, hipStream_t stream,
+                               const PairArgs *inputs = nullptr, bool *inputs_done = nullptr)
 {
     const int ww = w_in * w_out;
     const int32_t stride = ww + w_out;
@@ -2132,7 +2247,9 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
         f.partial[i] = partial;
         f.dst[i] = FinalDst{{x.dW, nullptr, nullptr, x.db}, x.db_copy, {0, ww, ww, ww, stride}};
     }
-    if (int rc = launch_grad_rows(r, b, batch, 1, plan.big, stream)) return rc;
+    bool pair_done;
+    if (int rc = launch_grads_and_pair(r, b, batch, 1, plan.big, inputs, &pair_done, stream)) return rc;
+    if (inputs_done) *inputs_done = pair_done;
     reduce_final_kernel<<<dim3((unsigned)((stride + 31) / 32), (unsigned)batch), 1024, 0, stream>>>(f, plan.partials, stride, stride);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -2371,6 +2488,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
     const GradPlan plan = grad_plan(g->n, w_in, w_out);
     // narrow layers with a self term: the kernel that forms the weight gradients also forms dZ and T (one read of dHout)
     const bool fused_inputs = need_dHin && self && plan.kind == GradPlan::STRIP32;
+    bool pair_done = fused_inputs; // so does one launch on few rows
 
     // ---- parameter gradients: per-row-block partial sums, then an fp64 combination ----
     const int32_t stride = 2 * w_in * w_out + 2 * w_out;
@@ -2397,12 +2515,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         switch (plan.kind) {
         case GradPlan::STRIP32:
             if (fused_inputs) { // weight gradients and the two input-gradient products in one sweep over the rows
-                PairBatch pb;
-                for (int i = 0; i < BATCH; ++i) {
-                    const PairArgs &x = list[i < batch ? i : 0];
-                    pb.p[i] = PairPtrs{x.A1, x.A2, x.B1, x.B2, x.bias1, x.bias2, nullptr, x.O1, x.O2, x.mask};
-                }
-                bwd_strip32_kernel<<<dim3(gb, by), 256, 0, stream>>>(r, b, list[0], pb, plan.partials);
+                bwd_strip32_kernel<<<dim3(gb, by), 256, 0, stream>>>(r, b, list[0], pair_batch(list, batch), plan.partials);
             } else {
                 grad_strip32_kernel<<<dim3(gb, by), 256, 0, stream>>>(r, b, plan.partials);
             }
@@ -2415,7 +2528,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
             });
             break;
         case GradPlan::TILED:
-            if (int rc = launch_grad_rows(r, b, batch, self ? 2 : 1, false, stream)) return rc;
+            if (int rc = launch_grads_and_pair(r, b, batch, self ? 2 : 1, false, need_dHin ? list : nullptr, &pair_done, stream)) return rc;
             break;
         }
         SG_LAUNCH_CHECK();
@@ -2425,7 +2538,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
 
     // ---- input gradient: dHin = A^^T (dP W_agg^T) + dHout W_self^T ----
     if (need_dHin) {
-        if (!fused_inputs) {
+        if (!pair_done) {
             ProfScope prof(SLICEGCN_PROF_DENSE_BWD, w_in, stream);
             if (int rc = launch_pair<true>(list, batch, stream)) return rc;
         }
@@ -2614,6 +2727,7 @@ extern "C" int slicegcn_linear_bwd(const float *X, int64_t ldx, int64_t n, int32
     a.mask = const_cast<uint32_t *>(m); a.mask_words = mask_words;
     a.n = n; a.K = w_out; a.Nout = w_in; a.ldw = w_out; a.act = act;
     if (int rc = check_in_place(&a, 1)) return rc; // before anything is launched
+    bool dX_done = false;
     if (dW || db) {
         const size_t need = linear_partial_bytes(red_blocks(n), w_in, w_out);
         SG_REQUIRE(ws != nullptr && ws_bytes >= need, SLICEGCN_EWORKSPACE, "linear_bwd: workspace of %zu bytes, %zu needed",
@@ -2621,9 +2735,10 @@ extern "C" int slicegcn_linear_bwd(const float *X, int64_t ldx, int64_t n, int32
         SG_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255u) == 0, SLICEGCN_EINVAL, "linear_bwd: workspace not 256-byte aligned");
         ProfScope prof(SLICEGCN_PROF_LINEAR_GRAD, w_out, stream);
         const LinearGradArgs args{X, m, dY, dW, db};
-        if (int rc = launch_linear_grads(&args, 1, ldx, n, w_in, w_out, mask_words, lddy, ws, ws_bytes, stream)) return rc;
+        if (int rc = launch_linear_grads(&args, 1, ldx, n, w_in, w_out, mask_words, lddy, ws, ws_bytes, stream, dX ? &a : nullptr, &dX_done))
+            return rc;
     }
-    if (dX) {
+    if (dX && !dX_done) {
         ProfScope prof(SLICEGCN_PROF_LINEAR_BWD, w_in, stream);
         if (int rc = launch_pair<true>(a, stream)) return rc;
     }
