@@ -1984,10 +1984,11 @@ int launch_grad_rows(ReduceArgs r, const ReduceBatch &b, int batch, int products
 
 // Weight gradients and the products of the input gradients read the same dHout and do not depend on each other: on few rows, where
 // either is a chain of a few dependent loads in a fraction of the chip, one launch does both.  The first `grads` workgroups of a slice form
-// weight gradients (products x grad_x), the others what pair_strip32_kernel (STRIP) or pair_rows_kernel would.  Backward passes of dense
+// weight gradients (products x grad_x), the others what pair_strip32_kernel or pair_rows_kernel would.  Backward passes of dense
 // layers, in two launches / one: 1000 rows 64 -> 8 10.1 / 6.8 us, 2048 rows 64 -> 64 11.9 / 8.8, 20 k rows 64 -> 64 27.2 / 23.1, 60 k rows
-// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1; of slice layers 2048 rows 64 -> 32 18.5 / 12.9, 30 k rows 64 -> 64 39.5 / 35.9.
-template <int WJ, bool STRIP, bool TWO>
+// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1, 169 k rows 256 -> 40 232 / 220, 400 k rows 128 -> 40 300 / 262 (with the two
+// kinds of workgroups in turn 337 and 392: the long ones have to start first); of slice layers 2048 rows 64 -> 32 18.5 / 12.9, 30 k rows 64 -> 64 39.5 / 35.9.
+template <int WJ, int NT, bool TWO> // NT: tiles of 32 columns, 0 for the strips
 __global__ __launch_bounds__(256, 3) void grad_pair_kernel(const ReduceArgs r, const ReduceBatch rb, const PairArgs p, const PairBatch pb,
                                                            uint32_t grad_x, uint32_t grads, int n_tiles, int n_col)
 {
@@ -1995,10 +1996,10 @@ __global__ __launch_bounds__(256, 3) void grad_pair_kernel(const ReduceArgs r, c
     if (wg < grads) {
         const bool self = wg >= grad_x;
         grad_rows_tile<1, 1, WJ>(slice_of(r, rb, blockIdx.y), self ? wg - grad_x : wg, self, n_tiles);
-    } else if constexpr (STRIP) {
+    } else if constexpr (NT == 0) {
         pair_strip32<true, TWO>(slice_of(p, pb), wg - grads, gridDim.x - grads);
     } else {
-        pair_rows_tile<1, TWO, true>(slice_of(p, pb), wg - grads, n_col);
+        pair_rows_tile<NT, TWO, true>(slice_of(p, pb), wg - grads, n_col);
     }
 }
 
@@ -2009,9 +2010,10 @@ inline bool may_share(const void *o, int64_t ldo, int64_t wo, const void *x, int
     return o && x && p < q + 4 * ((n - 1) * ldx + wx) && q < p + 4 * ((n - 1) * ldo + wo);
 }
 
-// launch_grad_rows, and launch_pair<true> for `list` in the same launch where both take their smallest tiles and nothing that is stored is
-// read by the other (an input gradient may take the place of an operand); `pair_done` says whether it was.  A layer whose gradients are cut
-// into chains shorter than RED_ROWS leaves the LDS form for it (5000 rows 96 -> 96 19.5 / 14.9 us, 2048 rows 256 -> 256 34.7 / 30.3).
+// launch_grad_rows, and launch_pair<true> for `list` in the same launch where the gradients take their smallest tiles, which leave the chip
+// idle (with larger ones 2.4 M rows 256 -> 47 take 2.86 ms together and 2.64 apart), and nothing that is stored is read by the other (an
+// input gradient may take the place of an operand); `pair_done` says whether it was.  A layer whose gradients are cut into chains shorter
+// than RED_ROWS leaves the LDS form for it (5000 rows 96 -> 96 19.5 / 14.9 us, 2048 rows 256 -> 256 34.7 / 30.3).
 int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, int products, bool big, const PairArgs *list, bool *pair_done,
                           hipStream_t stream)
 {
@@ -2019,7 +2021,8 @@ int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, 
     if (!list) return launch_grad_rows(r, b, batch, products, big, stream);
     const GradForm g = grad_form(r, batch, products, big, r.rows_per_block == RED_ROWS);
     const PairForm f = pair_form(list, batch);
-    bool merge = g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 && (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && f.nt == 1));
+    bool merge = g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 &&
+                 (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && (f.nt == 1 || (f.nt == 2 && g.wj != 0))));
     for (int i = 0; merge && i < batch; ++i)
         for (int q = 0; merge && q < batch; ++q)
             for (int o = 0; o < 2; ++o) {
@@ -2036,18 +2039,22 @@ int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, 
     const PairBatch pb = pair_batch(list, batch);
     const uint32_t grad_x = (uint32_t)g.blocks, grads = grad_x * products;
     const dim3 grid(grads + (unsigned)f.blocks, (unsigned)batch);
-    auto launch = [&](auto wj, auto strip, auto two) {
-        grad_pair_kernel<wj.value, strip.value, two.value><<<grid, 256, 0, stream>>>(t, b, list[0], pb, grad_x, grads, g.n_tiles, f.n_col);
+    auto launch = [&](auto wj, auto nt, auto two) {
+        grad_pair_kernel<wj.value, nt.value, two.value><<<grid, 256, 0, stream>>>(t, b, list[0], pb, grad_x, grads, g.n_tiles, f.n_col);
     };
-    using std::integral_constant;
+    const std::integral_constant<int, 0> c0;
+    const std::integral_constant<int, 1> c1;
+    const std::integral_constant<int, 2> c2;
     const std::true_type yes;
     const std::false_type no;
-    if (g.wj == 1) launch(integral_constant<int, 1>(), no, no); // layers wider than 64: one product, no strips
-    else if (g.wj == 2) launch(integral_constant<int, 2>(), no, no);
-    else if (f.kernel == PairForm::STRIP32 && f.two) launch(integral_constant<int, 0>(), yes, yes);
-    else if (f.kernel == PairForm::STRIP32) launch(integral_constant<int, 0>(), yes, no);
-    else if (f.two) launch(integral_constant<int, 0>(), no, yes);
-    else launch(integral_constant<int, 0>(), no, no);
+    switch (3 * g.wj + f.nt) { // wj > 0, layers wider than 64: one product, no strips
+    case 0: f.two ? launch(c0, c0, yes) : launch(c0, c0, no); break;
+    case 1: f.two ? launch(c0, c1, yes) : launch(c0, c1, no); break;
+    case 4: launch(c1, c1, no); break;
+    case 5: launch(c1, c2, no); break;
+    case 7: launch(c2, c1, no); break;
+    default: launch(c2, c2, no); break;
+    }
     SG_LAUNCH_CHECK();
     *pair_done = true;
     return SLICEGCN_OK;

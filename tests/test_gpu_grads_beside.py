@@ -8,8 +8,8 @@ from paper_2408_11500_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 33, 1000, 5001, 20_011])
-@pytest.mark.parametrize("w_in,w_out", [(1, 1), (64, 8), (31, 32), (32, 33), (64, 64), (65, 64), (96, 96), (100, 7), (7, 100), (130, 129), (300, 200)])
+@pytest.mark.parametrize("n", [1, 33, 1000, 5001, 20_011, 140_001])
+@pytest.mark.parametrize("w_in,w_out", [(1, 1), (64, 8), (31, 32), (32, 33), (64, 64), (65, 64), (96, 96), (100, 7), (7, 100), (130, 129), (256, 40), (300, 200)])
 def test_linear_bwd_together_and_apart(n, w_in, w_out):
     gen = torch.Generator(device="cuda").manual_seed(n + w_in)
     X, dY, W = (torch.randn(s, generator=gen, device="cuda") for s in ((n, w_in), (n, w_out), (w_in, w_out)))
