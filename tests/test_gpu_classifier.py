@@ -89,6 +89,25 @@ def test_softmax_ce_parity(n, c):
     assert loss2.item() == loss.item()
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 2305])
+@pytest.mark.parametrize("c,ld", [(4, 4), (8, 8), (40, 44), (64, 64), (63, 64), (64, 65), (17, 20), (15, 16), (65, 68)])
+def test_softmax_ce_row_forms(n, c, ld):
+    """Rows on 16-byte boundaries and others, up to and past the 64 classes that are held in registers; the last workgroup partly filled; the
+    gradient in place of the logits.  Padding columns are not read (NaN) and not written."""
+    rng = np.random.default_rng(n * 31 + c)
+    x, y = (rng.normal(size=(n, c)) * 3).astype(np.float32), rng.integers(0, c, n)
+    lo, go = oracle.softmax_ce(x, y)
+    full = torch.full((n, ld), float("nan"), device="cuda")
+    full[:, :c] = dev(x)
+    g, loss, ws = torch.full((n, ld), 9.0, device="cuda"), torch.zeros(1, device="cuda"), ws_tensor(B.slicegcn_softmax_ce_workspace_bytes(n))
+    B.slicegcn_softmax_ce(full[:, :c], dev(y, torch.int32), loss, g[:, :c], ws)
+    assert abs(loss.item() - lo) <= TOL * abs(lo) + 1e-7
+    assert_close(g[:, :c].cpu().numpy(), go, "dlogits")
+    assert torch.all(g[:, c:] == 9.0)
+    B.slicegcn_softmax_ce(full[:, :c], dev(y, torch.int32), loss, full[:, :c], ws)
+    assert torch.equal(full[:, :c], g[:, :c]) and bool(full[:, c:].isnan().all())
+
+
 def test_softmax_ce_extreme_logits_and_bad_label():
     x = np.array([[1000.0, 0.0], [0.0, 1000.0], [-1000.0, -1000.0]], dtype=np.float32)
     y = np.array([0, 0, 1])
