@@ -123,14 +123,17 @@ namespace slicegcn {
 // dimensions), M given by `m`.  Add may alias Y.  ws: 256-byte aligned, at least batch * spmm_workspace_bytes(m, width)
 // bytes (partial sums of rows cut into several items; may be NULL when that is 0).
 // prescaled: X rows carry dinv[u] already (the value stream is not read)
+// sums: final sums of weight gradients that are still due, formed beside the aggregation or before it
 constexpr int SPMM_BATCH = 8;
+struct FinalWork; // final_sum.h
 struct SpmmOperands {
     const float *X;
     float *Y;
     const float *Add; // NULL: nothing is added
 };
 int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, int batch, int64_t ldx, int32_t width,
-                int64_t ldy, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream, bool prescaled = false);
+                int64_t ldy, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream, bool prescaled = false,
+                const FinalWork *sums = nullptr);
 size_t spmm_workspace_bytes(const Csr &m, int32_t width, bool one_pass = false);
 
 // dense.hip: column sums of an n x w matrix: fp32 per block of rows into ws[blocks][w], then

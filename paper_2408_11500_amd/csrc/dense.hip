@@ -10,6 +10,7 @@
 // Lane layout of the 32x32x2 fp32 MFMA (64 lanes, l = lane): A operand = A[m = l % 32][k = l / 32],
 // B operand = B[k = l / 32][n = l % 32], accumulator register r (0..15) = C[8*(r/4) + 4*(l/32) + r%4][l % 32].
 #include "common.h"
+#include "final_sum.h"
 
 #include <type_traits>
 
@@ -1790,43 +1791,8 @@ __global__ __launch_bounds__(256) void colsum_partial_vec_kernel(const float *__
     }
 }
 
-// Final stage: out[e] = sum over row blocks of partial[b][e], in fp64, fixed order.
-// 32 elements x 32 parts per block of 1024 threads.
-struct FinalDst { float *ptr[4]; float *copy; int32_t begin[5]; }; // element ranges [begin[q], begin[q+1]) go to ptr[q], range 3 also to copy
-struct FinalBatch { const float *partial[BATCH]; FinalDst dst[BATCH]; };
-
-__global__ __launch_bounds__(1024) void reduce_final_kernel(const FinalBatch batch, int64_t n_blocks, int32_t row_stride, int32_t stride)
-{
-    const float *__restrict__ partial = batch.partial[blockIdx.y];
-    const FinalDst &dst = batch.dst[blockIdx.y];
-    __shared__ double red[32][33];
-    const int el = threadIdx.x % 32, part = threadIdx.x / 32;
-    const int64_t e = (int64_t)blockIdx.x * 32 + el;
-    const int64_t per = (n_blocks + 31) / 32;
-    const int64_t b0 = part * per, b1 = b0 + per < n_blocks ? b0 + per : n_blocks;
-    double acc = 0.0;
-    if (e < stride) {
-        int64_t b = b0;
-        for (; b + 8 <= b1; b += 8) { // eight independent loads in flight; the additions stay in block order
-            float q[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) q[i] = partial[(b + i) * row_stride + e];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc += (double)q[i];
-        }
-        for (; b < b1; ++b) acc += (double)partial[b * row_stride + e];
-    }
-    red[part][el] = acc;
-    __syncthreads();
-    if (part == 0 && e < stride) {
-        double s = 0.0;
-        for (int q = 0; q < 32; ++q) s += red[q][el];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (e >= dst.begin[q] && e < dst.begin[q + 1] && dst.ptr[q]) dst.ptr[q][e - dst.begin[q]] = (float)s;
-        if (e >= dst.begin[3] && e < dst.begin[4] && dst.copy) dst.copy[e - dst.begin[3]] = (float)s;
-    }
-}
+// 32 elements x 32 runs of blocks per workgroup
+__global__ __launch_bounds__(1024) void reduce_final_kernel(const FinalWork f) { final_sum<1024>(f, blockIdx.x, blockIdx.y); }
 
 inline int64_t red_blocks(int64_t n) { return (n + RED_ROWS - 1) / RED_ROWS; }
 
@@ -2195,14 +2161,20 @@ int launch_colsum_partial(const float *M, int64_t ld, int64_t n, int32_t w, floa
     return SLICEGCN_OK;
 }
 
-int launch_colsum_final(const float *ws_first, int64_t n, int32_t ws_row, int32_t count, float *out, hipStream_t stream)
+int launch_final_sum(const FinalWork &f, int batch, hipStream_t stream)
 {
-    FinalBatch f;
-    f.partial[0] = ws_first;
-    f.dst[0] = FinalDst{{out, nullptr, nullptr, nullptr}, nullptr, {0, count, count, count, count}};
-    reduce_final_kernel<<<(unsigned)((count + 31) / 32), 1024, 0, stream>>>(f, red_blocks(n), ws_row, count);
+    reduce_final_kernel<<<dim3((unsigned)((f.stride + FINAL_ELEMS - 1) / FINAL_ELEMS), (unsigned)batch), 1024, 0, stream>>>(f);
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
+}
+
+int launch_colsum_final(const float *ws_first, int64_t n, int32_t ws_row, int32_t count, float *out, hipStream_t stream)
+{
+    FinalWork f;
+    f.partial[0] = ws_first;
+    f.dst[0] = FinalDst{{out, nullptr, nullptr, nullptr}, nullptr, {0, count, count, count, count}};
+    f.n_blocks = red_blocks(n); f.row_stride = ws_row; f.stride = count;
+    return launch_final_sum(f, 1, stream);
 }
 
 size_t colsum_workspace_bytes(int64_t n, int32_t w) { return (size_t)red_blocks(n) * (size_t)w * sizeof(float); }
@@ -2246,7 +2218,8 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
     r.partial = nullptr; r.n = n; r.w_in = w_in; r.w_out = w_out; r.stride = stride; r.compact = 1;
     r.rows_per_block = plan.rows;
     ReduceBatch b;
-    FinalBatch f;
+    FinalWork f;
+    f.n_blocks = plan.partials; f.row_stride = f.stride = stride;
     for (int i = 0; i < BATCH; ++i) {
         const LinearGradArgs &x = list[i < batch ? i : 0];
         float *partial = reinterpret_cast<float *>(static_cast<char *>(ws) + (i < batch ? i : 0) * ws_each);
@@ -2257,9 +2230,7 @@ static int launch_linear_grads(const LinearGradArgs *list, int batch, int64_t ld
     bool pair_done;
     if (int rc = launch_grads_and_pair(r, b, batch, 1, plan.big, inputs, &pair_done, stream)) return rc;
     if (inputs_done) *inputs_done = pair_done;
-    reduce_final_kernel<<<dim3((unsigned)((stride + 31) / 32), (unsigned)batch), 1024, 0, stream>>>(f, plan.partials, stride, stride);
-    SG_LAUNCH_CHECK();
-    return SLICEGCN_OK;
+    return launch_final_sum(f, batch, stream);
 }
 
 // ---- one layer of a batch of slice models --------------------------------------------------
@@ -2499,6 +2470,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
 
     // ---- parameter gradients: per-row-block partial sums, then an fp64 combination ----
     const int32_t stride = 2 * w_in * w_out + 2 * w_out;
+    FinalWork sums;
     {
         ProfScope prof(SLICEGCN_PROF_GRAD_REDUCE, w_out, stream);
         ReduceArgs r;
@@ -2508,15 +2480,15 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         r.rows_per_block = plan.rows;
         r.hin_scale = (desc->flags & SLICEGCN_LAYER_IN_SCALED) ? g->sqrtd : nullptr;
         ReduceBatch b;
-        FinalBatch f;
+        sums.n_blocks = plan.partials; sums.row_stride = sums.stride = stride;
         const int ww = w_in * w_out;
         for (int i = 0; i < BATCH; ++i) {
             const slicegcn_layer_io &x = io[i < batch ? i : 0];
             float *partial = reinterpret_cast<float *>(parts + (i < batch ? i : 0) * part);
             b.p[i] = ReducePtrs{x.Z, self ? x.Hin : nullptr, x.dHout, relu ? x.mask : nullptr, partial};
-            f.partial[i] = partial;
-            f.dst[i] = FinalDst{{x.grads.dW_agg, self ? x.grads.dW_self : nullptr, x.grads.db, self ? x.grads.db_self : nullptr},
-                                self ? x.denc : nullptr, {0, ww, 2 * ww, 2 * ww + w_out, stride}};
+            sums.partial[i] = partial;
+            sums.dst[i] = FinalDst{{x.grads.dW_agg, self ? x.grads.dW_self : nullptr, x.grads.db, self ? x.grads.db_self : nullptr},
+                                   self ? x.denc : nullptr, {0, ww, 2 * ww, 2 * ww + w_out, stride}};
         }
         const unsigned by = (unsigned)batch, gb = (unsigned)((plan.partials + 3) / 4);
         switch (plan.kind) {
@@ -2539,8 +2511,8 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
             break;
         }
         SG_LAUNCH_CHECK();
-        reduce_final_kernel<<<dim3((unsigned)((stride + 31) / 32), by), 1024, 0, stream>>>(f, plan.partials, stride, stride);
-        SG_LAUNCH_CHECK();
+        if (!need_dHin)
+            if (int rc = launch_final_sum(sums, batch, stream)) return rc;
     }
 
     // ---- input gradient: dHin = A^^T (dP W_agg^T) + dHout W_self^T ----
@@ -2553,7 +2525,7 @@ static int layers_bwd(const slicegcn_graph *g, const slicegcn_layer_group *lg, c
         SpmmOperands ops[BATCH];
         for (int i = 0; i < batch; ++i)
             ops[i] = SpmmOperands{reinterpret_cast<float *>(dZs + i * mat), io[i].dHin, self ? io[i].dHin : nullptr};
-        if (int rc = launch_spmm(g, g->tr, ops, batch, ldz_in, w_in, lg->ldgi, lg->ldgi, agg_ws, agg * batch, stream, true)) return rc;
+        if (int rc = launch_spmm(g, g->tr, ops, batch, ldz_in, w_in, lg->ldgi, lg->ldgi, agg_ws, agg * batch, stream, true, &sums)) return rc;
     }
     return SLICEGCN_OK;
 }

@@ -32,6 +32,7 @@
 // from spmm_workspace_bytes), so a graph handle is read-only here and calls on different streams
 // only have to use different workspaces.
 #include "common.h"
+#include "final_sum.h"
 
 #include <mutex>
 
@@ -583,6 +584,23 @@ __global__ __launch_bounds__(256) void spmm_merged_kernel(const SpmmArgs a, cons
     else tiny_rows_body<LPR, V, S32, FACT, RAG>(a, io, b - g1 - g2);
 }
 
+// The same behind the first `extra` workgroups (a multiple of 8), which form the final sums of the weight gradients: those are a launch of
+// their own otherwise, on a small graph as long as the aggregation itself.  Backward passes of slice layers, sums in their own launch / here:
+// 2048 rows 64 -> 32 12.9 / 11.1 us, 5000 rows 200 -> 200 78.9 / 73.6, 60 k rows 32 -> 32 32.9 / 29.9; 169 k rows, four slices: 10 us less.
+template <int LPR>
+__global__ __launch_bounds__(256) void spmm_merged_sums_kernel(const SpmmArgs a, const SpmmBatch batch, int g1, int g2, const FinalWork f, int extra)
+{
+    const int b = (int)blockIdx.x - extra; // uniform per workgroup
+    if (b < 0) {
+        final_sum<256>(f, blockIdx.x, blockIdx.y);
+        return;
+    }
+    const SpmmIo io = pick_io(a, batch);
+    if (b < g1) wave_items_run_body<LPR, 4, true, true, false>(a, io, b);
+    else if (b < g1 + g2) group_items_body<LPR, 4, true, ITEM_SHORT, true, false>(a, io, b - g1);
+    else tiny_rows_body<LPR, 4, true, true, false>(a, io, b - g1 - g2);
+}
+
 // Rows with several items: add the partial slots in order.  One thread per (row, column); eight
 // independent slot reads are in flight at a time, the additions stay in slot order.
 __global__ __launch_bounds__(256) void spmm_fix_kernel(const SpmmArgs a, const SpmmBatch b, int32_t n_fix)
@@ -611,9 +629,10 @@ __global__ __launch_bounds__(256) void spmm_fix_kernel(const SpmmArgs a, const S
     io.Y[(int64_t)f.x * a.ldy + col] = acc;
 }
 
-// `batch`: slices aggregated in this launch; `passes`: column passes in this launch (the one-launch kernel only)
+// `batch`: slices aggregated in this launch; `passes`: column passes in this launch (the one-launch kernel only); `sums`: final sums to form in
+// the launch (may_join_sums)
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, hipStream_t stream)
+int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, const FinalWork *sums, hipStream_t stream)
 {
     const int64_t units_per_block = 4 * a.tiny_rounds * (64 / LPR);
     const int64_t g1 = (int64_t)N_CLASSES * a.big_blocks;
@@ -622,7 +641,16 @@ int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes,
     SG_REQUIRE(g1 + g2 + g3 + N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
     if (a.item_max <= ITEM_SHORT) { // cache-resident graph: one launch (big_blocks counts runs of 4 * ipw items)
         // the grid's first dimension is a multiple of 8, so that a class meets the same XCD in every slice and pass
-        const dim3 grid((unsigned)round_up(g1 + g2 + g3, N_CLASSES), (unsigned)batch, (unsigned)passes);
+        dim3 grid((unsigned)round_up(g1 + g2 + g3, N_CLASSES), (unsigned)batch, (unsigned)passes);
+        if constexpr (V == 4 && S32 && FACT && !RAG) {
+            if (sums) {
+                const unsigned extra = (unsigned)round_up((sums->stride + FINAL_ELEMS - 1) / FINAL_ELEMS, N_CLASSES);
+                grid.x += extra;
+                spmm_merged_sums_kernel<LPR><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2, *sums, (int)extra);
+                SG_LAUNCH_CHECK();
+                return SLICEGCN_OK;
+            }
+        }
         spmm_merged_kernel<LPR, V, S32, FACT, RAG><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2);
         SG_LAUNCH_CHECK();
         return SLICEGCN_OK;
@@ -641,32 +669,38 @@ int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes,
 }
 
 template <int LPR, int V, bool FACT>
-int launch_layout(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, hipStream_t stream)
+int launch_layout(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, const FinalWork *sums, hipStream_t stream)
 {
-    if constexpr (V == 1) return launch_variant<LPR, V, false, FACT, false>(a, b, batch, passes, stream);
+    if constexpr (V == 1) return launch_variant<LPR, V, false, FACT, false>(a, b, batch, passes, sums, stream);
     else {
         if (a.load_max > 0)
-            return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, true>(a, b, batch, passes, stream)
-                                    : launch_variant<LPR, V, false, FACT, true>(a, b, batch, passes, stream);
-        return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, false>(a, b, batch, passes, stream)
-                                : launch_variant<LPR, V, false, FACT, false>(a, b, batch, passes, stream);
+            return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, true>(a, b, batch, passes, sums, stream)
+                                    : launch_variant<LPR, V, false, FACT, true>(a, b, batch, passes, sums, stream);
+        return a.ldx_bytes != 0 ? launch_variant<LPR, V, true, FACT, false>(a, b, batch, passes, sums, stream)
+                                : launch_variant<LPR, V, false, FACT, false>(a, b, batch, passes, sums, stream);
     }
 }
 
 template <int LPR, int V>
-int launch_kernels(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, hipStream_t stream)
+int launch_kernels(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, const FinalWork *sums, hipStream_t stream)
 {
-    return a.dinv ? launch_layout<LPR, V, true>(a, b, batch, passes, stream) : launch_layout<LPR, V, false>(a, b, batch, passes, stream);
+    return a.dinv ? launch_layout<LPR, V, true>(a, b, batch, passes, sums, stream) : launch_layout<LPR, V, false>(a, b, batch, passes, sums, stream);
 }
 
-int launch_pass(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, int v, int lpr, hipStream_t stream)
+int launch_pass(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes, int v, int lpr, const FinalWork *sums, hipStream_t stream)
 {
-    if (v == 1) return launch_kernels<8, 1>(a, b, batch, passes, stream); // fewer than 4 columns
+    if (v == 1) return launch_kernels<8, 1>(a, b, batch, passes, sums, stream); // fewer than 4 columns
     switch (lpr) {
-    case 8: return launch_kernels<8, 4>(a, b, batch, passes, stream);
-    case 16: return launch_kernels<16, 4>(a, b, batch, passes, stream);
-    default: return launch_kernels<32, 4>(a, b, batch, passes, stream); // a pass is at most 128 columns
+    case 8: return launch_kernels<8, 4>(a, b, batch, passes, sums, stream);
+    case 16: return launch_kernels<16, 4>(a, b, batch, passes, sums, stream);
+    default: return launch_kernels<32, 4>(a, b, batch, passes, sums, stream); // a pass is at most 128 columns
     }
+}
+
+// Whether a launch can form final sums beside the aggregation (the form that the input gradients of layers take)
+inline bool may_join_sums(const SpmmArgs &a, int v, int passes)
+{
+    return a.item_max <= ITEM_SHORT && passes == 1 && v == 4 && a.ldx_bytes != 0 && a.dinv != nullptr && a.load_max <= 0;
 }
 
 } // namespace
@@ -682,7 +716,7 @@ size_t spmm_workspace_bytes(const Csr &m, int32_t width, bool one_pass)
 }
 
 int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, int batch, int64_t ldx, int32_t width,
-                int64_t ldy, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream, bool prescaled)
+                int64_t ldy, int64_t ldadd, void *ws, size_t ws_bytes, hipStream_t stream, bool prescaled, const FinalWork *sums)
 {
     SG_REQUIRE(batch >= 1 && batch <= MAX_BATCH, SLICEGCN_EINVAL, "aggregation: batch of %d", batch);
     // Operands of 1 to 3 columns: one float per lane, also where their rows have room for a 16-byte gather.  1 column in rows of 4 / 32
@@ -765,7 +799,11 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, 
         SG_REQUIRE(big_blocks * N_CLASSES <= INT32_MAX && small_blocks * N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
         a.big_blocks = (int32_t)big_blocks;
         a.small_blocks = (int32_t)small_blocks;
-        if (int rc = launch_pass(a, b, batch, passes, V, lpr, stream)) return rc;
+        const bool join = sums && may_join_sums(a, V, passes);
+        if (sums && !join)
+            if (int rc = launch_final_sum(*sums, batch, stream)) return rc;
+        if (int rc = launch_pass(a, b, batch, passes, V, lpr, join ? sums : nullptr, stream)) return rc;
+        sums = nullptr;
         if (sc.n_fix > 0) {
             const int64_t threads = sc.n_fix * (int64_t)(a.col_end - c0);
             spmm_fix_kernel<<<dim3((unsigned)((threads + 255) / 256), (unsigned)batch), 256, 0, stream>>>(a, b, (int32_t)sc.n_fix);

@@ -29,3 +29,28 @@ def test_linear_bwd_together_and_apart(n, w_in, w_out):
     over = X.clone()
     got = run(over, over)                                # in place of the layer's input, which the weight gradients read
     assert torch.equal(over, alone) and all(map(torch.equal, got, want))
+
+
+@pytest.mark.parametrize("n", [1, 40, 3001, 70_001])
+@pytest.mark.parametrize("w_in,w_out", [(1, 5), (3, 64), (4, 4), (33, 32), (64, 64), (100, 20), (128, 9), (130, 33), (301, 64)])
+@pytest.mark.parametrize("self_term", [True, False])
+def test_layer_gradients_beside_the_aggregation(n, w_in, w_out, self_term):
+    """The final sums of the weight gradients, formed in the launch of the input gradient's aggregation, or in their own without one."""
+    gen = torch.Generator(device="cuda").manual_seed(n + w_in)
+    src, dst = (torch.randint(0, n, (4 * n,), generator=gen, device="cuda") for _ in range(2))
+    g = B.slicegcn_build_norm_csr(src, dst, n)
+    X, G = (torch.randn((n, w), generator=gen, device="cuda") for w in (w_in, w_out))
+    W, Ws = (torch.randn((w_in, w_out), generator=gen, device="cuda") for _ in range(2))
+    b = torch.zeros(w_out, device="cuda")
+    Ws, bs = (Ws, b) if self_term else (None, None)
+    Z, H = torch.empty((n, (w_in + 3) // 4 * 4), device="cuda")[:, :w_in], torch.empty((n, w_out), device="cuda")
+    words = torch.zeros((n, (w_out + 31) // 32), dtype=torch.int32, device="cuda")
+    B.slicegcn_layer_fwd(g, X, W, b, Ws, bs, H, Z, words)
+    got = []
+    for dX in (torch.empty_like(X), None):
+        grads = [torch.full_like(t, 7.0) if t is not None else None for t in (W, b, Ws, bs)]
+        ws = torch.empty(B.slicegcn_layer_bwd_workspace_bytes(g, w_in, w_out, dX is not None), dtype=torch.uint8, device="cuda")
+        B.slicegcn_layer_bwd(g, X, W, Ws, Z, words, G, dX, *grads, ws)
+        got.append([t for t in grads if t is not None])
+    assert all(map(torch.equal, *got)) and not any(bool((t == 7.0).any()) for t in got[0])
+    g.destroy()
