@@ -1953,20 +1953,27 @@ int launch_grad_rows(ReduceArgs r, const ReduceBatch &b, int batch, int products
 // weight gradients (products x grad_x), the others what pair_strip32_kernel or pair_rows_kernel would.  Backward passes of dense
 // layers, in two launches / one: 1000 rows 64 -> 8 10.1 / 6.8 us, 2048 rows 64 -> 64 11.9 / 8.8, 20 k rows 64 -> 64 27.2 / 23.1, 60 k rows
 // 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1, 169 k rows 256 -> 40 232 / 220, 400 k rows 128 -> 40 300 / 262 (with the two
-// kinds of workgroups in turn 337 and 392: the long ones have to start first); of slice layers 2048 rows 64 -> 32 18.5 / 12.9, 30 k rows 64 -> 64 39.5 / 35.9.
-template <int WJ, int NT, bool TWO> // NT: tiles of 32 columns, 0 for the strips
+// kinds of workgroups in turn 337 and 392: the long ones have to start first).  The two products of a slice layer, dZ and T, are workgroups of
+// their own (pair_x each): half the chain, and nothing is shared but dHout.  Backward passes of slice layers, two launches / one / one with the
+// products apart: 2048 rows 64 -> 32 18.5 / 12.9 / 13.0 us, 30 k rows 64 -> 64 39.5 / 35.9 / 33.6, 5000 rows 64 -> 64 22.3 / 17.8 / 15.7.
+template <int WJ, int NT> // NT: tiles of 32 columns, 0 for the strips
 __global__ __launch_bounds__(256, 3) void grad_pair_kernel(const ReduceArgs r, const ReduceBatch rb, const PairArgs p, const PairBatch pb,
-                                                           uint32_t grad_x, uint32_t grads, int n_tiles, int n_col)
+                                                           uint32_t grad_x, uint32_t grads, int n_tiles, uint32_t pair_x, int n_col)
 {
     const uint32_t wg = blockIdx.x;
     if (wg < grads) {
         const bool self = wg >= grad_x;
         grad_rows_tile<1, 1, WJ>(slice_of(r, rb, blockIdx.y), self ? wg - grad_x : wg, self, n_tiles);
-    } else if constexpr (NT == 0) {
-        pair_strip32<true, TWO>(slice_of(p, pb), wg - grads, gridDim.x - grads);
-    } else {
-        pair_rows_tile<NT, TWO, true>(slice_of(p, pb), wg - grads, n_col);
+        return;
     }
+    PairArgs a = slice_of(p, pb);
+    uint32_t at = wg - grads;
+    if (at >= pair_x) {
+        at -= pair_x;
+        a.B1 = a.B2; a.O1 = a.O2; a.ldo1 = a.ldo2; a.mask = nullptr; a.scale_o1 = nullptr;
+    }
+    if constexpr (NT == 0) pair_strip32<true, false>(a, at, pair_x);
+    else pair_rows_tile<NT, false, true>(a, at, n_col);
 }
 
 // Whether the n x w rows at o, in leading dimension ldo, may share memory with those at x (by the address ranges from first to last element)
@@ -2004,22 +2011,21 @@ int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, 
     t.j_tiles = g.j_tiles;
     const PairBatch pb = pair_batch(list, batch);
     const uint32_t grad_x = (uint32_t)g.blocks, grads = grad_x * products;
-    const dim3 grid(grads + (unsigned)f.blocks, (unsigned)batch);
-    auto launch = [&](auto wj, auto nt, auto two) {
-        grad_pair_kernel<wj.value, nt.value, two.value><<<grid, 256, 0, stream>>>(t, b, list[0], pb, grad_x, grads, g.n_tiles, f.n_col);
+    const uint32_t pair_x = (uint32_t)f.blocks;
+    const dim3 grid(grads + pair_x * (f.two && list[0].O2 ? 2 : 1), (unsigned)batch);
+    auto launch = [&](auto wj, auto nt) {
+        grad_pair_kernel<wj.value, nt.value><<<grid, 256, 0, stream>>>(t, b, list[0], pb, grad_x, grads, g.n_tiles, pair_x, f.n_col);
     };
     const std::integral_constant<int, 0> c0;
     const std::integral_constant<int, 1> c1;
     const std::integral_constant<int, 2> c2;
-    const std::true_type yes;
-    const std::false_type no;
-    switch (3 * g.wj + f.nt) { // wj > 0, layers wider than 64: one product, no strips
-    case 0: f.two ? launch(c0, c0, yes) : launch(c0, c0, no); break;
-    case 1: f.two ? launch(c0, c1, yes) : launch(c0, c1, no); break;
-    case 4: launch(c1, c1, no); break;
-    case 5: launch(c1, c2, no); break;
-    case 7: launch(c2, c1, no); break;
-    default: launch(c2, c2, no); break;
+    switch (3 * g.wj + f.nt) { // wj > 0, layers wider than 64: no strips
+    case 0: launch(c0, c0); break;
+    case 1: launch(c0, c1); break;
+    case 4: launch(c1, c1); break;
+    case 5: launch(c1, c2); break;
+    case 7: launch(c2, c1); break;
+    default: launch(c2, c2); break;
     }
     SG_LAUNCH_CHECK();
     *pair_done = true;
