@@ -789,7 +789,10 @@ __device__ inline void emit_piece(const Buckets &s, const EmitArgs &a, const K *
         k[u] = __builtin_nontemporal_load(mine + (i < count ? i : count - 1));
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = a.dinv[row0 + (int64_t)(k[u] >> s.col_bits)] * a.dinv[(int32_t)(k[u] & col_mask)];
+    for (int u = 0; u < U; ++u) { // (at workgroup scope: past L1)
+        const float other = __hip_atomic_load(a.dinv + (int32_t)(k[u] & col_mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        v[u] = a.dinv[row0 + (int64_t)(k[u] >> s.col_bits)] * other;
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int i = u * 256 + (int)threadIdx.x;
@@ -800,8 +803,9 @@ __device__ inline void emit_piece(const Buckets &s, const EmitArgs &a, const K *
     }
 }
 // Workgroup b writes the first EMIT_PIECE entries of bucket b, the workgroups behind those the listed pieces in turn.  What bounds it is the
-// gather of dinv[col], 118 G/s at 2.4 M nodes: what streams past is kept out of the way of the gathered lines (1.09 -> 1.05 ms for 126 M
-// entries).  A 16-bit table of degrees in dinv's place, with the roots in LDS, fits the L2s but was slower (1.2 to 1.3 ms).
+// gather of dinv[col], 123 G/s at 2.4 M nodes: what streams past is kept out of the way of the gathered lines (1.09 -> 1.06 ms for 126 M
+// entries), and the gathers themselves out of L1 (1.02; as non-temporal loads 2.03).  A 16-bit table of degrees in dinv's place, with the
+// roots in LDS, fits the L2s but was slower (1.2 to 1.3 ms).
 template <class K>
 __global__ __launch_bounds__(256) void emit_kernel(const Buckets s, const EmitArgs a, const K *__restrict__ keys)
 {
