@@ -140,12 +140,17 @@ __device__ inline int scan_digits(const int32_t *cnt, int32_t *off, int32_t *wav
 
 // Distributes a tile of the edge list: the keys are ranked by digit in LDS (in any order within a digit: they are sorted later), laid out by
 // digit there and written as one run per digit.  at[digit * tiles + tile]: where the tile's run of a digit starts.
-// BUCKET: the digit is the bucket, the key keeps the row within it; otherwise the key is the whole (row, col).
+// The key keeps the low row bits (mask row_mask) and the column.  BUCKET: the digit is the bucket, the row bits are those within it.
+// Otherwise there is a second pass.  32-bit keys: row bits within the bucket as well, and the second digit goes to an array of its own
+// (6 bytes a key instead of 8, of which the counting reads 2: 126 M keys distributed 0.59 -> 0.62 ms, counted 0.25 -> 0.09, distributed again
+// 0.38 -> 0.35); 64-bit keys: the whole row.
 template <class K, bool BUCKET>
-__global__ __launch_bounds__(PT) void distribute_edges_kernel(const EdgeList e, int64_t n_tiles, int n_digits, const int32_t *__restrict__ at, K *__restrict__ out)
+__global__ __launch_bounds__(PT) void distribute_edges_kernel(const EdgeList e, int64_t n_tiles, int n_digits, const int32_t *__restrict__ at, K *__restrict__ out,
+                                                              int bits2, uint16_t *__restrict__ second)
 {
+    constexpr bool SPLIT = !BUCKET && sizeof(K) == 4;
     __shared__ K keys[2 * TILE_ITEMS];
-    __shared__ uint16_t digit[BUCKET ? 2 * TILE_ITEMS : 1];
+    __shared__ uint16_t digit[BUCKET || SPLIT ? 2 * TILE_ITEMS : 1], digit2[SPLIT ? 2 * TILE_ITEMS : 1];
     __shared__ int32_t cnt[MAX_DIGITS], off[MAX_DIGITS], wave_sums[PT / 64];
     constexpr int J = TILE_ITEMS / PT;
     cnt[threadIdx.x] = 0;
@@ -171,16 +176,20 @@ __global__ __launch_bounds__(PT) void distribute_edges_kernel(const EdgeList e, 
 #pragma unroll
         for (int w = 0; w < 2; ++w)
             if (rank[j][w] >= 0) {
-                const uint32_t d = row[j][w] >> e.shift, r = BUCKET ? row[j][w] & ((1u << e.shift) - 1u) : row[j][w];
+                const int within = e.shift - (SPLIT ? bits2 : 0); // row bits within the bucket
+                const uint32_t d = row[j][w] >> e.shift, r = BUCKET || SPLIT ? row[j][w] & ((1u << within) - 1u) : row[j][w];
                 const int pos = off[d] + rank[j][w];
                 keys[pos] = ((K)r << e.col_bits) | (K)col[j][w];
-                if (BUCKET) digit[pos] = (uint16_t)d;
+                if (BUCKET || SPLIT) digit[pos] = (uint16_t)d;
+                if (SPLIT) digit2[pos] = (uint16_t)((row[j][w] >> within) & ((1u << bits2) - 1u));
             }
     if ((int)threadIdx.x < n_digits) cnt[threadIdx.x] = at[(int64_t)threadIdx.x * n_tiles + blockIdx.x] - off[threadIdx.x]; // the ranks are in registers
     __syncthreads();
     for (int i = threadIdx.x; i < total; i += PT) {
         const K k = keys[i];
-        out[(int64_t)cnt[BUCKET ? digit[i] : (int)(k >> (e.col_bits + e.shift))] + i] = k;
+        const int64_t to = (int64_t)cnt[BUCKET || SPLIT ? digit[i] : (int)(k >> (e.col_bits + e.shift))] + i;
+        out[to] = k;
+        if (SPLIT) second[to] = digit2[i];
     }
 }
 
@@ -198,7 +207,8 @@ __global__ __launch_bounds__(PT) void tile_starts_kernel(const int32_t *__restri
 }
 
 struct SecondPass {
-    const uint64_t *keys;      // whole keys, by first-pass digit
+    const void *keys;          // by first-pass digit: keys of the sorting's type and their second digits, or whole 64-bit keys
+    const uint16_t *second;
     const int32_t *at1;        // see tile_starts_kernel
     const int32_t *tile_start; // [digits1 + 1]
     int64_t tiles1;
@@ -227,6 +237,19 @@ __device__ inline int64_t second_count(const SecondPass &p, const SecondTile &t,
     return ((int64_t)p.tile_start[t.d] << p.bits2) + (int64_t)d2 * t.tiles + t.tile;
 }
 
+// Key i as it is sorted, and its second digit
+template <class K> __device__ inline K low_key(const SecondPass &p, int64_t i)
+{
+    const K k = static_cast<const K *>(p.keys)[i];
+    return sizeof(K) == 4 ? k : k & (K)(((uint64_t)1 << (p.col_bits + p.row_shift)) - 1);
+}
+template <class K> __device__ inline int second_digit(const SecondPass &p, int64_t i)
+{
+    if constexpr (sizeof(K) == 4) return p.second[i];
+    else return (int)(static_cast<const K *>(p.keys)[i] >> (p.col_bits + p.row_shift)) & ((1 << p.bits2) - 1);
+}
+
+template <class K>
 __global__ __launch_bounds__(PT) void count_keys_kernel(const SecondPass p, int32_t *__restrict__ counts)
 {
     __shared__ int32_t cnt[MAX_DIGITS];
@@ -234,19 +257,18 @@ __global__ __launch_bounds__(PT) void count_keys_kernel(const SecondPass p, int3
     if (!second_tile(p, blockIdx.x, t)) return; // uniform per workgroup
     cnt[threadIdx.x] = 0;
     __syncthreads();
-    const int shift = p.col_bits + p.row_shift, mask = (1 << p.bits2) - 1;
     constexpr int J = TILE_KEYS / PT;
-    uint64_t k[J];
+    int d[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) { // every load before the first use
         const int64_t i = t.beg + j * PT + threadIdx.x;
-        k[j] = p.keys[i < t.end ? i : t.beg];
+        d[j] = second_digit<K>(p, i < t.end ? i : t.beg);
     }
 #pragma unroll
     for (int j = 0; j < J; ++j)
-        if (t.beg + j * PT + threadIdx.x < t.end) atomicAdd(&cnt[(int)(k[j] >> shift) & mask], 1);
+        if (t.beg + j * PT + threadIdx.x < t.end) atomicAdd(&cnt[d[j]], 1);
     __syncthreads();
-    if ((int)threadIdx.x <= mask) counts[second_count(p, t, threadIdx.x)] = cnt[threadIdx.x];
+    if ((int)threadIdx.x < 1 << p.bits2) counts[second_count(p, t, threadIdx.x)] = cnt[threadIdx.x];
 }
 
 template <class K>
@@ -260,29 +282,28 @@ __global__ __launch_bounds__(PT) void distribute_keys_kernel(const SecondPass p,
     if (!second_tile(p, blockIdx.x, t)) return; // uniform per workgroup
     cnt[threadIdx.x] = 0;
     __syncthreads();
-    const int shift = p.col_bits + p.row_shift, mask = (1 << p.bits2) - 1;
-    uint64_t k[J];
+    K k[J];
+    int d[J];
     int32_t rank[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-        const int64_t i = t.beg + j * PT + threadIdx.x;
-        k[j] = p.keys[i < t.end ? i : t.beg];
+        const int64_t i = t.beg + j * PT + threadIdx.x, from = i < t.end ? i : t.beg;
+        k[j] = low_key<K>(p, from);
+        d[j] = second_digit<K>(p, from);
     }
 #pragma unroll
-    for (int j = 0; j < J; ++j)
-        rank[j] = t.beg + j * PT + threadIdx.x < t.end ? atomicAdd(&cnt[(int)(k[j] >> shift) & mask], 1) : -1;
+    for (int j = 0; j < J; ++j) rank[j] = t.beg + j * PT + threadIdx.x < t.end ? atomicAdd(&cnt[d[j]], 1) : -1;
     __syncthreads();
     const int total = scan_digits(cnt, off, wave_sums);
     __syncthreads();
-    const uint64_t low = ((uint64_t)1 << shift) - 1;
 #pragma unroll
     for (int j = 0; j < J; ++j)
         if (rank[j] >= 0) {
-            const int d = (int)(k[j] >> shift) & mask, pos = off[d] + rank[j];
-            keys[pos] = (K)(k[j] & low);
-            digit[pos] = (uint16_t)d;
+            const int pos = off[d[j]] + rank[j];
+            keys[pos] = k[j];
+            digit[pos] = (uint16_t)d[j];
         }
-    if ((int)threadIdx.x <= mask) cnt[threadIdx.x] = at[second_count(p, t, threadIdx.x)] - off[threadIdx.x];
+    if ((int)threadIdx.x < 1 << p.bits2) cnt[threadIdx.x] = at[second_count(p, t, threadIdx.x)] - off[threadIdx.x];
     __syncthreads();
     for (int i = threadIdx.x; i < total; i += PT) out[(int64_t)cnt[digit[i]] + i] = keys[i];
 }
@@ -893,24 +914,25 @@ int sort_rows(const Layout &l, const int64_t *row, const int64_t *col, int64_t n
         count_edges_kernel<<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, counts, n_bad);
         SG_LAUNCH_CHECK();
         if (int rc = scan_i32(counts, at1, p.counts1(), ws, stream)) return rc; // the last element is only written: the total
-        SecondPass s{nullptr, at1, nullptr, p.tiles1, digits1, p.bits2, p.col_bits, p.row_shift};
+        SecondPass s{nullptr, nullptr, at1, nullptr, p.tiles1, digits1, p.bits2, p.col_bits, p.row_shift};
         int32_t *at2 = nullptr;
         if (p.bits2 == 0) {
-            distribute_edges_kernel<K, true><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, keys);
+            distribute_edges_kernel<K, true><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, keys, 0, nullptr);
             SG_LAUNCH_CHECK();
         } else {
-            uint64_t *whole = reinterpret_cast<uint64_t *>(spare);
+            uint16_t *second = sizeof(K) == 4 ? reinterpret_cast<uint16_t *>(spare + p.max_keys) : nullptr; // spare has 8 bytes a key
             int32_t *counts2 = nullptr, *tile_start = nullptr;
             if (int rc = ws.take((size_t)p.counts2() * 4, &counts2)) return rc;
             if (int rc = ws.take((size_t)p.counts2() * 4, &at2)) return rc;
             if (int rc = ws.take((size_t)(MAX_DIGITS + 1) * 4, &tile_start)) return rc;
-            s.keys = whole;
+            s.keys = spare;
+            s.second = second;
             s.tile_start = tile_start;
-            distribute_edges_kernel<uint64_t, false><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, whole);
+            distribute_edges_kernel<K, false><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, spare, p.bits2, second);
             SG_LAUNCH_CHECK();
             tile_starts_kernel<<<1, PT, 0, stream>>>(at1, p.tiles1, digits1, tile_start);
             SG_LAUNCH_CHECK();
-            count_keys_kernel<<<(unsigned)p.max_tiles2, PT, 0, stream>>>(s, counts2);
+            count_keys_kernel<K><<<(unsigned)p.max_tiles2, PT, 0, stream>>>(s, counts2);
             SG_LAUNCH_CHECK();
             if (int rc = scan_i32(counts2, at2, p.counts2(), ws, stream)) return rc; // elements past the last tile's are not used
             distribute_keys_kernel<K><<<(unsigned)p.max_tiles2, PT, 0, stream>>>(s, at2, keys);
