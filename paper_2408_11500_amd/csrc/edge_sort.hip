@@ -39,7 +39,9 @@ constexpr int DIGIT_BITS = 9, MAX_DIGITS = 1 << DIGIT_BITS, MAX_BITS = 2 * DIGIT
 constexpr int64_t BUCKET_KEYS = 2048;
 constexpr int MAX_ROW_SHIFT = 11;
 constexpr int PT = 512;           // threads of a distributing workgroup
-constexpr int TILE_ITEMS = 4096;  // edges (two keys each) or diagonal entries a workgroup takes from the edge list
+// edges (two keys each) or diagonal entries a workgroup takes from the edge list: longer runs per digit or more workgroups on a CU (126 M keys,
+// distributed: 2048 0.61 ms, 2560 0.60, 3072 0.57, 3584 0.64, 4096 0.62)
+constexpr int TILE_ITEMS = 3072;
 constexpr int TILE_KEYS = 8192;   // keys a workgroup takes in the second pass
 constexpr int SORT_KEYS = 8192;   // most keys one workgroup sorts in registers
 constexpr int MOST_KEYS = 16384;  // most a larger workgroup does; buckets of more are cut once more
@@ -140,9 +142,9 @@ __device__ inline int scan_digits(const int32_t *cnt, int32_t *off, int32_t *wav
 
 // Distributes a tile of the edge list: the keys are ranked by digit in LDS (in any order within a digit: they are sorted later), laid out by
 // digit there and written as one run per digit.  at[digit * tiles + tile]: where the tile's run of a digit starts.
-// The key keeps the low row bits (mask row_mask) and the column.  BUCKET: the digit is the bucket, the row bits are those within it.
+// BUCKET: the digit is the bucket, the key has the row within it and the column.
 // Otherwise there is a second pass.  32-bit keys: row bits within the bucket as well, and the second digit goes to an array of its own
-// (6 bytes a key instead of 8, of which the counting reads 2: 126 M keys distributed 0.59 -> 0.62 ms, counted 0.25 -> 0.09, distributed again
+// (6 bytes a key instead of 8, of which the counting reads 2: 126 M keys distributed 0.59 -> 0.57 ms, counted 0.25 -> 0.09, distributed again
 // 0.38 -> 0.35); 64-bit keys: the whole row.
 template <class K, bool BUCKET>
 __global__ __launch_bounds__(PT) void distribute_edges_kernel(const EdgeList e, int64_t n_tiles, int n_digits, const int32_t *__restrict__ at, K *__restrict__ out,
