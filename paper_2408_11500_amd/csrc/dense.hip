@@ -42,7 +42,7 @@ struct PairArgs {
 // The same products for a batch of slice models (equal shapes and leading dimensions): grid row y works on slice y, with
 // the pointers taken from here.  Small graphs need it: their kernels last microseconds and fill a fraction of the chip.
 constexpr int BATCH = SPMM_BATCH;
-// From so many rows of all slices of a launch on, layers up to 64 wide take the strip kernel (64 -> 64 with self term, strips / pair_rows_kernel:
+// From so many rows of all slices of a launch on, layers up to 64 wide take a strip kernel (64 -> 64 with self term, strips / pair_rows_kernel:
 // four slices of 66 k rows forward 75 / 71 us, backward 69 / 78; of 169 k rows 149 / 157 and 130 / 172).
 constexpr int64_t STRIP64_ROWS = 262144;
 struct PairPtrs {
@@ -864,7 +864,10 @@ inline PairForm pair_form(const PairArgs *list, int batch)
     const PairArgs &a = list[0];
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
     const int64_t strips = (a.n + 31) / 32, strip_blocks = (strips + 3) / 4;
-    if (a.K >= 4 && a.K <= 32 && a.Nout <= 32) // narrowest layers: per-wavefront strips, no barriers
+    // narrowest layers: per-wavefront strips, no barriers; but not on few rows whose K is a whole chunk of pair_rows_kernel, which issues far
+    // fewer instructions per row there and keeps more wavefronts on a SIMD (32 -> 32 with self term, strips / rows: 40 k rows 8.3 / 7.8 us, 80 k
+    // 13.4 / 11.2, 150 k 23.5 / 18.8, 200 k 29.7 / 21.9; input gradients of 100 k rows 12.3 / 8.1; K = 16, 20 k rows 6.2 / 7.8)
+    if (a.K >= 4 && a.K <= 32 && a.Nout <= 32 && (a.K < 32 || a.n * batch >= STRIP64_ROWS))
         return PairForm{PairForm::STRIP32, two, strip_blocks < 2048 ? strip_blocks : 2048, 0, 0};
     if (a.K >= 4 && a.K <= 64 && a.Nout <= 64 && a.n * batch >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
         // as many workgroups as the chip holds at once (two per CU): each stages the weights once (four slices of 169 k rows with 2048

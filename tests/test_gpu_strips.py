@@ -84,3 +84,27 @@ def test_layer_matches_fp64(graphs, n, w_in, w_out, self_term, pad):
         if self_term:
             assert_fp32(dWs, Xd.t() @ Gd, Xd.abs().t() @ Gd.abs(), "dW_self")
             assert_fp32(dbs, Gd.sum(0), Gd.abs().sum(0), "db_self")
+
+
+@pytest.mark.parametrize("w_out", [32, 20])
+@pytest.mark.parametrize("self_term", [True, False])
+def test_rows_and_strips_have_the_same_bits(w_out, self_term):
+    """32 columns in: strips from 2^18 rows on, the general kernel below; the last call has one row less."""
+    n, w_in = 1 << 18, 32
+    gen = torch.Generator(device="cuda").manual_seed(w_out)
+    X, G, W, Ws = (torch.randn(s, generator=gen, device="cuda") for s in ((n, w_in), (n, w_out), (w_in, w_out), (w_in, w_out)))
+    b, bs = (torch.randn(w_out, generator=gen, device="cuda") for _ in range(2))
+    if not self_term:
+        Ws = bs = None
+    none, got = torch.empty(0, dtype=torch.int64, device="cuda"), []
+    for rows in (n, n - 1):
+        g = B.slicegcn_build_norm_csr(none, none, rows)
+        Z, H, words = torch.empty((rows, w_in), device="cuda"), torch.empty((rows, w_out), device="cuda"), torch.zeros((rows, 1), dtype=torch.int32, device="cuda")
+        B.slicegcn_layer_fwd(g, X[:rows], W, b, Ws, bs, H, Z, words)
+        Y, bits = torch.empty((rows, w_out), device="cuda"), torch.zeros((rows, 1), dtype=torch.int32, device="cuda")
+        B.slicegcn_linear_fwd(X[:rows], W, b, Y, bits, act=B.ACT_RELU)
+        dX = torch.empty((rows, w_out), device="cuda")   # backward: the product with 32 columns in is that of a layer w_out -> 32
+        B.slicegcn_linear_bwd(G[:rows], W.t().contiguous(), None, X[:rows], dX, None, None, None, act=B.ACT_NONE)
+        got.append([t[:n - 1] for t in (H, words, Y, bits, dX)])
+        g.destroy()
+    assert all(map(torch.equal, *got))
