@@ -132,7 +132,8 @@ __device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int wi
 // by a whole term: every kernel and size gives the same bits for the same operands.  (Operands split into three bf16
 // terms on the bf16 matrix cores were as exact against fp64 and faster, 2.4 M rows 256 -> 256 2.16 ms, but rounded differently.)
 // Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 2.98 ms = 108 TFLOP/s (a kernel with rows and weights in LDS: 3.71), 169 k rows
-// 0.238 (0.288); slice layers 64 -> 64 with self term, 169 k rows: 47 us (61).
+// 0.238 (0.288); slice layers 64 -> 64 with self term, 169 k rows: 47 us (61).  A last chunk ends with its steps, in eights (before, all 32 were
+// multiplied: input gradients of 169 k rows 256 -> 40 80 -> 68 us, 2.4 M rows 256 -> 47 1.25 -> 1.15 ms; 100 k rows 200 -> 200 131 -> 122 us).
 template <int NT, bool TWO, bool BWD>
 __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, int n_col_tiles)
 {
@@ -280,11 +281,13 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
             for (int q = 0; q < KC / 8; ++q) x[q] *= f_in;
         }
         if (more) fetch_rows(cc + 1);
+        const int left = a.K - (TWO && cc >= chunks ? cc - chunks : cc) * KC; // steps of the product from this chunk on
         floatx4 w[2][NT]; // the weights of four steps are read while the four before them are multiplied
 #pragma unroll
         for (int t = 0; t < NT; ++t) w[0][t] = Bs[cc & 1][h][32 * t + m];
 #pragma unroll
         for (int q = 0; q < KC / 8; ++q) {
+            if (q > 0 && 8 * q >= left) break; // uniform; both operands are zero from here on
             if (q + 1 < KC / 8) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) w[(q + 1) & 1][t] = Bs[cc & 1][2 * (q + 1) + h][32 * t + m];
