@@ -118,6 +118,19 @@ __device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int wi
     }
 }
 
+// Four columns of a row from column c on, `left` of which exist; WHOLE: all four, of a row that exists
+template <bool WHOLE> __device__ inline void store_cols4(float *o, const float4 &v, bool row_ok, int left)
+{
+    if (WHOLE || (row_ok && left >= 4)) {
+        const floatx4_u w = {v.x, v.y, v.z, v.w};
+        *reinterpret_cast<floatx4_u *>(o) = w;
+    } else if (row_ok) {
+        if (left > 0) o[0] = v.x;
+        if (left > 1) o[1] = v.y;
+        if (left > 2) o[2] = v.z;
+    }
+}
+
 // Products of every layer the strip kernels do not take.  Forward: Hout = act(Z W_agg + b) + Hin W_self + b_self; backward: dZ = (dHout *
 // mask) W_agg^T, then T = dHout W_self^T over the same accumulators.  Workgroup = 4 wavefronts; a wavefront owns 32 rows and all
 // NT * 32 columns of the workgroup's tile.  A row is used by one wavefront only, so it goes from memory straight into
@@ -131,14 +144,17 @@ __device__ inline void store_tile_row(const floatx16 &c, float *o, int h, int wi
 // activation passes depends on the last bit of its sum where that is near zero (a few in 10^8), and then a row's gradient changes
 // by a whole term: every kernel and size gives the same bits for the same operands.  (Operands split into three bf16
 // terms on the bf16 matrix cores were as exact against fp64 and faster, 2.4 M rows 256 -> 256 2.16 ms, but rounded differently.)
-// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 2.98 ms = 108 TFLOP/s (a kernel with rows and weights in LDS: 3.71), 169 k rows
+// Bound by the matrix cores when wide: 2.4 M rows 256 -> 256 2.93 ms = 110 TFLOP/s (a kernel with rows and weights in LDS: 3.71), 169 k rows
 // 0.238 (0.288); slice layers 64 -> 64 with self term, 169 k rows: 47 us (61).  A last chunk ends with its steps, in eights (before, all 32 were
 // multiplied: input gradients of 169 k rows 256 -> 40 80 -> 68 us, 2.4 M rows 256 -> 47 1.25 -> 1.15 ms; 100 k rows 200 -> 200 131 -> 122 us).
 template <int NT, bool TWO, bool BWD>
 __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, int n_col_tiles)
 {
     constexpr int BN = NT * 32, KC = 32, GS = BN + 4; // GS: units per group of four k (padded: conflict-free writes and reads)
-    __shared__ floatx4 Bs[2][KC / 4][GS];
+    constexpr int TS = 36; // row stride of a wavefront's output tile
+    constexpr int POOL = 2 * (KC / 4) * GS > 4 * 32 * TS / 4 ? 2 * (KC / 4) * GS : 4 * 32 * TS / 4;
+    __shared__ floatx4 pool[POOL]; // the weights; behind the last chunk the output tiles
+    floatx4 (*Bs)[KC / 4][GS] = reinterpret_cast<floatx4 (*)[KC / 4][GS]>(pool);
     __shared__ __attribute__((aligned(16))) float bias_s[2][BN];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
@@ -253,6 +269,37 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
 #pragma unroll
         for (int t = 0; t < NT; ++t) store_tile_row(acc[t], O + row * ldo + col0 + 32 * t, h, a.Nout - col0 - 32 * t, f);
     };
+    // Behind the last chunk: through LDS, so that a row of a tile goes out as eight 16-byte stores of one instruction (from the accumulators
+    // an instruction stores 32 bytes to each of 32 rows, which takes the CU's L1 64 cycles instead of 16: 2.4 M rows 47 -> 256 1.23 -> 1.02 ms,
+    // 256 -> 256 3.03 -> 2.93, 169 k rows 40 -> 256 87 -> 68 us).
+    auto store_last = [&](float *O, int64_t ldo, float f) {
+        float (*tile)[TS] = reinterpret_cast<float (*)[TS]>(pool) + 32 * wave;
+        const int lr = lane >> 3, lc = (lane & 7) * 4;
+        const int64_t row0 = row_tile * 128 + wave * 32;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int left = a.Nout - col0 - 32 * t;
+            if (left <= 0) break; // uniform
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                floatx4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = acc[t][4 * q + i] * f;
+                *reinterpret_cast<floatx4 *>(&tile[m][8 * q + 4 * h]) = v;
+            }
+            __builtin_amdgcn_wave_barrier();
+            float *o = O + (row0 + lr) * ldo + col0 + 32 * t + lc;
+            if (row0 + 32 <= a.n && left >= 32) { // uniform per wavefront
+#pragma unroll
+                for (int it = 0; it < 4; ++it) store_cols4<true>(o + 8 * it * ldo, *reinterpret_cast<const float4 *>(&tile[lr + 8 * it][lc]), true, 32);
+            } else {
+#pragma unroll
+                for (int it = 0; it < 4; ++it)
+                    store_cols4<false>(o + 8 * it * ldo, *reinterpret_cast<const float4 *>(&tile[lr + 8 * it][lc]), row0 + lr + 8 * it < a.n, left - lc);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
 
     clear();
     fetch_weights(0);
@@ -287,7 +334,8 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
         for (int t = 0; t < NT; ++t) w[0][t] = Bs[cc & 1][h][32 * t + m];
 #pragma unroll
         for (int q = 0; q < KC / 8; ++q) {
-            if (q > 0 && 8 * q >= left) break; // uniform; both operands are zero from here on
+            // uniform; both operands are zero from here on (not with both products of a backward pass: it costs them 20 registers)
+            if (!(TWO && BWD) && q > 0 && 8 * q >= left) break;
             if (q + 1 < KC / 8) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) w[(q + 1) & 1][t] = Bs[cc & 1][2 * (q + 1) + h][32 * t + m];
@@ -314,8 +362,8 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
         }
     }
     if constexpr (BWD) {
-        if (!TWO) store_all(a.O1, a.ldo1, 1.f);
-        else if (a.O2) store_all(a.O2, a.ldo2, 1.f);
+        if (!TWO) store_last(a.O1, a.ldo1, 1.f);
+        else if (a.O2) store_last(a.O2, a.ldo2, 1.f);
     } else {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -330,7 +378,7 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
                 activate(acc[t], t);
             }
         }
-        store_all(a.O1, a.ldo1, a.scale_o1 ? a.scale_o1[row] : 1.f);
+        store_last(a.O1, a.ldo1, a.scale_o1 ? a.scale_o1[row] : 1.f);
     }
 }
 template <int NT, bool TWO, bool BWD>
@@ -372,19 +420,6 @@ template <bool NARROW = false> struct LaneCols {
         v.w = none || two ? 0.f : w;
     }
 };
-
-// Four columns of a row from column c on, `left` of which exist; WHOLE: all four, of a row that exists
-template <bool WHOLE> __device__ inline void store_cols4(float *o, const float4 &v, bool row_ok, int left)
-{
-    if (WHOLE || (row_ok && left >= 4)) {
-        const floatx4_u w = {v.x, v.y, v.z, v.w};
-        *reinterpret_cast<floatx4_u *>(o) = w;
-    } else if (row_ok) {
-        if (left > 0) o[0] = v.x;
-        if (left > 1) o[1] = v.y;
-        if (left > 2) o[2] = v.z;
-    }
-}
 
 // Variant for the narrowest layers (4 <= K <= 32, at most 32 output columns: every layer of the workload
 // with slices and hidden width 32).  These layers are HBM bound (about 10 flop per byte), so the kernel
