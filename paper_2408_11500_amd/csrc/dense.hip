@@ -1877,7 +1877,7 @@ inline GradPlan grad_plan(int64_t n, int32_t w_in, int32_t w_out)
 }
 
 // A dense layer's weight and bias gradients: by grad_rows_kernel or, where both widths are large, in 128 x 128 tiles (`big`: layers
-// wider than 64; see launch_grad_rows), a partial sum per RED_ROWS node rows.  On few rows that leaves most of the chip idle behind
+// wider than 64; see grad_form), a partial sum per RED_ROWS node rows.  On few rows that leaves most of the chip idle behind
 // chains of RED_ROWS rows, so up to SMALL_LINEAR elements of the wider operand the rows are split until 512 workgroups of one tile are
 // there or a workgroup is down to one step, as far as the workspace has room (`capacity` partial sums; the least workspace leaves
 // RED_ROWS): the last bits of these gradients depend on it.  Split / in chains of 1024, 96 -> 96: 1000 rows 11 / 57 us, 5000 rows
