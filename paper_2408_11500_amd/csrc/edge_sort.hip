@@ -20,6 +20,8 @@ namespace {
 
 constexpr int TPB = 256;
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + TPB - 1) / TPB); }
+// pieces of at most `size` that `count` items fill; counts reach 2^31 - 1, where adding size - 1 first would not fit
+__device__ inline int32_t pieces_of(int32_t count, int32_t size) { return count / size + (count % size != 0 ? 1 : 0); }
 inline unsigned bits_for(uint64_t v)
 {
     unsigned b = 1;
@@ -201,7 +203,7 @@ __global__ __launch_bounds__(PT) void tile_starts_kernel(const int32_t *__restri
 {
     __shared__ int32_t cnt[MAX_DIGITS], off[MAX_DIGITS], wave_sums[PT / 64];
     const int d = threadIdx.x;
-    cnt[d] = d < n_digits ? (at1[(int64_t)(d + 1) * tiles1] - at1[(int64_t)d * tiles1] + TILE_KEYS - 1) / TILE_KEYS : 0;
+    cnt[d] = d < n_digits ? pieces_of(at1[(int64_t)(d + 1) * tiles1] - at1[(int64_t)d * tiles1], TILE_KEYS) : 0;
     __syncthreads();
     const int total = scan_digits(cnt, off, wave_sums);
     if (d < n_digits) tile_start[d] = off[d];
@@ -522,7 +524,7 @@ constexpr int EMIT_PIECE = 2048; // entries a workgroup writes
 // lists pieces `first` ... of a bucket or part with so many distinct keys
 __device__ inline void list_pieces(const Buckets &s, int64_t id, int32_t kept, int32_t first, int tid)
 {
-    const int32_t all = (kept + EMIT_PIECE - 1) / EMIT_PIECE, more = all - first;
+    const int32_t more = pieces_of(kept, EMIT_PIECE) - first;
     if (more <= 0) return; // uniform per workgroup
     __shared__ int32_t at;
     if (tid == 0) at = atomicAdd(s.n_pieces, more);
@@ -558,7 +560,7 @@ __global__ __launch_bounds__(256) void sort_buckets_kernel(const Buckets s, cons
     const int64_t b = blockIdx.x, row0 = b << s.row_shift;
     const int32_t beg = s.start[b], cnt = s.start[b + 1] - beg;
     if (cnt > MOST_KEYS) { // uniform per workgroup
-        const int32_t tiles = (cnt + TILE_KEYS - 1) / TILE_KEYS;
+        const int32_t tiles = pieces_of(cnt, TILE_KEYS);
         if (tid == 0) {
             place = atomicAdd(s.n_huge, 1);
             first_tile = atomicAdd(s.n_tiles, tiles);

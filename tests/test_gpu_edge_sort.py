@@ -103,6 +103,25 @@ def test_all_pairs_alike():
     check(src, dst, n, ALL)
 
 
+def test_most_candidates_in_one_bucket():
+    """2^31 - 1 candidate entries, the most that is accepted, nearly all of them in one bucket: its tiles are counted in 32 bits."""
+    n, m = 1000, 2 ** 31 - 1
+    src, dst = (torch.full((m,), v, dtype=torch.int64, device="cuda") for v in (7, 9))
+    src[-3:], dst[-3:] = torch.tensor([999, 7, 0], device="cuda"), torch.tensor([0, 8, 999], device="cuda")
+    g = sg.slicegcn_build_norm_csr(src, dst, n, 0)
+    del src, dst
+    rowptr, colidx, deg, _, _ = arrays(g)
+    assert torch.nonzero(deg)[:, 0].tolist() == [0, 7, 999] and deg[[0, 7, 999]].tolist() == [1, 2, 1]
+    assert colidx.tolist() == [999, 8, 9, 0] and int(rowptr[-1]) == 4
+    X = torch.randn((n, 4), device="cuda")
+    Y = torch.empty_like(X)
+    sg.slicegcn_spmm_slice(g, X, Y, transpose=True)
+    # row 9 of the transposed pattern: 1 / sqrt(2 entries in row 7) times 1 (row 9 is empty)
+    assert torch.allclose(Y[9], X[7] / 2 ** 0.5, rtol=1e-6, atol=0) and not bool(Y[1:8].any())
+    g.destroy()
+    torch.cuda.empty_cache()
+
+
 def test_star():
     n = 300_001
     check(np.zeros(n - 1, np.int64), np.arange(1, n), n, ALL)
