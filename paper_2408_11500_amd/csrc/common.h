@@ -38,6 +38,19 @@ void set_error(const char *fmt, ...) __attribute__((format(printf, 1, 2)));
 
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
+
+// A grid holds fewer than 2^32 threads along a dimension; one of more wraps and runs a part of its workgroups without an error.  Grids that can
+// come near that are launched in parts of so many workgroups (of 256 threads; a multiple of the number of XCDs): launch(first, count)
+constexpr int64_t MAX_GRID = (int64_t)1 << 23;
+template <class F> inline int launch_parts(int64_t blocks, F launch)
+{
+    for (int64_t first = 0; first < blocks; first += MAX_GRID) {
+        launch((unsigned)first, (unsigned)(blocks - first < MAX_GRID ? blocks - first : MAX_GRID));
+        SG_LAUNCH_CHECK();
+    }
+    return SLICEGCN_OK;
+}
+
 __host__ __device__ inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // ---- aggregation schedule -------------------------------------------------------------

@@ -560,13 +560,13 @@ __device__ __forceinline__ void tiny_rows_body(const SpmmArgs &a, const SpmmIo &
 }
 
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_wave_items_kernel(const SpmmArgs a, const SpmmBatch b) { const SpmmIo io = pick_io(a, b); wave_items_body<LPR, V, S32, FACT, RAG>(a, io, blockIdx.x); }
+__global__ __launch_bounds__(256) void spmm_wave_items_kernel(const SpmmArgs a, const SpmmBatch b, unsigned first) { const SpmmIo io = pick_io(a, b); wave_items_body<LPR, V, S32, FACT, RAG>(a, io, blockIdx.x + first); }
 
 template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_group_items_kernel(const SpmmArgs a, const SpmmBatch b) { const SpmmIo io = pick_io(a, b); group_items_body<LPR, V, S32, GI_MAX, FACT, RAG>(a, io, blockIdx.x); }
+__global__ __launch_bounds__(256) void spmm_group_items_kernel(const SpmmArgs a, const SpmmBatch b, unsigned first) { const SpmmIo io = pick_io(a, b); group_items_body<LPR, V, S32, GI_MAX, FACT, RAG>(a, io, blockIdx.x + first); }
 
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a, const SpmmBatch b) { const SpmmIo io = pick_io(a, b); tiny_rows_body<LPR, V, S32, FACT, RAG>(a, io, blockIdx.x); }
+__global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a, const SpmmBatch b, unsigned first) { const SpmmIo io = pick_io(a, b); tiny_rows_body<LPR, V, S32, FACT, RAG>(a, io, blockIdx.x + first); }
 
 // All three item kinds in one launch: workgroups [0, g1) take wavefront items, [g1, g1 + g2)
 // lane-group items, the rest tiny rows (g1 and g2 are multiples of 8, so workgroup b still
@@ -575,10 +575,10 @@ __global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a, c
 // they overlap (cfg2: 0.075 -> 0.056 ms per call).  Large graphs keep the three launches: there the
 // class pieces must have the L2s to themselves before the whole rows start (merged: cfg5 4.09 -> 4.30 ms).
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_merged_kernel(const SpmmArgs a, const SpmmBatch batch, int g1, int g2)
+__global__ __launch_bounds__(256) void spmm_merged_kernel(const SpmmArgs a, const SpmmBatch batch, int g1, int g2, unsigned first)
 {
     const SpmmIo io = pick_io(a, batch);
-    const int b = blockIdx.x; // uniform per workgroup
+    const int b = blockIdx.x + first; // uniform per workgroup
     if (b < g1) wave_items_run_body<LPR, V, S32, FACT, RAG>(a, io, b);
     else if (b < g1 + g2) group_items_body<LPR, V, S32, ITEM_SHORT, FACT, RAG>(a, io, b - g1);
     else tiny_rows_body<LPR, V, S32, FACT, RAG>(a, io, b - g1 - g2);
@@ -641,31 +641,34 @@ int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes,
     SG_REQUIRE(g1 + g2 + g3 + N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
     if (a.item_max <= ITEM_SHORT) { // cache-resident graph: one launch (big_blocks counts runs of 4 * ipw items)
         // the grid's first dimension is a multiple of 8, so that a class meets the same XCD in every slice and pass
-        dim3 grid((unsigned)round_up(g1 + g2 + g3, N_CLASSES), (unsigned)batch, (unsigned)passes);
+        const int64_t blocks = round_up(g1 + g2 + g3, N_CLASSES);
         if constexpr (V == 4 && S32 && FACT && !RAG) {
-            if (sums) {
-                const unsigned extra = (unsigned)round_up((sums->stride + FINAL_ELEMS - 1) / FINAL_ELEMS, N_CLASSES);
-                grid.x += extra;
+            const int64_t extra = sums ? round_up((sums->stride + FINAL_ELEMS - 1) / FINAL_ELEMS, N_CLASSES) : 0;
+            if (sums && blocks + extra <= MAX_GRID) {
+                const dim3 grid((unsigned)(blocks + extra), (unsigned)batch, (unsigned)passes);
                 spmm_merged_sums_kernel<LPR><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2, *sums, (int)extra);
                 SG_LAUNCH_CHECK();
                 return SLICEGCN_OK;
             }
         }
-        spmm_merged_kernel<LPR, V, S32, FACT, RAG><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2);
-        SG_LAUNCH_CHECK();
-        return SLICEGCN_OK;
+        if (sums)
+            if (int rc = launch_final_sum(*sums, batch, stream)) return rc;
+        return launch_parts(blocks, [&](unsigned first, unsigned count) {
+            spmm_merged_kernel<LPR, V, S32, FACT, RAG><<<dim3(count, (unsigned)batch, (unsigned)passes), 256, 0, stream>>>(a, b, (int)g1, (int)g2, first);
+        });
     }
-    if (g1 > 0) {
-        spmm_wave_items_kernel<LPR, V, S32, FACT, RAG><<<dim3((unsigned)g1, (unsigned)batch), 256, 0, stream>>>(a, b);
-        SG_LAUNCH_CHECK();
-    }
-    if (g2 > 0) {
-        spmm_group_items_kernel<LPR, V, S32, ITEM_LONG, FACT, RAG><<<dim3((unsigned)g2, (unsigned)batch), 256, 0, stream>>>(a, b);
-        SG_LAUNCH_CHECK();
-    }
-    spmm_tiny_rows_kernel<LPR, V, S32, FACT, RAG><<<dim3((unsigned)g3, (unsigned)batch), 256, 0, stream>>>(a, b);
-    SG_LAUNCH_CHECK();
-    return SLICEGCN_OK;
+    // a part of a grid starts at a multiple of 8, so that workgroup b still serves class b mod 8
+    if (int rc = launch_parts(g1, [&](unsigned first, unsigned count) {
+            spmm_wave_items_kernel<LPR, V, S32, FACT, RAG><<<dim3(count, (unsigned)batch), 256, 0, stream>>>(a, b, first);
+        }))
+        return rc;
+    if (int rc = launch_parts(g2, [&](unsigned first, unsigned count) {
+            spmm_group_items_kernel<LPR, V, S32, ITEM_LONG, FACT, RAG><<<dim3(count, (unsigned)batch), 256, 0, stream>>>(a, b, first);
+        }))
+        return rc;
+    return launch_parts(g3, [&](unsigned first, unsigned count) {
+        spmm_tiny_rows_kernel<LPR, V, S32, FACT, RAG><<<dim3(count, (unsigned)batch), 256, 0, stream>>>(a, b, first);
+    });
 }
 
 template <int LPR, int V, bool FACT>

@@ -30,3 +30,25 @@ def test_every_row_once(width, chunks):
         # fp32: three roundings of a stored value, one of its product, six of the sum, of terms that add up to at most max|X|
         assert float((Y.double() - want / 7).abs().max()) <= 11 * 2.0 ** -24 * float(X.abs().max())
         g.destroy()
+
+
+def test_more_workgroups_than_one_grid():
+    """Whole rows beyond the 2^32 threads of one grid: eight 128-column rows a workgroup, 2^27 rows and some.  Every row is formed."""
+    n = 2 ** 27 + 4099
+    v = torch.arange(n, device="cuda")
+    src, dst = torch.cat([v, v]), torch.cat([(v + 1) % n, (v + 5) % n])     # four neighbours and the diagonal
+    g = sg.slicegcn_build_norm_csr(src, dst, n)
+    del src, dst
+    x = (v % 61).float()
+    del v
+    torch.cuda.empty_cache()
+    X = torch.empty((n, 128), device="cuda").copy_(x[:, None])
+    Y = torch.full((n, 128), float("nan"), device="cuda")
+    sg.slicegcn_spmm_slice(g, X, Y)
+    want = (x + sum(torch.roll(x, s) for s in (1, 5, -1, -5))) / 5
+    for i in range(0, n, 2 ** 22):
+        # whole numbers up to 60 times 1/5 in fp32: three roundings of the stored value, one of each product, four of the sum
+        assert float((Y[i:i + 2 ** 22] - want[i:i + 2 ** 22, None]).abs().max()) <= 8 * 2.0 ** -24 * 60
+    g.destroy()
+    del X, Y
+    torch.cuda.empty_cache()
