@@ -382,9 +382,9 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
     }
 }
 template <int NT, bool TWO, bool BWD>
-__global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair_rows_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles)
+__global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair_rows_kernel(const PairArgs common, const PairBatch batch, int n_col_tiles, unsigned first)
 {
-    pair_rows_tile<NT, TWO, BWD>(slice_of(common, batch), blockIdx.x, n_col_tiles);
+    pair_rows_tile<NT, TWO, BWD>(slice_of(common, batch), blockIdx.x + first, n_col_tiles);
 }
 
 // Four consecutive floats of an operand row as a strip kernel's lane loads them.  The lane that owns columns [c, c + 4) loads
@@ -958,16 +958,18 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
         else launch_strip64<2, 2, BWD>(a, b, grid, stream);
         break;
     case PairForm::ROWS:
-        switch (2 * f.nt + (f.two ? 1 : 0)) {
-        case 2: pair_rows_kernel<1, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 3: pair_rows_kernel<1, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 4: pair_rows_kernel<2, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 5: pair_rows_kernel<2, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 6: pair_rows_kernel<3, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        case 7: pair_rows_kernel<3, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        default: pair_rows_kernel<4, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col); break;
-        }
-        break;
+        return launch_parts(f.blocks, [&](unsigned first, unsigned count) { // one to three columns in: any number of rows comes here
+            const dim3 grid(count, (unsigned)batch);
+            switch (2 * f.nt + (f.two ? 1 : 0)) {
+            case 2: pair_rows_kernel<1, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col, first); break;
+            case 3: pair_rows_kernel<1, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col, first); break;
+            case 4: pair_rows_kernel<2, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col, first); break;
+            case 5: pair_rows_kernel<2, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col, first); break;
+            case 6: pair_rows_kernel<3, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col, first); break;
+            case 7: pair_rows_kernel<3, true, BWD><<<grid, 256, 0, stream>>>(a, b, n_col, first); break;
+            default: pair_rows_kernel<4, false, BWD><<<grid, 256, 0, stream>>>(a, b, n_col, first); break;
+            }
+        });
     }
     SG_LAUNCH_CHECK();
     return SLICEGCN_OK;
@@ -2036,7 +2038,8 @@ int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, 
     const GradForm g = grad_form(r, batch, products, big, r.rows_per_block == RED_ROWS);
     const PairForm f = pair_form(list, batch);
     bool merge = g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 &&
-                 (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && (f.nt == 1 || (f.nt == 2 && g.wj != 0))));
+                 (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && (f.nt == 1 || (f.nt == 2 && g.wj != 0)))) &&
+                 products * g.blocks + 2 * f.blocks <= MAX_GRID;
     for (int i = 0; merge && i < batch; ++i)
         for (int q = 0; merge && q < batch; ++q)
             for (int o = 0; o < 2; ++o) {

@@ -142,3 +142,25 @@ def test_workspace_decides_the_split_of_the_gradients_only(n, w_in, w_out):
         assert torch.equal(got[0][0], other[0])
         if not split:
             assert torch.equal(got[0][1], other[1]) and torch.equal(got[0][2], other[2])
+
+
+def test_narrow_products_of_more_than_2_31_rows():
+    """One column in: any number of rows goes to the general kernel, whose workgroups are then more than one grid holds."""
+    n = 2 ** 31 + 77
+    x = torch.empty((n, 1), device="cuda").uniform_(0.5, 1.5, generator=torch.Generator(device="cuda").manual_seed(1))
+    W, b, y = torch.tensor([[1.25]], device="cuda"), torch.tensor([0.5], device="cuda"), torch.full((n, 1), float("nan"), device="cuda")
+
+    def worst(want):   # fp32: the product and the sum are rounded, of values below 2.5
+        return max(float((y[i:i + 2 ** 28] - want(x[i:i + 2 ** 28])).abs().max()) for i in range(0, n, 2 ** 28))
+
+    B.slicegcn_linear_fwd(x, W, b, y, None, act=B.ACT_NONE)
+    assert worst(lambda v: v * 1.25 + 0.5) <= 2 * 2.0 ** -24 * 2.5
+    dW, db = torch.empty_like(W), torch.empty_like(b)
+    ws = torch.empty(B.slicegcn_linear_bwd_full_workspace_bytes(n, 1, 1), dtype=torch.uint8, device="cuda")
+    B.slicegcn_linear_bwd(x, W, None, x, y, dW, db, ws, act=B.ACT_NONE)
+    assert worst(lambda v: v * 1.25) <= 2.0 ** -24 * 2.5
+    total, squares = (sum(float(f(x[i:i + 2 ** 28].double()).sum()) for i in range(0, n, 2 ** 28)) for f in (lambda v: v, lambda v: v * v))
+    # chains of 1024 fp32 terms of one sign, added up in fp64
+    assert abs(float(db) / total - 1) <= 1024 * 2.0 ** -24 and abs(float(dW) / squares - 1) <= 1025 * 2.0 ** -24
+    del x, y, ws
+    torch.cuda.empty_cache()
