@@ -215,7 +215,7 @@ struct EdgeSort {
     const void *keys;
     int64_t max_pieces;
     bool wide;
-    alignas(8) unsigned char state[192]; // pointers into the workspace, for edge_sort.hip alone
+    alignas(8) unsigned char state[256]; // pointers into the workspace, for edge_sort.hip alone
 };
 size_t edge_sort_bytes(int64_t n_edges, int64_t n, bool sym, bool loops);
 int edge_sort_rows(const int64_t *row, const int64_t *col, int64_t n_edges, int64_t n, bool sym, bool loops, int32_t *deg, float *dinv, float *sqrtd,

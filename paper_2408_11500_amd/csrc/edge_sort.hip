@@ -4,14 +4,16 @@
 //                       keys for up to 512 buckets, two above; each reads them twice, to count and to move.  Runs of a digit are
 //                       written in one piece per tile; the order within a bucket is whatever the LDS atomics give;
 //   sort                a workgroup sorts a bucket in registers, drops repeats and counts its rows (degrees and their roots included),
-//                       so that no later pass looks for row starts;
+//                       so that no later pass looks for row starts; larger buckets are cut first;
 //   emit                column indices and values, once the row pointers are there (a scan of the degrees).
-// Keys within a bucket are the low bits of the row and the column, 32 bits up to 2^25 nodes, so all but the first pass move 4 bytes per
-// entry.  The result is a function of the set of pairs alone: integer counters decide only where a key waits to be sorted.
+// Keys within a bucket are the low bits of the row and the column, 32 bits up to 2^25 nodes.  Then the first pass writes 6 bytes per key (the
+// second digit apart), the second counts from 2 of them, reads 6 and writes 4, and sorting and emission move 4.  The result is a function
+// of the set of pairs alone: integer counters decide only where a key waits to be sorted.
 //
-// 62 M edges, 2.4 M nodes (126 M keys): 3.7 ms with the schedule, where a device radix sort of 44-bit keys (six passes over 8-byte
-// keys), a sweep for repeats and one for the values took 6.6.  Of it: counting and distributing 0.22 + 0.59 and 0.24 + 0.38 (5.5 GB, 3.9 TB/s),
-// sorting 0.64 + 0.36 (vector unit and LDS crossbar: about 90 comparisons per key), columns and values 1.06 (gather of dinv[col]).
+// 62 M edges, 2.4 M nodes (126 M keys): 3.6 ms with the schedule, where a device radix sort of 44-bit keys (six passes over 8-byte
+// keys), a sweep for repeats and one for the values took 6.6.  Of it: counting and distributing 0.23 + 0.57 and 0.09 + 0.35 (4 TB/s in the
+// first pass), sorting 0.65 + 0.30 and 0.07 for the cuts (vector unit and LDS crossbar: about 90 comparisons per key), columns and values
+// 1.03 (gather of dinv[col]).
 #include "common.h"
 
 namespace slicegcn {
@@ -496,29 +498,88 @@ __device__ inline void put_row(const RowOut &o, int64_t row, int32_t d)
     }
 }
 
-constexpr int SUB_BITS = 11, SUBS = 1 << SUB_BITS;
+// Buckets a hub, a few of them or repeats make so large that one workgroup would be the whole build's last are cut by the next SUB_BITS bits of
+// their keys, which many workgroups count and deal in tiles as in the passes before; parts of more than MOST_KEYS keys are cut again, up to
+// MAX_LEVELS times in all (as many as leave at most SUB_BITS bits), and runs of parts that fit a workgroup's registers are sorted each on
+// its own.  What is left of more than MOST_KEYS keys with at most SUB_BITS bits between them (all keys of up to 2^SUB_BITS nodes, in buckets of one
+// row) holds repeats: its tiles are marked in a bitmap.
+// Builds with one workgroup per part and a bitmap of its values, gone over once per 2^19 of them / cut again (a radix sort of all keys): star
+// of a million leaves 0.72 / 0.43 ms (0.48); one pair 20 M times, 1000 nodes 5.5 / 0.87 (0.89), 3 M nodes 5.6 / 1.5 (2.0); a row of
+// 100 000 among 2 M edges of 40 M nodes 6.3 / 4.1 (3.0); 40 000 pairs 1250 times each, 200 nodes 1.84 / 0.87 (1.69), 3 M nodes 2.4 / 3.1 (4.5).
+constexpr int SUB_BITS = 11, SUBS = 1 << SUB_BITS, MAX_LEVELS = 3;
+struct Cut {
+    int32_t bucket, parent; // parent: the part (its cut * SUBS + its number) that is cut here, -1: the whole bucket
+    int32_t beg, end;       // the keys
+    int32_t tiles;          // tiles not counted yet; whoever counts the last one groups the parts
+    int32_t open;           // groups, parts of repeats and cuts of parts not finished yet
+};
 struct Buckets {
     const int32_t *start; // [n_buckets + 1]
     int32_t *kept;        // distinct keys of every bucket, from its start on
     int32_t *big;         // buckets of more than SORT_KEYS keys, in no particular order
-    int32_t *huge;        // buckets of more than MOST_KEYS keys, likewise; such a bucket is cut by the high bits of its keys into SUBS parts,
-    int2 *tiles;          // in tiles of TILE_KEYS keys: (h, tile) of all tiles, for the h-th such bucket
-    int32_t *sub_count;   // [h * SUBS + u] keys of part u; at the end the distinct keys of the parts before it
-    int32_t *sub_kept;    // [h * SUBS + u] how many keys of the part have been dealt out; then the distinct keys of the group it begins, or 0
-    int32_t *sub_start;   // [h * (SUBS + 1) + u] the part's first key
-    int2 *groups;         // (h * SUBS + first part, parts) of every group of parts, which are sorted together
+    Cut *cuts;            // max_cuts per level
+    int2 *tiles;          // max_tiles per level: (cut, tile) of all tiles of TILE_KEYS keys
+    int32_t *sub_count;   // [cut * SUBS + u] keys of part u; at the end the distinct keys of the parts before it
+    int32_t *sub_kept;    // [cut * SUBS + u] how many keys of the part have been dealt out; then its distinct keys, those of a group at its first part
+    int32_t *sub_start;   // [cut * (SUBS + 1) + u] the part's first key
+    int4 *groups;         // (cut * SUBS + first part, parts, -1, level) of every group of parts, which are sorted together, and
+                          // (cut * SUBS + part, r, tile, level) of every tile of MOST_KEYS keys of the r-th part of repeats; level -1: a
+                          // bucket of repeats that has never been cut
+    int32_t *repeats;     // [r * REPEAT_WORDS] the bitmap of the r-th part of repeats, its last word the number of tiles not marked yet
     int2 *pieces;         // (bucket, piece) of every piece but the first of the buckets with more than EMIT_PIECE distinct keys, and of all
-                          // pieces of groups (-1 - h * SUBS - first part in the bucket's place), in no order
-    int32_t *n_big, *n_huge, *n_tiles, *n_groups, *n_pieces;
+                          // pieces of groups (-1 - cut * SUBS - first part in the bucket's place), in no order
+    int32_t *n_big, *n_groups, *n_pieces, *n_repeats, *n_cuts, *n_tiles; // n_cuts, n_tiles: per level
     int64_t n, n_buckets;
-    int col_bits, row_shift;
-    __host__ __device__ int sub_shift() const { return row_shift + col_bits > SUB_BITS ? row_shift + col_bits - SUB_BITS : 0; }
+    int32_t max_cuts, max_tiles;
+    int col_bits, row_shift, levels;
+    __host__ __device__ int shift(int level) const // of the part number in a key
+    {
+        const int s = row_shift + col_bits - SUB_BITS * (level + 1);
+        return s > 0 ? s : 0;
+    }
     __device__ int rows_of(int64_t b) const
     {
         const int64_t left = n - (b << row_shift);
         return left < ((int64_t)1 << row_shift) ? (int)left : 1 << row_shift;
     }
 };
+inline int cut_levels(int key_bits)
+{
+    const int levels = (key_bits + SUB_BITS - 1) / SUB_BITS - 1;
+    return levels < 1 ? 1 : levels;
+}
+template <class K> __device__ inline int part_of(K key, int shift) { return (int)(key >> shift) & (SUBS - 1); }
+
+// another cut of keys [beg, end), in so many tiles; returns its number.  Uniform per workgroup
+__device__ inline int32_t new_cut(const Buckets &s, int level, int32_t bucket, int32_t parent, int32_t beg, int32_t end, int32_t tiles, int tid)
+{
+    __shared__ int32_t place, first_tile;
+    __syncthreads(); // of the cut before
+    if (tid == 0) {
+        place = level * s.max_cuts + atomicAdd(s.n_cuts + level, 1);
+        first_tile = level * s.max_tiles + atomicAdd(s.n_tiles + level, tiles);
+        s.cuts[place] = Cut{bucket, parent, beg, end, tiles, 0};
+    }
+    __syncthreads();
+    for (int32_t t = tid; t < tiles; t += blockDim.x) s.tiles[first_tile + t] = make_int2(place, t);
+    for (int u = tid; u < SUBS; u += blockDim.x) s.sub_count[place * SUBS + u] = s.sub_kept[place * SUBS + u] = 0;
+    return place;
+}
+constexpr int BITMAP_WORDS = SUBS / 32, REPEAT_WORDS = BITMAP_WORDS + 1;
+// another part of repeats; uniform per workgroup
+__device__ inline void new_repeats(const Buckets &s, int level, int32_t part, int32_t count, int tid)
+{
+    __shared__ int32_t first, number;
+    const int32_t tiles = pieces_of(count, MOST_KEYS);
+    __syncthreads(); // of the part before
+    if (tid == 0) {
+        first = atomicAdd(s.n_groups, tiles);
+        number = atomicAdd(s.n_repeats, 1);
+    }
+    __syncthreads();
+    for (int32_t t = tid; t < tiles; t += blockDim.x) s.groups[first + t] = make_int4(part, number, t, level);
+    for (int w = tid; w < REPEAT_WORDS; w += blockDim.x) s.repeats[number * REPEAT_WORDS + w] = w < BITMAP_WORDS ? 0 : tiles;
+}
 
 constexpr int EMIT_PIECE = 2048; // entries a workgroup writes
 // lists pieces `first` ... of a bucket or part with so many distinct keys
@@ -555,21 +616,19 @@ __global__ __launch_bounds__(256) void sort_buckets_kernel(const Buckets s, cons
 {
     __shared__ K buf[SORT_KEYS];
     __shared__ K last[256];
-    __shared__ int32_t sums[4], place, first_tile;
+    __shared__ int32_t sums[4];
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x, row0 = b << s.row_shift;
     const int32_t beg = s.start[b], cnt = s.start[b + 1] - beg;
     if (cnt > MOST_KEYS) { // uniform per workgroup
-        const int32_t tiles = pieces_of(cnt, TILE_KEYS);
-        if (tid == 0) {
-            place = atomicAdd(s.n_huge, 1);
-            first_tile = atomicAdd(s.n_tiles, tiles);
-            s.huge[place] = (int32_t)b;
-            s.kept[b] = 0;
+        const bool repeats = s.shift(-1) <= SUB_BITS;
+        const int32_t h = new_cut(s, 0, (int32_t)b, -1, beg, beg + cnt, repeats ? 0 : pieces_of(cnt, TILE_KEYS), tid);
+        if (repeats) { // its first part is the whole bucket
+            if (tid < 2) s.sub_start[h * (SUBS + 1) + tid] = beg + tid * cnt;
+            if (tid == 0) s.cuts[h].open = 1;
+            new_repeats(s, -1, h * SUBS, cnt, tid);
         }
-        __syncthreads();
-        for (int32_t t = tid; t < tiles; t += 256) s.tiles[first_tile + t] = make_int2(place, t);
-        for (int u = tid; u < SUBS; u += 256) s.sub_count[place * SUBS + u] = s.sub_kept[place * SUBS + u] = 0;
+        if (tid == 0) s.kept[b] = 0;
         for (int r = tid; r < s.rows_of(b); r += 256) o.deg[row0 + r] = 0; // the groups add to it
         return;
     }
@@ -589,205 +648,275 @@ __global__ __launch_bounds__(256) void sort_buckets_kernel(const Buckets s, cons
     list_pieces(s, b, m, 1, tid);
 }
 
-// The buckets a hub (or a few) makes so large that one workgroup would be the whole build's last: their keys are counted and dealt by their
-// SUB_BITS high bits, in tiles as in the passes before, by many workgroups, and runs of parts that fit a workgroup's registers are
-// then sorted each on its own.  (One workgroup per such bucket: 3.3 ms for a star of a million nodes, 7.7 ms for 126 M entries whose hubs
-// have neighbouring ids.)
-struct HugeTile { int h; int64_t b, beg, end; };
-__device__ inline HugeTile huge_tile(const Buckets &s, int at)
+// How many keys of this lane's part the workgroup has met before: a counter in LDS, one addition for a wavefront whose keys are all of
+// one part, as those of repeats and hubs are (64 additions to one word otherwise).  -1 without a key.
+__device__ inline int32_t count_part(int32_t *cnt, int part, bool in)
 {
-    const int2 t = s.tiles[at];
-    const int64_t b = s.huge[t.x], beg = s.start[b] + (int64_t)t.y * TILE_KEYS, end = s.start[b + 1];
-    return HugeTile{t.x, b, beg, beg + TILE_KEYS < end ? beg + TILE_KEYS : end};
+    const unsigned long long lanes = __ballot(in);
+    if (lanes == 0) return -1;
+    const int leader = __ffsll(lanes) - 1, lane = threadIdx.x & 63, lead = __shfl(part, leader, 64);
+    if (__ballot(in && part != lead) != 0) return in ? atomicAdd(&cnt[part], 1) : -1;
+    int32_t base = 0;
+    if (lane == leader) base = atomicAdd(&cnt[lead], __popcll(lanes));
+    base = __shfl(base, leader, 64);
+    return in ? base + __popcll(lanes & ((1ull << lane) - 1ull)) : -1;
+}
+__device__ inline int32_t load_shared(const int32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); } // written in this launch
+// Counts `done` down for the whole workgroup, behind everything it has written; true where nothing is left, and then all that the others
+// wrote before is there to be read, by load_shared.  Uniform per workgroup.
+// STORES: some of it was written by plain stores, and making those known to the other XCDs takes a write-back of the L2 (100 M keys of
+// 40 000 values, one per tile and group: sorting 2.0 ms instead of 0.6); workgroups take runs of groups and count once per run and cut.
+// Otherwise all of it are additions at device scope, which are performed in one place for all XCDs, and none is outstanding behind the wait
+// (126 M keys of an R-MAT graph, cut buckets counted: 58 us with the write-back, 26 without, grouping included).
+template <bool STORES> __device__ inline bool last_of(int32_t *left, int32_t done, int tid)
+{
+    __shared__ int last;
+    __builtin_amdgcn_s_waitcnt(0); // no access of this wavefront is outstanding
+    __syncthreads();
+    if (tid == 0) {
+        last = __hip_atomic_fetch_sub(left, done, STORES ? __ATOMIC_RELEASE : __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == done;
+        if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+    const bool yes = last;
+    __syncthreads();
+    return yes;
+}
+// the run of `count` items in order that this workgroup takes
+struct Run { int beg, end; };
+__device__ inline Run run_of(int count)
+{
+    const int per = (count + (int)gridDim.x - 1) / (int)gridDim.x, beg = min(per * (int)blockIdx.x, count);
+    return Run{beg, min(beg + per, count)};
+}
+
+// Where the parts of a cut start, and its groups: runs of parts of together at most MOST_KEYS keys.  Parts of more are cut again or, at the last
+// level, listed as repeats.  next: SUBS words
+__device__ inline void group_parts(const Buckets &s, int h, int level, int32_t *next, int tid)
+{
+    constexpr int R = SUBS / PT;
+    __shared__ int32_t end[SUBS], sums[PT / 64], n_sorted, n_large, first;
+    __shared__ int2 list[SUBS]; // groups from the front, larger parts from the back
+    const Cut &cut = s.cuts[h];
+    const int32_t start = cut.beg;
+    int32_t c[R], sum = 0, total;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        c[q] = load_shared(&s.sub_count[h * SUBS + tid * R + q]);
+        sum += c[q];
+    }
+    int32_t from = scan_threads<PT>(sum, sums, tid, total);
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        s.sub_start[h * (SUBS + 1) + tid * R + q] = start + from;
+        from += c[q];
+        end[tid * R + q] = from;
+    }
+    if (tid == 0) s.sub_start[h * (SUBS + 1) + SUBS] = start + total;
+    __syncthreads();
+    for (int u = tid; u < SUBS; u += PT) {
+        const int32_t before = u > 0 ? end[u - 1] : 0;
+        int lo = u + 1, hi = SUBS; // most parts [u, lo) that fit, one at least
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (end[mid - 1] - before <= MOST_KEYS) lo = mid; else hi = mid - 1;
+        }
+        next[u] = lo;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int n = 0, large = 0;
+        for (int u = 0, v; u < SUBS; u = v) {
+            v = next[u];
+            const int32_t count = end[v - 1] - (u > 0 ? end[u - 1] : 0);
+            if (count > MOST_KEYS) list[SUBS - ++large] = make_int2(u, count);
+            else if (count > 0) list[n++] = make_int2(u, v - u);
+        }
+        n_sorted = n;
+        n_large = large;
+        s.cuts[h].open = n + large;
+        first = atomicAdd(s.n_groups, n);
+    }
+    __syncthreads();
+    for (int i = tid; i < n_sorted; i += PT) s.groups[first + i] = make_int4(h * SUBS + list[i].x, list[i].y, -1, level);
+    for (int i = 1; i <= n_large; ++i) {
+        const int u = list[SUBS - i].x, part = h * SUBS + u;
+        const int32_t count = list[SUBS - i].y, beg = start + end[u] - count;
+        if (level + 1 < s.levels) new_cut(s, level + 1, cut.bucket, part, beg, beg + count, pieces_of(count, TILE_KEYS), tid);
+        else new_repeats(s, level, part, count, tid);
+    }
+}
+
+struct CutTile { int h; int64_t beg, end; };
+__device__ inline CutTile cut_tile(const Buckets &s, int level, int at)
+{
+    const int2 t = s.tiles[level * s.max_tiles + at];
+    const int64_t beg = s.cuts[t.x].beg + (int64_t)t.y * TILE_KEYS, end = s.cuts[t.x].end;
+    return CutTile{t.x, beg, beg + TILE_KEYS < end ? beg + TILE_KEYS : end};
 }
 constexpr int TILE_BLOCKS = 1024; // workgroups that take the tiles in turn
-template <class K> __global__ __launch_bounds__(PT) void count_huge_kernel(const Buckets s, const K *__restrict__ keys)
+template <class K> __global__ __launch_bounds__(PT) void count_cuts_kernel(const Buckets s, int level, const K *__restrict__ in)
 {
     __shared__ int32_t cnt[SUBS];
-    const int shift = s.sub_shift(), tid = threadIdx.x, n_tiles = *s.n_tiles;
-    for (int at = blockIdx.x; at < n_tiles; at += gridDim.x) {
-        const HugeTile t = huge_tile(s, at);
-        for (int u = tid; u < SUBS; u += PT) cnt[u] = 0;
-        __syncthreads();
+    const int shift = s.shift(level), tid = threadIdx.x;
+    const Run run = run_of(s.n_tiles[level]);
+    int counted = 0; // tiles of the present cut in cnt
+    for (int at = run.beg; at < run.end; ++at) {
+        const CutTile t = cut_tile(s, level, at);
+        if (counted == 0) {
+            for (int u = tid; u < SUBS; u += PT) cnt[u] = 0;
+            __syncthreads();
+        }
         K k[TILE_KEYS / PT];
 #pragma unroll
-        for (int j = 0; j < TILE_KEYS / PT; ++j) k[j] = keys[t.beg + j * PT + tid < t.end ? t.beg + j * PT + tid : t.beg];
+        for (int j = 0; j < TILE_KEYS / PT; ++j) k[j] = in[t.beg + j * PT + tid < t.end ? t.beg + j * PT + tid : t.beg];
 #pragma unroll
-        for (int j = 0; j < TILE_KEYS / PT; ++j)
-            if (t.beg + j * PT + tid < t.end) atomicAdd(&cnt[k[j] >> shift], 1);
+        for (int j = 0; j < TILE_KEYS / PT; ++j) count_part(cnt, part_of(k[j], shift), t.beg + j * PT + tid < t.end);
+        ++counted;
+        if (at + 1 < run.end && s.tiles[level * s.max_tiles + at + 1].x == t.h) continue; // uniform
         __syncthreads();
         for (int u = tid; u < SUBS; u += PT)
             if (cnt[u] > 0) atomicAdd(&s.sub_count[t.h * SUBS + u], cnt[u]);
+        if (last_of<false>(&s.cuts[t.h].tiles, counted, tid)) group_parts(s, t.h, level, cnt, tid);
         __syncthreads();
+        counted = 0;
     }
 }
-// Where the parts of a huge bucket start, and its groups: runs of parts of together at most MOST_KEYS keys, or one part of more.
-__global__ __launch_bounds__(PT) void group_huge_kernel(const Buckets s)
-{
-    constexpr int R = SUBS / PT;
-    __shared__ int32_t end[SUBS], sums[PT / 64], n_new, first;
-    __shared__ int2 list[SUBS];
-    const int tid = threadIdx.x, n_huge = *s.n_huge;
-    for (int h = blockIdx.x; h < n_huge; h += gridDim.x) {
-        int32_t c[R], sum = 0, total;
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            c[q] = s.sub_count[h * SUBS + tid * R + q];
-            sum += c[q];
-        }
-        const int32_t start = s.start[s.huge[h]];
-        int32_t from = scan_threads<PT>(sum, sums, tid, total);
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            s.sub_start[h * (SUBS + 1) + tid * R + q] = start + from;
-            from += c[q];
-            end[tid * R + q] = from;
-        }
-        if (tid == 0) s.sub_start[h * (SUBS + 1) + SUBS] = start + total;
-        __syncthreads();
-        if (tid == 0) {
-            int n = 0;
-            for (int u = 0; u < SUBS;) {
-                const int32_t before = u > 0 ? end[u - 1] : 0;
-                int lo = u + 1, hi = SUBS; // most parts [u, lo) that fit, one at least
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (end[mid - 1] - before <= MOST_KEYS) lo = mid; else hi = mid - 1;
-                }
-                if (end[lo - 1] > before) list[n++] = make_int2(h * SUBS + u, lo - u);
-                u = lo;
-            }
-            n_new = n;
-            first = atomicAdd(s.n_groups, n);
-        }
-        __syncthreads();
-        for (int i = tid; i < n_new; i += PT) s.groups[first + i] = list[i];
-        __syncthreads();
-    }
-}
-template <class K> __global__ __launch_bounds__(PT) void deal_huge_kernel(const Buckets s, const K *__restrict__ keys, K *__restrict__ dealt)
+template <class K> __global__ __launch_bounds__(PT) void deal_cuts_kernel(const Buckets s, int level, const K *__restrict__ in, K *__restrict__ out)
 {
     __shared__ int32_t cnt[SUBS];
-    const int shift = s.sub_shift(), tid = threadIdx.x, n_tiles = *s.n_tiles;
+    const int shift = s.shift(level), tid = threadIdx.x, n_tiles = s.n_tiles[level];
     for (int at = blockIdx.x; at < n_tiles; at += gridDim.x) {
-        const HugeTile t = huge_tile(s, at);
+        const CutTile t = cut_tile(s, level, at);
         for (int u = tid; u < SUBS; u += PT) cnt[u] = 0;
         __syncthreads();
         K k[TILE_KEYS / PT];
         int32_t rank[TILE_KEYS / PT];
 #pragma unroll
-        for (int j = 0; j < TILE_KEYS / PT; ++j) k[j] = keys[t.beg + j * PT + tid < t.end ? t.beg + j * PT + tid : t.beg];
+        for (int j = 0; j < TILE_KEYS / PT; ++j) k[j] = in[t.beg + j * PT + tid < t.end ? t.beg + j * PT + tid : t.beg];
 #pragma unroll
-        for (int j = 0; j < TILE_KEYS / PT; ++j) rank[j] = t.beg + j * PT + tid < t.end ? atomicAdd(&cnt[k[j] >> shift], 1) : -1;
+        for (int j = 0; j < TILE_KEYS / PT; ++j) rank[j] = count_part(cnt, part_of(k[j], shift), t.beg + j * PT + tid < t.end);
         __syncthreads();
         for (int u = tid; u < SUBS; u += PT)
             if (cnt[u] > 0) cnt[u] = s.sub_start[t.h * (SUBS + 1) + u] + atomicAdd(&s.sub_kept[t.h * SUBS + u], cnt[u]);
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < TILE_KEYS / PT; ++j)
-            if (rank[j] >= 0) dealt[(int64_t)cnt[k[j] >> shift] + rank[j]] = k[j];
+            if (rank[j] >= 0) out[(int64_t)cnt[part_of(k[j], shift)] + rank[j]] = k[j];
         __syncthreads();
     }
 }
 
-// The larger buckets, and the groups of the huge ones.  A part of more keys than fit (repeats, or a row nearly as dense as its columns
-// allow) goes through a bitmap of its keys' low bits, BITMAP of them at a time, which drops repeats by itself.
+// The larger buckets, the groups of the cut ones and their parts of repeats.  Whoever finishes a cut's last group adds up the distinct keys
+// before each of its parts, and so on up to the bucket, whose rows' roots it writes.
 constexpr int BIG_THREADS = 512;
 template <class K>
-__global__ __launch_bounds__(BIG_THREADS) void sort_big_buckets_kernel(const Buckets s, const RowOut o, K *__restrict__ keys, const K *__restrict__ dealt)
+__global__ __launch_bounds__(BIG_THREADS) void sort_big_buckets_kernel(const Buckets s, const RowOut o, K *keys, K *spare)
 {
-    constexpr int WORDS = MOST_KEYS * sizeof(K) / 4, BITMAP = 32 * WORDS, U = 16;
-    __shared__ __attribute__((aligned(16))) uint32_t mem[WORDS]; // the keys being sorted, or the bitmap
+    constexpr int R = SUBS / BIG_THREADS, U = 16;
+    __shared__ __attribute__((aligned(16))) K buf[MOST_KEYS];
     __shared__ K last[BIG_THREADS];
-    __shared__ int32_t sums[BIG_THREADS / 64];
-    K *buf = reinterpret_cast<K *>(mem);
-    const int tid = threadIdx.x, shift = s.sub_shift();
-    const int n_groups = *s.n_groups, n_big = *s.n_big;
-    for (int at = blockIdx.x; at < n_groups + n_big; at += gridDim.x) {
-        __syncthreads(); // buf is used again
-        if (at >= n_groups) { // uniform per workgroup
-            const int64_t b = s.big[at - n_groups], row0 = b << s.row_shift;
-            const int32_t beg = s.start[b], cnt = s.start[b + 1] - beg;
-            K *mine = keys + beg;
-            const int32_t m = sort_distinct<K, MOST_KEYS / BIG_THREADS, BIG_THREADS>(mine, cnt, buf, last, sums, tid);
-            for (int32_t i = tid; i < m; i += BIG_THREADS) mine[i] = buf[i];
-            put_rows<K, BIG_THREADS>(s, o, row0, s.rows_of(b), buf, m, tid);
-            if (tid == 0) s.kept[b] = m;
-            list_pieces(s, b, m, 1, tid);
-            continue;
-        }
-        const int2 g = s.groups[at];
-        const int h = g.x / SUBS, u = g.x % SUBS;
-        const int64_t b = s.huge[h], row0 = b << s.row_shift;
-        const int32_t beg = s.sub_start[h * (SUBS + 1) + u], cnt = s.sub_start[h * (SUBS + 1) + u + g.y] - beg;
-        const K *from = dealt + beg;
-        K *mine = keys + beg;
+    __shared__ int32_t sums[BIG_THREADS / 64], bits[BITMAP_WORDS];
+    const int tid = threadIdx.x;
+    const int n_groups = *s.n_groups;
+    const Run run = run_of(n_groups + *s.n_big);
+    const int groups_end = min(run.end, n_groups);
+    int marked = 0, finished = 0; // tiles of the present part of repeats in bits; groups and parts of the present cut that are done
+    for (int at = run.beg; at < groups_end; ++at) {
+        const int4 g = s.groups[at];
+        const int level = g.w, u = g.x % SUBS, parts = g.z < 0 ? g.y : 1;
+        const int next = at + 1 < groups_end ? s.groups[at + 1].x : -1; // the part of the next item
+        int h = g.x / SUBS;
+        const int64_t b = s.cuts[h].bucket, row0 = b << s.row_shift;
+        const int32_t beg = s.sub_start[h * (SUBS + 1) + u], cnt = s.sub_start[h * (SUBS + 1) + u + parts] - beg;
+        const K *from = (level & 1 ? keys : spare) + beg; // where the level's parts were dealt to
         int32_t m = 0;
-        if (cnt > MOST_KEYS) { // one part
-            const K high = (K)u << shift;
-            for (int64_t x0 = 0; x0 < ((int64_t)1 << shift); x0 += BITMAP) {
+        if (g.z >= 0) { // a tile of repeats
+            const K low = ((K)1 << s.shift(level)) - 1, high = from[0] & ~low;
+            const int32_t left = cnt - g.z * MOST_KEYS, count = left < MOST_KEYS ? left : MOST_KEYS;
+            const K *tile = from + g.z * (int64_t)MOST_KEYS;
+            int32_t *words = s.repeats + g.y * REPEAT_WORDS;
+            if (marked == 0) {
+                if (tid < BITMAP_WORDS) bits[tid] = 0;
                 __syncthreads();
-                for (int i = tid; i < WORDS; i += BIG_THREADS) mem[i] = 0u;
-                __syncthreads();
-                for (int64_t i0 = tid; i0 < cnt; i0 += BIG_THREADS * U) {
-                    K k[U];
-#pragma unroll
-                    for (int q = 0; q < U; ++q) k[q] = from[i0 + q * BIG_THREADS < cnt ? i0 + q * BIG_THREADS : i0]; // repeats do no harm
-#pragma unroll
-                    for (int q = 0; q < U; ++q) {
-                        const int64_t x = (int64_t)(k[q] - high) - x0;
-                        if (x >= 0 && x < BITMAP && !(mem[x >> 5] >> (x & 31) & 1u)) atomicOr(&mem[x >> 5], 1u << (x & 31));
-                    }
-                }
-                __syncthreads();
-                constexpr int W = WORDS / BIG_THREADS; // words per thread
-                int32_t bits = 0, all;
-#pragma unroll
-                for (int q = 0; q < W; ++q) bits += __popc(mem[tid * W + q]);
-                int32_t to = m + scan_threads<BIG_THREADS>(bits, sums, tid, all);
-#pragma unroll 1
-                for (int q = 0; q < W; ++q)
-                    for (uint32_t w = mem[tid * W + q]; w != 0u; w &= w - 1u) mine[to++] = high + (K)(x0 + (tid * W + q) * 32 + __ffs(w) - 1);
-                m += all;
             }
-            __syncthreads(); // the keys are read back below
+            for (int32_t i0 = tid; i0 < count; i0 += BIG_THREADS * U) {
+                K k[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) k[q] = tile[i0 + q * BIG_THREADS < count ? i0 + q * BIG_THREADS : i0]; // once more does no harm
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int x = (int)(k[q] & low);
+                    if (!((uint32_t)bits[x >> 5] >> (x & 31) & 1u)) atomicOr(&bits[x >> 5], (int)(1u << (x & 31)));
+                }
+            }
+            ++marked;
+            if (next == g.x) continue; // uniform: the next tile of this part
+            __syncthreads();
+            if (tid < BITMAP_WORDS && (bits[tid] & ~load_shared(words + tid)) != 0) atomicOr(words + tid, bits[tid]);
+            if (last_of<false>(words + BITMAP_WORDS, marked, tid)) { // uniform; the others have nothing to finish
+                if (tid < BITMAP_WORDS) bits[tid] = load_shared(words + tid);
+                __syncthreads();
+                const int x0 = tid * R, four = bits[x0 >> 5] >> (x0 & 31) & 15;
+                static_assert(R == 4, "four values of a part per thread");
+                int32_t to = scan_threads<BIG_THREADS>(__popc(four), sums, tid, m);
+#pragma unroll
+                for (int q = 0; q < R; ++q)
+                    if (four >> q & 1) buf[to++] = high + (K)(x0 + q);
+                __syncthreads();
+            }
+            marked = 0;
         } else {
             m = sort_distinct<K, MOST_KEYS / BIG_THREADS, BIG_THREADS>(from, cnt, buf, last, sums, tid);
+        }
+        if (m > 0) {
+            K *mine = keys + beg; // from's own keys at odd levels, which are in buf now
             for (int32_t i = tid; i < m; i += BIG_THREADS) mine[i] = buf[i];
+            const int r0 = (int)(buf[0] >> s.col_bits), r1 = (int)(buf[m - 1] >> s.col_bits);
+            for (int r = r0 + tid; r <= r1; r += BIG_THREADS) {
+                const int32_t d = first_at_or_above(buf, m, (uint64_t)(r + 1) << s.col_bits) - first_at_or_above(buf, m, (uint64_t)r << s.col_bits);
+                if (d > 0) atomicAdd(&o.deg[row0 + r], d);
+            }
+            for (int q = tid; q < parts; q += BIG_THREADS) s.sub_kept[g.x + q] = q == 0 ? m : 0;
+            list_pieces(s, -1 - (int64_t)g.x, m, 0, tid);
+            ++finished;
         }
-        const K *sorted = cnt > MOST_KEYS ? mine : buf;
-        const int rows = s.rows_of(b), r0 = (int)(((uint64_t)u << shift) >> s.col_bits), r1 = (int)((((uint64_t)(u + g.y) << shift) - 1) >> s.col_bits);
-        for (int r = r0 + tid; r <= r1 && r < rows; r += BIG_THREADS) { // the rows the group's values can lie in
-            const int32_t d = first_at_or_above(sorted, m, (uint64_t)(r + 1) << s.col_bits) - first_at_or_above(sorted, m, (uint64_t)r << s.col_bits);
-            if (d > 0) atomicAdd(&o.deg[row0 + r], d);
+        __syncthreads(); // buf and bits are used again
+        if (finished == 0 || (next >= 0 && next / SUBS == h)) continue; // uniform
+        while (last_of<true>(&s.cuts[h].open, finished, tid)) {
+            int32_t c[R], sum = 0, total;
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                c[q] = load_shared(&s.sub_kept[h * SUBS + tid * R + q]);
+                sum += c[q];
+            }
+            int32_t before = scan_threads<BIG_THREADS>(sum, sums, tid, total);
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                s.sub_count[h * SUBS + tid * R + q] = before;
+                before += c[q];
+            }
+            const int32_t parent = s.cuts[h].parent;
+            if (parent < 0) {
+                for (int r = tid; r < s.rows_of(b); r += BIG_THREADS) put_row(o, row0 + r, load_shared(&o.deg[row0 + r]));
+                break;
+            }
+            if (tid == 0) s.sub_kept[parent] = total;
+            h = parent / SUBS;
+            finished = 1;
         }
-        for (int q = tid; q < g.y; q += BIG_THREADS) s.sub_kept[g.x + q] = q == 0 ? m : 0;
-        list_pieces(s, -1 - (int64_t)g.x, m, 0, tid);
+        finished = 0;
     }
-}
-
-// where the groups of a huge bucket begin among its distinct keys, and its rows' roots
-__global__ __launch_bounds__(PT) void finish_huge_kernel(const Buckets s, const RowOut o)
-{
-    constexpr int R = SUBS / PT;
-    __shared__ int32_t sums[PT / 64];
-    const int n_huge = *s.n_huge, tid = threadIdx.x;
-    for (int h = blockIdx.x; h < n_huge; h += gridDim.x) {
-        int32_t c[R], sum = 0, total;
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            c[q] = s.sub_kept[h * SUBS + tid * R + q];
-            sum += c[q];
-        }
-        int32_t from = scan_threads<PT>(sum, sums, tid, total);
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            s.sub_count[h * SUBS + tid * R + q] = from;
-            from += c[q];
-        }
-        const int64_t b = s.huge[h], row0 = b << s.row_shift;
-        for (int r = tid; r < s.rows_of(b); r += PT) put_row(o, row0 + r, o.deg[row0 + r]);
-        __syncthreads();
+    for (int at = max(run.beg, n_groups); at < run.end; ++at) {
+        const int64_t b = s.big[at - n_groups], row0 = b << s.row_shift;
+        const int32_t beg = s.start[b], cnt = s.start[b + 1] - beg;
+        K *mine = keys + beg;
+        const int32_t m = sort_distinct<K, MOST_KEYS / BIG_THREADS, BIG_THREADS>(mine, cnt, buf, last, sums, tid);
+        for (int32_t i = tid; i < m; i += BIG_THREADS) mine[i] = buf[i];
+        put_rows<K, BIG_THREADS>(s, o, row0, s.rows_of(b), buf, m, tid);
+        if (tid == 0) s.kept[b] = m;
+        list_pieces(s, b, m, 1, tid);
+        __syncthreads(); // buf is used again
     }
 }
 
@@ -845,24 +974,44 @@ __global__ __launch_bounds__(256) void emit_kernel(const Buckets s, const EmitAr
         if (p.x >= 0) {
             const int64_t row0 = (int64_t)p.x << s.row_shift;
             emit_piece(s, a, keys, row0, s.start[p.x], a.rowptr[row0], s.kept[p.x], p.y * EMIT_PIECE);
-        } else { // a group of parts of a huge bucket
-            const int part = -1 - p.x, h = part / SUBS;
-            const int64_t row0 = (int64_t)s.huge[h] << s.row_shift;
-            emit_piece(s, a, keys, row0, s.sub_start[h * (SUBS + 1) + part % SUBS], a.rowptr[row0] + (int64_t)s.sub_count[part], s.sub_kept[part], p.y * EMIT_PIECE);
+        } else { // a group of parts: behind the distinct keys of the parts before it, in its cut and those around it
+            const int part = -1 - p.x;
+            int h = part / SUBS;
+            const int64_t row0 = (int64_t)s.cuts[h].bucket << s.row_shift;
+            const int32_t first = s.sub_start[h * (SUBS + 1) + part % SUBS];
+            int64_t base = a.rowptr[row0];
+            for (int at_part = part;; h = at_part / SUBS) {
+                base += s.sub_count[at_part];
+                at_part = s.cuts[h].parent;
+                if (at_part < 0) break;
+            }
+            emit_piece(s, a, keys, row0, first, base, s.sub_kept[part], p.y * EMIT_PIECE);
         }
     }
 }
 
-constexpr int N_COUNTS = 5; // n_big ... n_pieces
+constexpr int N_COUNTS = 4 + 2 * MAX_LEVELS; // n_big ... n_tiles
 // Workspace: what lives until the entries are emitted, then what the distribution needs
 struct Layout {
     BucketPlan p;
-    size_t spare_bytes() const { return (size_t)p.max_keys * (p.bits2 ? 8 : p.key_bytes()); }
+    // keys, and behind them first the second digits and then, when those are used up, the tables of the cuts
+    size_t keys_bytes() const { return Arena::rounded((size_t)p.max_keys * p.key_bytes()); }
+    size_t spare_bytes() const
+    {
+        const size_t second = p.bits2 && !p.wide ? (size_t)p.max_keys * 2 : 0;
+        return keys_bytes() + (second > table_bytes() ? second : table_bytes());
+    }
+    size_t table_bytes() const
+    {
+        const size_t cuts = (size_t)(levels() * max_cuts());
+        return 2 * Arena::rounded(cuts * SUBS * 4) + Arena::rounded(cuts * (SUBS + 1) * 4);
+    }
+    int levels() const { return cut_levels(p.row_shift + p.col_bits); }
     int64_t max_big() const { return p.max_keys / SORT_KEYS + 1; }
-    int64_t max_huge() const { return p.max_keys / MOST_KEYS + 1; }
-    int64_t max_tiles() const { return p.max_keys / TILE_KEYS + max_huge(); }
-    // two groups in a row hold more than MOST_KEYS keys, or they would be one
-    int64_t max_groups() const { return 2 * (p.max_keys / MOST_KEYS) + max_huge(); }
+    int64_t max_cuts() const { return p.max_keys / MOST_KEYS + 1; } // of a level
+    int64_t max_tiles() const { return p.max_keys / TILE_KEYS + max_cuts(); }
+    // two groups of a cut in a row hold more than MOST_KEYS keys, or they would be one
+    int64_t max_groups() const { return levels() * (2 * (p.max_keys / MOST_KEYS) + max_cuts()) + p.max_keys / MOST_KEYS + max_cuts(); }
     int64_t max_pieces() const { return p.max_keys / EMIT_PIECE + 1 + max_groups(); }
     size_t bytes(int64_t n) const
     {
@@ -870,9 +1019,8 @@ struct Layout {
         size_t scan = scan_bytes(p.counts1());
         if (p.bits2 && scan_bytes(p.counts2()) > scan) scan = scan_bytes(p.counts2());
         if (scan_bytes(n + 1) > scan) scan = scan_bytes(n + 1);
-        return Arena::rounded((size_t)p.max_keys * p.key_bytes()) + Arena::rounded(spare_bytes()) + r(p.n_buckets + 1) + r(p.n_buckets) + r(max_big()) +
-               r(max_huge()) + r(2 * max_tiles()) + 2 * r(max_huge() * SUBS) + r(max_huge() * (SUBS + 1)) + r(2 * max_groups()) +
-               r(2 * max_pieces()) + r(N_COUNTS) + 2 * r(p.counts1()) +
+        return keys_bytes() + Arena::rounded(spare_bytes()) + r(p.n_buckets + 1) + r(p.n_buckets) + r(max_big()) +
+               Arena::rounded((size_t)(levels() * max_cuts()) * sizeof(Cut)) + r(2 * levels() * max_tiles()) + r(4 * max_groups()) + r(max_cuts() * REPEAT_WORDS) + r(2 * max_pieces()) + r(N_COUNTS) + 2 * r(p.counts1()) +
                2 * r(p.counts2()) + r(MAX_DIGITS + 1) + scan;
     }
 };
@@ -890,18 +1038,25 @@ int sort_rows(const Layout &l, const int64_t *row, const int64_t *col, int64_t n
     if (int rc = ws.take((size_t)(p.n_buckets + 1) * 4, &start)) return rc;
     if (int rc = ws.take((size_t)p.n_buckets * 4, &b.kept)) return rc;
     if (int rc = ws.take((size_t)l.max_big() * 4, &b.big)) return rc;
-    if (int rc = ws.take((size_t)l.max_huge() * 4, &b.huge)) return rc;
-    if (int rc = ws.take((size_t)l.max_tiles() * sizeof(int2), &b.tiles)) return rc;
-    if (int rc = ws.take((size_t)l.max_huge() * SUBS * 4, &b.sub_count)) return rc;
-    if (int rc = ws.take((size_t)l.max_huge() * SUBS * 4, &b.sub_kept)) return rc;
-    if (int rc = ws.take((size_t)l.max_huge() * (SUBS + 1) * 4, &b.sub_start)) return rc;
-    if (int rc = ws.take((size_t)l.max_groups() * sizeof(int2), &b.groups)) return rc;
+    const int64_t cuts = l.levels() * l.max_cuts();
+    if (int rc = ws.take((size_t)cuts * sizeof(Cut), &b.cuts)) return rc;
+    if (int rc = ws.take((size_t)(l.levels() * l.max_tiles()) * sizeof(int2), &b.tiles)) return rc;
+    Arena tables{reinterpret_cast<char *>(spare) + l.keys_bytes(), l.table_bytes(), 0}; // used behind the distribution only
+    if (int rc = tables.take((size_t)cuts * SUBS * 4, &b.sub_count)) return rc;
+    if (int rc = tables.take((size_t)cuts * SUBS * 4, &b.sub_kept)) return rc;
+    if (int rc = tables.take((size_t)cuts * (SUBS + 1) * 4, &b.sub_start)) return rc;
+    if (int rc = ws.take((size_t)l.max_groups() * sizeof(int4), &b.groups)) return rc;
+    if (int rc = ws.take((size_t)l.max_cuts() * REPEAT_WORDS * 4, &b.repeats)) return rc;
     if (int rc = ws.take((size_t)l.max_pieces() * sizeof(int2), &b.pieces)) return rc;
     if (int rc = ws.take(N_COUNTS * 4, &b.n_big)) return rc;
-    b.n_huge = b.n_big + 1;
-    b.n_tiles = b.n_big + 2;
-    b.n_groups = b.n_big + 3;
-    b.n_pieces = b.n_big + 4;
+    b.n_groups = b.n_big + 1;
+    b.n_pieces = b.n_big + 2;
+    b.n_repeats = b.n_big + 3;
+    b.n_cuts = b.n_big + 4;
+    b.n_tiles = b.n_cuts + MAX_LEVELS;
+    b.max_cuts = (int32_t)l.max_cuts();
+    b.max_tiles = (int32_t)l.max_tiles();
+    b.levels = l.levels();
     b.start = start;
     b.n = n;
     b.n_buckets = p.n_buckets;
@@ -921,10 +1076,11 @@ int sort_rows(const Layout &l, const int64_t *row, const int64_t *col, int64_t n
         SecondPass s{nullptr, nullptr, at1, nullptr, p.tiles1, digits1, p.bits2, p.col_bits, p.row_shift};
         int32_t *at2 = nullptr;
         if (p.bits2 == 0) {
-            distribute_edges_kernel<K, true><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, keys, 0, nullptr);
+            if constexpr (sizeof(K) == 4) // 64-bit keys have more buckets
+                distribute_edges_kernel<K, true><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, keys, 0, nullptr);
             SG_LAUNCH_CHECK();
         } else {
-            uint16_t *second = sizeof(K) == 4 ? reinterpret_cast<uint16_t *>(spare + p.max_keys) : nullptr; // spare has 8 bytes a key
+            uint16_t *second = sizeof(K) == 4 ? reinterpret_cast<uint16_t *>(tables.base) : nullptr;
             int32_t *counts2 = nullptr, *tile_start = nullptr;
             if (int rc = ws.take((size_t)p.counts2() * 4, &counts2)) return rc;
             if (int rc = ws.take((size_t)p.counts2() * 4, &at2)) return rc;
@@ -950,21 +1106,17 @@ int sort_rows(const Layout &l, const int64_t *row, const int64_t *col, int64_t n
     ws.used = mark; // later users are ordered behind these kernels on the stream
     sort_buckets_kernel<K><<<(unsigned)p.n_buckets, 256, 0, stream>>>(b, rows, keys);
     SG_LAUNCH_CHECK();
-    const unsigned huge_blocks = (unsigned)(l.max_huge() < 512 ? l.max_huge() : 512), tile_blocks = (unsigned)(l.max_tiles() < TILE_BLOCKS ? l.max_tiles() : TILE_BLOCKS);
-    if (p.max_keys > MOST_KEYS) {
-        count_huge_kernel<K><<<tile_blocks, PT, 0, stream>>>(b, keys);
-        SG_LAUNCH_CHECK();
-        group_huge_kernel<<<huge_blocks, PT, 0, stream>>>(b);
-        SG_LAUNCH_CHECK();
-        deal_huge_kernel<K><<<tile_blocks, PT, 0, stream>>>(b, keys, spare);
-        SG_LAUNCH_CHECK();
+    if (p.max_keys > MOST_KEYS && p.row_shift + p.col_bits > SUB_BITS) {
+        const unsigned tile_blocks = (unsigned)(l.max_tiles() < TILE_BLOCKS ? l.max_tiles() : TILE_BLOCKS);
+        for (int level = 0; level < l.levels(); ++level) { // a level's parts lie in the other array
+            count_cuts_kernel<K><<<tile_blocks, PT, 0, stream>>>(b, level, level & 1 ? spare : keys);
+            SG_LAUNCH_CHECK();
+            deal_cuts_kernel<K><<<tile_blocks, PT, 0, stream>>>(b, level, level & 1 ? spare : keys, level & 1 ? keys : spare);
+            SG_LAUNCH_CHECK();
+        }
     }
     if (p.max_keys > SORT_KEYS) { // two workgroups per CU
         sort_big_buckets_kernel<K><<<512, BIG_THREADS, 0, stream>>>(b, rows, keys, spare);
-        SG_LAUNCH_CHECK();
-    }
-    if (p.max_keys > MOST_KEYS) {
-        finish_huge_kernel<<<huge_blocks, PT, 0, stream>>>(b, rows);
         SG_LAUNCH_CHECK();
     }
     if (int rc = scan_i32(rows.deg, rowptr, n + 1, ws, stream)) return rc; // deg[n] is read, what it holds is not used

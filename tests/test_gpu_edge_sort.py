@@ -103,6 +103,24 @@ def test_all_pairs_alike():
     check(src, dst, n, ALL)
 
 
+@pytest.mark.parametrize("n,low", [(300, 256), (2048, 2048), (2049, 2048), (9000, 2048), (10_000, 2), (200_000, 64), (3_000_000, 1024), (2 ** 24, 1024), (40_000_003, 16)])
+def test_parts_cut_again(n, low):
+    """Hubs whose parts are cut once, twice and three times before a workgroup sorts them, and parts that hold repeats when no bits are left to
+    cut by (`low` values: one of them, or nearly all of them)."""
+    rng = np.random.default_rng(n)
+    k = min(n - 1, 120_000)
+    rows = [(np.full(k, 3), n - 1 - np.arange(k)),                                     # neighbours side by side
+            (np.full(k, 4), rng.choice(n, k, replace=False)),                          # and all over
+            (np.full(70_000, 6), min(2048, n - low) + rng.integers(0, max(low - 1, 1), 70_000)),     # one part of repeats
+            (np.full(40_000, n - 2), np.full(40_000, n - 1)),                          # one pair
+            (rng.integers(0, n, 3000), rng.integers(0, n, 3000))]
+    src, dst = (np.concatenate([r[i] for r in rows]) for i in (0, 1))
+    p = rng.permutation(src.size)
+    check(src[p], dst[p], n, 0)
+    check(src[p], dst[p], n, ALL)
+    check(src, dst, n, ALL)      # wavefronts whose keys are all of one part
+
+
 def test_most_candidates_in_one_bucket():
     """2^31 - 1 candidate entries, the most that is accepted, nearly all of them in one bucket: its tiles are counted in 32 bits."""
     n, m = 1000, 2 ** 31 - 1
