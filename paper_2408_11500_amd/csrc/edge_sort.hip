@@ -35,12 +35,13 @@ inline unsigned bits_for(uint64_t v)
 // How the entries are cut into buckets.  Bucket b holds the entries of the rows [b << row_shift, (b + 1) << row_shift); an entry is a
 // key (row within the bucket) << col_bits | col.
 //   * enough buckets that one holds about BUCKET_KEYS entries and is sorted by one workgroup in registers (126 M keys, sorting and
-//     distributing: 1024 per bucket 2.44 ms, 2048 2.33, 4096 2.36);
+//     distributing: 1024 per bucket 2.44 ms, 2048 2.33, 4096 2.36), half as many with 64-bit keys, whose comparisons cost more (44 M keys
+//     of 40 M nodes, build: 2.97 ms with 2048, 2.87 with 1024);
 //   * no more than 2^MAX_ROW_SHIFT rows in a bucket as far as the bits go (a workgroup counts the rows of its bucket);
 //   * 32-bit keys where that takes no more than MAX_BITS bits of bucket number (up to 2^25 nodes), 64-bit keys above;
 //   * up to 2^DIGIT_BITS buckets one pass over the edges distributes them, above it two passes by half of the bits each.
 constexpr int DIGIT_BITS = 9, MAX_DIGITS = 1 << DIGIT_BITS, MAX_BITS = 2 * DIGIT_BITS;
-constexpr int64_t BUCKET_KEYS = 2048;
+constexpr int64_t BUCKET_KEYS = 2048, BUCKET_KEYS_64 = 1024;
 constexpr int MAX_ROW_SHIFT = 11;
 constexpr int PT = 512;           // threads of a distributing workgroup
 // edges (two keys each) or diagonal entries a workgroup takes from the edge list: longer runs per digit or more workgroups on a CU (126 M keys,
@@ -67,9 +68,9 @@ BucketPlan bucket_plan(int64_t n_edges, int64_t n, bool sym, bool loops)
     p.max_keys = n_edges * (sym ? 2 : 1) + (loops ? n : 0);
     p.col_bits = (int)bits_for((uint64_t)(n - 1));
     int bits = 0; // of the bucket number
-    while (bits < MAX_BITS && bits < p.col_bits && (p.max_keys >> bits) > BUCKET_KEYS) ++bits;
-    if (bits < p.col_bits - MAX_ROW_SHIFT) bits = p.col_bits - MAX_ROW_SHIFT < MAX_BITS ? p.col_bits - MAX_ROW_SHIFT : MAX_BITS;
     p.wide = 2 * p.col_bits - MAX_BITS > 32;
+    while (bits < MAX_BITS && bits < p.col_bits && (p.max_keys >> bits) > (p.wide ? BUCKET_KEYS_64 : BUCKET_KEYS)) ++bits;
+    if (bits < p.col_bits - MAX_ROW_SHIFT) bits = p.col_bits - MAX_ROW_SHIFT < MAX_BITS ? p.col_bits - MAX_ROW_SHIFT : MAX_BITS;
     if (!p.wide && bits < 2 * p.col_bits - 32) bits = 2 * p.col_bits - 32;
     p.row_shift = p.col_bits - bits;
     p.n_buckets = ((n - 1) >> p.row_shift) + 1;
@@ -359,6 +360,9 @@ template <class K> __device__ inline K pick_side(K a, K b, K bound)
     return lo > top ? lo : top;
 }
 
+// 64-bit keys: one comparison and one choice (as above it would be three of each: 44 M keys of 40 M nodes sorted 2.4 ms instead of 1.6)
+__device__ inline uint64_t pick_side(uint64_t a, uint64_t b, uint64_t bound) { return (b < a) != (bound != 0) ? b : a; }
+
 // steps of distance D * KPT, D / 2 * KPT, ..., KPT (one element per lane each)
 template <class K, int KPT, int D> __device__ inline void lane_steps(K (&k)[KPT], int tid)
 {
@@ -505,7 +509,7 @@ __device__ inline void put_row(const RowOut &o, int64_t row, int32_t d)
 // row) holds repeats: its tiles are marked in a bitmap.
 // Builds with one workgroup per part and a bitmap of its values, gone over once per 2^19 of them / cut again (a radix sort of all keys): star
 // of a million leaves 0.72 / 0.43 ms (0.48); one pair 20 M times, 1000 nodes 5.5 / 0.87 (0.89), 3 M nodes 5.6 / 1.5 (2.0); a row of
-// 100 000 among 2 M edges of 40 M nodes 6.3 / 4.1 (3.0); 40 000 pairs 1250 times each, 200 nodes 1.84 / 0.87 (1.69), 3 M nodes 2.4 / 3.1 (4.5).
+// 100 000 among 2 M edges of 40 M nodes 6.3 / 3.0 (3.0); 40 000 pairs 1250 times each, 200 nodes 1.84 / 0.87 (1.69), 3 M nodes 2.4 / 3.1 (4.5).
 constexpr int SUB_BITS = 11, SUBS = 1 << SUB_BITS, MAX_LEVELS = 3;
 struct Cut {
     int32_t bucket, parent; // parent: the part (its cut * SUBS + its number) that is cut here, -1: the whole bucket
@@ -606,8 +610,12 @@ template <class K> __device__ inline int32_t first_at_or_above(const K *sorted, 
 template <class K, int THREADS>
 __device__ inline void put_rows(const Buckets &s, const RowOut &o, int64_t row0, int rows, const K *sorted, int32_t count, int tid)
 {
-    for (int r = tid; r < rows; r += THREADS)
-        put_row(o, row0 + r, first_at_or_above(sorted, count, (uint64_t)(r + 1) << s.col_bits) - first_at_or_above(sorted, count, (uint64_t)r << s.col_bits));
+    const int lane = tid & 63; // two searches per row: 44 M keys of 40 M nodes sorted 1.47 ms instead of 1.33
+    for (int r0 = (tid >> 6) * 63; r0 < rows; r0 += THREADS / 64 * 63) { // the next lane's row starts where this one's ends
+        const int r = r0 + lane;
+        const int32_t beg = first_at_or_above(sorted, count, (uint64_t)r << s.col_bits), end = __shfl_down(beg, 1, 64);
+        if (lane < 63 && r < rows) put_row(o, row0 + r, end - beg);
+    }
 }
 
 // One workgroup per bucket: sorts its keys in registers, drops repeats, writes them back and counts its rows.  Larger buckets are listed.
