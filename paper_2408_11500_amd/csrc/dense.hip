@@ -157,7 +157,9 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
     floatx4 (*Bs)[KC / 4][GS] = reinterpret_cast<floatx4 (*)[KC / 4][GS]>(pool);
     __shared__ __attribute__((aligned(16))) float bias_s[2][BN];
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    // In a scalar register it leaves four vector registers more, without which three tiles of an input gradient spill two (169 k rows 288 -> 40
+    // 69.8 -> 66.8 us, 800 k rows 326 -> 312); with one tile it was slower (20 k rows 32 -> 256 11.1 -> 11.9).
+    const int wave = NT == 3 && BWD && !TWO ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
     // tile_place in 32 bits: the 64-bit division is as long as a small layer's loads
     const uint32_t group = wg / (8u * n_col_tiles);
