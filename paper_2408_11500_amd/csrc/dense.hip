@@ -904,16 +904,30 @@ inline PairForm pair_form(const PairArgs *list, int batch)
     const PairArgs &a = list[0];
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
     const int64_t strips = (a.n + 31) / 32, strip_blocks = (strips + 3) / 4;
-    // narrowest layers: per-wavefront strips, no barriers; but not on few rows whose K is a whole chunk of pair_rows_kernel, which issues far
-    // fewer instructions per row there and keeps more wavefronts on a SIMD (32 -> 32 with self term, strips / rows: 40 k rows 8.3 / 7.8 us, 80 k
-    // 13.4 / 11.2, 150 k 23.5 / 18.8, 200 k 29.7 / 21.9; input gradients of 100 k rows 12.3 / 8.1; K = 16, 20 k rows 6.2 / 7.8)
-    if (a.K >= 4 && a.K <= 32 && a.Nout <= 32 && (a.K < 32 || a.n * batch >= STRIP64_ROWS))
-        return PairForm{PairForm::STRIP32, two, strip_blocks < 2048 ? strip_blocks : 2048, 0, 0};
+    // narrowest layers: per-wavefront strips, no barriers; but below STRIP64_ROWS not those whose K is a whole chunk of pair_rows_kernel or no
+    // more than its first eight steps, which issues far fewer instructions per row there and keeps more wavefronts on a SIMD.  Strips / rows, 32
+    // columns out:
+    //     K    with self term, 20 k rows   66 k          169 k         262 k         input gradients, 20 k   169 k
+    //     8    6.3 / 6.3 us                11.3 / 8.6    20.7 / 17.0   26.0 / 20.2   5.5 / 3.9               13.2 / 10.9
+    //     12   6.3 / 6.3                   11.1 / 8.9    20.8 / 18.2   26.0 / 22.0   4.7 / 4.1               12.3 / 11.3
+    //     16   6.3 / 7.3                   11.1 / 11.1   21.4 / 22.9   26.1 / 27.4   5.5 / 4.5               14.1 / 13.9
+    //     24   6.3 / 7.9                   11.1 / 13.7   21.0 / 28.3   26.2 / 34.3   5.5 / 5.0               13.9 / 16.2
+    //     28   6.3 / 7.3                   11.1 / 12.5   20.9 / 25.9   25.7 / 33.0   4.7 / 4.5               13.1 / 15.4
+    //     32   6.1 / 5.9                   10.9 / 9.5    20.8 / 19.5   25.9 / 25.8   5.4 / 4.1               13.5 / 12.2
+    // (from there on strips: 2.4 M rows with self term, K = 8 165 / 181, K = 16 166 / 224, K = 32 189 / 198).
+    const int64_t resident = 512 / batch; // as many workgroups as the chip holds at once: two per CU
+    if (a.K >= 4 && a.K <= 32 && a.Nout <= 32 && ((a.K > 8 && a.K < 32) || a.n * batch >= STRIP64_ROWS)) {
+        // Each stages the weights once, and a second strip is requested while the first is multiplied (K = 16 with self term, 2048 / 512
+        // workgroups: 130 k rows 20.4 / 17.0 us, 169 k 26.0 / 21.3, 262 k 32.8 / 26.1, 800 k 73 / 66; input gradients 130 k 14.0 / 11.8, 262 k
+        // 23.5 / 16.8).  More where the launch is long: 2.4 M rows of 8 columns out 217 / 240, input gradients of 12 columns 91 / 96, and
+        // beside weight gradients 800 k rows 16 -> 28 73.7 / 76.1.
+        const int64_t most = strip_blocks * batch <= (two ? 8192 : 2048) ? resident : 2048;
+        return PairForm{PairForm::STRIP32, two, strip_blocks < most ? strip_blocks : most, 0, 0};
+    }
     if (a.K >= 4 && a.K <= 64 && a.Nout <= 64 && a.n * batch >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
-        // as many workgroups as the chip holds at once (two per CU): each stages the weights once (four slices of 169 k rows with 2048
-        // workgroups: forward 164 us instead of 149, backward 151 instead of 130)
-        const int64_t most = 512 / batch;
-        return PairForm{PairForm::STRIP64, two, strip_blocks < most ? strip_blocks : most, 0, 0};
+        // (each workgroup stages the weights once: four slices of 169 k rows with 2048 workgroups forward 164 us instead of 149, backward
+        // 151 instead of 130)
+        return PairForm{PairForm::STRIP64, two, strip_blocks < resident ? strip_blocks : resident, 0, 0};
     }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
@@ -2021,7 +2035,8 @@ __global__ __launch_bounds__(256, 3) void grad_pair_kernel(const ReduceArgs r, c
     else pair_rows_tile<NT, false, true>(a, at, n_col);
 }
 
-// Whether the n x w rows at o, in leading dimension ldo, may share memory with those at x (by the address ranges from first to last element)
+// Whether the n x w rows at o, in leading dimension ldo, may share memory with those at x, by the address ranges from first to last element:
+// column ranges of one wide matrix count as shared, though nothing overlaps, and are worked on in two launches
 inline bool may_share(const void *o, int64_t ldo, int64_t wo, const void *x, int64_t ldx, int64_t wx, int64_t n)
 {
     const uintptr_t p = reinterpret_cast<uintptr_t>(o), q = reinterpret_cast<uintptr_t>(x);
@@ -2029,7 +2044,8 @@ inline bool may_share(const void *o, int64_t ldo, int64_t wo, const void *x, int
 }
 
 // launch_grad_rows, and launch_pair<true> for `list` in the same launch where the gradients take their smallest tiles, which leave the chip
-// idle (with larger ones 2.4 M rows 256 -> 47 take 2.86 ms together and 2.64 apart), and nothing that is stored is read by the other (an
+// idle (with larger ones 2.4 M rows 256 -> 47 take 2.86 ms together and 2.64 apart; up to 32 -> 3, where they are the only tiles, one launch is
+// faster on any number of rows: 32 -> 2, 169 k rows 31.2 / 24.1 us, 800 k 70 / 55, 2.4 M 196 / 184), and nothing that is stored is read by the other (an
 // input gradient may take the place of an operand); `pair_done` says whether it was.  A layer whose gradients are cut into chains shorter
 // than RED_ROWS leaves the LDS form for it (5000 rows 96 -> 96 19.5 / 14.9 us, 2048 rows 256 -> 256 34.7 / 30.3).
 int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, int products, bool big, const PairArgs *list, bool *pair_done,

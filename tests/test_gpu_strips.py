@@ -7,14 +7,16 @@ from paper_2408_11500_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 
-ROWS32, ROWS64 = 65_536 + 21, (1 << 21) + 13   # from 2^16 rows on the 32-wide kernels, from 2^21 on all of the 64-wide ones
+# From 2^16 rows on the weight gradients, and the products with 9 to 31 columns in, of the 32-wide kernels; from 2^18 on the products with 4 to 8
+# and with 32 columns in as well; from 2^21 on all of the 64-wide ones.
+ROWS32, ROWS32_ALL, ROWS64 = 65_536 + 21, (1 << 18) + 21, (1 << 21) + 13
 
 
 @pytest.fixture(scope="module")
 def graphs():
     """No edges but the diagonal: the aggregation copies, so that the products stand alone."""
     none = torch.empty(0, dtype=torch.int64, device="cuda")
-    made = {n: B.slicegcn_build_norm_csr(none, none, n) for n in (ROWS32, ROWS64)}
+    made = {n: B.slicegcn_build_norm_csr(none, none, n) for n in (ROWS32, ROWS32_ALL, ROWS64)}
     yield made
     for g in made.values():
         g.destroy()
@@ -35,6 +37,8 @@ def assert_fp32(got, want, scale, what):
 
 CASES = [(ROWS32, i, o, self_term, pad) for i, o in ((32, 32), (25, 32), (32, 25), (4, 4), (5, 31), (3, 32), (32, 2), (1, 1), (30, 7))
          for self_term, pad in ((True, 0), (True, 3), (False, 1))]
+CASES += [(ROWS32_ALL, i, o, self_term, pad) for i, o in ((32, 32), (25, 32), (32, 25), (32, 2), (4, 4), (5, 31), (31, 7))
+          for self_term, pad in ((True, 0), (True, 3), (False, 1))]
 CASES += [(ROWS64, i, o, self_term, pad) for i, o, self_term, pad in ((64, 64, True, 3), (25, 64, True, 3), (40, 30, True, 0), (40, 30, False, 1),
                                                                      (2, 50, True, 3), (2, 50, False, 0), (61, 3, True, 3), (64, 64, False, 0))]
 
@@ -86,11 +90,12 @@ def test_layer_matches_fp64(graphs, n, w_in, w_out, self_term, pad):
             assert_fp32(dbs, Gd.sum(0), Gd.abs().sum(0), "db_self")
 
 
+@pytest.mark.parametrize("w_in", [32, 8, 7, 4])
 @pytest.mark.parametrize("w_out", [32, 20])
 @pytest.mark.parametrize("self_term", [True, False])
-def test_rows_and_strips_have_the_same_bits(w_out, self_term):
-    """32 columns in: strips from 2^18 rows on, the general kernel below; the last call has one row less."""
-    n, w_in = 1 << 18, 32
+def test_rows_and_strips_have_the_same_bits(w_in, w_out, self_term):
+    """4 to 8 and 32 columns in: strips from 2^18 rows on, the general kernel below; the last call has one row less."""
+    n = 1 << 18
     gen = torch.Generator(device="cuda").manual_seed(w_out)
     X, G, W, Ws = (torch.randn(s, generator=gen, device="cuda") for s in ((n, w_in), (n, w_out), (w_in, w_out), (w_in, w_out)))
     b, bs = (torch.randn(w_out, generator=gen, device="cuda") for _ in range(2))
@@ -99,11 +104,11 @@ def test_rows_and_strips_have_the_same_bits(w_out, self_term):
     none, got = torch.empty(0, dtype=torch.int64, device="cuda"), []
     for rows in (n, n - 1):
         g = B.slicegcn_build_norm_csr(none, none, rows)
-        Z, H, words = torch.empty((rows, w_in), device="cuda"), torch.empty((rows, w_out), device="cuda"), torch.zeros((rows, 1), dtype=torch.int32, device="cuda")
+        Z, H, words = torch.empty((rows, (w_in + 3) // 4 * 4), device="cuda")[:, :w_in], torch.empty((rows, w_out), device="cuda"), torch.zeros((rows, 1), dtype=torch.int32, device="cuda")
         B.slicegcn_layer_fwd(g, X[:rows], W, b, Ws, bs, H, Z, words)
         Y, bits = torch.empty((rows, w_out), device="cuda"), torch.zeros((rows, 1), dtype=torch.int32, device="cuda")
         B.slicegcn_linear_fwd(X[:rows], W, b, Y, bits, act=B.ACT_RELU)
-        dX = torch.empty((rows, w_out), device="cuda")   # backward: the product with 32 columns in is that of a layer w_out -> 32
+        dX = torch.empty((rows, w_out), device="cuda")   # backward: the product with w_in columns in is that of a layer w_out -> w_in
         B.slicegcn_linear_bwd(G[:rows], W.t().contiguous(), None, X[:rows], dX, None, None, None, act=B.ACT_NONE)
         got.append([t[:n - 1] for t in (H, words, Y, bits, dX)])
         g.destroy()
