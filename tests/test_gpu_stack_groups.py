@@ -116,10 +116,7 @@ def test_encoding_fused_or_not_after_a_pass(graph):
         assert float((a - b).abs().max()) <= 3e-6 * float(a.abs().max()) * (1 if a.shape[0] == N else 16)
 
 
-@pytest.mark.parametrize("first,hs", [(37, 64), (64, 40), (30, 30)])
-def test_group_takes_the_strip_kernels_and_one_slice_does_not(monkeypatch, first, hs):
-    """Together the slices of a launch have rows enough for the strip kernels, one alone has not: the same bits."""
-    n, k = 66_003, 4
+def in_a_group_and_alone(monkeypatch, n, k, first, hs, self_term=True):
     rng = np.random.default_rng(first)
     g = sg.slicegcn_build_norm_csr(dev(rng.integers(0, n, 3 * n), torch.int64), dev(rng.integers(0, n, 3 * n), torch.int64), n)
     runs = []
@@ -133,13 +130,26 @@ def test_group_takes_the_strip_kernels_and_one_slice_does_not(monkeypatch, first
         st.E.copy_(r(k, hs))
         for i in range(k):
             for l, (wi, wo) in enumerate(st.widths):
-                st.set_params(i, l, r(wi, wo) * 0.1, r(wo), r(wi, wo) * 0.1, r(wo))
+                st.set_params(i, l, r(wi, wo) * 0.1, r(wo), *((r(wi, wo) * 0.1, r(wo)) if self_term else (None, None)))
         assert st.group == (k if limit else 1)
         dH = r(n, k * hs)
         st.forward()
         st.backward(dH)
         runs.append([st.Hcat.clone(), st.dE.clone(), st.dXin[:, :first].clone()] +
-                    [gr[key].clone() for per_slice in st.grads for gr in per_slice for key in ("dW_agg", "db", "dW_self", "db_self")])
+                    [gr[key].clone() for per_slice in st.grads for gr in per_slice for key in ("dW_agg", "db", "dW_self", "db_self") if gr[key] is not None])
     g.destroy()
     for a, b in zip(*runs):
         assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("first,hs", [(37, 64), (64, 40), (30, 30)])
+def test_group_takes_the_strip_kernels_and_one_slice_does_not(monkeypatch, first, hs):
+    """Together the slices of a launch have rows enough for the strip kernels, one alone has not: the same bits."""
+    in_a_group_and_alone(monkeypatch, 66_003, 4, first, hs)
+
+
+@pytest.mark.parametrize("n,first,hs,self_term", [(20_011, 64, 64, True), (20_011, 37, 40, True), (20_011, 5, 64, True), (20_011, 30, 31, True),
+                                                  (66_003, 64, 64, False), (66_003, 37, 40, False), (66_003, 5, 64, False)])
+def test_weight_gradients_of_a_group_in_strips_and_of_one_slice_in_tiles(monkeypatch, n, first, hs, self_term):
+    """Blocks of 256 rows: pairs of products go to the strips from 160 of them on (79 a slice), single products from 512 on (258 a slice)."""
+    in_a_group_and_alone(monkeypatch, n, 4, first, hs, self_term)
