@@ -103,13 +103,27 @@ __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restri
     }
 }
 
-// Counters for the host: rows of every kind; the column class boundaries stay on the device.
-__global__ void sched_summary_kernel(const int32_t *__restrict__ counts, int64_t n_groups, const int32_t *__restrict__ colptr,
-                                     int64_t n, int32_t *__restrict__ summary, ClassBounds *__restrict__ cb)
+// Counters for the host: rows of every kind, and how many more of SAMPLES rows have all of their columns within a LOCAL_SPAN-th of the
+// nodes than have not (one row per thread beside the wavefront that searches the boundaries, which takes longer); the column class boundaries
+// stay on the device.
+constexpr int SAMPLES = 960, LOCAL_SPAN = 16;
+__global__ __launch_bounds__(SAMPLES + 64) void sched_summary_kernel(const int32_t *__restrict__ counts, int64_t n_groups, const int32_t *__restrict__ colptr, int64_t n,
+                                                           const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+                                                           int32_t *__restrict__ summary, ClassBounds *__restrict__ cb)
 {
     const int t = threadIdx.x;
+    bool near = false, far = false;
     if (t < 3) summary[t] = counts[(t + 1) * n_groups] - counts[t * n_groups];
-    if (t <= N_CLASSES) cb->first[t] = class_bound(colptr, n, t);
+    if (t <= N_CLASSES) {
+        cb->first[t] = class_bound(colptr, n, t);
+    } else if (t >= 64) {
+        const int64_t row = n * (t - 64) / SAMPLES;
+        const int32_t beg = rowptr[row], end = rowptr[row + 1];
+        near = end - beg >= 2 && (int64_t)(colidx[end - 1] - colidx[beg]) * LOCAL_SPAN <= n;
+        far = end - beg >= 2 && !near;
+    }
+    const int more = __syncthreads_count(near) - __syncthreads_count(far);
+    if (t == 3) summary[t] = more;
 }
 
 // ---- long rows: cut by column class ------------------------------------------------------
@@ -291,10 +305,11 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
     sched_rows_kernel<false><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, counts, n_groups, nullptr, nullptr);
     SG_LAUNCH_CHECK();
     if (int rc = scan_i32(counts, offs, 3 * n_groups + 1, ws, stream)) return rc; // the last element is only written
-    sched_summary_kernel<<<1, 64, 0, stream>>>(offs, n_groups, colptr, n, counters, cb);
+    sched_summary_kernel<<<1, SAMPLES + 64, 0, stream>>>(offs, n_groups, colptr, n, m.rowptr, m.colidx, counters, cb);
     SG_LAUNCH_CHECK();
-    int32_t kinds[3];
-    if (int rc = read_counters(counters, kinds, 3, stream)) return rc;
+    int32_t kinds[4];
+    if (int rc = read_counters(counters, kinds, 4, stream)) return rc;
+    out.local = kinds[3] > 0;
     const int64_t n_group = kinds[ROW_GROUP], n_wave = kinds[ROW_WAVE], n_long = kinds[ROW_LONG];
 
     int32_t *long_rows = nullptr, *class_beg = nullptr, *cnt = nullptr, *off = nullptr;

@@ -102,6 +102,7 @@ struct Schedule {
     int32_t small_off[N_CLASSES] = {0}, small_cnt[N_CLASSES] = {0}; // lane-group pieces of class c
     int32_t wbig_off = 0, wbig_cnt = 0;     // wavefront items of rows kept whole
     int32_t wsmall_off = 0, wsmall_cnt = 0; // lane-group items that are whole rows
+    bool local = false; // most rows' columns lie close together, so that gathers mostly meet in the L2s
     int64_t n_items = 0;
     int64_t n_fix = 0;
     int64_t n_slots = 0;

@@ -55,6 +55,7 @@ struct SpmmArgs {
     int32_t n;
     int32_t item_max;     // longest lane-group item of the schedule (ITEM_SHORT or ITEM_LONG)
     int32_t ipw;          // wavefront items per wavefront (1 to 4 in the one-launch kernel, otherwise 1); a workgroup takes 4 * ipw
+    int32_t rounds;       // lane-group items per lane group (1 to MAX_RUN in the one-launch kernel, otherwise 1)
     int32_t deal;         // log2 of the chunks of lane-group whole rows a class takes in turn
     int32_t tiny_rounds;  // short rows per lane group (2, 4, 6 or 8)
     int32_t big_blocks;   // workgroups per class in the wavefront-item section
@@ -289,6 +290,7 @@ constexpr int NO_UNIT = INT32_MIN;
 // eight turns per class or single chunks, so that no class runs dry.
 constexpr int MAX_DEAL = 5;
 __device__ inline int64_t dealt(int q, int c, int deal) { return ((((int64_t)(q >> deal) * N_CLASSES + c) << deal) + (q & ((1 << deal) - 1))); }
+constexpr int MAX_RUN = 8; // items per lane group, RUNS
 constexpr int64_t SMALL_GRID = 1024; // workgroups of one kind a cache-resident graph is cut into before runs grow
 
 // One gather phase of the tiny-row path: sub-round t hands unit (t * GROUPS + grp) of the wavefront
@@ -476,7 +478,7 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, const Spm
 
 // Lane-group items (whole rows and class pieces of 5..GI_MAX entries, GI_MAX = the schedule's item_max):
 // workgroup b serves class b mod 8 and takes 4 * G consecutive items of its list (first the class's own pieces, then its
-// share of the whole rows), lane group grp of wavefront w the item w * G + grp of them.  The group reads the item's
+// share of the whole rows; RUNS: a.rounds times as many), lane group grp of wavefront w the item w * G + grp of them.  The group reads the item's
 // (column, value) pairs with one read per LPR entries (lane `sub` holds entries sub, sub + LPR, ...), and each gather takes
 // its pair from the holding lane by a cross-lane read, eight gathers in flight.
 // One item per lane group, not a run of several: what is in flight together on an XCD is then a short stretch of rows
@@ -484,61 +486,87 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, const Spm
 // item's pairs are free.  Runs of 8 / 4 / 2 / 1 items per lane group: 6.3 M entries, 300 k nodes 70 / 64 / 63 / 63 us;
 // 41 M entries, 1 M nodes 0.422 / 0.410 / 0.406 / 0.404 ms; 126 M entries 1.246 / 1.237 / 1.232 / 1.229 ms; 2 M nodes in
 // communities, breadth-first order 1.55 / 1.53 / 1.42 / 1.29 ms (all 32 columns).
-template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG>
+// RUNS, where a graph stays in cache and is numbered so that a row's columns are neighbours (meshes, bands): gathers return at once there,
+// the chain descriptor, pairs, gathers, store bounds a wavefront, and runs overlap it (the next round's pairs are requested behind the
+// first gathers).  1 M nodes, 1 / 8 items per lane group: 5 entries a row 64 columns 217 / 168 us, 128 columns 422 / 309, 7 entries 64 columns
+// 222 / 177, 9 entries 273 / 242, 17 entries 327 / 309; but uniform random graphs of 7 entries a row 235 / 247, 128 columns 461 / 487.
+template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG, bool RUNS>
 __device__ __forceinline__ void group_items_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
-    constexpr int G = 64 / LPR;                 // items per wavefront
+    constexpr int G = 64 / LPR;                 // items in flight per wavefront
     constexpr int K = LPR >= GI_MAX ? 1 : GI_MAX / LPR; // index registers per lane (K * LPR >= GI_MAX entries)
     constexpr int U = 8;
-    constexpr int RUN = 4 * G;                  // items per workgroup
+    constexpr int ROUND = 4 * G;                // items a workgroup has in flight
     using L = Ld<V>;
+    const int run = RUNS ? ROUND * a.rounds : ROUND; // items per workgroup
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int cls = block % N_CLASSES, blk = block / N_CLASSES;
-    const int piece_blocks = (a.small_cnt[cls] + RUN - 1) / RUN;
+    const int piece_blocks = (a.small_cnt[cls] + run - 1) / run;
     const int grp = lane / LPR, sub = lane % LPR, gbase = lane - sub;
-    int64_t item = wave * G + grp;
+    const bool pieces = blk < piece_blocks; // uniform per workgroup
+    const int64_t at = (pieces ? blk : dealt(blk - piece_blocks, cls, a.deal)) * run;
+    const int64_t left = (pieces ? a.small_cnt[cls] : a.wsmall_cnt) - at - wave * G; // from this wavefront's first item on
+    const int4 *items = reinterpret_cast<const int4 *>(a.items) + (pieces ? a.small_off[cls] : a.wsmall_off) + at + wave * G;
+    if (RUNS && left <= 0) return; // uniform per wavefront
+    // Round r works on the ROUND consecutive items from r * ROUND on.  RUNS: lane r * G + g holds the descriptor of round r, group g.
     int4 d = make_int4(0, 0, 0, NO_UNIT);
-    if (blk < piece_blocks) { // uniform per workgroup
-        item += (int64_t)blk * RUN;
-        if (item < a.small_cnt[cls]) d = *reinterpret_cast<const int4 *>(a.items + a.small_off[cls] + item);
-    } else {
-        item += dealt(blk - piece_blocks, cls, a.deal) * RUN;
-        if (item < a.wsmall_cnt) d = *reinterpret_cast<const int4 *>(a.items + a.wsmall_off + item);
-    }
+    static_assert(MAX_RUN * G <= 64, "one descriptor per lane");
+    const int q = RUNS ? lane / G * ROUND + lane % G : grp;
+    if ((!RUNS || lane < a.rounds * G) && q < left) d = items[q];
+    const int rounds = !RUNS ? 1 : left < run ? (int)(left + ROUND - 1) / ROUND : a.rounds;
     const int col = io.col0 + sub * V;
     const bool col_ok = col < io.col_end;
     const int colc = load_col<RAG>(a, io, col);
-    const int beg = d.y, end = d.z, len = end - beg;
+    auto of_round = [&](int x, int r) { return RUNS ? __shfl(x, r * G + grp, 64) : x; };
+    int beg = of_round(d.y, 0), end = of_round(d.z, 0);
     int c_k[K];
     float v_k[K];
+    auto pairs = [&](int (&c)[K], float (&v)[K], int from, int to) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int e = beg + sub + LPR * k;
-        const bool ok = e < end;
-        c_k[k] = ok ? a.colidx[e] : 0;
-        v_k[k] = ok ? ld_val<FACT>(a, e) : 0.f;
-    }
-    Acc<V> acc;
-#pragma unroll
-    for (int j0 = 0; j0 < GI_MAX; j0 += U) {
-        if (!__any(j0 < len)) break; // wavefront-uniform
-        int c[U];
-        float v[U];
-        typename L::T x[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int jj = j0 + u;
-            const int cc = __shfl(c_k[jj / LPR < K ? jj / LPR : 0], gbase + jj % LPR, 64);
-            v[u] = shfl_val<FACT>(v_k[jj / LPR < K ? jj / LPR : 0], gbase + jj % LPR);
-            c[u] = jj < len ? cc : 0; // an absent entry re-reads row 0 and is not accumulated
+        for (int k = 0; k < K; ++k) {
+            const int e = from + sub + LPR * k;
+            const bool ok = e < to;
+            c[k] = ok ? a.colidx[e] : 0;
+            v[k] = ok ? ld_val<FACT>(a, e) : 0.f;
         }
+    };
+    pairs(c_k, v_k, beg, end);
+    for (int r = 0; r < rounds; ++r) {
+        const int row = of_round(d.x, r), dst = of_round(d.w, r), len = end - beg;
+        int c_n[K];
+        float v_n[K];
+        if (RUNS) {
+            const int next = r + 1 < rounds ? r + 1 : 0;
+            beg = of_round(d.y, next);
+            end = next ? of_round(d.z, next) : beg;
+        }
+        Acc<V> acc;
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], colc);
+        for (int j0 = 0; j0 < GI_MAX; j0 += U) {
+            if (!__any(j0 < len)) break; // wavefront-uniform
+            int c[U];
+            float v[U];
+            typename L::T x[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (j0 + u < len) acc.fma(v[u], x[u]);
+            for (int u = 0; u < U; ++u) {
+                const int jj = j0 + u;
+                const int cc = __shfl(c_k[jj / LPR < K ? jj / LPR : 0], gbase + jj % LPR, 64);
+                v[u] = shfl_val<FACT>(v_k[jj / LPR < K ? jj / LPR : 0], gbase + jj % LPR);
+                c[u] = jj < len ? cc : 0; // an absent entry re-reads row 0 and is not accumulated
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], colc);
+            if (RUNS && j0 == 0) pairs(c_n, v_n, beg, end); // the next round's, behind the first gathers (none behind the last round)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (j0 + u < len) acc.fma(v[u], x[u]);
+        }
+        if (dst != NO_UNIT && col_ok) store_result<V, RAG>(acc, a, io, row, dst, col);
+        if (RUNS) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) { c_k[k] = c_n[k]; v_k[k] = v_n[k]; }
+        }
     }
-    if (d.w != NO_UNIT && col_ok) store_result<V, RAG>(acc, a, io, d.x, d.w, col);
 }
 
 // Rows of at most TINY_ROW entries, up to 64 consecutive positions of the schedule per wavefront (consecutive
@@ -563,7 +591,7 @@ template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __global__ __launch_bounds__(256) void spmm_wave_items_kernel(const SpmmArgs a, const SpmmBatch b, unsigned first) { const SpmmIo io = pick_io(a, b); wave_items_body<LPR, V, S32, FACT, RAG>(a, io, blockIdx.x + first); }
 
 template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG>
-__global__ __launch_bounds__(256) void spmm_group_items_kernel(const SpmmArgs a, const SpmmBatch b, unsigned first) { const SpmmIo io = pick_io(a, b); group_items_body<LPR, V, S32, GI_MAX, FACT, RAG>(a, io, blockIdx.x + first); }
+__global__ __launch_bounds__(256) void spmm_group_items_kernel(const SpmmArgs a, const SpmmBatch b, unsigned first) { const SpmmIo io = pick_io(a, b); group_items_body<LPR, V, S32, GI_MAX, FACT, RAG, false>(a, io, blockIdx.x + first); }
 
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a, const SpmmBatch b, unsigned first) { const SpmmIo io = pick_io(a, b); tiny_rows_body<LPR, V, S32, FACT, RAG>(a, io, blockIdx.x + first); }
@@ -574,20 +602,20 @@ __global__ __launch_bounds__(256) void spmm_tiny_rows_kernel(const SpmmArgs a, c
 // each of three launches would pay its own ramp-up and its own chain of dependent loads; in one launch
 // they overlap (cfg2: 0.075 -> 0.056 ms per call).  Large graphs keep the three launches: there the
 // class pieces must have the L2s to themselves before the whole rows start (merged: cfg5 4.09 -> 4.30 ms).
-template <int LPR, int V, bool S32, bool FACT, bool RAG>
+template <int LPR, int V, bool S32, bool FACT, bool RAG, bool RUNS>
 __global__ __launch_bounds__(256) void spmm_merged_kernel(const SpmmArgs a, const SpmmBatch batch, int g1, int g2, unsigned first)
 {
     const SpmmIo io = pick_io(a, batch);
     const int b = blockIdx.x + first; // uniform per workgroup
     if (b < g1) wave_items_run_body<LPR, V, S32, FACT, RAG>(a, io, b);
-    else if (b < g1 + g2) group_items_body<LPR, V, S32, ITEM_SHORT, FACT, RAG>(a, io, b - g1);
+    else if (b < g1 + g2) group_items_body<LPR, V, S32, ITEM_SHORT, FACT, RAG, RUNS>(a, io, b - g1);
     else tiny_rows_body<LPR, V, S32, FACT, RAG>(a, io, b - g1 - g2);
 }
 
 // The same behind the first `extra` workgroups (a multiple of 8), which form the final sums of the weight gradients: those are a launch of
 // their own otherwise, on a small graph as long as the aggregation itself.  Backward passes of slice layers, sums in their own launch / here:
 // 2048 rows 64 -> 32 12.9 / 11.1 us, 5000 rows 200 -> 200 78.9 / 73.6, 60 k rows 32 -> 32 32.9 / 29.9; 169 k rows, four slices: 10 us less.
-template <int LPR>
+template <int LPR, bool RUNS>
 __global__ __launch_bounds__(256) void spmm_merged_sums_kernel(const SpmmArgs a, const SpmmBatch batch, int g1, int g2, const FinalWork f, int extra)
 {
     const int b = (int)blockIdx.x - extra; // uniform per workgroup
@@ -597,7 +625,7 @@ __global__ __launch_bounds__(256) void spmm_merged_sums_kernel(const SpmmArgs a,
     }
     const SpmmIo io = pick_io(a, batch);
     if (b < g1) wave_items_run_body<LPR, 4, true, true, false>(a, io, b);
-    else if (b < g1 + g2) group_items_body<LPR, 4, true, ITEM_SHORT, true, false>(a, io, b - g1);
+    else if (b < g1 + g2) group_items_body<LPR, 4, true, ITEM_SHORT, true, false, RUNS>(a, io, b - g1);
     else tiny_rows_body<LPR, 4, true, true, false>(a, io, b - g1 - g2);
 }
 
@@ -646,7 +674,8 @@ int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes,
             const int64_t extra = sums ? round_up((sums->stride + FINAL_ELEMS - 1) / FINAL_ELEMS, N_CLASSES) : 0;
             if (sums && blocks + extra <= MAX_GRID) {
                 const dim3 grid((unsigned)(blocks + extra), (unsigned)batch, (unsigned)passes);
-                spmm_merged_sums_kernel<LPR><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2, *sums, (int)extra);
+                if (a.rounds > 1) spmm_merged_sums_kernel<LPR, true><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2, *sums, (int)extra);
+                else spmm_merged_sums_kernel<LPR, false><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2, *sums, (int)extra);
                 SG_LAUNCH_CHECK();
                 return SLICEGCN_OK;
             }
@@ -654,7 +683,9 @@ int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes,
         if (sums)
             if (int rc = launch_final_sum(*sums, batch, stream)) return rc;
         return launch_parts(blocks, [&](unsigned first, unsigned count) {
-            spmm_merged_kernel<LPR, V, S32, FACT, RAG><<<dim3(count, (unsigned)batch, (unsigned)passes), 256, 0, stream>>>(a, b, (int)g1, (int)g2, first);
+            const dim3 grid(count, (unsigned)batch, (unsigned)passes);
+            if (a.rounds > 1) spmm_merged_kernel<LPR, V, S32, FACT, RAG, true><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2, first);
+            else spmm_merged_kernel<LPR, V, S32, FACT, RAG, false><<<grid, 256, 0, stream>>>(a, b, (int)g1, (int)g2, first);
         });
     }
     // a part of a grid starts at a multiple of 8, so that workgroup b still serves class b mod 8
@@ -784,18 +815,20 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, 
             return (int)(t < 1 ? 1 : t > most ? most : t);
         };
         a.ipw = resident ? turns(sc.wbig_cnt, 4, 4) : 1;
+        a.rounds = resident && sc.local ? turns(sc.wsmall_cnt, groups, MAX_RUN) : 1;
         a.tiny_rounds = resident ? 2 * turns(g->n, 2 * groups, 4) : 8;
         // workgroups per class: the class's own pieces, then its share of the whole-row chunks
         const int64_t ipb = 4 * a.ipw;
         const int64_t wbig_chunks = ((int64_t)sc.wbig_cnt + ipb - 1) / ipb;
-        const int64_t wsmall_chunks = ((int64_t)sc.wsmall_cnt + groups - 1) / groups;
+        const int64_t run = groups * a.rounds;
+        const int64_t wsmall_chunks = ((int64_t)sc.wsmall_cnt + run - 1) / run;
         a.deal = 0;
         while (a.deal < MAX_DEAL && (wsmall_chunks >> (a.deal + 1)) >= 8 * N_CLASSES) ++a.deal;
         const int64_t wsmall_blocks = round_up(wsmall_chunks, N_CLASSES << a.deal) / N_CLASSES;
         int64_t big_blocks = 0, small_blocks = 0;
         for (int c = 0; c < N_CLASSES; ++c) {
             const int64_t x = (sc.big_cnt[c] + ipb - 1) / ipb + (wbig_chunks + N_CLASSES - 1 - c) / N_CLASSES;
-            const int64_t y = (sc.small_cnt[c] + groups - 1) / groups + wsmall_blocks;
+            const int64_t y = (sc.small_cnt[c] + run - 1) / run + wsmall_blocks;
             big_blocks = x > big_blocks ? x : big_blocks;
             small_blocks = y > small_blocks ? y : small_blocks;
         }

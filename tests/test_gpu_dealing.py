@@ -52,3 +52,64 @@ def test_more_workgroups_than_one_grid():
     g.destroy()
     del X, Y
     torch.cuda.empty_cache()
+
+
+@pytest.fixture(scope="module", params=["symmetric", "directed", "breadth first"])
+def band(request):
+    """Columns within 200 of the row, 1 to 32 entries and more, and a few rows of about 280 entries that are cut: graphs numbered like this take
+    several items per lane group."""
+    n, rng = 70_003, np.random.default_rng(7)
+    deg = rng.integers(0, 16, n)
+    src = np.repeat(np.arange(n), deg)
+    dst = np.clip(src + rng.integers(-200, 201, src.size), 0, n - 1)
+    hubs = rng.integers(0, n, 6)
+    src = np.concatenate([src, np.repeat(hubs, 280)])
+    dst = np.concatenate([dst, rng.integers(0, n, 6 * 280)])
+    flags = {"symmetric": sg.binding.SYMMETRIZE, "directed": 0, "breadth first": sg.binding.SYMMETRIZE | sg.binding.REORDER_BFS}[request.param]
+    g = sg.slicegcn_build_norm_csr(dev(src, torch.int64), dev(dst, torch.int64), n, flags | sg.binding.ADD_SELF_LOOPS)
+    h = g.to_host()
+    rows = torch.as_tensor(np.repeat(np.arange(n), np.diff(h["rowptr"]))).cuda()
+    yield g, n, rows, torch.as_tensor(h["colidx"]).long().cuda(), torch.as_tensor(h["vals"]).double().cuda(), torch.as_tensor(h["dinv"]).cuda(), flags == 0
+    g.destroy()
+
+
+def aggregated(band, X, transpose):
+    """A X and |A| |X| in 64 bits."""
+    g, n, rows, cols, vals, dinv, _ = band
+    if transpose:
+        rows, cols = cols, rows
+    return [torch.zeros((n, X.shape[1]), dtype=torch.float64, device="cuda").index_add_(0, rows, vals[:, None] * x[cols]) for x in (X.double(), X.double().abs())]
+
+
+@pytest.mark.parametrize("width,ld", [(3, 3), (25, 25), (25, 32), (32, 32), (64, 64), (100, 101), (128, 128), (300, 304)])   # 2 to 8 items per lane group
+@pytest.mark.parametrize("prescaled", [False, True])
+def test_several_items_per_lane_group(band, width, ld, prescaled):
+    g, n, dinv, directed = band[0], band[1], band[5], band[6]
+    X = torch.full((n, ld), float("nan"), device="cuda")
+    X[:, :width] = torch.randn((n, width), generator=torch.Generator(device="cuda").manual_seed(width), device="cuda")
+    given = X * dinv[:, None] if prescaled else X
+    for transpose in (False, True) if directed else (False,):
+        Y = torch.full((n, ld + 1), 7.0, device="cuda")
+        sg.slicegcn_spmm_slice(g, given[:, :width], Y[:, :width], transpose=transpose, prescaled=prescaled)
+        want, size = aggregated(band, X[:, :width], transpose)
+        # fp32 sums of at most 600 terms, and four roundings of a value, its factors and the product
+        assert bool(((Y[:, :width].double() - want).abs() <= 604 * 2.0 ** -24 * size).all()) and bool((Y[:, width:] == 7.0).all())
+
+
+@pytest.mark.parametrize("w_in,w_out", [(32, 20), (64, 33), (128, 16)])
+def test_several_items_per_lane_group_beside_final_sums(band, w_in, w_out):
+    """A layer's input gradient, in whose launch the final sums of its weight gradients are formed."""
+    g, n, directed = band[0], band[1], band[6]
+    gen = torch.Generator(device="cuda").manual_seed(w_in)
+    X, Z, G, W, Ws = (torch.randn(s, generator=gen, device="cuda") for s in ((n, w_in), (n, w_in), (n, w_out), (w_in, w_out), (w_in, w_out)))
+    got = []
+    for dX in (torch.empty((n, w_in), device="cuda"), None):
+        grads = [torch.full(s, 7.0, device="cuda") for s in ((w_in, w_out), (w_out,), (w_in, w_out), (w_out,))]
+        ws = torch.empty(sg.binding.slicegcn_layer_bwd_workspace_bytes(g, w_in, w_out, dX is not None), dtype=torch.uint8, device="cuda")
+        sg.binding.slicegcn_layer_bwd(g, X, W, Ws, Z, None, G, dX, *grads, ws, act=sg.binding.ACT_NONE)
+        got.append(grads)
+        if dX is not None:
+            want = aggregated(band, G.double() @ W.double().t(), directed)[0] + G.double() @ Ws.double().t()
+            size = aggregated(band, G.double().abs() @ W.double().abs().t(), directed)[0] + G.double().abs() @ Ws.double().abs().t()
+            assert bool(((dX.double() - want).abs() <= (604 + 2 * w_out) * 2.0 ** -24 * size).all())
+    assert all(map(torch.equal, *got))
