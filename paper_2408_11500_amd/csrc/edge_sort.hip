@@ -105,10 +105,15 @@ template <class F> __device__ inline void for_each_key(const EdgeList &e, int64_
     }
 }
 
+constexpr int MAX_LEVELS = 3;                // see Cut
+constexpr int N_COUNTS = 4 + 2 * MAX_LEVELS; // Buckets' n_big ... n_tiles, which the first kernel of a sort clears
+
 // counts[digit * tiles + tile]: keys of every digit in a tile of the edge list
-__global__ __launch_bounds__(PT) void count_edges_kernel(const EdgeList e, int64_t n_tiles, int n_digits, int32_t *__restrict__ counts, int32_t *__restrict__ n_bad)
+__global__ __launch_bounds__(PT) void count_edges_kernel(const EdgeList e, int64_t n_tiles, int n_digits, int32_t *__restrict__ counts, int32_t *__restrict__ n_bad,
+                                                         int32_t *__restrict__ cleared)
 {
     __shared__ int32_t cnt[MAX_DIGITS];
+    if (blockIdx.x == 0 && threadIdx.x < N_COUNTS) cleared[threadIdx.x] = 0;
     for (int d = threadIdx.x; d < MAX_DIGITS; d += PT) cnt[d] = 0;
     __syncthreads();
     int bad = 0;
@@ -147,13 +152,16 @@ __device__ inline int scan_digits(const int32_t *cnt, int32_t *off, int32_t *wav
 
 // Distributes a tile of the edge list: the keys are ranked by digit in LDS (in any order within a digit: they are sorted later), laid out by
 // digit there and written as one run per digit.  at[digit * tiles + tile]: where the tile's run of a digit starts.
-// BUCKET: the digit is the bucket, the key has the row within it and the column.
+// BUCKET: the digit is the bucket, the key has the row within it and the column.  at = NULL: there is one tile, which knows where its digits
+// start and counts the pairs out of range itself; the buckets' starts go to `start` (no counting, no scan: 300 edges of 100 nodes, build
+// SMALL_BEFORE -> SMALL_AFTER us).
 // Otherwise there is a second pass.  32-bit keys: row bits within the bucket as well, and the second digit goes to an array of its own
 // (6 bytes a key instead of 8, of which the counting reads 2: 126 M keys distributed 0.59 -> 0.57 ms, counted 0.25 -> 0.09, distributed again
 // 0.38 -> 0.35); 64-bit keys: the whole row.
 template <class K, bool BUCKET>
 __global__ __launch_bounds__(PT) void distribute_edges_kernel(const EdgeList e, int64_t n_tiles, int n_digits, const int32_t *__restrict__ at, K *__restrict__ out,
-                                                              int bits2, uint16_t *__restrict__ second)
+                                                              int bits2, uint16_t *__restrict__ second, int32_t *__restrict__ start, int32_t *__restrict__ n_bad,
+                                                              int32_t *__restrict__ cleared)
 {
     constexpr bool SPLIT = !BUCKET && sizeof(K) == 4;
     __shared__ K keys[2 * TILE_ITEMS];
@@ -190,7 +198,15 @@ __global__ __launch_bounds__(PT) void distribute_edges_kernel(const EdgeList e, 
                 if (BUCKET || SPLIT) digit[pos] = (uint16_t)d;
                 if (SPLIT) digit2[pos] = (uint16_t)((row[j][w] >> within) & ((1u << bits2) - 1u));
             }
-    if ((int)threadIdx.x < n_digits) cnt[threadIdx.x] = at[(int64_t)threadIdx.x * n_tiles + blockIdx.x] - off[threadIdx.x]; // the ranks are in registers
+    if (BUCKET && !at) { // uniform
+        if (bad) atomicAdd(n_bad, bad);
+        cnt[threadIdx.x] = 0;
+        if ((int)threadIdx.x < n_digits) start[threadIdx.x] = off[threadIdx.x];
+        if (threadIdx.x == 0) start[n_digits] = total;
+        if (threadIdx.x < N_COUNTS) cleared[threadIdx.x] = 0;
+    } else if ((int)threadIdx.x < n_digits) {
+        cnt[threadIdx.x] = at[(int64_t)threadIdx.x * n_tiles + blockIdx.x] - off[threadIdx.x]; // the ranks are in registers
+    }
     __syncthreads();
     for (int i = threadIdx.x; i < total; i += PT) {
         const K k = keys[i];
@@ -510,7 +526,7 @@ __device__ inline void put_row(const RowOut &o, int64_t row, int32_t d)
 // Builds with one workgroup per part and a bitmap of its values, gone over once per 2^19 of them / cut again (a radix sort of all keys): star
 // of a million leaves 0.72 / 0.43 ms (0.48); one pair 20 M times, 1000 nodes 5.5 / 0.87 (0.89), 3 M nodes 5.6 / 1.5 (2.0); a row of
 // 100 000 among 2 M edges of 40 M nodes 6.3 / 3.0 (3.0); 40 000 pairs 1250 times each, 200 nodes 1.84 / 0.87 (1.69), 3 M nodes 2.4 / 3.1 (4.5).
-constexpr int SUB_BITS = 11, SUBS = 1 << SUB_BITS, MAX_LEVELS = 3;
+constexpr int SUB_BITS = 11, SUBS = 1 << SUB_BITS;
 struct Cut {
     int32_t bucket, parent; // parent: the part (its cut * SUBS + its number) that is cut here, -1: the whole bucket
     int32_t beg, end;       // the keys
@@ -998,7 +1014,6 @@ __global__ __launch_bounds__(256) void emit_kernel(const Buckets s, const EmitAr
     }
 }
 
-constexpr int N_COUNTS = 4 + 2 * MAX_LEVELS; // n_big ... n_tiles
 // Workspace: what lives until the entries are emitted, then what the distribution needs
 struct Layout {
     BucketPlan p;
@@ -1071,21 +1086,25 @@ int sort_rows(const Layout &l, const int64_t *row, const int64_t *col, int64_t n
     b.col_bits = p.col_bits;
     b.row_shift = p.row_shift;
     const size_t mark = ws.used;
-    SG_HIP(hipMemsetAsync(b.n_big, 0, N_COUNTS * 4, stream));
-    if (p.n_items > 0) {
+    if (p.tiles1 == 1 && p.bits2 == 0) {
+        const EdgeList e{row, col, n_edges, n, p.n_items, sym ? 1 : 0, p.col_bits, p.row_shift};
+        if constexpr (sizeof(K) == 4) // 64-bit keys take two passes
+            distribute_edges_kernel<K, true><<<1, PT, 0, stream>>>(e, 1, (int)p.n_buckets, nullptr, keys, 0, nullptr, start, n_bad, b.n_big);
+        SG_LAUNCH_CHECK();
+    } else if (p.n_items > 0) {
         int32_t *counts = nullptr, *at1 = nullptr;
         if (int rc = ws.take((size_t)p.counts1() * 4, &counts)) return rc;
         if (int rc = ws.take((size_t)p.counts1() * 4, &at1)) return rc;
         const EdgeList e{row, col, n_edges, n, p.n_items, sym ? 1 : 0, p.col_bits, p.row_shift + p.bits2};
         const int digits1 = (int)p.digits1();
-        count_edges_kernel<<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, counts, n_bad);
+        count_edges_kernel<<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, counts, n_bad, b.n_big);
         SG_LAUNCH_CHECK();
         if (int rc = scan_i32(counts, at1, p.counts1(), ws, stream)) return rc; // the last element is only written: the total
         SecondPass s{nullptr, nullptr, at1, nullptr, p.tiles1, digits1, p.bits2, p.col_bits, p.row_shift};
         int32_t *at2 = nullptr;
         if (p.bits2 == 0) {
-            if constexpr (sizeof(K) == 4) // 64-bit keys have more buckets
-                distribute_edges_kernel<K, true><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, keys, 0, nullptr);
+            if constexpr (sizeof(K) == 4)
+                distribute_edges_kernel<K, true><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, keys, 0, nullptr, nullptr, nullptr, nullptr);
             SG_LAUNCH_CHECK();
         } else {
             uint16_t *second = sizeof(K) == 4 ? reinterpret_cast<uint16_t *>(tables.base) : nullptr;
@@ -1096,7 +1115,7 @@ int sort_rows(const Layout &l, const int64_t *row, const int64_t *col, int64_t n
             s.keys = spare;
             s.second = second;
             s.tile_start = tile_start;
-            distribute_edges_kernel<K, false><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, spare, p.bits2, second);
+            distribute_edges_kernel<K, false><<<(unsigned)p.tiles1, PT, 0, stream>>>(e, p.tiles1, digits1, at1, spare, p.bits2, second, nullptr, nullptr, nullptr);
             SG_LAUNCH_CHECK();
             tile_starts_kernel<<<1, PT, 0, stream>>>(at1, p.tiles1, digits1, tile_start);
             SG_LAUNCH_CHECK();
@@ -1109,6 +1128,7 @@ int sort_rows(const Layout &l, const int64_t *row, const int64_t *col, int64_t n
         bucket_starts_kernel<<<blocks_for(p.n_buckets + 1), TPB, 0, stream>>>(s, at2, p.n_buckets, start);
         SG_LAUNCH_CHECK();
     } else {
+        SG_HIP(hipMemsetAsync(b.n_big, 0, N_COUNTS * 4, stream));
         SG_HIP(hipMemsetAsync(start, 0, (size_t)(p.n_buckets + 1) * 4, stream));
     }
     ws.used = mark; // later users are ordered behind these kernels on the stream

@@ -1,4 +1,4 @@
-"""The builder's distribution and sort at the sizes where they change their way: one and two distributing passes, buckets sorted with 4 to 32
+"""The builder's distribution and sort at the sizes where they change their way: one tile of edges, one and two distributing passes, buckets sorted with 4 to 32
 keys per thread, buckets cut once more (and parts of theirs that go through a bitmap: repeats), 64-bit keys, empty rows."""
 import numpy as np
 import pytest
@@ -66,6 +66,19 @@ ALL = sg.binding.SYMMETRIZE | sg.binding.ADD_SELF_LOOPS
 def test_random_pairs(n, m, flags):
     rng = np.random.default_rng(n + m)
     check(rng.integers(0, n, m), rng.integers(0, n, m), n, flags)
+
+
+@pytest.mark.parametrize("flags", [0, sg.binding.SYMMETRIZE, sg.binding.ADD_SELF_LOOPS, ALL])
+@pytest.mark.parametrize("n,m", [(100, 300), (2047, 1024), (2048, 1024), (2048, 1025), (2, 3072), (2000, 3072), (2000, 3073), (1_048_576, 3071),
+                                 (1_048_576, 3072), (1_048_576, 3073), (1_048_577, 3072)])
+def test_one_tile_of_edges(n, m, flags):
+    """Up to 3072 edges and diagonal entries, up to 512 buckets: no counting before the distribution; and one more of either."""
+    rng = np.random.default_rng(n + m)
+    src, dst = rng.integers(0, n, m), rng.integers(0, n, m)
+    check(src, dst, n, flags)
+    src[m // 2] = n
+    with pytest.raises(sg.binding.SliceGCNError, match=r"1 edge\(s\) name a node outside"):
+        check(src, dst, n, flags)
 
 
 @pytest.mark.parametrize("keys", [1, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193, 16383, 16384, 16385, 50_000])
