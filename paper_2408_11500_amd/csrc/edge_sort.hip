@@ -6,7 +6,7 @@
 //   sort                a workgroup sorts a bucket in registers, drops repeats and counts its rows (degrees and their roots included),
 //                       so that no later pass looks for row starts; larger buckets are cut first;
 //   emit                column indices and values, once the row pointers are there (a scan of the degrees).
-// Keys within a bucket are the low bits of the row and the column, 32 bits up to 2^25 nodes.  Then the first pass writes 6 bytes per key (the
+// Keys within a bucket are the low bits of the row and the column, 32 bits up to 2^25 nodes (see BucketPlan).  Then the first pass writes 6 bytes per key (the
 // second digit apart), the second counts from 2 of them, reads 6 and writes 4, and sorting and emission move 4.  The result is a function
 // of the set of pairs alone: integer counters decide only where a key waits to be sorted.
 //
@@ -38,10 +38,13 @@ inline unsigned bits_for(uint64_t v)
 //     distributing: 1024 per bucket 2.44 ms, 2048 2.33, 4096 2.36), half as many with 64-bit keys, whose comparisons cost more (44 M keys
 //     of 40 M nodes, build: 2.97 ms with 2048, 2.87 with 1024);
 //   * no more than 2^MAX_ROW_SHIFT rows in a bucket as far as the bits go (a workgroup counts the rows of its bucket);
-//   * 32-bit keys where that takes no more than MAX_BITS bits of bucket number (up to 2^25 nodes), 64-bit keys above;
+//   * 32-bit keys where that takes no more than MAX_BITS bits of bucket number (up to 2^25 nodes), 64-bit keys above, and where it takes all of
+//     those bits (from 2^24 nodes on) for buckets of fewer than SPARSE_KEYS keys: a workgroup for every few keys costs more than wider ones
+//     (30 M nodes, 32 / 64 bits: 8 keys a bucket 1.73 / 0.92 ms, 118 2.34 / 2.01, 145 4.89 / 4.71 for both directions, 152 2.78 / 2.87, 175 2.59 / 2.64);
 //   * up to 2^DIGIT_BITS buckets one pass over the edges distributes them, above it two passes by half of the bits each.
 constexpr int DIGIT_BITS = 9, MAX_DIGITS = 1 << DIGIT_BITS, MAX_BITS = 2 * DIGIT_BITS;
 constexpr int64_t BUCKET_KEYS = 2048, BUCKET_KEYS_64 = 1024;
+constexpr int64_t SPARSE_KEYS = 150;
 constexpr int MAX_ROW_SHIFT = 11;
 constexpr int PT = 512;           // threads of a distributing workgroup
 // edges (two keys each) or diagonal entries a workgroup takes from the edge list: longer runs per digit or more workgroups on a CU (126 M keys,
@@ -68,7 +71,7 @@ BucketPlan bucket_plan(int64_t n_edges, int64_t n, bool sym, bool loops)
     p.max_keys = n_edges * (sym ? 2 : 1) + (loops ? n : 0);
     p.col_bits = (int)bits_for((uint64_t)(n - 1));
     int bits = 0; // of the bucket number
-    p.wide = 2 * p.col_bits - MAX_BITS > 32;
+    p.wide = 2 * p.col_bits - MAX_BITS > 32 || (2 * p.col_bits - MAX_BITS == 32 && (p.max_keys >> MAX_BITS) < SPARSE_KEYS);
     while (bits < MAX_BITS && bits < p.col_bits && (p.max_keys >> bits) > (p.wide ? BUCKET_KEYS_64 : BUCKET_KEYS)) ++bits;
     if (bits < p.col_bits - MAX_ROW_SHIFT) bits = p.col_bits - MAX_ROW_SHIFT < MAX_BITS ? p.col_bits - MAX_ROW_SHIFT : MAX_BITS;
     if (!p.wide && bits < 2 * p.col_bits - 32) bits = 2 * p.col_bits - 32;
@@ -154,7 +157,7 @@ __device__ inline int scan_digits(const int32_t *cnt, int32_t *off, int32_t *wav
 // digit there and written as one run per digit.  at[digit * tiles + tile]: where the tile's run of a digit starts.
 // BUCKET: the digit is the bucket, the key has the row within it and the column.  at = NULL: there is one tile, which knows where its digits
 // start and counts the pairs out of range itself; the buckets' starts go to `start` (no counting, no scan: 300 edges of 100 nodes, build
-// SMALL_BEFORE -> SMALL_AFTER us).
+// 142 -> 109 us).
 // Otherwise there is a second pass.  32-bit keys: row bits within the bucket as well, and the second digit goes to an array of its own
 // (6 bytes a key instead of 8, of which the counting reads 2: 126 M keys distributed 0.59 -> 0.57 ms, counted 0.25 -> 0.09, distributed again
 // 0.38 -> 0.35); 64-bit keys: the whole row.

@@ -81,6 +81,17 @@ def test_one_tile_of_edges(n, m, flags):
         check(src, dst, n, flags)
 
 
+@pytest.mark.parametrize("n,m", [(1 << 24, 5000), ((1 << 24) + 1, 5000), ((1 << 24) + 1, 20_000_000)])
+def test_few_keys_per_bucket(n, m):
+    """From 2^24 nodes on 32-bit keys would take a bucket for every 128 rows: 64 bits for fewer than 150 keys a bucket (the last has 152)."""
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    src, dst = (torch.randint(0, n, (m,), generator=gen, device="cuda") for _ in range(2))
+    dst[:400] = src[:400]                                # self pairs
+    src[400:20_400 if m > 10 ** 6 else 2400] = n - 1     # a row beyond a bucket's others
+    check(src, dst, n, sg.binding.SYMMETRIZE)
+    check(src, dst, n, 0)
+
+
 @pytest.mark.parametrize("keys", [1, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193, 16383, 16384, 16385, 50_000])
 def test_one_row(keys):
     """One row of so many pairs (with the repeats a third more), the others nearly empty: every size of the
