@@ -4,7 +4,7 @@
 // per stored entry.
 //
 //   entries   edge_sort.hip: edges distributed to buckets of rows, sorted there in registers, repeats dropped, rows counted;
-//   schedule  rows sorted into the item lists by ballot as well; only rows that are cut by column class
+//   schedule  rows sorted into the item lists by ballot; only rows that are cut by column class
 //             need per-row tables.
 //
 // What bounds a build beside the sort is the host: device allocations and synchronisations.  All scratch
@@ -25,7 +25,7 @@ namespace {
 constexpr int TPB = 256;
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + TPB - 1) / TPB); }
 
-// Device words the host reads back: [0] out-of-range edges, [1] stored entries, [2] ... the schedule's and the row order's.
+// Device words the host reads back: [0] out-of-range edges, [1] those the transposed pattern's sort counts again, [2] ... the schedule's and the row order's.
 constexpr int N_COUNTERS = 64;
 
 // ---- schedule ---------------------------------------------------------------------------

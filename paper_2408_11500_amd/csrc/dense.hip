@@ -704,9 +704,18 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     }
     __syncthreads(); // the only workgroup barrier: from here on a wavefront touches its own tile only
 
-    // One strip from the registers fetched; `next`: the strip to fetch meanwhile.  WHOLE: 32 rows and NW columns to store.
-    auto strip_step = [&](int64_t strip, int64_t next, auto whole) {
-        constexpr bool WHOLE = decltype(whole)::value;
+    // One strip from the registers fetched; `next`: the strip to fetch meanwhile.  32 rows and NW columns to store (WHOLE), 32 rows and at least four
+    // columns (FULL_ROWS), or whatever there is (then nothing is fetched).
+    // FULL_ROWS: a lane without four columns of its own stores the row's last four once more, so that no store depends on a branch and the
+    // next strip's loads stay in flight as with WHOLE (2.4 M rows, fetched behind stores with a test per lane /
+    // here: 25 -> 40 208 / 158 us, 64 -> 47 297 / 255, 40 -> 10 173 / 128; input gradients 190 / 151, 290 / 252, 164 / 135).
+    constexpr std::integral_constant<int, 0> REST;
+    constexpr std::integral_constant<int, 1> FULL_ROWS;
+    constexpr std::integral_constant<int, 2> WHOLE;
+    constexpr bool AHEAD = !TWO || KC == 1; // two products of up to 64 columns leave no registers for it (64 -> 16 with self term 508 / 523 us)
+    const int last4 = a.Nout - 4, cs = cn < last4 ? cn : last4; // first column of the four that this lane stores
+    auto strip_step = [&](int64_t strip, int64_t next, auto form) {
+        constexpr bool ALL_ROWS = form.value >= FULL_ROWS.value;
         float out_f[PN]; // output factors of this strip's rows (the fetch below overwrites fo)
 #pragma unroll
         for (int it = 0; it < PN; ++it) out_f[it] = so_ld && !scale_operand ? fo[it] : 1.f;
@@ -736,7 +745,7 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
         uint32_t word[KC];
 #pragma unroll
         for (int w = 0; w < KC; ++w) word[w] = !BWD ? 0u : !a.mask ? ~0u : pw[w];
-        if (WHOLE) fetch(next, std::true_type()); // flies during the MFMAs and the stores below
+        if (ALL_ROWS) fetch(next, std::true_type()); // flies during the MFMAs and the stores below
         floatx16 acc1[NC], acc2[NC];
 #pragma unroll
         for (int t = 0; t < NC; ++t)
@@ -823,9 +832,15 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
 #pragma unroll
             for (int it = 0; it < PN; ++it) {
                 const int64_t row = row0 + rn + RN * it;
-                float4 v = *reinterpret_cast<const float4 *>(&tl[rn + RN * it][cn]);
+                float4 v;
+                if constexpr (form.value == FULL_ROWS.value) {
+                    const floatx4_u u = *reinterpret_cast<const floatx4_u *>(&tl[rn + RN * it][cs]);
+                    v = make_float4(u.x, u.y, u.z, u.w);
+                } else {
+                    v = *reinterpret_cast<const float4 *>(&tl[rn + RN * it][cn]);
+                }
                 if (scaled) scale4(v, out_f[it]);
-                store_cols4<WHOLE>(O + row * ldo + cn, v, row < a.n, a.Nout - cn);
+                store_cols4<ALL_ROWS>(O + row * ldo + (form.value == FULL_ROWS.value ? cs : cn), v, row < a.n, a.Nout - cn);
             }
             __builtin_amdgcn_wave_barrier();
         };
@@ -833,26 +848,30 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
         if constexpr (BWD && TWO) {
             if (a.O2) store_tile(acc2, a.O2, a.ldo2, false);
         }
-        if (!BWD && a.act == SLICEGCN_ACT_RELU && lane < 32 && (WHOLE || row0 + lane < a.n)) {
+        if (!BWD && a.act == SLICEGCN_ACT_RELU && lane < 32 && (ALL_ROWS || row0 + lane < a.n)) {
 #pragma unroll
             for (int t = 0; t < NC; ++t)
-                if (WHOLE || 32 * t < a.Nout) a.mask[(row0 + lane) * a.mask_words + t] = my_word[t];
+                if (form.value == WHOLE.value || 32 * t < a.Nout) a.mask[(row0 + lane) * a.mask_words + t] = my_word[t];
         }
     };
     int64_t strip = first;
+    auto ahead = [&](int64_t s) { return s + step < n_full ? s + step : s; };
     if (a.Nout == NW) {
 #pragma unroll 1
-        for (; strip < n_full; strip += step) strip_step(strip, strip + step < n_full ? strip + step : strip, std::true_type());
-    } else {
+        for (; strip < n_full; strip += step) strip_step(strip, ahead(strip), WHOLE);
+    } else if (AHEAD && a.Nout >= 4) {
+#pragma unroll 1
+        for (; strip < n_full; strip += step) strip_step(strip, ahead(strip), FULL_ROWS);
+    } else if (!AHEAD || NC == 1) { // (two tiles along the columns are never fewer than 33 columns)
 #pragma unroll 1
         for (; strip < n_full; strip += step) {
-            strip_step(strip, 0, std::false_type());
+            strip_step(strip, 0, REST);
             if (strip + step < n_full) fetch(strip + step, std::true_type());
         }
     }
     if (strip == n_full && a.n % 32 != 0) { // the rows left
         fetch(strip, std::false_type());
-        strip_step(strip, 0, std::false_type());
+        strip_step(strip, 0, REST);
     }
 }
 

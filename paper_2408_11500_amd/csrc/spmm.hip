@@ -66,8 +66,8 @@ struct SpmmArgs {
     int32_t load_max;     // ragged rows (RAG kernels): last column a 16-byte load may start at; 0: rows end on a whole vector
     int32_t big_off[N_CLASSES], big_cnt[N_CLASSES];     // wavefront pieces of class c
     int32_t small_off[N_CLASSES], small_cnt[N_CLASSES]; // lane-group pieces of class c
-    int32_t wbig_off, wbig_cnt;     // wavefront items of rows kept whole (dealt to the classes four at a time)
-    int32_t wsmall_off, wsmall_cnt; // lane-group whole rows (dealt one wavefront's share at a time)
+    int32_t wbig_off, wbig_cnt;     // wavefront items of rows kept whole (dealt to the classes a workgroup's share at a time)
+    int32_t wsmall_off, wsmall_cnt; // lane-group whole rows (dealt in stretches of 2^deal workgroups' shares)
 };
 
 // The operands of one launch: a batch of slices aggregated over the same graph (workgroups of grid row y work on slice y).

@@ -113,3 +113,32 @@ def test_rows_and_strips_have_the_same_bits(w_in, w_out, self_term):
         got.append([t[:n - 1] for t in (H, words, Y, bits, dX)])
         g.destroy()
     assert all(map(torch.equal, *got))
+
+
+@pytest.mark.parametrize("w_in,w_out", [(25, 40), (32, 33), (4, 63), (17, 34), (33, 4), (40, 5), (64, 30), (64, 3), (64, 47), (61, 62), (34, 33)])
+def test_rows_and_strips_up_to_64_wide_have_the_same_bits(w_in, w_out):
+    """Columns out that do not fill the tiles: lanes at a row's end store its last four columns once more.  Strips from 2^18 rows on, the last
+    one not whole; the general kernel below.  Rows on any boundary, NaN and guards behind them."""
+    n = (1 << 18) + 21
+    gen = torch.Generator(device="cuda").manual_seed(w_in + 64 * w_out)
+    X, (W, Ws, b, bs) = operand(gen, n, w_in, 1), (torch.randn(s, generator=gen, device="cuda") for s in ((w_in, w_out), (w_in, w_out), (w_out,), (w_out,)))
+    none, got = torch.empty(0, dtype=torch.int64, device="cuda"), []
+    for rows in (n, (1 << 18) - 1):
+        g = B.slicegcn_build_norm_csr(none, none, rows)
+        Z = torch.empty((rows, (w_in + 3) // 4 * 4), device="cuda")[:, :w_in]
+        H, Y, P, dX = (torch.full((rows, w_out + 1), 7.0, device="cuda") for _ in range(4))
+        words, bits = (torch.zeros((rows, (w_out + 31) // 32), dtype=torch.int32, device="cuda") for _ in range(2))
+        B.slicegcn_layer_fwd(g, X[:rows], W, b, Ws, bs, H[:, :w_out], Z, words)
+        B.slicegcn_linear_fwd(X[:rows], W, b, Y[:, :w_out], bits, act=B.ACT_RELU)
+        B.slicegcn_linear_fwd(X[:rows], W, b, P[:, :w_out])
+        # backward: the product with w_in columns in is that of a layer w_out -> w_in
+        B.slicegcn_linear_bwd(P[:, :w_out], W.t().contiguous(), None, X[:rows], dX[:, :w_out], None, None, None, act=B.ACT_NONE)
+        assert all(bool((t[:, w_out] == 7.0).all()) for t in (H, Y, P, dX))
+        got.append([t[:(1 << 18) - 1].clone() for t in (H, words, Y, bits, P, dX)])
+        tail = [t[(1 << 18) - 1:] for t in (P, dX)]
+        if rows == n:   # the last strips, against fp64
+            Xd = X[(1 << 18) - 1:].double()
+            for t, c in ((tail[0], b.double()), (tail[1], 0.)):
+                assert_fp32(t[:, :w_out], Xd @ W.double() + c, Xd.abs() @ W.double().abs() + (c.abs() if torch.is_tensor(c) else 0.), "tail")
+        g.destroy()
+    assert all(map(torch.equal, *got))
