@@ -103,8 +103,8 @@ __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restri
     }
 }
 
-// Counters for the host: rows of every kind, and how many more of SAMPLES rows have all of their columns within a LOCAL_SPAN-th of the
-// nodes than have not (one row per thread beside the wavefront that searches the boundaries, which takes longer); the column class boundaries
+// Counters for the host: rows of every kind, and how many more of SAMPLES rows have all of their columns (but for the diagonal, beside two or more)
+// within a LOCAL_SPAN-th of the nodes than have not (one row per thread beside the wavefront that searches the boundaries, which takes longer); the column class boundaries
 // stay on the device.
 constexpr int SAMPLES = 960, LOCAL_SPAN = 16;
 __global__ __launch_bounds__(SAMPLES + 64) void sched_summary_kernel(const int32_t *__restrict__ counts, int64_t n_groups, const int32_t *__restrict__ colptr, int64_t n,
@@ -119,11 +119,15 @@ __global__ __launch_bounds__(SAMPLES + 64) void sched_summary_kernel(const int32
     } else if (t >= 64) {
         const int64_t row = n * (t - 64) / SAMPLES;
         const int32_t beg = rowptr[row], end = rowptr[row + 1];
-        near = end - beg >= 2 && (int64_t)(colidx[end - 1] - colidx[beg]) * LOCAL_SPAN <= n;
-        far = end - beg >= 2 && !near;
+        if (end - beg >= 2) {
+            const int more = end - beg > 2 ? 1 : 0, first = colidx[beg], last = colidx[end - 1];
+            const int lo = first == row ? colidx[beg + more] : first, hi = last == row ? colidx[end - 1 - more] : last;
+            near = (int64_t)(hi - lo) * LOCAL_SPAN <= n;
+            far = !near;
+        }
     }
-    const int more = __syncthreads_count(near) - __syncthreads_count(far);
-    if (t == 3) summary[t] = more;
+    const int excess = __syncthreads_count(near) - __syncthreads_count(far);
+    if (t == 3) summary[t] = excess;
 }
 
 // ---- long rows: cut by column class ------------------------------------------------------

@@ -486,10 +486,11 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, const Spm
 // item's pairs are free.  Runs of 8 / 4 / 2 / 1 items per lane group: 6.3 M entries, 300 k nodes 70 / 64 / 63 / 63 us;
 // 41 M entries, 1 M nodes 0.422 / 0.410 / 0.406 / 0.404 ms; 126 M entries 1.246 / 1.237 / 1.232 / 1.229 ms; 2 M nodes in
 // communities, breadth-first order 1.55 / 1.53 / 1.42 / 1.29 ms (all 32 columns).
-// RUNS, where a graph stays in cache and is numbered so that a row's columns are neighbours (meshes, bands): gathers return at once there,
+// RUNS, where a graph stays in cache and a row's columns lie close together (meshes, bands, rows that all point at a few nodes): gathers return at once there,
 // the chain descriptor, pairs, gathers, store bounds a wavefront, and runs overlap it (the next round's pairs are requested behind the
 // first gathers).  1 M nodes, 1 / 8 items per lane group: 5 entries a row 64 columns 217 / 168 us, 128 columns 422 / 309, 7 entries 64 columns
-// 222 / 177, 9 entries 273 / 242, 17 entries 327 / 309; but uniform random graphs of 7 entries a row 235 / 247, 128 columns 461 / 487.
+// 222 / 177, 9 entries 273 / 242, 17 entries 327 / 309; 885 k nodes, 12 entries a row in the columns below 885, 16 columns 106 / 93; but uniform
+// random graphs of 7 entries a row 235 / 247, 128 columns 461 / 487.
 template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG, bool RUNS>
 __device__ __forceinline__ void group_items_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {

@@ -54,18 +54,18 @@ def test_more_workgroups_than_one_grid():
     torch.cuda.empty_cache()
 
 
-@pytest.fixture(scope="module", params=["symmetric", "directed", "breadth first"])
+@pytest.fixture(scope="module", params=["symmetric", "directed", "breadth first", "few columns"])
 def band(request):
-    """Columns within 200 of the row, 1 to 32 entries and more, and a few rows of about 280 entries that are cut: graphs numbered like this take
-    several items per lane group."""
+    """Columns within 200 of the row, 1 to 32 entries and more, and a few rows of about 280 entries that are cut; or columns below 70 and the
+    diagonal: graphs numbered like this take several items per lane group."""
     n, rng = 70_003, np.random.default_rng(7)
     deg = rng.integers(0, 16, n)
     src = np.repeat(np.arange(n), deg)
-    dst = np.clip(src + rng.integers(-200, 201, src.size), 0, n - 1)
+    dst = rng.integers(0, 70, src.size) if request.param == "few columns" else np.clip(src + rng.integers(-200, 201, src.size), 0, n - 1)
     hubs = rng.integers(0, n, 6)
     src = np.concatenate([src, np.repeat(hubs, 280)])
     dst = np.concatenate([dst, rng.integers(0, n, 6 * 280)])
-    flags = {"symmetric": sg.binding.SYMMETRIZE, "directed": 0, "breadth first": sg.binding.SYMMETRIZE | sg.binding.REORDER_BFS}[request.param]
+    flags = {"symmetric": sg.binding.SYMMETRIZE, "directed": 0, "few columns": 0, "breadth first": sg.binding.SYMMETRIZE | sg.binding.REORDER_BFS}[request.param]
     g = sg.slicegcn_build_norm_csr(dev(src, torch.int64), dev(dst, torch.int64), n, flags | sg.binding.ADD_SELF_LOOPS)
     h = g.to_host()
     rows = torch.as_tensor(np.repeat(np.arange(n), np.diff(h["rowptr"]))).cuda()
