@@ -273,11 +273,14 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
     };
     // Behind the last chunk: through LDS, so that a row of a tile goes out as eight 16-byte stores of one instruction (from the accumulators
     // an instruction stores 32 bytes to each of 32 rows, which takes the CU's L1 64 cycles instead of 16: 2.4 M rows 47 -> 256 1.23 -> 1.02 ms,
-    // 256 -> 256 3.03 -> 2.93, 169 k rows 40 -> 256 87 -> 68 us).
+    // 256 -> 256 3.03 -> 2.93, 169 k rows 40 -> 256 87 -> 68 us).  In a tile that is not full a lane without four columns of its own stores the
+    // row's last four once more, and below four columns a lane stores a row: no branches per lane (2.4 M rows 12 -> 44 213 -> 153 us, 256 -> 47
+    // 872 -> 830, 70 -> 7 213 -> 191, 160 -> 3 334 -> 317; input gradients 197 -> 143, 848 -> 819, 236 -> 216, 349 -> 335).
     auto store_last = [&](float *O, int64_t ldo, float f) {
         float (*tile)[TS] = reinterpret_cast<float (*)[TS]>(pool) + 32 * wave;
         const int lr = lane >> 3, lc = (lane & 7) * 4;
         const int64_t row0 = row_tile * 128 + wave * 32;
+        constexpr bool ROW_PER_LANE = !(NT == 3 && BWD && !TWO); // (it would spill two registers there)
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int left = a.Nout - col0 - 32 * t;
@@ -294,6 +297,16 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
             if (row0 + 32 <= a.n && left >= 32) { // uniform per wavefront
 #pragma unroll
                 for (int it = 0; it < 4; ++it) store_cols4<true>(o + 8 * it * ldo, *reinterpret_cast<const float4 *>(&tile[lr + 8 * it][lc]), true, 32);
+            } else if (row0 + 32 <= a.n && left >= 4) {
+                const int back = lc > left - 4 ? lc - (left - 4) : 0;
+#pragma unroll
+                for (int it = 0; it < 4; ++it)
+                    *reinterpret_cast<floatx4_u *>(o + 8 * it * ldo - back) = *reinterpret_cast<const floatx4_u *>(&tile[lr + 8 * it][lc - back]);
+            } else if (ROW_PER_LANE && left < 4) {
+                float *narrow = O + row * ldo + col0 + 32 * t;
+#pragma unroll
+                for (int c = 0; c < 4; c += 2)
+                    if (my_row < a.n && c + h < left) narrow[c + h] = tile[m][c + h];
             } else {
 #pragma unroll
                 for (int it = 0; it < 4; ++it)

@@ -142,3 +142,22 @@ def test_rows_and_strips_up_to_64_wide_have_the_same_bits(w_in, w_out):
                 assert_fp32(t[:, :w_out], Xd @ W.double() + c, Xd.abs() @ W.double().abs() + (c.abs() if torch.is_tensor(c) else 0.), "tail")
         g.destroy()
     assert all(map(torch.equal, *got))
+
+
+@pytest.mark.parametrize("n", [300, 20_032])
+@pytest.mark.parametrize("w_in,w_out", [(70, 1), (70, 3), (93, 7), (159, 21), (65, 31), (96, 34), (130, 67), (257, 35), (288, 97), (3, 99)])
+def test_last_columns_of_the_general_kernel(n, w_in, w_out):
+    """Output tiles that are not full, in strips of 32 rows and in a last one that is not: last columns stored once more, rows of up to three columns
+    by a lane each.  Against fp64, guards behind the rows."""
+    gen = torch.Generator(device="cuda").manual_seed(w_in + w_out)
+    X, W, b = operand(gen, n, w_in, 1), *(torch.randn(s, generator=gen, device="cuda") for s in ((w_in, w_out), (w_out,)))
+    Y, P, dX = (torch.full((n, w_out + 1), 7.0, device="cuda") for _ in range(3))
+    words = torch.zeros((n, (w_out + 31) // 32), dtype=torch.int32, device="cuda")
+    B.slicegcn_linear_fwd(X, W, b, P[:, :w_out])
+    B.slicegcn_linear_fwd(X, W, b, Y[:, :w_out], words, act=B.ACT_RELU)
+    B.slicegcn_linear_bwd(P[:, :w_out], W.t().contiguous(), None, X, dX[:, :w_out], None, None, None, act=B.ACT_NONE)
+    assert all(bool((t[:, w_out] == 7.0).all()) for t in (Y, P, dX))
+    want, size = X.double() @ W.double(), X.double().abs() @ W.double().abs()
+    assert_fp32(P[:, :w_out], want + b.double(), size + b.double().abs(), "Y")
+    assert torch.equal(Y[:, :w_out], P[:, :w_out].clamp_min(0.))
+    assert_fp32(dX[:, :w_out], want, size, "dX")
