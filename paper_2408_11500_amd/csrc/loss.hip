@@ -36,7 +36,7 @@ __device__ inline void ce_store_partial(const double *row_loss, double *__restri
 // sub + 16 i.  All loads of a group's four rows are requested before the first is used (rows past the end re-read the last): bound by
 // bytes on many rows and by one chain of loads on few.  With the
 // final sum, and a kernel that took the rows in turn: 2.4 M rows of 47 218 us (519), 169 k rows of 41 22 (35), 2048 rows of 8 6.9 (9.1).
-template <bool VEC>
+template <bool VEC, int R>
 __global__ __launch_bounds__(256) void softmax_ce_rows_kernel(const float *logits, int64_t ld, int64_t n, int32_t c,
                                                               const int32_t *__restrict__ labels, float *dlogits,
                                                               int64_t ldd, double *__restrict__ partial)
@@ -45,7 +45,8 @@ __global__ __launch_bounds__(256) void softmax_ce_rows_kernel(const float *logit
     const int grp = threadIdx.x / CE_LPR, sub = threadIdx.x % CE_LPR, lane0 = threadIdx.x & 48; // first lane of the group in its wavefront
     const float inv_n = 1.0f / (float)n;
     auto col = [&](int i) { return VEC ? 4 * sub + i : sub + CE_LPR * i; };
-    float x[4][4];
+    static_assert(!VEC || R == 4, "a load of four columns");
+    float x[4][R];
     int label[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(256) void softmax_ce_rows_kernel(const float *logit
             x[q][0] = w.x; x[q][1] = w.y; x[q][2] = w.z; x[q][3] = w.w;
         } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[q][i] = p[col(i) < c ? col(i) : c - 1];
+            for (int i = 0; i < R; ++i) x[q][i] = p[col(i) < c ? col(i) : c - 1];
         }
     }
 #pragma unroll
@@ -66,9 +67,9 @@ __global__ __launch_bounds__(256) void softmax_ce_rows_kernel(const float *logit
         const int64_t v = (int64_t)blockIdx.x * CE_ROWS_PER_BLOCK + local;
         const bool bad = label[q] < 0 || label[q] >= c;
         const int y = bad ? 0 : label[q];
-        float m = -INFINITY, mine = 0.f, e[4];
+        float m = -INFINITY, mine = 0.f, e[R];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < R; ++i) {
             if (col(i) >= c) x[q][i] = -INFINITY;
             m = fmaxf(m, x[q][i]);
             if ((VEC ? y % 4 : y / CE_LPR) == i) mine = x[q][i];
@@ -77,22 +78,28 @@ __global__ __launch_bounds__(256) void softmax_ce_rows_kernel(const float *logit
 #pragma unroll
         for (int s = 1; s < CE_LPR; s <<= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) e[i] = col(i) < c ? expf(x[q][i] - m) : 0.f;
-        float sum = VEC ? (e[0] + e[1]) + (e[2] + e[3]) : ((e[0] + e[1]) + e[2]) + e[3];
+        for (int i = 0; i < R; ++i) e[i] = col(i) < c ? expf(x[q][i] - m) : 0.f;
+        float sum = e[0];
+        if constexpr (VEC) {
+            sum = (e[0] + e[1]) + (e[2] + e[3]);
+        } else {
+#pragma unroll
+            for (int i = 1; i < R; ++i) sum += e[i];
+        }
 #pragma unroll
         for (int s = 1; s < CE_LPR; s <<= 1) sum += __shfl_xor(sum, s, 64);
         if (sub == 0) row_loss[local] = v >= n ? 0.0 : bad ? (double)NAN : (double)(m + logf(sum)) - (double)at_label;
         if (dlogits && v < n) {
             float *g = dlogits + v * ldd;
             const float inv_sum = 1.0f / sum;
-            float d[4];
+            float d[R];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) d[i] = (e[i] * inv_sum - (col(i) == y ? 1.f : 0.f)) * inv_n;
+            for (int i = 0; i < R; ++i) d[i] = (e[i] * inv_sum - (col(i) == y ? 1.f : 0.f)) * inv_n;
             if constexpr (VEC) {
                 if (col(0) < c) *reinterpret_cast<float4 *>(g + col(0)) = make_float4(d[0], d[1], d[2], d[3]);
             } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < R; ++i)
                     if (col(i) < c) g[col(i)] = d[i];
             }
         }
@@ -196,8 +203,9 @@ extern "C" int slicegcn_softmax_ce(const float *logits, int64_t ld, int64_t n, i
     ProfScope prof(SLICEGCN_PROF_LOSS, n_classes, stream);
     const bool vec = n_classes % 4 == 0 && ld % 4 == 0 && aligned16(logits) && (dlogits == nullptr || (ldd % 4 == 0 && aligned16(dlogits)));
     if (n_classes > 64) softmax_ce_kernel<<<(unsigned)nb, 256, 0, stream>>>(logits, ld, n, n_classes, labels, dlogits, ldd, partial);
-    else if (vec) softmax_ce_rows_kernel<true><<<(unsigned)nb, 256, 0, stream>>>(logits, ld, n, n_classes, labels, dlogits, ldd, partial);
-    else softmax_ce_rows_kernel<false><<<(unsigned)nb, 256, 0, stream>>>(logits, ld, n, n_classes, labels, dlogits, ldd, partial);
+    else if (vec) softmax_ce_rows_kernel<true, 4><<<(unsigned)nb, 256, 0, stream>>>(logits, ld, n, n_classes, labels, dlogits, ldd, partial);
+    else if (n_classes <= CE_LPR) softmax_ce_rows_kernel<false, 1><<<(unsigned)nb, 256, 0, stream>>>(logits, ld, n, n_classes, labels, dlogits, ldd, partial);
+    else softmax_ce_rows_kernel<false, 4><<<(unsigned)nb, 256, 0, stream>>>(logits, ld, n, n_classes, labels, dlogits, ldd, partial);
     SG_LAUNCH_CHECK();
     ce_final_kernel<<<1, 256, 0, stream>>>(partial, nb, n, loss);
     SG_LAUNCH_CHECK();
