@@ -273,8 +273,8 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
     };
     // Behind the last chunk: through LDS, so that a row of a tile goes out as eight 16-byte stores of one instruction (from the accumulators
     // an instruction stores 32 bytes to each of 32 rows, which takes the CU's L1 64 cycles instead of 16: 2.4 M rows 47 -> 256 1.23 -> 1.02 ms,
-    // 256 -> 256 3.03 -> 2.93, 169 k rows 40 -> 256 87 -> 68 us).  In a tile that is not full a lane without four columns of its own stores the
-    // row's last four once more, and below four columns a lane stores a row: no branches per lane (2.4 M rows 12 -> 44 213 -> 153 us, 256 -> 47
+    // 256 -> 256 3.03 -> 2.93, 169 k rows 40 -> 256 87 -> 68 us).  In a tile that is not full the lane at a row's end stores the row's last
+    // four columns, some of them once more, and below four columns a lane stores a row: no branches per lane and store (2.4 M rows 12 -> 44 213 -> 153 us, 256 -> 47
     // 872 -> 830, 70 -> 7 213 -> 191, 160 -> 3 334 -> 317; input gradients 197 -> 143, 848 -> 819, 236 -> 216, 349 -> 335).
     auto store_last = [&](float *O, int64_t ldo, float f) {
         float (*tile)[TS] = reinterpret_cast<float (*)[TS]>(pool) + 32 * wave;
@@ -299,9 +299,11 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
                 for (int it = 0; it < 4; ++it) store_cols4<true>(o + 8 * it * ldo, *reinterpret_cast<const float4 *>(&tile[lr + 8 * it][lc]), true, 32);
             } else if (row0 + 32 <= a.n && left >= 4) {
                 const int back = lc > left - 4 ? lc - (left - 4) : 0;
+                if (lc < left) {
 #pragma unroll
-                for (int it = 0; it < 4; ++it)
-                    *reinterpret_cast<floatx4_u *>(o + 8 * it * ldo - back) = *reinterpret_cast<const floatx4_u *>(&tile[lr + 8 * it][lc - back]);
+                    for (int it = 0; it < 4; ++it)
+                        *reinterpret_cast<floatx4_u *>(o + 8 * it * ldo - back) = *reinterpret_cast<const floatx4_u *>(&tile[lr + 8 * it][lc - back]);
+                }
             } else if (ROW_PER_LANE && left < 4) {
                 float *narrow = O + row * ldo + col0 + 32 * t;
 #pragma unroll
@@ -723,6 +725,9 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     // FULL_ROWS: a lane without four columns of its own stores the row's last four once more, so that no store depends on a branch and the
     // next strip's loads stay in flight as with WHOLE (2.4 M rows, fetched behind stores with a test per lane /
     // here: 25 -> 40 208 / 158 us, 64 -> 47 297 / 255, 40 -> 10 173 / 128; input gradients 190 / 151, 290 / 252, 164 / 135).
+    // Not where rows lie apart in more than half of the last-level cache: lines are written in part there, which bounds the kernel, and the last four columns cost one such write more (rows of
+    // 64 or 32 floats: 25 -> 40 245 / 272, 40 -> 10 214 / 238, 50 -> 33 324 / 345; but 1 M rows 40 -> 10 80 / 61).
+    constexpr int64_t PARTIAL_LINES = (int64_t)128 << 20;
     constexpr std::integral_constant<int, 0> REST;
     constexpr std::integral_constant<int, 1> FULL_ROWS;
     constexpr std::integral_constant<int, 2> WHOLE;
@@ -873,10 +878,10 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     if (a.Nout == NW) {
 #pragma unroll 1
         for (; strip < n_full; strip += step) strip_step(strip, ahead(strip), WHOLE);
-    } else if (AHEAD && a.Nout >= 4) {
+    } else if (AHEAD && a.Nout >= 4 && (a.ldo1 < a.Nout + 8 || a.n * a.ldo1 * 4 <= PARTIAL_LINES)) {
 #pragma unroll 1
         for (; strip < n_full; strip += step) strip_step(strip, ahead(strip), FULL_ROWS);
-    } else if (!AHEAD || NC == 1) { // (two tiles along the columns are never fewer than 33 columns)
+    } else {
 #pragma unroll 1
         for (; strip < n_full; strip += step) {
             strip_step(strip, 0, REST);
