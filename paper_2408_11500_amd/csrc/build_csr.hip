@@ -50,26 +50,34 @@ __device__ inline int32_t class_bound(const int32_t *__restrict__ colptr, int64_
     return (int32_t)lo;
 }
 
-// Kinds of rows (see common.h): whole rows make one item each, long ones are cut by column class.
-constexpr int ROW_TINY = -1, ROW_WAVE = 0, ROW_GROUP = 1, ROW_LONG = 2;
+// Kinds of rows (see common.h): whole rows make one item each, long ones (ranges of their length, the longest first) are cut by
+// column class, tiny ones are listed.
+constexpr int ROW_WAVE = 0, ROW_GROUP = 1, ROW_LONG = 2, ROW_TINY = ROW_LONG + LONG_BINS, ROW_KINDS = ROW_TINY + 1;
 __device__ inline int row_kind(int32_t d, int32_t item_max)
 {
-    return d <= TINY_ROW ? ROW_TINY : d <= item_max ? ROW_GROUP : d <= PART_ROW ? ROW_WAVE : ROW_LONG;
+    if (d <= TINY_ROW) return ROW_TINY;
+    if (d <= PART_ROW) return d <= item_max ? ROW_GROUP : ROW_WAVE;
+    int range = 0; // doublings of 2 * PART_ROW below d
+    if (item_max > ITEM_SHORT) {
+#pragma unroll
+        for (int b = 1; b < LONG_BINS; ++b) range += d > PART_ROW << b;
+    }
+    return ROW_LONG + LONG_BINS - 1 - range;
 }
 
 // Thread p handles the row at position p of the schedule (order[p], or p itself in natural order), so that the items
 // come out in schedule order.  FILL = false: rows of every kind per workgroup, counts[kind * n_groups + workgroup];
-// FILL = true, with the scan of those counts: the items of the whole rows (wavefront items, then lane-group items)
-// and the list of the long rows, whichever is asked for.
+// FILL = true, with the scan of those counts: the items of the whole rows (wavefront items, then lane-group items) and the list of the
+// tiny rows, and the list of the long rows, whichever is asked for.
 template <bool FILL>
 __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ order,
                                                          int64_t n, int32_t item_max, int32_t *__restrict__ counts, int64_t n_groups,
-                                                         Segment *__restrict__ items, int32_t *__restrict__ long_rows)
+                                                         Segment *__restrict__ items, TinyRow *__restrict__ tiny, int32_t *__restrict__ long_rows)
 {
-    __shared__ int32_t per_wave[4][3];
+    __shared__ int32_t per_wave[4][ROW_KINDS];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t p = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    int kind = ROW_TINY;
+    int kind = -1;
     int32_t row = 0, beg = 0, end = 0;
     if (p < n) {
         row = order ? order[p] : (int32_t)p;
@@ -79,22 +87,28 @@ __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restri
     }
     int32_t rank = 0;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < ROW_KINDS; ++k) {
         const unsigned long long bits = __ballot(kind == k);
         if (kind == k) rank = __popcll(bits & ((1ull << lane) - 1ull));
         if (lane == 0) per_wave[wave][k] = __popcll(bits);
     }
     __syncthreads();
     if (!FILL) {
-        if (threadIdx.x < 3)
+        if (threadIdx.x < ROW_KINDS)
             counts[threadIdx.x * n_groups + blockIdx.x] = per_wave[0][threadIdx.x] + per_wave[1][threadIdx.x] +
                                                           per_wave[2][threadIdx.x] + per_wave[3][threadIdx.x];
         return;
     }
-    if (kind == ROW_TINY) return;
+    if (kind < 0) return;
     for (int w = 0; w < wave; ++w) rank += per_wave[w][kind];
-    const int32_t at = counts[kind * n_groups + blockIdx.x] + rank; // the scan ran over the three kinds back to back
-    if (kind == ROW_LONG) {
+    const int32_t at = counts[kind * n_groups + blockIdx.x] + rank; // the scan ran over the kinds back to back
+    if (kind == ROW_TINY) {
+        const uint32_t more = end > beg ? (uint32_t)(end - beg - 1) : 0u;
+        TinyRow r;
+        r.row = (uint32_t)row | more << 31;
+        r.beg = (end > beg ? (uint32_t)beg : NO_ENTRIES) | more >> 1 << 31;
+        if (tiny) tiny[at - counts[ROW_TINY * n_groups]] = r;
+    } else if (kind >= ROW_LONG) {
         if (long_rows) long_rows[at - counts[ROW_LONG * n_groups]] = row;
     } else if (items) {
         Segment sg;
@@ -113,7 +127,7 @@ __global__ __launch_bounds__(SAMPLES + 64) void sched_summary_kernel(const int32
 {
     const int t = threadIdx.x;
     bool near = false, far = false;
-    if (t < 3) summary[t] = counts[(t + 1) * n_groups] - counts[t * n_groups];
+    if (t < ROW_KINDS) summary[t] = counts[(t + 1) * n_groups] - counts[t * n_groups];
     if (t <= N_CLASSES) {
         cb->first[t] = class_bound(colptr, n, t);
     } else if (t >= 64) {
@@ -127,7 +141,7 @@ __global__ __launch_bounds__(SAMPLES + 64) void sched_summary_kernel(const int32
         }
     }
     const int excess = __syncthreads_count(near) - __syncthreads_count(far);
-    if (t == 3) summary[t] = excess;
+    if (t == ROW_KINDS) summary[t] = excess;
 }
 
 // ---- long rows: cut by column class ------------------------------------------------------
@@ -274,7 +288,7 @@ int64_t candidates(int64_t n_edges, int64_t n, uint32_t flags) // entries the pa
 
 size_t sched_bytes(int64_t n, int64_t n_keys)
 {
-    const int64_t groups = 3 * (int64_t)blocks_for(n) + 1, n_long = n_keys / PART_ROW < n ? n_keys / PART_ROW : n;
+    const int64_t groups = ROW_KINDS * (int64_t)blocks_for(n) + 1, n_long = n_keys / PART_ROW < n ? n_keys / PART_ROW : n;
     const int64_t tables = N_TABLES * (n_long + 1);
     const size_t a = scan_bytes(groups), b = scan_bytes(tables);
     return 2 * Arena::rounded((size_t)groups * 4) + Arena::rounded((size_t)n_long * 4) + Arena::rounded((size_t)n_long * N_CLASSES * 4) + 2 * Arena::rounded((size_t)tables * 4) +
@@ -303,18 +317,21 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
     const int64_t n_groups = blocks_for(n);
     int32_t *counts = nullptr, *offs = nullptr;
     ClassBounds *cb = nullptr;
-    if (int rc = ws.take((size_t)(3 * n_groups + 1) * 4, &counts)) return rc;
-    if (int rc = ws.take((size_t)(3 * n_groups + 1) * 4, &offs)) return rc;
+    if (int rc = ws.take((size_t)(ROW_KINDS * n_groups + 1) * 4, &counts)) return rc;
+    if (int rc = ws.take((size_t)(ROW_KINDS * n_groups + 1) * 4, &offs)) return rc;
     if (int rc = ws.take(sizeof(ClassBounds), &cb)) return rc;
-    sched_rows_kernel<false><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, counts, n_groups, nullptr, nullptr);
+    sched_rows_kernel<false><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, counts, n_groups, nullptr, nullptr, nullptr);
     SG_LAUNCH_CHECK();
-    if (int rc = scan_i32(counts, offs, 3 * n_groups + 1, ws, stream)) return rc; // the last element is only written
+    if (int rc = scan_i32(counts, offs, ROW_KINDS * n_groups + 1, ws, stream)) return rc; // the last element is only written
     sched_summary_kernel<<<1, SAMPLES + 64, 0, stream>>>(offs, n_groups, colptr, n, m.rowptr, m.colidx, counters, cb);
     SG_LAUNCH_CHECK();
-    int32_t kinds[4];
-    if (int rc = read_counters(counters, kinds, 4, stream)) return rc;
-    out.local = kinds[3] > 0;
-    const int64_t n_group = kinds[ROW_GROUP], n_wave = kinds[ROW_WAVE], n_long = kinds[ROW_LONG];
+    int32_t kinds[ROW_KINDS + 1];
+    if (int rc = read_counters(counters, kinds, ROW_KINDS + 1, stream)) return rc;
+    out.local = kinds[ROW_KINDS] > 0;
+    const int64_t n_group = kinds[ROW_GROUP], n_wave = kinds[ROW_WAVE];
+    int64_t n_long = 0;
+    for (int b = 0; b < LONG_BINS; ++b) n_long += kinds[ROW_LONG + b];
+    out.tiny_cnt = kinds[ROW_TINY];
 
     int32_t *long_rows = nullptr, *class_beg = nullptr, *cnt = nullptr, *off = nullptr;
     int32_t starts[N_TABLES + 1] = {0};
@@ -324,7 +341,7 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
         if (int rc = ws.take((size_t)n_long * N_CLASSES * 4, &class_beg)) return rc;
         if (int rc = ws.take((size_t)(N_TABLES * stride) * 4, &cnt)) return rc;
         if (int rc = ws.take((size_t)(N_TABLES * stride) * 4, &off)) return rc;
-        sched_rows_kernel<true><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, offs, n_groups, nullptr, long_rows);
+        sched_rows_kernel<true><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, offs, n_groups, nullptr, nullptr, long_rows);
         SG_LAUNCH_CHECK();
         long_count_kernel<<<blocks_for(stride * N_CLASSES), TPB, 0, stream>>>(m.rowptr, m.colidx, long_rows, n_long, cb, item_max, class_beg, cnt);
         SG_LAUNCH_CHECK();
@@ -348,13 +365,14 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
     out.n_items = base + starts[T_SLOT];
     out.n_slots = starts[T_FIX] - starts[T_SLOT];
     out.n_fix = starts[N_TABLES] - starts[T_FIX];
-    const size_t item_bytes = Arena::rounded((size_t)out.n_items * sizeof(Segment));
+    const size_t item_bytes = Arena::rounded((size_t)out.n_items * sizeof(Segment)), fix_bytes = Arena::rounded((size_t)out.n_fix * sizeof(FixRow));
     char *block = nullptr;
-    if (int rc = keep.take(item_bytes + (size_t)out.n_fix * sizeof(FixRow), &block)) return rc;
+    if (int rc = keep.take(item_bytes + fix_bytes + (size_t)out.tiny_cnt * sizeof(TinyRow), &block)) return rc;
     out.items = reinterpret_cast<Segment *>(block);
     out.fix = reinterpret_cast<FixRow *>(block + item_bytes);
-    if (base > 0) {
-        sched_rows_kernel<true><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, offs, n_groups, out.items, nullptr);
+    out.tiny = reinterpret_cast<TinyRow *>(block + item_bytes + fix_bytes);
+    if (base > 0 || out.tiny_cnt > 0) {
+        sched_rows_kernel<true><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, offs, n_groups, out.items, out.tiny, nullptr);
         SG_LAUNCH_CHECK();
     }
     if (n_long > 0) {

@@ -55,7 +55,7 @@ __host__ __device__ inline bool aligned16(const void *p) { return (reinterpret_c
 
 // ---- aggregation schedule -------------------------------------------------------------
 // Rows are split by their number of stored entries d:
-//   d <= TINY_ROW            : handled whole, 64 consecutive rows per wavefront, in natural order;
+//   d <= TINY_ROW            : handled whole, up to 64 of them per wavefront, in schedule order;
 //   TINY_ROW < d <= item_max : one lane-group item (the whole row);
 //   d > item_max             : wavefront items of at most SEG_NNZ entries;
 //   d > PART_ROW             : the row is first cut by column class
@@ -72,12 +72,16 @@ __host__ __device__ inline bool aligned16(const void *p) { return (reinterpret_c
 // classes in fixed-size chunks, round-robin, and run behind the class's pieces.  A row with
 // several items gets one partial-sum slot per item (in a workspace the caller of the aggregation
 // provides) and is finished by a fix-up pass that adds the slots in order.
+// Where item_max is ITEM_LONG the long rows are taken in ranges of d, longest first (LONG_BINS, bounds doubling from 2 * PART_ROW on):
+// wavefronts that run at the same time have pieces of similar length, and no long piece starts when a launch is about to end (figures at
+// spmm.hip's wave_items_body).  A resident graph's wavefronts take several pieces of the list in turn, which should not all be long ones.
 constexpr int TINY_ROW = 4;
 constexpr int ITEM_SHORT = 32;
 constexpr int ITEM_LONG = 64;
 constexpr int PART_ROW = 256;
 constexpr int SEG_NNZ = 2048;
 constexpr int N_CLASSES = 8;   // column classes, one per XCD
+constexpr int LONG_BINS = 6;   // ranges of rows cut by column class
 constexpr int PASS_COLS = 128; // columns per pass of the aggregation (floats per partial-sum slot)
 
 struct Segment { // 16 bytes, read as one int4
@@ -94,10 +98,20 @@ struct FixRow { // a row whose items went to partial slots [slot_beg, slot_end)
     int32_t pad;
 };
 
+// A row of at most TINY_ROW entries in 8 bytes, read as one int2: the row and where its entries begin in 31 bits each, its entries less
+// one in the upper bits; a row without entries begins at NO_ENTRIES.
+struct TinyRow {
+    uint32_t row;
+    uint32_t beg;
+};
+constexpr uint32_t NO_ENTRIES = 0x7fffffffu;
+
 struct Schedule {
     int32_t item_max = ITEM_LONG; // longest lane-group item (whole row or class piece)
     Segment *items = nullptr; // per class its wavefront pieces, then its lane-group pieces; then the whole-row lists
     FixRow *fix = nullptr;
+    TinyRow *tiny = nullptr;  // rows of at most TINY_ROW entries, in schedule order
+    int32_t tiny_cnt = 0;
     int32_t big_off[N_CLASSES] = {0}, big_cnt[N_CLASSES] = {0};     // wavefront pieces of class c
     int32_t small_off[N_CLASSES] = {0}, small_cnt[N_CLASSES] = {0}; // lane-group pieces of class c
     int32_t wbig_off = 0, wbig_cnt = 0;     // wavefront items of rows kept whole

@@ -1,11 +1,12 @@
 // Slice aggregation Y = A^ X (+ Add): the neighbour sum of the SliceGCN layer equation.
 //
 // Work split (fixed per graph when it is built, see the schedule notes in common.h):
-//   * rows of at most TINY_ROW stored entries: 64 consecutive rows per wavefront (8-lane groups,
-//     narrow slices).  Lane i loads the row pointers and entries of row i; the gather phase
+//   * rows of at most TINY_ROW stored entries: up to 64 of them, in row order, per wavefront (8-lane groups,
+//     narrow slices).  Lane i loads the list's element and the entries of row i; the gather phase
 //     then hands row (t * GROUPS + grp) to lane group grp in sub-round t through cross-lane reads,
 //     so one wavefront keeps many independent row gathers in flight and the output stream stays
-//     contiguous;
+//     nearly contiguous (listed by their number of entries instead, so that no gather is of an absent one, 10 M nodes,
+//     32 columns: 422 -> 490 us, as the stores of a list lie apart);
 //   * lane-group items (whole rows of up to item_max entries, short class pieces of partitioned
 //     rows): one item per lane group, its (column, value) pairs read LPR at a time by the
 //     group's lanes and handed out by cross-lane reads;
@@ -41,23 +42,22 @@ namespace slicegcn {
 namespace {
 
 struct SpmmArgs {
-    const int32_t *rowptr;
     const int32_t *colidx;
     const float *vals;
     const Segment *items;
     const FixRow *fix;
-    const int32_t *order; // row at every position of the schedule (NULL: natural order), for the short rows
+    const TinyRow *tiny;  // the short rows, in schedule order
     const float *dinv;    // factored form only: X rows come pre-scaled by dinv[u], sums are scaled by dinv[row] on store
     float *scratch;
     int64_t scratch_stride; // floats of partial-sum slots per operand of the batch
     int64_t ldx, ldy, ldadd;
     uint32_t ldx_bytes;   // S32 kernels: byte stride of X rows (n * ldx * 4 < 2^32, n and ldx * 4 < 2^24)
-    int32_t n;
     int32_t item_max;     // longest lane-group item of the schedule (ITEM_SHORT or ITEM_LONG)
     int32_t ipw;          // wavefront items per wavefront (1 to 4 in the one-launch kernel, otherwise 1); a workgroup takes 4 * ipw
     int32_t rounds;       // lane-group items per lane group (1 to MAX_RUN in the one-launch kernel, otherwise 1)
     int32_t deal;         // log2 of the chunks of lane-group whole rows a class takes in turn
     int32_t tiny_rounds;  // short rows per lane group (2, 4, 6 or 8)
+    int32_t tiny_cnt;     // their number
     int32_t big_blocks;   // workgroups per class in the wavefront-item section
     int32_t small_blocks; // workgroups per class in the lane-group-item section
     int32_t slot_cols;    // floats per partial-sum slot
@@ -250,6 +250,7 @@ __device__ inline void gather_chunk(Acc<V> &acc, const SpmmArgs &a, const SpmmIo
             int c[U];
             float v[U];
             typename L::T x[U];
+            const int left = (cnt - t * G + G - 1) / G; // sub-steps
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int src = ((t + u) * G + grp) & 63;
@@ -257,7 +258,8 @@ __device__ inline void gather_chunk(Acc<V> &acc, const SpmmArgs &a, const SpmmIo
                 v[u] = shfl_val<FACT>(v_l, src);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], col);
+            for (int u = 0; u < U; ++u)
+                if (u < left) x[u] = load_x<V, S32>(a, io.X, c[u], col);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if ((t + u) * G + grp < cnt) acc.fma(v[u], x[u]);
@@ -367,10 +369,15 @@ __device__ inline void batch_units(const SpmmArgs &a, const SpmmIo &io, int beg_
 // entry base + i, and the next 64 are requested before the current ones are consumed.  (Giving a
 // wavefront several items and prefetching across them was measured and changes nothing: the
 // kernel is bound by the traffic of the gathers, not by the latency of its index loads.)
+// The XCDs' fabric serves 7.2 TB/s of 128-byte rows that miss the L2s, wherever they lie, and the L1s deliver 28 TB/s of rows that hit;
+// a loop over the same column indices in one list per class, without items, gathers 24.8 TB/s (233 k nodes, 106 M entries, 128 columns) and
+// 18.1 (2.4 M nodes, 94 M entries, 32 and 64 columns).  Long rows' pieces in ranges of length, no access without an entry and descriptors
+// through the scalar cache: this kernel 2.28 -> 2.19 ms (128 columns of the former graph), 745 -> 706 us and 1.48 -> 1.43 ms (of the latter).
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __device__ __forceinline__ void wave_items_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // told to be the same for a wavefront: its item's descriptor comes through the scalar cache
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int cls = block % N_CLASSES, j = block / N_CLASSES;
     const int piece_blocks = (a.big_cnt[cls] + 3) >> 2;
     int64_t item;
@@ -570,20 +577,22 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, const SpmmIo
     }
 }
 
-// Rows of at most TINY_ROW entries, up to 64 consecutive positions of the schedule per wavefront (consecutive
-// rows in natural order).
+// Rows of at most TINY_ROW entries, up to 64 consecutive ones of their list per wavefront.
 template <int LPR, int V, bool S32, bool FACT, bool RAG>
 __device__ __forceinline__ void tiny_rows_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
     const int units = a.tiny_rounds * (64 / LPR); // rows per wavefront
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int first = (block * 4 + wave) * units;
-    if (first >= a.n) return; // uniform per wavefront
+    const int64_t first = ((int64_t)block * 4 + wave) * units;
+    if (first >= a.tiny_cnt) return; // uniform per wavefront
     int beg_l = 0, end_l = 0, row_l = 0, dst_l = NO_UNIT;
-    if (lane < units && first + lane < a.n) {
-        const int row = a.order ? a.order[first + lane] : first + lane;
-        const int b = a.rowptr[row], e = a.rowptr[row + 1];
-        if (e - b <= TINY_ROW) { row_l = row; beg_l = b; end_l = e; dst_l = row; }
+    if (lane < units && first + lane < a.tiny_cnt) {
+        const TinyRow r = a.tiny[first + lane];
+        row_l = dst_l = (int)(r.row & NO_ENTRIES);
+        if (r.beg != NO_ENTRIES) {
+            beg_l = (int)(r.beg & NO_ENTRIES);
+            end_l = beg_l + 1 + (int)(r.row >> 31 | r.beg >> 31 << 1);
+        }
     }
     batch_units<LPR, V, S32, FACT, RAG>(a, io, beg_l, end_l, row_l, dst_l, lane);
 }
@@ -666,7 +675,7 @@ int launch_variant(const SpmmArgs &a, const SpmmBatch &b, int batch, int passes,
     const int64_t units_per_block = 4 * a.tiny_rounds * (64 / LPR);
     const int64_t g1 = (int64_t)N_CLASSES * a.big_blocks;
     const int64_t g2 = (int64_t)N_CLASSES * a.small_blocks;
-    const int64_t g3 = (a.n + units_per_block - 1) / units_per_block;
+    const int64_t g3 = (a.tiny_cnt + units_per_block - 1) / units_per_block;
     SG_REQUIRE(g1 + g2 + g3 + N_CLASSES <= INT32_MAX, SLICEGCN_ERANGE, "spmm: grid too large");
     if (a.item_max <= ITEM_SHORT) { // cache-resident graph: one launch (big_blocks counts runs of 4 * ipw items)
         // the grid's first dimension is a multiple of 8, so that a class meets the same XCD in every slice and pass
@@ -778,14 +787,13 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, 
         aligned = aligned && aligned16(o.X);
         any_add = any_add || o.Add;
     }
-    a.rowptr = m.rowptr; a.colidx = m.colidx; a.vals = m.vals; a.items = sc.items; a.fix = sc.fix; a.order = g->order;
+    a.colidx = m.colidx; a.vals = m.vals; a.items = sc.items; a.fix = sc.fix; a.tiny = sc.tiny;
     a.scratch = static_cast<float *>(ws);
     a.scratch_stride = (int64_t)(each / sizeof(float));
     a.dinv = prescaled ? g->dinv : nullptr;
     a.ldx = ldx; a.ldy = ldy; a.ldadd = ldadd;
     const bool s32 = g->n < (1 << 24) && ldx * 4 < (1 << 24) && (int64_t)g->n * ldx * 4 < ((int64_t)1 << 32);
     a.ldx_bytes = s32 ? (uint32_t)(ldx * 4) : 0u;
-    a.n = (int32_t)g->n;
     a.item_max = sc.item_max;
     const int64_t w4 = round_up(width, 4);
     a.slot_cols = (int32_t)(multi_pass || w4 < PASS_COLS ? w4 : PASS_COLS);
@@ -794,6 +802,7 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, 
     a.load_max = whole ? 0 : width - 4;
     a.wbig_off = sc.wbig_off; a.wbig_cnt = sc.wbig_cnt;
     a.wsmall_off = sc.wsmall_off; a.wsmall_cnt = sc.wsmall_cnt;
+    a.tiny_cnt = sc.tiny_cnt;
     for (int c = 0; c < N_CLASSES; ++c) {
         a.big_off[c] = sc.big_off[c]; a.big_cnt[c] = sc.big_cnt[c];
         a.small_off[c] = sc.small_off[c]; a.small_cnt[c] = sc.small_cnt[c];
@@ -817,7 +826,7 @@ int launch_spmm(const slicegcn_graph *g, const Csr &m, const SpmmOperands *ops, 
         };
         a.ipw = resident ? turns(sc.wbig_cnt, 4, 4) : 1;
         a.rounds = resident && sc.local ? turns(sc.wsmall_cnt, groups, MAX_RUN) : 1;
-        a.tiny_rounds = resident ? 2 * turns(g->n, 2 * groups, 4) : 8;
+        a.tiny_rounds = resident ? 2 * turns(sc.tiny_cnt, 2 * groups, 4) : 8;
         // workgroups per class: the class's own pieces, then its share of the whole-row chunks
         const int64_t ipb = 4 * a.ipw;
         const int64_t wbig_chunks = ((int64_t)sc.wbig_cnt + ipb - 1) / ipb;
