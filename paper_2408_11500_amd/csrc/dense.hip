@@ -69,7 +69,21 @@ __device__ inline float outer_bias(const PairArgs &a, int col) { return (a.bias2
 
 __device__ inline void scale4(float4 &v, float s) { v.x *= s; v.y *= s; v.z *= s; v.w *= s; }
 
+// base + count for a base that is the same for the wavefront and count < 2^30, by an access's own 32-bit offset
+template <class T> __device__ inline const T *plus(const T *base, uint32_t count)
+{
+    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + count * 4u);
+}
+
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+// The halves of `bits`, which is the same for the wavefront, into lanes lo and hi (constants) of v.  One instruction each; chosen per lane, with the lanes'
+// conditions in scalar registers, it is five and a branch.  (The instructions read a scalar register that a vector compare may have
+// just written: two wait states.)
+__device__ __forceinline__ void set_lanes(uint32_t &v, unsigned long long bits, int lo, int hi)
+{
+    asm("s_nop 1\n\tv_writelane_b32 %0, %1, %3\n\tv_writelane_b32 %0, %2, %4" : "+v"(v) : "s"((uint32_t)bits), "s"((uint32_t)(bits >> 32)), "n"(lo), "n"(hi));
+}
 
 // Four floats of row `row` starting at column k (k % 4 == 0), zero beyond column K.
 __device__ inline float4 load_k4(const float *__restrict__ base, int64_t ld, int64_t row, int k, int K, bool vec_ok)
@@ -455,7 +469,7 @@ __device__ __forceinline__ void pair_strip32(const PairArgs &a, uint32_t wg, uin
     constexpr bool PAIR = TWO && !BWD; // two operand strips
     __shared__ __attribute__((aligned(16))) float T1[4][32][ST];
     __shared__ __attribute__((aligned(16))) float T2[PAIR ? 4 : 1][32][ST];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int m = lane & 31, h = lane >> 5;
     const int lr = lane >> 3, lc = (lane & 7) * 4; // coalesced layout: row lr + 8 * it, columns lc..lc+3
     const LaneCols<> cols(lc, a.K);
@@ -479,22 +493,25 @@ __device__ __forceinline__ void pair_strip32(const PairArgs &a, uint32_t wg, uin
     // applied where the strip is consumed, so that the next strip's loads stay in flight behind the MFMAs).  One
     // load per lane and strip handed on by cross-lane reads was measured slower (the LDS pipe carries the tiles).
     float f2[PAIR ? 4 : 1], fo[BWD ? 1 : 4];
+    const uint32_t ld1 = (uint32_t)a.lda1, ld2 = (uint32_t)a.lda2;
     auto fetch = [&](int64_t strip, auto whole) {
-        const int64_t r0 = strip * 32, end = a.n - 1;
-        auto row = [&](int64_t r) { return whole || r < end ? r : end; }; // rows past the end re-read the last
+        const int64_t r0 = strip * 32;
+        const int end = whole ? 31 : (int)(a.n - 1 - r0);
+        auto row = [&](int i) { return (uint32_t)(whole || i < end ? i : end); }; // rows past the end re-read the last
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            const int64_t r = row(r0 + lr + 8 * it);
-            p1[it] = cols.load(a.A1 + r * a.lda1);
+            const int64_t r = r0 + (whole ? 8 * it : 0);
+            const uint32_t mine = row(whole ? lr : lr + 8 * it);
+            p1[it] = cols.load(plus(a.A1 + r * a.lda1, mine * ld1));
             if (PAIR) {
-                p2[it] = cols.load(a.A2 + r * a.lda2);
-                f2[it] = s2[r * s2_ld];
+                p2[it] = cols.load(plus(a.A2 + r * a.lda2, mine * ld2));
+                f2[it] = *plus(s2 + r * s2_ld, mine * (uint32_t)s2_ld);
             }
-            if (!BWD) fo[it] = so[r * so_ld];
+            if (!BWD) fo[it] = *plus(so + r * so_ld, mine * (uint32_t)so_ld);
         }
         if (BWD) {
-            pw = words[row(r0 + m) * word_ld];
-            ps = so[row(r0 + m) * so_ld];
+            pw = *plus(words + r0 * word_ld, row(m) * (uint32_t)word_ld);
+            ps = *plus(so + r0 * so_ld, row(m) * (uint32_t)so_ld);
         }
     };
     if (first < n_full) fetch(first, std::true_type());
@@ -568,22 +585,22 @@ __device__ __forceinline__ void pair_strip32(const PairArgs &a, uint32_t wg, uin
         const int64_t row0 = strip * 32;
         uint32_t my_word = 0u; // lane L < 32 collects the activation word of strip row L
         float o1[16], o2[16];
+        if constexpr (BWD) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            if (!BWD) {
-                const float p = acc1[r] + bias1;
-                const bool pos = p > 0.f && col_ok;
-                if (a.act == SLICEGCN_ACT_RELU) {
-                    const unsigned long long bal = __ballot(pos);
-                    if (lane < 32 && r == 4 * (lane >> 3) + (lane & 3))
-                        my_word = ((lane >> 2) & 1) ? (uint32_t)(bal >> 32) : (uint32_t)bal;
+            for (int r = 0; r < 16; ++r) { o1[r] = acc1[r]; o2[r] = acc2[r]; }
+        } else { // columns past the last have zero weights and biases: not active
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o1[r] = acc1[r] + bias1;
+            if (a.act == SLICEGCN_ACT_RELU) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const bool pos = o1[r] > 0.f;
+                    set_lanes(my_word, __ballot(pos), 8 * (r / 4) + r % 4, 8 * (r / 4) + 4 + r % 4);
+                    o1[r] = pos ? o1[r] : 0.f;
                 }
-                const float rl = (a.act == SLICEGCN_ACT_RELU) ? (p > 0.f ? p : 0.f) : p;
-                o1[r] = rl + (TWO ? acc2[r] + bias2 : 0.f);
-            } else {
-                o1[r] = acc1[r];
-                o2[r] = acc2[r];
             }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o1[r] += TWO ? acc2[r] + bias2 : 0.f;
         }
         // Outputs leave through the wavefront's tile so that a row goes out as eight 16-byte stores
         // (register r of lane (m, h) is strip row 8*(r/4) + 4*h + r%4, column m).
@@ -632,8 +649,16 @@ __global__ __launch_bounds__(256) void pair_strip32_kernel(const PairArgs common
 // Layers up to 64 wide (4 <= K <= 32 * KC, at most 32 * NC output columns) on many rows: a wavefront owns strips of 32 rows, reads a strip with
 // coalesced 16-byte loads, parks it in its own LDS tile and reads it back in the operand layout of the matrix instruction.  The weights
 // do not fit in registers next to the accumulators, so the workgroup keeps them (zero padded, already transposed for the backward
-// products) in LDS and every MFMA reads its B operand from there; the two operand strips of the forward pass go through the
-// wavefront's one tile in turn.  Compiled for two wavefronts per SIMD: one computes while the other moves its strip.
+// products) in LDS and every MFMA takes its B operand from there: four consecutive k of a column lie together, so that one 16-byte read
+// serves four instructions, and the reads of the next eight k are issued before the instructions of these.  (Left to itself the compiler
+// read the weights of two instructions right before them and waited for the LDS each time, and it moved the next strip's loads behind all
+// of the instructions; the barriers in `step` hold the order.)  The two operand strips of the forward pass go through the
+// wavefront's one tile in turn.  Compiled for two wavefronts per SIMD: one computes while the other moves its strip.  A strip's addresses are a
+// base that is the same for the wavefront and a 32-bit offset that is the same for every strip, and activation words are collected by lane writes
+// (set_lanes): 85 + 230 vector instructions per strip instead of 172 + 440.  2.4 M rows 64 -> 64 forward 459 -> 401 us, 25 -> 64 295 -> 250, input
+// gradients 404 -> 381; four slices of 169 k rows 145 -> 128, 93 -> 76, 131 -> 122.  Without their loads and stores the kernels take 106 us (input
+// gradients, four slices), without the matrix instructions 83, which is the rate of a copy.  Strips handed out by a counter per workgroup
+// instead of fixed shares: no gain, input gradients 381 -> 399.
 template <int KC, int NC, bool BWD, bool TWO>
 __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs common, const PairBatch batch)
 {
@@ -646,9 +671,9 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     constexpr int QN = 4 * KC;                  // float4 of the reduction axis per row
     constexpr bool PAIR = TWO && !BWD;          // two operand strips
     __shared__ __attribute__((aligned(16))) float Tl[4][32][ST];
-    __shared__ float W1s[KW][NW];
-    __shared__ float W2s[TWO ? KW : 1][NW];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ float4 W1s[KW / 4][NW];
+    __shared__ float4 W2s[TWO ? KW / 4 : 1][NW];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int m = lane & 31, h = lane >> 5;
     const int rk = lane / LK, rn = lane / LN, cn = (lane % LN) * 4; // coalesced layouts of an operand and of an output strip
     const LaneCols<> cols((lane % LK) * 4, a.K);
@@ -671,25 +696,32 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     uint32_t pw[KC];                // backward: activation words of strip row m
     float ps = 1.f;                 // and its row factor
     float f2[PAIR ? PK : 1], fo[PN]; // factors of the rows this lane loads and stores
+    const uint32_t ld1 = (uint32_t)a.lda1, ld2 = (uint32_t)a.lda2;
     auto fetch = [&](int64_t strip, auto whole) {
-        const int64_t r0 = strip * 32, end = a.n - 1;
-        auto row = [&](int64_t r) { return whole || r < end ? r : end; }; // rows past the end re-read the last
+        const int64_t r0 = strip * 32;
+        const int end = whole ? 31 : (int)(a.n - 1 - r0);
+        auto row = [&](int i) { return (uint32_t)(whole || i < end ? i : end); }; // rows past the end re-read the last
 #pragma unroll
         for (int it = 0; it < PK; ++it) {
-            const int64_t r = row(r0 + rk + RK * it);
-            p1[it] = cols.load(a.A1 + r * a.lda1);
+            const int64_t r = r0 + (whole ? RK * it : 0);
+            const uint32_t mine = row(whole ? rk : rk + RK * it);
+            p1[it] = cols.load(plus(a.A1 + r * a.lda1, mine * ld1));
             if (PAIR) {
-                p2[it] = cols.load(a.A2 + r * a.lda2);
-                f2[it] = s2[r * s2_ld];
+                p2[it] = cols.load(plus(a.A2 + r * a.lda2, mine * ld2));
+                f2[it] = *plus(s2 + r * s2_ld, mine * (uint32_t)s2_ld);
             }
         }
         if (BWD) {
+            const uint32_t mine = row(m);
 #pragma unroll
-            for (int w = 0; w < KC; ++w) pw[w] = words[row(r0 + m) * word_ld + (32 * w < a.K ? w : 0)];
-            ps = so[row(r0 + m) * so_ld];
+            for (int w = 0; w < KC; ++w) pw[w] = *plus(words + r0 * word_ld + (32 * w < a.K ? w : 0), mine * (uint32_t)word_ld);
+            ps = *plus(so + r0 * so_ld, mine * (uint32_t)so_ld);
         }
 #pragma unroll
-        for (int it = 0; it < PN; ++it) fo[it] = so[row(r0 + rn + RN * it) * so_ld];
+        for (int it = 0; it < PN; ++it) {
+            const int64_t r = r0 + (whole ? RN * it : 0);
+            fo[it] = *plus(so + r * so_ld, row(whole ? rn : rn + RN * it) * (uint32_t)so_ld);
+        }
     };
     if (first < n_full) fetch(first, std::true_type());
 
@@ -708,8 +740,8 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
     for (int i = 0; i < WN; ++i) {
         const int idx = threadIdx.x + 256 * i, kk = BWD ? idx % KW : idx / NW, j = BWD ? idx / KW : idx % NW;
         const bool there = kk < a.K && j < a.Nout;
-        W1s[kk][j] = there ? w1[i] : 0.f;
-        if (TWO) W2s[kk][j] = there ? w2[i] : 0.f;
+        reinterpret_cast<float *>(&W1s[kk / 4][j])[kk % 4] = there ? w1[i] : 0.f;
+        if (TWO) reinterpret_cast<float *>(&W2s[kk / 4][j])[kk % 4] = there ? w2[i] : 0.f;
     }
     float bias1[NC], bias2[NC];
 #pragma unroll
@@ -764,78 +796,60 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
         uint32_t word[KC];
 #pragma unroll
         for (int w = 0; w < KC; ++w) word[w] = !BWD ? 0u : !a.mask ? ~0u : pw[w];
+        __builtin_amdgcn_sched_barrier(0);
         if (ALL_ROWS) fetch(next, std::true_type()); // flies during the MFMAs and the stores below
         floatx16 acc1[NC], acc2[NC];
 #pragma unroll
         for (int t = 0; t < NC; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) { acc1[t][r] = 0.f; acc2[t][r] = 0.f; }
-        if (BWD) { // both products read dHout; the first one through the activation bits (dP = dHout * mask)
+        // Steps of eight k, those of the second product behind those of the first.  Backward both read dHout, the first one through the
+        // activation bits (dP = dHout * mask); forward a step's operand is replaced by the second strip's when it is done with.
+        constexpr int STEPS = TWO ? 2 * QN : QN;
+        float4 bw[2][NC];
+        auto weights = [&](int s) {
 #pragma unroll
-            for (int q = 0; q < QN; ++q)
+            for (int t = 0; t < NC; ++t) bw[s & 1][t] = s < QN ? W1s[2 * s + h][32 * t + m] : W2s[TWO ? 2 * (s - QN) + h : 0][32 * t + m];
+        };
+        weights(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int kk = 8 * q + 4 * h + i;
-                    const float g = pick(a1[q], i);
-                    const float gp = (((word[q >> 2] >> (8 * (q & 3) + 4 * h + i)) & 1u) ? g : 0.f) * in_f;
+        for (int s = 0; s < STEPS; ++s) { // step
+            const int q = s < QN ? s : s - QN;
+            if (s + 1 < STEPS) weights(s + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int t = 0; t < NC; ++t)
-                        acc1[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(gp, W1s[kk][32 * t + m], acc1[t], 0, 0, 0);
+            for (int i = 0; i < 4; ++i) {
+                float x = pick(a1[q], i);
+                if (BWD && s < QN) x = (((word[q >> 2] >> (8 * (q & 3) + 4 * h + i)) & 1u) ? x : 0.f) * in_f;
+#pragma unroll
+                for (int t = 0; t < NC; ++t) {
+                    if (s < QN) acc1[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, pick(bw[s & 1][t], i), acc1[t], 0, 0, 0);
+                    else acc2[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, pick(bw[s & 1][t], i), acc2[t], 0, 0, 0);
                 }
-            if (TWO) {
-#pragma unroll
-                for (int q = 0; q < QN; ++q)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int kk = 8 * q + 4 * h + i;
-#pragma unroll
-                        for (int t = 0; t < NC; ++t)
-                            acc2[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(pick(a1[q], i), W2s[kk][32 * t + m], acc2[t], 0, 0, 0);
-                    }
             }
-        } else {
-#pragma unroll
-            for (int q = 0; q < QN; ++q)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int kk = 8 * q + 4 * h + i;
-#pragma unroll
-                    for (int t = 0; t < NC; ++t)
-                        acc1[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(pick(a1[q], i), W1s[kk][32 * t + m], acc1[t], 0, 0, 0);
-                }
-            if (TWO) {
-#pragma unroll
-                for (int q = 0; q < QN; ++q) a1[q] = *reinterpret_cast<const float4 *>(&tl[m][8 * q + 4 * h]);
-#pragma unroll
-                for (int q = 0; q < QN; ++q)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int kk = 8 * q + 4 * h + i;
-#pragma unroll
-                        for (int t = 0; t < NC; ++t)
-                            acc2[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(pick(a1[q], i), W2s[kk][32 * t + m], acc2[t], 0, 0, 0);
-                    }
-            }
+            if (PAIR && s < QN) a1[q] = *reinterpret_cast<const float4 *>(&tl[m][8 * q + 4 * h]);
+            __builtin_amdgcn_sched_barrier(0);
         }
         const int64_t row0 = strip * 32;
         uint32_t my_word[NC]; // lane L < 32 collects the activation words of strip row L
-        if (!BWD) { // the forward result replaces the first accumulator
+        if (!BWD) { // the forward result replaces the first accumulator (columns past the last have zero weights and biases: not active)
 #pragma unroll
             for (int t = 0; t < NC; ++t) {
                 my_word[t] = 0u;
-                const bool col_ok = 32 * t + m < a.Nout;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float p = acc1[t][r] + bias1[t];
-                    const bool pos = p > 0.f && col_ok;
-                    if (a.act == SLICEGCN_ACT_RELU) {
+                for (int r = 0; r < 16; ++r) acc1[t][r] += bias1[t];
+                if (a.act == SLICEGCN_ACT_RELU) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const bool pos = acc1[t][r] > 0.f;
                         const unsigned long long bal = __ballot(pos);
-                        if (lane < 32 && r == 4 * (lane >> 3) + (lane & 3))
-                            my_word[t] = ((lane >> 2) & 1) ? (uint32_t)(bal >> 32) : (uint32_t)bal;
+                        set_lanes(my_word[t], bal, 8 * (r / 4) + r % 4, 8 * (r / 4) + 4 + r % 4);
+                        acc1[t][r] = pos ? acc1[t][r] : 0.f;
                     }
-                    const float rl = (a.act == SLICEGCN_ACT_RELU) ? (p > 0.f ? p : 0.f) : p;
-                    acc1[t][r] = rl + (TWO ? acc2[t][r] + bias2[t] : 0.f);
                 }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc1[t][r] += TWO ? acc2[t][r] + bias2[t] : 0.f;
             }
         }
         // Outputs leave through the wavefront's tile so that a row goes out as 16-byte stores
@@ -874,14 +888,13 @@ __global__ __launch_bounds__(256, 2) void pair_strip64_kernel(const PairArgs com
         }
     };
     int64_t strip = first;
-    auto ahead = [&](int64_t s) { return s + step < n_full ? s + step : s; };
-    if (a.Nout == NW) {
+    auto in_turn = [&](auto form) {
 #pragma unroll 1
-        for (; strip < n_full; strip += step) strip_step(strip, ahead(strip), WHOLE);
-    } else if (AHEAD && a.Nout >= 4 && (a.ldo1 < a.Nout + 8 || a.n * a.ldo1 * 4 <= PARTIAL_LINES)) {
-#pragma unroll 1
-        for (; strip < n_full; strip += step) strip_step(strip, ahead(strip), FULL_ROWS);
-    } else {
+        for (; strip < n_full; strip += step) strip_step(strip, strip + step < n_full ? strip + step : strip, form);
+    };
+    if (a.Nout == NW) in_turn(WHOLE);
+    else if (AHEAD && a.Nout >= 4 && (a.ldo1 < a.Nout + 8 || a.n * a.ldo1 * 4 <= PARTIAL_LINES)) in_turn(FULL_ROWS);
+    else {
 #pragma unroll 1
         for (; strip < n_full; strip += step) {
             strip_step(strip, 0, REST);
@@ -954,7 +967,8 @@ inline PairForm pair_form(const PairArgs *list, int batch)
     //     32   6.1 / 5.9                   10.9 / 9.5    20.8 / 19.5   25.9 / 25.8   5.4 / 4.1               13.5 / 12.2
     // (from there on strips: 2.4 M rows with self term, K = 8 165 / 181, K = 16 166 / 224, K = 32 189 / 198).
     const int64_t resident = 512 / batch; // as many workgroups as the chip holds at once: two per CU
-    if (a.K >= 4 && a.K <= 32 && a.Nout <= 32 && ((a.K > 8 && a.K < 32) || a.n * batch >= STRIP64_ROWS)) {
+    const bool near = a.lda1 < (1 << 24) && a.lda2 < (1 << 24) && a.mask_words < (1 << 24); // a strip's rows lie within 32-bit offsets
+    if (near && a.K >= 4 && a.K <= 32 && a.Nout <= 32 && ((a.K > 8 && a.K < 32) || a.n * batch >= STRIP64_ROWS)) {
         // Each stages the weights once, and a second strip is requested while the first is multiplied (K = 16 with self term, 2048 / 512
         // workgroups: 130 k rows 20.4 / 17.0 us, 169 k 26.0 / 21.3, 262 k 32.8 / 26.1, 800 k 73 / 66; input gradients 130 k 14.0 / 11.8, 262 k
         // 23.5 / 16.8).  More where the launch is long: 2.4 M rows of 8 columns out 217 / 240, input gradients of 12 columns 91 / 96, and
@@ -962,7 +976,7 @@ inline PairForm pair_form(const PairArgs *list, int batch)
         const int64_t most = strip_blocks * batch <= (two ? 8192 : 2048) ? resident : 2048;
         return PairForm{PairForm::STRIP32, two, strip_blocks < most ? strip_blocks : most, 0, 0};
     }
-    if (a.K >= 4 && a.K <= 64 && a.Nout <= 64 && a.n * batch >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
+    if (near && a.K >= 4 && a.K <= 64 && a.Nout <= 64 && a.n * batch >= STRIP64_ROWS) { // up to 64 wide: strips, weights in LDS
         // (each workgroup stages the weights once: four slices of 169 k rows with 2048 workgroups forward 164 us instead of 149, backward
         // 151 instead of 130)
         return PairForm{PairForm::STRIP64, two, strip_blocks < resident ? strip_blocks : resident, 0, 0};
