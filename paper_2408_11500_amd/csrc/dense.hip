@@ -70,9 +70,16 @@ __device__ inline float outer_bias(const PairArgs &a, int col) { return (a.bias2
 __device__ inline void scale4(float4 &v, float s) { v.x *= s; v.y *= s; v.z *= s; v.w *= s; }
 
 // base + count for a base that is the same for the wavefront and count < 2^30, by an access's own 32-bit offset
-template <class T> __device__ inline const T *plus(const T *base, uint32_t count)
+template <class T> __device__ __forceinline__ const T *plus(const T *base, uint32_t count)
 {
     return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + count * 4u);
+}
+// The same number, as far as the compiler knows a new one: an offset that does not change in a loop has its extension to 64 bits moved out of
+// it, and then every access adds it to its base per lane
+__device__ __forceinline__ uint32_t fresh(uint32_t v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -1104,12 +1111,14 @@ __device__ __forceinline__ void grad_rows_tile(const ReduceArgs &a, int64_t wg, 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const TilePlace place = tile_place(wg, n_tiles);
-    const int64_t block = place.row_tile, r_begin = block * a.rows_per_block;
+    // tile_place in 32 bits and scalar registers (the division is done by vector instructions)
+    const uint32_t group = (uint32_t)wg / (8u * n_tiles);
+    const int col_tile = __builtin_amdgcn_readfirstlane((uint32_t)wg / 8 - group * n_tiles);
+    const int64_t block = (uint32_t)__builtin_amdgcn_readfirstlane(group * 8 + (uint32_t)wg % 8), r_begin = block * a.rows_per_block;
     if (r_begin >= a.n) return; // uniform per workgroup
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
-    const int i_base = (place.col_tile / a.j_tiles) * (WI * MI * 32) + (SPLIT ? 0 : wave / (SPLIT ? 1 : WJ) * (MI * 32));
-    const int j_base = (place.col_tile % a.j_tiles) * ((SPLIT ? 1 : WJ) * NJ * 32) + (SPLIT ? 0 : wave % (SPLIT ? 1 : WJ) * (NJ * 32));
+    const int i_base = (col_tile / a.j_tiles) * (WI * MI * 32) + (SPLIT ? 0 : wave / (SPLIT ? 1 : WJ) * (MI * 32));
+    const int j_base = (col_tile % a.j_tiles) * ((SPLIT ? 1 : WJ) * NJ * 32) + (SPLIT ? 0 : wave % (SPLIT ? 1 : WJ) * (NJ * 32));
     if (!SPLIT && (i_base >= a.w_in || j_base >= a.w_out)) return; // uniform per wavefront; no barriers in this form
     const float *X = self ? a.Hin : a.Z;
     const int64_t ldx = self ? a.ldi : a.ldz;
@@ -1117,72 +1126,92 @@ __device__ __forceinline__ void grad_rows_tile(const ReduceArgs &a, int64_t wg, 
     const uint32_t *mask = self ? nullptr : a.mask;
     const bool sums = i_base == 0; // this workgroup (wavefront) also forms the column sums of its columns
 
-    // columns past the last one re-read the last: what they give is not stored
-    const float *px[MI], *pg[NJ]; // this lane's column of row h
-    const uint32_t *pw[NJ];
+    // This lane's columns of row h of a pair, as offsets from the pair's first row, which is the same for the wavefront.  Columns past the last one
+    // re-read the last: what they give is not stored
+    int cx[MI], cg[NJ], cw[NJ];
 #pragma unroll
-    for (int t = 0; t < MI; ++t) px[t] = X + h * ldx + (i_base + 32 * t + m < a.w_in ? i_base + 32 * t + m : a.w_in - 1);
+    for (int t = 0; t < MI; ++t) cx[t] = i_base + 32 * t + m < a.w_in ? i_base + 32 * t + m : a.w_in - 1;
 #pragma unroll
     for (int t = 0; t < NJ; ++t) {
-        pg[t] = a.dHout + h * a.ldo + (j_base + 32 * t + m < a.w_out ? j_base + 32 * t + m : a.w_out - 1);
-        pw[t] = mask + h * a.mask_words + ((j_base + 32 * t < a.w_out ? j_base + 32 * t : a.w_out - 1) >> 5);
+        cg[t] = j_base + 32 * t + m < a.w_out ? j_base + 32 * t + m : a.w_out - 1;
+        cw[t] = (j_base + 32 * t < a.w_out ? j_base + 32 * t : a.w_out - 1) >> 5;
     }
+    constexpr int64_t FAR = (int64_t)1 << 28; // a row's length in 32 bits of bytes
+    const bool near = ldx < FAR && a.ldo < FAR && (!mask || a.mask_words < FAR);
+    const uint32_t hx = (uint32_t)(h * ldx), hg = (uint32_t)(h * a.ldo), hw = mask ? (uint32_t)(h * a.mask_words) : 0u;
     float nx[PAIRS][MI], np[PAIRS][NJ], nf[PAIRS];
     uint32_t nw[PAIRS][NJ];
-#pragma unroll
-    for (int p = 0; p < PAIRS; ++p) {
-        nf[p] = 1.f;
-#pragma unroll
-        for (int t = 0; t < NJ; ++t) nw[p][t] = ~0u;
-    }
     auto row_of = [&](int64_t r0, int p) { return r0 + (SPLIT ? 32 * (p / 4) + 8 * wave + 2 * (p % 4) : 2 * p); }; // of pair p, and the next one
     auto fetch = [&](int64_t r0) {
-        int64_t at[PAIRS]; // rows past the end re-read the last (what they give is zeroed below): no load depends on a lane
-        if (r0 + ROWS <= r_end) {
+        if (near && r0 + ROWS <= r_end) {
+            int64_t at = r0;
+            asm("" : "+s"(at)); // (or the compiler keeps a 64-bit address per load and lane, steps them all, and spills)
+            const float *x = X + at * ldx, *g = a.dHout + at * a.ldo;
+            uint32_t ox[MI], og[NJ];
 #pragma unroll
-            for (int p = 0; p < PAIRS; ++p) at[p] = row_of(r0, p);
-        } else {
+            for (int t = 0; t < MI; ++t) ox[t] = fresh(hx + cx[t]);
 #pragma unroll
-            for (int p = 0; p < PAIRS; ++p) at[p] = row_of(r0, p) + h < r_end ? row_of(r0, p) : r_end - 1 - h;
-        }
+            for (int t = 0; t < NJ; ++t) og[t] = fresh(hg + cg[t]);
 #pragma unroll
-        for (int p = 0; p < PAIRS; ++p) {
+            for (int p = 0; p < PAIRS; ++p) {
+                const int64_t r = row_of(0, p);
 #pragma unroll
-            for (int t = 0; t < MI; ++t) nx[p][t] = px[t][at[p] * ldx];
+                for (int t = 0; t < MI; ++t) nx[p][t] = *plus(x + r * ldx, ox[t]);
 #pragma unroll
-            for (int t = 0; t < NJ; ++t) np[p][t] = pg[t][at[p] * a.ldo];
-        }
-        if (mask) {
+                for (int t = 0; t < NJ; ++t) np[p][t] = *plus(g + r * a.ldo, og[t]);
+            }
+            if (mask) {
 #pragma unroll
-            for (int p = 0; p < PAIRS; ++p)
+                for (int t = 0; t < NJ; ++t) {
+                    const uint32_t ow = fresh(hw + cw[t]);
 #pragma unroll
-                for (int t = 0; t < NJ; ++t) nw[p][t] = pw[t][at[p] * a.mask_words];
-        }
-        if (x_scale) {
+                    for (int p = 0; p < PAIRS; ++p) nw[p][t] = *plus(mask + row_of(at, p) * a.mask_words, ow);
+                }
+            }
+            if (x_scale) {
 #pragma unroll
-            for (int p = 0; p < PAIRS; ++p) nf[p] = x_scale[at[p] + h];
+                for (int p = 0; p < PAIRS; ++p) nf[p] = *plus(x_scale + row_of(at, p), h);
+            }
+        } else { // rows past the end re-read the last (what they give is zeroed below)
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) {
+                const int64_t at = row_of(r0, p) + h < r_end ? row_of(r0, p) + h : r_end - 1;
+#pragma unroll
+                for (int t = 0; t < MI; ++t) nx[p][t] = X[at * ldx + cx[t]];
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) np[p][t] = a.dHout[at * a.ldo + cg[t]];
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) nw[p][t] = mask ? mask[at * a.mask_words + cw[t]] : 0u;
+                nf[p] = x_scale ? x_scale[at] : 1.f;
+            }
         }
     };
 
     floatx16 acc[MI][NJ];
     float accb[NJ]; // lanes 0..31: column sums
 #pragma unroll
-    for (int tj = 0; tj < NJ; ++tj) {
-        accb[tj] = 0.f;
-#pragma unroll
-        for (int ti = 0; ti < MI; ++ti)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[ti][tj][r] = 0.f;
-    }
+    for (int t = 0; t < NJ; ++t) accb[t] = 0.f;
     fetch(r_begin);
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += ROWS) {
+    auto step = [&](int64_t r0) {
         float x[PAIRS][MI], g[PAIRS][NJ];
 #pragma unroll
         for (int p = 0; p < PAIRS; ++p) {
 #pragma unroll
-            for (int t = 0; t < MI; ++t) x[p][t] = x_scale ? nx[p][t] * nf[p] : nx[p][t];
+            for (int t = 0; t < MI; ++t) x[p][t] = nx[p][t];
 #pragma unroll
-            for (int t = 0; t < NJ; ++t) g[p][t] = (nw[p][t] >> m) & 1u ? np[p][t] : 0.f;
+            for (int t = 0; t < NJ; ++t) g[p][t] = np[p][t];
+        }
+        if (x_scale) {
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+                for (int t = 0; t < MI; ++t) x[p][t] *= nf[p];
+        }
+        if (mask) { // the lane's bit, extended to a word
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) g[p][t] = __int_as_float(__float_as_int(g[p][t]) & __builtin_amdgcn_sbfe((int)nw[p][t], m, 1));
         }
         if (r0 + ROWS > r_end) {
 #pragma unroll
@@ -1200,14 +1229,21 @@ __device__ __forceinline__ void grad_rows_tile(const ReduceArgs &a, int64_t wg, 
 #pragma unroll
             for (int ti = 0; ti < MI; ++ti)
 #pragma unroll
-                for (int tj = 0; tj < NJ; ++tj) acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[p][ti], g[p][tj], acc[ti][tj], 0, 0, 0);
+                for (int tj = 0; tj < NJ; ++tj)
+                    acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[p][ti], g[p][tj], acc[ti][tj], 0, 0, 0);
         if (sums) {
 #pragma unroll
             for (int p = 0; p < PAIRS; ++p)
 #pragma unroll
                 for (int t = 0; t < NJ; ++t) accb[t] = (accb[t] + g[p][t]) + __shfl_xor(g[p][t], 32, 64); // rows in order
         }
-    }
+    };
+#pragma unroll
+    for (int ti = 0; ti < MI; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < NJ; ++tj) acc[ti][tj] = floatx16(0.f);
+#pragma unroll 1
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += ROWS) step(r0);
 
     const int ww = a.w_in * a.w_out;
     float *out = a.partial + block * a.stride, *out_b = out + (a.compact ? ww : 2 * ww + (self ? a.w_out : 0));
