@@ -1574,7 +1574,7 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
     __shared__ __attribute__((aligned(16))) float Hs[4][SR][WI];
     __shared__ __attribute__((aligned(16))) float Gs[4][SR][WJ];
     __shared__ uint32_t Ms[4][SR][NJ];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int m = lane & 31, h = lane >> 5;
     const int ri = lane / LI, ci = (lane % LI) * 4; // coalesced layout of the w_in-wide operands
     const int rj = lane / LJ, cj = (lane % LJ) * 4; // and of dHout
@@ -1599,12 +1599,6 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
     uint32_t (*ms)[NJ] = Ms[wave];
 
     floatx16 accA[MI][NJ], accS[MI][NJ];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) { accA[i][j][r] = 0.f; accS[i][j][r] = 0.f; }
     float sum_p[NJ], sum_g[NJ]; // column 32 j + m of dP and of dHout over the node rows 2 s + h
 #pragma unroll
     for (int j = 0; j < NJ; ++j) { sum_p[j] = 0.f; sum_g[j] = 0.f; }
@@ -1612,24 +1606,29 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
     float4 pz[PI], ph[SELF ? PI : 1], pg[PJ];
     float hf[SELF ? PI : 1]; // factors of the rows of Hin this lane loads (scaled layout); applied on the way to LDS
     uint32_t pw;
+    // (32-bit offsets within a strip: as many rows as come here would not fit into memory if eight of them did not lie within 4 GB)
+    const uint32_t ldz = (uint32_t)a.ldz, ldi = (uint32_t)a.ldi, ldo = (uint32_t)a.ldo;
     auto fetch = [&](int64_t strip, auto whole) {
-        const int64_t r0 = strip * SR, end = a.n - 1;
-        auto row = [&](int64_t r) { return whole || r < end ? r : end; }; // rows past the end re-read the last
+        const int64_t r0 = strip * SR;
+        const int end = whole ? SR - 1 : (int)(a.n - 1 - r0);
+        auto row = [&](int i) { return (uint32_t)(whole || i < end ? i : end); }; // rows past the end re-read the last
+        constexpr int RI = 64 / LI, RJ = 64 / LJ;
 #pragma unroll
         for (int it = 0; it < PI; ++it) {
-            const int64_t r = row(r0 + ri + (64 / LI) * it);
-            pz[it] = ic.load(a.Z + r * a.ldz);
+            const int64_t r = r0 + (whole ? RI * it : 0);
+            const uint32_t mine = row(whole ? ri : ri + RI * it);
+            pz[it] = ic.load(plus(a.Z + r * a.ldz, mine * ldz));
             if (SELF) {
-                ph[it] = ic.load(a.Hin + r * a.ldi);
-                hf[it] = hs_f[r * hs_ld];
+                ph[it] = ic.load(plus(a.Hin + r * a.ldi, mine * ldi));
+                hf[it] = *plus(hs_f + r * hs_ld, mine * (uint32_t)hs_ld);
             }
         }
 #pragma unroll
-        for (int it = 0; it < PJ; ++it) pg[it] = oc.load(a.dHout + row(r0 + rj + (64 / LJ) * it) * a.ldo);
-        pw = words[row(r0 + lane / NJ % SR) * word_ld + (32 * word < a.w_out && word_ld ? word : 0)];
+        for (int it = 0; it < PJ; ++it) pg[it] = oc.load(plus(a.dHout + (r0 + (whole ? RJ * it : 0)) * a.ldo, row(whole ? rj : rj + RJ * it) * ldo));
+        pw = *plus(words + r0 * word_ld, row(lane / NJ % SR) * (uint32_t)word_ld + (32 * word < a.w_out && word_ld ? word : 0));
     };
-    auto strip_step = [&](int64_t strip, int64_t next, auto whole) {
-        constexpr bool WHOLE = decltype(whole)::value;
+    auto strip_step = [&](int64_t strip, int64_t next, auto whole, auto first) { // first: of the wavefront (the accumulators are the constant zero)
+        constexpr bool WHOLE = decltype(whole)::value, FIRST = decltype(first)::value;
 #pragma unroll
         for (int it = 0; it < PI; ++it) {
             if (place_i) {
@@ -1653,44 +1652,62 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
         if (lane < SR * NJ) ms[lane / NJ][word] = a.mask ? pw : ~0u;
         __builtin_amdgcn_wave_barrier();
         if (WHOLE) fetch(next, std::true_type());
+        // the operands of two node rows are read while the two before them are multiplied
+        float rg[2][NJ], rz[2][MI], rh[2][MI];
+        uint32_t rw[2][NJ];
+        auto read = [&](int s2) {
+            const int k = 2 * s2 + h, at = s2 & 1;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) { rg[at][j] = gs[k][32 * j + m]; rw[at][j] = ms[k][j]; }
+#pragma unroll
+            for (int i = 0; i < MI; ++i) { rz[at][i] = zs[k][32 * i + m]; rh[at][i] = SELF ? hs[k][32 * i + m] : 0.f; }
+        };
+        read(0);
 #pragma unroll
         for (int s2 = 0; s2 < SR / 2; ++s2) {
-            const int k = 2 * s2 + h;
-            float g[NJ], pp[NJ], z[MI], hh[MI];
+            if (s2 + 1 < SR / 2) read(s2 + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const int at = s2 & 1;
+            float pp[NJ];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                g[j] = gs[k][32 * j + m];
-                pp[j] = ((ms[k][j] >> m) & 1u) ? g[j] : 0.f;
+            for (int j = 0; j < NJ; ++j) { // the lane's bit of the word, extended to a word
+                const float g = rg[at][j];
+                pp[j] = __int_as_float(__float_as_int(g) & __builtin_amdgcn_sbfe((int)rw[at][j], m, 1));
                 if constexpr (BLOCKS) { // rows in order
                     sum_p[j] = (sum_p[j] + pp[j]) + __shfl_xor(pp[j], 32, 64);
-                    if (SELF) sum_g[j] = (sum_g[j] + g[j]) + __shfl_xor(g[j], 32, 64);
+                    if (SELF) sum_g[j] = (sum_g[j] + g) + __shfl_xor(g, 32, 64);
                 } else {
                     sum_p[j] += pp[j];
-                    sum_g[j] += g[j];
+                    sum_g[j] += g;
                 }
-            }
-#pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                z[i] = zs[k][32 * i + m];
-                hh[i] = SELF ? hs[k][32 * i + m] : 0.f;
             }
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    accA[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(z[i], pp[j], accA[i][j], 0, 0, 0);
-                    if (SELF) accS[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(hh[i], g[j], accS[i][j], 0, 0, 0);
+                    accA[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(rz[at][i], pp[j], FIRST && s2 == 0 ? floatx16(0.f) : accA[i][j], 0, 0, 0);
+                    if (SELF) accS[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(rh[at][i], rg[at][j], FIRST && s2 == 0 ? floatx16(0.f) : accS[i][j], 0, 0, 0);
                 }
         }
         __builtin_amdgcn_wave_barrier();
     };
     int64_t strip = w_id; // wavefront w takes strips w, w + hop, ...
-    if (strip < n_full) fetch(strip, std::true_type());
+    auto ahead = [&](int64_t s) { return s + hop < n_full ? s + hop : s; };
+    if (strip < n_full) {
+        fetch(strip, std::true_type());
+        strip_step(strip, ahead(strip), std::true_type(), std::true_type());
+        strip += hop;
+    } else {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) accA[i][j] = accS[i][j] = floatx16(0.f);
+    }
 #pragma unroll 1
-    for (; strip < n_full; strip += hop) strip_step(strip, strip + hop < n_full ? strip + hop : strip, std::true_type());
+    for (; strip < n_full; strip += hop) strip_step(strip, ahead(strip), std::true_type(), std::false_type());
     if (strip == n_full && strip < past) { // the rows left
         fetch(strip, std::false_type());
-        strip_step(strip, 0, std::false_type());
+        strip_step(strip, 0, std::false_type(), std::false_type());
     }
     if constexpr (BLOCKS) {
         const int tid = threadIdx.x, ww = a.w_in * a.w_out;
@@ -1762,15 +1779,18 @@ constexpr int GB_T = 128;
 __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
 {
     const ReduceArgs a = slice_of(common, batch, blockIdx.y);
-    const TilePlace place = tile_place(blockIdx.x, n_tiles);
+    // tile_place in 32 bits and scalar registers
+    const uint32_t group = blockIdx.x / (8u * n_tiles);
+    const int col_tile = __builtin_amdgcn_readfirstlane(blockIdx.x / 8 - group * n_tiles);
+    const int64_t block = (uint32_t)__builtin_amdgcn_readfirstlane(group * 8 + blockIdx.x % 8);
     __shared__ __attribute__((aligned(16))) float Xs[RED_RK][GB_T];
     __shared__ __attribute__((aligned(16))) float Ps[RED_RK][GB_T];
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    const int i_base = place.col_tile / common.j_tiles * GB_T, j_base = place.col_tile % common.j_tiles * GB_T;
+    const int i_base = col_tile / common.j_tiles * GB_T, j_base = col_tile % common.j_tiles * GB_T;
     const int wi = (wave >> 1) * 64, wj = (wave & 1) * 64;
-    const int64_t r_begin = place.row_tile * a.rows_per_block;
+    const int64_t r_begin = block * a.rows_per_block;
     if (r_begin >= a.n) return; // uniform per workgroup
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
     const bool bias_wave = i_base == 0 && (wave >> 1) == 0;
@@ -1779,7 +1799,8 @@ __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs 
     const LaneCols<> xc(i_base + c4, a.w_in), pc(j_base + c4, a.w_out);
     const bool place_x = i_base + GB_T > a.w_in, place_p = j_base + GB_T > a.w_out; // uniform
     const int j = j_base + c4 < a.w_out ? j_base + c4 : a.w_out - 1;
-    const uint32_t *words = a.mask ? a.mask + (j >> 5) : reinterpret_cast<const uint32_t *>(a.dHout); // none: read anything, use all ones
+    const uint32_t *words = a.mask ? a.mask : reinterpret_cast<const uint32_t *>(a.dHout); // none: read anything, use all ones
+    const int word = a.mask ? j >> 5 : 0;
     const int64_t word_ld = a.mask ? a.mask_words : 0;
 
     floatx16 acc[2][2];
@@ -1793,13 +1814,25 @@ __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs 
 
     float4 rx[4], rp[4];
     uint32_t rw[4];
+    const bool near = a.ldz < (1 << 24) && a.ldo < (1 << 24) && word_ld < (1 << 24); // a step's rows lie within 32-bit offsets
+    const uint32_t ox = (uint32_t)lr * (uint32_t)a.ldz, op = (uint32_t)lr * (uint32_t)a.ldo, ow = (uint32_t)lr * (uint32_t)word_ld;
     auto fetch = [&](int64_t r0, auto whole) {
+        if (whole && near) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int64_t r = r0 + lr + 8 * it, row = whole || r < r_end ? r : r_end - 1; // rows past the end re-read the last
-            rx[it] = xc.load(a.Z + row * a.ldz);
-            rp[it] = pc.load(a.dHout + row * a.ldo);
-            rw[it] = words[row * word_ld];
+            for (int it = 0; it < 4; ++it) {
+                const int64_t r = r0 + 8 * it;
+                rx[it] = xc.load(plus(a.Z + r * a.ldz, ox));
+                rp[it] = pc.load(plus(a.dHout + r * a.ldo, op));
+                rw[it] = *plus(words + r * word_ld, ow + word);
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int64_t r = r0 + lr + 8 * it, row = whole || r < r_end ? r : r_end - 1; // rows past the end re-read the last
+                rx[it] = xc.load(a.Z + row * a.ldz);
+                rp[it] = pc.load(a.dHout + row * a.ldo);
+                rw[it] = words[row * word_ld + word];
+            }
         }
     };
     // `next`: first row to fetch meanwhile.  The activation bits are applied on the way to LDS, not where they are fetched: the next
@@ -1810,26 +1843,31 @@ __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs 
             float4 x = rx[it], p = rp[it];
             if (place_x) xc.place(x);
             if (place_p) pc.place(p);
-            const uint32_t bits = a.mask ? rw[it] >> (j & 31) : ~0u;
-            p.x = bits & 1u ? p.x : 0.f;
-            p.y = bits & 2u ? p.y : 0.f;
-            p.z = bits & 4u ? p.z : 0.f;
-            p.w = bits & 8u ? p.w : 0.f;
+            if (a.mask) { // a bit of the word, extended to a word
+                auto masked = [&](float v, int c) { return __int_as_float(__float_as_int(v) & __builtin_amdgcn_sbfe((int)rw[it], (j & 31) + c, 1)); };
+                p = make_float4(masked(p.x, 0), masked(p.y, 1), masked(p.z, 2), masked(p.w, 3));
+            }
             if (!whole && r0 + lr + 8 * it >= r_end) x = p = make_float4(0.f, 0.f, 0.f, 0.f);
             *reinterpret_cast<float4 *>(&Xs[lr + 8 * it][c4]) = x;
             *reinterpret_cast<float4 *>(&Ps[lr + 8 * it][c4]) = p;
         }
         __syncthreads();
         if constexpr (decltype(more)::value) fetch(next, std::true_type());
+        float xs[2][2], ps[2][2]; // the operands of two node rows are read while the two before them are multiplied
+        auto read = [&](int kp) {
+            const int k = 2 * kp + h;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) { xs[kp & 1][t] = Xs[k][wi + 32 * t + m]; ps[kp & 1][t] = Ps[k][wj + 32 * t + m]; }
+        };
+        read(0);
 #pragma unroll
         for (int kp = 0; kp < RED_RK / 2; ++kp) {
-            const int k = 2 * kp + h;
-            const float a0 = Xs[k][wi + m], a1 = Xs[k][wi + 32 + m];
-            const float b0 = Ps[k][wj + m], b1 = Ps[k][wj + 32 + m];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+            if (kp + 1 < RED_RK / 2) read(kp + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < 2; ++tj) acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[kp & 1][ti], ps[kp & 1][tj], acc[ti][tj], 0, 0, 0);
         }
         if (bias_wave) {
 #pragma unroll
@@ -1846,7 +1884,7 @@ __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs 
         step(r0, 0, std::false_type(), std::false_type());
     }
 
-    float *out = a.partial + place.row_tile * a.stride;
+    float *out = a.partial + block * a.stride;
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
