@@ -426,6 +426,216 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
     pair_rows_tile<NT, TWO, BWD>(slice_of(common, batch), blockIdx.x + first, n_col_tiles);
 }
 
+// The single products of wide layers on many rows.  What bounded pair_rows_kernel there was waiting: fp32 matrix instructions take the vector
+// pipe, so nothing but other matrix instructions fills a wait, and a workgroup asked for its next 32 steps of rows and weights when the
+// current ones began, 0.9 us ahead.  Here a workgroup stays for the whole launch, one per CU and of eight wavefronts, with all of its columns'
+// weights in LDS (up to 128 KB; no barrier behind the first), and a wavefront keeps the next R chunks of its rows in flight
+// across the ends of its strips of 32 rows.  No memory access of the loop depends on a branch that another path does not match, so that the
+// compiler's waits are for the chunk in turn: past the last row the last one is read and stored again, a product's chunks are padded to
+// a multiple of R by reading the last one again (no instruction is issued for these).  The column tiles of a strip are worked on at about the same time on the
+// same XCD.  The order of the sums is that of pair_rows_kernel: the same bits.
+// Bound by the matrix instructions and, under their load, by a clock of about 2.2 GHz (143 TFLOP/s): 1 M rows 256 -> 256 are 81 % of its cycles, other
+// vector instructions 6 %.  rows / wide, forward and input gradients with a mask: 2.4 M rows 256 -> 256 3.09 / 2.73 and 3.17 / 2.69 ms, 256 -> 47
+// 846 / 750 and 1087 / 785 us, 800 k 200 -> 200 844 / 725 and 876 / 711, 66 k 512 -> 512 336 / 290 and 327 / 298, 169 k 40 -> 256 67.6 / 57.4.
+constexpr int WIDE_WAVES = 8, WIDE_WEIGHTS = 32768; // wavefronts of a workgroup; floats of its weights
+inline constexpr int wide_k(int nt) { return WIDE_WEIGHTS / (32 * nt) / 8 * 8; } // longest product of a workgroup with nt tiles of columns
+template <int NT, int R, bool RAGGED, bool BWD> // RAGGED: K is no multiple of 32
+__global__ __launch_bounds__(64 * WIDE_WAVES, 2) void pair_wide_kernel(const PairArgs common, const PairBatch batch, int n_tiles, int walkers)
+{
+    constexpr int BN = NT * 32, KC = 32, TS = 36;
+    __shared__ floatx4 Bs[wide_k(NT) / 4][BN]; // units of four k of a column
+    __shared__ __attribute__((aligned(16))) float tiles[WIDE_WAVES][16][TS];
+    __shared__ __attribute__((aligned(16))) float bias_s[BN];
+    const PairArgs a = slice_of(common, batch);
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroup b runs on XCD b mod 8: the column tiles of a walker are neighbours there
+    const int slot = blockIdx.x / 8, tile = slot % n_tiles, walker = slot / n_tiles * 8 + blockIdx.x % 8;
+    const int col0 = tile * BN, K = a.K;
+    const int chunks = (K + KC - 1) / KC, padded = (chunks + R - 1) / R * R;
+    const int64_t n = a.n, strips = (n + 31) / 32, stride = (int64_t)walkers * WIDE_WAVES;
+    const int64_t first = (int64_t)wave * walkers + walker; // a last, partial turn goes to the first wavefronts of many workgroups
+    const bool masked = BWD && a.mask != nullptr;
+    const uint32_t lda = (uint32_t)a.lda1, ldm = BWD && !masked ? 0 : (uint32_t)a.mask_words;
+    const uint32_t *words = masked ? a.mask : reinterpret_cast<const uint32_t *>(a.A1);
+
+    // chunk c of strip s; a lane loads the k of its row that it feeds to the matrix cores: 8 q + 4 h + i
+    floatx4 ring[R][KC / 8];
+    uint32_t ring_word[R];
+    auto load = [&](floatx4 (&x)[KC / 8], uint32_t &word, int64_t s, int c) {
+        if (c >= chunks) c = chunks - 1;
+        const int64_t row0 = s * 32;
+        uint32_t r = m;
+        if (row0 + 32 > n) r = (uint32_t)min((int64_t)m, n - 1 - row0); // uniform
+        const float *p = a.A1 + row0 * (int64_t)lda;
+        const uint32_t off = r * lda + c * KC + 4 * h;
+#pragma unroll
+        for (int q = 0; q < KC / 8; ++q) { // nothing behind the row is read: moved into place where it is used
+            const int over = RAGGED ? max(c * KC + 8 * q + 4 * h + 4 - K, 0) : 0;
+            x[q] = *reinterpret_cast<const floatx4_u *>(plus(p, off + 8 * q - over));
+        }
+        if (BWD) word = *plus(words + row0 * (int64_t)ldm, masked ? r * ldm + c : 0u);
+    };
+    if (first < strips) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) load(ring[j], ring_word[j], first, j);
+    }
+
+    // Units of four k of a column; zero past K.  Consecutive threads walk the contiguous axis of W (columns forward, groups of four k backward),
+    // and eight units of a thread are requested before the first is stored.
+    const int groups = (K + 7) / 8 * 2, units = (groups + 7) / 8 * 8 * BN;
+    for (int u0 = tid; u0 < units; u0 += 8 * 64 * WIDE_WAVES) {
+        floatx4 w[8];
+        auto group_of = [&](int u) { return BWD ? (u & 7) + u / (8 * BN) * 8 : u / BN; };
+        auto column_of = [&](int u) { return BWD ? (u >> 3) % BN : u % BN; };
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int u = u0 + 64 * WIDE_WAVES * j, k = 4 * group_of(u), col = min(col0 + column_of(u), a.Nout - 1);
+            const int64_t step = BWD ? 1 : a.ldw;
+            const float *p = a.B1 + (BWD ? (int64_t)col * a.ldw : col);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float v = p[min(k + i, K - 1) * step];
+                w[j][i] = k + i < K ? v : 0.f;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int u = u0 + 64 * WIDE_WAVES * j;
+            if (group_of(u) < groups) Bs[group_of(u)][column_of(u)] = w[j];
+        }
+    }
+    if (!BWD && tid < BN) bias_s[tid] = inner_bias<false>(a, col0 + tid < a.Nout ? col0 + tid : a.Nout - 1);
+    __syncthreads();
+
+    float (*out)[TS] = tiles[wave];
+    const int lr = lane >> 3, lc = (lane & 7) * 4;
+    const floatx4 *w_first = &Bs[h][m];
+    floatx4 w[2][NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) w[0][t] = w_first[32 * t];
+    for (int64_t s = first; s < strips; s += stride) {
+        const int64_t next = s + stride < strips ? s + stride : s;
+        floatx16 acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+        for (int c0 = 0; c0 < padded; c0 += R) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int c = c0 + j, left = K - c * KC; // steps from this chunk on
+                if (left > 0) { // uniform; no access to memory in here
+                    floatx4 (&x)[KC / 8] = ring[j];
+                    if (RAGGED && left < KC) {
+#pragma unroll
+                        for (int q = 0; q < KC / 8; ++q) {
+                            const int over = 8 * q + 4 * h + 4 - left; // columns the load was moved back by
+                            const bool one = over & 1, two = over & 2, none = over >= 4, any = over > 0;
+                            const float y0 = one ? x[q][1] : x[q][0], y1 = one ? x[q][2] : x[q][1], y2 = one ? x[q][3] : x[q][2], y3 = one ? 0.f : x[q][3];
+                            const floatx4 z = {two ? y2 : y0, two ? y3 : y1, two ? 0.f : y2, two ? 0.f : y3};
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) x[q][i] = none ? 0.f : any ? z[i] : x[q][i];
+                        }
+                    }
+                    if (masked) {
+                        const int word = (int)(ring_word[j] >> (4 * h));
+#pragma unroll
+                        for (int q = 0; q < KC / 8; ++q)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) // a bit extended to a word
+                                x[q][i] = __int_as_float(__float_as_int(x[q][i]) & __builtin_amdgcn_sbfe(word, 8 * q + i, 1));
+                    }
+                    const floatx4 *w_at = w_first + c * (KC / 4) * BN;
+#pragma unroll
+                    for (int q = 0; q < KC / 8; ++q) { // the weights of four steps are read while the four before them are multiplied
+                        if (RAGGED && q > 0 && 8 * q >= left) break; // uniform: both operands are zero from here on
+                        const floatx4 *w_next = q + 1 < KC / 8 || left > KC ? w_at + 2 * (q + 1) * BN : w_first;
+                        if (!RAGGED || q + 1 < KC / 8 || left >= KC) {
+#pragma unroll
+                            for (int t = 0; t < NT; ++t) w[(q + 1) & 1][t] = w_next[32 * t];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+#pragma unroll
+                            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[q & 1][t][i], x[q][i], acc[t], 0, 0, 0);
+                    }
+                    if (RAGGED && left < KC) { // the next strip's first
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) w[0][t] = w_first[32 * t];
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                const bool over = c + R >= padded; // uniform
+                load(ring[j], ring_word[j], over ? next : s, over ? c + R - padded : c + R);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+
+        const int64_t row0 = s * 32;
+        const bool full = row0 + 32 <= n; // uniform
+        const int most = full ? 31 : (int)(n - 1 - row0); // last row of the strip
+        const bool relu = !BWD && a.act == SLICEGCN_ACT_RELU;
+        uint32_t bits[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int left = a.Nout - col0 - 32 * t;
+            if (!BWD) { // bias, activation and its bits; register r of lane (m, h): column 8 * (r / 4) + 4 * h + r % 4
+                float4 bias[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) bias[q] = *reinterpret_cast<const float4 *>(&bias_s[32 * t + 8 * q + 4 * h]);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[t][r] += pick(bias[r / 4], r % 4);
+                if (relu) { // uniform
+                    uint32_t b = 0u;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const bool on = acc[t][r] > 0.f;
+                        b |= (uint32_t)on << (8 * (r / 4) + r % 4);
+                        acc[t][r] = on ? acc[t][r] : 0.f;
+                    }
+                    b <<= 4 * h;
+                    b |= __shfl_xor(b, 32, 64);
+                    if (left < 32) b &= left > 0 ? (1u << left) - 1u : 0u;
+                    bits[t] = b;
+                }
+            }
+            if (left <= 0) break; // uniform
+            // through LDS, half of the rows at a time, so that a row of a tile goes out as eight 16-byte stores of one instruction; in a tile
+            // that is not full the lanes at a row's end store its last four columns again
+            const int back = left < 32 && lc > left - 4 ? lc - (left - 4) : 0;
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                if ((m >> 4) == half) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const floatx4 v = {acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+                        *reinterpret_cast<floatx4 *>(&out[m & 15][8 * q + 4 * h]) = v;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    const int r = 16 * half + 8 * it + lr;
+                    floatx4 v;
+                    if (left >= 32) v = *reinterpret_cast<const floatx4 *>(&out[8 * it + lr][lc]); // uniform
+                    else v = *reinterpret_cast<const floatx4_u *>(&out[8 * it + lr][lc - back]);
+                    float *o = a.O1 + row0 * a.ldo1 + col0 + 32 * t;
+                    *reinterpret_cast<floatx4_u *>(o + (int)((uint32_t)min(r, most) * (uint32_t)a.ldo1) + lc - back) = v;
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        if (relu) {
+            uint32_t *word = a.mask + row0 * (int64_t)ldm + (col0 >> 5) + (uint32_t)min(m, most) * ldm;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                if (a.Nout - col0 - 32 * t > 0) word[t] = bits[t]; // both halves of the wavefront the same
+        }
+    }
+}
+
 // Four consecutive floats of an operand row as a strip kernel's lane loads them.  The lane that owns columns [c, c + 4) loads
 // from column min(c, K - 4) on, so that nothing outside the row's K columns is read and no load depends on a branch: a loop of such loads
 // and of unconditional stores has wait counts the compiler knows, and the next strip's loads and the last one's stores stay in flight (with
@@ -952,12 +1162,12 @@ int check_in_place(const PairArgs *list, int batch)
 
 // Which kernel forms the products, with how many workgroups per slice
 struct PairForm {
-    enum Kernel { STRIP32, STRIP64, ROWS } kernel;
+    enum Kernel { STRIP32, STRIP64, WIDE, ROWS } kernel;
     bool two;
     int64_t blocks;
-    int nt, n_col; // ROWS: tiles of 32 columns a workgroup takes, workgroups along the columns
+    int nt, n_col; // ROWS, WIDE: tiles of 32 columns a workgroup takes, workgroups along the columns
 };
-inline PairForm pair_form(const PairArgs *list, int batch)
+inline PairForm pair_form(const PairArgs *list, int batch, bool wide = true) // wide: also pair_wide_kernel
 {
     const PairArgs &a = list[0];
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
@@ -988,13 +1198,26 @@ inline PairForm pair_form(const PairArgs *list, int batch)
         // 151 instead of 130)
         return PairForm{PairForm::STRIP64, two, strip_blocks < resident ? strip_blocks : resident, 0, 0};
     }
+    const int tiles = (a.Nout + 31) / 32;
+    // Wide single products: a workgroup per CU that holds its columns' weights, from eight strips of rows a SIMD on (below, staging the weights and
+    // an uneven last turn cost more than the deeper reads give: rows / wide, 66 k rows 128 -> 128, two strips, 31.3 / 37.7 us; 100 k rows 100 -> 96,
+    // three, 31.5 / 34.0; 66 k 256 -> 256, four, 98.4 / 93.7, its input gradients 93.6 / 96.8; 169 k 128 -> 128, five, 67.5 / 66.6 and 64.7 / 67.7; above,
+    // 300 k 47 <- 131, nine, 76.4 / 74.2; 169 k 256 -> 256, ten, 221 / 196 and 218 / 197; 400 k 37 -> 70, twelve, 65.5 / 51.0).
+    if (wide && near && !two && a.K >= 4 && tiles >= 2 && tiles <= 128 && (a.Nout % 32 == 0 || a.Nout % 32 >= 4) && a.ldo1 < (1 << 24) && !a.scale_o1 &&
+        !in_place(list, batch)) {
+        // as few tiles of padding as can be, then as many per workgroup as can be
+        int nt = 2;
+        for (int t = 3; t <= 4; ++t)
+            if ((tiles + t - 1) / t * t <= (tiles + nt - 1) / nt * nt && a.K <= wide_k(t)) nt = t;
+        const int n_col = (tiles + nt - 1) / nt, per = 32 / (n_col * batch) > 0 ? 32 / (n_col * batch) : 1; // walkers per XCD
+        if (a.K <= wide_k(nt) && strips * n_col * batch >= 8 * 1024) return PairForm{PairForm::WIDE, false, 8 * (int64_t)per * n_col, nt, n_col};
+    }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
     // Tiles of 32 columns a workgroup takes: two keep three or four workgroups on a CU, where four (two workgroups) take 244 us instead
     // of 238 for 169 k rows 256 -> 256 and 158 instead of 130 for 20 k rows 512 -> 512; three for widths of three tiles, which two would
     // pad to four; one where that would leave fewer than eight workgroups per CU (20 k rows 256 -> 256: 38 us instead of 41,
     // 169 k rows 256 -> 40: 67 instead of 75; 169 k rows 256 -> 256, above the line: 253 instead of 238).
-    const int tiles = (a.Nout + 31) / 32;
     int nt = tiles % 2 != 0 && tiles % 3 == 0 ? 3 : tiles < 2 ? 1 : 2;
     if (row_tiles * ((tiles + nt - 1) / nt) * batch < 2048) nt = 1;
     if (tiles > nt && in_place(list, batch)) nt = tiles; // whole rows
@@ -1009,6 +1232,18 @@ inline PairBatch pair_batch(const PairArgs *list, int batch)
         b.p[i] = PairPtrs{x.A1, x.A2, x.B1, x.B2, x.bias1, x.bias2, x.enc, x.O1, x.O2, x.mask};
     }
     return b;
+}
+
+template <int NT, bool BWD>
+void launch_wide(const PairArgs &a, const PairBatch &b, dim3 grid, int n_col, hipStream_t stream)
+{
+    const int walkers = (int)grid.x / n_col;
+    const auto launch = [&](auto r) {
+        if (a.K % 32 == 0) pair_wide_kernel<NT, r.value, false, BWD><<<grid, 64 * WIDE_WAVES, 0, stream>>>(a, b, n_col, walkers);
+        else pair_wide_kernel<NT, r.value, true, BWD><<<grid, 64 * WIDE_WAVES, 0, stream>>>(a, b, n_col, walkers);
+    };
+    if (a.K <= 64) launch(std::integral_constant<int, 2>());
+    else launch(std::integral_constant<int, 4>());
 }
 
 // `list`: one entry per slice model of the batch (1 to BATCH, equal but for the pointers)
@@ -1031,6 +1266,11 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
         if (a.K <= 32) launch_strip64<1, 2, BWD>(a, b, grid, stream);
         else if (a.Nout <= 32) launch_strip64<2, 1, BWD>(a, b, grid, stream);
         else launch_strip64<2, 2, BWD>(a, b, grid, stream);
+        break;
+    case PairForm::WIDE:
+        if (f.nt == 2) launch_wide<2, BWD>(a, b, grid, n_col, stream);
+        else if (f.nt == 3) launch_wide<3, BWD>(a, b, grid, n_col, stream);
+        else launch_wide<4, BWD>(a, b, grid, n_col, stream);
         break;
     case PairForm::ROWS:
         return launch_parts(f.blocks, [&](unsigned first, unsigned count) { // one to three columns in: any number of rows comes here
@@ -2180,7 +2420,7 @@ int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, 
     *pair_done = false;
     if (!list) return launch_grad_rows(r, b, batch, products, big, stream);
     const GradForm g = grad_form(r, batch, products, big, r.rows_per_block == RED_ROWS);
-    const PairForm f = pair_form(list, batch);
+    const PairForm f = pair_form(list, batch, false);
     bool merge = g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 &&
                  (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && (f.nt == 1 || (f.nt == 2 && g.wj != 0)))) &&
                  products * g.blocks + 2 * f.blocks <= MAX_GRID;

@@ -1,0 +1,58 @@
+"""Single products of wide layers on many rows (pair_wide_kernel): bit for bit what the same rows give a few at a time, which
+takes the general kernel, and within an fp32 sum's bound of fp64."""
+import pytest
+import torch
+
+from paper_2408_11500_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+# rows, columns in, columns out: odd and whole chunks of k, one to many of them, full and partial tiles of columns and strips of rows
+SIZES = [(262_144, 256, 64), (131_073, 4, 160), (87_390, 47, 288), (262_177, 64, 36), (131_101, 65, 256), (65_536, 301, 253), (262_145, 511, 63),
+         (87_401, 33, 269), (131_100, 100, 229)]
+FEW = 4096
+
+
+def _in_pieces(n, f):
+    for a in range(0, n, FEW):
+        f(slice(a, min(n, a + FEW)))
+
+
+@pytest.mark.parametrize("n,w_in,w_out", SIZES)
+def test_wide_products_same_bits_as_few_rows(n, w_in, w_out):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    X, W, b, pad = rand(n, w_in + 3)[:, :w_in], rand(w_in, w_out), rand(w_out), 5
+    words = (w_out + 31) // 32
+    for act in (B.ACT_RELU, B.ACT_NONE):
+        Y, Y2 = (torch.full((n, w_out + pad), 7.0, device="cuda") for _ in range(2))
+        M, M2 = (torch.full((n, words + 1), -3, dtype=torch.int32, device="cuda") for _ in range(2))
+        B.slicegcn_linear_fwd(X, W, b, Y[:, :w_out], M[:, :words], act=act)
+        _in_pieces(n, lambda r: B.slicegcn_linear_fwd(X[r], W, b, Y2[r, :w_out], M2[r, :words], act=act))
+        assert torch.equal(Y, Y2) and torch.equal(M, M2)  # the padding too
+    some = torch.cat([torch.arange(40), torch.arange(n - 40, n)]).cuda()
+    want, size = X[some].double() @ W.double() + b.double(), X[some].double().abs() @ W.double().abs() + b.double().abs()
+    assert bool(((Y[some, :w_out].double() - want).abs() <= (w_in + 2) * 2.0 ** -24 * size).all())
+
+    dY = rand(n, w_out)
+    mask = torch.randint(-2 ** 31, 2 ** 31 - 1, (n, words), generator=gen, device="cuda", dtype=torch.int32)
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+    for m, act in ((mask, B.ACT_RELU), (None, B.ACT_NONE)):
+        D, D2 = (torch.full((n, w_in + pad), 7.0, device="cuda") for _ in range(2))
+        B.slicegcn_linear_bwd(X, W, m, dY, D[:, :w_in], None, None, ws, act=act)
+        _in_pieces(n, lambda r: B.slicegcn_linear_bwd(X[r], W, None if m is None else m[r], dY[r], D2[r, :w_in], None, None, ws, act=act))
+        assert torch.equal(D, D2)
+
+
+def test_wide_product_keeps_rows_with_infinities_apart():
+    n = 131_072
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    X, W = torch.randn((n, 96), generator=gen, device="cuda"), torch.randn((96, 256), generator=gen, device="cuda")
+    b, Y = torch.zeros(256, device="cuda"), torch.empty((n, 256), device="cuda")
+    B.slicegcn_linear_fwd(X, W, b, Y, None)
+    X[5, 95], X[n - 1, 0] = float("inf"), float("nan")
+    Z = torch.empty_like(Y)
+    B.slicegcn_linear_fwd(X, W, b, Z, None)
+    assert bool(Z[5].isinf().all()) and bool(Z[n - 1].isnan().all())
+    Z[5], Z[n - 1] = Y[5], Y[n - 1]
+    assert torch.equal(Y, Z)
