@@ -426,7 +426,7 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
     pair_rows_tile<NT, TWO, BWD>(slice_of(common, batch), blockIdx.x + first, n_col_tiles);
 }
 
-// The single products of wide layers on many rows.  What bounded pair_rows_kernel there was waiting: fp32 matrix instructions take the vector
+// Products of wide layers on many rows, one at a time.  What bounded pair_rows_kernel there was waiting: fp32 matrix instructions take the vector
 // pipe, so nothing but other matrix instructions fills a wait, and a workgroup asked for its next 32 steps of rows and weights when the
 // current ones began, 0.9 us ahead.  Here a workgroup stays for the whole launch, one per CU and of eight wavefronts, with all of its columns'
 // weights in LDS (up to 128 KB; no barrier behind the first), and a wavefront keeps the next R chunks of its rows in flight
@@ -436,7 +436,8 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
 // same XCD.  The order of the sums is that of pair_rows_kernel: the same bits.
 // Bound by the matrix instructions and, under their load, by a clock of about 2.2 GHz (143 TFLOP/s): 1 M rows 256 -> 256 are 81 % of its cycles, other
 // vector instructions 6 %.  rows / wide, forward and input gradients with a mask: 2.4 M rows 256 -> 256 3.09 / 2.73 and 3.17 / 2.69 ms, 256 -> 47
-// 846 / 750 and 1087 / 785 us, 800 k 200 -> 200 844 / 725 and 876 / 711, 66 k 512 -> 512 336 / 290 and 327 / 298, 169 k 40 -> 256 67.6 / 57.4.
+// 846 / 750 and 1087 / 785 us, 800 k 200 -> 200 844 / 725 and 876 / 711, 66 k 512 -> 512 336 / 290 and 327 / 298, 169 k 40 -> 256 67.6 / 57.4; both input
+// gradients of two slices of 233 k rows 128 <- 128 355 / 307.
 constexpr int WIDE_WAVES = 8, WIDE_WEIGHTS = 32768; // wavefronts of a workgroup; floats of its weights
 inline constexpr int wide_k(int nt) { return WIDE_WEIGHTS / (32 * nt) / 8 * 8; } // longest product of a workgroup with nt tiles of columns
 template <int NT, int R, bool RAGGED, bool BWD> // RAGGED: K is no multiple of 32
@@ -476,6 +477,8 @@ __global__ __launch_bounds__(64 * WIDE_WAVES, 2) void pair_wide_kernel(const Pai
         }
         if (BWD) word = *plus(words + row0 * (int64_t)ldm, masked ? r * ldm + c : 0u);
     };
+    auto factor_of = [&](int64_t s) { return BWD && a.scale_o1 ? a.scale_o1[min(s * 32 + m, n - 1)] : 1.f; }; // of the row this lane feeds
+    float next_f = first < strips ? factor_of(first) : 1.f;
     if (first < strips) {
 #pragma unroll
         for (int j = 0; j < R; ++j) load(ring[j], ring_word[j], first, j);
@@ -516,6 +519,8 @@ __global__ __launch_bounds__(64 * WIDE_WAVES, 2) void pair_wide_kernel(const Pai
     for (int t = 0; t < NT; ++t) w[0][t] = w_first[32 * t];
     for (int64_t s = first; s < strips; s += stride) {
         const int64_t next = s + stride < strips ? s + stride : s;
+        const float f = next_f;
+        next_f = factor_of(next);
         floatx16 acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -545,6 +550,11 @@ __global__ __launch_bounds__(64 * WIDE_WAVES, 2) void pair_wide_kernel(const Pai
 #pragma unroll
                             for (int i = 0; i < 4; ++i) // a bit extended to a word
                                 x[q][i] = __int_as_float(__float_as_int(x[q][i]) & __builtin_amdgcn_sbfe(word, 8 * q + i, 1));
+                    }
+                    if (BWD && a.scale_o1) { // uniform
+                        asm volatile(""); // (a branch)
+#pragma unroll
+                        for (int q = 0; q < KC / 8; ++q) x[q] *= f;
                     }
                     const floatx4 *w_at = w_first + c * (KC / 4) * BN;
 #pragma unroll
@@ -1167,7 +1177,7 @@ struct PairForm {
     int64_t blocks;
     int nt, n_col; // ROWS, WIDE: tiles of 32 columns a workgroup takes, workgroups along the columns
 };
-inline PairForm pair_form(const PairArgs *list, int batch, bool wide = true) // wide: also pair_wide_kernel
+inline PairForm pair_form(const PairArgs *list, int batch, bool backward, bool wide = true) // wide: may take pair_wide_kernel
 {
     const PairArgs &a = list[0];
     const bool two = a.A2 != nullptr && a.B2 != nullptr;
@@ -1199,18 +1209,20 @@ inline PairForm pair_form(const PairArgs *list, int batch, bool wide = true) // 
         return PairForm{PairForm::STRIP64, two, strip_blocks < resident ? strip_blocks : resident, 0, 0};
     }
     const int tiles = (a.Nout + 31) / 32;
-    // Wide single products: a workgroup per CU that holds its columns' weights, from eight strips of rows a SIMD on (below, staging the weights and
+    // Wide single products, and the two input gradients of a slice layer as two of them (forward the sum would have to be read back): a workgroup per CU that holds its columns' weights, from eight strips of rows a SIMD on (below, staging the weights and
     // an uneven last turn cost more than the deeper reads give: rows / wide, 66 k rows 128 -> 128, two strips, 31.3 / 37.7 us; 100 k rows 100 -> 96,
     // three, 31.5 / 34.0; 66 k 256 -> 256, four, 98.4 / 93.7, its input gradients 93.6 / 96.8; 169 k 128 -> 128, five, 67.5 / 66.6 and 64.7 / 67.7; above,
-    // 300 k 47 <- 131, nine, 76.4 / 74.2; 169 k 256 -> 256, ten, 221 / 196 and 218 / 197; 400 k 37 -> 70, twelve, 65.5 / 51.0).
-    if (wide && near && !two && a.K >= 4 && tiles >= 2 && tiles <= 128 && (a.Nout % 32 == 0 || a.Nout % 32 >= 4) && a.ldo1 < (1 << 24) && !a.scale_o1 &&
-        !in_place(list, batch)) {
+    // 300 k 47 <- 131, nine, 76.4 / 74.2; 169 k 256 -> 256, ten, 221 / 196 and 218 / 197; 400 k 37 -> 70, twelve, 65.5 / 51.0).  Not where K is one whole
+    // chunk of pair_rows_kernel, which loads it without tests and has nothing to wait for twice (400 k rows 32 -> 128 66 / 68, 128 <- 32 52 / 57; but
+    // 200 <- 16 156 / 105, 24 -> 256 of 1 M rows 359 / 293).
+    const bool form = backward || (!two && !a.scale_o1), columns = tiles >= 2 && tiles <= 128 && (a.Nout % 32 == 0 || a.Nout % 32 >= 4);
+    if (wide && near && form && columns && a.K >= 4 && a.K != 32 && a.ldo1 < (1 << 24) && a.ldo2 < (1 << 24) && !in_place(list, batch)) {
         // as few tiles of padding as can be, then as many per workgroup as can be
         int nt = 2;
         for (int t = 3; t <= 4; ++t)
             if ((tiles + t - 1) / t * t <= (tiles + nt - 1) / nt * nt && a.K <= wide_k(t)) nt = t;
         const int n_col = (tiles + nt - 1) / nt, per = 32 / (n_col * batch) > 0 ? 32 / (n_col * batch) : 1; // walkers per XCD
-        if (a.K <= wide_k(nt) && strips * n_col * batch >= 8 * 1024) return PairForm{PairForm::WIDE, false, 8 * (int64_t)per * n_col, nt, n_col};
+        if (a.K <= wide_k(nt) && strips * n_col * batch >= 8 * 1024) return PairForm{PairForm::WIDE, two, 8 * (int64_t)per * n_col, nt, n_col};
     }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
@@ -1245,6 +1257,24 @@ void launch_wide(const PairArgs &a, const PairBatch &b, dim3 grid, int n_col, hi
     if (a.K <= 64) launch(std::integral_constant<int, 2>());
     else launch(std::integral_constant<int, 4>());
 }
+template <bool BWD>
+int launch_wide(const PairArgs *list, int batch, const PairForm &f, hipStream_t stream)
+{
+    const dim3 grid((unsigned)f.blocks, (unsigned)batch);
+    const PairBatch b = pair_batch(list, batch);
+    if (f.nt == 2) launch_wide<2, BWD>(list[0], b, grid, f.n_col, stream);
+    else if (f.nt == 3) launch_wide<3, BWD>(list[0], b, grid, f.n_col, stream);
+    else launch_wide<4, BWD>(list[0], b, grid, f.n_col, stream);
+    SG_LAUNCH_CHECK();
+    if (!BWD || !f.two || !list[0].O2) return SLICEGCN_OK;
+    PairArgs second[BATCH]; // of a slice layer's two input-gradient products: no mask, no row factors
+    for (int i = 0; i < batch; ++i) {
+        PairArgs &p = second[i] = list[i];
+        p.A1 = p.A2; p.lda1 = p.lda2; p.B1 = p.B2; p.O1 = p.O2; p.ldo1 = p.ldo2;
+        p.mask = nullptr; p.scale_o1 = nullptr; p.O2 = nullptr;
+    }
+    return launch_wide<BWD>(second, batch, f, stream);
+}
 
 // `list`: one entry per slice model of the batch (1 to BATCH, equal but for the pointers)
 template <bool BWD>
@@ -1253,7 +1283,7 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
     if (int rc = check_in_place(list, batch)) return rc;
     const PairArgs &a = list[0];
     const PairBatch b = pair_batch(list, batch);
-    const PairForm f = pair_form(list, batch);
+    const PairForm f = pair_form(list, batch, BWD);
     SG_REQUIRE(f.blocks <= INT32_MAX, SLICEGCN_ERANGE, "dense product: grid too large");
     const dim3 grid((unsigned)f.blocks, (unsigned)batch);
     const int n_col = f.n_col;
@@ -1268,10 +1298,7 @@ int launch_pair(const PairArgs *list, int batch, hipStream_t stream)
         else launch_strip64<2, 2, BWD>(a, b, grid, stream);
         break;
     case PairForm::WIDE:
-        if (f.nt == 2) launch_wide<2, BWD>(a, b, grid, n_col, stream);
-        else if (f.nt == 3) launch_wide<3, BWD>(a, b, grid, n_col, stream);
-        else launch_wide<4, BWD>(a, b, grid, n_col, stream);
-        break;
+        return launch_wide<BWD>(list, batch, f, stream);
     case PairForm::ROWS:
         return launch_parts(f.blocks, [&](unsigned first, unsigned count) { // one to three columns in: any number of rows comes here
             const dim3 grid(count, (unsigned)batch);
@@ -2420,7 +2447,7 @@ int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, 
     *pair_done = false;
     if (!list) return launch_grad_rows(r, b, batch, products, big, stream);
     const GradForm g = grad_form(r, batch, products, big, r.rows_per_block == RED_ROWS);
-    const PairForm f = pair_form(list, batch, false);
+    const PairForm f = pair_form(list, batch, true, false);
     bool merge = g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 &&
                  (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && (f.nt == 1 || (f.nt == 2 && g.wj != 0)))) &&
                  products * g.blocks + 2 * f.blocks <= MAX_GRID;

@@ -1,8 +1,9 @@
-"""Single products of wide layers on many rows (pair_wide_kernel): bit for bit what the same rows give a few at a time, which
+"""Products of wide layers on many rows (pair_wide_kernel): bit for bit what the same rows give a few at a time, which
 takes the general kernel, and within an fp32 sum's bound of fp64."""
 import pytest
 import torch
 
+import paper_2408_11500_amd as sg
 from paper_2408_11500_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -56,3 +57,31 @@ def test_wide_product_keeps_rows_with_infinities_apart():
     assert bool(Z[5].isinf().all()) and bool(Z[n - 1].isnan().all())
     Z[5], Z[n - 1] = Y[5], Y[n - 1]
     assert torch.equal(Y, Z)
+
+
+@pytest.mark.parametrize("n,w_in,w_out", [(262_177, 128, 128), (262_150, 96, 65), (262_151, 70, 36), (131_080, 301, 33), (87_400, 260, 100)])
+def test_wide_input_gradients_of_a_layer_same_bits_as_few_rows(n, w_in, w_out):
+    """A graph of pairs and single nodes: its rows can be worked on a few at a time.  dZ takes row factors and the activation bits, T neither."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda")
+
+    def graph(count):
+        a = torch.arange(0, count - 1, 6, device="cuda")
+        return sg.slicegcn_build_norm_csr(a, a + 1, count, B.SYMMETRIZE | B.ADD_SELF_LOOPS)
+
+    Wa, Ws, words = rand(w_in, w_out), rand(w_in, w_out), (w_out + 31) // 32
+    Hin, Z, dH = rand(n, w_in), rand(n, (w_in + 3) // 4 * 4)[:, :w_in], rand(n, w_out + 1)[:, :w_out]
+    mask = torch.randint(-2 ** 31, 2 ** 31 - 1, (n, words), generator=gen, device="cuda", dtype=torch.int32)
+
+    def backward(g, r):
+        dHin, grads = torch.empty((len(Hin[r]), w_in), device="cuda"), [torch.empty_like(x) for x in (Wa, Wa[0], Wa, Wa[0])]
+        ws = torch.empty(B.slicegcn_layer_bwd_workspace_bytes(g, w_in, w_out, True), dtype=torch.uint8, device="cuda")
+        B.slicegcn_layer_bwd(g, Hin[r], Wa, Ws, Z[r], mask[r], dH[r], dHin, *grads, ws)
+        return dHin
+
+    step = FEW - FEW % 6
+    whole, piece, last = graph(n), graph(step), graph(n % step)
+    got = backward(whole, slice(0, n))
+    for a in range(0, n, step):
+        r = slice(a, min(n, a + step))
+        assert torch.equal(got[r], backward(piece if a + step <= n else last, r))
