@@ -53,6 +53,9 @@ __device__ inline int32_t class_bound(const int32_t *__restrict__ colptr, int64_
 // Kinds of rows (see common.h): whole rows make one item each, long ones (ranges of their length, the longest first) are cut by
 // column class, tiny ones are listed.
 constexpr int ROW_WAVE = 0, ROW_GROUP = 1, ROW_LONG = 2, ROW_TINY = ROW_LONG + LONG_BINS, ROW_KINDS = ROW_TINY + 1;
+// Kinds that are counted: those of the ranges in use.  The tiny rows are the others (with all kinds in the scan of the counts, 270 k nodes took a second
+// launch for it, 750 us a build instead of 742).
+inline __host__ __device__ int counted_kinds(int32_t item_max) { return ROW_LONG + (item_max > ITEM_SHORT ? LONG_BINS : 1); }
 __device__ inline int row_kind(int32_t d, int32_t item_max)
 {
     if (d <= TINY_ROW) return ROW_TINY;
@@ -62,7 +65,7 @@ __device__ inline int row_kind(int32_t d, int32_t item_max)
 #pragma unroll
         for (int b = 1; b < LONG_BINS; ++b) range += d > PART_ROW << b;
     }
-    return ROW_LONG + LONG_BINS - 1 - range;
+    return counted_kinds(item_max) - 1 - range;
 }
 
 // Thread p handles the row at position p of the schedule (order[p], or p itself in natural order), so that the items
@@ -86,29 +89,36 @@ __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restri
         kind = row_kind(end - beg, item_max);
     }
     int32_t rank = 0;
+    const int counted = counted_kinds(item_max);
 #pragma unroll
     for (int k = 0; k < ROW_KINDS; ++k) {
+        if (k >= counted && k < ROW_TINY) continue; // uniform
         const unsigned long long bits = __ballot(kind == k);
         if (kind == k) rank = __popcll(bits & ((1ull << lane) - 1ull));
         if (lane == 0) per_wave[wave][k] = __popcll(bits);
     }
     __syncthreads();
     if (!FILL) {
-        if (threadIdx.x < ROW_KINDS)
+        if (threadIdx.x < counted)
             counts[threadIdx.x * n_groups + blockIdx.x] = per_wave[0][threadIdx.x] + per_wave[1][threadIdx.x] +
                                                           per_wave[2][threadIdx.x] + per_wave[3][threadIdx.x];
         return;
     }
     if (kind < 0) return;
     for (int w = 0; w < wave; ++w) rank += per_wave[w][kind];
-    const int32_t at = counts[kind * n_groups + blockIdx.x] + rank; // the scan ran over the kinds back to back
     if (kind == ROW_TINY) {
+        if (!tiny) return;
+        int32_t at = (int32_t)blockIdx.x * TPB + rank; // the rows before this one, less those of the other kinds among the workgroups before
+        for (int k = 0; k < counted; ++k) at -= counts[k * n_groups + blockIdx.x] - counts[k * n_groups];
         const uint32_t more = end > beg ? (uint32_t)(end - beg - 1) : 0u;
         TinyRow r;
         r.row = (uint32_t)row | more << 31;
         r.beg = (end > beg ? (uint32_t)beg : NO_ENTRIES) | more >> 1 << 31;
-        if (tiny) tiny[at - counts[ROW_TINY * n_groups]] = r;
-    } else if (kind >= ROW_LONG) {
+        tiny[at] = r;
+        return;
+    }
+    const int32_t at = counts[kind * n_groups + blockIdx.x] + rank; // the scan ran over the kinds back to back
+    if (kind >= ROW_LONG) {
         if (long_rows) long_rows[at - counts[ROW_LONG * n_groups]] = row;
     } else if (items) {
         Segment sg;
@@ -121,13 +131,13 @@ __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restri
 // within a LOCAL_SPAN-th of the nodes than have not (one row per thread beside the wavefront that searches the boundaries, which takes longer); the column class boundaries
 // stay on the device.
 constexpr int SAMPLES = 960, LOCAL_SPAN = 16;
-__global__ __launch_bounds__(SAMPLES + 64) void sched_summary_kernel(const int32_t *__restrict__ counts, int64_t n_groups, const int32_t *__restrict__ colptr, int64_t n,
+__global__ __launch_bounds__(SAMPLES + 64) void sched_summary_kernel(const int32_t *__restrict__ counts, int64_t n_groups, int counted, const int32_t *__restrict__ colptr, int64_t n,
                                                            const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
                                                            int32_t *__restrict__ summary, ClassBounds *__restrict__ cb)
 {
     const int t = threadIdx.x;
     bool near = false, far = false;
-    if (t < ROW_KINDS) summary[t] = counts[(t + 1) * n_groups] - counts[t * n_groups];
+    if (t < counted) summary[t] = counts[(t + 1) * n_groups] - counts[t * n_groups];
     if (t <= N_CLASSES) {
         cb->first[t] = class_bound(colptr, n, t);
     } else if (t >= 64) {
@@ -141,7 +151,7 @@ __global__ __launch_bounds__(SAMPLES + 64) void sched_summary_kernel(const int32
         }
     }
     const int excess = __syncthreads_count(near) - __syncthreads_count(far);
-    if (t == ROW_KINDS) summary[t] = excess;
+    if (t == counted) summary[t] = excess;
 }
 
 // ---- long rows: cut by column class ------------------------------------------------------
@@ -288,7 +298,7 @@ int64_t candidates(int64_t n_edges, int64_t n, uint32_t flags) // entries the pa
 
 size_t sched_bytes(int64_t n, int64_t n_keys)
 {
-    const int64_t groups = ROW_KINDS * (int64_t)blocks_for(n) + 1, n_long = n_keys / PART_ROW < n ? n_keys / PART_ROW : n;
+    const int64_t groups = ROW_TINY * (int64_t)blocks_for(n) + 1, n_long = n_keys / PART_ROW < n ? n_keys / PART_ROW : n;
     const int64_t tables = N_TABLES * (n_long + 1);
     const size_t a = scan_bytes(groups), b = scan_bytes(tables);
     return 2 * Arena::rounded((size_t)groups * 4) + Arena::rounded((size_t)n_long * 4) + Arena::rounded((size_t)n_long * N_CLASSES * 4) + 2 * Arena::rounded((size_t)tables * 4) +
@@ -315,23 +325,24 @@ int build_schedule(slicegcn_graph *g, const Csr &m, const int32_t *colptr, uint3
     if (flags & SLICEGCN_SCHED_LONG_ITEMS) item_max = ITEM_LONG;
     out.item_max = item_max;
     const int64_t n_groups = blocks_for(n);
+    const int counted = counted_kinds(item_max);
     int32_t *counts = nullptr, *offs = nullptr;
     ClassBounds *cb = nullptr;
-    if (int rc = ws.take((size_t)(ROW_KINDS * n_groups + 1) * 4, &counts)) return rc;
-    if (int rc = ws.take((size_t)(ROW_KINDS * n_groups + 1) * 4, &offs)) return rc;
+    if (int rc = ws.take((size_t)(counted * n_groups + 1) * 4, &counts)) return rc;
+    if (int rc = ws.take((size_t)(counted * n_groups + 1) * 4, &offs)) return rc;
     if (int rc = ws.take(sizeof(ClassBounds), &cb)) return rc;
     sched_rows_kernel<false><<<(unsigned)n_groups, TPB, 0, stream>>>(m.rowptr, g->order, n, item_max, counts, n_groups, nullptr, nullptr, nullptr);
     SG_LAUNCH_CHECK();
-    if (int rc = scan_i32(counts, offs, ROW_KINDS * n_groups + 1, ws, stream)) return rc; // the last element is only written
-    sched_summary_kernel<<<1, SAMPLES + 64, 0, stream>>>(offs, n_groups, colptr, n, m.rowptr, m.colidx, counters, cb);
+    if (int rc = scan_i32(counts, offs, counted * n_groups + 1, ws, stream)) return rc; // the last element is only written
+    sched_summary_kernel<<<1, SAMPLES + 64, 0, stream>>>(offs, n_groups, counted, colptr, n, m.rowptr, m.colidx, counters, cb);
     SG_LAUNCH_CHECK();
-    int32_t kinds[ROW_KINDS + 1];
-    if (int rc = read_counters(counters, kinds, ROW_KINDS + 1, stream)) return rc;
-    out.local = kinds[ROW_KINDS] > 0;
+    int32_t kinds[ROW_KINDS];
+    if (int rc = read_counters(counters, kinds, counted + 1, stream)) return rc;
+    out.local = kinds[counted] > 0;
     const int64_t n_group = kinds[ROW_GROUP], n_wave = kinds[ROW_WAVE];
     int64_t n_long = 0;
-    for (int b = 0; b < LONG_BINS; ++b) n_long += kinds[ROW_LONG + b];
-    out.tiny_cnt = kinds[ROW_TINY];
+    for (int k = ROW_LONG; k < counted; ++k) n_long += kinds[k];
+    out.tiny_cnt = (int32_t)(n - n_wave - n_group - n_long);
 
     int32_t *long_rows = nullptr, *class_beg = nullptr, *cnt = nullptr, *off = nullptr;
     int32_t starts[N_TABLES + 1] = {0};
