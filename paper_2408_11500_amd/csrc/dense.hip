@@ -11,6 +11,7 @@
 // B operand = B[k = l / 32][n = l % 32], accumulator register r (0..15) = C[8*(r/4) + 4*(l/32) + r%4][l % 32].
 #include "common.h"
 #include "final_sum.h"
+#include "wide_rules.h"
 
 #include <type_traits>
 
@@ -438,13 +439,11 @@ __global__ __launch_bounds__(256, NT == 4 || (TWO && NT == 3) ? 2 : 3) void pair
 // vector instructions 6 %.  rows / wide, forward and input gradients with a mask: 2.4 M rows 256 -> 256 3.09 / 2.73 and 3.17 / 2.69 ms, 256 -> 47
 // 846 / 750 and 1087 / 785 us, 800 k 200 -> 200 844 / 725 and 876 / 711, 66 k 512 -> 512 336 / 290 and 327 / 298, 169 k 40 -> 256 67.6 / 57.4; both input
 // gradients of two slices of 233 k rows 128 <- 128 355 / 307.
-constexpr int WIDE_WAVES = 8, WIDE_WEIGHTS = 32768; // wavefronts of a workgroup; floats of its weights
-inline constexpr int wide_k(int nt) { return WIDE_WEIGHTS / (32 * nt) / 8 * 8; } // longest product of a workgroup with nt tiles of columns
 template <int NT, int R, bool RAGGED, bool BWD> // RAGGED: K is no multiple of 32
 __global__ __launch_bounds__(64 * WIDE_WAVES, 2) void pair_wide_kernel(const PairArgs common, const PairBatch batch, int n_tiles, int walkers)
 {
-    constexpr int BN = NT * 32, KC = 32, TS = 36;
-    __shared__ floatx4 Bs[wide_k(NT) / 4][BN]; // units of four k of a column
+    constexpr int BN = NT * 32, KC = WIDE_CHUNK, TS = 36;
+    __shared__ floatx4 Bs[wide_groups(wide_k(NT))][BN]; // units of four k of a column
     __shared__ __attribute__((aligned(16))) float tiles[WIDE_WAVES][16][TS];
     __shared__ __attribute__((aligned(16))) float bias_s[BN];
     const PairArgs a = slice_of(common, batch);
@@ -486,7 +485,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES, 2) void pair_wide_kernel(const Pai
 
     // Units of four k of a column; zero past K.  Consecutive threads walk the contiguous axis of W (columns forward, groups of four k backward),
     // and eight units of a thread are requested before the first is stored.
-    const int groups = (K + 7) / 8 * 2, units = (groups + 7) / 8 * 8 * BN;
+    const int groups = (K + 7) / 8 * 2, units = wide_groups(K) * BN;
     for (int u0 = tid; u0 < units; u0 += 8 * 64 * WIDE_WAVES) {
         floatx4 w[8];
         auto group_of = [&](int u) { return BWD ? (u & 7) + u / (8 * BN) * 8 : u / BN; };
@@ -560,7 +559,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES, 2) void pair_wide_kernel(const Pai
 #pragma unroll
                     for (int q = 0; q < KC / 8; ++q) { // the weights of four steps are read while the four before them are multiplied
                         if (RAGGED && q > 0 && 8 * q >= left) break; // uniform: both operands are zero from here on
-                        const floatx4 *w_next = q + 1 < KC / 8 || left > KC ? w_at + 2 * (q + 1) * BN : w_first;
+                        const floatx4 *w_next = wide_more(left, q) ? w_at + 2 * (q + 1) * BN : w_first;
                         if (!RAGGED || q + 1 < KC / 8 || left >= KC) {
 #pragma unroll
                             for (int t = 0; t < NT; ++t) w[(q + 1) & 1][t] = w_next[32 * t];

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 # rows, columns in, columns out: odd and whole chunks of k, one to many of them, full and partial tiles of columns and strips of rows
 SIZES = [(262_144, 256, 64), (131_073, 4, 160), (87_390, 47, 288), (262_177, 64, 36), (131_101, 65, 256), (65_536, 301, 253), (262_145, 511, 63),
-         (87_401, 33, 269), (131_100, 100, 229)]
+         (87_401, 33, 269), (131_100, 100, 229),
+         (262_145, 333, 96), (262_145, 96, 333)]  # three tiles whose weights fill LDS to the last group of k
 FEW = 4096
 
 
