@@ -1208,20 +1208,20 @@ inline PairForm pair_form(const PairArgs *list, int batch, bool backward, bool w
         return PairForm{PairForm::STRIP64, two, strip_blocks < resident ? strip_blocks : resident, 0, 0};
     }
     const int tiles = (a.Nout + 31) / 32;
-    // Wide single products, and the two input gradients of a slice layer as two of them (forward the sum would have to be read back): a workgroup per CU that holds its columns' weights, from eight strips of rows a SIMD on (below, staging the weights and
-    // an uneven last turn cost more than the deeper reads give: rows / wide, 66 k rows 128 -> 128, two strips, 31.3 / 37.7 us; 100 k rows 100 -> 96,
-    // three, 31.5 / 34.0; 66 k 256 -> 256, four, 98.4 / 93.7, its input gradients 93.6 / 96.8; 169 k 128 -> 128, five, 67.5 / 66.6 and 64.7 / 67.7; above,
-    // 300 k 47 <- 131, nine, 76.4 / 74.2; 169 k 256 -> 256, ten, 221 / 196 and 218 / 197; 400 k 37 -> 70, twelve, 65.5 / 51.0).  Not where K is one whole
-    // chunk of pair_rows_kernel, which loads it without tests and has nothing to wait for twice (400 k rows 32 -> 128 66 / 68, 128 <- 32 52 / 57; but
-    // 200 <- 16 156 / 105, 24 -> 256 of 1 M rows 359 / 293).
-    const bool form = backward || (!two && !a.scale_o1), columns = tiles >= 2 && tiles <= 128 && (a.Nout % 32 == 0 || a.Nout % 32 >= 4);
+    // Wide single products, and the two input gradients of a slice layer as two of them (forward the sum would have to be read back), where a workgroup per CU
+    // that holds its columns' weights has strips enough (wide_even; one slice below and above its line, rows / wide: 66 k rows 128 -> 128, two strips a SIMD,
+    // 31.3 / 37.7 us; 100 k 100 -> 96, three, 31.5 / 34.0; 66 k 256 -> 256, four, 98.4 / 93.7, its input gradients 93.6 / 96.8; 169 k 128 -> 128, five,
+    // 67.5 / 66.6 and 64.7 / 67.7; 300 k 47 <- 131, nine, 76.4 / 74.2; 169 k 256 -> 256, ten, 221 / 196 and 218 / 197; 400 k 37 -> 70, twelve, 65.5 / 51.0).  Not
+    // where K is one whole chunk of pair_rows_kernel, which loads it without tests and has nothing to wait for twice (400 k rows 32 -> 128 66 / 68,
+    // 128 <- 32 52 / 57; but 200 <- 16 156 / 105, 24 -> 256 of 1 M rows 359 / 293).
+    const bool form = backward || (!two && !a.scale_o1), columns = tiles >= 2 && (a.Nout % 32 == 0 || a.Nout % 32 >= 4);
     if (wide && near && form && columns && a.K >= 4 && a.K != 32 && a.ldo1 < (1 << 24) && a.ldo2 < (1 << 24) && !in_place(list, batch)) {
         // as few tiles of padding as can be, then as many per workgroup as can be
         int nt = 2;
         for (int t = 3; t <= 4; ++t)
             if ((tiles + t - 1) / t * t <= (tiles + nt - 1) / nt * nt && a.K <= wide_k(t)) nt = t;
-        const int n_col = (tiles + nt - 1) / nt, per = 32 / (n_col * batch) > 0 ? 32 / (n_col * batch) : 1; // walkers per XCD
-        if (a.K <= wide_k(nt) && strips * n_col * batch >= 8 * 1024) return PairForm{PairForm::WIDE, two, 8 * (int64_t)per * n_col, nt, n_col};
+        const int n_col = (tiles + nt - 1) / nt, walkers = wide_walkers(n_col * batch);
+        if (a.K <= wide_k(nt) && wide_even(n_col * batch, strips)) return PairForm{PairForm::WIDE, two, 8 * (int64_t)walkers * n_col, nt, n_col};
     }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
     const int64_t row_tiles = (a.n + 127) / 128;
