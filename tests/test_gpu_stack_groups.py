@@ -153,3 +153,16 @@ def test_group_takes_the_strip_kernels_and_one_slice_does_not(monkeypatch, first
 def test_weight_gradients_of_a_group_in_strips_and_of_one_slice_in_tiles(monkeypatch, n, first, hs, self_term):
     """Blocks of 256 rows: pairs of products go to the strips from 160 of them on (79 a slice), single products from 512 on (258 a slice)."""
     in_a_group_and_alone(monkeypatch, n, 4, first, hs, self_term)
+
+
+@pytest.mark.parametrize("n,k,first,hs", [(87_403, 3, 37, 100), (66_003, 4, 64, 96), (35_011, 8, 40, 132), (52_451, 2, 47, 260)])
+def test_group_takes_the_wide_products_and_one_slice_does_not(monkeypatch, n, k, first, hs):
+    """Input gradients of wide layers: together the slices of a launch have strips enough for pair_wide_kernel, which forms the two products of each one
+    after the other; alone a slice goes to the general kernel: the same bits."""
+    in_a_group_and_alone(monkeypatch, n, k, first, hs)
+
+
+def test_group_with_more_column_tiles_than_fill_the_chip(monkeypatch):
+    """Ten tiles of columns by eight slices and by six: the general kernel and the wide one."""
+    in_a_group_and_alone(monkeypatch, 9_001, 8, 20, 320)
+    in_a_group_and_alone(monkeypatch, 9_001, 6, 20, 320)

@@ -1,5 +1,5 @@
-"""Products of wide layers on many rows (pair_wide_kernel): bit for bit what the same rows give a few at a time, which
-takes the general kernel, and within an fp32 sum's bound of fp64."""
+"""Products of wide layers on many rows (pair_wide_kernel; where one of the two widths is narrow, the direction that has it as its columns may be another
+kernel's): bit for bit what the same rows give a few at a time, which takes the general kernel, and within an fp32 sum's bound of fp64."""
 import pytest
 import torch
 
@@ -12,6 +12,9 @@ pytestmark = pytest.mark.gpu
 SIZES = [(262_144, 256, 64), (131_073, 4, 160), (87_390, 47, 288), (262_177, 64, 36), (131_101, 65, 256), (65_536, 301, 253), (262_145, 511, 63),
          (87_401, 33, 269), (131_100, 100, 229),
          (262_145, 333, 96), (262_145, 96, 333)]  # three tiles whose weights fill LDS to the last group of k
+# two, three and four tiles of columns a workgroup, two and four chunks ahead, whole and partial last chunks, each forward and as an input gradient
+SIZES += [(262_177, 128, 100), (262_146, 64, 96), (262_149, 96, 40), (262_155, 128, 96), (262_158, 96, 64), (262_155, 96, 128), (262_159, 64, 100),
+          (262_151, 40, 100), (52_450, 64, 320), (52_451, 47, 310), (52_450, 320, 64), (52_451, 310, 47)]
 FEW = 4096
 
 
