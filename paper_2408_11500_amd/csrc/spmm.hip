@@ -488,6 +488,9 @@ __device__ __forceinline__ void wave_items_run_body(const SpmmArgs &a, const Spm
 // first gathers).  1 M nodes, 1 / 8 items per lane group: 5 entries a row 64 columns 217 / 168 us, 128 columns 422 / 309, 7 entries 64 columns
 // 222 / 177, 9 entries 273 / 242, 17 entries 327 / 309; 885 k nodes, 12 entries a row in the columns below 885, 16 columns 106 / 93; but uniform
 // random graphs of 7 entries a row 235 / 247, 128 columns 461 / 487.
+// On graphs that stay in cache the compiler is kept from moving a set's first gather into the branch that adds it (the entry may be absent), behind all others,
+// where the wavefront waits for memory a second time: 2 k nodes, 11 k edges, 64 columns 4.05 -> 3.70 us, 15 k nodes, 64 k edges, 100 columns 10.3 -> 9.7,
+// from some 100 k nodes on level; streamed graphs are 0.5 % slower with it (2 M nodes in communities, inference 10.84 -> 10.89 ms).
 template <int LPR, int V, bool S32, int GI_MAX, bool FACT, bool RAG, bool RUNS>
 __device__ __forceinline__ void group_items_body(const SpmmArgs &a, const SpmmIo &io, int block)
 {
@@ -554,6 +557,7 @@ __device__ __forceinline__ void group_items_body(const SpmmArgs &a, const SpmmIo
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) x[u] = load_x<V, S32>(a, io.X, c[u], colc);
+            if (GI_MAX == ITEM_SHORT) asm volatile("" ::: "memory"); // all gathers are requested before one is used (see above)
             if (RUNS && j0 == 0) pairs(c_n, v_n, beg, end); // the next round's, behind the first gathers (none behind the last round)
 #pragma unroll
             for (int u = 0; u < U; ++u)
