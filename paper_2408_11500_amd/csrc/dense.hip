@@ -1208,28 +1208,32 @@ inline PairForm pair_form(const PairArgs *list, int batch, bool backward, bool w
         return PairForm{PairForm::STRIP64, two, strip_blocks < resident ? strip_blocks : resident, 0, 0};
     }
     const int tiles = (a.Nout + 31) / 32;
-    // Wide single products, and the two input gradients of a slice layer as two of them (forward the sum would have to be read back), where a workgroup per CU
-    // that holds its columns' weights has strips enough (wide_even; one slice below and above its line, rows / wide: 66 k rows 128 -> 128, two strips a SIMD,
-    // 31.3 / 37.7 us; 100 k 100 -> 96, three, 31.5 / 34.0; 66 k 256 -> 256, four, 98.4 / 93.7, its input gradients 93.6 / 96.8; 169 k 128 -> 128, five,
-    // 67.5 / 66.6 and 64.7 / 67.7; 300 k 47 <- 131, nine, 76.4 / 74.2; 169 k 256 -> 256, ten, 221 / 196 and 218 / 197; 400 k 37 -> 70, twelve, 65.5 / 51.0).  Not
-    // where K is one whole chunk of pair_rows_kernel, which loads it without tests and has nothing to wait for twice (400 k rows 32 -> 128 66 / 68,
-    // 128 <- 32 52 / 57; but 200 <- 16 156 / 105, 24 -> 256 of 1 M rows 359 / 293).
-    const bool form = backward || (!two && !a.scale_o1), columns = tiles >= 2 && (a.Nout % 32 == 0 || a.Nout % 32 >= 4);
-    if (wide && near && form && columns && a.K >= 4 && a.K != 32 && a.ldo1 < (1 << 24) && a.ldo2 < (1 << 24) && !in_place(list, batch)) {
-        // as few tiles of padding as can be, then as many per workgroup as can be
-        int nt = 2;
-        for (int t = 3; t <= 4; ++t)
-            if ((tiles + t - 1) / t * t <= (tiles + nt - 1) / nt * nt && a.K <= wide_k(t)) nt = t;
-        const int n_col = (tiles + nt - 1) / nt, walkers = wide_walkers(n_col * batch);
-        if (a.K <= wide_k(nt) && wide_even(n_col * batch, strips)) return PairForm{PairForm::WIDE, two, 8 * (int64_t)walkers * n_col, nt, n_col};
-    }
-    // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
-    const int64_t row_tiles = (a.n + 127) / 128;
-    // Tiles of 32 columns a workgroup takes: two keep three or four workgroups on a CU, where four (two workgroups) take 244 us instead
+    // Tiles of 32 columns a workgroup of pair_rows_kernel takes: two keep three or four workgroups on a CU, where four (two workgroups) take 244 us instead
     // of 238 for 169 k rows 256 -> 256 and 158 instead of 130 for 20 k rows 512 -> 512; three for widths of three tiles, which two would
     // pad to four; one where that would leave fewer than eight workgroups per CU (20 k rows 256 -> 256: 38 us instead of 41,
     // 169 k rows 256 -> 40: 67 instead of 75; 169 k rows 256 -> 256, above the line: 253 instead of 238).
     int nt = tiles % 2 != 0 && tiles % 3 == 0 ? 3 : tiles < 2 ? 1 : 2;
+    // Wide single products, and the two input gradients of a slice layer as two of them (forward the sum would have to be read back), where a workgroup per CU
+    // that holds its columns' weights has strips enough (wide_even; one slice below and above its line, rows / wide: 66 k rows 128 -> 128, two strips a SIMD,
+    // 31.3 / 37.7 us; 100 k 100 -> 96, three, 31.5 / 34.0; 66 k 256 -> 256, four, 98.4 / 93.7, its input gradients 93.6 / 96.8; 169 k 128 -> 128, five,
+    // 67.5 / 66.6 and 64.7 / 67.7; 300 k 47 <- 131, nine, 76.4 / 74.2; 169 k 256 -> 256, ten, 221 / 196 and 218 / 197; 400 k 37 -> 70, twelve, 65.5 / 51.0),
+    // enough to multiply (wide_long) and no more tiles of padding than pair_rows_kernel (280 k rows 400 -> 96, four tiles for three, 0.83 times as fast).  Not
+    // where K is one whole chunk of pair_rows_kernel, which loads it without tests and has nothing to wait for twice (400 k rows 32 -> 128 66 / 68,
+    // 128 <- 32 52 / 57).
+    const bool form = backward || (!two && !a.scale_o1), columns = tiles >= 2 && (a.Nout % 32 == 0 || a.Nout % 32 >= 4);
+    if (wide && near && form && columns && a.K >= 4 && a.K != 32 && a.ldo1 < (1 << 24) && a.ldo2 < (1 << 24) && !in_place(list, batch)) {
+        // as few tiles of padding as can be, then as many per workgroup as can be
+        const auto padded = [&](int t) { return (tiles + t - 1) / t * t; };
+        int wt = 2;
+        for (int t = 3; t <= 4; ++t)
+            if (padded(t) <= padded(wt) && a.K <= wide_k(t)) wt = t;
+        const int n_col = padded(wt) / wt, walkers = wide_walkers(n_col * batch);
+        const bool lines = a.ldo1 % 32 == 0 && (!a.O2 || a.ldo2 % 32 == 0);
+        if (padded(wt) <= padded(nt) && a.K <= wide_k(wt) && wide_long(wt, n_col, a.K, lines) && wide_even(wt, n_col * batch, a.K, strips))
+            return PairForm{PairForm::WIDE, two, 8 * (int64_t)walkers * n_col, wt, n_col};
+    }
+    // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
+    const int64_t row_tiles = (a.n + 127) / 128;
     if (row_tiles * ((tiles + nt - 1) / nt) * batch < 2048) nt = 1;
     if (tiles > nt && in_place(list, batch)) nt = tiles; // whole rows
     const int n_col = (tiles + nt - 1) / nt;
@@ -1253,8 +1257,9 @@ void launch_wide(const PairArgs &a, const PairBatch &b, dim3 grid, int n_col, hi
         if (a.K % 32 == 0) pair_wide_kernel<NT, r.value, false, BWD><<<grid, 64 * WIDE_WAVES, 0, stream>>>(a, b, n_col, walkers);
         else pair_wide_kernel<NT, r.value, true, BWD><<<grid, 64 * WIDE_WAVES, 0, stream>>>(a, b, n_col, walkers);
     };
-    if (a.K <= 64) launch(std::integral_constant<int, 2>());
-    else launch(std::integral_constant<int, 4>());
+    if constexpr (NT > 2) // two tiles: longer products alone (wide_long)
+        if (a.K <= 64) return launch(std::integral_constant<int, 2>());
+    launch(std::integral_constant<int, 4>());
 }
 template <bool BWD>
 int launch_wide(const PairArgs *list, int batch, const PairForm &f, hipStream_t stream)

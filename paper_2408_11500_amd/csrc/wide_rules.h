@@ -27,10 +27,29 @@ constexpr int wide_walkers(int per_strip) { return WIDE_CUS / per_strip; }
 //     22 (11)            24.3 k 175 / 203, 174 / 216           95.3 k 640 / 762, 647 / 780
 //     17 (17)            15.7 k 178 / 263, 179 / 279           61.7 k 646 / 979, 661 / 999
 //     32 of 40           eight slices, input gradients 320 <- 320 of 19.7 k rows 693 / 912 (the last workgroups start when the others end)
-constexpr bool wide_even(int per_strip, long long strips)
+// With 28 two tiles a workgroup lose at any length (280 k rows 448 columns out of 128 steps 0.94 to 1.01 times as fast, of 192 0.95 to 1.00).
+constexpr bool wide_even(int nt, int per_strip, int K, long long strips)
 {
     const int used = wide_walkers(per_strip) * per_strip;
-    return used >= 30 ? strips * per_strip >= 8192 : used >= 28 && strips * per_strip >= 12288;
+    return used >= 30 ? strips * per_strip >= 8192 : used >= 28 && nt >= 3 && K >= 96 && strips * per_strip >= 12288;
+}
+// Whether products of K steps have enough to multiply, by the tiles of 32 columns a workgroup takes and the workgroups along the columns.  Short ones are bound
+// by what is stored, and a row's columns come from n_col workgroups that drift apart: lines that two of them share are written in parts, and the rows
+// are read n_col times.  Times as fast as pair_rows_kernel, forward and input gradients of 280 k and 900 k rows, stored in whole lines or not:
+//     nt 4, n_col 1 to 4  K 8 0.89 to 1.40   16 0.93 to 1.47   24 1.00 to 1.48   33 0.97 to 1.22   64 0.98 to 1.13   128 1.03 to 1.15
+//     nt 4, n_col 5 to 8  K 8 0.69 to 1.38   16 0.74 to 1.49   24 0.84 to 1.43   33 0.98 to 1.17   64 1.03 to 1.12   128 1.04 to 1.18
+//     nt 3, n_col 1, 2    K 8 0.89 to 1.14   16 0.99 to 1.21   24 1.03 to 1.30   33 0.99 to 1.23   64 0.96 to 1.23   128 0.99 to 1.17
+//     nt 3, n_col 3 to 6  K 8 0.68 to 1.29   16 0.83 to 1.27   24 0.92 to 1.29   33 0.88 to 1.23   64 0.92 to 1.13    96 0.98 to 1.11   128 1.02 to 1.12
+//     nt 2, n_col 5       K 8 0.70 to 1.03   16 0.83 to 1.03   33 0.85 to 1.05   64 0.87 to 0.98   96 0.93 to 1.01   128 1.00 to 1.06   192 1.00 to 1.10
+//     nt 2, n_col 1       K 65 0.95 to 1.17   96 0.98 to 1.20   128 1.03 to 1.22   192 1.01 to 1.15   (up to 64 a strip kernel's)
+// Five chunks are read like eight (nt 2 0.92 to 1.05, nt 3 0.94 to 1.06, nt 4 1.01 to 1.14).
+// `lines`: rows begin on lines of 128 bytes.  Where they do not, a product of a single chunk loses as well (1 M rows of 93 columns out of 30 steps 0.88 to 1.04,
+// 786 k of 509 out of 25 0.86 to 0.94; in whole lines 24 steps 1.03 to 1.38).
+constexpr bool wide_long(int nt, int n_col, int K, bool lines)
+{
+    if (nt == 4) return K >= (n_col <= 4 && lines ? 24 : 33);
+    if ((K + WIDE_CHUNK - 1) / WIDE_CHUNK == 5) return false;
+    return nt == 3 ? K >= (n_col > 2 ? 96 : lines ? 24 : 33) : K >= (n_col == 1 ? 65 : 128);
 }
 
 } // namespace slicegcn

@@ -155,7 +155,7 @@ def test_weight_gradients_of_a_group_in_strips_and_of_one_slice_in_tiles(monkeyp
     in_a_group_and_alone(monkeypatch, n, 4, first, hs, self_term)
 
 
-@pytest.mark.parametrize("n,k,first,hs", [(87_403, 3, 37, 100), (66_003, 4, 64, 96), (35_011, 8, 40, 132), (52_451, 2, 47, 260)])
+@pytest.mark.parametrize("n,k,first,hs", [(87_403, 3, 37, 100), (66_003, 4, 64, 96), (35_011, 8, 40, 164), (52_451, 2, 47, 260)])
 def test_group_takes_the_wide_products_and_one_slice_does_not(monkeypatch, n, k, first, hs):
     """Input gradients of wide layers: together the slices of a launch have strips enough for pair_wide_kernel, which forms the two products of each one
     after the other; alone a slice goes to the general kernel: the same bits."""

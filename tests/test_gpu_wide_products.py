@@ -14,7 +14,9 @@ SIZES = [(262_144, 256, 64), (131_073, 4, 160), (87_390, 47, 288), (262_177, 64,
          (262_145, 333, 96), (262_145, 96, 333)]  # three tiles whose weights fill LDS to the last group of k
 # two, three and four tiles of columns a workgroup, two and four chunks ahead, whole and partial last chunks, each forward and as an input gradient
 SIZES += [(262_177, 128, 100), (262_146, 64, 96), (262_149, 96, 40), (262_155, 128, 96), (262_158, 96, 64), (262_155, 96, 128), (262_159, 64, 100),
-          (262_151, 40, 100), (52_450, 64, 320), (52_451, 47, 310), (52_450, 320, 64), (52_451, 310, 47)]
+          (262_151, 40, 100), (262_157, 40, 96)]
+# several workgroups along the columns, and beside them shorter products, which go to the general kernel
+SIZES += [(131_105, 48, 160), (87_390, 100, 288), (65_570, 40, 512), (52_450, 128, 320), (52_451, 310, 47), (52_450, 64, 320)]
 FEW = 4096
 
 
