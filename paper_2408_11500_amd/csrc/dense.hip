@@ -114,10 +114,12 @@ typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4))); // 16-b
 // Workgroup b of a grid of row tiles x column tiles (1-D, 8 row tiles x all column tiles per group of workgroups): the column
 // tiles of one row tile run back to back on the same XCD (workgroup b goes to XCD b mod 8), so the rows are fetched from memory
 // once and re-read from L2.  The last group of 8 row tiles may be partial.
-struct TilePlace { int64_t row_tile; int col_tile; };
-__device__ inline TilePlace tile_place(int64_t b, int n_col_tiles)
+// (In 32 bits: a 64-bit division is as long as a small layer's loads.)
+struct TilePlace { uint32_t row_tile, col_tile; };
+__device__ inline TilePlace tile_place(uint32_t b, uint32_t n_col_tiles)
 {
-    return TilePlace{(b / (8 * n_col_tiles)) * 8 + (b % 8), (int)((b / 8) % n_col_tiles)};
+    const uint32_t group = b / (8 * n_col_tiles);
+    return TilePlace{group * 8 + b % 8, b / 8 - group * n_col_tiles};
 }
 
 // Four consecutive columns per lane and register group of a 32-column tile to row `o` (+ 4 * h + 8 * q); `width` columns exist from
@@ -183,10 +185,9 @@ __device__ __forceinline__ void pair_rows_tile(const PairArgs &a, uint32_t wg, i
     // 69.8 -> 66.8 us, 800 k rows 326 -> 312); with one tile it was slower (20 k rows 32 -> 256 11.1 -> 11.9).
     const int wave = NT == 3 && BWD && !TWO ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6, lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    // tile_place in 32 bits: the 64-bit division is as long as a small layer's loads
-    const uint32_t group = wg / (8u * n_col_tiles);
-    const int64_t row_tile = (int64_t)group * 8 + wg % 8;
-    const int col0 = (int)(wg / 8 - group * n_col_tiles) * BN;
+    const TilePlace place = tile_place(wg, n_col_tiles);
+    const int64_t row_tile = place.row_tile;
+    const int col0 = (int)place.col_tile * BN;
     if (row_tile * 128 >= a.n) return; // uniform per workgroup
     const int chunks = (a.K + KC - 1) / KC, total = TWO ? 2 * chunks : chunks;
 
@@ -1382,10 +1383,9 @@ __device__ __forceinline__ void grad_rows_tile(const ReduceArgs &a, int64_t wg, 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int m = lane & 31, h = lane >> 5;
-    // tile_place in 32 bits and scalar registers (the division is done by vector instructions)
-    const uint32_t group = (uint32_t)wg / (8u * n_tiles);
-    const int col_tile = __builtin_amdgcn_readfirstlane((uint32_t)wg / 8 - group * n_tiles);
-    const int64_t block = (uint32_t)__builtin_amdgcn_readfirstlane(group * 8 + (uint32_t)wg % 8), r_begin = block * a.rows_per_block;
+    const TilePlace place = tile_place((uint32_t)wg, n_tiles); // (the division is done by vector instructions)
+    const int col_tile = __builtin_amdgcn_readfirstlane(place.col_tile);
+    const int64_t block = (uint32_t)__builtin_amdgcn_readfirstlane(place.row_tile), r_begin = block * a.rows_per_block;
     if (r_begin >= a.n) return; // uniform per workgroup
     const int64_t r_end = r_begin + a.rows_per_block < a.n ? r_begin + a.rows_per_block : a.n;
     const int i_base = (col_tile / a.j_tiles) * (WI * MI * 32) + (SPLIT ? 0 : wave / (SPLIT ? 1 : WJ) * (MI * 32));
@@ -2047,13 +2047,13 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
 // (109 TFLOP/s), 169 k rows 312 -> 251 us; three wavefronts per SIMD (two: 3.01 ms), one buffer (two, with half the barriers: 3.14).
 constexpr int GB_T = 128;
 
+template <bool NEAR> // a step's rows lie within 32-bit offsets
 __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs common, const ReduceBatch batch, int n_tiles)
 {
     const ReduceArgs a = slice_of(common, batch, blockIdx.y);
-    // tile_place in 32 bits and scalar registers
-    const uint32_t group = blockIdx.x / (8u * n_tiles);
-    const int col_tile = __builtin_amdgcn_readfirstlane(blockIdx.x / 8 - group * n_tiles);
-    const int64_t block = (uint32_t)__builtin_amdgcn_readfirstlane(group * 8 + blockIdx.x % 8);
+    const TilePlace place = tile_place(blockIdx.x, n_tiles);
+    const int col_tile = __builtin_amdgcn_readfirstlane(place.col_tile);
+    const int64_t block = (uint32_t)__builtin_amdgcn_readfirstlane(place.row_tile);
     __shared__ __attribute__((aligned(16))) float Xs[RED_RK][GB_T];
     __shared__ __attribute__((aligned(16))) float Ps[RED_RK][GB_T];
     const int tid = threadIdx.x;
@@ -2085,10 +2085,9 @@ __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs 
 
     float4 rx[4], rp[4];
     uint32_t rw[4];
-    const bool near = a.ldz < (1 << 24) && a.ldo < (1 << 24) && word_ld < (1 << 24); // a step's rows lie within 32-bit offsets
     const uint32_t ox = (uint32_t)lr * (uint32_t)a.ldz, op = (uint32_t)lr * (uint32_t)a.ldo, ow = (uint32_t)lr * (uint32_t)word_ld;
     auto fetch = [&](int64_t r0, auto whole) {
-        if (whole && near) {
+        if (whole && NEAR) {
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 const int64_t r = r0 + 8 * it;
@@ -2109,18 +2108,26 @@ __global__ __launch_bounds__(256, 3) void grad_big_mfma_kernel(const ReduceArgs 
     // `next`: first row to fetch meanwhile.  The activation bits are applied on the way to LDS, not where they are fetched: the next
     // step's accesses stay in flight behind this one's products.
     auto step = [&](int64_t r0, int64_t next, auto whole, auto more) {
+        if (place_x) {
+#pragma unroll
+            for (int it = 0; it < 4; ++it) xc.place(rx[it]);
+        }
+        if (place_p) {
+#pragma unroll
+            for (int it = 0; it < 4; ++it) pc.place(rp[it]);
+        }
+        if (a.mask) { // a bit of the word, extended to a word
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                auto masked = [&](float v, int c) { return __int_as_float(__float_as_int(v) & __builtin_amdgcn_sbfe((int)rw[it], (j & 31) + c, 1)); };
+                rp[it] = make_float4(masked(rp[it].x, 0), masked(rp[it].y, 1), masked(rp[it].z, 2), masked(rp[it].w, 3));
+            }
+        }
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            float4 x = rx[it], p = rp[it];
-            if (place_x) xc.place(x);
-            if (place_p) pc.place(p);
-            if (a.mask) { // a bit of the word, extended to a word
-                auto masked = [&](float v, int c) { return __int_as_float(__float_as_int(v) & __builtin_amdgcn_sbfe((int)rw[it], (j & 31) + c, 1)); };
-                p = make_float4(masked(p.x, 0), masked(p.y, 1), masked(p.z, 2), masked(p.w, 3));
-            }
-            if (!whole && r0 + lr + 8 * it >= r_end) x = p = make_float4(0.f, 0.f, 0.f, 0.f);
-            *reinterpret_cast<float4 *>(&Xs[lr + 8 * it][c4]) = x;
-            *reinterpret_cast<float4 *>(&Ps[lr + 8 * it][c4]) = p;
+            if (!whole && r0 + lr + 8 * it >= r_end) rx[it] = rp[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+            *reinterpret_cast<float4 *>(&Xs[lr + 8 * it][c4]) = rx[it];
+            *reinterpret_cast<float4 *>(&Ps[lr + 8 * it][c4]) = rp[it];
         }
         __syncthreads();
         if constexpr (decltype(more)::value) fetch(next, std::true_type());
@@ -2391,7 +2398,8 @@ int launch_grad_rows(ReduceArgs r, const ReduceBatch &b, int batch, int products
         });
         break;
     case GradForm::LDS:
-        grad_big_mfma_kernel<<<grid, 256, 0, stream>>>(r, b, f.n_tiles);
+        if (r.ldz < (1 << 24) && r.ldo < (1 << 24) && r.mask_words < (1 << 24)) grad_big_mfma_kernel<true><<<grid, 256, 0, stream>>>(r, b, f.n_tiles);
+        else grad_big_mfma_kernel<false><<<grid, 256, 0, stream>>>(r, b, f.n_tiles);
         break;
     case GradForm::ROWS:
         grid.z = (unsigned)products;
