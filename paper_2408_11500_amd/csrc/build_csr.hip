@@ -78,6 +78,7 @@ __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restri
                                                          Segment *__restrict__ items, TinyRow *__restrict__ tiny, int32_t *__restrict__ long_rows)
 {
     __shared__ int32_t per_wave[4][ROW_KINDS];
+    __shared__ int32_t before[ROW_TINY]; // rows of every counted kind among the workgroups before
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t p = (int64_t)blockIdx.x * TPB + threadIdx.x;
     int kind = -1;
@@ -90,6 +91,8 @@ __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restri
     }
     int32_t rank = 0;
     const int counted = counted_kinds(item_max);
+    // (all kinds at once: one after the other by every thread that needs them, 1.9 M nodes, 7.7 M edges 14.5 instead of 10.9 us)
+    if (FILL && tiny && threadIdx.x < counted) before[threadIdx.x] = counts[threadIdx.x * n_groups + blockIdx.x] - counts[threadIdx.x * n_groups];
 #pragma unroll
     for (int k = 0; k < ROW_KINDS; ++k) {
         if (k >= counted && k < ROW_TINY) continue; // uniform
@@ -109,7 +112,7 @@ __global__ __launch_bounds__(256) void sched_rows_kernel(const int32_t *__restri
     if (kind == ROW_TINY) {
         if (!tiny) return;
         int32_t at = (int32_t)blockIdx.x * TPB + rank; // the rows before this one, less those of the other kinds among the workgroups before
-        for (int k = 0; k < counted; ++k) at -= counts[k * n_groups + blockIdx.x] - counts[k * n_groups];
+        for (int k = 0; k < counted; ++k) at -= before[k];
         const uint32_t more = end > beg ? (uint32_t)(end - beg - 1) : 0u;
         TinyRow r;
         r.row = (uint32_t)row | more << 31;
