@@ -1368,7 +1368,7 @@ __device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatc
 //   WJ > 0  the four wavefronts own tiles of their own, WJ of them along w_out, over all rows (wider dense layers)
 // Column sums (bias gradients) run in row order over the loaded values.
 // A kernel that staged 32 x 32 tiles in LDS re-read its operands per tile and waited at two barriers per 32 rows.  Pairs of products:
-// two slices of 233 k rows 301 x 128 1.65 -> 1.19 ms (64 TFLOP/s), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
+// two slices of 233 k rows 301 x 128 1.65 -> 1.19 ms (0.79 with scalar bases and 32-bit offsets, 96 TFLOP/s), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
 // 256 x 47 1.93 -> 1.40 ms, 60 k rows 64 x 64 46 -> 22 us.  Bound by the loads, one register of two rows' pieces at a time.
 // Grid: x = 8 row blocks x all tiles per group of workgroups (a row block's tiles meet on one XCD), y = slice, z = product.
 template <int MI, int NJ, int WJ>
@@ -2042,9 +2042,10 @@ __global__ __launch_bounds__(256, WPS) void grad_strip64_kernel(const ReduceArgs
 // 64 x 64 quarter (four MFMA accumulators).  Per step 32 rows of the X tile and of the dP tile are
 // staged in LDS (the next step's loads are issued into registers before this step's MFMAs); the
 // node axis is the MFMA's k axis.  32 flop per staged byte instead of 8 for 32 x 32 tiles.  The tiles of a row block run back to back on
-// one XCD (grid as in grad_rows_kernel).  Loads are unconditional and the activation bits are applied on the way to LDS: applied
-// where they were fetched, with a test per row, every step waited for its own accesses.  2.4 M rows 256 x 256 3.66 -> 2.95 ms
-// (109 TFLOP/s), 169 k rows 312 -> 251 us; three wavefronts per SIMD (two: 3.01 ms), one buffer (two, with half the barriers: 3.14).
+// one XCD (grid as in grad_rows_kernel).  Loads are unconditional, in one form per kernel, and columns are moved into place and activation bits applied on
+// the way to LDS, each in one branch a step: with two forms of loads behind a test a step of a tile that is not full waited for its own accesses (1 M rows
+// 65 x 65 401 -> 320 us, 324 k rows 70 x 280 395 -> 325, 400 k rows 128 x 128 178 -> 161, 169 k rows 256 x 256 240 -> 230; 408 k rows 264 x 84, five workgroups on some
+// CUs, 452 -> 426).  Three wavefronts per SIMD (two: 2 % slower), one buffer (two, with half the barriers: 6 %).
 constexpr int GB_T = 128;
 
 template <bool NEAR> // a step's rows lie within 32-bit offsets

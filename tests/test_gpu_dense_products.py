@@ -164,3 +164,33 @@ def test_narrow_products_of_more_than_2_31_rows():
     assert abs(float(db) / total - 1) <= 1024 * 2.0 ** -24 and abs(float(dW) / squares - 1) <= 1025 * 2.0 ** -24
     del x, y, ws
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n,w_in,w_out", [(70, 1470, 1409), (32, 1408, 1537)])
+@pytest.mark.parametrize("far", ["X", "dY"])
+@pytest.mark.parametrize("act", [B.ACT_NONE, B.ACT_RELU])
+def test_gradients_in_wide_tiles_of_rows_far_apart(n, w_in, w_out, far, act):
+    """Tiles of 128 x 128: rows so far apart that a step's do not lie within 32-bit offsets, whole and partial steps and tiles, have the same
+    gradients as the same rows side by side."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X, dY = torch.randn((n, w_in), generator=gen, device="cuda"), torch.randn((n, w_out), generator=gen, device="cuda")
+    mask = torch.randint(-2 ** 31, 2 ** 31 - 1, (n, (w_out + 31) // 32), generator=gen, device="cuda", dtype=torch.int32) if act else None
+    W = torch.zeros((w_in, w_out), device="cuda")
+    ws = torch.empty(B.slicegcn_linear_bwd_full_workspace_bytes(n, w_in, w_out), dtype=torch.uint8, device="cuda")
+
+    def grads(X, dY):
+        dW, db = torch.empty_like(W), torch.empty(w_out, device="cuda")
+        B.slicegcn_linear_bwd(X, W, mask, dY, None, dW, db, ws, act=act)
+        return dW, db
+
+    want = grads(X, dY)
+    near = X if far == "X" else dY
+    apart = torch.empty(n * (2 ** 24 + 3), device="cuda").as_strided(near.shape, (2 ** 24 + 3, 1))
+    apart.copy_(near)
+    got = grads(apart, dY) if far == "X" else grads(X, apart)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    G = dY.double()
+    if act:
+        G = G * torch.stack([(mask >> j) & 1 for j in range(32)], dim=2).reshape(n, -1)[:, :w_out]
+    assert_fp32(want[0], X.double().t() @ G, X.double().abs().t() @ G.abs(), "dW")
+    assert_fp32(want[1], G.sum(0), G.abs().sum(0), "db")
