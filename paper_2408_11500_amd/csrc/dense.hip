@@ -2417,8 +2417,8 @@ int launch_grad_rows(ReduceArgs r, const ReduceBatch &b, int batch, int products
 // either is a chain of a few dependent loads in a fraction of the chip, one launch does both.  The first `grads` workgroups of a slice form
 // weight gradients (products x grad_x), the others what pair_strip32_kernel or pair_rows_kernel would.  Backward passes of dense
 // layers, in two launches / one: 1000 rows 64 -> 8 10.1 / 6.8 us, 2048 rows 64 -> 64 11.9 / 8.8, 20 k rows 64 -> 64 27.2 / 23.1, 60 k rows
-// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1, 169 k rows 256 -> 40 232 / 220, 400 k rows 128 -> 40 300 / 262 (with the two
-// kinds of workgroups in turn 337 and 392: the long ones have to start first).  The two products of a slice layer, dZ and T, are workgroups of
+// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1, 169 k rows 256 -> 40 159 / 148, 400 k rows 128 -> 40 254 / 216 (with the two
+// kinds of workgroups in turn half as long again: the long ones have to start first).  The two products of a slice layer, dZ and T, are workgroups of
 // their own (pair_x each): half the chain, and nothing is shared but dHout.  Backward passes of slice layers, two launches / one / one with the
 // products apart: 2048 rows 64 -> 32 18.5 / 12.9 / 13.0 us, 30 k rows 64 -> 64 39.5 / 35.9 / 33.6, 5000 rows 64 -> 64 22.3 / 17.8 / 15.7.
 template <int WJ, int NT> // NT: tiles of 32 columns, 0 for the strips
@@ -2452,7 +2452,9 @@ inline bool may_share(const void *o, int64_t ldo, int64_t wo, const void *x, int
 // launch_grad_rows, and launch_pair<true> for `list` in the same launch where the gradients take their smallest tiles, which leave the chip
 // idle (with larger ones 2.4 M rows 256 -> 47 take 2.86 ms together and 2.64 apart; up to 32 -> 3, where they are the only tiles, one launch is
 // faster on any number of rows: 32 -> 2, 169 k rows 31.2 / 24.1 us, 800 k 70 / 55, 2.4 M 196 / 184), and nothing that is stored is read by the other (an
-// input gradient may take the place of an operand); `pair_done` says whether it was.  A layer whose gradients are cut into chains shorter
+// input gradient may take the place of an operand); `pair_done` says whether it was.  Also where the input gradient alone would be
+// pair_wide_kernel's: its product fills the waits of the gradients' loads (apart, with that kernel / together: 262 k rows 128 -> 40 129 / 127 us, 450 k 259 / 232,
+// 1 M 495 / 491, 233 k 256 -> 41 258 / 237, 500 k 497 / 488, 1 M 100 -> 64 529 / 495, 200 k 512 -> 40 423 / 397).  A layer whose gradients are cut into chains shorter
 // than RED_ROWS leaves the LDS form for it (5000 rows 96 -> 96 19.5 / 14.9 us, 2048 rows 256 -> 256 34.7 / 30.3).
 int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, int products, bool big, const PairArgs *list, bool *pair_done,
                           hipStream_t stream)
