@@ -1368,8 +1368,11 @@ __device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatc
 //   WJ > 0  the four wavefronts own tiles of their own, WJ of them along w_out, over all rows (wider dense layers)
 // Column sums (bias gradients) run in row order over the loaded values.
 // A kernel that staged 32 x 32 tiles in LDS re-read its operands per tile and waited at two barriers per 32 rows.  Pairs of products:
-// two slices of 233 k rows 301 x 128 1.65 -> 1.19 ms (0.79 with scalar bases and 32-bit offsets, 96 TFLOP/s), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
-// 256 x 47 1.93 -> 1.40 ms, 60 k rows 64 x 64 46 -> 22 us.  Bound by the loads, one register of two rows' pieces at a time.
+// two slices of 233 k rows 301 x 128 1.65 -> 1.19 ms (0.79 with scalar bases and 32-bit offsets), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
+// 256 x 47 1.93 -> 1.40 ms, 60 k rows 64 x 64 46 -> 22 us.  Bound by the loads, one register of two rows' pieces at a time.  A load's base comes from the
+// one before it by an addition: with a product of row and leading dimension each, some 140 scalar multiplications per step, chains of few rows were 2 to 6 % slower than
+// with an address per lane, and all of them slower than now: backward passes of layers 7.6 k rows 72 -> 222 39.0 -> 36.3 us, 30 k rows 100 -> 64 46.1 -> 42.1;
+// 169 k rows 256 x 40 127 -> 97, 300 k 64 x 200 221 -> 153, 2.4 M 47 x 256 1.26 -> 1.18 ms, without activation bits 1.09 / 1.10 (500 k 40 x 300 421 / 436 us).
 // Grid: x = 8 row blocks x all tiles per group of workgroups (a row block's tiles meet on one XCD), y = slice, z = product.
 template <int MI, int NJ, int WJ>
 __device__ __forceinline__ void grad_rows_tile(const ReduceArgs &a, int64_t wg, bool self, int n_tiles) // self: the product Hin^T dHout
@@ -1413,9 +1416,12 @@ __device__ __forceinline__ void grad_rows_tile(const ReduceArgs &a, int64_t wg, 
     float nx[PAIRS][MI], np[PAIRS][NJ], nf[PAIRS];
     uint32_t nw[PAIRS][NJ];
     auto row_of = [&](int64_t r0, int p) { return r0 + (SPLIT ? 32 * (p / 4) + 8 * wave + 2 * (p % 4) : 2 * p); }; // of pair p, and the next one
+    // from a pair to the next, and from a wavefront's eight rows to its next eight (opaque, or the compiler makes products of them again)
+    int64_t two_x = 2 * ldx, two_g = 2 * a.ldo, two_w = 2 * a.mask_words, far_x = 26 * ldx, far_g = 26 * a.ldo, far_w = 26 * a.mask_words;
+    asm("" : "+s"(two_x), "+s"(two_g), "+s"(two_w), "+s"(far_x), "+s"(far_g), "+s"(far_w));
     auto fetch = [&](int64_t r0) {
         if (near && r0 + ROWS <= r_end) {
-            int64_t at = r0;
+            int64_t at = row_of(r0, 0);
             asm("" : "+s"(at)); // (or the compiler keeps a 64-bit address per load and lane, steps them all, and spills)
             const float *x = X + at * ldx, *g = a.dHout + at * a.ldo;
             uint32_t ox[MI], og[NJ];
@@ -1425,23 +1431,28 @@ __device__ __forceinline__ void grad_rows_tile(const ReduceArgs &a, int64_t wg, 
             for (int t = 0; t < NJ; ++t) og[t] = fresh(hg + cg[t]);
 #pragma unroll
             for (int p = 0; p < PAIRS; ++p) {
-                const int64_t r = row_of(0, p);
 #pragma unroll
-                for (int t = 0; t < MI; ++t) nx[p][t] = *plus(x + r * ldx, ox[t]);
+                for (int t = 0; t < MI; ++t) nx[p][t] = *plus(x, ox[t]);
 #pragma unroll
-                for (int t = 0; t < NJ; ++t) np[p][t] = *plus(g + r * a.ldo, og[t]);
+                for (int t = 0; t < NJ; ++t) np[p][t] = *plus(g, og[t]);
+                x += SPLIT && p % 4 == 3 ? far_x : two_x;
+                g += SPLIT && p % 4 == 3 ? far_g : two_g;
             }
             if (mask) {
+                const uint32_t *w = mask + at * a.mask_words;
+                uint32_t ow[NJ];
 #pragma unroll
-                for (int t = 0; t < NJ; ++t) {
-                    const uint32_t ow = fresh(hw + cw[t]);
+                for (int t = 0; t < NJ; ++t) ow[t] = fresh(hw + cw[t]);
 #pragma unroll
-                    for (int p = 0; p < PAIRS; ++p) nw[p][t] = *plus(mask + row_of(at, p) * a.mask_words, ow);
+                for (int p = 0; p < PAIRS; ++p) {
+#pragma unroll
+                    for (int t = 0; t < NJ; ++t) nw[p][t] = *plus(w, ow[t]);
+                    w += SPLIT && p % 4 == 3 ? far_w : two_w;
                 }
             }
             if (x_scale) {
 #pragma unroll
-                for (int p = 0; p < PAIRS; ++p) nf[p] = *plus(x_scale + row_of(at, p), h);
+                for (int p = 0; p < PAIRS; ++p) nf[p] = *plus(x_scale + at + (row_of(0, p) - row_of(0, 0)), h);
             }
         } else { // rows past the end re-read the last (what they give is zeroed below)
 #pragma unroll
