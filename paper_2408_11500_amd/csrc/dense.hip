@@ -2428,7 +2428,7 @@ int launch_grad_rows(ReduceArgs r, const ReduceBatch &b, int batch, int products
 // either is a chain of a few dependent loads in a fraction of the chip, one launch does both.  The first `grads` workgroups of a slice form
 // weight gradients (products x grad_x), the others what pair_strip32_kernel or pair_rows_kernel would.  Backward passes of dense
 // layers, in two launches / one: 1000 rows 64 -> 8 10.1 / 6.8 us, 2048 rows 64 -> 64 11.9 / 8.8, 20 k rows 64 -> 64 27.2 / 23.1, 60 k rows
-// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1, 169 k rows 256 -> 40 159 / 148, 400 k rows 128 -> 40 254 / 216 (with the two
+// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1, 169 k rows 256 -> 40 159 / 148 (with the two
 // kinds of workgroups in turn half as long again: the long ones have to start first).  The two products of a slice layer, dZ and T, are workgroups of
 // their own (pair_x each): half the chain, and nothing is shared but dHout.  Backward passes of slice layers, two launches / one / one with the
 // products apart: 2048 rows 64 -> 32 18.5 / 12.9 / 13.0 us, 30 k rows 64 -> 64 39.5 / 35.9 / 33.6, 5000 rows 64 -> 64 22.3 / 17.8 / 15.7.
@@ -2460,12 +2460,13 @@ inline bool may_share(const void *o, int64_t ldo, int64_t wo, const void *x, int
     return o && x && p < q + 4 * ((n - 1) * ldx + wx) && q < p + 4 * ((n - 1) * ldo + wo);
 }
 
+constexpr int64_t LONG_PRODUCT = 72000000; // elements of the input gradient
 // launch_grad_rows, and launch_pair<true> for `list` in the same launch where the gradients take their smallest tiles, which leave the chip
 // idle (with larger ones 2.4 M rows 256 -> 47 take 2.86 ms together and 2.64 apart; up to 32 -> 3, where they are the only tiles, one launch is
 // faster on any number of rows: 32 -> 2, 169 k rows 31.2 / 24.1 us, 800 k 70 / 55, 2.4 M 196 / 184), and nothing that is stored is read by the other (an
-// input gradient may take the place of an operand); `pair_done` says whether it was.  Also where the input gradient alone would be
-// pair_wide_kernel's: its product fills the waits of the gradients' loads (apart, with that kernel / together: 262 k rows 128 -> 40 129 / 127 us, 450 k 259 / 232,
-// 1 M 495 / 491, 233 k 256 -> 41 258 / 237, 500 k 497 / 488, 1 M 100 -> 64 529 / 495, 200 k 512 -> 40 423 / 397).  A layer whose gradients are cut into chains shorter
+// input gradient may take the place of an operand); `pair_done` says whether it was.  Not where the input gradient alone is
+// pair_wide_kernel's and long (together / apart: 262 k rows 128 -> 40 121 / 126 us, 350 k 154 / 158, 450 k 207 / 204, 600 k 265 / 250, 1 M 441 / 398, 233 k 256 -> 41
+// 212 / 206, 300 k 264 / 252, 500 k 432 / 394, 200 k 512 -> 40 347 / 335; 700 k 100 -> 36 299 / 306, 1 M 100 -> 64 444 / 442).  A layer whose gradients are cut into chains shorter
 // than RED_ROWS leaves the LDS form for it (5000 rows 96 -> 96 19.5 / 14.9 us, 2048 rows 256 -> 256 34.7 / 30.3).
 int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, int products, bool big, const PairArgs *list, bool *pair_done,
                           hipStream_t stream)
@@ -2474,7 +2475,8 @@ int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, 
     if (!list) return launch_grad_rows(r, b, batch, products, big, stream);
     const GradForm g = grad_form(r, batch, products, big, r.rows_per_block == RED_ROWS);
     const PairForm f = pair_form(list, batch, true, false);
-    bool merge = g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 &&
+    const bool apart = r.n * batch * list[0].Nout >= LONG_PRODUCT && pair_form(list, batch, true).kernel == PairForm::WIDE;
+    bool merge = !apart && g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 &&
                  (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && (f.nt == 1 || (f.nt == 2 && g.wj != 0)))) &&
                  products * g.blocks + 2 * f.blocks <= MAX_GRID;
     for (int i = 0; merge && i < batch; ++i)

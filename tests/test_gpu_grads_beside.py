@@ -31,6 +31,12 @@ def test_linear_bwd_together_and_apart(n, w_in, w_out):
     assert torch.equal(over, alone) and all(map(torch.equal, got, want))
 
 
+@pytest.mark.parametrize("n,w_in,w_out", [(262_149, 128, 40), (562_501, 128, 40), (281_251, 256, 33), (281_249, 256, 64), (140_700, 512, 40)])
+def test_linear_bwd_of_many_rows(n, w_in, w_out):
+    """Below and above the length from which the input gradient goes to the kernel of wide products instead, at 72 M elements."""
+    test_linear_bwd_together_and_apart(n, w_in, w_out)
+
+
 @pytest.mark.parametrize("n", [1, 40, 3001, 70_001])
 @pytest.mark.parametrize("w_in,w_out", [(1, 5), (3, 64), (4, 4), (33, 32), (64, 64), (100, 20), (128, 9), (130, 33), (301, 64)])
 @pytest.mark.parametrize("self_term", [True, False])
