@@ -1229,8 +1229,8 @@ inline PairForm pair_form(const PairArgs *list, int batch, bool backward, bool w
         for (int t = 3; t <= 4; ++t)
             if (padded(t) <= padded(wt) && a.K <= wide_k(t)) wt = t;
         const int n_col = padded(wt) / wt, walkers = wide_walkers(n_col * batch);
-        const bool lines = a.ldo1 % 32 == 0 && (!a.O2 || a.ldo2 % 32 == 0);
-        if (padded(wt) <= padded(nt) && a.K <= wide_k(wt) && wide_long(wt, n_col, a.K, lines) && wide_even(wt, n_col * batch, a.K, strips))
+        const bool lines = a.ldo1 % 32 == 0 && (!a.O2 || a.ldo2 % 32 == 0), bits = backward ? a.mask != nullptr : a.act == SLICEGCN_ACT_RELU;
+        if (padded(wt) <= padded(nt) && a.K <= wide_k(wt) && wide_long(wt, n_col, a.K, lines, bits, two) && wide_even(n_col * batch, strips))
             return PairForm{PairForm::WIDE, two, 8 * (int64_t)walkers * n_col, wt, n_col};
     }
     // everything else: 1-D grid per slice, 8 row tiles x all column tiles per group of workgroups (see the kernel)
@@ -1258,9 +1258,8 @@ void launch_wide(const PairArgs &a, const PairBatch &b, dim3 grid, int n_col, hi
         if (a.K % 32 == 0) pair_wide_kernel<NT, r.value, false, BWD><<<grid, 64 * WIDE_WAVES, 0, stream>>>(a, b, n_col, walkers);
         else pair_wide_kernel<NT, r.value, true, BWD><<<grid, 64 * WIDE_WAVES, 0, stream>>>(a, b, n_col, walkers);
     };
-    if constexpr (NT > 2) // two tiles: longer products alone (wide_long)
-        if (a.K <= 64) return launch(std::integral_constant<int, 2>());
-    launch(std::integral_constant<int, 4>());
+    if (a.K <= 64) launch(std::integral_constant<int, 2>());
+    else launch(std::integral_constant<int, 4>());
 }
 template <bool BWD>
 int launch_wide(const PairArgs *list, int batch, const PairForm &f, hipStream_t stream)

@@ -27,29 +27,27 @@ constexpr int wide_walkers(int per_strip) { return WIDE_CUS / per_strip; }
 //     22 (11)            24.3 k 175 / 203, 174 / 216           95.3 k 640 / 762, 647 / 780
 //     17 (17)            15.7 k 178 / 263, 179 / 279           61.7 k 646 / 979, 661 / 999
 //     32 of 40           eight slices, input gradients 320 <- 320 of 19.7 k rows 693 / 912 (the last workgroups start when the others end)
-// With 28 two tiles a workgroup lose at any length (280 k rows 448 columns out of 128 steps 0.94 to 1.01 times as fast, of 192 0.95 to 1.00).
-constexpr bool wide_even(int nt, int per_strip, int K, long long strips)
+// (one shape each; over drawn ones, times as fast as pair_rows_kernel, geometric mean: 32 of 32 1.13 to 1.20, 30 1.03 to 1.16, 28 1.01 to 1.06, 27 1.04).
+constexpr bool wide_even(int per_strip, long long strips) { return wide_walkers(per_strip) * per_strip >= 27 && strips * per_strip >= 8192; }
+// Whether products of K steps have enough to multiply, by the tiles of 32 columns a workgroup takes, the workgroups along the columns, whether rows begin on lines
+// of 128 bytes (`lines`) and whether activation bits are read or written (`bits`).  Short ones are bound by what is stored, and a row's columns come from n_col
+// workgroups that drift apart: lines that two of them share are written in parts.  Times as fast as pair_rows_kernel, geometric mean (and the
+// tenth from below) of 2700 drawn products of 30 k to 1.2 M rows, forward and input gradients, into the same memory (results in memory of their own differ by up
+// to a fifth with the place alone):
+//     K         nt 4, lines             nt 4                    nt 3, lines             nt 3                    nt 2
+//     4 to 7    0.98 (bits 1.08)        0.86 (0.94)             0.97 (1.01)             0.92 (0.99)             0.87 (0.88 to 0.95)
+//     8 to 15   1.04 (1.11)             0.95 (1.01)             1.03 (1.05)             0.94 (1.02)             0.90 (0.90 to 0.96)
+//     16 to 23  1.15 (1.20)             1.02 (1.08)             1.06 (1.12)             1.10 (1.11)             0.95 to 0.97
+//     24 to 31  1.11 to 1.25            1.09 to 1.19            1.08 to 1.22            1.12 to 1.21            1.08
+//     33 to 64  1.16 to 1.33 (least tenth 0.98 to 1.23)         1.13 to 1.32 (1.02 to 1.24)                     1.06 (0.92)
+//     65 to 128 1.15 to 1.23 (1.05 to 1.13)                     1.11 to 1.23 (1.01 to 1.13)                     1.06 to 1.21 (0.98 to 1.13)
+//     to 160, five chunks, read like eight  1.09 to 1.13        1.04 to 1.11                                    1.00 to 1.01 (0.94)
+//     above     1.13 to 1.21                                    1.10 to 1.18                                    1.08 to 1.15
+// In lines up to 15 steps forward products with five workgroups or more along the columns 0.92 to 0.98.  The two input gradients of a slice layer (`two`), of which
+// pair_rows_kernel loads dH_out once: 8 to 15 steps, not in lines, whole backward passes 1.02 to 1.06, up to 7 1.01 to 1.03.
+constexpr bool wide_long(int nt, int n_col, int K, bool lines, bool bits, bool two)
 {
-    const int used = wide_walkers(per_strip) * per_strip;
-    return used >= 30 ? strips * per_strip >= 8192 : used >= 28 && nt >= 3 && K >= 96 && strips * per_strip >= 12288;
-}
-// Whether products of K steps have enough to multiply, by the tiles of 32 columns a workgroup takes and the workgroups along the columns.  Short ones are bound
-// by what is stored, and a row's columns come from n_col workgroups that drift apart: lines that two of them share are written in parts, and the rows
-// are read n_col times.  Times as fast as pair_rows_kernel, forward and input gradients of 280 k and 900 k rows, stored in whole lines or not:
-//     nt 4, n_col 1 to 4  K 8 0.89 to 1.40   16 0.93 to 1.47   24 1.00 to 1.48   33 0.97 to 1.22   64 0.98 to 1.13   128 1.03 to 1.15
-//     nt 4, n_col 5 to 8  K 8 0.69 to 1.38   16 0.74 to 1.49   24 0.84 to 1.43   33 0.98 to 1.17   64 1.03 to 1.12   128 1.04 to 1.18
-//     nt 3, n_col 1, 2    K 8 0.89 to 1.14   16 0.99 to 1.21   24 1.03 to 1.30   33 0.99 to 1.23   64 0.96 to 1.23   128 0.99 to 1.17
-//     nt 3, n_col 3 to 6  K 8 0.68 to 1.29   16 0.83 to 1.27   24 0.92 to 1.29   33 0.88 to 1.23   64 0.92 to 1.13    96 0.98 to 1.11   128 1.02 to 1.12
-//     nt 2, n_col 5       K 8 0.70 to 1.03   16 0.83 to 1.03   33 0.85 to 1.05   64 0.87 to 0.98   96 0.93 to 1.01   128 1.00 to 1.06   192 1.00 to 1.10
-//     nt 2, n_col 1       K 65 0.95 to 1.17   96 0.98 to 1.20   128 1.03 to 1.22   192 1.01 to 1.15   (up to 64 a strip kernel's)
-// Five chunks are read like eight (nt 2 0.92 to 1.05, nt 3 0.94 to 1.06, nt 4 1.01 to 1.14).
-// `lines`: rows begin on lines of 128 bytes.  Where they do not, a product of a single chunk loses as well (1 M rows of 93 columns out of 30 steps 0.88 to 1.04,
-// 786 k of 509 out of 25 0.86 to 0.94; in whole lines 24 steps 1.03 to 1.38).
-constexpr bool wide_long(int nt, int n_col, int K, bool lines)
-{
-    if (nt == 4) return K >= (n_col <= 4 && lines ? 24 : 33);
-    if ((K + WIDE_CHUNK - 1) / WIDE_CHUNK == 5) return false;
-    return nt == 3 ? K >= (n_col > 2 ? 96 : lines ? 24 : 33) : K >= (n_col == 1 ? 65 : 128);
+    return nt == 2 ? K >= 24 : two || K >= 16 || (lines && n_col <= 4 && K >= (bits ? 4 : 8));
 }
 
 } // namespace slicegcn

@@ -15,8 +15,8 @@ SIZES = [(262_144, 256, 64), (131_073, 4, 160), (87_390, 47, 288), (262_177, 64,
 # two, three and four tiles of columns a workgroup, two and four chunks ahead, whole and partial last chunks, each forward and as an input gradient
 SIZES += [(262_177, 128, 100), (262_146, 64, 96), (262_149, 96, 40), (262_155, 128, 96), (262_158, 96, 64), (262_155, 96, 128), (262_159, 64, 100),
           (262_151, 40, 100), (262_157, 40, 96)]
-# several workgroups along the columns, and beside them shorter products, which go to the general kernel
-SIZES += [(131_105, 48, 160), (87_390, 100, 288), (65_570, 40, 512), (52_450, 128, 320), (52_451, 310, 47), (52_450, 64, 320)]
+# several workgroups along the columns, five with two tiles each and up to two chunks of k among them, and beside them shorter products, which go to the general kernel
+SIZES += [(52_452, 47, 310), (52_453, 320, 64), (131_105, 48, 160), (87_390, 100, 288), (65_570, 40, 512), (52_450, 128, 320), (52_451, 310, 47), (52_450, 64, 320)]
 FEW = 4096
 
 
@@ -65,7 +65,7 @@ def test_wide_product_keeps_rows_with_infinities_apart():
     assert torch.equal(Y, Z)
 
 
-@pytest.mark.parametrize("n,w_in,w_out", [(262_177, 128, 128), (262_150, 96, 65), (262_151, 70, 36), (131_080, 301, 33), (87_400, 260, 100)])
+@pytest.mark.parametrize("n,w_in,w_out", [(262_177, 128, 128), (262_150, 96, 65), (262_151, 70, 36), (131_080, 301, 33), (87_400, 260, 100), (131_081, 250, 9), (262_161, 90, 4)])
 def test_wide_input_gradients_of_a_layer_same_bits_as_few_rows(n, w_in, w_out):
     """A graph of pairs and single nodes: its rows can be worked on a few at a time.  dZ takes row factors and the activation bits, T neither."""
     gen = torch.Generator(device="cuda").manual_seed(n)

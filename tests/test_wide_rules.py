@@ -31,27 +31,26 @@ def test_weights_requested_lie_in_lds(tmp_path):
 
 
 def test_grids_fill_the_chip_once(tmp_path):
-    """No launch leaves more than an eighth of the CUs idle, and none has more workgroups than there are CUs, each of which a workgroup takes whole."""
+    """No launch leaves more than five of the 32 CUs that share an L2 idle, and none has more workgroups than there are CUs, each of which a workgroup takes whole."""
     run(tmp_path, """
-    for (int nt = 2; nt <= 4; ++nt)
-        for (int K : {4, 96, 512})
-            for (int per_strip = 1; per_strip <= 1024; ++per_strip)
-                for (long long strips : {1LL, 255LL, 256LL, 820LL, 8192LL, 1LL << 20, 1LL << 26}) {
-                    const int used = wide_walkers(per_strip) * per_strip;
-                    const bool even = wide_even(nt, per_strip, K, strips);
-                    if (used > WIDE_CUS || (even && used < 28)) { std::printf("%d: %d of %d", per_strip, used, WIDE_CUS); return 1; }
-                    if (used == WIDE_CUS && strips == 8192 && !even) { std::printf("%d fills them", per_strip); return 1; }
-                }""")
+    for (int per_strip = 1; per_strip <= 1024; ++per_strip)
+        for (long long strips : {1LL, 255LL, 256LL, 820LL, 8192LL, 1LL << 20, 1LL << 26}) {
+            const int used = wide_walkers(per_strip) * per_strip;
+            const bool even = wide_even(per_strip, strips);
+            if (used > WIDE_CUS || (even && used < 27)) { std::printf("%d: %d of %d", per_strip, used, WIDE_CUS); return 1; }
+            if (used == WIDE_CUS && strips == 8192 && !even) { std::printf("%d fills them", per_strip); return 1; }
+        }""")
 
 
 def test_products_too_short_for_their_columns(tmp_path):
-    """Shapes that were measured slower than by the general kernel, and beside them shapes that are faster: tiles a workgroup takes, workgroups along the
-    columns, steps of k, rows that begin on whole lines."""
-    slower = [(2, 5, 64, 1), (2, 7, 96, 1), (2, 5, 160, 1), (3, 5, 16, 0), (3, 6, 8, 0), (3, 3, 33, 1), (3, 1, 12, 0), (3, 1, 130, 1), (2, 1, 64, 1),
-              (4, 8, 24, 0), (4, 5, 16, 1), (4, 2, 8, 1), (4, 4, 25, 0), (3, 1, 30, 0)]
-    faster = [(2, 5, 128, 1), (2, 1, 96, 0), (3, 5, 128, 0), (3, 2, 48, 1), (4, 8, 64, 0), (4, 4, 24, 1), (4, 2, 160, 0), (4, 1, 256, 0)]
-    table = lambda shapes: ", ".join("{%d, %d, %d, %d}" % s for s in shapes)
+    """Kinds of shapes that are slower than by the general kernel on average, and beside them kinds that are faster: tiles a workgroup takes, workgroups along the
+    columns, steps of k, rows that begin on whole lines, activation bits, two products."""
+    slower = [(2, 5, 16, 1, 1, 0), (2, 7, 23, 1, 0, 1), (3, 1, 7, 0, 1, 0), (3, 5, 15, 0, 0, 0), (3, 6, 15, 1, 1, 0), (4, 2, 15, 0, 0, 0), (4, 8, 8, 0, 1, 0), (4, 5, 15, 1, 0, 0),
+              (4, 2, 7, 1, 0, 0)]
+    faster = [(2, 5, 24, 0, 0, 0), (2, 5, 128, 1, 0, 1), (2, 1, 96, 0, 1, 0), (3, 1, 16, 0, 0, 0), (3, 6, 48, 1, 0, 0), (3, 2, 130, 0, 0, 1), (4, 1, 8, 1, 0, 0), (4, 4, 4, 1, 1, 0),
+              (4, 8, 16, 0, 0, 0), (4, 2, 160, 0, 1, 0), (3, 2, 4, 0, 1, 1)]
+    table = lambda shapes: ", ".join("{%d, %d, %d, %d, %d, %d}" % s for s in shapes)
     run(tmp_path, """
-    const int slower[][4] = {%s}, faster[][4] = {%s};
-    for (auto &s : slower) if (wide_long(s[0], s[1], s[2], s[3])) { std::printf("%%d %%d %%d", s[0], s[1], s[2]); return 1; }
-    for (auto &s : faster) if (!wide_long(s[0], s[1], s[2], s[3])) { std::printf("%%d %%d %%d", s[0], s[1], s[2]); return 1; }""" % (table(slower), table(faster)))
+    const int slower[][6] = {%s}, faster[][6] = {%s};
+    for (auto &s : slower) if (wide_long(s[0], s[1], s[2], s[3], s[4], s[5])) { std::printf("%%d %%d %%d", s[0], s[1], s[2]); return 1; }
+    for (auto &s : faster) if (!wide_long(s[0], s[1], s[2], s[3], s[4], s[5])) { std::printf("%%d %%d %%d", s[0], s[1], s[2]); return 1; }""" % (table(slower), table(faster)))
