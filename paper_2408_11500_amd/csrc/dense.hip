@@ -2465,7 +2465,8 @@ constexpr int64_t LONG_PRODUCT = 72000000; // elements of the input gradient
 // faster on any number of rows: 32 -> 2, 169 k rows 31.2 / 24.1 us, 800 k 70 / 55, 2.4 M 196 / 184), and nothing that is stored is read by the other (an
 // input gradient may take the place of an operand); `pair_done` says whether it was.  Not where the input gradient alone is
 // pair_wide_kernel's and long (together / apart: 262 k rows 128 -> 40 121 / 126 us, 350 k 154 / 158, 450 k 207 / 204, 600 k 265 / 250, 1 M 441 / 398, 233 k 256 -> 41
-// 212 / 206, 300 k 264 / 252, 500 k 432 / 394, 200 k 512 -> 40 347 / 335; 700 k 100 -> 36 299 / 306, 1 M 100 -> 64 444 / 442).  A layer whose gradients are cut into chains shorter
+// 212 / 206, 300 k 264 / 252, 500 k 432 / 394, 200 k 512 -> 40 347 / 335; 700 k 100 -> 36 299 / 306, 1 M 100 -> 64 444 / 442,
+// 128 -> 28 356 / 319; but fewer steps 600 k 128 -> 20 194 / 201, 400 k 224 -> 16 without activation bits 233 / 248, and two tiles a workgroup 300 k 310 -> 40 300 / 315).  A layer whose gradients are cut into chains shorter
 // than RED_ROWS leaves the LDS form for it (5000 rows 96 -> 96 19.5 / 14.9 us, 2048 rows 256 -> 256 34.7 / 30.3).
 int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, int products, bool big, const PairArgs *list, bool *pair_done,
                           hipStream_t stream)
@@ -2474,7 +2475,8 @@ int launch_grads_and_pair(const ReduceArgs &r, const ReduceBatch &b, int batch, 
     if (!list) return launch_grad_rows(r, b, batch, products, big, stream);
     const GradForm g = grad_form(r, batch, products, big, r.rows_per_block == RED_ROWS);
     const PairForm f = pair_form(list, batch, true, false);
-    const bool apart = r.n * batch * list[0].Nout >= LONG_PRODUCT && pair_form(list, batch, true).kernel == PairForm::WIDE;
+    const PairForm alone = pair_form(list, batch, true);
+    const bool apart = alone.kernel == PairForm::WIDE && alone.nt > 2 && list[0].K >= 24 && r.n * batch * list[0].Nout >= LONG_PRODUCT;
     bool merge = !apart && g.kernel == GradForm::ROWS && g.mi == 1 && g.nj == 1 &&
                  (f.kernel == PairForm::STRIP32 || (f.kernel == PairForm::ROWS && (f.nt == 1 || (f.nt == 2 && g.wj != 0)))) &&
                  products * g.blocks + 2 * f.blocks <= MAX_GRID;
