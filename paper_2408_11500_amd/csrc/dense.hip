@@ -1367,7 +1367,7 @@ __device__ inline ReduceArgs slice_of(const ReduceArgs &common, const ReduceBatc
 //   WJ > 0  the four wavefronts own tiles of their own, WJ of them along w_out, over all rows (wider dense layers)
 // Column sums (bias gradients) run in row order over the loaded values.
 // A kernel that staged 32 x 32 tiles in LDS re-read its operands per tile and waited at two barriers per 32 rows.  Pairs of products:
-// two slices of 233 k rows 301 x 128 1.65 -> 1.19 ms (0.79 with scalar bases and 32-bit offsets), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
+// two slices of 233 k rows 301 x 128 1.65 -> 1.19 ms (0.75 with scalar bases and 32-bit offsets, 102 TFLOP/s), 800 k rows 64 x 64 338 -> 235, 169 k rows 64 x 64 76 -> 63; dense layers: 2.4 M rows
 // 256 x 47 1.93 -> 1.40 ms, 60 k rows 64 x 64 46 -> 22 us.  Bound by the loads, one register of two rows' pieces at a time.  A load's base comes from the
 // one before it by an addition: with a product of row and leading dimension each, some 140 scalar multiplications per step, chains of few rows were 2 to 6 % slower than
 // with an address per lane, and all of them slower than now: backward passes of layers 7.6 k rows 72 -> 222 39.0 -> 36.3 us, 30 k rows 100 -> 64 46.1 -> 42.1;
@@ -2427,7 +2427,7 @@ int launch_grad_rows(ReduceArgs r, const ReduceBatch &b, int batch, int products
 // either is a chain of a few dependent loads in a fraction of the chip, one launch does both.  The first `grads` workgroups of a slice form
 // weight gradients (products x grad_x), the others what pair_strip32_kernel or pair_rows_kernel would.  Backward passes of dense
 // layers, in two launches / one: 1000 rows 64 -> 8 10.1 / 6.8 us, 2048 rows 64 -> 64 11.9 / 8.8, 20 k rows 64 -> 64 27.2 / 23.1, 60 k rows
-// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1, 169 k rows 256 -> 40 159 / 148 (with the two
+// 256 -> 64 99 / 90, 100 k rows 64 -> 64 49.6 / 41.1, 169 k rows 256 -> 40 152 / 145 (with the two
 // kinds of workgroups in turn half as long again: the long ones have to start first).  The two products of a slice layer, dZ and T, are workgroups of
 // their own (pair_x each): half the chain, and nothing is shared but dHout.  Backward passes of slice layers, two launches / one / one with the
 // products apart: 2048 rows 64 -> 32 18.5 / 12.9 / 13.0 us, 30 k rows 64 -> 64 39.5 / 35.9 / 33.6, 5000 rows 64 -> 64 22.3 / 17.8 / 15.7.
