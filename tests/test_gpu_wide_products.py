@@ -17,6 +17,8 @@ SIZES += [(262_177, 128, 100), (262_146, 64, 96), (262_149, 96, 40), (262_155, 1
           (262_151, 40, 100), (262_157, 40, 96)]
 # several workgroups along the columns, five with two tiles each and up to two chunks of k among them, and beside them shorter products, which go to the general kernel
 SIZES += [(52_452, 47, 310), (52_453, 320, 64), (131_105, 48, 160), (87_390, 100, 288), (65_570, 40, 512), (52_450, 128, 320), (52_451, 310, 47), (52_450, 64, 320)]
+# less than a chunk of k, into whole lines (five columns of padding): with activation bits from four steps on, without from eight
+SIZES += [(262_150, 5, 91), (262_151, 91, 6), (131_091, 9, 251), (131_092, 251, 14)]
 FEW = 4096
 
 
